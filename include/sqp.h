@@ -180,11 +180,11 @@ int sqp_w4a16_gemm_static(int M, int N, int K, int group, const void *x, const u
 
 /* Search of the smoothing strength for one layer (Sec 2.2: alpha is chosen on a grid to
  * minimise the quantisation loss of Eq. 4; the paper's grid is 0, 0.05, ..., 1).  The
- * per-channel maxima of Eq. 6 do not depend on alpha and are computed once; then for each
+ * per-channel maxima of Eq. 6 and the product x_cal * w do not depend on alpha and are computed
+ * once (the product where w_s has room to hold it meanwhile, in fp32); then for each
  * alphas[i], in order:  s = Eq. 6,  x_hat = x_cal / s and w_s = s * w (Eq. 5),  w_s quantised
  * (Eq. 1),  loss[i] = Eq. 4 on the calibration rows.  *best = index of the smallest loss (the
- * lowest index on ties).  Every step is the kernel of the corresponding entry point above, so
- * loss[i] equals what those calls would give, bit for bit.
+ * lowest index on ties).  loss[i] equals what the entry points above would give, bit for bit.
  *   alphas   HOST array of n_alpha values in [0, 1], 1 <= n_alpha <= 4096
  *   x_cal [T][K] fp16, w [K][N] fp16                                    (in)
  *   amax [2K] fp32, s [K] fp32, x_hat [T][K] fp16, w_s [K][N] fp16, packed / scales / zeros of

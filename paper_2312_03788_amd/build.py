@@ -21,13 +21,14 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hi
 # for them by hand (inline assembly): a register the compiler spilled or copied to scratch memory
 # between issue and wait would silently hold stale data.  The build therefore checks the
 # compiler's output for these kernels and fails otherwise:
-#   decode kernel: no scratch memory and no spilled vector register at all (resource-usage remarks);
+#   decode, slice and loss kernels: no scratch memory and no spilled vector register at all (resource-usage remarks);
 #   tiled kernel:  the compiler spills some store addresses of the epilogue; every scratch access
 #                  must come after the kernel's last barrier, i.e. after the main loop and its
 #                  final wait for all outstanding loads (checked in the generated assembly).
 GUARDED_KERNELS = {"sqp_gemm_decode.hip": ("w4a16_decode_kernel", "none"),
                    "sqp_gemm_slice.hip": ("w4a16_decode_slice_kernel", "none"),
-                   "sqp_gemm_prefill.hip": ("w4a16_prefill_kernel", "after-last-barrier")}
+                   "sqp_gemm_prefill.hip": ("w4a16_prefill_kernel", "after-last-barrier"),
+                   "sqp_loss.hip": ("loss_split_kernel", "none")}
 
 
 def _check_no_spills(src, remarks):

@@ -73,6 +73,12 @@ size_t sqp_gemm_prefill_partial_bytes(int M, int N, int K, int group);
 // then the factor for one alpha.  Arguments are already validated.
 int sqp_channel_absmax(int T, int K, int N, const void *x_cal, const void *w, float *amax, hipStream_t stream);
 int sqp_smooth_factor(int K, float alpha, const float *amax, float *s, hipStream_t stream);
+// The factors of n_alpha alphas (host array) at once: factors [n_alpha][K].
+int sqp_smooth_factors(int K, int n_alpha, const float *alphas, const float *amax, float *factors, hipStream_t stream);
+// x_hat = x / s (Eq. 5) and s * w quantised and packed (Eq. 5, Eq. 1), the smoothed weight kept in
+// registers only: the same bits as sqp_smooth_apply_x, sqp_smooth_apply_w and sqp_quantize_pack give.
+int sqp_smooth_quantize(int T, int N, int K, int group, const void *x, const void *w, const float *s, void *x_hat,
+                        uint32_t *packed, void *scales, uint8_t *zeros, hipStream_t stream);
 
 #ifdef __HIPCC__
 // SiLU(g) = g / (1 + exp(-g)) in fp32 (the hardware exponential: about 1 ulp of fp32).

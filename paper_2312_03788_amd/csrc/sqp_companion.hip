@@ -120,45 +120,58 @@ __global__ void __launch_bounds__(256) smooth_factor_kernel(int K, float alpha, 
     if (j < K) s[j] = smooth_factor_of(amax[j], amax[K + j], alpha);
 }
 
+// The same for a batch of alphas: factors[i][j] (one grid row per alpha).
+struct AlphaBatch {
+    float a[64];
+};
+__global__ void __launch_bounds__(256) smooth_factors_kernel(int K, AlphaBatch alphas, const float *amax, float *factors)
+{
+    const int j = blockIdx.x * 256 + threadIdx.x;
+    if (j < K) factors[(size_t)blockIdx.y * K + j] = smooth_factor_of(amax[j], amax[K + j], alphas.a[blockIdx.y]);
+}
+
 // ------------------------------------------------------------------ Eq. 5
 
-__global__ void __launch_bounds__(256) apply_x_kernel(long total_oct, int KO, const uint4 *x, const float4 *s, uint4 *out)
+__device__ __forceinline__ uint4 smooth_x8(const uint4 &v, const float4 &s0, const float4 &s1)
 {
-    long i = (long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= total_oct) return;
-    int ko = (int)(i % KO);
-    uint4 v = x[i];
-    float4 s0 = s[2 * ko], s1 = s[2 * ko + 1];
     uint4 r;
     r.x = pack_h2(h2f_lo(v.x) / s0.x, h2f_hi(v.x) / s0.y);
     r.y = pack_h2(h2f_lo(v.y) / s0.z, h2f_hi(v.y) / s0.w);
     r.z = pack_h2(h2f_lo(v.z) / s1.x, h2f_hi(v.z) / s1.y);
     r.w = pack_h2(h2f_lo(v.w) / s1.z, h2f_hi(v.w) / s1.w);
-    out[i] = r;
+    return r;
+}
+// The product is rounded to fp32 and then to fp16, as Eq. 5's kernel is defined.  The empty asm keeps
+// the compiler from folding the two into a mixed-precision multiply-add with one rounding, which
+// gave another fp16 value in about one product of ten million where the result feeds arithmetic.
+__device__ __forceinline__ float mul_f32(float a, float b)
+{
+    float p = a * b;
+    asm("" : "+v"(p));
+    return p;
+}
+__device__ __forceinline__ uint32_t smooth_w2(uint32_t v, float sj) { return pack_h2(mul_f32(sj, h2f_lo(v)), mul_f32(sj, h2f_hi(v))); }
+__device__ __forceinline__ uint4 smooth_w8(const uint4 &v, float sj)
+{
+    return make_uint4(smooth_w2(v.x, sj), smooth_w2(v.y, sj), smooth_w2(v.z, sj), smooth_w2(v.w, sj));
+}
+
+__global__ void __launch_bounds__(256) apply_x_kernel(long total_oct, int KO, const uint4 *x, const float4 *s, uint4 *out)
+{
+    long i = (long)blockIdx.x * 256 + threadIdx.x;
+    if (i >= total_oct) return;
+    const int ko = (int)(i % KO);
+    out[i] = smooth_x8(x[i], s[2 * ko], s[2 * ko + 1]);
 }
 
 __global__ void __launch_bounds__(256) apply_w_kernel(long total_oct, int NO, const uint4 *w, const float *s, uint4 *out)
 {
     long i = (long)blockIdx.x * 256 + threadIdx.x;
     if (i >= total_oct) return;
-    float sj = s[i / NO];
-    uint4 v = load_stream(w + i);
-    uint4 r;
-    r.x = pack_h2(sj * h2f_lo(v.x), sj * h2f_hi(v.x));
-    r.y = pack_h2(sj * h2f_lo(v.y), sj * h2f_hi(v.y));
-    r.z = pack_h2(sj * h2f_lo(v.z), sj * h2f_hi(v.z));
-    r.w = pack_h2(sj * h2f_lo(v.w), sj * h2f_hi(v.w));
-    store_stream(out + i, r);
+    store_stream(out + i, smooth_w8(load_stream(w + i), s[i / NO]));
 }
 
 // ------------------------------------------------------------------ Eq. 1
-#ifndef SQP_QP_SPLIT128
-#define SQP_QP_SPLIT128 2   // threads sharing a group of 128 rows
-#endif
-#ifndef SQP_QP_SPLIT64
-#define SQP_QP_SPLIT64 1
-#endif
-
 struct GroupParams {
     float d;     // the fp16-rounded step, as float
     uint16_t d16;
@@ -196,106 +209,73 @@ __device__ __forceinline__ uint32_t code_of(float v, const GroupParams &p)
 // words with such a value are redone with the division (a wave-uniform branch).
 constexpr float NEAR_TIE = 4.0e-6f;
 
-__device__ __forceinline__ uint32_t code_fast(float v, float inv, int z, bool &near_tie)
+// Groups of 32, 64, 128 or 256 rows: a workgroup of 256 threads (512 for groups of 256) quantises
+// 128 (256) rows x 256 columns, i.e. 128 / G groups at once.  Thread (part = tid / 32, oct = tid % 32)
+// holds rows 16 part .. 16 part + 15 of columns 8 oct .. 8 oct + 7 in registers (16 loads of 16
+// bytes; a wave's load covers two rows x 512 contiguous bytes).  Column minima and maxima (exact
+// packed fp16 min / max) meet in LDS; the step, the zero point and the reciprocal step of a column
+// and group are then computed by one thread alone (three IEEE divisions per column and group, not
+// per thread and column) and handed to the others through LDS.  Coding pass, per weight:
+// t = fma(w, 1 / Delta, Z) -- within 1.9e-6 of (correctly rounded w / Delta) + Z wherever the code
+// is not clamped, see NEAR_TIE -- then round, clamp to [0, 15] as a float, and the eight codes of a
+// word are assembled by a fused multiply-add chain (sum c_i 16^i per half word is exact in fp32).
+// A word containing a value within NEAR_TIE of a rounding tie is redone with the division of the
+// definition (wave-uniform branch, about 0.4 % of the words).
+// SMOOTH: the weight is multiplied by the smoothing factor of its row as it is read (one rounding to
+// fp16, as sqp_smooth_apply_w does it), and the workgroups past the last group of rows
+// (blockIdx.y >= qrows) divide the activations, one launch for what the search needs per alpha.
+// Measured, per alpha on 512 x 5120 x 5120: three launches of 5.3 + 15.9 + 18.6 us become one of 25.
+// Groups of 64 on 5120 x 27648: 83 us with one column pair per thread (4-byte loads) -> 65 us
+// (5.7 TB/s of bytes read and written).
+struct SmoothArgs {
+    const float *s;      // [K] smoothing factors
+    const uint4 *x;      // [T][K] activations
+    uint4 *x_hat;
+    long x_octs;         // T * K / 8
+    int KO;              // K / 8
+    int qrows;           // grid rows that quantise
+};
+template <int G, bool SMOOTH>
+__global__ void __launch_bounds__(G == 256 ? 512 : 256)
+quantize_pack_tile_kernel(int N, int K, const uint4 *__restrict__ w, uint32_t *__restrict__ packed,
+                          uint16_t *__restrict__ scales, uint8_t *__restrict__ zeros, SmoothArgs sm)
 {
-    const float t = v * inv;
-    const float r = rintf(t);
-    near_tie |= fabsf(t - r) >= 0.5f - NEAR_TIE;
-    int q = (int)r + z;
-    q = q < 0 ? 0 : (q > 15 ? 15 : q);
-    return (uint32_t)q;
-}
-
-// SPLIT adjacent threads quantise one group of G rows of two adjacent columns, G / SPLIT rows
-// each; the weights stay in registers between the min/max pass (exact packed fp16 min/max,
-// combined across the SPLIT lanes by shuffles) and the coding pass.  Fewer rows per thread
-// mean fewer registers and more waves in flight to overlap the loads of one with the
-// arithmetic of another; with SPLIT = 2 a wave still reads whole 128-byte lines (32 column
-// pairs of one row per half).  grid: (ceil(SPLIT * N/2 / 256), K/G), block 256.
-template <int G, int SPLIT>
-__global__ void __launch_bounds__(256) quantize_pack_reg_kernel(int N, const uint32_t *w, uint2 *packed, uint32_t *scales, uint16_t *zeros)
-{
-    constexpr int R = G / SPLIT;  // rows per thread
-    static_assert(R % 8 == 0, "whole packed words per thread");
-    const int gid = blockIdx.x * 256 + threadIdx.x;
-    const int n2 = gid / SPLIT, part = gid % SPLIT;
-    const int N2 = N >> 1;
-    // N2 * SPLIT is a multiple of SPLIT, so the SPLIT lanes of a group are in or out together
-    if (n2 >= N2) return;
-    const int t = blockIdx.y;
-    const uint32_t *wp = w + ((size_t)t * G + (size_t)part * R) * N2 + n2;
-    uint32_t v[R];
-#pragma unroll
-    for (int i = 0; i < R; i++) v[i] = wp[(size_t)i * N2];
-    h16x2 mn = __builtin_bit_cast(h16x2, v[0]), mx = mn;
-#pragma unroll
-    for (int i = 1; i < R; i++) {
-        const h16x2 c = __builtin_bit_cast(h16x2, v[i]);
-        mn = __builtin_elementwise_min(mn, c);
-        mx = __builtin_elementwise_max(mx, c);
-    }
-#pragma unroll
-    for (int off = 1; off < SPLIT; off <<= 1) {
-        const h16x2 omn = __builtin_bit_cast(h16x2, __shfl_xor(__builtin_bit_cast(int, mn), off, 64));
-        const h16x2 omx = __builtin_bit_cast(h16x2, __shfl_xor(__builtin_bit_cast(int, mx), off, 64));
-        mn = __builtin_elementwise_min(mn, omn);
-        mx = __builtin_elementwise_max(mx, omx);
-    }
-    const GroupParams p0 = group_params((float)mn.x, (float)mx.x), p1 = group_params((float)mn.y, (float)mx.y);
-    if (part == 0) {
-        scales[(size_t)t * N2 + n2] = (uint32_t)p0.d16 | ((uint32_t)p1.d16 << 16);
-        zeros[(size_t)t * N2 + n2] = (uint16_t)(p0.z | (p1.z << 8));
-    }
-    const float inv0 = 1.0f / p0.d, inv1 = 1.0f / p1.d;
-    uint2 *pp = packed + ((size_t)t * (G / 8) + (size_t)part * (R / 8)) * N2 + n2;
-#pragma unroll
-    for (int j = 0; j < R / 8; j++) {
-        uint32_t w0 = 0, w1 = 0;
-        bool near_tie = false;
-#pragma unroll
-        for (int i = 0; i < 8; i++) {
-            w0 |= code_fast(h2f_lo(v[8 * j + i]), inv0, p0.z, near_tie) << (4 * i);
-            w1 |= code_fast(h2f_hi(v[8 * j + i]), inv1, p1.z, near_tie) << (4 * i);
-        }
-        if (__builtin_amdgcn_ballot_w64(near_tie) != 0ull) {
-            w0 = 0;
-            w1 = 0;
-#pragma unroll
-            for (int i = 0; i < 8; i++) {
-                w0 |= code_of(h2f_lo(v[8 * j + i]), p0) << (4 * i);
-                w1 |= code_of(h2f_hi(v[8 * j + i]), p1) << (4 * i);
+    constexpr int THREADS = G == 256 ? 512 : 256;
+    constexpr int PARTS = THREADS / 32;       // 16-row parts of a workgroup
+    constexpr int GP = G / 16;                // parts of a group
+    constexpr int GB = PARTS / GP;            // groups of a workgroup
+    __shared__ uint4 red[PARTS][2][32];       // [part][min | max][oct]
+    __shared__ float par_d[GB][256], par_inv[GB][256], par_z[GB][256];  // per group and column of the workgroup
+    if constexpr (SMOOTH) {
+        if ((int)blockIdx.y >= sm.qrows) {
+            const long stride = (long)(gridDim.y - sm.qrows) * gridDim.x * THREADS;
+            for (long i = ((long)(blockIdx.y - sm.qrows) * gridDim.x + blockIdx.x) * THREADS + threadIdx.x; i < sm.x_octs; i += stride) {
+                const int ko = (int)(i % sm.KO);
+                const float4 *s4 = reinterpret_cast<const float4 *>(sm.s);
+                sm.x_hat[i] = smooth_x8(sm.x[i], s4[2 * ko], s4[2 * ko + 1]);
             }
+            return;
         }
-        pp[(size_t)j * N2] = make_uint2(w0, w1);
     }
-}
-
-// Groups of 128 rows, the configuration of every benchmark layer: a block of 256 threads
-// quantises 128 rows x 256 columns.  Thread (part = tid / 32, oct = tid % 32) holds rows
-// 16 part .. 16 part + 15 of columns 8 oct .. 8 oct + 7 in registers (16 loads of 16 bytes; a
-// wave's load covers two rows x 512 contiguous bytes).  Column minima and maxima (exact packed
-// fp16 min / max) meet in LDS; the step, the zero point and the reciprocal step of column
-// 8 oct + part are then computed by thread (part, oct) alone (three IEEE divisions per column,
-// not per thread and column) and handed to the other parts through LDS.  Coding pass, per
-// weight: t = fma(w, 1 / Delta, Z) -- within 1.9e-6 of (correctly rounded w / Delta) + Z
-// wherever the code is not clamped, see NEAR_TIE -- then round, clamp to [0, 15] as a float,
-// and the eight codes of a word are assembled by a fused multiply-add chain (sum c_i 16^i per
-// half word is exact in fp32).  A word containing a value within NEAR_TIE of a rounding tie is
-// redone with the division of the definition (wave-uniform branch, about 0.4 % of the words).
-__global__ void __launch_bounds__(256) quantize_pack_g128_kernel(int N, const uint4 *__restrict__ w, uint32_t *__restrict__ packed,
-                                                                 uint16_t *__restrict__ scales, uint8_t *__restrict__ zeros)
-{
-    __shared__ uint4 red[8][2][32];     // [part][min | max][oct]: 8 KB
-    __shared__ float par_d[256], par_inv[256], par_z[256];  // per column of the block
     const int oct = threadIdx.x & 31, part = threadIdx.x >> 5;
     const int NO = N >> 3;
     const int o = blockIdx.x * 32 + oct;
-    const bool in = o < NO;
-    const int t = blockIdx.y;
-    const uint4 *wp = w + ((size_t)t * 128 + (size_t)part * 16) * NO + (in ? o : 0);
+    const int row0 = blockIdx.y * (PARTS * 16) + part * 16;   // a group ends inside K or not at all, so a part does as well
+    const bool in = o < NO && row0 < K;
+    const int grp = part / GP;                                 // this thread's group in the workgroup
+    const uint4 *wp = w + (size_t)(row0 < K ? row0 : 0) * NO + (o < NO ? o : 0);
     uint4 v[16];
 #pragma unroll
-    for (int i = 0; i < 16; i++) v[i] = load_stream(wp + (size_t)i * NO);
+    for (int i = 0; i < 16; i++) v[i] = SMOOTH ? wp[(size_t)i * NO] : load_stream(wp + (size_t)i * NO);
+    if constexpr (SMOOTH) {  // (no streaming hint on these loads: the next alpha reads the same weight again)
+        const float *sp = sm.s + (row0 < K ? row0 : 0);
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            v[i] = smooth_w8(v[i], sp[i]);
+            // (kept as packed fp16: the compiler would hold the 128 fp32 values otherwise)
+            asm volatile("" : "+v"(v[i].x), "+v"(v[i].y), "+v"(v[i].z), "+v"(v[i].w));
+        }
+    }
     h16x2 mn[4], mx[4];
     {
         const uint32_t q[4] = {v[0].x, v[0].y, v[0].z, v[0].w};
@@ -319,39 +299,42 @@ __global__ void __launch_bounds__(256) quantize_pack_g128_kernel(int N, const ui
     red[part][0][oct] = as_u4(mn);
     red[part][1][oct] = as_u4(mx);
     __syncthreads();
-    {
-        // thread (part, oct): column 8 oct + part, i.e. half (part & 1) of dword (part >> 1) of the octet
-        const uint32_t *rmn = reinterpret_cast<const uint32_t *>(&red[0][0][oct]) + (part >> 1);
-        const uint32_t *rmx = reinterpret_cast<const uint32_t *>(&red[0][1][oct]) + (part >> 1);
+    // THREADS threads, 256 columns x GB groups: column 8 oct + c of a group, i.e. half (c & 1) of
+    // dword (c >> 1) of the octet
+    for (int u = part; u < 8 * GB; u += PARTS) {
+        const int c = u & 7, g = u >> 3;
+        const uint32_t *rmn = reinterpret_cast<const uint32_t *>(&red[g * GP][0][oct]) + (c >> 1);
+        const uint32_t *rmx = reinterpret_cast<const uint32_t *>(&red[g * GP][1][oct]) + (c >> 1);
         constexpr int PSTRIDE = 2 * 32 * 4;  // dwords between parts
         float lo = 0.f, hi = 0.f;
 #pragma unroll
-        for (int pp = 0; pp < 8; pp++) {
+        for (int pp = 0; pp < GP; pp++) {
             const h16x2 a = __builtin_bit_cast(h16x2, rmn[pp * PSTRIDE]), b = __builtin_bit_cast(h16x2, rmx[pp * PSTRIDE]);
-            const float fa = (part & 1) ? (float)a.y : (float)a.x, fb = (part & 1) ? (float)b.y : (float)b.x;
+            const float fa = (c & 1) ? (float)a.y : (float)a.x, fb = (c & 1) ? (float)b.y : (float)b.x;
             lo = pp == 0 ? fa : fminf(lo, fa);
             hi = pp == 0 ? fb : fmaxf(hi, fb);
         }
         const GroupParams gp = group_params(lo, hi);
-        const int col = oct * 8 + part;
-        par_d[col] = gp.d;
-        par_inv[col] = 1.0f / gp.d;
-        par_z[col] = (float)gp.z;
+        const int col = oct * 8 + c;
+        par_d[g][col] = gp.d;
+        par_inv[g][col] = 1.0f / gp.d;
+        par_z[g][col] = (float)gp.z;
         const int n = blockIdx.x * 256 + col;
-        if (n < N) {
+        const int t = blockIdx.y * GB + g;
+        if (n < N && t * G < K) {
             scales[(size_t)t * N + n] = gp.d16;
             zeros[(size_t)t * N + n] = (uint8_t)gp.z;
         }
     }
     __syncthreads();
     if (!in) return;
-    uint32_t *pp0 = packed + ((size_t)t * 16 + (size_t)part * 2) * N + (size_t)o * 8;
+    uint32_t *pp0 = packed + (size_t)(row0 >> 3) * N + (size_t)o * 8;
 #pragma unroll
     for (int j = 0; j < 2; j++) {
         uint32_t word[8];
 #pragma unroll
         for (int c = 0; c < 8; c++) {
-            const float inv = par_inv[oct * 8 + c], zf = par_z[oct * 8 + c];
+            const float inv = par_inv[grp][oct * 8 + c], zf = par_z[grp][oct * 8 + c];
             float code[8], worst = 0.f;
 #pragma unroll
             for (int i = 0; i < 8; i++) {
@@ -368,7 +351,7 @@ __global__ void __launch_bounds__(256) quantize_pack_g128_kernel(int N, const ui
             word[c] = (uint32_t)lo4 | ((uint32_t)hi4 << 16);
             if (__builtin_amdgcn_ballot_w64(worst >= 0.5f - NEAR_TIE) != 0ull) {
                 GroupParams gp;
-                gp.d = par_d[oct * 8 + c];
+                gp.d = par_d[grp][oct * 8 + c];
                 gp.z = (int)zf;
                 gp.d16 = 0;
                 uint32_t wd = 0;
@@ -387,18 +370,25 @@ __global__ void __launch_bounds__(256) quantize_pack_g128_kernel(int N, const ui
     }
 }
 
-// Any group size (multiple of 8): the group is read twice.
-__global__ void __launch_bounds__(256) quantize_pack_any_kernel(int N, int G, const uint32_t *w, uint2 *packed, uint32_t *scales, uint16_t *zeros)
+// Any other group size (multiple of 8): the group is read twice.  SMOOTH: rows times s as above.
+template <bool SMOOTH>
+__global__ void __launch_bounds__(256) quantize_pack_any_kernel(int N, int G, const uint32_t *w, uint2 *packed, uint32_t *scales, uint16_t *zeros,
+                                                                const float *s)
 {
     const int n2 = blockIdx.x * 256 + threadIdx.x;
     const int N2 = N >> 1;
     if (n2 >= N2) return;
     const int t = blockIdx.y;
     const uint32_t *wp = w + (size_t)t * G * N2 + n2;
-    uint32_t v0 = wp[0];
+    auto load = [&](int i) {
+        const uint32_t v = wp[(size_t)i * N2];
+        if constexpr (!SMOOTH) return v;
+        return smooth_w2(v, s[(size_t)t * G + i]);
+    };
+    uint32_t v0 = load(0);
     float mn0 = h2f_lo(v0), mx0 = mn0, mn1 = h2f_hi(v0), mx1 = mn1;
     for (int i = 1; i < G; i++) {
-        uint32_t v = wp[(size_t)i * N2];
+        uint32_t v = load(i);
         float a = h2f_lo(v), b = h2f_hi(v);
         mn0 = fminf(mn0, a);
         mx0 = fmaxf(mx0, a);
@@ -413,7 +403,7 @@ __global__ void __launch_bounds__(256) quantize_pack_any_kernel(int N, int G, co
         uint32_t w0 = 0, w1 = 0;
 #pragma unroll
         for (int i = 0; i < 8; i++) {
-            uint32_t v = wp[(size_t)(8 * j + i) * N2];
+            uint32_t v = load(8 * j + i);
             w0 |= code_of(h2f_lo(v), p0) << (4 * i);
             w1 |= code_of(h2f_hi(v), p1) << (4 * i);
         }
@@ -479,6 +469,17 @@ int sqp_smooth_factor(int K, float alpha, const float *amax, float *s, hipStream
     return sqp_launch_status();
 }
 
+int sqp_smooth_factors(int K, int n_alpha, const float *alphas, const float *amax, float *factors, hipStream_t st)
+{
+    for (int i0 = 0; i0 < n_alpha; i0 += 64) {
+        AlphaBatch b;
+        const int n = n_alpha - i0 < 64 ? n_alpha - i0 : 64;
+        for (int i = 0; i < 64; i++) b.a[i] = alphas[i0 + (i < n ? i : 0)];
+        smooth_factors_kernel<<<dim3((K + 255) / 256, n), 256, 0, st>>>(K, b, amax, factors + (size_t)i0 * K);
+    }
+    return sqp_launch_status();
+}
+
 extern "C" int sqp_smooth_apply_x(int M, int K, const void *x, const float *s, void *x_out, void *stream)
 {
     if (!x || !s || !x_out) return SQP_ERR_NULL;
@@ -539,6 +540,41 @@ extern "C" int sqp_transpose_nk(int N, int K, const void *w_nk, void *w_kn, void
     return sqp_launch_status();
 }
 
+template <int G, bool SMOOTH>
+static void launch_quantize_tile(int N, int K, const void *w, uint32_t *packed, void *scales, uint8_t *zeros, SmoothArgs sm, hipStream_t st)
+{
+    constexpr int THREADS = G == 256 ? 512 : 256, ROWS = THREADS / 2;
+    const int gx = (N + 255) / 256, rows = (K + ROWS - 1) / ROWS;
+    int extra = 0;
+    if (SMOOTH) {
+        // activations: about eight octets per thread
+        sm.qrows = rows;
+        extra = (int)((sm.x_octs + 8L * THREADS * gx - 1) / (8L * THREADS * gx));
+        if (extra > 65535 - rows) extra = 65535 - rows;
+    }
+    quantize_pack_tile_kernel<G, SMOOTH><<<dim3(gx, rows + extra), THREADS, 0, st>>>(N, K, (const uint4 *)w, packed, (uint16_t *)scales, zeros, sm);
+}
+
+// Groups of 32, 64, 128 and 256 rows read the weight once, others twice.
+template <bool SMOOTH>
+static int launch_quantize(int N, int K, int group, const void *w, uint32_t *packed, void *scales, uint8_t *zeros, const SmoothArgs &sm,
+                           hipStream_t st)
+{
+    switch (group) {
+        case 32: launch_quantize_tile<32, SMOOTH>(N, K, w, packed, scales, zeros, sm, st); break;
+        case 64: launch_quantize_tile<64, SMOOTH>(N, K, w, packed, scales, zeros, sm, st); break;
+        case 128: launch_quantize_tile<128, SMOOTH>(N, K, w, packed, scales, zeros, sm, st); break;
+        case 256: launch_quantize_tile<256, SMOOTH>(N, K, w, packed, scales, zeros, sm, st); break;
+        default:
+            quantize_pack_any_kernel<SMOOTH><<<dim3((N / 2 + 255) / 256, K / group), 256, 0, st>>>(
+                N, group, (const uint32_t *)w, (uint2 *)packed, (uint32_t *)scales, (uint16_t *)zeros, sm.s);
+            if (SMOOTH)
+                apply_x_kernel<<<(unsigned)((sm.x_octs + 255) / 256), 256, 0, st>>>(sm.x_octs, sm.KO, sm.x, (const float4 *)sm.s, sm.x_hat);
+            break;
+    }
+    return sqp_launch_status();
+}
+
 extern "C" int sqp_quantize_pack(int N, int K, int group, const void *w, uint32_t *packed, void *scales, uint8_t *zeros, void *stream)
 {
     if (!w || !packed || !scales || !zeros) return SQP_ERR_NULL;
@@ -546,22 +582,22 @@ extern "C" int sqp_quantize_pack(int N, int K, int group, const void *w, uint32_
     if (rc) return rc;
     if (K / group > 65535) return SQP_ERR_SHAPE;
     if (sqp_misaligned(w) || sqp_misaligned(packed) || sqp_misaligned(scales) || sqp_misaligned(zeros)) return SQP_ERR_ALIGN;
-    hipStream_t st = (hipStream_t)stream;
-    dim3 grid((N / 2 + 255) / 256, K / group);
-    dim3 grid2((N + 255) / 256, K / group);  // two threads per column pair
-    const uint32_t *wp = (const uint32_t *)w;
-    uint2 *pp = (uint2 *)packed;
-    uint32_t *sp = (uint32_t *)scales;
-    uint16_t *zp = (uint16_t *)zeros;
-    switch (group) {
-        case 32: quantize_pack_reg_kernel<32, 1><<<grid, 256, 0, st>>>(N, wp, pp, sp, zp); break;
-        case 64: quantize_pack_reg_kernel<64, SQP_QP_SPLIT64><<<SQP_QP_SPLIT64 == 2 ? grid2 : grid, 256, 0, st>>>(N, wp, pp, sp, zp); break;
-        case 128:
-            quantize_pack_g128_kernel<<<dim3((N + 255) / 256, K / 128), 256, 0, st>>>(N, (const uint4 *)w, packed, (uint16_t *)scales, zeros);
-            break;
-        default: quantize_pack_any_kernel<<<grid, 256, 0, st>>>(N, group, wp, pp, sp, zp); break;
-    }
-    return sqp_launch_status();
+    return launch_quantize<false>(N, K, group, w, packed, scales, zeros, SmoothArgs(), (hipStream_t)stream);
+}
+
+// s * w quantised and x / s, as sqp_smooth_apply_w, sqp_quantize_pack and sqp_smooth_apply_x give
+// them, without the smoothed weight in between.  Arguments are already validated.
+int sqp_smooth_quantize(int T, int N, int K, int group, const void *x, const void *w, const float *s, void *x_hat,
+                        uint32_t *packed, void *scales, uint8_t *zeros, hipStream_t st)
+{
+    SmoothArgs sm;
+    sm.s = s;
+    sm.x = (const uint4 *)x;
+    sm.x_hat = (uint4 *)x_hat;
+    sm.x_octs = (long)T * (K / 8);
+    sm.KO = K / 8;
+    sm.qrows = 0;
+    return launch_quantize<true>(N, K, group, w, packed, scales, zeros, sm, st);
 }
 
 extern "C" int sqp_dequantize(int N, int K, int group, const uint32_t *packed, const void *scales, const uint8_t *zeros, void *w_hat, void *stream)

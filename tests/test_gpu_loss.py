@@ -35,7 +35,9 @@ def _oracle_chain(orc, xcal, w, alpha, group):
 @pytest.mark.parametrize("M,K,N,group,alpha", [
     (4, 1024, 1024, 128, 0.5), (37, 264, 72, 24, 0.25), (130, 512, 136, 64, 0.85), (129, 40, 8, 8, 0.5),
     (512, 2048, 520, 128, 0.5), (300, 1024, 1000, 256, 0.0),
-    (256, 1024, 384, 128, 0.5), (128, 192, 128, 32, 0.3)])  # the last two: whole tiles only (the variant without bounds checks)
+    (256, 1024, 384, 128, 0.5), (128, 192, 128, 32, 0.3),  # whole tiles only (the variant without bounds checks)
+    # one product after the other: one row, one column octet, one stage; groups of 1.5 stages; two groups per half stage
+    (1, 128, 8, 64, 0.5), (257, 384, 200, 192, 0.5), (129, 256, 72, 32, 0.35)])
 def test_quant_loss_parity(orc, sqp, M, K, N, group, alpha):
     print("case loss", M, K, N, group, alpha, flush=True)
     _, xcal, w = wl.layer_inputs(1, K, N)
@@ -117,3 +119,39 @@ def test_alpha_search_equals_single_calls(orc, sqp):
     # `best` missing (the last pointer before the stream): rejected before anything is enqueued.
     # Every call above and this one must fail validation: the pointers are not real.
     assert L.sqp_alpha_search(T, N, K, g, 2, ok_alpha, *([good] * 11), None, None) == -1
+
+
+@pytest.mark.parametrize("T,K,N,group", [
+    (40, 640, 128, 128),    # the product with the unsmoothed weight kept in w_s; one tile, five stages
+    (129, 1408, 200, 64),   # two tiles of rows, the second with one row; ragged columns
+    (64, 1024, 256, 256),   # groups of two stages
+    (1, 768, 136, 384),     # a group size whose quantise kernel reads twice
+    (200, 1152, 328, 32),   # two groups per half stage
+    (130, 384, 136, 32),    # K too short for w_s to hold the product: single calls in turn
+    (70, 192, 72, 64)])     # K not a multiple of 128: the interleaved loss kernel
+def test_alpha_search_routes_equal_single_calls(sqp, T, K, N, group):
+    """Every route of the search gives the losses of the single calls bit for bit, and leaves the
+    last alpha's factors, activations, weight and codes in its work buffers."""
+    import ctypes
+    print("case search", T, K, N, group, flush=True)
+    _, _, w = wl.layer_inputs(1, K, N)
+    dx, dw = dev(wl.activation(T, K, seed=3000)), dev(w)
+    alphas = [0.5, 0.0, 0.35]
+    L, n = sqp.lib(), len(alphas)
+    new = lambda shape, dt: torch.empty(shape, dtype=dt, device="cuda")
+    amax, s, xh, ws = new(2 * K, torch.float32), new(K, torch.float32), torch.empty_like(dx), torch.empty_like(dw)
+    p, sc, z = new((K // 8, N), torch.int32), new((K // group, N), torch.float16), new((K // group, N), torch.uint8)
+    scratch, loss, best = new(L.sqp_quant_loss_scratch_doubles(T, N), torch.float64), new(n, torch.float64), new(1, torch.int32)
+    ptr = lambda t: ctypes.c_void_p(t.data_ptr())
+    assert L.sqp_alpha_search(T, N, K, group, n, (ctypes.c_float * n)(*alphas),
+                              *[ptr(t) for t in (dx, dw, amax, s, xh, ws, p, sc, z, scratch, loss, best)],
+                              ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    singles = []
+    for a in alphas:
+        s1 = sqp.smooth_scales(dx, dw, a)
+        ws1, xh1 = sqp.smooth_apply_w(dw, s1), sqp.smooth_apply_x(dx, s1)
+        q1 = sqp.quantize_pack(ws1, group)
+        singles.append(float(host(sqp.quant_loss(dx, dw, xh1, *q1, group))[0]))
+    assert list(host(loss)) == singles and int(host(best)[0]) == int(np.argmin(singles))
+    for got, want in ((s, s1), (xh, xh1), (ws, ws1), (p, q1[0]), (sc, q1[1]), (z, q1[2])):
+        assert torch.equal(got.view(torch.uint8), want.view(torch.uint8))
