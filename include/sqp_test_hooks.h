@@ -18,16 +18,22 @@ extern "C" {
 void sqp_debug_set_decode_max_m(int m);            /* rows up to which that path is used (default 64) */
 void sqp_debug_set_decode_split(int split);        /* force the number of K parts; 0 = automatic */
 void sqp_debug_set_decode_plan(int nw, int split); /* force strips per workgroup and K parts; (0, 0) = automatic */
-void sqp_debug_set_decode_kw(int kw);              /* 1 = never two waves per strip; 0 = automatic */
-void sqp_debug_set_decode_kp(int kp);              /* two chunks per iteration (twice the waves): 0 = automatic, 1 = never, 2 = wherever built */
+void sqp_debug_set_decode_kw(int kw);              /* waves per strip: 0 = automatic, 1 = never two, 2 = two wherever built */
+void sqp_debug_set_decode_kp(int kp);              /* two chunks per iteration (twice the waves): 0 = automatic, 1 = never,
+                                                      2 = where the rules would with enough chunks, 3 = wherever built */
 void sqp_debug_set_decode_slice(int mode);         /* column-slice kernel (M <= 16, groups of 128): 0 = automatic, -1 = never,
                                                       1 = always with 32-column slices, 2 = always with 64-column slices */
 /* Which kernel a call would take: -1 = the strip kernel below, 0 / 1 = the column-slice kernel
  * with 32- / 64-column slices.  Host arithmetic only. */
 int sqp_debug_decode_slice_choice(int M, int N, int K, int group);
-/* The plan the heuristic picks for a shape: strips per workgroup, K parts, k-steps per chunk
- * (0 = the generic one-thread-per-element kernel).  Host arithmetic only. */
+/* The plan by strips for a shape: strips per workgroup, K parts, k-steps of one group up to 128 k
+ * (0 = the generic one-thread-per-element kernel).  Calls with up to 16 rows and groups that are
+ * multiples of 128 run it.  Host arithmetic only. */
 void sqp_debug_decode_plan(int M, int N, int K, int group, int *nw, int *split, int *kspg);
+
+/* What a call of the strip kernel launches: strips per workgroup, K parts, waves per strip and chunks
+ * per iteration (0: by rules on the number of workgroups).  Host arithmetic only. */
+void sqp_debug_decode_launch(int M, int N, int K, int group, int *nw, int *split, int *kw, int *kp);
 
 /* Tiled matrix-core path (M > 64). */
 void sqp_debug_set_prefill_tiles(int mode);        /* 0 = automatic, 1 = full tiles only, 2 = half-width tiles only */

@@ -11,7 +11,8 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsqp.so")
 
-SOURCES = ["sqp_api.hip", "sqp_companion.hip", "sqp_gemm_decode.hip", "sqp_gemm_prefill.hip", "sqp_gemm_slice.hip", "sqp_loss.hip", "sqp_mlp.hip", "sqp_static.hip"]
+SOURCES = ["sqp_api.hip", "sqp_companion.hip", "sqp_gemm_decode.hip", "sqp_gemm_prefill.hip", "sqp_gemm_slice.hip", "sqp_loss.hip", "sqp_mlp.hip", "sqp_static.hip",
+           "sqp_strip_g128_rows32.hip", "sqp_strip_g128_rows64.hip", "sqp_strip_g64.hip", "sqp_strip_g32.hip", "sqp_strip_one_group.hip"]
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-I" + os.path.join(ROOT, "include"),
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
@@ -25,7 +26,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hi
 #   tiled kernel:  the compiler spills some store addresses of the epilogue; every scratch access
 #                  must come after the kernel's last barrier, i.e. after the main loop and its
 #                  final wait for all outstanding loads (checked in the generated assembly).
-GUARDED_KERNELS = {"sqp_gemm_decode.hip": ("w4a16_decode_kernel", "none"),
+GUARDED_KERNELS = {**{s: ("w4a16_decode_kernel", "none") for s in SOURCES if s.startswith("sqp_strip_")},
                    "sqp_gemm_slice.hip": ("w4a16_decode_slice_kernel", "none"),
                    "sqp_gemm_prefill.hip": ("w4a16_prefill_kernel", "after-last-barrier"),
                    "sqp_loss.hip": ("loss_split_kernel", "none")}
@@ -99,7 +100,7 @@ def _compile(src):
 
 def build(verbose=False):
     os.makedirs(OBJ, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=4) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(_compile, SOURCES))
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     subprocess.run(cmd, check=True)

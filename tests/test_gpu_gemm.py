@@ -285,6 +285,33 @@ def test_decode_two_chunks_per_iteration(orc, sqp, M, K, N, nw, split):
         L.sqp_debug_set_decode_slice(0)
 
 
+@pytest.mark.parametrize("nw,kw,kp", [(2, 2, 1), (2, 2, 3), (4, 1, 3)])
+@pytest.mark.parametrize("M,K,N,group,split", [
+    (17, 128, 136, 128, 1), (33, 640, 264, 128, 2), (48, 1152, 520, 384, 3), (49, 1280, 200, 256, 1), (64, 128 * 13, 328, 128, 5),
+    (1, 256, 72, 64, 1), (16, 1152, 264, 64, 4), (20, 640, 136, 64, 1), (47, 896, 392, 64, 3), (64, 384, 8, 64, 1),
+    (3, 128, 264, 32, 1), (32, 1408, 136, 32, 2), (40, 640, 520, 32, 1), (61, 768, 264, 32, 6)])
+def test_decode_wide_variants(orc, sqp, M, K, N, group, split, nw, kw, kp):
+    """The eight-wave and two-wave-per-strip variants of every row-tile count, with one and several
+    groups per chunk and several chunks per group: row tiles finished by different waves, chunk
+    ranges shorter than the pipeline, odd ranges, ragged columns; repeated runs are bit-identical."""
+    print("case wide", M, K, N, group, split, nw, kw, kp, flush=True)
+    xs, p, sc, z = _layer(orc, M, K, N, group)
+    L = sqp.lib()
+    L.sqp_debug_set_decode_plan(nw, split)
+    L.sqp_debug_set_decode_kw(kw)
+    L.sqp_debug_set_decode_kp(kp)
+    L.sqp_debug_set_decode_slice(-1)
+    try:
+        y0 = _check(orc, sqp, xs, p, sc, z, group)
+        y1 = _check(orc, sqp, xs, p, sc, z, group)
+        assert np.array_equal(y0.view(np.uint16), y1.view(np.uint16))
+    finally:
+        L.sqp_debug_set_decode_plan(0, 0)
+        L.sqp_debug_set_decode_kw(0)
+        L.sqp_debug_set_decode_kp(0)
+        L.sqp_debug_set_decode_slice(0)
+
+
 @pytest.mark.parametrize("mode", [1, 2])
 @pytest.mark.parametrize("M,K,N", [
     (1, 128, 8), (3, 256, 40), (5, 1152, 72), (16, 384, 520), (7, 1024, 1032), (16, 1536, 2056), (9, 128 * 7, 200),

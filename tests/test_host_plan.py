@@ -125,6 +125,36 @@ def test_decode_plan_small_model_values(L):
     assert _decode_plan(L, 16, 22016, 4096, 128)[:2] == (4, 2)     # 86 tiles: 172 workgroups, not 258
 
 
+def test_wide_plan_invariants(L):
+    """17 to 64 rows, and groups of 32 and 64: at most one eight-wave or two four-wave workgroups per
+    compute unit while the column tiles allow it, chunks for every workgroup, partial sums below
+    the static array's size."""
+    def launch(M, N, K, group):
+        v = [ctypes.c_int() for _ in range(4)]
+        L.sqp_debug_decode_launch(M, N, K, group, *[ctypes.byref(x) for x in v])
+        return tuple(x.value for x in v)
+    L.sqp_w4a16_gemm_workspace_bytes.restype = ctypes.c_size_t
+    shapes = [s for m in ("7b", "13b", "34b") for s in wl.MODEL_SHAPES[m]] + [(128, 8), (1024, 264), (65536, 64), (5120, 18432), (768, 262144)]
+    for (K, N) in shapes:
+        for group in (32, 64, 128, 256):
+            for M in (1, 16, 17, 32, 33, 64):
+                if M <= 16 and group >= 128:
+                    continue
+                nw, split, kw, kp = launch(M, N, K, group)
+                tiles, chunks = -(-N // (64 * nw)), K // 128
+                assert nw in (2, 4) and kw in (1, 2) and kp in (1, 2) and not (nw == 4 and kw == 2)
+                assert 1 <= split <= max(1, chunks // 2)
+                if -(-N // 128) <= 256:
+                    assert split == 1 or tiles * split <= (256 if kp == 2 else 512)
+                assert kp == 1 or chunks >= 8 * split
+                assert L.sqp_w4a16_gemm_workspace_bytes(M, N, K, group) <= (512 << 10) + (48 << 20)
+    assert launch(48, 15360, 5120, 128) == (2, 2, 2, 2)      # 120 tiles x 2 parts
+    assert launch(20, 4096, 4096, 64) == (2, 8, 2, 1)        # four chunks each: one per iteration
+    assert launch(48, 18432, 5120, 128) == (2, 3, 2, 1)      # 144 tiles: three parts, two workgroups per unit
+    assert launch(48, 44032, 8192, 128) == (2, 2, 2, 1)
+    assert launch(20, 8192, 22016, 128) == (4, 8, 1, 2)
+
+
 @pytest.mark.parametrize("shape", [1, 2])
 def test_tile_plan_invariants(L, shape):
     """Both full-tile shapes (1: 128 x 512, 2: 256 x 256)."""
