@@ -98,6 +98,56 @@ __global__ void __launch_bounds__(256) rmsnorm_reg_kernel(int H8, float inv_h, f
     }
 }
 
+// Few rows (a decode step): the launch is a chain of latencies, so the weight is fetched together with
+// the row instead of behind the reduction, and a row is spread over up to 16 waves (one or two
+// pieces per thread).
+template <int W, int NI>
+__global__ void __launch_bounds__(64 * W) rmsnorm_few_rows_kernel(int H8, float inv_h, float eps, const uint4 *__restrict__ x,
+                                                                  const uint4 *__restrict__ gamma, uint4 *__restrict__ y)
+{
+    __shared__ float red[W];
+    const uint4 *xr = x + (size_t)blockIdx.x * H8;
+    uint4 v[NI], g[NI];
+#pragma unroll
+    for (int j = 0; j < NI; j++) {
+        const int i = threadIdx.x + 64 * W * j;
+        v[j] = i < H8 ? xr[i] : make_uint4(0, 0, 0, 0);
+        g[j] = i < H8 ? gamma[i] : make_uint4(0, 0, 0, 0);
+    }
+    float ss = 0.f;
+#pragma unroll
+    for (int j = 0; j < NI; j++) {
+        const float a0 = lo_of(v[j].x), a1 = hi_of(v[j].x), a2 = lo_of(v[j].y), a3 = hi_of(v[j].y);
+        const float a4 = lo_of(v[j].z), a5 = hi_of(v[j].z), a6 = lo_of(v[j].w), a7 = hi_of(v[j].w);
+        ss += ((a0 * a0 + a1 * a1) + (a2 * a2 + a3 * a3)) + ((a4 * a4 + a5 * a5) + (a6 * a6 + a7 * a7));
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+    __syncthreads();
+    float part[W];
+#pragma unroll
+    for (int i = 0; i < W; i++) part[i] = red[i];
+#pragma unroll
+    for (int half = W / 2; half >= 1; half >>= 1)
+#pragma unroll
+        for (int i = 0; i < half; i++) part[i] = part[2 * i] + part[2 * i + 1];
+    const float r = 1.0f / sqrtf(part[0] * inv_h + eps);
+    uint4 *yr = y + (size_t)blockIdx.x * H8;
+#pragma unroll
+    for (int j = 0; j < NI; j++) {
+        const int i = threadIdx.x + 64 * W * j;
+        if (i < H8) {
+            uint4 o;
+            o.x = pack2(lo_of(v[j].x) * r * lo_of(g[j].x), hi_of(v[j].x) * r * hi_of(g[j].x));
+            o.y = pack2(lo_of(v[j].y) * r * lo_of(g[j].y), hi_of(v[j].y) * r * hi_of(g[j].y));
+            o.z = pack2(lo_of(v[j].z) * r * lo_of(g[j].z), hi_of(v[j].z) * r * hi_of(g[j].z));
+            o.w = pack2(lo_of(v[j].w) * r * lo_of(g[j].w), hi_of(v[j].w) * r * hi_of(g[j].w));
+            yr[i] = o;
+        }
+    }
+}
+
 __global__ void __launch_bounds__(256) scale_columns_kernel(long total_oct, int NO, const uint4 *__restrict__ w,
                                                             const float4 *__restrict__ s, uint4 *__restrict__ out)
 {
@@ -134,6 +184,12 @@ __global__ void __launch_bounds__(256) interleave_kernel(long total_oct, int IO,
 
 }  // namespace
 
+// Up to this many rows the kernel with the row spread over more waves is the faster one (us, 256
+// threads per row -> up to 1024, rows cold): 16 x 4096 2.5 -> 2.1, 16 x 8192 3.25 -> 2.5, 48 x 8192 4.4 -> 3.0,
+// 512 x 5120 5.3 -> 4.5, 512 x 8192 7.1 -> 5.7, but 1024 x 5120 6.9 -> 7.6, 2048 x 8192 14.6 -> 16.0 (fewer rows
+// in flight per compute unit).
+constexpr int RMSNORM_FEW_ROWS = 512;
+
 extern "C" int sqp_rmsnorm(int M, int H, const void *x, const void *gamma, float eps, void *y, void *stream)
 {
     if (!x || !gamma || !y) return SQP_ERR_NULL;
@@ -145,6 +201,13 @@ extern "C" int sqp_rmsnorm(int M, int H, const void *x, const void *gamma, float
     hipStream_t st = (hipStream_t)stream;
     const uint4 *xp = (const uint4 *)x, *gp = (const uint4 *)gamma;
     uint4 *yp = (uint4 *)y;
+    if (M <= RMSNORM_FEW_ROWS && H8 <= 2048) {
+        if (H8 <= 256) rmsnorm_few_rows_kernel<4, 1><<<(unsigned)M, 256, 0, st>>>(H8, inv_h, eps, xp, gp, yp);
+        else if (H8 <= 512) rmsnorm_few_rows_kernel<8, 1><<<(unsigned)M, 512, 0, st>>>(H8, inv_h, eps, xp, gp, yp);
+        else if (H8 <= 1024) rmsnorm_few_rows_kernel<16, 1><<<(unsigned)M, 1024, 0, st>>>(H8, inv_h, eps, xp, gp, yp);
+        else rmsnorm_few_rows_kernel<16, 2><<<(unsigned)M, 1024, 0, st>>>(H8, inv_h, eps, xp, gp, yp);
+        return sqp_launch_status();
+    }
     if (H8 <= 256) rmsnorm_reg_kernel<1><<<(unsigned)M, 256, 0, st>>>(H8, inv_h, eps, xp, gp, yp);
     else if (H8 <= 512) rmsnorm_reg_kernel<2><<<(unsigned)M, 256, 0, st>>>(H8, inv_h, eps, xp, gp, yp);
     else if (H8 <= 1024) rmsnorm_reg_kernel<4><<<(unsigned)M, 256, 0, st>>>(H8, inv_h, eps, xp, gp, yp);

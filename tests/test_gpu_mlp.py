@@ -18,7 +18,9 @@ def sqp():
     return m
 
 
-@pytest.mark.parametrize("M,H", [(5, 64), (33, 4096), (16, 8192), (3, 264), (4, 22016), (2, 40000), (7, 2056)])
+@pytest.mark.parametrize("M,H", [(5, 64), (33, 4096), (16, 8192), (3, 264), (4, 22016), (2, 40000), (7, 2056),
+                                 # one piece per thread up to 8192 halves, two up to 16384; rows past the few
+                                 (1, 4104), (2, 8200), (3, 16384), (2, 16392), (512, 2048), (513, 2048)])
 def test_rmsnorm(orc, sqp, M, H):
     """fp32 arithmetic on the device against the fp64 definition: the sum of H squares carries
     a relative error of about sqrt(H) 2^-24, the three fp32 operations another 2^-23, all far
