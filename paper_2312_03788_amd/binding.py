@@ -5,11 +5,13 @@ the GPU, be contiguous and have the dtype the C ABI expects; outputs are allocat
 with torch (device memory plumbing only) unless passed in.
 """
 import ctypes
+import importlib.util
 import os
 
 import torch  # also makes sure the process-wide HIP runtime is the one torch uses
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
+_TORCH_PART = os.path.join(_HERE, "_sqp_torch.so")  # native marshalling of the serving calls
 _LIB_PATH = os.environ.get("SQP_LIBRARY", os.path.join(_HERE, "libsqp.so"))  # override: another build
 
 EXPORTS = ["sqp_status_string", "sqp_smooth_scales", "sqp_smooth_apply_x", "sqp_smooth_apply_w",
@@ -23,13 +25,14 @@ class SqpError(RuntimeError):
 
 
 _lib = None
+_fast = None  # the native module, bound to _lib's entry points
 
 
 def lib():
     """Load libsqp.so (built beforehand by paper_2312_03788_amd/build.py)."""
-    global _lib
+    global _lib, _fast
     if _lib is None:
-        if not os.path.exists(_LIB_PATH):
+        if not os.path.exists(_LIB_PATH) or not os.path.exists(_TORCH_PART):
             raise SqpError("libsqp.so is not built: run `python -m paper_2312_03788_amd.build`")
         L = ctypes.CDLL(_LIB_PATH)
         L.sqp_status_string.restype = ctypes.c_char_p
@@ -56,6 +59,13 @@ def lib():
         for name in EXPORTS[1:]:
             getattr(L, name).restype = ctypes.c_int
         L.sqp_quant_loss_scratch_doubles.restype = ctypes.c_long
+        spec = importlib.util.spec_from_file_location("_sqp_torch", _TORCH_PART)
+        fast = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(fast)
+        fast.bind(*[ctypes.cast(f, ctypes.c_void_p).value for f in (
+            L.sqp_w4a16_gemm, L.sqp_w4a16_gemm_silu_mul, L.sqp_w4a16_gemm_static, L.sqp_w4a16_gemm_workspace_bytes,
+            L.sqp_rmsnorm, L.sqp_smooth_apply_x)])
+        _fast = fast
         _lib = L
     return _lib
 
@@ -79,7 +89,24 @@ def _stream():
     return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # absent in builds without a GPU runtime
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
+def _here():
+    """(current device, its current stream): what the native calls run on.  The general path comes
+    first in a process, so that torch has initialised the GPU by then."""
+    dev = _current_device()
+    return dev, _raw_stream(dev)
+
+
+def _native(t):
+    """Whether the native marshalling may be tried (it declines anything but plain GPU tensors)."""
+    return _fast is not None and isinstance(t, torch.Tensor) and t.is_cuda
+
+
 _workspaces = {}  # device index -> torch buffer handed to the library (kept alive here)
+_held = {}        # device index -> size of the one in use
 
 
 def set_workspace(nbytes, device=None):
@@ -92,10 +119,12 @@ def set_workspace(nbytes, device=None):
         if nbytes <= 0:
             _check(lib().sqp_set_workspace(None, 0, _stream()), "sqp_set_workspace")
             _workspaces.setdefault(dev.index, []).append(None)
+            _held[dev.index] = 0
             return None
         buf = torch.empty(int(nbytes), dtype=torch.uint8, device=dev)
         _check(lib().sqp_set_workspace(ctypes.c_void_p(buf.data_ptr()), int(nbytes), _stream()), "sqp_set_workspace")
         _workspaces.setdefault(dev.index, []).append(buf)
+        _held[dev.index] = int(nbytes)
     return buf
 
 
@@ -133,6 +162,10 @@ def smooth_scales(x_cal, w, alpha, out=None):
 
 def smooth_apply_x(x, s, out=None):
     """Eq. 5, activation side: x / s per input channel."""
+    if _native(x):
+        o = _fast.apply_x(x, s, out, *_here())
+        if o is not None:
+            return o
     M, K = x.shape
     o = out if out is not None else torch.empty_like(x)
     _check(lib().sqp_smooth_apply_x(M, K, _dev(x, torch.float16, "x"), _dev(s, torch.float32, "s"),
@@ -179,6 +212,11 @@ def dequantize(packed, scales, zeros, group=128, out=None):
 
 def w4a16_gemm(x, packed, scales, zeros, group=128, out=None):
     """Eq. 3: y [M,N] fp16 = x [M,K] fp16 times the group-wise 4-bit weight."""
+    if _native(x):
+        dev, stream = _here()
+        y = _fast.gemm(0, x, packed, scales, zeros, group, out, dev, stream, _held.get(dev, 0))
+        if y is not None:
+            return y
     M, K = x.shape
     N = packed.shape[1]
     if packed.shape[0] * 8 != K:
@@ -195,6 +233,10 @@ def w4a16_gemm_static(x, packed, scales, zeros, group=128, out=None):
     """Eq. 3 through the entry point that allocates nothing and needs no workspace (partial
     sums in the library's static device array); `out` should be passed by callers that must
     not allocate."""
+    if _native(x):
+        y = _fast.gemm(2, x, packed, scales, zeros, group, out, *_here(), 0)
+        if y is not None:
+            return y
     M, K = x.shape
     N = packed.shape[1]
     if packed.shape[0] * 8 != K:
@@ -208,6 +250,11 @@ def w4a16_gemm_static(x, packed, scales, zeros, group=128, out=None):
 
 def w4a16_gemm_silu_mul(x, packed, scales, zeros, group=128, out=None):
     """Merged, interleaved gate/up projection with SiLU(gate) * up fused: y [M, N/2] fp16."""
+    if _native(x):
+        dev, stream = _here()
+        y = _fast.gemm(1, x, packed, scales, zeros, group, out, dev, stream, _held.get(dev, 0))
+        if y is not None:
+            return y
     M, K = x.shape
     N = packed.shape[1]
     if packed.shape[0] * 8 != K:
@@ -222,6 +269,10 @@ def w4a16_gemm_silu_mul(x, packed, scales, zeros, group=128, out=None):
 
 def rmsnorm(x, gamma, eps, out=None):
     """LlamaRMSNorm with an fp16 weight (possibly already divided by a smoothing factor)."""
+    if _native(x):
+        y = _fast.rmsnorm(x, gamma, eps, out, *_here())
+        if y is not None:
+            return y
     M, H = x.shape
     y = out if out is not None else torch.empty_like(x)
     _check(lib().sqp_rmsnorm(M, H, _dev(x, torch.float16, "x"), _dev(gamma, torch.float16, "gamma"), float(eps),

@@ -1,8 +1,10 @@
-"""Build the HIP library (gfx950 only) in-tree: paper_2312_03788_amd/libsqp.so."""
+"""Build the HIP library (gfx950 only) and the binding's native part in-tree:
+paper_2312_03788_amd/libsqp.so and paper_2312_03788_amd/_sqp_torch.so."""
 import os
 import re
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -10,6 +12,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsqp.so")
+TORCH_LIB = os.path.join(HERE, "_sqp_torch.so")
 
 SOURCES = ["sqp_api.hip", "sqp_companion.hip", "sqp_gemm_decode.hip", "sqp_gemm_prefill.hip", "sqp_gemm_slice.hip", "sqp_loss.hip", "sqp_mlp.hip", "sqp_static.hip",
            "sqp_strip_g128_rows32.hip", "sqp_strip_g128_rows64.hip", "sqp_strip_g64.hip", "sqp_strip_g32.hip", "sqp_strip_one_group.hip"]
@@ -98,10 +101,24 @@ def _compile(src):
     return obj
 
 
+def _build_torch_part():
+    """The host-only argument marshalling (csrc/sqp_torch.cpp), against the installed torch."""
+    import torch
+    from torch.utils import cpp_extension
+    libdir = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-w",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I" + sysconfig.get_paths()["include"]]
+    cmd += ["-I" + p for p in cpp_extension.include_paths()]
+    cmd += [os.path.join(CSRC, "sqp_torch.cpp"), "-o", TORCH_LIB, "-L" + libdir, "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath," + libdir]
+    subprocess.run(cmd, check=True)
+
+
 def build(verbose=False):
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=8) as ex:
+        torch_part = ex.submit(_build_torch_part)
         objs = list(ex.map(_compile, SOURCES))
+        torch_part.result()
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     subprocess.run(cmd, check=True)
     if verbose:

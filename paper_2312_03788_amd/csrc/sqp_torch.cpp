@@ -1,0 +1,167 @@
+// Argument marshalling of the serving calls (GEMM, RMSNorm, activation smoothing) for torch tensors, in
+// C++: a decode launch takes 5 to 15 us on the GPU, the same checks and the ctypes conversion in
+// Python 11 us per GEMM call.  Holds no arithmetic and no state but the addresses of the
+// library's entry points, which the Python binding hands over (so that it always calls the library
+// that the binding loaded).
+//
+// Every function returns the output tensor, or None for anything but the plain case (wrong type,
+// device, layout or shape, tensor subclasses, a workspace that has to grow, an error code): the
+// binding then takes its general path, which reports the error.
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+
+#include <ATen/ops/empty.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include <climits>
+
+namespace {
+
+typedef int (*GemmFn)(int, int, int, int, const void *, const uint32_t *, const void *, const uint8_t *, void *, void *);
+typedef size_t (*WorkspaceFn)(int, int, int, int);
+typedef int (*RmsnormFn)(int, int, const void *, const void *, float, void *, void *);
+typedef int (*ApplyFn)(int, int, const void *, const float *, void *, void *);
+
+GemmFn g_gemm[3];  // plain, fused activation, static scratch
+WorkspaceFn g_workspace_bytes;
+RmsnormFn g_rmsnorm;
+ApplyFn g_apply_x;
+
+// The tensor behind an argument if it is a dense GPU tensor of this type on device `dev`, else null.
+const at::Tensor *plain(PyObject *o, at::ScalarType type, long dev)
+{
+    if (!THPVariable_Check(o)) return nullptr;
+    const at::Tensor &t = THPVariable_Unpack(o);
+    if (!t.defined() || t.key_set().has(c10::DispatchKey::Python) || t.layout() != at::kStrided || !t.is_cuda()) return nullptr;
+    if (t.scalar_type() != type || t.get_device() != dev || !t.is_contiguous()) return nullptr;
+    return &t;
+}
+
+// `out` as given, or a new tensor like `like` with rows x cols elements (a given one is only taken
+// if it has exactly that many).
+bool output(PyObject *out, const at::Tensor &like, long rows, long cols, long dev, at::Tensor &y)
+{
+    if (out == Py_None) {
+        y = at::empty({rows, cols}, like.options());
+        return true;
+    }
+    const at::Tensor *t = plain(out, at::kHalf, dev);
+    if (!t || t->numel() != rows * cols) return false;
+    y = *t;
+    return true;
+}
+
+PyObject *result(PyObject *out, const at::Tensor &y)
+{
+    if (out == Py_None) return THPVariable_Wrap(y);
+    Py_INCREF(out);
+    return out;
+}
+
+bool fits(long v) { return v > 0 && v <= INT_MAX; }
+
+// gemm(which, x, packed, scales, zeros, group, out, device, stream, workspace bytes held)
+PyObject *gemm(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    if (n != 10) Py_RETURN_NONE;
+    const long which = PyLong_AsLong(a[0]), group = PyLong_AsLong(a[5]), dev = PyLong_AsLong(a[7]);
+    void *stream = PyLong_AsVoidPtr(a[8]);
+    const size_t held = PyLong_AsSize_t(a[9]);
+    if (PyErr_Occurred()) {
+        PyErr_Clear();
+        Py_RETURN_NONE;
+    }
+    if (which < 0 || which > 2 || !g_gemm[which]) Py_RETURN_NONE;
+    const at::Tensor *x = plain(a[1], at::kHalf, dev), *packed = plain(a[2], at::kInt, dev);
+    const at::Tensor *scales = plain(a[3], at::kHalf, dev), *zeros = plain(a[4], at::kByte, dev);
+    if (!x || !packed || !scales || !zeros || x->dim() != 2 || packed->dim() != 2) Py_RETURN_NONE;
+    const long M = x->size(0), K = x->size(1), N = packed->size(1);
+    if (!fits(M) || !fits(K) || !fits(N) || !fits(group) || packed->size(0) * 8 != K) Py_RETURN_NONE;
+    if (which != 2 && g_workspace_bytes((int)M, (int)N, (int)K, (int)group) > held) Py_RETURN_NONE;
+    try {
+        at::Tensor y;
+        if (!output(a[6], *x, M, which == 1 ? N / 2 : N, dev, y)) Py_RETURN_NONE;
+        if (g_gemm[which]((int)M, (int)N, (int)K, (int)group, x->data_ptr(), (const uint32_t *)packed->data_ptr(), scales->data_ptr(),
+                          (const uint8_t *)zeros->data_ptr(), y.data_ptr(), stream) != 0)
+            Py_RETURN_NONE;
+        return result(a[6], y);
+    } catch (...) {  // e.g. out of memory: the general path raises it as Python does
+        Py_RETURN_NONE;
+    }
+}
+
+// rmsnorm(x, gamma, eps, out, device, stream)
+PyObject *rmsnorm(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    if (n != 6) Py_RETURN_NONE;
+    const double eps = PyFloat_AsDouble(a[2]);
+    const long dev = PyLong_AsLong(a[4]);
+    void *stream = PyLong_AsVoidPtr(a[5]);
+    if (PyErr_Occurred()) {
+        PyErr_Clear();
+        Py_RETURN_NONE;
+    }
+    const at::Tensor *x = plain(a[0], at::kHalf, dev), *gamma = plain(a[1], at::kHalf, dev);
+    if (!x || !gamma || x->dim() != 2 || !fits(x->size(0)) || !fits(x->size(1))) Py_RETURN_NONE;
+    try {
+        at::Tensor y;
+        if (!output(a[3], *x, x->size(0), x->size(1), dev, y)) Py_RETURN_NONE;
+        if (g_rmsnorm((int)x->size(0), (int)x->size(1), x->data_ptr(), gamma->data_ptr(), (float)eps, y.data_ptr(), stream) != 0) Py_RETURN_NONE;
+        return result(a[3], y);
+    } catch (...) {
+        Py_RETURN_NONE;
+    }
+}
+
+// apply_x(x, s, out, device, stream)
+PyObject *apply_x(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    if (n != 5) Py_RETURN_NONE;
+    const long dev = PyLong_AsLong(a[3]);
+    void *stream = PyLong_AsVoidPtr(a[4]);
+    if (PyErr_Occurred()) {
+        PyErr_Clear();
+        Py_RETURN_NONE;
+    }
+    const at::Tensor *x = plain(a[0], at::kHalf, dev), *s = plain(a[1], at::kFloat, dev);
+    if (!x || !s || x->dim() != 2 || !fits(x->size(0)) || !fits(x->size(1))) Py_RETURN_NONE;
+    try {
+        at::Tensor y;
+        if (!output(a[2], *x, x->size(0), x->size(1), dev, y)) Py_RETURN_NONE;
+        if (g_apply_x((int)x->size(0), (int)x->size(1), x->data_ptr(), (const float *)s->data_ptr(), y.data_ptr(), stream) != 0) Py_RETURN_NONE;
+        return result(a[2], y);
+    } catch (...) {
+        Py_RETURN_NONE;
+    }
+}
+
+// bind(addresses of sqp_w4a16_gemm, _silu_mul, _static, _workspace_bytes, sqp_rmsnorm, sqp_smooth_apply_x)
+PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    void *p[6];
+    if (n != 6) {
+        PyErr_SetString(PyExc_TypeError, "bind takes six addresses");
+        return nullptr;
+    }
+    for (int i = 0; i < 6; i++) p[i] = PyLong_AsVoidPtr(a[i]);
+    if (PyErr_Occurred()) return nullptr;
+    for (int i = 0; i < 3; i++) g_gemm[i] = (GemmFn)p[i];
+    g_workspace_bytes = (WorkspaceFn)p[3];
+    g_rmsnorm = (RmsnormFn)p[4];
+    g_apply_x = (ApplyFn)p[5];
+    Py_RETURN_NONE;
+}
+
+PyMethodDef methods[] = {
+    {"bind", (PyCFunction)(void (*)(void))bind, METH_FASTCALL, nullptr},
+    {"gemm", (PyCFunction)(void (*)(void))gemm, METH_FASTCALL, nullptr},
+    {"rmsnorm", (PyCFunction)(void (*)(void))rmsnorm, METH_FASTCALL, nullptr},
+    {"apply_x", (PyCFunction)(void (*)(void))apply_x, METH_FASTCALL, nullptr},
+    {nullptr, nullptr, 0, nullptr},
+};
+
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_sqp_torch", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+extern "C" __attribute__((visibility("default"))) PyObject *PyInit__sqp_torch() { return PyModule_Create(&module); }

@@ -15,7 +15,7 @@ import pytest
 import torch
 
 import workloads as wl
-from gpu_util import gemm_tolerance_ok
+from gpu_util import dev, gemm_tolerance_ok
 
 pytestmark = pytest.mark.gpu
 
@@ -321,3 +321,46 @@ def test_companion_outputs_between_guards(orc, sqp, K, N, group):
     assert L.sqp_interleave_gate_up(K, N, _ptr(dw), _ptr(dw), wi.ptr, st) == 0
     wi.check("interleave out")
     assert np.array_equal(wi.numpy()[:, 0::2].view(np.uint16), w.view(np.uint16))
+
+
+def test_native_marshalling_equals_general_path(orc, sqp):
+    """The serving calls through the native marshalling give the general path's bits, with and without
+    an output; what the general path refuses is refused with the same error, and what it takes
+    (a flat output of the right size, a tensor subclass) is still taken."""
+    import paper_2312_03788_amd.binding as b
+    _, xcal, w = wl.layer_inputs(1, 512, 272)
+    p, sc, z = (dev(a) for a in orc.quantize_pack(w, 128))
+    x, s = dev(np.ascontiguousarray(xcal[:5])), dev(orc.smooth_scales(xcal, w, 0.5))
+    gamma = torch.ones(512, dtype=torch.float16, device="cuda")
+    new = lambda n: torch.empty((5, n), dtype=torch.float16, device="cuda")
+    calls = [(sqp.w4a16_gemm, (x, p, sc, z, 128), 272), (sqp.w4a16_gemm_static, (x, p, sc, z, 128), 272),
+             (sqp.w4a16_gemm_silu_mul, (x, p, sc, z, 128), 136), (sqp.rmsnorm, (x, gamma, 1e-5), 512), (sqp.smooth_apply_x, (x, s), 512)]
+
+    class Tagged(torch.Tensor):
+        pass
+
+    def general(fn, *args, **kw):
+        held, b._fast = b._fast, None
+        try:
+            return fn(*args, **kw)
+        finally:
+            b._fast = held
+
+    for fn, args, n in calls:
+        want = general(fn, *args)
+        assert b._native(x) and fn(*args).shape == want.shape == (5, n)
+        for out in (None, new(n), torch.empty(5 * n, dtype=torch.float16, device="cuda")):
+            got = fn(*args, out=out)
+            assert out is None or got is out
+            assert torch.equal(got.reshape(5, n), want) and got.dtype == torch.float16
+        assert torch.equal(fn(args[0].as_subclass(Tagged), *args[1:]).as_subclass(torch.Tensor), want)
+        bad = [(x.float(),) + args[1:], (x.cpu(),) + args[1:], (torch.cat([x, x], 1)[:, ::2],) + args[1:],
+               (x.reshape(-1)[:5 * 512 - 5].reshape(5, 511),) + args[1:], args[:1] + (args[1].double(),) + args[2:]]
+        for a in bad:
+            messages = []
+            for run in (fn, lambda *v: general(fn, *v)):
+                with pytest.raises((b.SqpError, RuntimeError)) as e:
+                    run(*a)
+                messages.append(str(e.value))
+            assert messages[0] == messages[1], messages
+    torch.cuda.synchronize()
