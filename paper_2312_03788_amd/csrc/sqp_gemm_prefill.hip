@@ -34,21 +34,46 @@ namespace {
 
 constexpr int BK = 64;
 
-// NT: 32-column MFMA tiles per wave (wave tile 128 rows x 32 NT columns); WM: waves along the
-// rows, the other 4 / WM along the columns.
-//   <4, 1>: 128 x 512 tile, the four waves side by side on the same 128 rows.  Every packed word
+// Issue order of the vector instructions of one k-step, in groups of four, for a wave tile of RT x NT
+// MFMA tiles (see the kernel): P<m> and P0' the A operands, S the shifts, AO / ADD / MUL<t> the B
+// operands.  P<m> starts when row tile m - 1's MFMAs do; P0' and the last MUL close the list.
+enum { G_P = 0, G_P0N = 8, G_S = 9, G_AO = 10, G_ADD = G_AO + 4, G_MUL = G_ADD + 4 };
+template <int RT, int NT>
+struct Order {
+    static constexpr int NG = RT + 1 + 3 * NT;
+    int g[NG];
+    constexpr Order() : g()
+    {
+        for (int i = 0; i < NG; i++) g[i] = -1;
+        for (int m = 1; m < RT; m++) g[NG * (m - 1) / RT] = G_P + m;
+        g[NG - 2] = G_P0N;
+        g[NG - 1] = G_MUL + NT - 1;
+        int at = 0;
+        auto put = [&](int v) { while (g[at] >= 0) at++; g[at] = v; };
+        put(G_S);
+        for (int t = 0; t < NT; t++) put(G_AO + t);
+        for (int t = 0; t < NT; t++) put(G_ADD + t);
+        for (int t = 0; t + 1 < NT; t++) put(G_MUL + t);
+    }
+};
+
+// RT, NT: 32-row and 32-column MFMA tiles per wave; WM: waves along the rows, the other 4 / WM along
+// the columns.  A workgroup owns 32 RT WM rows x 32 NT (4 / WM) columns:
+//   <4, 4, 1>: 128 x 512, the four waves side by side on the same 128 rows.  Every packed word
 //           is then loaded and unpacked by exactly one wave, and a workgroup stages half as
 //           many activation bytes per matrix instruction as with the square tile.
-//   <4, 2>: 256 x 256 tile, waves 2 x 2 (the two waves of a column pair unpack the same words).
-//   <2, *>: the same with half the columns (128 x 256 / 256 x 128), used for the tiles left over
+//   <4, 4, 2>: 256 x 256, waves 2 x 2 (the two waves of a column pair unpack the same words).
+//   <4, 2, *>: the same with half the columns (128 x 256 / 256 x 128), used for the tiles left over
 //           after the last full round so that the tail of a launch costs half a round, and for
 //           the K-split launches.
-// Workgroup b of the launch handles tile tile0 + b / (full columns / columns) of the tn x tm grid
-// of full tiles (column index fastest), column half b % 2 of it when it covers half.
+//   <3, 2, 1>, <5, 2, 1>, <6, 2, 1>: 96, 160 or 192 rows x 256 columns, K-split launches of row
+//           counts that would leave much of a 128-row tile empty.
+// Workgroup b of the launch handles tile tile0 + b of the grid of such tiles (column index fastest,
+// tn tiles per row).
 // G32: quantisation groups of 32 rows, i.e. two groups per 64-row stage (the steps and zero
 // points of both are loaded per stage and the unpack switches sets after the second k-step);
 // otherwise the group is a multiple of 64 rows.
-template <int NT, int WM, bool G32>
+template <int RT, int NT, int WM, bool G32>
 __global__ void __launch_bounds__(256)
 w4a16_prefill_kernel(int M, int N, int K, int group, int tile0, int tn, const h16 *__restrict__ x,
                      const uint32_t *__restrict__ packed, const h16 *__restrict__ scales,
@@ -56,31 +81,31 @@ w4a16_prefill_kernel(int M, int N, int K, int group, int tile0, int tn, const h1
 {
     constexpr int W = 4;                   // waves: one per SIMD
     constexpr int WNW = W / WM;            // waves along the columns
-    constexpr int BM = 128 * WM;           // rows per workgroup
-    constexpr int FULLN = WNW * 128;       // columns of a full tile of this arrangement
+    constexpr int BM = 32 * RT * WM;       // rows per workgroup
     constexpr int WN = 32 * NT;            // columns per wave
+    static_assert(NT == 2 || NT == 4, "a lane's columns are one load");
     typedef uint32_t wvec __attribute__((ext_vector_type(NT)));
     typedef std::conditional_t<NT == 4, u32x2, uint32_t> scvec;
     constexpr int D = 3;                   // register stages of packed weights (two in flight)
     constexpr int XD = 4;                  // LDS slots of activations
-    constexpr int XSTAGE = BM * BK * 2;   // 16 or 32 KB: blocks of 8 rows x 128 bytes
-    constexpr int OX = (BM / 8) / W;       // direct loads per wave per stage (one per 1 KB block)
-    constexpr int WGN = WNW * WN;          // columns per workgroup: a full tile's or half of them
-    static_assert(OX % 4 == 0, "the loads of a stage are spread evenly over its four k-steps");
+    constexpr int XSTAGE = BM * BK * 2;    // blocks of 8 rows x 128 bytes
+    constexpr int OX = (BM / 8) / W;       // direct loads per wave per stage (one per 1 KB block), spread over its four k-steps
+    constexpr int WGN = WNW * WN;          // columns per workgroup
     constexpr int NQ = G32 ? 2 : 1;        // quantisation groups per stage
     constexpr int OW = 4 + 2 * NQ;
+    static_assert(2 * (OX + OW) < 64, "vmcnt field");
     __shared__ __attribute__((aligned(1024))) unsigned char xring[XD * XSTAGE];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / WNW, wn = wave % WNW;
     const int l32 = lane & 31, kb = lane >> 5;
-    const int tile = tile0 + (int)blockIdx.x / (FULLN / WGN);
-    const int nbase = (tile % tn) * FULLN + (WGN == FULLN ? 0 : ((int)blockIdx.x & 1) * WGN);
+    const int tile = tile0 + (int)blockIdx.x;
+    const int nbase = (tile % tn) * WGN;
     const int m0 = (tile / tn) * BM;
     const int n0 = nbase + wn * WN;
     // K split across gridDim.y workgroups (part != nullptr): this one takes stages
-    // [stage0, stage0 + stages) and leaves its fp32 sums in part[blockIdx.y][M][N].
+    // [stage0, stage0 + stages) and leaves its fp32 sums in part[blockIdx.y][blockIdx.x][BM][WGN].
     const int stages_all = K / BK;
     const int stage0 = (int)((long)stages_all * blockIdx.y / gridDim.y);
     const int stages = (int)((long)stages_all * (blockIdx.y + 1) / gridDim.y) - stage0;
@@ -89,9 +114,9 @@ w4a16_prefill_kernel(int M, int N, int K, int group, int tile0, int tn, const h1
     int ncol = n0 + NT * l32;
     if (ncol >= N) ncol = 0;
 
-    f32x16 acc[4][NT];
+    f32x16 acc[RT][NT];
 #pragma unroll
-    for (int mt = 0; mt < 4; mt++)
+    for (int mt = 0; mt < RT; mt++)
 #pragma unroll
         for (int t = 0; t < NT; t++)
 #pragma unroll
@@ -148,8 +173,7 @@ w4a16_prefill_kernel(int M, int N, int K, int group, int tile0, int tn, const h1
         }
     };
 
-    // Activations: wave w copies blocks w, w+4, ..., w+28 of the stage (a block = 8 rows x 128
-    // bytes).  Lane i of a block handles row i / 8 of the block and fetches piece
+    // Activations: wave w copies blocks w, w+4, ... of the stage (a block = 8 rows x 128 bytes).  Lane i of a block handles row i / 8 of the block and fetches piece
     // (i % 8) ^ key(row) of that row's 128 bytes, key(row) = (row / 2) % 8; the hardware puts
     // lane i at byte 16*i of the block.
     uint32_t xoff[OX];
@@ -180,19 +204,19 @@ w4a16_prefill_kernel(int M, int N, int K, int group, int tile0, int tn, const h1
         zq += wrap ? (long)N * NQ : 0;
     };
     const uint32_t xrd0 = (uint32_t)(size_t)xring +
-                          (uint32_t)(((wm * 128 + l32) >> 3) * 1024 + ((wm * 128 + l32) & 7) * 128);
+                          (uint32_t)(((wm * 32 * RT + l32) >> 3) * 1024 + ((wm * 32 * RT + l32) & 7) * 128);
     const int xkey = (l32 >> 1) & 7;
 
-    auto read_a = [&](u32x4 (&xa)[4], int slot, int ks) {
+    auto read_a = [&](u32x4 (&xa)[RT], int slot, int ks) {
         const uint32_t poff = xrd0 + (uint32_t)(slot * XSTAGE) + (uint32_t)((((ks * 2 + kb) ^ xkey)) * 16);
 #pragma unroll
-        for (int mt = 0; mt < 4; mt++)
+        for (int mt = 0; mt < RT; mt++)
             asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(xa[mt]) : "v"(poff), "n"(mt * 4096) : "memory");
     };
-    auto wait_a = [&](u32x4 (&xa)[4]) {
+    auto wait_a = [&](u32x4 (&xa)[RT]) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-        for (int mt = 0; mt < 4; mt++) asm volatile("" : "+v"(xa[mt]));
+        for (int mt = 0; mt < RT; mt++) asm volatile("" : "+v"(xa[mt]));
     };
 
     // per-stage constants of the unpack: -(1024 + Z), -(64 + Z) and the step, each in both
@@ -224,8 +248,11 @@ w4a16_prefill_kernel(int M, int N, int K, int group, int tile0, int tn, const h1
     // (four slots) and weight registers (three stages) are refilled during stage s with the
     // loads of stage s+2.
     Stage stg[D];
-    u32x4 xa[2][4];          // raw A fragments from LDS: [k-step parity][row tile]
-    uint32_t aq[2][4];       // permuted A operand of row tile m in aq[m % 2]
+    u32x4 xa[2][RT];         // raw A fragments from LDS: [k-step parity][row tile]
+    // permuted A operand of row tile m in aq[m % AQ]: never the one that the row tile in front is using,
+    // for row tile 0 of the next k-step behind the last either
+    constexpr int AQ = RT % 2 == 0 ? 2 : 3;
+    uint32_t aq[AQ][4];
     uint32_t bq[2][NT][4];   // B operands (dequantised weights): [k-step parity][column tile]
     uint32_t w8[NT];
     const uint32_t sel_a = 0x05040100u, sel_b = 0x07060302u;  // v_perm_b32 selectors of permute_x
@@ -237,7 +264,7 @@ w4a16_prefill_kernel(int M, int N, int K, int group, int tile0, int tn, const h1
     // the compiler's own order left many such pairs.  So every MFMA and every vector
     // instruction of the k-step is a volatile asm statement (these keep their order), grouped
     // so that a result is used no sooner than 4 instructions later:
-    //   MFMA i (row tile i / NT, column tile i % NT), then the next 4-5 entries of the list
+    //   MFMA i (row tile i / NT, column tile i % NT), then the next 4-5 entries of the list, e.g. for 4 x 4
     //     P1, S, AO.., P2, AO.., ADD.., P3, ADD.., MUL.., P0', MUL
     //   P<m>: 4 perms giving row tile m's A operand (P0': row tile 0 of the NEXT k-step, after
     //   the wait for its LDS reads); S: word >> 8; AO/ADD/MUL<t>: the and-or, add and multiply
@@ -256,23 +283,17 @@ w4a16_prefill_kernel(int M, int N, int K, int group, int tile0, int tn, const h1
         if (j == 2) asm volatile("v_perm_b32 %0, %1, %2, %3" : "=v"(dst[2]) : "v"(v.w), "v"(v.y), "s"(sel_a));
         if (j == 3) asm volatile("v_perm_b32 %0, %1, %2, %3" : "=v"(dst[3]) : "v"(v.w), "v"(v.y), "s"(sel_b));
     };
-    enum { G_P1, G_P2, G_P3, G_P0N, G_S, G_AO, G_ADD = G_AO + 4, G_MUL = G_ADD + 4 };
-    constexpr int NG = NT == 4 ? 17 : 11;
-    constexpr int order4[17] = {G_P1, G_S, G_AO + 0, G_AO + 1, G_P2, G_AO + 2, G_AO + 3, G_ADD + 0, G_P3,
-                                G_ADD + 1, G_ADD + 2, G_ADD + 3, G_MUL + 0, G_MUL + 1, G_MUL + 2, G_P0N, G_MUL + 3};
-    constexpr int order2[17] = {G_P1, G_S, G_P2, G_AO + 0, G_AO + 1, G_P3, G_ADD + 0, G_ADD + 1, G_MUL + 0, G_P0N, G_MUL + 1,
-                                0, 0, 0, 0, 0, 0};
-    constexpr int NMF = 4 * NT;                 // MFMAs per k-step
-    constexpr int WAIT_AT = NT == 4 ? 13 : 5;   // the LDS wait goes in front of this MFMA
+    constexpr Order<RT, NT> order{};
+    constexpr int NG = Order<RT, NT>::NG;
+    constexpr int NMF = RT * NT;                        // MFMAs per k-step
+    constexpr int WAIT_AT = NMF * (NG - 2) / NG - 1;    // the LDS wait goes in front of this MFMA (P0' follows the next)
 
     // one entry j of group g; wn = the packed words of the next k-step, kn = that k-step's
     // position in its stage (it selects the quantisation group's constants)
     auto valu = [&](int g, int j, int cur, const wvec &wn, int kn) {
         const int nxt = cur ^ 1;
         const int qs = G32 ? (kn >> 1) : 0;
-        if (g == G_P1) perm4(aq[1], xa[cur][1], j);
-        else if (g == G_P2) perm4(aq[0], xa[cur][2], j);
-        else if (g == G_P3) perm4(aq[1], xa[cur][3], j);
+        if (g > G_P && g < G_P0N) perm4(aq[(g - G_P) % AQ], xa[cur][g - G_P], j);
         else if (g == G_P0N) perm4(aq[0], xa[nxt][0], j);
         else if (g == G_S) {
             if (j < NT) asm volatile("v_lshrrev_b32 %0, 8, %1" : "=v"(w8[j]) : "v"(wn[j]));
@@ -330,7 +351,7 @@ w4a16_prefill_kernel(int M, int N, int K, int group, int tile0, int tn, const h1
             for (int ks = 0; ks < 4; ks++) {
                 const int cur = ks & 1, nxt = cur ^ 1;
 #pragma unroll
-                for (int j = 0; j < OX / 4; j++) issue_x(slot_fill, (OX / 4) * ks + j);
+                for (int j = OX * ks / 4; j < OX * (ks + 1) / 4; j++) issue_x(slot_fill, j);
                 if (ks < 3) {
                     read_a(xa[nxt], slot, ks + 1);
                 } else {
@@ -344,10 +365,10 @@ w4a16_prefill_kernel(int M, int N, int K, int group, int tile0, int tn, const h1
 #pragma unroll
                 for (int i = 0; i < NMF; i++) {
                     if (i == WAIT_AT) wait_a(xa[nxt]);
-                    mfma(acc[i / NT][i % NT], aq[(i / NT) & 1], bq[cur][i % NT]);
+                    mfma(acc[i / NT][i % NT], aq[(i / NT) % AQ], bq[cur][i % NT]);
 #pragma unroll
                     for (int e = i * (4 * NG) / NMF; e < (i + 1) * (4 * NG) / NMF; e++)
-                        valu(NT == 4 ? order4[e / 4] : order2[e / 4], e % 4, cur, wn, (ks + 1) & 3);
+                        valu(order.g[e / 4], e % 4, cur, wn, (ks + 1) & 3);
                 }
             }
             // End of the last iteration.  (1) Drain the clamped look-ahead loads: their
@@ -380,30 +401,30 @@ w4a16_prefill_kernel(int M, int N, int K, int group, int tile0, int tn, const h1
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int e_l32 = tid & 31, e_kb = (tid >> 5) & 1, e_wave = tid >> 6;
-    const int nout = nbase + (e_wave % WNW) * WN + NT * e_l32;
-    const int mrow0 = m0 + (e_wave / WNW) * 128 + 4 * e_kb;
+    const int nloc = (e_wave % WNW) * WN + NT * e_l32;   // first column within the tile
+    const int nout = nbase + nloc;
+    const int mloc0 = (e_wave / WNW) * 32 * RT + 4 * e_kb, mrow0 = m0 + mloc0;
     if (part != nullptr) {
-        if (nout < N) {
-            float *pcol = part + (size_t)blockIdx.y * M * N + nout;
+        float *ptile = part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * (BM * WGN) + nloc;
 #pragma unroll
-            for (int mt = 0; mt < 4; mt++)
+        for (int mt = 0; mt < RT; mt++)
 #pragma unroll
-                for (int r = 0; r < 16; r++) {
-                    const int m = mrow0 + mt * 32 + 8 * (r >> 2) + (r & 3);
-                    if (m < M) {
-                        if constexpr (NT == 4)
-                            *reinterpret_cast<f32x4 *>(pcol + (size_t)m * N) = f32x4{acc[mt][0][r], acc[mt][1][r], acc[mt][2][r], acc[mt][3][r]};
-                        else
-                            *reinterpret_cast<float2 *>(pcol + (size_t)m * N) = make_float2(acc[mt][0][r], acc[mt][1][r]);
-                    }
+            for (int r = 0; r < 16; r++) {
+                const int mo = mt * 32 + 8 * (r >> 2) + (r & 3);
+                if (mrow0 + mo < M && nout < N) {
+                    float *p = ptile + (size_t)(mloc0 + mo) * WGN;
+                    if constexpr (NT == 4)
+                        *reinterpret_cast<f32x4 *>(p) = f32x4{acc[mt][0][r], acc[mt][1][r], acc[mt][2][r], acc[mt][3][r]};
+                    else
+                        *reinterpret_cast<float2 *>(p) = make_float2(acc[mt][0][r], acc[mt][1][r]);
                 }
-        }
+            }
         return;
     }
     if (nout < N) {
         h16 *ycol = y + nout;
 #pragma unroll
-        for (int mt = 0; mt < 4; mt++)
+        for (int mt = 0; mt < RT; mt++)
 #pragma unroll
             for (int r = 0; r < 16; r++) {
                 const int m = mrow0 + mt * 32 + 8 * (r >> 2) + (r & 3);
@@ -434,17 +455,22 @@ w4a16_prefill_kernel(int M, int N, int K, int group, int tile0, int tn, const h1
     }
 }
 
-// y = fp16(sum over the K parts, in part order) of the fp32 partial matrices: 8 elements
-// per thread.
-__global__ void __launch_bounds__(256) splitk_reduce_kernel(const float *__restrict__ part, long total8, long stride, int parts,
-                                                            h16 *__restrict__ y, int epi)
+// y = fp16(sum over the K parts, in part order) of the fp32 partial tiles part[parts][tiles][bm][wgn]
+// that the launch of tiles tile0 .. left: 8 adjacent columns per thread.  grid: (bm wgn / 2048, tiles);
+// wgn 128 or 256.
+__global__ void __launch_bounds__(256) splitk_reduce_kernel(const float *__restrict__ part, int M, int N, int bm, int wgn, int tile0, int tn,
+                                                            int parts, h16 *__restrict__ y, int epi)
 {
-    const long i = (long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= total8) return;
-    const f32x4 *p = reinterpret_cast<const f32x4 *>(part) + 2 * i;
+    const int e = (blockIdx.x * 256 + threadIdx.x) * 8;      // element of the tile
+    const int row = wgn == 256 ? e >> 8 : e >> 7, col = e & (wgn - 1);
+    const int tile = tile0 + blockIdx.y;
+    const int m = (tile / tn) * bm + row, n = (tile % tn) * wgn + col;
+    if (m >= M || n >= N) return;
+    const f32x4 *p = reinterpret_cast<const f32x4 *>(part + (size_t)blockIdx.y * bm * wgn + e);
+    const size_t stride = (size_t)gridDim.y * bm * wgn / 4;  // one part, in 16-byte pieces
     f32x4 a = p[0], b = p[1];
     for (int s = 1; s < parts; s++) {
-        const f32x4 *q = reinterpret_cast<const f32x4 *>(part + (size_t)s * stride) + 2 * i;
+        const f32x4 *q = p + s * stride;
         a += q[0];
         b += q[1];
     }
@@ -452,13 +478,13 @@ __global__ void __launch_bounds__(256) splitk_reduce_kernel(const float *__restr
         h16x4 o;
         o.x = (h16)(sqp_silu(a.x) * a.y); o.y = (h16)(sqp_silu(a.z) * a.w);
         o.z = (h16)(sqp_silu(b.x) * b.y); o.w = (h16)(sqp_silu(b.z) * b.w);
-        reinterpret_cast<h16x4 *>(y)[i] = o;
+        *reinterpret_cast<h16x4 *>(y + (size_t)m * (N >> 1) + (n >> 1)) = o;
         return;
     }
     h16x8 o;
     o.s0 = (h16)a.x; o.s1 = (h16)a.y; o.s2 = (h16)a.z; o.s3 = (h16)a.w;
     o.s4 = (h16)b.x; o.s5 = (h16)b.y; o.s6 = (h16)b.z; o.s7 = (h16)b.w;
-    reinterpret_cast<h16x8 *>(y)[i] = o;
+    *reinterpret_cast<h16x8 *>(y + (size_t)m * N + n) = o;
 }
 
 int compute_units()
@@ -551,43 +577,175 @@ extern "C" void sqp_debug_prefill_plan(int M, int N, int K, int cus, long *full,
     *ksplit = p.ksplit;
 }
 
+// What a call launches: up to two launches of tiles of 32 rt rows x 32 nt columns per wave, each over
+// `tiles` tiles from tile0 of a grid with tn tiles per row, in `parts` K parts (1: straight to y).
+struct TileLaunch {
+    int rt, nt;
+    long tile0, tiles;
+    int tn, parts;
+};
+struct LaunchPlan {
+    int wm, count;
+    TileLaunch l[2];
+};
+
+// Test hook: one launch of this variant over the whole output (0: automatic).
+static int g_force_rt = 0, g_force_nt = 0, g_force_parts = 0;
+extern "C" void sqp_debug_set_prefill_variant(int rt, int nt, int parts)
+{
+    g_force_rt = rt;
+    g_force_nt = nt;
+    g_force_parts = parts;
+}
+
+static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, bool have_workspace)
+{
+    const TilePlan p = plan_tiles(M, N, K, group, cus, have_workspace);
+    LaunchPlan q = {p.wm, 0, {}};
+    const int stages = K / BK, tnf = (N + (4 / p.wm) * 128 - 1) / ((4 / p.wm) * 128);
+    if (g_force_rt > 0 && group != 32) {
+        const int wg = 128 * g_force_nt;
+        const int tn = (N + wg - 1) / wg, tm = (M + 32 * g_force_rt - 1) / (32 * g_force_rt);
+        q.wm = 1;
+        q.count = 1;
+        int parts = g_force_nt == 2 && have_workspace ? g_force_parts : 1;
+        if (parts > stages) parts = stages;
+        q.l[0] = TileLaunch{g_force_rt, g_force_nt, 0, (long)tn * tm, tn, parts < 1 ? 1 : parts};
+        return q;
+    }
+    const bool hooked = g_tile_mode != 0 || g_tile_shape != 0 || g_ksplit >= 0;
+    // Everything in one round of the chip: the variant and the number of K parts with the least estimated time.
+    // Estimate (us), fitted to 400 measured launches of 51 shapes (rms 7 %): per 64-row stage of K
+    // 0.72 / 0.77 / 0.97 / 1.11 for tiles of 96 / 128 / 160 / 192 rows x 256 columns and 1.43 for
+    // 128 x 512, plus the fp32 parts' way out and back at 5.6 TB/s; more than 12 parts never won.
+    // What it buys (us, 128-row tiles only -> chosen): 8192->8192 at 72 / 150 / 190 / 320 / 640 rows
+    // 33.6 -> 27.7, 47.0 -> 37.9, 47.6 -> 39.8, 71.1 -> 56.7, 116 -> 96; 4096->22016 at 80 / 160 / 320 rows
+    // 43.7 -> 35.4, 65.5 -> 47.9, 99 -> 76; 8192->10240 at 160 rows 56 -> 43: a 128-row tile computes
+    // rows that are not there.
+    if (!hooked && group != 32) {
+        const double part_us = (double)M * N * 8 / 5.6e6;
+        double best = 0;
+        const long tiles44 = (long)((N + 511) / 512) * ((M + 127) / 128);
+        if (tiles44 <= cus) {
+            best = stages * 1.43;
+            q.wm = 1;
+            q.count = 1;
+            q.l[0] = TileLaunch{4, 4, 0, tiles44, (N + 511) / 512, 1};
+        }
+        const double stage_us[7] = {0, 0, 0, 0.72, 0.77, 0.97, 1.11};
+        const int tn = (N + 255) / 256;
+        for (int rt = 3; rt <= 6; rt++) {
+            const long tiles = (long)tn * ((M + 32 * rt - 1) / (32 * rt));
+            int most = have_workspace ? (int)(cus / tiles) : 1;
+            if (most > stages / 8) most = stages / 8;  // at least 8 stages per part
+            if (most > 12) most = 12;
+            if (tiles > cus) continue;
+            for (int parts = 1; parts <= (most > 1 ? most : 1); parts++) {
+                const double t = (stages + parts - 1) / parts * stage_us[rt] + (parts > 1 ? parts * part_us : 0.0);
+                if (q.count == 0 || t < best) {
+                    best = t;
+                    q.count = 1;
+                    q.l[0] = TileLaunch{rt, 2, 0, tiles, tn, parts};
+                }
+            }
+        }
+        if (q.count) return q;
+    }
+    if (p.full > 0) q.l[q.count++] = TileLaunch{4, 4, 0, p.full, tnf, 1};
+    if (p.half > 0) {
+        int parts = p.ksplit;
+        // Few tiles left over after the whole rounds: split in K as well, as far as they then fill the
+        // chip once.
+        if (!hooked && p.full > 0 && have_workspace) {
+            int most = (int)(cus / p.half);
+            if (most > stages / 8) most = stages / 8;
+            if (most > 16) most = 16;
+            const double part_us = (double)p.half * 128 * 256 * 8 / 4.5e6;
+            double best = stages * 0.77;
+            for (int n = 2; n <= most; n++) {
+                const double t = (stages + n - 1) / n * 0.77 + n * part_us + 3;
+                if (t < best) {
+                    best = t;
+                    parts = n;
+                }
+            }
+        }
+        q.l[q.count++] = TileLaunch{4, 2, 2 * p.full, p.half, 2 * tnf, parts};
+    }
+    return q;
+}
+
+// Test hook: the launches of a call (no GPU needed): up to two of (rt, nt, tiles, parts).
+extern "C" int sqp_debug_prefill_launches(int M, int N, int K, int group, int cus, int *out8)
+{
+    const LaunchPlan q = plan_launches(M, N, K, group, cus, true);
+    for (int i = 0; i < q.count; i++) {
+        out8[4 * i] = q.l[i].rt;
+        out8[4 * i + 1] = q.l[i].nt;
+        out8[4 * i + 2] = (int)q.l[i].tiles;
+        out8[4 * i + 3] = q.l[i].parts;
+    }
+    return q.count;
+}
+
+static size_t launch_partial_bytes(const TileLaunch &l, int wm)
+{
+    return l.parts >= 2 ? (size_t)l.parts * l.tiles * (32 * l.rt * wm) * (l.nt * 128 / wm) * sizeof(float) : 0;
+}
+
 size_t sqp_gemm_prefill_partial_bytes(int M, int N, int K, int group)
 {
     if (group % BK != 0 && !(group == 32 && K % BK == 0)) return sqp_gemm_decode_partial_bytes(M < 64 ? M : 64, N, K, group);  // row-block fallback
-    const TilePlan p = plan_tiles(M, N, K, group, compute_units(), true);
-    return p.ksplit >= 2 ? (size_t)p.ksplit * M * N * sizeof(float) : 0;
+    const LaunchPlan q = plan_launches(M, N, K, group, compute_units(), true);
+    size_t need = 0;
+    for (int i = 0; i < q.count; i++) {
+        const size_t b = launch_partial_bytes(q.l[i], q.wm);
+        need = b > need ? b : need;
+    }
+    return need;
 }
 
-template <int WM, bool G32>
-static int launch_tiles(const TilePlan &p, int M, int N, int K, int group, const h16 *x, const uint32_t *packed, const h16 *scales,
-                        const uint8_t *zeros, h16 *y, int epi, const SqpWorkspace &ws, hipStream_t stream)
+template <int RT, int NT, int WM, bool G32>
+static void launch_variant(const TileLaunch &l, int M, int N, int K, int group, const h16 *x, const uint32_t *packed, const h16 *scales,
+                           const uint8_t *zeros, h16 *y, int epi, float *part, hipStream_t stream)
 {
-    constexpr int FULLN = (4 / WM) * 128;
-    const int tn = (N + FULLN - 1) / FULLN;
-    if (p.ksplit >= 2) {
-        if ((size_t)p.ksplit * M * N * sizeof(float) > ws.partial_bytes) return SQP_ERR_WORKSPACE;
-        float *part = ws.partial;
-        w4a16_prefill_kernel<2, WM, G32><<<dim3((unsigned)p.half, p.ksplit), 256, 0, stream>>>(M, N, K, group, 0, tn, x, packed, scales, zeros, y, part, epi);
-        const long total8 = (long)M * N / 8;
-        splitk_reduce_kernel<<<(unsigned)((total8 + 255) / 256), 256, 0, stream>>>(part, total8, (long)M * N, p.ksplit, y, epi);
-        return sqp_launch_status();
-    }
-    if (p.full > 0)
-        w4a16_prefill_kernel<4, WM, G32><<<dim3((unsigned)p.full), 256, 0, stream>>>(M, N, K, group, 0, tn, x, packed, scales, zeros, y, nullptr, epi);
-    if (p.half > 0)
-        w4a16_prefill_kernel<2, WM, G32><<<dim3((unsigned)p.half), 256, 0, stream>>>(M, N, K, group, (int)p.full, tn, x, packed, scales, zeros, y, nullptr, epi);
-    return sqp_launch_status();
+    w4a16_prefill_kernel<RT, NT, WM, G32><<<dim3((unsigned)l.tiles, l.parts), 256, 0, stream>>>(
+        M, N, K, group, (int)l.tile0, l.tn, x, packed, scales, zeros, y, l.parts >= 2 ? part : nullptr, epi);
 }
 
 int sqp_gemm_prefill(int M, int N, int K, int group, const h16 *x, const uint32_t *packed,
                      const h16 *scales, const uint8_t *zeros, h16 *y, int epi, const SqpWorkspace &ws, hipStream_t stream)
 {
-    if (group % BK == 0 || (group == 32 && K % BK == 0)) {
-        const TilePlan p = plan_tiles(M, N, K, group, compute_units(), ws.partial != nullptr);
-        if (group == 32) return launch_tiles<1, true>(p, M, N, K, group, x, packed, scales, zeros, y, epi, ws, stream);  // one tile shape only
-        if (p.wm == 1) return launch_tiles<1, false>(p, M, N, K, group, x, packed, scales, zeros, y, epi, ws, stream);
-        return launch_tiles<2, false>(p, M, N, K, group, x, packed, scales, zeros, y, epi, ws, stream);
-    }
     // group sizes the tiled kernel does not cover (neither a multiple of 64, nor 32 with K a multiple of 64)
-    return decode_in_row_blocks(M, N, K, group, x, packed, scales, zeros, y, epi, ws, stream);
+    if (!(group % BK == 0 || (group == 32 && K % BK == 0)))
+        return decode_in_row_blocks(M, N, K, group, x, packed, scales, zeros, y, epi, ws, stream);
+    const LaunchPlan q = plan_launches(M, N, K, group, compute_units(), ws.partial != nullptr);
+    for (int i = 0; i < q.count; i++)
+        if (launch_partial_bytes(q.l[i], q.wm) > (ws.partial ? ws.partial_bytes : 0)) return SQP_ERR_WORKSPACE;
+    for (int i = 0; i < q.count; i++) {
+        const TileLaunch &l = q.l[i];
+#define SQP_TILES(RT, NT, WM, G32) launch_variant<RT, NT, WM, G32>(l, M, N, K, group, x, packed, scales, zeros, y, epi, ws.partial, stream)
+        if (group == 32) {
+            if (l.nt == 4) SQP_TILES(4, 4, 1, true);
+            else SQP_TILES(4, 2, 1, true);
+        } else if (q.wm == 2) {
+            if (l.nt == 4) SQP_TILES(4, 4, 2, false);
+            else SQP_TILES(4, 2, 2, false);
+        } else if (l.nt == 4) {
+            SQP_TILES(4, 4, 1, false);
+        } else {
+            switch (l.rt) {
+                case 3: SQP_TILES(3, 2, 1, false); break;
+                case 5: SQP_TILES(5, 2, 1, false); break;
+                case 6: SQP_TILES(6, 2, 1, false); break;
+                default: SQP_TILES(4, 2, 1, false); break;
+            }
+        }
+#undef SQP_TILES
+        if (l.parts >= 2) {
+            const int bm = 32 * l.rt * q.wm, wgn = l.nt * 128 / q.wm;
+            splitk_reduce_kernel<<<dim3(bm * wgn / 2048, (unsigned)l.tiles), 256, 0, stream>>>(ws.partial, M, N, bm, wgn, (int)l.tile0, l.tn, l.parts, y, epi);
+        }
+    }
+    return sqp_launch_status();
 }

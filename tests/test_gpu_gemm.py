@@ -190,6 +190,60 @@ def test_prefill_k_split(orc, sqp, M, K, N, group, ksplit, shape):
     assert ok, "worst err/tol %.3f, %d elements out of tolerance" % (worst, nbad)
 
 
+@pytest.mark.parametrize("rt,nt,parts", [(3, 2, 1), (3, 2, 4), (4, 2, 2), (4, 4, 1), (5, 2, 1), (5, 2, 3), (6, 2, 1), (6, 2, 5)])
+@pytest.mark.parametrize("M,K,N,group", [
+    (65, 64, 8, 64), (96, 320, 264, 64), (97, 1024, 520, 128), (160, 640, 256, 128), (161, 384, 776, 192),
+    (192, 512, 248, 512), (193, 768, 264, 256), (321, 448, 1032, 64)])
+def test_prefill_tile_heights(orc, sqp, M, K, N, group, rt, nt, parts):
+    """Tiles of 96, 128, 160 and 192 rows with and without K parts, and of 512 columns: one row or column
+    past a tile and one short of it, one stage, parts that start inside a group; plain and with
+    the fused activation; repeated runs are bit-identical."""
+    print("case tile heights", M, K, N, group, rt, nt, parts, flush=True)
+    xs, p, sc, z = _layer(orc, M, K, N, group)
+    L = sqp.lib()
+    L.sqp_debug_set_prefill_variant(rt, nt, parts)
+    try:
+        y0 = _check(orc, sqp, xs, p, sc, z, group)
+        y1 = _check(orc, sqp, xs, p, sc, z, group)
+    finally:
+        L.sqp_debug_set_prefill_variant(0, 0, 0)
+    assert np.array_equal(y0.view(np.uint16), y1.view(np.uint16))
+
+
+def test_prefill_left_over_k_parts(orc, sqp):
+    """A grid of one full round and a few tiles, K long enough that the left-over half-width tiles are
+    split in K too (M = 2050, N = 8144: 17 x 16 = 272 tiles).  Sampled rows against the oracle, from
+    the whole rounds and the left-over tiles; every element against full tiles only, within
+    the fp32 accumulation of both (K 2^-23 of the sum of magnitudes) and one fp16 ulp; the fused
+    activation likewise through its own pair of launches."""
+    import ctypes
+    K, N, M = 2048, 8144, 2050
+    print("case prefill left over", M, K, N, flush=True)
+    out = (ctypes.c_int * 8)()
+    L = sqp.lib()
+    assert L.sqp_debug_prefill_launches(M, N, K, 128, 256, out) == 2 and out[3] == 1 and out[7] >= 2, list(out)
+    xs, p, sc, z = _layer(orc, M, K, N, 128)
+    args = (dev(xs), dev(p), dev(sc), dev(z), 128)
+    rng = np.random.Generator(np.random.PCG64(22))
+    rows = np.unique(np.concatenate([[0, M - 1, 2047, 2048], rng.choice(M, 20, replace=False)]))
+    y_ref, t_ref = orc.w4a16_gemm_ref(np.ascontiguousarray(xs[rows]), p, sc, z, 128)
+    y, h = sqp.w4a16_gemm(*args), sqp.w4a16_gemm_silu_mul(*args)
+    ok, worst, nbad = gemm_tolerance_ok(orc, host(y)[rows], y_ref, t_ref)
+    assert ok, "worst err/tol %.3f, %d elements out of tolerance" % (worst, nbad)
+    L.sqp_debug_set_prefill_tiles(1)
+    try:
+        y1, h1 = sqp.w4a16_gemm(*args), sqp.w4a16_gemm_silu_mul(*args)
+    finally:
+        L.sqp_debug_set_prefill_tiles(0)
+    mags = args[0].float().abs() @ sqp.dequantize(*args[1:4], 128).float().abs()
+    ulp = torch.exp2(torch.floor(torch.log2(y1.float().abs().clamp(min=2.0 ** -14))) - 10)
+    assert bool(((y.float() - y1.float()).abs() <= K * 2.0 ** -23 * mags + ulp).all())
+    e = K * 2.0 ** -23 * torch.maximum(mags[:, 0::2], mags[:, 1::2])      # |SiLU'| <= 1.1, |SiLU(g)| <= |g|
+    g, u = y1[:, 0::2].float().abs() + ulp[:, 0::2], y1[:, 1::2].float().abs() + ulp[:, 1::2]
+    ulp_h = torch.exp2(torch.floor(torch.log2(h1.float().abs().clamp(min=2.0 ** -14))) - 10)
+    assert bool(((h.float() - h1.float()).abs() <= e * (1.1 * u + g + e) + ulp_h).all())
+
+
 def test_cfg4_34b_m256_sampled(orc, sqp):
     """34B-shaped 8192 -> 8192 at M = 256 with the library's own plan (half-width tiles and a
     K split): 24 sampled rows plus the first and last against the oracle."""

@@ -193,6 +193,34 @@ def test_tile_plan_bench_shapes(L):
             L.sqp_debug_set_prefill_shape(0)
 
 
+def test_prefill_launches_invariants(L):
+    """The launches of the tiled path cover every tile once, one-round plans stay within the chip, K
+    parts keep at least eight stages each and their partial sums fit the static array."""
+    out = (ctypes.c_int * 8)()
+    L.sqp_w4a16_gemm_workspace_bytes.restype = ctypes.c_size_t
+    for M in (65, 96, 97, 128, 160, 161, 192, 300, 512, 700, 1024, 2048, 3001, 4096):
+        for (K, N) in [s for m in ("7b", "13b", "34b") for s in wl.MODEL_SHAPES[m]] + [(1024, 264), (256, 8), (8192, 256)]:
+            for group in (64, 128, 32):
+                n = L.sqp_debug_prefill_launches(M, N, K, group, 256, out)
+                v = [tuple(out[4 * i:4 * i + 4]) for i in range(n)]
+                assert n in (1, 2)
+                if n == 1:
+                    rt, nt, tiles, parts = v[0]
+                    assert tiles >= -(-N // (128 * nt)) * -(-M // (32 * rt))
+                    assert parts == 1 or tiles * parts <= 256
+                else:
+                    assert v[0][:2] == (4, 4) and v[1][:2] == (4, 2) and v[0][2] % 256 == 0 and v[0][3] == 1
+                    assert v[0][2] + v[1][2] // 2 == -(-N // 512) * -(-M // 128) and v[1][2] * v[1][3] <= 256
+                for rt, nt, tiles, parts in v:
+                    assert parts >= 1 and (parts == 1 or (nt == 2 and K // 64 // parts >= 8))
+                assert L.sqp_w4a16_gemm_workspace_bytes(M, N, K, group) <= (512 << 10) + (48 << 20)
+    one = lambda M, N, K: (L.sqp_debug_prefill_launches(M, N, K, 128, 256, out), tuple(out[:4]))
+    assert one(160, 10240, 8192) == (1, (5, 2, 40, 6))       # one tile of 160 rows
+    assert one(190, 8192, 8192) == (1, (3, 2, 64, 4))        # two of 96
+    assert one(512, 22016, 4096) == (1, (4, 4, 172, 1))
+    assert L.sqp_debug_prefill_launches(3001, 44032, 8192, 128, 256, out) == 2 and tuple(out[4:8]) == (4, 2, 32, 8)
+
+
 def test_quant_loss_argument_errors(L):
     P = ctypes.c_void_p
     good, odd, null = P(0x1000), P(0x1008), P(0)
