@@ -9,20 +9,16 @@
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// Streaming accesses to the weight, every byte of which is touched once per call: the
-// non-temporal hint lets them pass through the caches (a plain read probe streams 12-15 %
-// faster with it on this chip; measured here: weight abs-max +7 %, weight scaling +4 %; no gain
-// for quantise + pack, and a loss for the much smaller activation tensor, which stay plain).
+// Streaming reads of the weight, every byte of which is touched once per call: the non-temporal
+// hint lets them pass through the caches (a plain read probe streams 12-15 % faster with it on this
+// chip).  Stores go without it: with hinted loads, plain stores are faster (weight scaling on
+// 22016 x 8192 115 -> 105 us, transpose 147 -> 125 us), and so is the activation tensor's pass, which
+// fits the Infinity Cache.
 __device__ __forceinline__ uint4 load_stream(const uint4 *p)
 {
     const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
     return make_uint4(v.x, v.y, v.z, v.w);
 }
-__device__ __forceinline__ void store_stream(uint4 *p, const uint4 &v)
-{
-    __builtin_nontemporal_store(u32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4 *>(p));
-}
-
 namespace {
 
 __device__ __forceinline__ float h2f_lo(uint32_t v) { return (float)__builtin_bit_cast(h16x2, v).x; }
@@ -97,6 +93,7 @@ __global__ void __launch_bounds__(256) absmax_w_kernel(int N, float alpha, const
     const int NO = N >> 3;
     const uint4 *row = w + (size_t)j * NO;
     float m = 0.0f;
+#pragma unroll 4  // four loads in flight per thread: 65 -> 61 us on 22016 x 8192
     for (int o = threadIdx.x; o < NO; o += 256) {
         const uint4 v = load_stream(row + o);
         uint32_t q[4] = {v.x, v.y, v.z, v.w};
@@ -168,7 +165,7 @@ __global__ void __launch_bounds__(256) apply_w_kernel(long total_oct, int NO, co
 {
     long i = (long)blockIdx.x * 256 + threadIdx.x;
     if (i >= total_oct) return;
-    store_stream(out + i, smooth_w8(load_stream(w + i), s[i / NO]));
+    out[i] = smooth_w8(load_stream(w + i), s[i / NO]);
 }
 
 // ------------------------------------------------------------------ Eq. 1
@@ -501,32 +498,45 @@ extern "C" int sqp_smooth_apply_w(int K, int N, const void *w, const float *s, v
 }
 
 // fp16 [N][K] (one row per output feature, the orientation checkpoints store) -> [K][N] (the
-// orientation of Eq. 2 that every other entry point takes).  64 x 64 tile per workgroup through
-// LDS: 16-byte reads along K, 16-byte writes along N; the LDS row stride of 66 halves keeps the
-// 2-byte column reads of a wave on different banks.  grid: (K/64 rounded up, N/64 rounded up).
-__global__ void __launch_bounds__(256) transpose_nk_kernel(int N, int K, const h16 *__restrict__ in, h16 *__restrict__ out)
+// orientation of Eq. 2 that every other entry point takes).  128 x 128 tile per workgroup.  A thread
+// loads an 8 x 8 block (eight pieces of 16 bytes; 16 lanes cover 256 bytes of a row), transposes it
+// in registers (v_perm_b32) and hands its octets over through LDS in pieces of 16 bytes, so that it can
+// store 256 bytes of a row with 16 lanes too.  LDS holds [k][n] with the octets of a row XOR-ed by the
+// k block: 16 lanes touch 16 different octet columns both ways.  Measured on 8192 x 22016: 158 us with
+// 64 x 64 tiles whose halves crossed LDS one by one -> 125 us (5.8 TB/s read and written).
+// Workgroups take the tiles with n fastest: the rows of the result are finished front to back.
+__global__ void __launch_bounds__(256) transpose_nk_kernel(int N, int K, const uint4 *__restrict__ in, uint4 *__restrict__ out)
 {
-    __shared__ h16 tile[64][66];
-    const int k0 = blockIdx.x * 64, n0 = blockIdx.y * 64;
-    const int r = threadIdx.x >> 3, c8 = (threadIdx.x & 7) * 8;
+    __shared__ uint4 tile[128][16];
+    const int hi = threadIdx.x >> 4, lo = threadIdx.x & 15;
+    const int NO = N >> 3, KO = K >> 3;                        // N % 8 == 0, K % 8 == 0: a block is in or out as a whole
+    const int tn = (N + 127) / 128;
+    const int nb = (int)(blockIdx.x % tn) * 16, kb = (int)(blockIdx.x / tn) * 16;  // first octets of the tile
+    uint4 v[8];
+    if (nb + hi < NO && kb + lo < KO) {
 #pragma unroll
-    for (int rr = 0; rr < 64; rr += 32) {
-        const int n = n0 + r + rr, k = k0 + c8;
-        h16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (n < N && k < K) v = *reinterpret_cast<const h16x8 *>(in + (size_t)n * K + k);  // K % 8 == 0
+        for (int i = 0; i < 8; i++) v[i] = load_stream(in + (size_t)((nb + hi) * 8 + i) * KO + kb + lo);
+    } else {
 #pragma unroll
-        for (int i = 0; i < 8; i++) tile[r + rr][c8 + i] = v[i];
+        for (int i = 0; i < 8; i++) v[i] = make_uint4(0, 0, 0, 0);
+    }
+    // v[i] = row n = i, k = 0..7  ->  t[k] = n 0..7 of column k: pairs of rows, then halves of the pairs
+#pragma unroll
+    for (int d = 0; d < 4; d++) {
+        auto word = [&](int i) { return d == 0 ? v[i].x : (d == 1 ? v[i].y : (d == 2 ? v[i].z : v[i].w)); };
+        uint4 even, odd;  // columns k = 2 d and 2 d + 1
+        even.x = __builtin_amdgcn_perm(word(1), word(0), 0x05040100u); odd.x = __builtin_amdgcn_perm(word(1), word(0), 0x07060302u);
+        even.y = __builtin_amdgcn_perm(word(3), word(2), 0x05040100u); odd.y = __builtin_amdgcn_perm(word(3), word(2), 0x07060302u);
+        even.z = __builtin_amdgcn_perm(word(5), word(4), 0x05040100u); odd.z = __builtin_amdgcn_perm(word(5), word(4), 0x07060302u);
+        even.w = __builtin_amdgcn_perm(word(7), word(6), 0x05040100u); odd.w = __builtin_amdgcn_perm(word(7), word(6), 0x07060302u);
+        tile[lo * 8 + 2 * d][hi ^ lo] = even;
+        tile[lo * 8 + 2 * d + 1][hi ^ lo] = odd;
     }
     __syncthreads();
+    // now hi is the k block, lo the n octet
+    if (nb + lo < NO && kb + hi < KO) {
 #pragma unroll
-    for (int rr = 0; rr < 64; rr += 32) {
-        const int k = k0 + r + rr, n = n0 + c8;
-        if (k < K && n < N) {                                                              // N % 8 == 0
-            h16x8 v;
-#pragma unroll
-            for (int i = 0; i < 8; i++) v[i] = tile[c8 + i][r + rr];
-            *reinterpret_cast<h16x8 *>(out + (size_t)k * N + n) = v;
-        }
+        for (int i = 0; i < 8; i++) out[(size_t)((kb + hi) * 8 + i) * NO + nb + lo] = tile[hi * 8 + i][lo ^ hi];
     }
 }
 
@@ -536,7 +546,7 @@ extern "C" int sqp_transpose_nk(int N, int K, const void *w_nk, void *w_kn, void
     if (N <= 0 || K <= 0 || (N % 8) || (K % 8) || sqp_too_big(K, N)) return SQP_ERR_SHAPE;
     if (sqp_misaligned(w_nk) || sqp_misaligned(w_kn)) return SQP_ERR_ALIGN;
     if ((N + 63) / 64 > 65535) return SQP_ERR_SHAPE;
-    transpose_nk_kernel<<<dim3((K + 63) / 64, (N + 63) / 64), 256, 0, (hipStream_t)stream>>>(N, K, (const h16 *)w_nk, (h16 *)w_kn);
+    transpose_nk_kernel<<<(unsigned)((long)((N + 127) / 128) * ((K + 127) / 128)), 256, 0, (hipStream_t)stream>>>(N, K, (const uint4 *)w_nk, (uint4 *)w_kn);
     return sqp_launch_status();
 }
 
@@ -550,7 +560,9 @@ static void launch_quantize_tile(int N, int K, const void *w, uint32_t *packed, 
         // activations: about eight octets per thread
         sm.qrows = rows;
         extra = (int)((sm.x_octs + 8L * THREADS * gx - 1) / (8L * THREADS * gx));
-        if (extra > 65535 - rows) extra = 65535 - rows;
+        if (extra > 65535 - rows) extra = 65535 - rows;  // (a grid row covers any share of them)
+        if (extra == 0)
+            apply_x_kernel<<<(unsigned)((sm.x_octs + 255) / 256), 256, 0, st>>>(sm.x_octs, sm.KO, sm.x, (const float4 *)sm.s, sm.x_hat);
     }
     quantize_pack_tile_kernel<G, SMOOTH><<<dim3(gx, rows + extra), THREADS, 0, st>>>(N, K, (const uint4 *)w, packed, (uint16_t *)scales, zeros, sm);
 }

@@ -112,7 +112,8 @@ def test_dequantize_random_words(orc, sqp):
     assert np.array_equal(what.view(np.uint16), orc.dequantize(p, s, z, g).view(np.uint16))
 
 
-@pytest.mark.parametrize("N,K", [(8, 8), (72, 264), (1000, 520), (4096, 11008), (64, 64)])
+@pytest.mark.parametrize("N,K", [(8, 8), (72, 264), (1000, 520), (4096, 11008), (64, 64),
+                                 (128, 136), (136, 128), (120, 120)])  # one octet past a 128 x 128 tile and short of it
 def test_transpose_nk(sqp, N, K):
     """[N][K] -> [K][N]: an exact copy of every value (compared with numpy's transpose)."""
     rng = np.random.Generator(np.random.PCG64(N * 7 + K))
