@@ -76,7 +76,8 @@ int sqp_smooth_factor(int K, float alpha, const float *amax, float *s, hipStream
 // The factors of n_alpha alphas (host array) at once: factors [n_alpha][K].
 int sqp_smooth_factors(int K, int n_alpha, const float *alphas, const float *amax, float *factors, hipStream_t stream);
 // x_hat = x / s (Eq. 5) and s * w quantised and packed (Eq. 5, Eq. 1), the smoothed weight kept in
-// registers only: the same bits as sqp_smooth_apply_x, sqp_smooth_apply_w and sqp_quantize_pack give.
+// registers only: the same values as sqp_smooth_apply_x, sqp_smooth_apply_w and sqp_quantize_pack
+// give, but every 8 k of x_hat in the order of the unpacked codes (k0, k4, k1, k5, k2, k6, k3, k7).
 int sqp_smooth_quantize(int T, int N, int K, int group, const void *x, const void *w, const float *s, void *x_hat,
                         uint32_t *packed, void *scales, uint8_t *zeros, hipStream_t stream);
 

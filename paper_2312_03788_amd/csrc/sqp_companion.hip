@@ -129,6 +129,13 @@ __global__ void __launch_bounds__(256) smooth_factors_kernel(int K, AlphaBatch a
 
 // ------------------------------------------------------------------ Eq. 5
 
+// (k0 .. k7) -> (k0, k4, k1, k5, k2, k6, k3, k7): the order in which the GEMM kernels unpack a word.
+__device__ __forceinline__ uint4 code_order(const uint4 &v)
+{
+    return make_uint4(__builtin_amdgcn_perm(v.z, v.x, 0x05040100u), __builtin_amdgcn_perm(v.z, v.x, 0x07060302u),
+                      __builtin_amdgcn_perm(v.w, v.y, 0x05040100u), __builtin_amdgcn_perm(v.w, v.y, 0x07060302u));
+}
+
 __device__ __forceinline__ uint4 smooth_x8(const uint4 &v, const float4 &s0, const float4 &s1)
 {
     uint4 r;
@@ -153,12 +160,14 @@ __device__ __forceinline__ uint4 smooth_w8(const uint4 &v, float sj)
     return make_uint4(smooth_w2(v.x, sj), smooth_w2(v.y, sj), smooth_w2(v.z, sj), smooth_w2(v.w, sj));
 }
 
+template <bool CODE_ORDER>
 __global__ void __launch_bounds__(256) apply_x_kernel(long total_oct, int KO, const uint4 *x, const float4 *s, uint4 *out)
 {
     long i = (long)blockIdx.x * 256 + threadIdx.x;
     if (i >= total_oct) return;
     const int ko = (int)(i % KO);
-    out[i] = smooth_x8(x[i], s[2 * ko], s[2 * ko + 1]);
+    const uint4 r = smooth_x8(x[i], s[2 * ko], s[2 * ko + 1]);
+    out[i] = CODE_ORDER ? code_order(r) : r;
 }
 
 __global__ void __launch_bounds__(256) apply_w_kernel(long total_oct, int NO, const uint4 *w, const float *s, uint4 *out)
@@ -249,7 +258,7 @@ quantize_pack_tile_kernel(int N, int K, const uint4 *__restrict__ w, uint32_t *_
             for (long i = ((long)(blockIdx.y - sm.qrows) * gridDim.x + blockIdx.x) * THREADS + threadIdx.x; i < sm.x_octs; i += stride) {
                 const int ko = (int)(i % sm.KO);
                 const float4 *s4 = reinterpret_cast<const float4 *>(sm.s);
-                sm.x_hat[i] = smooth_x8(sm.x[i], s4[2 * ko], s4[2 * ko + 1]);
+                sm.x_hat[i] = code_order(smooth_x8(sm.x[i], s4[2 * ko], s4[2 * ko + 1]));
             }
             return;
         }
@@ -483,7 +492,7 @@ extern "C" int sqp_smooth_apply_x(int M, int K, const void *x, const float *s, v
     if (M <= 0 || K <= 0 || (K % 8) || sqp_too_big(M, K)) return SQP_ERR_SHAPE;
     if (sqp_misaligned(x) || sqp_misaligned(s) || sqp_misaligned(x_out)) return SQP_ERR_ALIGN;
     long total = (long)M * (K / 8);
-    apply_x_kernel<<<(unsigned)((total + 255) / 256), 256, 0, (hipStream_t)stream>>>(total, K / 8, (const uint4 *)x, (const float4 *)s, (uint4 *)x_out);
+    apply_x_kernel<false><<<(unsigned)((total + 255) / 256), 256, 0, (hipStream_t)stream>>>(total, K / 8, (const uint4 *)x, (const float4 *)s, (uint4 *)x_out);
     return sqp_launch_status();
 }
 
@@ -562,7 +571,7 @@ static void launch_quantize_tile(int N, int K, const void *w, uint32_t *packed, 
         extra = (int)((sm.x_octs + 8L * THREADS * gx - 1) / (8L * THREADS * gx));
         if (extra > 65535 - rows) extra = 65535 - rows;  // (a grid row covers any share of them)
         if (extra == 0)
-            apply_x_kernel<<<(unsigned)((sm.x_octs + 255) / 256), 256, 0, st>>>(sm.x_octs, sm.KO, sm.x, (const float4 *)sm.s, sm.x_hat);
+            apply_x_kernel<true><<<(unsigned)((sm.x_octs + 255) / 256), 256, 0, st>>>(sm.x_octs, sm.KO, sm.x, (const float4 *)sm.s, sm.x_hat);
     }
     quantize_pack_tile_kernel<G, SMOOTH><<<dim3(gx, rows + extra), THREADS, 0, st>>>(N, K, (const uint4 *)w, packed, (uint16_t *)scales, zeros, sm);
 }
@@ -581,7 +590,7 @@ static int launch_quantize(int N, int K, int group, const void *w, uint32_t *pac
             quantize_pack_any_kernel<SMOOTH><<<dim3((N / 2 + 255) / 256, K / group), 256, 0, st>>>(
                 N, group, (const uint32_t *)w, (uint2 *)packed, (uint32_t *)scales, (uint16_t *)zeros, sm.s);
             if (SMOOTH)
-                apply_x_kernel<<<(unsigned)((sm.x_octs + 255) / 256), 256, 0, st>>>(sm.x_octs, sm.KO, sm.x, (const float4 *)sm.s, sm.x_hat);
+                apply_x_kernel<true><<<(unsigned)((sm.x_octs + 255) / 256), 256, 0, st>>>(sm.x_octs, sm.KO, sm.x, (const float4 *)sm.s, sm.x_hat);
             break;
     }
     return sqp_launch_status();
@@ -598,7 +607,8 @@ extern "C" int sqp_quantize_pack(int N, int K, int group, const void *w, uint32_
 }
 
 // s * w quantised and x / s, as sqp_smooth_apply_w, sqp_quantize_pack and sqp_smooth_apply_x give
-// them, without the smoothed weight in between.  Arguments are already validated.
+// them, without the smoothed weight in between and with x / s in code order.  Arguments are
+// already validated.
 int sqp_smooth_quantize(int T, int N, int K, int group, const void *x, const void *w, const float *s, void *x_hat,
                         uint32_t *packed, void *scales, uint8_t *zeros, hipStream_t st)
 {

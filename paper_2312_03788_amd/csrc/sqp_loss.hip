@@ -36,7 +36,8 @@ constexpr int LBM = 128, LBN = 128, LBK = 64, LPAD = 8;  // row stride 144 bytes
 //   X_hat W_hat: X_hat by direct global->LDS loads into a ring of three 32 KB slots (rows of
 //     256 bytes, 16-byte pieces XOR-swizzled by row so that a read of 32 rows spreads over the
 //     banks), packed words straight into registers (a word is one lane's B operand), two stages in
-//     flight, one barrier per stage; loads and waits in assembly as in the GEMM kernels.
+//     flight, one barrier per stage; loads and waits in assembly as in the GEMM kernels.  The search
+//     stores X_hat with every 8 k in the order of the unpacked codes (MODE 2): no permute here.
 // Column mapping: accumulator tile t, lane l: column 64 wn + 2 (l % 32) + t (two adjacent columns
 // per lane: 8-byte loads of packed words).
 // MODE: 0 = both halves, partials[block];  1 = X W only, accumulators to yacc;  2 = X_hat W_hat
@@ -220,23 +221,20 @@ loss_split_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, con
             const int grow = m0 + row < M ? m0 + row : M - 1;
             xoff[j] = (uint32_t)grow * (uint32_t)K * 2u + (uint32_t)(((lane & 15) ^ (row & 15)) * 16);
         }
-        auto issue = [&](Stage &st, int slot) {
-#pragma unroll
-            for (int j = 0; j < OX; j++)
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(xq + xoff[j]),
-                                                 (__attribute__((address_space(3))) void *)(lds + slot * SSLOT + (wave + 8 * j) * 1024), 16, 0, 0);
-#pragma unroll
-            for (int ks = 0; ks < 4; ks++) {
-                const unsigned char *base = wq + ks * wrow2;  // wave-uniform
-                asm volatile("global_load_dwordx2 %0, %1, %2" : "=v"(st.w[ks]) : "v"(voff_w), "s"(base) : "memory");
-            }
-#pragma unroll
-            for (int g = 0; g < NQ; g++) {
-                const long row = (long)__builtin_amdgcn_readfirstlane(prow + g) * N;  // wave-uniform
+        // One quarter of a stage's loads (spread over the k-steps of the stage in progress: all at once they
+        // fill the memory pipeline and hold the waves up in front of their arithmetic).
+        auto issue_part = [&](Stage &st, int slot, int part) {
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(xq + xoff[part]),
+                                             (__attribute__((address_space(3))) void *)(lds + slot * SSLOT + (wave + 8 * part) * 1024), 16, 0, 0);
+            const unsigned char *base = wq + part * wrow2;  // wave-uniform
+            asm volatile("global_load_dwordx2 %0, %1, %2" : "=v"(st.w[part]) : "v"(voff_w), "s"(base) : "memory");
+            if (part < NQ) {
+                const long row = (long)__builtin_amdgcn_readfirstlane(prow + part) * N;  // wave-uniform
                 const unsigned char *sg = reinterpret_cast<const unsigned char *>(scales) + row * 2, *zg = zeros + row;
-                asm volatile("global_load_dword %0, %1, %2" : "=v"(st.sc[g]) : "v"(voff_s), "s"(sg) : "memory");
-                asm volatile("global_load_ushort %0, %1, %2" : "=v"(st.zr[g]) : "v"(voff_z), "s"(zg) : "memory");
+                asm volatile("global_load_dword %0, %1, %2" : "=v"(st.sc[part]) : "v"(voff_s), "s"(sg) : "memory");
+                asm volatile("global_load_ushort %0, %1, %2" : "=v"(st.zr[part]) : "v"(voff_z), "s"(zg) : "memory");
             }
+            if (part < 3) return;
             // step to the next stage, unless this was the last
             const bool more = ist + 1 < stages;
             ist += more ? 1 : 0;
@@ -249,6 +247,10 @@ loss_split_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, con
                 if (kin >= hpg) { kin -= hpg; prow++; }
                 if (kin >= hpg) { kin -= hpg; prow++; }
             }
+        };
+        auto issue = [&](Stage &st, int slot) {
+#pragma unroll
+            for (int i = 0; i < 4; i++) issue_part(st, slot, i);
         };
         auto landed = [&](Stage &st) {         // all but the youngest stage's loads have arrived
             asm volatile("s_waitcnt vmcnt(%0)" ::"n"(OX + OW) : "memory");
@@ -263,7 +265,8 @@ loss_split_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, con
         // LDS address of this lane's A fragment (row 64 wm + l32, + 32 for the second row tile) in slot 0
         const uint32_t xrd = (uint32_t)(size_t)lds + (uint32_t)((wm * 64 + l32) * 256);
         const int xkey = l32 & 15;
-        auto compute = [&](const Stage &st, int slot) {
+        // stage st in `slot`, with the loads into stage nst and slot nslot in between
+        auto compute = [&](const Stage &st, int slot, Stage &nst, int nslot) {
             u32x4 xa[2][2];
             auto read_a = [&](int ks) {
                 const uint32_t a = xrd + (uint32_t)(slot * SSLOT) + (uint32_t)(((kh * 8 + ks * 2 + kb) ^ xkey) * 16);
@@ -298,18 +301,20 @@ loss_split_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, con
 #pragma unroll
                 for (int mt = 0; mt < 2; mt++) asm volatile("" : "+v"(xa[ks & 1][mt]));
                 if (ks < 3) read_a(ks + 1);
+                issue_part(nst, nslot, ks);
                 __builtin_amdgcn_sched_barrier(0);
                 if (ks < 3) unpack(ks + 1);
 #pragma unroll
                 for (int mt = 0; mt < 2; mt++) {
-                    const h16x8 a = permute_x(xa[ks & 1][mt]);
+                    // (MODE 2: the search stores X_hat in the order of the unpacked codes)
+                    const h16x8 a = MODE == 2 ? __builtin_bit_cast(h16x8, xa[ks & 1][mt]) : permute_x(xa[ks & 1][mt]);
 #pragma unroll
                     for (int t = 0; t < 2; t++)
                         acc[mt][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b[ks & 1][t], acc[mt][t], 0, 0, 0);
                 }
-                __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);  // first operand: 4 VALU
+                if constexpr (MODE != 2) __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);  // first operand: 4 VALU
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // 1 MFMA
-                __builtin_amdgcn_sched_group_barrier(0x002, 9, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -332,8 +337,8 @@ loss_split_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, con
                 // Stages past the end only keep the load counts in step.
                 landed(st[d]);
                 asm volatile("s_barrier" ::: "memory");
-                issue(st[(d + 2) % D], (d + 2) % D);
-                if (b * D + d < stages) compute(st[d], d);
+                if (b * D + d < stages) compute(st[d], d, st[(d + 2) % D], (d + 2) % D);
+                else issue(st[(d + 2) % D], (d + 2) % D);
             }
         }
         // the look-ahead loads still in flight land in registers and slots that nothing else may use before
@@ -631,6 +636,8 @@ extern "C" int sqp_alpha_search(int T, int N, int K, int group, int n_alpha, con
         }
         sum_partials_kernel<<<n_alpha, 256, 0, st>>>(tile_sums, (long)blocks, loss);
         argmin_kernel<<<1, 64, 0, st>>>(loss, n_alpha, best);
+        // x_hat and w_s as the single calls leave them
+        if (rc == SQP_OK) rc = sqp_smooth_apply_x(T, K, x_cal, s, x_hat, stream);
         if (rc == SQP_OK) rc = sqp_smooth_apply_w(K, N, w, s, w_s, stream);
         return rc != SQP_OK ? rc : sqp_launch_status();
     }
