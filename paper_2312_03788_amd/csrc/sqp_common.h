@@ -69,6 +69,9 @@ int sqp_gemm_entry(int M, int N, int K, int group, const void *x, const uint32_t
 size_t sqp_gemm_decode_partial_bytes(int M, int N, int K, int group);
 size_t sqp_gemm_prefill_partial_bytes(int M, int N, int K, int group);
 
+// Compute units of the current device.
+int sqp_compute_units();
+
 // Eq. 6 in two steps: per-channel maxima amax = [max_t|x_cal[t][j]| (K) | max_n|w[j][n]| (K)],
 // then the factor for one alpha.  Arguments are already validated.
 int sqp_channel_absmax(int T, int K, int N, const void *x_cal, const void *w, float *amax, hipStream_t stream);

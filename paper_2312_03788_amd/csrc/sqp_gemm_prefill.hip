@@ -487,7 +487,9 @@ __global__ void __launch_bounds__(256) splitk_reduce_kernel(const float *__restr
     *reinterpret_cast<h16x8 *>(y + (size_t)m * N + n) = o;
 }
 
-int compute_units()
+}  // namespace
+
+int sqp_compute_units()
 {
     static int cus = 0;  // same on every device of a node
     if (cus == 0) {
@@ -498,8 +500,6 @@ int compute_units()
     }
     return cus;
 }
-
-}  // namespace
 
 // Test/benchmark hooks.  Tiles: 0 = automatic tile choice, 1 = full tiles only, 2 = half tiles
 // only.  K split: -1 = automatic, 0 or 1 = never, k >= 2 = k parts.  Shape: 0 = automatic,
@@ -696,7 +696,7 @@ static size_t launch_partial_bytes(const TileLaunch &l, int wm)
 size_t sqp_gemm_prefill_partial_bytes(int M, int N, int K, int group)
 {
     if (group % BK != 0 && !(group == 32 && K % BK == 0)) return sqp_gemm_decode_partial_bytes(M < 64 ? M : 64, N, K, group);  // row-block fallback
-    const LaunchPlan q = plan_launches(M, N, K, group, compute_units(), true);
+    const LaunchPlan q = plan_launches(M, N, K, group, sqp_compute_units(), true);
     size_t need = 0;
     for (int i = 0; i < q.count; i++) {
         const size_t b = launch_partial_bytes(q.l[i], q.wm);
@@ -719,7 +719,7 @@ int sqp_gemm_prefill(int M, int N, int K, int group, const h16 *x, const uint32_
     // group sizes the tiled kernel does not cover (neither a multiple of 64, nor 32 with K a multiple of 64)
     if (!(group % BK == 0 || (group == 32 && K % BK == 0)))
         return decode_in_row_blocks(M, N, K, group, x, packed, scales, zeros, y, epi, ws, stream);
-    const LaunchPlan q = plan_launches(M, N, K, group, compute_units(), ws.partial != nullptr);
+    const LaunchPlan q = plan_launches(M, N, K, group, sqp_compute_units(), ws.partial != nullptr);
     for (int i = 0; i < q.count; i++)
         if (launch_partial_bytes(q.l[i], q.wm) > (ws.partial ? ws.partial_bytes : 0)) return SQP_ERR_WORKSPACE;
     for (int i = 0; i < q.count; i++) {

@@ -17,6 +17,7 @@
 // partial; a second kernel adds the partials in a fixed order, so the result does not depend on
 // scheduling.
 #include "sqp_common.h"
+#include "sqp_quantize_tile.h"
 #include "sqp_w4_unpack.h"
 
 namespace {
@@ -42,25 +43,56 @@ constexpr int LBM = 128, LBN = 128, LBK = 64, LPAD = 8;  // row stride 144 bytes
 // per lane: 8-byte loads of packed words).
 // MODE: 0 = both halves, partials[block];  1 = X W only, accumulators to yacc;  2 = X_hat W_hat
 // starting from yacc, partials[block].  yacc: [block][wm, wn][register / 4][lane][4] floats.
-// What bounds it: the reads of X_hat from LDS, its way from L2 into LDS and the matrix cores take
-// 0.2 to 0.5 us of a stage's 1.2 us each and overlap only in part (a version without arithmetic takes
-// 0.5 us per stage, one without the unpack 0.95; a fourth ring slot changes nothing).
-// Measured on 512 x 5120 x 5120 (160 tiles): second half 54 us, first half 75 us, both in one call
-// 116 us, where the interleaved kernel takes 176 (8192 x 8192: 185 against 230).  The loss is off its
-// 64-bit value by up to 6e-8 relative, as with the interleaved kernel.
+// What bounds it: the memory pipeline (48 KB per stage and compute unit out of L2), the unpack and the
+// matrix cores take 0.4 to 0.5 us of a stage each and overlap in part: 1.0 us per stage (1.2 with all
+// loads of a stage issued at once).  Reads from LDS and a fourth ring slot change nothing.
+// Measured on 512 x 5120 x 5120 (160 tiles): second half 46 us, first half 75 us, both in one call
+// 114 us, where the interleaved kernel takes 147 (8192 x 8192: 188 against 230).  The loss is off its
+// 64-bit value by up to 7e-8 relative, as with the interleaved kernel.
 constexpr int SBK = 128;                      // k per stage
 constexpr int SSLOT = LBM * SBK * 2;          // bytes of X_hat per stage
 constexpr int SROW = SBK + LPAD;              // halves per LDS row of the X W tiles
 
-template <int MODE, bool G32>
+// PREP (MODE 2; 0 or the group size): the workgroups past row loss_rows of the grid, as many as the loss
+// leaves compute units idle, prepare the next alpha meanwhile: weight tiles smoothed and quantised in
+// turn, activations divided.
+struct NextAlpha {
+    const float *s;            // [K] its smoothing factors
+    const uint4 *x, *w;        // activations, unsmoothed weight
+    uint4 *x_hat;              // what it fills
+    uint32_t *packed;
+    uint16_t *scales;
+    uint8_t *zeros;
+    int loss_rows, workgroups;
+};
+template <int MODE, bool G32, int PREP>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
 loss_split_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, const h16 *__restrict__ w,
                   const h16 *__restrict__ xh, const uint32_t *__restrict__ packed, const h16 *__restrict__ scales,
-                  const uint8_t *__restrict__ zeros, float *__restrict__ yacc, double *__restrict__ partials)
+                  const uint8_t *__restrict__ zeros, float *__restrict__ yacc, double *__restrict__ partials, NextAlpha next)
 {
     constexpr int D = 3;                      // ring slots / register stages of the second half
     __shared__ __attribute__((aligned(1024))) unsigned char lds[D * SSLOT];
     __shared__ double red[8];
+    if constexpr (PREP != 0) {
+        if ((int)blockIdx.y >= next.loss_rows) {
+            typedef QuantizeTile<PREP, 512> Tile;
+            static_assert(sizeof(Tile) <= sizeof(lds), "the quantiser's LDS fits the ring");
+            const int wg = ((int)blockIdx.y - next.loss_rows) * gridDim.x + blockIdx.x;
+            if (wg >= next.workgroups) return;
+            const int tx = (N + 255) / 256, tiles = tx * ((K + 255) / 256);
+            for (int t = wg; t < tiles; t += next.workgroups)
+                quantize_tile<PREP, 512, true>(t % tx, t / tx, N, K, next.w, next.s, next.packed, next.scales, next.zeros,
+                                               *reinterpret_cast<Tile *>(lds));
+            const int KO = K >> 3;
+            const float4 *s4 = reinterpret_cast<const float4 *>(next.s);
+            for (long i = (long)wg * 512 + threadIdx.x; i < (long)M * KO; i += (long)next.workgroups * 512) {
+                const int ko = (int)(i % KO);
+                next.x_hat[i] = code_order(smooth_x8(next.x[i], s4[2 * ko], s4[2 * ko + 1]));
+            }
+            return;
+        }
+    }
     static_assert(2 * 128 * SROW * 2 <= D * SSLOT && 4 * 64 * 64 * 4 <= D * SSLOT, "the tiles of X W and the exchange reuse the ring");
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -385,11 +417,27 @@ void launch_loss_split(int M, int N, int K, int group, const void *x, const void
 {
     const dim3 grid((N + LBN - 1) / LBN, (M + LBM - 1) / LBM);
     if (group == 32)
-        loss_split_kernel<MODE, true><<<grid, 512, 0, st>>>(M, N, K, group, (const h16 *)x, (const h16 *)w, (const h16 *)x_hat, packed,
-                                                            (const h16 *)scales, zeros, yacc, partials);
+        loss_split_kernel<MODE, true, 0><<<grid, 512, 0, st>>>(M, N, K, group, (const h16 *)x, (const h16 *)w, (const h16 *)x_hat, packed,
+                                                               (const h16 *)scales, zeros, yacc, partials, NextAlpha());
     else
-        loss_split_kernel<MODE, false><<<grid, 512, 0, st>>>(M, N, K, group, (const h16 *)x, (const h16 *)w, (const h16 *)x_hat, packed,
-                                                             (const h16 *)scales, zeros, yacc, partials);
+        loss_split_kernel<MODE, false, 0><<<grid, 512, 0, st>>>(M, N, K, group, (const h16 *)x, (const h16 *)w, (const h16 *)x_hat, packed,
+                                                                (const h16 *)scales, zeros, yacc, partials, NextAlpha());
+}
+
+// The second half of one alpha beside the preparation of the next (groups of 32, 64, 128, 256).
+void launch_loss_and_next(int M, int N, int K, int group, const void *x_hat, const uint32_t *packed, const void *scales,
+                          const uint8_t *zeros, float *yacc, double *partials, NextAlpha next, hipStream_t st)
+{
+    const int gx = (N + LBN - 1) / LBN, gy = (M + LBM - 1) / LBM;
+    next.loss_rows = gy;
+    const dim3 grid(gx, gy + (next.workgroups + gx - 1) / gx);
+#define SQP_LOSS_NEXT(G32, G) \
+    loss_split_kernel<2, G32, G><<<grid, 512, 0, st>>>(M, N, K, group, nullptr, nullptr, (const h16 *)x_hat, packed, (const h16 *)scales, zeros, yacc, partials, next)
+    if (group == 32) SQP_LOSS_NEXT(true, 32);
+    else if (group == 64) SQP_LOSS_NEXT(false, 64);
+    else if (group == 128) SQP_LOSS_NEXT(false, 128);
+    else SQP_LOSS_NEXT(false, 256);
+#undef SQP_LOSS_NEXT
 }
 
 // ---------------------------------------------------------------- both products interleaved
@@ -619,7 +667,7 @@ extern "C" int sqp_alpha_search(int T, int N, int K, int group, int n_alpha, con
     // smooths the weight as it reads it, and w_s gets the last alpha's smoothed weight at the end.
     // Taken wherever they fit there, i.e. from about K = 2 T on (4 bytes per element of the padded
     // [T][N] against 2 per element of [K][N]); shorter K runs the single calls in turn.
-    // Measured, 21 alphas on 512 x 5120 x 5120: 4.71 -> 1.81 ms.
+    // Measured, 21 alphas on 512 x 5120 x 5120: 4.71 -> 1.26 ms.
     const size_t blocks = (size_t)((T + LBM - 1) / LBM) * ((N + LBN - 1) / LBN);
     const size_t ybytes = blocks * LBM * LBN * sizeof(float), fbytes = (size_t)n_alpha * K * sizeof(float);
     if (loss_split_covers(K, group) && ybytes + fbytes + n_alpha * blocks * sizeof(double) <= (size_t)K * N * sizeof(h16)) {
@@ -629,10 +677,35 @@ extern "C" int sqp_alpha_search(int T, int N, int K, int group, int n_alpha, con
         if (rc == SQP_OK) rc = sqp_smooth_factor(K, alphas[n_alpha - 1], amax, s, st);
         if (rc != SQP_OK) return rc;
         launch_loss_split<1>(T, N, K, group, x_cal, w, nullptr, nullptr, nullptr, nullptr, yacc, nullptr, st);
+        // Where the loss tiles leave at least a quarter of the chip idle (160 of 256 on 512 x 5120), the next
+        // alpha is prepared there meanwhile, into a second set of buffers behind the tile sums; the last
+        // alpha uses the caller's set.  Per alpha on 512 x 5120 x 5120: 69 us one after the other, 56 beside.
+        const int idle = sqp_compute_units() - (int)(blocks < 65536 ? blocks : 65536);
+        auto up256 = [](size_t v) { return (v + 255) & ~(size_t)255; };
+        const size_t rows = (size_t)(K / group);
+        const size_t at_packed = up256(ybytes + fbytes + n_alpha * blocks * sizeof(double));
+        const size_t at_scales = up256(at_packed + (size_t)K / 8 * N * 4), at_zeros = up256(at_scales + rows * N * 2);
+        const size_t at_x = up256(at_zeros + rows * N), end = at_x + (size_t)T * K * sizeof(h16);
+        const bool beside = 4 * idle >= sqp_compute_units() && (group == 32 || group == 64 || group == 128 || group == 256) &&
+                            end <= (size_t)K * N * sizeof(h16);
+        unsigned char *const base = (unsigned char *)w_s;
+        struct {
+            void *x_hat;
+            uint32_t *packed;
+            void *scales;
+            uint8_t *zeros;
+        } set[2] = {{x_hat, packed, scales, zeros}, {base + at_x, (uint32_t *)(base + at_packed), base + at_scales, base + at_zeros}};
         for (int i = 0; i < n_alpha && rc == SQP_OK; i++) {
-            const float *f = factors + (size_t)i * K;
-            rc = sqp_smooth_quantize(T, N, K, group, x_cal, w, f, x_hat, packed, scales, zeros, st);
-            launch_loss_split<2>(T, N, K, group, nullptr, nullptr, x_hat, packed, scales, zeros, yacc, tile_sums + i * blocks, st);
+            const auto &cur = set[beside ? (n_alpha - 1 - i) & 1 : 0], &nxt = set[beside ? (n_alpha - i) & 1 : 0];
+            if (!beside || i == 0)
+                rc = sqp_smooth_quantize(T, N, K, group, x_cal, w, factors + (size_t)i * K, cur.x_hat, cur.packed, cur.scales, cur.zeros, st);
+            if (beside && i + 1 < n_alpha) {
+                const NextAlpha next = {factors + (size_t)(i + 1) * K, (const uint4 *)x_cal, (const uint4 *)w, (uint4 *)nxt.x_hat,
+                                        nxt.packed, (uint16_t *)nxt.scales, nxt.zeros, 0, idle};
+                launch_loss_and_next(T, N, K, group, cur.x_hat, cur.packed, cur.scales, cur.zeros, yacc, tile_sums + i * blocks, next, st);
+            } else {
+                launch_loss_split<2>(T, N, K, group, nullptr, nullptr, cur.x_hat, cur.packed, cur.scales, cur.zeros, yacc, tile_sums + i * blocks, st);
+            }
         }
         sum_partials_kernel<<<n_alpha, 256, 0, st>>>(tile_sums, (long)blocks, loss);
         argmin_kernel<<<1, 64, 0, st>>>(loss, n_alpha, best);

@@ -121,23 +121,24 @@ def test_alpha_search_equals_single_calls(orc, sqp):
     assert L.sqp_alpha_search(T, N, K, g, 2, ok_alpha, *([good] * 11), None, None) == -1
 
 
-@pytest.mark.parametrize("T,K,N,group", [
-    (40, 640, 128, 128),    # the product with the unsmoothed weight kept in w_s; one tile, five stages
-    (129, 1408, 200, 64),   # two tiles of rows, the second with one row; ragged columns
-    (64, 1024, 256, 256),   # groups of two stages
-    (1, 768, 136, 384),     # a group size whose quantise kernel reads twice
-    (200, 1152, 328, 32),   # two groups per half stage
-    (130, 384, 136, 32),    # K too short for w_s to hold the product: single calls in turn
-    (70, 192, 72, 64)])     # K not a multiple of 128: the interleaved loss kernel
-def test_alpha_search_routes_equal_single_calls(sqp, T, K, N, group):
+@pytest.mark.parametrize("T,K,N,group,n", [
+    (40, 640, 128, 128, 3),    # the product with the unsmoothed weight kept in w_s; one tile, five stages
+    (129, 1408, 200, 64, 3),   # two tiles of rows, the second with one row; ragged columns
+    (64, 1024, 256, 256, 3),   # groups of two stages; the next alpha prepared beside the loss
+    (30, 2048, 200, 64, 3), (20, 1408, 264, 128, 2), (17, 2048, 136, 32, 3), (20, 1408, 264, 128, 1), (33, 2304, 520, 128, 4),  # likewise
+    (1, 768, 136, 384, 3),     # a group size whose quantise kernel reads twice
+    (200, 1152, 328, 32, 3),   # two groups per half stage
+    (130, 384, 136, 32, 3),    # K too short for w_s to hold the product: single calls in turn
+    (70, 192, 72, 64, 3)])     # K not a multiple of 128: the interleaved loss kernel
+def test_alpha_search_routes_equal_single_calls(sqp, T, K, N, group, n):
     """Every route of the search gives the losses of the single calls bit for bit, and leaves the
     last alpha's factors, activations, weight and codes in its work buffers."""
     import ctypes
     print("case search", T, K, N, group, flush=True)
     _, _, w = wl.layer_inputs(1, K, N)
     dx, dw = dev(wl.activation(T, K, seed=3000)), dev(w)
-    alphas = [0.5, 0.0, 0.35]
-    L, n = sqp.lib(), len(alphas)
+    alphas = [0.5, 0.0, 0.35, 0.9][:n]
+    L = sqp.lib()
     new = lambda shape, dt: torch.empty(shape, dtype=dt, device="cuda")
     amax, s, xh, ws = new(2 * K, torch.float32), new(K, torch.float32), torch.empty_like(dx), torch.empty_like(dw)
     p, sc, z = new((K // 8, N), torch.int32), new((K // group, N), torch.float16), new((K // group, N), torch.uint8)
