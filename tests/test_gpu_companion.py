@@ -23,7 +23,9 @@ def _ulp_diff_f32(a, b):
 
 
 @pytest.mark.parametrize("T,K,N,alpha", [(512, 1024, 1024, 0.5), (37, 264, 72, 0.25), (3, 8, 8, 0.0),
-                                         (100, 2048, 520, 1.0), (512, 4096, 4096, 0.85)])
+                                         (100, 2048, 520, 1.0), (512, 4096, 4096, 0.85),
+                                         # rows and columns around the direct kernel's 64 x 64 workgroups, and past its rows
+                                         (63, 72, 8, 0.5), (65, 128, 16, 0.5), (1024, 136, 8, 0.5), (1025, 136, 8, 0.5)])
 def test_smooth_scales(orc, sqp, T, K, N, alpha):
     print("case smooth_scales", T, K, N, alpha, flush=True)
     xcal = wl.activation(T, K, seed=3000)
