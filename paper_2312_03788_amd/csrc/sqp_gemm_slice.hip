@@ -25,19 +25,18 @@
 
 namespace {
 
-// WV: waves per workgroup.  D: stages (registers for the weight side, LDS slots for the
-// activations) per wave; D - 1 chunks are in flight per wave while one is consumed.
+// WV: waves per workgroup.  Each wave has two stages (registers for the weight side, LDS slots for the
+// activations): one chunk is in flight while one is consumed.  (Three and four stages are 5 to 20 %
+// slower at one and eight rows, and so are 12 and 16 waves.)
 // XB: blocks of four activation rows that are fetched (M <= 4 XB); the other rows of the
 // 16-row matrix operand are whatever the LDS holds, and only feed output rows that are never stored.
-template <int TB, int WV, int D, int XB>
+template <int TB, int WV, int XB>
 __global__ void __launch_bounds__(WV * 64)
 w4a16_decode_slice_kernel(int M, int N, int K, const h16 *__restrict__ x, const uint32_t *__restrict__ packed,
                           const h16 *__restrict__ scales, const uint8_t *__restrict__ zeros, h16 *__restrict__ y, int epi)
 {
-    constexpr int P = D - 1;
+    constexpr int D = 2;
     constexpr int XSTAGE = XB * 1024;  // one chunk of x: 4 XB rows of 256 bytes, as 1 KB blocks of four rows
-    constexpr int LOADS = XB + 4 + 2;  // per chunk and wave: activations, weights, steps and zero points
-    static_assert((P - 1) * LOADS < 64, "vmcnt field");
     static_assert(TB == 2 || TB == 4, "column blocks of 16 per workgroup");
     constexpr int RING = WV * D * XSTAGE, EXCH = WV * TB * 1024;  // the exchange of sums at the end reuses the rings
     __shared__ __attribute__((aligned(1024))) unsigned char xring[RING > EXCH ? RING : EXCH];
@@ -76,54 +75,38 @@ w4a16_decode_slice_kernel(int M, int N, int K, const h16 *__restrict__ x, const 
     const unsigned char *sq = reinterpret_cast<const unsigned char *>(scales) + (long)c0 * N * 2;
     const unsigned char *zq = zeros + (long)c0 * N;
     const unsigned char *xq = reinterpret_cast<const unsigned char *>(x) + (long)c0 * 256;
-    int issued = 0;  // issue calls so far; the pointers are at own chunk min(issued, nmine - 1)
 
     // Weight-side loads, in assembly so that this kernel decides when to wait for them (a stage
     // must not be read before `landed`).  They carry the non-temporal hint (every weight byte
-    // is read once per launch).  `live` (wave-uniform) is false for the look-ahead past the
-    // wave's last chunk: those loads are issued under an empty execution mask, fetch nothing and
-    // write no register, but keep their place in the in-order load queue, so the wait counts
-    // are the same in every iteration.  Mask change, loads and restore are one statement.
-    auto issue_w = [&](Stage &s, bool live) {
+    // is read once per launch).
+    auto issue_w = [&](Stage &s) {
         const unsigned char *b0 = wq, *b1 = wq + wstep1, *b2 = wq + 2 * wstep1, *b3 = wq + 3 * wstep1;
-        const uint32_t m = __builtin_amdgcn_readfirstlane(live ? 0xffffffffu : 0u);
-        uint64_t saved;
         if constexpr (TB == 2) {
-            asm volatile("s_mov_b64 %[sv], exec\n\t"
-                         "s_and_b32 exec_lo, exec_lo, %[m]\n\t"
-                         "s_and_b32 exec_hi, exec_hi, %[m]\n\t"
-                         "global_load_dwordx2 %[w0], %[vw], %[b0] nt\n\t"
+            asm volatile("global_load_dwordx2 %[w0], %[vw], %[b0] nt\n\t"
                          "global_load_dwordx2 %[w1], %[vw], %[b1] nt\n\t"
                          "global_load_dwordx2 %[w2], %[vw], %[b2] nt\n\t"
                          "global_load_dwordx2 %[w3], %[vw], %[b3] nt\n\t"
                          "global_load_dword %[sc], %[vs], %[sq] nt\n\t"
-                         "global_load_ushort %[zr], %[vz], %[zq] nt\n\t"
-                         "s_mov_b64 exec, %[sv]"
-                         : [w0] "=&v"(s.w[0]), [w1] "=&v"(s.w[1]), [w2] "=&v"(s.w[2]), [w3] "=&v"(s.w[3]), [sc] "=&v"(s.sc),
-                           [zr] "=&v"(s.zr), [sv] "=&s"(saved)
-                         : [m] "s"(m), [vw] "v"(voff_w), [vs] "v"(voff_s), [vz] "v"(voff_z), [b0] "s"(b0), [b1] "s"(b1),
-                           [b2] "s"(b2), [b3] "s"(b3), [sq] "s"(sq), [zq] "s"(zq)
-                         : "memory", "scc");  // s_and_b32 writes SCC
+                         "global_load_ushort %[zr], %[vz], %[zq] nt"
+                         : [w0] "=&v"(s.w[0]), [w1] "=&v"(s.w[1]), [w2] "=&v"(s.w[2]), [w3] "=&v"(s.w[3]), [sc] "=&v"(s.sc), [zr] "=&v"(s.zr)
+                         : [vw] "v"(voff_w), [vs] "v"(voff_s), [vz] "v"(voff_z), [b0] "s"(b0), [b1] "s"(b1), [b2] "s"(b2), [b3] "s"(b3),
+                           [sq] "s"(sq), [zq] "s"(zq)
+                         : "memory");
         } else {
-            asm volatile("s_mov_b64 %[sv], exec\n\t"
-                         "s_and_b32 exec_lo, exec_lo, %[m]\n\t"
-                         "s_and_b32 exec_hi, exec_hi, %[m]\n\t"
-                         "global_load_dwordx4 %[w0], %[vw], %[b0] nt\n\t"
+            asm volatile("global_load_dwordx4 %[w0], %[vw], %[b0] nt\n\t"
                          "global_load_dwordx4 %[w1], %[vw], %[b1] nt\n\t"
                          "global_load_dwordx4 %[w2], %[vw], %[b2] nt\n\t"
                          "global_load_dwordx4 %[w3], %[vw], %[b3] nt\n\t"
                          "global_load_dwordx2 %[sc], %[vs], %[sq] nt\n\t"
-                         "global_load_dword %[zr], %[vz], %[zq] nt\n\t"
-                         "s_mov_b64 exec, %[sv]"
-                         : [w0] "=&v"(s.w[0]), [w1] "=&v"(s.w[1]), [w2] "=&v"(s.w[2]), [w3] "=&v"(s.w[3]), [sc] "=&v"(s.sc),
-                           [zr] "=&v"(s.zr), [sv] "=&s"(saved)
-                         : [m] "s"(m), [vw] "v"(voff_w), [vs] "v"(voff_s), [vz] "v"(voff_z), [b0] "s"(b0), [b1] "s"(b1),
-                           [b2] "s"(b2), [b3] "s"(b3), [sq] "s"(sq), [zq] "s"(zq)
-                         : "memory", "scc");  // s_and_b32 writes SCC
+                         "global_load_dword %[zr], %[vz], %[zq] nt"
+                         : [w0] "=&v"(s.w[0]), [w1] "=&v"(s.w[1]), [w2] "=&v"(s.w[2]), [w3] "=&v"(s.w[3]), [sc] "=&v"(s.sc), [zr] "=&v"(s.zr)
+                         : [vw] "v"(voff_w), [vs] "v"(voff_s), [vz] "v"(voff_z), [b0] "s"(b0), [b1] "s"(b1), [b2] "s"(b2), [b3] "s"(b3),
+                           [sq] "s"(sq), [zq] "s"(zq)
+                         : "memory");
         }
     };
     auto landed = [&](Stage &s) {
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((P - 1) * LOADS) : "memory");
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // one chunk is in flight at a time
 #pragma unroll
         for (int ks = 0; ks < 4; ks++) asm volatile("" : "+v"(s.w[ks]));
         asm volatile("" : "+v"(s.sc));
@@ -135,7 +118,7 @@ w4a16_decode_slice_kernel(int M, int N, int K, const h16 *__restrict__ x, const 
     // (i % 16) ^ (row % 16) of that row, so that a row's pieces (whole 128-byte lines) come from
     // adjacent lanes, while in LDS (where the hardware puts lane i at byte 16 i of the block)
     // the pieces the 16 rows need for one k-step fall into 16 different bank groups.  Rows past
-    // M re-read row M - 1.  Past the wave's last chunk the loads re-read that chunk (cache hits).
+    // M re-read row M - 1.
     unsigned char *const ring = xring + wv * (D * XSTAGE);
     uint32_t xoff[XB];
 #pragma unroll
@@ -156,12 +139,10 @@ w4a16_decode_slice_kernel(int M, int N, int K, const h16 *__restrict__ x, const 
     const uint32_t xrd = (uint32_t)(size_t)ring + (uint32_t)((lr >> 2) * 1024 + (lr & 3) * 256);
 
     auto advance = [&]() {
-        issued++;
-        const bool more = issued < nmine;
-        wq += more ? (long)WV * 4 * wstep1 : 0;
-        sq += more ? (long)WV * N * 2 : 0;
-        zq += more ? (long)WV * N : 0;
-        xq += more ? WV * 256 : 0;
+        wq += (long)WV * 4 * wstep1;
+        sq += (long)WV * N * 2;
+        zq += (long)WV * N;
+        xq += WV * 256;
     };
 
     auto compute = [&](const Stage &s, int slot) {
@@ -207,38 +188,27 @@ w4a16_decode_slice_kernel(int M, int N, int K, const h16 *__restrict__ x, const 
             for (int r = 0; r < 4; r++) acc[b][r] = fmaf(delta[b], accg[b][r], acc[b][r]);
     };
 
-    // Software pipeline over the wave's own chunks, P ahead; the chunk count is padded to a
-    // multiple of D (stage and slot indices are static), padded iterations only keep the load
-    // counts in step.  Slot (i + P) % D, filled in iteration i, was consumed in iteration i - 1
-    // by this same wave (its LDS reads have been waited for), so no barrier is needed.
-    Stage st[D];
-#pragma unroll
-    for (int j = 0; j < P; j++) {
-        issue_x(j);
-        issue_w(st[j], j < nmine);
+    // Software pipeline over the wave's own chunks: the next one is in flight while one is consumed.
+    // Slot and stage of chunk i + 1 were consumed in iteration i - 1 by this same wave (its LDS
+    // reads have been waited for), so no barrier is needed.  Nothing is issued past the last chunk
+    // (wave-uniform branches): look-ahead loads that fetched its activations again cost the wait for
+    // them at the end (1 to 4 % per launch).
+    Stage st[2];
+    auto issue = [&](int d) {
+        issue_x(d);
+        issue_w(st[d]);
         advance();
-    }
-    const int nblk = (nmine + D - 1) / D;
-    for (int blk = 0; blk < nblk; blk++) {
-#pragma unroll
-        for (int d = 0; d < D; d++) {
-            const int i = blk * D + d;
-            landed(st[d]);
-            issue_x((d + P) % D);
-            issue_w(st[(d + P) % D], i + P < nmine);
-            advance();
-            if (i < nmine) compute(st[d], d);
+    };
+    if (nmine > 0) issue(0);
+    for (int i = 0; i < nmine; i += 2) {
+        landed(st[0]);
+        if (i + 1 < nmine) issue(1);
+        compute(st[0], 0);
+        if (i + 1 < nmine) {
+            landed(st[1]);
+            if (i + 2 < nmine) issue(0);
+            compute(st[1], 1);
         }
-    }
-    // Look-ahead loads may still be in flight: wait for them with every stage still allocated,
-    // so that nothing else lives in those registers (or is read from LDS) while they land.
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-#pragma unroll
-    for (int j = 0; j < D; j++) {
-#pragma unroll
-        for (int ks = 0; ks < 4; ks++) asm volatile("" ::"v"(st[j].w[ks]));
-        asm volatile("" ::"v"(st[j].sc));
-        asm volatile("" ::"v"(st[j].zr));
     }
 
     // ---- the waves add their sums through LDS (the rings are idle once every wave is here), in
@@ -300,7 +270,7 @@ int sqp_gemm_slice(int variant, int M, int N, int K, const h16 *x, const uint32_
                    const uint8_t *zeros, h16 *y, int epi, hipStream_t stream)
 {
 #define SQP_SLICE_LAUNCH(TB, XB) \
-    w4a16_decode_slice_kernel<TB, 8, 2, XB><<<(N + 16 * TB - 1) / (16 * TB), 8 * 64, 0, stream>>>(M, N, K, x, packed, scales, zeros, y, epi)
+    w4a16_decode_slice_kernel<TB, 8, XB><<<(N + 16 * TB - 1) / (16 * TB), 8 * 64, 0, stream>>>(M, N, K, x, packed, scales, zeros, y, epi)
     const int xb = (M + 3) / 4;  // blocks of four rows that hold real rows
     if (variant == 0) {
         if (xb == 1) SQP_SLICE_LAUNCH(2, 1);
