@@ -124,8 +124,9 @@ int sqp_dequantize(int N, int K, int group, const uint32_t *packed, const void *
  * sqp_w4a16_gemm_workspace_bytes() is 0 for those shapes):
  *   - no workspace set: the plan without a split runs (same result within the tolerance of
  *     Eq. 3's fp32 accumulation, slower on narrow layers);
- *   - workspace smaller than sqp_w4a16_gemm_workspace_bytes() of the shape:
- *     SQP_ERR_WORKSPACE, nothing enqueued.
+ *   - workspace smaller than sqp_w4a16_gemm_workspace_bytes() of the shape: a plan that fits
+ *     it runs, down to sqp_w4a16_gemm_workspace_least_bytes(); below that SQP_ERR_WORKSPACE,
+ *     nothing enqueued.
  * Calls that use the workspace must not overlap on the device (order them on one stream, or
  * with events): they share its tickets and partial sums. */
 int sqp_w4a16_gemm(int M, int N, int K, int group, const void *x, const uint32_t *packed,
@@ -135,6 +136,10 @@ int sqp_w4a16_gemm(int M, int N, int K, int group, const void *x, const uint32_t
  * this shape on the current device: 0 if the plan does not split the inner dimension,
  * otherwise 512 KB of tickets plus the fp32 partial sums.  Host arithmetic only. */
 size_t sqp_w4a16_gemm_workspace_bytes(int M, int N, int K, int group);
+
+/* The smallest workspace with which a call of this shape is not refused (at most the bytes above;
+ * the two differ where the preferred plan splits more than it has to).  Host arithmetic only. */
+size_t sqp_w4a16_gemm_workspace_least_bytes(int M, int N, int K, int group);
 
 /* Hands the library a caller-owned device buffer for the partial sums of Eq. 3's split
  * launches on the CURRENT device (process-wide, one per device; the library keeps only the

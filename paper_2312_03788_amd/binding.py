@@ -56,6 +56,8 @@ def lib():
         L.sqp_alpha_search.argtypes = [i, i, i, i, i, ctypes.POINTER(ctypes.c_float)] + [vp] * 13
         L.sqp_w4a16_gemm_workspace_bytes.argtypes = [i, i, i, i]
         L.sqp_w4a16_gemm_workspace_bytes.restype = ctypes.c_size_t
+        L.sqp_w4a16_gemm_workspace_least_bytes.argtypes = [i, i, i, i]
+        L.sqp_w4a16_gemm_workspace_least_bytes.restype = ctypes.c_size_t
         for name in EXPORTS[1:]:
             getattr(L, name).restype = ctypes.c_int
         L.sqp_quant_loss_scratch_doubles.restype = ctypes.c_long
@@ -137,13 +139,16 @@ def _ensure_workspace(M, N, K, group, device):
     """Device-memory plumbing for the GEMM calls: make sure the workspace set on the tensor's
     device covers this shape's plan (grown with some slack so that a sweep over shapes
     settles after a few calls).  Callers that must not allocate (graph capture) call
-    set_workspace themselves beforehand."""
+    set_workspace themselves beforehand; during a capture the buffer only grows where the call
+    would be refused otherwise."""
     need = workspace_bytes(M, N, K, group)
     if need == 0:
         return
     held = _workspaces.get(device.index)
     have = held[-1].numel() if held and held[-1] is not None else 0
     if need > have:
+        if torch.cuda.is_current_stream_capturing() and have >= int(lib().sqp_w4a16_gemm_workspace_least_bytes(M, N, K, group)):
+            return
         set_workspace(max(need, 2 * have, 16 << 20), device)
 
 

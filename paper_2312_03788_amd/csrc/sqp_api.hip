@@ -174,6 +174,13 @@ extern "C" size_t sqp_w4a16_gemm_workspace_bytes(int M, int N, int K, int group)
     return partial ? SQP_WS_TICKET_BYTES + partial : 0;
 }
 
+extern "C" size_t sqp_w4a16_gemm_workspace_least_bytes(int M, int N, int K, int group)
+{
+    if (M <= 0 || sqp_check_quant_shape(N, K, group) != SQP_OK || sqp_too_big(M, K) || sqp_too_big(M, N)) return 0;
+    const size_t partial = streaming_path(M) ? sqp_gemm_decode_least_bytes(M, N, K, group) : sqp_gemm_prefill_least_bytes(M, N, K, group);
+    return partial ? SQP_WS_TICKET_BYTES + partial : 0;
+}
+
 // Shared by every GEMM entry point: argument checks, then the weight-streaming path (small M)
 // or the tiled matrix-core path.
 int sqp_gemm_entry(int M, int N, int K, int group, const void *x, const uint32_t *packed, const void *scales,

@@ -52,8 +52,8 @@ int sqp_zero_tickets(unsigned *tickets, hipStream_t stream);
 // Decode (weight-streaming) and prefill (tiled matrix-core) back ends of sqp_w4a16_gemm.
 // Arguments are already validated.
 // epi: 0 = y [M][N] fp16; 1 = SiLU(gate) * up of interleaved (gate, up) column pairs, y [M][N/2].
-// A plan that splits K needs ws; without one (partial == nullptr) the non-split plan runs;
-// with one that is too small the call fails with SQP_ERR_WORKSPACE and enqueues nothing.
+// A plan that splits K needs ws; without one (partial == nullptr) the non-split plan runs; with one below
+// the least size (see below) the call fails with SQP_ERR_WORKSPACE and enqueues nothing.
 int sqp_gemm_decode(int M, int N, int K, int group, const h16 *x, const uint32_t *packed,
                     const h16 *scales, const uint8_t *zeros, h16 *y, int epi, const SqpWorkspace &ws, hipStream_t stream);
 int sqp_gemm_prefill(int M, int N, int K, int group, const h16 *x, const uint32_t *packed,
@@ -68,6 +68,9 @@ int sqp_gemm_entry(int M, int N, int K, int group, const void *x, const uint32_t
 // Bytes of partial sums the preferred plan of a shape needs (0: it does not split K).
 size_t sqp_gemm_decode_partial_bytes(int M, int N, int K, int group);
 size_t sqp_gemm_prefill_partial_bytes(int M, int N, int K, int group);
+// Bytes below which a call with a workspace is refused; between the two a plan that fits runs.
+size_t sqp_gemm_decode_least_bytes(int M, int N, int K, int group);
+size_t sqp_gemm_prefill_least_bytes(int M, int N, int K, int group);
 
 // Compute units of the current device.
 int sqp_compute_units();

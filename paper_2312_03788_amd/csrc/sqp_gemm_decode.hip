@@ -245,19 +245,36 @@ extern "C" void sqp_debug_decode_launch(int M, int N, int K, int group, int *nw,
     *kp = p.kp;
 }
 
+// Bytes of partial tiles a plan leaves (kspg: k-steps per chunk, mt: 16-row tiles of the kernel).
+static size_t plan_bytes(const Plan &p, int N, int K, int group, int kspg, int mt)
+{
+    const bool one_group = kspg < 4 || group % 128 == 0;  // one and eight strips (test hooks) exist there only
+    int nw = p.nw;
+    if (nw != 2 && !(nw == 1 && one_group) && !(nw == 8 && one_group && mt < 3)) nw = 4;
+    size_t bytes = 0;
+    sqp_strip_split(mt, nw, kspg, N, K, p.split, &bytes);
+    return bytes;
+}
+
 size_t sqp_gemm_decode_partial_bytes(int M, int N, int K, int group)
 {
     const int kspg = chunk_ksteps(K, group);
     if (kspg == 0) return 0;  // generic kernel
     if (slice_variant(M, N, K, group) >= 0) return 0;
-    const Plan p = plan_for(M, N, K, group, true);
-    const int mt = sqp_strip_row_tiles(M);
-    int nw = p.nw;
-    const bool one_group = kspg < 4 || group % 128 == 0;  // one and eight strips (test hooks) exist there only
-    if (nw != 2 && !(nw == 1 && one_group) && !(nw == 8 && one_group && mt < 3)) nw = 4;
-    size_t bytes = 0;
-    sqp_strip_split(mt, nw, kspg, N, K, p.split, &bytes);
-    return bytes;
+    return plan_bytes(plan_for(M, N, K, group, true), N, K, group, kspg, sqp_strip_row_tiles(M));
+}
+
+// What a workspace has to hold at least for a call not to be refused: the partial tiles of the plan
+// by strips (one group per chunk, row tiles in steps of 16, 32 and 64), where wide_plan asks for more.
+// Callers with a buffer of that size are served with fewer K parts.
+size_t sqp_gemm_decode_least_bytes(int M, int N, int K, int group)
+{
+    const size_t want = sqp_gemm_decode_partial_bytes(M, N, K, group);
+    if (want == 0 || g_force_plan.nw > 0 || g_force_split > 0) return want;
+    const int kspg = group == 32 ? 1 : (group == 64 ? 2 : 4);
+    const size_t strips = plan_bytes(make_plan(M, N, K, kspg == 4 ? 128 : group, M <= 16 && group == 128), N, K, group, kspg,
+                                     M <= 16 ? 1 : (M <= 32 ? 2 : 4));
+    return strips < want ? strips : want;
 }
 
 int sqp_gemm_decode(int M, int N, int K, int group, const h16 *x, const uint32_t *packed, const h16 *scales,
@@ -270,7 +287,9 @@ int sqp_gemm_decode(int M, int N, int K, int group, const h16 *x, const uint32_t
         if (epi != 0) return SQP_ERR_SHAPE;  // the fused activation needs a group size the matrix-core kernels cover
         return sqp_gemm_generic(M, N, K, group, x, packed, scales, zeros, y, stream);
     }
-    const Plan p = plan_for(M, N, K, group, ws.partial != nullptr);
+    Plan p = plan_for(M, N, K, group, ws.partial != nullptr);
+    if (ws.partial != nullptr && ws.partial_bytes >= sqp_gemm_decode_least_bytes(M, N, K, group))
+        while (p.split > 1 && plan_bytes(p, N, K, group, kspg, sqp_strip_row_tiles(M)) > ws.partial_bytes) p.split--;
     if (kspg < 4) return sqp_strip_one_group(group, p, M, N, K, 1, x, packed, scales, zeros, y, epi, ws, stream);
     if (group == 32) return sqp_strip_g32(p, M, N, K, 1, x, packed, scales, zeros, y, epi, ws, stream);
     if (group == 64) return sqp_strip_g64(p, M, N, K, 1, x, packed, scales, zeros, y, epi, ws, stream);

@@ -598,8 +598,16 @@ extern "C" void sqp_debug_set_prefill_variant(int rt, int nt, int parts)
     g_force_parts = parts;
 }
 
-static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, bool have_workspace)
+static size_t launch_partial_bytes(const TileLaunch &l, int wm)
 {
+    return l.parts >= 2 ? (size_t)l.parts * l.tiles * (32 * l.rt * wm) * (l.nt * 128 / wm) * sizeof(float) : 0;
+}
+
+// room: bytes there are for partial sums (0: none).  A plan in 128-row tiles that needs more is returned as
+// it is and refused by the caller; the estimates below only take what fits.
+static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, size_t room)
+{
+    const bool have_workspace = room > 0;
     const TilePlan p = plan_tiles(M, N, K, group, cus, have_workspace);
     LaunchPlan q = {p.wm, 0, {}};
     const int stages = K / BK, tnf = (N + (4 / p.wm) * 128 - 1) / ((4 / p.wm) * 128);
@@ -642,10 +650,11 @@ static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, bool ha
             if (tiles > cus) continue;
             for (int parts = 1; parts <= (most > 1 ? most : 1); parts++) {
                 const double t = (stages + parts - 1) / parts * stage_us[rt] + (parts > 1 ? parts * part_us : 0.0);
-                if (q.count == 0 || t < best) {
+                const TileLaunch l = {rt, 2, 0, tiles, tn, parts};
+                if (launch_partial_bytes(l, 1) <= room && (q.count == 0 || t < best)) {
                     best = t;
                     q.count = 1;
-                    q.l[0] = TileLaunch{rt, 2, 0, tiles, tn, parts};
+                    q.l[0] = l;
                 }
             }
         }
@@ -654,6 +663,7 @@ static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, bool ha
     if (p.full > 0) q.l[q.count++] = TileLaunch{4, 4, 0, p.full, tnf, 1};
     if (p.half > 0) {
         int parts = p.ksplit;
+        while (!hooked && parts > 1 && launch_partial_bytes(TileLaunch{4, 2, 0, p.half, 0, parts}, p.wm) > room) parts--;
         // Few tiles left over after the whole rounds: split in K as well, as far as they then fill the
         // chip once.
         if (!hooked && p.full > 0 && have_workspace) {
@@ -664,7 +674,7 @@ static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, bool ha
             double best = stages * 0.77;
             for (int n = 2; n <= most; n++) {
                 const double t = (stages + n - 1) / n * 0.77 + n * part_us + 3;
-                if (t < best) {
+                if (t < best && launch_partial_bytes(TileLaunch{4, 2, 0, p.half, 0, n}, 1) <= room) {
                     best = t;
                     parts = n;
                 }
@@ -678,7 +688,7 @@ static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, bool ha
 // Test hook: the launches of a call (no GPU needed): up to two of (rt, nt, tiles, parts).
 extern "C" int sqp_debug_prefill_launches(int M, int N, int K, int group, int cus, int *out8)
 {
-    const LaunchPlan q = plan_launches(M, N, K, group, cus, true);
+    const LaunchPlan q = plan_launches(M, N, K, group, cus, SIZE_MAX);
     for (int i = 0; i < q.count; i++) {
         out8[4 * i] = q.l[i].rt;
         out8[4 * i + 1] = q.l[i].nt;
@@ -688,21 +698,28 @@ extern "C" int sqp_debug_prefill_launches(int M, int N, int K, int group, int cu
     return q.count;
 }
 
-static size_t launch_partial_bytes(const TileLaunch &l, int wm)
-{
-    return l.parts >= 2 ? (size_t)l.parts * l.tiles * (32 * l.rt * wm) * (l.nt * 128 / wm) * sizeof(float) : 0;
-}
-
 size_t sqp_gemm_prefill_partial_bytes(int M, int N, int K, int group)
 {
     if (group % BK != 0 && !(group == 32 && K % BK == 0)) return sqp_gemm_decode_partial_bytes(M < 64 ? M : 64, N, K, group);  // row-block fallback
-    const LaunchPlan q = plan_launches(M, N, K, group, sqp_compute_units(), true);
+    const LaunchPlan q = plan_launches(M, N, K, group, sqp_compute_units(), SIZE_MAX);
     size_t need = 0;
     for (int i = 0; i < q.count; i++) {
         const size_t b = launch_partial_bytes(q.l[i], q.wm);
         need = b > need ? b : need;
     }
     return need;
+}
+
+// What a workspace has to hold at least for a call not to be refused: the K parts of the plan in 128-row
+// tiles as [parts][M][N].  With less than the preferred plan's bytes, one that fits runs.
+size_t sqp_gemm_prefill_least_bytes(int M, int N, int K, int group)
+{
+    if (group % BK != 0 && !(group == 32 && K % BK == 0)) return sqp_gemm_decode_least_bytes(M < 64 ? M : 64, N, K, group);
+    const size_t want = sqp_gemm_prefill_partial_bytes(M, N, K, group);
+    if (g_force_rt > 0) return want;
+    const TilePlan p = plan_tiles(M, N, K, group, sqp_compute_units(), true);
+    const size_t base = p.ksplit >= 2 ? (size_t)p.ksplit * M * N * sizeof(float) : 0;
+    return base < want ? base : want;
 }
 
 template <int RT, int NT, int WM, bool G32>
@@ -719,9 +736,11 @@ int sqp_gemm_prefill(int M, int N, int K, int group, const h16 *x, const uint32_
     // group sizes the tiled kernel does not cover (neither a multiple of 64, nor 32 with K a multiple of 64)
     if (!(group % BK == 0 || (group == 32 && K % BK == 0)))
         return decode_in_row_blocks(M, N, K, group, x, packed, scales, zeros, y, epi, ws, stream);
-    const LaunchPlan q = plan_launches(M, N, K, group, sqp_compute_units(), ws.partial != nullptr);
+    const size_t room = ws.partial ? ws.partial_bytes : 0;
+    if (room > 0 && room < sqp_gemm_prefill_least_bytes(M, N, K, group)) return SQP_ERR_WORKSPACE;
+    const LaunchPlan q = plan_launches(M, N, K, group, sqp_compute_units(), room);
     for (int i = 0; i < q.count; i++)
-        if (launch_partial_bytes(q.l[i], q.wm) > (ws.partial ? ws.partial_bytes : 0)) return SQP_ERR_WORKSPACE;
+        if (launch_partial_bytes(q.l[i], q.wm) > room) return SQP_ERR_WORKSPACE;
     for (int i = 0; i < q.count; i++) {
         const TileLaunch &l = q.l[i];
 #define SQP_TILES(RT, NT, WM, G32) launch_variant<RT, NT, WM, G32>(l, M, N, K, group, x, packed, scales, zeros, y, epi, ws.partial, stream)

@@ -323,6 +323,41 @@ def test_companion_outputs_between_guards(orc, sqp, K, N, group):
     assert np.array_equal(wi.numpy()[:, 0::2].view(np.uint16), w.view(np.uint16))
 
 
+@pytest.mark.parametrize("M,K,N,group", [(56, 768, 10240, 128), (40, 1024, 520, 64), (65, 2048, 520, 128), (130, 1024, 264, 32),
+                                         (150, 1536, 1032, 256), (2050, 2048, 8144, 128)])
+def test_workspace_between_least_and_preferred(orc, sqp, M, K, N, group):
+    """Buffers from the least size (nothing beside the tickets, where that is 0) to the preferred one: a
+    plan that fits runs, inside its buffer; 16 bytes below the least size the call is refused."""
+    print("case least workspace", M, K, N, group, flush=True)
+    L = sqp.lib()
+    least, want = int(L.sqp_w4a16_gemm_workspace_least_bytes(M, N, K, group)), sqp.workspace_bytes(M, N, K, group)
+    assert 0 <= least <= want and want > 0
+    xs, p, sc, z = _layer(orc, M, K, N, group)
+    dx, dp, dsc, dz = _dev(xs), _dev(p), _dev(sc), _dev(z)
+    rows = np.unique(np.linspace(0, M - 1, min(M, 48)).astype(int))
+    y_ref, t_ref = orc.w4a16_gemm_ref(np.ascontiguousarray(xs[rows]), p, sc, z, group)
+    y = Guarded(2 * M * N, torch.float16, (M, N))
+    try:
+        lo = max(least, TICKET_BYTES + 16)
+        for size in sorted({lo, lo + (want - lo) // 3 // 16 * 16, max(lo, want - 16), want}):
+            ws = Guarded(size)
+            _set_ws(L, ws.ptr, size)
+            y.view().zero_()
+            assert _gemm(L, M, N, K, group, dx, dp, dsc, dz, y.ptr) == 0, size
+            torch.cuda.synchronize()
+            ok, worst, nbad = gemm_tolerance_ok(orc, y.numpy()[rows], y_ref, t_ref)
+            assert ok, (size, worst, nbad)
+            ws.check("workspace")
+            y.check("y")
+        if least > TICKET_BYTES + 16:
+            ws = Guarded(least)
+            _set_ws(L, ws.ptr, least - 16)
+            assert _gemm(L, M, N, K, group, dx, dp, dsc, dz, y.ptr) == -6
+    finally:
+        torch.cuda.synchronize()
+        sqp.set_workspace(0)
+
+
 def test_native_marshalling_equals_general_path(orc, sqp):
     """The serving calls through the native marshalling give the general path's bits, with and without
     an output; what the general path refuses is refused with the same error, and what it takes
