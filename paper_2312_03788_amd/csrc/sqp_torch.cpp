@@ -6,7 +6,9 @@
 //
 // Every function returns the output tensor, or None for anything but the plain case (wrong type,
 // device, layout or shape, tensor subclasses, a workspace that has to grow, an error code): the
-// binding then takes its general path, which reports the error.
+// binding then takes its general path, which reports the error.  Tensor methods may throw (nested
+// tensors have no size in every dimension), so all of them are called inside a try block.  The library's
+// calls run without the GIL, as under ctypes: a launch may have to wait for room in the queue.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -72,18 +74,22 @@ PyObject *gemm(PyObject *, PyObject *const *a, Py_ssize_t n)
         Py_RETURN_NONE;
     }
     if (which < 0 || which > 2 || !g_gemm[which]) Py_RETURN_NONE;
-    const at::Tensor *x = plain(a[1], at::kHalf, dev), *packed = plain(a[2], at::kInt, dev);
-    const at::Tensor *scales = plain(a[3], at::kHalf, dev), *zeros = plain(a[4], at::kByte, dev);
-    if (!x || !packed || !scales || !zeros || x->dim() != 2 || packed->dim() != 2) Py_RETURN_NONE;
-    const long M = x->size(0), K = x->size(1), N = packed->size(1);
-    if (!fits(M) || !fits(K) || !fits(N) || !fits(group) || packed->size(0) * 8 != K) Py_RETURN_NONE;
-    if (which != 2 && g_workspace_bytes((int)M, (int)N, (int)K, (int)group) > held) Py_RETURN_NONE;
     try {
+        const at::Tensor *x = plain(a[1], at::kHalf, dev), *packed = plain(a[2], at::kInt, dev);
+        const at::Tensor *scales = plain(a[3], at::kHalf, dev), *zeros = plain(a[4], at::kByte, dev);
+        if (!x || !packed || !scales || !zeros || x->dim() != 2 || packed->dim() != 2) Py_RETURN_NONE;
+        const long M = x->size(0), K = x->size(1), N = packed->size(1);
+        if (!fits(M) || !fits(K) || !fits(N) || !fits(group) || packed->size(0) * 8 != K) Py_RETURN_NONE;
+        if (which != 2 && g_workspace_bytes((int)M, (int)N, (int)K, (int)group) > held) Py_RETURN_NONE;
         at::Tensor y;
         if (!output(a[6], *x, M, which == 1 ? N / 2 : N, dev, y)) Py_RETURN_NONE;
-        if (g_gemm[which]((int)M, (int)N, (int)K, (int)group, x->data_ptr(), (const uint32_t *)packed->data_ptr(), scales->data_ptr(),
-                          (const uint8_t *)zeros->data_ptr(), y.data_ptr(), stream) != 0)
-            Py_RETURN_NONE;
+        const void *xp = x->data_ptr(), *pp = packed->data_ptr(), *sp = scales->data_ptr(), *zp = zeros->data_ptr();
+        void *yp = y.data_ptr();
+        int rc;
+        Py_BEGIN_ALLOW_THREADS
+        rc = g_gemm[which]((int)M, (int)N, (int)K, (int)group, xp, (const uint32_t *)pp, sp, (const uint8_t *)zp, yp, stream);
+        Py_END_ALLOW_THREADS
+        if (rc != 0) Py_RETURN_NONE;
         return result(a[6], y);
     } catch (...) {  // e.g. out of memory: the general path raises it as Python does
         Py_RETURN_NONE;
@@ -101,12 +107,19 @@ PyObject *rmsnorm(PyObject *, PyObject *const *a, Py_ssize_t n)
         PyErr_Clear();
         Py_RETURN_NONE;
     }
-    const at::Tensor *x = plain(a[0], at::kHalf, dev), *gamma = plain(a[1], at::kHalf, dev);
-    if (!x || !gamma || x->dim() != 2 || !fits(x->size(0)) || !fits(x->size(1))) Py_RETURN_NONE;
     try {
+        const at::Tensor *x = plain(a[0], at::kHalf, dev), *gamma = plain(a[1], at::kHalf, dev);
+        if (!x || !gamma || x->dim() != 2 || !fits(x->size(0)) || !fits(x->size(1))) Py_RETURN_NONE;
+        const long M = x->size(0), H = x->size(1);
         at::Tensor y;
-        if (!output(a[3], *x, x->size(0), x->size(1), dev, y)) Py_RETURN_NONE;
-        if (g_rmsnorm((int)x->size(0), (int)x->size(1), x->data_ptr(), gamma->data_ptr(), (float)eps, y.data_ptr(), stream) != 0) Py_RETURN_NONE;
+        if (!output(a[3], *x, M, H, dev, y)) Py_RETURN_NONE;
+        const void *xp = x->data_ptr(), *gp = gamma->data_ptr();
+        void *yp = y.data_ptr();
+        int rc;
+        Py_BEGIN_ALLOW_THREADS
+        rc = g_rmsnorm((int)M, (int)H, xp, gp, (float)eps, yp, stream);
+        Py_END_ALLOW_THREADS
+        if (rc != 0) Py_RETURN_NONE;
         return result(a[3], y);
     } catch (...) {
         Py_RETURN_NONE;
@@ -123,12 +136,19 @@ PyObject *apply_x(PyObject *, PyObject *const *a, Py_ssize_t n)
         PyErr_Clear();
         Py_RETURN_NONE;
     }
-    const at::Tensor *x = plain(a[0], at::kHalf, dev), *s = plain(a[1], at::kFloat, dev);
-    if (!x || !s || x->dim() != 2 || !fits(x->size(0)) || !fits(x->size(1))) Py_RETURN_NONE;
     try {
+        const at::Tensor *x = plain(a[0], at::kHalf, dev), *s = plain(a[1], at::kFloat, dev);
+        if (!x || !s || x->dim() != 2 || !fits(x->size(0)) || !fits(x->size(1))) Py_RETURN_NONE;
+        const long M = x->size(0), K = x->size(1);
         at::Tensor y;
-        if (!output(a[2], *x, x->size(0), x->size(1), dev, y)) Py_RETURN_NONE;
-        if (g_apply_x((int)x->size(0), (int)x->size(1), x->data_ptr(), (const float *)s->data_ptr(), y.data_ptr(), stream) != 0) Py_RETURN_NONE;
+        if (!output(a[2], *x, M, K, dev, y)) Py_RETURN_NONE;
+        const void *xp = x->data_ptr(), *sp = s->data_ptr();
+        void *yp = y.data_ptr();
+        int rc;
+        Py_BEGIN_ALLOW_THREADS
+        rc = g_apply_x((int)M, (int)K, xp, (const float *)sp, yp, stream);
+        Py_END_ALLOW_THREADS
+        if (rc != 0) Py_RETURN_NONE;
         return result(a[2], y);
     } catch (...) {
         Py_RETURN_NONE;

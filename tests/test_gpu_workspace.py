@@ -399,3 +399,22 @@ def test_native_marshalling_equals_general_path(orc, sqp):
                 messages.append(str(e.value))
             assert messages[0] == messages[1], messages
     torch.cuda.synchronize()
+
+
+def test_native_marshalling_declines_without_aborting(sqp):
+    """Tensor methods that throw (a nested tensor has no size in its ragged dimension) end in
+    the general path's exception, never in an abort."""
+    ragged = torch.nested.nested_tensor([torch.zeros(512), torch.zeros(256)], dtype=torch.float16, device="cuda")
+    x = torch.zeros((2, 512), dtype=torch.float16, device="cuda")
+    p = torch.zeros((64, 272), dtype=torch.int32, device="cuda")
+    sc = torch.zeros((4, 272), dtype=torch.float16, device="cuda")
+    z = torch.zeros((4, 272), dtype=torch.uint8, device="cuda")
+    for fn in (sqp.w4a16_gemm, sqp.w4a16_gemm_static, sqp.w4a16_gemm_silu_mul):
+        fn(x, p, sc, z, 128)
+        with pytest.raises(RuntimeError):
+            fn(ragged, p, sc, z, 128)
+    with pytest.raises(RuntimeError):
+        sqp.rmsnorm(ragged, sc[0, :], 1e-5)
+    with pytest.raises(RuntimeError):
+        sqp.smooth_apply_x(ragged, torch.ones(512, device="cuda"))
+    torch.cuda.synchronize()
