@@ -18,7 +18,7 @@
 //     (1024 + Z or 64 + Z) is subtracted with a packed fp16 add, which is exact.
 //   - The MFMA accumulates one chunk in fp32, then the step Delta (a per-lane scalar in the
 //     16x16 accumulator layout: column = lane % 16) scales it into the running sum:
-//     sum_k x (q - Z) Delta = Delta * sum_k x (q - Z).  (The 64-row variant multiplies the
+//     sum_k x (q - Z) Delta = Delta * sum_k x (q - Z).  (The 48- and 64-row variants multiply the
 //     unpacked weights by Delta instead, which is less vector work there.)
 //   - Weight loads and all waits are written in assembly: D - 1 chunks of weights stay in
 //     flight per wave while one is consumed, and the compiler's conservative waits (it cannot
@@ -114,10 +114,11 @@ w4a16_decode_kernel(int M, int N, int K, int cpg, const h16 *__restrict__ x, con
     constexpr int NQ = KS > GS ? KS / GS : 1;    // groups in this wave's share of a chunk
     constexpr int SQ = KS / NQ;                  // k-steps of one group there
     constexpr int OW = KS + 2 * NQ;              // weight-side loads per wave per chunk
-    // With four row tiles the per-chunk scaling of 64 accumulator registers costs more vector
-    // work than multiplying the unpacked weights by the step (4 packed multiplies per word, as
-    // in the tiled kernel), so that variant accumulates fp16(w_hat) products directly.
-    constexpr bool SCALED_B = MT == 4;
+    // With three and four row tiles the per-chunk scaling of 48 or 64 accumulator registers costs more
+    // vector work than multiplying the unpacked weights by the step (4 packed multiplies per word, as
+    // in the tiled kernel), so those variants accumulate fp16(w_hat) products directly: 33 to 64 rows
+    // give the products of the rounded weight whichever variant runs.
+    constexpr bool SCALED_B = MT >= 3;
     static_assert((P - 1) * (OX + OW) < 64, "vmcnt field");
     constexpr int EXCHANGE = (KW * KP - 1) * NW * REGS * 256;  // bytes of the sums a strip's waves exchange at the end
     __shared__ __attribute__((aligned(1024))) unsigned char xring[XD * XSTAGE > EXCHANGE ? XD * XSTAGE : EXCHANGE];

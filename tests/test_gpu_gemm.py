@@ -52,6 +52,27 @@ def test_decode_row_counts(orc, sqp, M):
     _check(orc, sqp, xs, p, sc, z, 128)
 
 
+@pytest.mark.parametrize("group", [32, 64, 128, 256])
+@pytest.mark.parametrize("M", [33, 47, 48, 49, 64])
+def test_rows_33_to_64_take_the_rounded_weight(sqp, M, group):
+    """33 to 64 rows multiply w_hat = fp16((code - Z) Delta), the value sqp_dequantize gives: a row of
+    x with two ones is the fp16 rounding of a sum of two such values, which fp32 holds exactly (steps
+    within a factor of 8 and codes up to 15, so exponents less than 13 apart)."""
+    print("case rounded weight", M, group, flush=True)
+    K, N = 768, 72
+    rng = np.random.Generator(np.random.PCG64(1000 * group + M))
+    p = rng.integers(0, 2**32, size=(K // 8, N), dtype=np.uint32)
+    sc = rng.uniform(0.01, 0.08, size=(K // group, N)).astype(np.float16)
+    z = rng.integers(0, 16, size=(K // group, N), dtype=np.uint8)
+    x = np.zeros((M, K), np.float16)
+    at = np.stack([rng.choice(K, 2, replace=False) for _ in range(M)])
+    x[np.arange(M)[:, None], at] = 1.0
+    dp, dsc, dz = dev(p), dev(sc), dev(z)
+    w_hat = host(sqp.dequantize(dp, dsc, dz, group)).astype(np.float32)
+    y = host(sqp.w4a16_gemm(dev(x), dp, dsc, dz, group))
+    assert np.array_equal(y, (w_hat[at[:, 0]] + w_hat[at[:, 1]]).astype(np.float16))
+
+
 @pytest.mark.parametrize("M,K,N,group", [
     (3, 128, 8, 128), (5, 256, 72, 128), (16, 384, 520, 128), (9, 1152, 200, 128), (4, 256, 64, 32),
     (16, 320, 136, 64), (33, 1024, 264, 256), (2, 48, 24, 24), (6, 64, 16, 8), (64, 2048, 1000, 128),
