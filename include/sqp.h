@@ -119,18 +119,34 @@ int sqp_dequantize(int N, int K, int group, const uint32_t *packed, const void *
  * Rows M <= 64 take the weight-streaming (memory-bound) path, larger M the tiled
  * matrix-core path.  When the output has too few tiles to occupy the chip, the launch plan
  * splits the inner dimension across workgroups and passes fp32 partial sums through the
- * workspace set with sqp_set_workspace (with few rows, or few rows and a short K, groups of 128
- * run a kernel that splits K inside each workgroup instead and uses no workspace:
- * sqp_w4a16_gemm_workspace_bytes() is 0 for those shapes):
+ * workspace set with sqp_set_workspace.  sqp_w4a16_gemm_workspace_bytes() is 0 for the shapes
+ * that never touch it: with few rows, or few rows and a short K, groups of 128 (they split K
+ * inside each workgroup); M <= 64 with a K of fewer than eight chunks of 128 (or of one group of 32 or
+ * 64); larger M with more tiles of 128 x 512 than a quarter of the chip's compute units (those can
+ * split too, but only in a scratch buffer of their own: sqp_w4a16_gemm_scratch).  For the others:
  *   - no workspace set: the plan without a split runs (same result within the tolerance of
  *     Eq. 3's fp32 accumulation, slower on narrow layers);
  *   - workspace smaller than sqp_w4a16_gemm_workspace_bytes() of the shape: a plan that fits
  *     it runs, down to sqp_w4a16_gemm_workspace_least_bytes(); below that SQP_ERR_WORKSPACE,
  *     nothing enqueued.
  * Calls that use the workspace must not overlap on the device (order them on one stream, or
- * with events): they share its tickets and partial sums. */
+ * with events): they share its tickets and partial sums.  Calls of shapes whose
+ * sqp_w4a16_gemm_workspace_bytes() is 0 may overlap with anything. */
 int sqp_w4a16_gemm(int M, int N, int K, int group, const void *x, const uint32_t *packed,
                    const void *scales, const uint8_t *zeros, void *y, void *stream);
+
+/* The same call (silu_mul != 0: sqp_w4a16_gemm_silu_mul) with a scratch buffer of its own, where a grid
+ * that fills the chip leaves a last round of few tiles, or tiles of another height fit better with K
+ * split: the partial sums of those K parts go there.  The buffer belongs to this call until the work
+ * enqueued by it has run, needs no preparation and holds nothing afterwards; NULL or a smaller
+ * one: a plan that fits runs (as sqp_w4a16_gemm without any).  Everything else, the workspace of
+ * the shapes that use it included, is as for sqp_w4a16_gemm. */
+int sqp_w4a16_gemm_scratch(int M, int N, int K, int group, int silu_mul, const void *x, const uint32_t *packed,
+                           const void *scales, const uint8_t *zeros, void *y, void *scratch, size_t scratch_bytes,
+                           void *stream);
+
+/* Bytes of scratch the preferred plan of sqp_w4a16_gemm_scratch uses (0: none).  Host arithmetic only. */
+size_t sqp_w4a16_gemm_scratch_bytes(int M, int N, int K, int group);
 
 /* Bytes of workspace the launch plan of sqp_w4a16_gemm / sqp_w4a16_gemm_silu_mul uses for
  * this shape on the current device: 0 if the plan does not split the inner dimension,

@@ -17,7 +17,7 @@ _LIB_PATH = os.environ.get("SQP_LIBRARY", os.path.join(_HERE, "libsqp.so"))  # o
 EXPORTS = ["sqp_status_string", "sqp_smooth_scales", "sqp_smooth_apply_x", "sqp_smooth_apply_w",
            "sqp_quantize_pack", "sqp_dequantize", "sqp_w4a16_gemm", "sqp_quant_loss", "sqp_transpose_nk",
            "sqp_w4a16_gemm_silu_mul", "sqp_rmsnorm", "sqp_scale_columns", "sqp_interleave_gate_up",
-           "sqp_set_workspace", "sqp_alpha_search", "sqp_w4a16_gemm_static"]
+           "sqp_set_workspace", "sqp_alpha_search", "sqp_w4a16_gemm_static", "sqp_w4a16_gemm_scratch"]
 
 
 class SqpError(RuntimeError):
@@ -48,6 +48,9 @@ def lib():
         L.sqp_transpose_nk.argtypes = [i, i, vp, vp, vp]
         L.sqp_w4a16_gemm_silu_mul.argtypes = [i, i, i, i, vp, vp, vp, vp, vp, vp]
         L.sqp_w4a16_gemm_static.argtypes = [i, i, i, i, vp, vp, vp, vp, vp, vp]
+        L.sqp_w4a16_gemm_scratch.argtypes = [i, i, i, i, i, vp, vp, vp, vp, vp, vp, ctypes.c_size_t, vp]
+        L.sqp_w4a16_gemm_scratch_bytes.argtypes = [i, i, i, i]
+        L.sqp_w4a16_gemm_scratch_bytes.restype = ctypes.c_size_t
         L.sqp_rmsnorm.argtypes = [i, i, vp, vp, f, vp, vp]
         L.sqp_scale_columns.argtypes = [i, i, vp, vp, vp, vp]
         L.sqp_interleave_gate_up.argtypes = [i, i, vp, vp, vp, vp]
@@ -66,7 +69,7 @@ def lib():
         spec.loader.exec_module(fast)
         fast.bind(*[ctypes.cast(f, ctypes.c_void_p).value for f in (
             L.sqp_w4a16_gemm, L.sqp_w4a16_gemm_silu_mul, L.sqp_w4a16_gemm_static, L.sqp_w4a16_gemm_workspace_bytes,
-            L.sqp_rmsnorm, L.sqp_smooth_apply_x)])
+            L.sqp_rmsnorm, L.sqp_smooth_apply_x, L.sqp_w4a16_gemm_scratch, L.sqp_w4a16_gemm_scratch_bytes)])
         _fast = fast
         _lib = L
     return _lib
@@ -131,14 +134,17 @@ def set_workspace(nbytes, device=None):
 
 
 def workspace_bytes(M, N, K, group=128):
-    """Bytes of workspace the launch plan of the GEMM uses for this shape (0: none)."""
+    """Bytes of workspace the launch plan of the GEMM uses for this shape (0: none, and the call may
+    overlap with any other)."""
     return int(lib().sqp_w4a16_gemm_workspace_bytes(M, N, K, group))
 
 
 def _ensure_workspace(M, N, K, group, device):
     """Device-memory plumbing for the GEMM calls: make sure the workspace set on the tensor's
     device covers this shape's plan (grown with some slack so that a sweep over shapes
-    settles after a few calls).  Callers that must not allocate (graph capture) call
+    settles after a few calls).  There is one per device: calls of shapes whose workspace_bytes is not 0
+    must not overlap on the device, so a program that issues them on several streams orders them
+    with events (every other shape may overlap with anything).  Callers that must not allocate (graph capture) call
     set_workspace themselves beforehand; during a capture the buffer only grows where the call
     would be refused otherwise."""
     need = workspace_bytes(M, N, K, group)
@@ -150,6 +156,41 @@ def _ensure_workspace(M, N, K, group, device):
         if torch.cuda.is_current_stream_capturing() and have >= int(lib().sqp_w4a16_gemm_workspace_least_bytes(M, N, K, group)):
             return
         set_workspace(max(need, 2 * have, 16 << 20), device)
+
+
+def _call_scratch(M, N, K, group, x, out):
+    """Scratch of one GEMM call (or None): a tensor of the current stream, so that dropping it when the call
+    returns hands it to work that is ordered behind the call.  Not for a caller that passes `out`
+    under graph capture (it may not allocate), nor for tensors of another device than the current one."""
+    nbytes = int(lib().sqp_w4a16_gemm_scratch_bytes(M, N, K, group))
+    if nbytes == 0 or not x.is_cuda or x.device.index != torch.cuda.current_device():
+        return None
+    if out is not None and torch.cuda.is_current_stream_capturing():
+        return None
+    try:
+        return torch.empty(nbytes, dtype=torch.uint8, device=x.device)
+    except torch.cuda.OutOfMemoryError:
+        return None
+
+
+def _gemm(fused, x, packed, scales, zeros, group, out):
+    """The GEMM calls' general path."""
+    what = "sqp_w4a16_gemm_silu_mul" if fused else "sqp_w4a16_gemm"
+    M, K = x.shape
+    N = packed.shape[1]
+    if packed.shape[0] * 8 != K:
+        raise SqpError("x and packed disagree on K")
+    y = out if out is not None else torch.empty((M, N // 2 if fused else N), dtype=torch.float16, device=x.device)
+    _ensure_workspace(M, N, K, group, x.device)
+    args = [M, N, K, group, _dev(x, torch.float16, "x"), _dev(packed, torch.int32, "packed"),
+            _dev(scales, torch.float16, "scales"), _dev(zeros, torch.uint8, "zeros"), _dev(y, torch.float16, "y")]
+    scratch = _call_scratch(M, N, K, group, x, out)
+    if scratch is None:
+        _check(getattr(lib(), what)(*args, _stream()), what)
+    else:
+        args.insert(4, fused)
+        _check(lib().sqp_w4a16_gemm_scratch(*args, ctypes.c_void_p(scratch.data_ptr()), scratch.numel(), _stream()), what)
+    return y
 
 
 def smooth_scales(x_cal, w, alpha, out=None):
@@ -222,16 +263,7 @@ def w4a16_gemm(x, packed, scales, zeros, group=128, out=None):
         y = _fast.gemm(0, x, packed, scales, zeros, group, out, dev, stream, _held.get(dev, 0))
         if y is not None:
             return y
-    M, K = x.shape
-    N = packed.shape[1]
-    if packed.shape[0] * 8 != K:
-        raise SqpError("x and packed disagree on K")
-    y = out if out is not None else torch.empty((M, N), dtype=torch.float16, device=x.device)
-    _ensure_workspace(M, N, K, group, x.device)
-    _check(lib().sqp_w4a16_gemm(M, N, K, group, _dev(x, torch.float16, "x"), _dev(packed, torch.int32, "packed"),
-                                _dev(scales, torch.float16, "scales"), _dev(zeros, torch.uint8, "zeros"),
-                                _dev(y, torch.float16, "y"), _stream()), "sqp_w4a16_gemm")
-    return y
+    return _gemm(0, x, packed, scales, zeros, group, out)
 
 
 def w4a16_gemm_static(x, packed, scales, zeros, group=128, out=None):
@@ -260,16 +292,7 @@ def w4a16_gemm_silu_mul(x, packed, scales, zeros, group=128, out=None):
         y = _fast.gemm(1, x, packed, scales, zeros, group, out, dev, stream, _held.get(dev, 0))
         if y is not None:
             return y
-    M, K = x.shape
-    N = packed.shape[1]
-    if packed.shape[0] * 8 != K:
-        raise SqpError("x and packed disagree on K")
-    y = out if out is not None else torch.empty((M, N // 2), dtype=torch.float16, device=x.device)
-    _ensure_workspace(M, N, K, group, x.device)
-    _check(lib().sqp_w4a16_gemm_silu_mul(M, N, K, group, _dev(x, torch.float16, "x"), _dev(packed, torch.int32, "packed"),
-                                         _dev(scales, torch.float16, "scales"), _dev(zeros, torch.uint8, "zeros"),
-                                         _dev(y, torch.float16, "y"), _stream()), "sqp_w4a16_gemm_silu_mul")
-    return y
+    return _gemm(1, x, packed, scales, zeros, group, out)
 
 
 def rmsnorm(x, gamma, eps, out=None):

@@ -127,7 +127,7 @@ int sqp_zero_tickets(unsigned *tickets, hipStream_t stream)
 SqpWorkspace sqp_caller_workspace()
 {
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return SqpWorkspace{nullptr, nullptr, 0};
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return SqpWorkspace{};
     return g_caller_ws[dev];
 }
 
@@ -136,14 +136,14 @@ extern "C" int sqp_set_workspace(void *dev_ptr, size_t bytes, void *stream)
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return SQP_ERR_WORKSPACE;
     if (dev_ptr == nullptr || bytes == 0) {
-        g_caller_ws[dev] = SqpWorkspace{nullptr, nullptr, 0};
+        g_caller_ws[dev] = SqpWorkspace{};
         return SQP_OK;
     }
     if (sqp_misaligned(dev_ptr)) return SQP_ERR_ALIGN;
     if (bytes <= SQP_WS_TICKET_BYTES) return SQP_ERR_WORKSPACE;
     int rc = sqp_zero_tickets((unsigned *)dev_ptr, (hipStream_t)stream);
     if (rc) return rc;
-    SqpWorkspace ws;
+    SqpWorkspace ws = {};
     ws.tickets = (unsigned *)dev_ptr;
     ws.partial = (float *)((unsigned char *)dev_ptr + SQP_WS_TICKET_BYTES);
     ws.partial_bytes = (bytes - SQP_WS_TICKET_BYTES) & ~(size_t)15;
@@ -181,6 +181,12 @@ extern "C" size_t sqp_w4a16_gemm_workspace_least_bytes(int M, int N, int K, int 
     return partial ? SQP_WS_TICKET_BYTES + partial : 0;
 }
 
+extern "C" size_t sqp_w4a16_gemm_scratch_bytes(int M, int N, int K, int group)
+{
+    if (M <= 0 || sqp_check_quant_shape(N, K, group) != SQP_OK || sqp_too_big(M, K) || sqp_too_big(M, N)) return 0;
+    return streaming_path(M) ? 0 : sqp_gemm_prefill_scratch_bytes(M, N, K, group);
+}
+
 // Shared by every GEMM entry point: argument checks, then the weight-streaming path (small M)
 // or the tiled matrix-core path.
 int sqp_gemm_entry(int M, int N, int K, int group, const void *x, const uint32_t *packed, const void *scales,
@@ -202,11 +208,24 @@ extern "C" int sqp_w4a16_gemm(int M, int N, int K, int group, const void *x, con
     return sqp_gemm_entry(M, N, K, group, x, packed, scales, zeros, y, 0, sqp_caller_workspace(), stream);
 }
 
+// The fused epilogue: the half-width output keeps 16-byte rows, and it exists in the matrix-core kernels only.
+static bool fused_covers(int N, int group) { return N % 16 == 0 && (group == 32 || group == 64 || group % 128 == 0); }
+
 extern "C" int sqp_w4a16_gemm_silu_mul(int M, int N, int K, int group, const void *x, const uint32_t *packed,
                                        const void *scales, const uint8_t *zeros, void *y, void *stream)
 {
-    if (N % 16) return SQP_ERR_SHAPE;          // the half-width output keeps 16-byte rows
-    // the fused epilogue exists in the matrix-core kernels only
-    if (!(group == 32 || group == 64 || group % 128 == 0)) return SQP_ERR_SHAPE;
+    if (!fused_covers(N, group)) return SQP_ERR_SHAPE;
     return sqp_gemm_entry(M, N, K, group, x, packed, scales, zeros, y, 1, sqp_caller_workspace(), stream);
+}
+
+extern "C" int sqp_w4a16_gemm_scratch(int M, int N, int K, int group, int silu_mul, const void *x, const uint32_t *packed,
+                                      const void *scales, const uint8_t *zeros, void *y, void *scratch, size_t scratch_bytes,
+                                      void *stream)
+{
+    if (silu_mul && !fused_covers(N, group)) return SQP_ERR_SHAPE;
+    if (scratch && sqp_misaligned(scratch)) return SQP_ERR_ALIGN;
+    SqpWorkspace ws = sqp_caller_workspace();
+    ws.own = (float *)scratch;
+    ws.own_bytes = scratch ? scratch_bytes & ~(size_t)15 : 0;
+    return sqp_gemm_entry(M, N, K, group, x, packed, scales, zeros, y, silu_mul ? 1 : 0, ws, stream);
 }

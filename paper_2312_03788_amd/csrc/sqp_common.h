@@ -37,14 +37,19 @@ static inline int sqp_launch_status()
 // launches: the last workgroup of a tile to arrive resets it) followed by the partial sums.
 // It is never allocated here: it is the caller's buffer (sqp_set_workspace) or the library's
 // static device array (sqp_w4a16_gemm_static).  partial == nullptr: none, plans do not split.
+// own: scratch that belongs to this call alone (sqp_w4a16_gemm_scratch), for plans that split tiles of
+// a grid that fills the chip by itself.  Those never go through the shared buffer: such calls may
+// overlap with any other call.
 constexpr size_t SQP_WS_TICKETS = (size_t)1 << 17;                       // counters
 constexpr size_t SQP_WS_TICKET_BYTES = SQP_WS_TICKETS * sizeof(unsigned);  // 512 KB
 struct SqpWorkspace {
     unsigned *tickets;
     float *partial;
     size_t partial_bytes;
+    float *own;
+    size_t own_bytes;
 };
-// The workspace the caller has set for the current device (partial == nullptr if none).
+// The workspace the caller has set for the current device (partial == nullptr if none; own == nullptr).
 SqpWorkspace sqp_caller_workspace();
 // Enqueue a kernel that zeroes the ticket area.
 int sqp_zero_tickets(unsigned *tickets, hipStream_t stream);
@@ -68,6 +73,8 @@ int sqp_gemm_entry(int M, int N, int K, int group, const void *x, const uint32_t
 // Bytes of partial sums the preferred plan of a shape needs (0: it does not split K).
 size_t sqp_gemm_decode_partial_bytes(int M, int N, int K, int group);
 size_t sqp_gemm_prefill_partial_bytes(int M, int N, int K, int group);
+// Bytes of the call's own scratch the preferred plan uses (0: none, or the workspace serves it).
+size_t sqp_gemm_prefill_scratch_bytes(int M, int N, int K, int group);
 // Bytes below which a call with a workspace is refused; between the two a plan that fits runs.
 size_t sqp_gemm_decode_least_bytes(int M, int N, int K, int group);
 size_t sqp_gemm_prefill_least_bytes(int M, int N, int K, int group);

@@ -222,13 +222,40 @@ extern "C" void sqp_debug_decode_plan(int M, int N, int K, int group, int *nw, i
     *kspg = group == 32 ? 1 : (group == 64 ? 2 : (group % 128 == 0 ? 4 : 0));
 }
 
+// Bytes of partial tiles a plan leaves (kspg: k-steps per chunk, mt: 16-row tiles of the kernel).
+static size_t plan_bytes(const Plan &p, int N, int K, int group, int kspg, int mt)
+{
+    const bool one_group = kspg < 4 || group % 128 == 0;  // one and eight strips (test hooks) exist there only
+    int nw = p.nw;
+    if (nw != 2 && !(nw == 1 && one_group) && !(nw == 8 && one_group && mt < 3)) nw = 4;
+    size_t bytes = 0;
+    sqp_strip_split(mt, nw, kspg, N, K, p.split, &bytes);
+    return bytes;
+}
+
+// The same for the plan by strips: one group per chunk, row tiles in steps of 16, 32 and 64.
+static size_t strips_bytes(int M, int N, int K, int group)
+{
+    const int kspg = group == 32 ? 1 : (group == 64 ? 2 : 4);
+    return plan_bytes(make_plan(M, N, K, kspg == 4 ? 128 : group, M <= 16 && group == 128), N, K, group, kspg,
+                      M <= 16 ? 1 : (M <= 32 ? 2 : 4));
+}
+
 // The plan a call runs with: the heuristic's, overridden by the test hooks, without a split
 // when there is no workspace to put partial sums in.
 static Plan plan_for(int M, int N, int K, int group, bool have_workspace)
 {
     const int chunk = 32 * chunk_ksteps(K, group);
-    Plan p = chunk == 128 && (M > 16 || group < 128) ? wide_plan(M, N, K, group)
-                                                     : make_plan(M, N, K, chunk, M <= 16 && group == 128);
+    Plan p;
+    if (chunk == 128 && (M > 16 || group < 128)) {
+        p = wide_plan(M, N, K, group);
+        // Where the plan by strips does not split (fewer than eight chunks of K, or 470 and more four-strip
+        // tiles) nothing is split: such a shape reports no workspace, and callers run it beside calls
+        // that use theirs.
+        if (strips_bytes(M, N, K, group) == 0) p.split = 1;
+    } else {
+        p = make_plan(M, N, K, chunk, M <= 16 && group == 128);
+    }
     if (g_force_plan.nw > 0) p = g_force_plan;
     if (g_force_split > 0) p.split = g_force_split;
     if (!have_workspace) p.split = 1;
@@ -245,17 +272,6 @@ extern "C" void sqp_debug_decode_launch(int M, int N, int K, int group, int *nw,
     *kp = p.kp;
 }
 
-// Bytes of partial tiles a plan leaves (kspg: k-steps per chunk, mt: 16-row tiles of the kernel).
-static size_t plan_bytes(const Plan &p, int N, int K, int group, int kspg, int mt)
-{
-    const bool one_group = kspg < 4 || group % 128 == 0;  // one and eight strips (test hooks) exist there only
-    int nw = p.nw;
-    if (nw != 2 && !(nw == 1 && one_group) && !(nw == 8 && one_group && mt < 3)) nw = 4;
-    size_t bytes = 0;
-    sqp_strip_split(mt, nw, kspg, N, K, p.split, &bytes);
-    return bytes;
-}
-
 size_t sqp_gemm_decode_partial_bytes(int M, int N, int K, int group)
 {
     const int kspg = chunk_ksteps(K, group);
@@ -265,15 +281,13 @@ size_t sqp_gemm_decode_partial_bytes(int M, int N, int K, int group)
 }
 
 // What a workspace has to hold at least for a call not to be refused: the partial tiles of the plan
-// by strips (one group per chunk, row tiles in steps of 16, 32 and 64), where wide_plan asks for more.
+// by strips, where wide_plan asks for more.
 // Callers with a buffer of that size are served with fewer K parts.
 size_t sqp_gemm_decode_least_bytes(int M, int N, int K, int group)
 {
     const size_t want = sqp_gemm_decode_partial_bytes(M, N, K, group);
     if (want == 0 || g_force_plan.nw > 0 || g_force_split > 0) return want;
-    const int kspg = group == 32 ? 1 : (group == 64 ? 2 : 4);
-    const size_t strips = plan_bytes(make_plan(M, N, K, kspg == 4 ? 128 : group, M <= 16 && group == 128), N, K, group, kspg,
-                                     M <= 16 ? 1 : (M <= 32 ? 2 : 4));
+    const size_t strips = strips_bytes(M, N, K, group);
     return strips < want ? strips : want;
 }
 

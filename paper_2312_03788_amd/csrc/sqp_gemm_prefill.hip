@@ -586,6 +586,7 @@ struct TileLaunch {
 };
 struct LaunchPlan {
     int wm, count;
+    bool own;  // K parts go to the call's own scratch, not to the workspace
     TileLaunch l[2];
 };
 
@@ -603,13 +604,19 @@ static size_t launch_partial_bytes(const TileLaunch &l, int wm)
     return l.parts >= 2 ? (size_t)l.parts * l.tiles * (32 * l.rt * wm) * (l.nt * 128 / wm) * sizeof(float) : 0;
 }
 
-// room: bytes there are for partial sums (0: none).  A plan in 128-row tiles that needs more is returned as
-// it is and refused by the caller; the estimates below only take what fits.
-static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, size_t room)
+// room_ws, room_own: bytes there are for partial sums in the workspace and in the call's own scratch (0:
+// none).  The workspace serves the shapes whose 128-row tiles are too few for the chip even at half
+// width; all others split only where the call brings its own scratch, because the workspace is shared
+// and callers may run those shapes beside calls that use it.
+// A plan in 128-row tiles that needs more is returned as it is and refused by the caller; the
+// estimates below only take what fits.
+static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, size_t room_ws, size_t room_own)
 {
+    const bool own = g_force_rt == 0 && plan_tiles(M, N, K, group, cus, true).ksplit < 2;
+    const size_t room = own ? room_own : room_ws;
     const bool have_workspace = room > 0;
     const TilePlan p = plan_tiles(M, N, K, group, cus, have_workspace);
-    LaunchPlan q = {p.wm, 0, {}};
+    LaunchPlan q = {p.wm, 0, own, {}};
     const int stages = K / BK, tnf = (N + (4 / p.wm) * 128 - 1) / ((4 / p.wm) * 128);
     if (g_force_rt > 0 && group != 32) {
         const int wg = 128 * g_force_nt;
@@ -688,7 +695,7 @@ static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, size_t 
 // Test hook: the launches of a call (no GPU needed): up to two of (rt, nt, tiles, parts).
 extern "C" int sqp_debug_prefill_launches(int M, int N, int K, int group, int cus, int *out8)
 {
-    const LaunchPlan q = plan_launches(M, N, K, group, cus, SIZE_MAX);
+    const LaunchPlan q = plan_launches(M, N, K, group, cus, SIZE_MAX, SIZE_MAX);
     for (int i = 0; i < q.count; i++) {
         out8[4 * i] = q.l[i].rt;
         out8[4 * i + 1] = q.l[i].nt;
@@ -698,16 +705,28 @@ extern "C" int sqp_debug_prefill_launches(int M, int N, int K, int group, int cu
     return q.count;
 }
 
-size_t sqp_gemm_prefill_partial_bytes(int M, int N, int K, int group)
+static size_t plan_partial_bytes(const LaunchPlan &q)
 {
-    if (group % BK != 0 && !(group == 32 && K % BK == 0)) return sqp_gemm_decode_partial_bytes(M < 64 ? M : 64, N, K, group);  // row-block fallback
-    const LaunchPlan q = plan_launches(M, N, K, group, sqp_compute_units(), SIZE_MAX);
     size_t need = 0;
     for (int i = 0; i < q.count; i++) {
         const size_t b = launch_partial_bytes(q.l[i], q.wm);
         need = b > need ? b : need;
     }
     return need;
+}
+
+size_t sqp_gemm_prefill_partial_bytes(int M, int N, int K, int group)
+{
+    if (group % BK != 0 && !(group == 32 && K % BK == 0)) return sqp_gemm_decode_partial_bytes(M < 64 ? M : 64, N, K, group);  // row-block fallback
+    const LaunchPlan q = plan_launches(M, N, K, group, sqp_compute_units(), SIZE_MAX, 0);
+    return plan_partial_bytes(q);
+}
+
+size_t sqp_gemm_prefill_scratch_bytes(int M, int N, int K, int group)
+{
+    if (group % BK != 0 && !(group == 32 && K % BK == 0)) return 0;
+    const LaunchPlan q = plan_launches(M, N, K, group, sqp_compute_units(), SIZE_MAX, SIZE_MAX);
+    return q.own ? plan_partial_bytes(q) : 0;
 }
 
 // What a workspace has to hold at least for a call not to be refused: the K parts of the plan in 128-row
@@ -736,14 +755,14 @@ int sqp_gemm_prefill(int M, int N, int K, int group, const h16 *x, const uint32_
     // group sizes the tiled kernel does not cover (neither a multiple of 64, nor 32 with K a multiple of 64)
     if (!(group % BK == 0 || (group == 32 && K % BK == 0)))
         return decode_in_row_blocks(M, N, K, group, x, packed, scales, zeros, y, epi, ws, stream);
-    const size_t room = ws.partial ? ws.partial_bytes : 0;
-    if (room > 0 && room < sqp_gemm_prefill_least_bytes(M, N, K, group)) return SQP_ERR_WORKSPACE;
-    const LaunchPlan q = plan_launches(M, N, K, group, sqp_compute_units(), room);
-    for (int i = 0; i < q.count; i++)
-        if (launch_partial_bytes(q.l[i], q.wm) > room) return SQP_ERR_WORKSPACE;
+    const size_t room_ws = ws.partial ? ws.partial_bytes : 0, room_own = ws.own ? ws.own_bytes : 0;
+    if (room_ws > 0 && room_ws < sqp_gemm_prefill_least_bytes(M, N, K, group)) return SQP_ERR_WORKSPACE;
+    const LaunchPlan q = plan_launches(M, N, K, group, sqp_compute_units(), room_ws, room_own);
+    float *const part = q.own ? ws.own : ws.partial;
+    if (plan_partial_bytes(q) > (q.own ? room_own : room_ws)) return SQP_ERR_WORKSPACE;
     for (int i = 0; i < q.count; i++) {
         const TileLaunch &l = q.l[i];
-#define SQP_TILES(RT, NT, WM, G32) launch_variant<RT, NT, WM, G32>(l, M, N, K, group, x, packed, scales, zeros, y, epi, ws.partial, stream)
+#define SQP_TILES(RT, NT, WM, G32) launch_variant<RT, NT, WM, G32>(l, M, N, K, group, x, packed, scales, zeros, y, epi, part, stream)
         if (group == 32) {
             if (l.nt == 4) SQP_TILES(4, 4, 1, true);
             else SQP_TILES(4, 2, 1, true);
@@ -763,7 +782,7 @@ int sqp_gemm_prefill(int M, int N, int K, int group, const h16 *x, const uint32_
 #undef SQP_TILES
         if (l.parts >= 2) {
             const int bm = 32 * l.rt * q.wm, wgn = l.nt * 128 / q.wm;
-            splitk_reduce_kernel<<<dim3(bm * wgn / 2048, (unsigned)l.tiles), 256, 0, stream>>>(ws.partial, M, N, bm, wgn, (int)l.tile0, l.tn, l.parts, y, epi);
+            splitk_reduce_kernel<<<dim3(bm * wgn / 2048, (unsigned)l.tiles), 256, 0, stream>>>(part, M, N, bm, wgn, (int)l.tile0, l.tn, l.parts, y, epi);
         }
     }
     return sqp_launch_status();

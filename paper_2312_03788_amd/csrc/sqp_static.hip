@@ -34,7 +34,7 @@ extern "C" int sqp_w4a16_gemm_static(int M, int N, int K, int group, const void 
             ptr = g_scratch_ptr[dev] = (unsigned char *)p;
         }
     }
-    SqpWorkspace ws;
+    SqpWorkspace ws = {};
     ws.tickets = (unsigned *)ptr;
     ws.partial = (float *)(ptr + SQP_WS_TICKET_BYTES);
     ws.partial_bytes = SQP_STATIC_PARTIAL_BYTES;

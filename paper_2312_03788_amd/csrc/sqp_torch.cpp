@@ -21,11 +21,13 @@ namespace {
 
 typedef int (*GemmFn)(int, int, int, int, const void *, const uint32_t *, const void *, const uint8_t *, void *, void *);
 typedef size_t (*WorkspaceFn)(int, int, int, int);
+typedef int (*ScratchGemmFn)(int, int, int, int, int, const void *, const uint32_t *, const void *, const uint8_t *, void *, void *, size_t, void *);
 typedef int (*RmsnormFn)(int, int, const void *, const void *, float, void *, void *);
 typedef int (*ApplyFn)(int, int, const void *, const float *, void *, void *);
 
 GemmFn g_gemm[3];  // plain, fused activation, static scratch
-WorkspaceFn g_workspace_bytes;
+WorkspaceFn g_workspace_bytes, g_scratch_bytes;
+ScratchGemmFn g_gemm_scratch;
 RmsnormFn g_rmsnorm;
 ApplyFn g_apply_x;
 
@@ -81,13 +83,23 @@ PyObject *gemm(PyObject *, PyObject *const *a, Py_ssize_t n)
         const long M = x->size(0), K = x->size(1), N = packed->size(1);
         if (!fits(M) || !fits(K) || !fits(N) || !fits(group) || packed->size(0) * 8 != K) Py_RETURN_NONE;
         if (which != 2 && g_workspace_bytes((int)M, (int)N, (int)K, (int)group) > held) Py_RETURN_NONE;
-        at::Tensor y;
+        // scratch of this call alone: freed to the allocator's pool of this stream when the call returns, so
+        // whatever takes it next is ordered behind the kernels (with `out` the general path looks
+        // whether the caller may not allocate)
+        const size_t own = which == 2 ? 0 : g_scratch_bytes((int)M, (int)N, (int)K, (int)group);
+        if (own > 0 && a[6] != Py_None) Py_RETURN_NONE;
+        at::Tensor y, scratch;
         if (!output(a[6], *x, M, which == 1 ? N / 2 : N, dev, y)) Py_RETURN_NONE;
         const void *xp = x->data_ptr(), *pp = packed->data_ptr(), *sp = scales->data_ptr(), *zp = zeros->data_ptr();
         void *yp = y.data_ptr();
+        if (own > 0) scratch = at::empty({(long)own}, x->options().dtype(at::kByte));
+        void *op = own > 0 ? scratch.data_ptr() : nullptr;
         int rc;
         Py_BEGIN_ALLOW_THREADS
-        rc = g_gemm[which]((int)M, (int)N, (int)K, (int)group, xp, (const uint32_t *)pp, sp, (const uint8_t *)zp, yp, stream);
+        if (own > 0)
+            rc = g_gemm_scratch((int)M, (int)N, (int)K, (int)group, which, xp, (const uint32_t *)pp, sp, (const uint8_t *)zp, yp, op, own, stream);
+        else
+            rc = g_gemm[which]((int)M, (int)N, (int)K, (int)group, xp, (const uint32_t *)pp, sp, (const uint8_t *)zp, yp, stream);
         Py_END_ALLOW_THREADS
         if (rc != 0) Py_RETURN_NONE;
         return result(a[6], y);
@@ -155,20 +167,23 @@ PyObject *apply_x(PyObject *, PyObject *const *a, Py_ssize_t n)
     }
 }
 
-// bind(addresses of sqp_w4a16_gemm, _silu_mul, _static, _workspace_bytes, sqp_rmsnorm, sqp_smooth_apply_x)
+// bind(addresses of sqp_w4a16_gemm, _silu_mul, _static, _workspace_bytes, sqp_rmsnorm, sqp_smooth_apply_x,
+//      sqp_w4a16_gemm_scratch, _scratch_bytes)
 PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    void *p[6];
-    if (n != 6) {
-        PyErr_SetString(PyExc_TypeError, "bind takes six addresses");
+    void *p[8];
+    if (n != 8) {
+        PyErr_SetString(PyExc_TypeError, "bind takes eight addresses");
         return nullptr;
     }
-    for (int i = 0; i < 6; i++) p[i] = PyLong_AsVoidPtr(a[i]);
+    for (int i = 0; i < 8; i++) p[i] = PyLong_AsVoidPtr(a[i]);
     if (PyErr_Occurred()) return nullptr;
     for (int i = 0; i < 3; i++) g_gemm[i] = (GemmFn)p[i];
     g_workspace_bytes = (WorkspaceFn)p[3];
     g_rmsnorm = (RmsnormFn)p[4];
     g_apply_x = (ApplyFn)p[5];
+    g_gemm_scratch = (ScratchGemmFn)p[6];
+    g_scratch_bytes = (WorkspaceFn)p[7];
     Py_RETURN_NONE;
 }
 

@@ -323,8 +323,8 @@ def test_companion_outputs_between_guards(orc, sqp, K, N, group):
     assert np.array_equal(wi.numpy()[:, 0::2].view(np.uint16), w.view(np.uint16))
 
 
-@pytest.mark.parametrize("M,K,N,group", [(56, 768, 10240, 128), (40, 1024, 520, 64), (65, 2048, 520, 128), (130, 1024, 264, 32),
-                                         (150, 1536, 1032, 256), (2050, 2048, 8144, 128)])
+@pytest.mark.parametrize("M,K,N,group", [(56, 1024, 2056, 128), (40, 1024, 520, 64), (65, 2048, 520, 128), (130, 1024, 264, 32),
+                                         (150, 1536, 1032, 256)])
 def test_workspace_between_least_and_preferred(orc, sqp, M, K, N, group):
     """Buffers from the least size (nothing beside the tickets, where that is 0) to the preferred one: a
     plan that fits runs, inside its buffer; 16 bytes below the least size the call is refused."""
@@ -356,6 +356,114 @@ def test_workspace_between_least_and_preferred(orc, sqp, M, K, N, group):
     finally:
         torch.cuda.synchronize()
         sqp.set_workspace(0)
+
+
+@pytest.mark.parametrize("M,K,N,group,fused", [(2050, 2048, 8144, 128, 0), (660, 2048, 5184, 64, 1)])
+def test_scratch_of_one_call(orc, sqp, M, K, N, group, fused):
+    """Grids that fill the chip: no workspace asked for and none touched; with a scratch buffer of the
+    call's own the K parts stay inside it, whatever its size; a misaligned one is refused."""
+    print("case scratch", M, K, N, group, fused, flush=True)
+    L = sqp.lib()
+    want = int(L.sqp_w4a16_gemm_scratch_bytes(M, N, K, group))
+    assert sqp.workspace_bytes(M, N, K, group) == 0 and want > 0
+    xs, p, sc, z = _layer(orc, M, K, N, group)
+    dx, dp, dsc, dz = _dev(xs), _dev(p), _dev(sc), _dev(z)
+    rows = np.unique(np.linspace(0, M - 1, 24).astype(int))
+    y_ref, t_ref = orc.w4a16_gemm_ref(np.ascontiguousarray(xs[rows]), p, sc, z, group)
+    NY = N // 2 if fused else N
+    y, ws = Guarded(2 * M * NY, torch.float16, (M, NY)), Guarded(1 << 20)
+    st = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    call = lambda own, size: L.sqp_w4a16_gemm_scratch(M, N, K, group, fused, _ptr(dx), _ptr(dp), _ptr(dsc), _ptr(dz), y.ptr, own,
+                                                      ctypes.c_size_t(size), st)
+    outs = []
+    try:
+        _set_ws(L, ws.ptr, 1 << 20)
+        torch.cuda.synchronize()
+        ws.body[TICKET_BYTES:] = FILL
+        for size in (0, 16, want // 3 // 16 * 16, want - 16, want):
+            own = Guarded(size)
+            y.view().zero_()
+            assert call(own.ptr if size else None, size) == 0, size
+            torch.cuda.synchronize()
+            if not fused:
+                ok, worst, nbad = gemm_tolerance_ok(orc, y.numpy()[rows], y_ref, t_ref)
+                assert ok, (size, worst, nbad)
+            outs.append(y.numpy().copy())
+            own.check("scratch")
+            y.check("y")
+        assert (ws.body.cpu().numpy()[TICKET_BYTES:] == FILL).all(), "the shared workspace was written"
+        # the binding passes a buffer of the preferred size, with and without an output
+        fn = sqp.w4a16_gemm_silu_mul if fused else sqp.w4a16_gemm
+        out = torch.empty((M, NY), dtype=torch.float16, device="cuda")
+        for got in (fn(dx, dp, dsc, dz, group), fn(dx, dp, dsc, dz, group, out=out)):
+            assert np.array_equal(got.cpu().numpy().view(np.uint16), outs[-1].view(np.uint16))
+        if fused:  # the plain product's gate and up, each fp16-rounded (2^-11) and summed in another order
+            gu = sqp.w4a16_gemm(dx, dp, dsc, dz, group).double()
+            h = torch.nn.functional.silu(gu[:, 0::2]) * gu[:, 1::2]
+            for o in outs:
+                d = (torch.from_numpy(o).cuda().double() - h).abs()
+                assert bool((d <= 4 * 2.0 ** -11 * h.abs() + 2.0 ** -10 * gu[:, 1::2].abs() * gu[:, 0::2].abs() + 1e-3).all())
+        assert call(ctypes.c_void_p(own.raw.data_ptr() + GUARD + 8), want) == -3
+    finally:
+        torch.cuda.synchronize()
+        sqp.set_workspace(0)
+
+
+def test_prefill_beside_decode_on_another_stream(orc, sqp):
+    """A prompt whose tiles fill the chip on one stream beside split decode calls on another, through the
+    binding: each gives the bits it gives alone.  (The prompt's shape reports no workspace, so the
+    two need no ordering.)"""
+    print("case two streams", flush=True)
+    pre, dec = (2050, 2048, 8144, 128), (16, 2048, 328, 128)
+    assert sqp.workspace_bytes(pre[0], pre[2], pre[1], pre[3]) == 0 and sqp.workspace_bytes(dec[0], dec[2], dec[1], dec[3]) > 0
+    args = []
+    for (M, K, N, g) in (pre, dec):
+        xs, p, sc, z = _layer(orc, M, K, N, g)
+        args.append((_dev(xs), _dev(p), _dev(sc), _dev(z), g))
+    sqp.set_workspace(32 << 20)
+    try:
+        alone = [sqp.w4a16_gemm(*a) for a in args]
+        torch.cuda.synchronize()
+        streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+        outs = [[], []]
+        for _ in range(12):
+            for i, reps in ((0, 1), (1, 8)):
+                with torch.cuda.stream(streams[i]):
+                    outs[i] += [sqp.w4a16_gemm(*args[i]) for _ in range(reps)]
+        torch.cuda.synchronize()
+        for i in (0, 1):
+            for y in outs[i]:
+                assert torch.equal(y, alone[i])
+    finally:
+        torch.cuda.synchronize()
+        sqp.set_workspace(0)
+
+
+def test_scratch_under_capture(orc, sqp):
+    """Under graph capture a call that is given its output allocates nothing and takes the plan without K
+    parts; one that is not takes scratch from the graph's pool, as its output.  Replays are bit-identical
+    to the eager calls, with eager work in between."""
+    M, K, N, g = 2050, 2048, 8144, 128
+    xs, p, sc, z = _layer(orc, M, K, N, g)
+    dx, dp, dsc, dz = _dev(xs), _dev(p), _dev(sc), _dev(z)
+    y_ref, t_ref = orc.w4a16_gemm_ref(np.ascontiguousarray(xs[-4:]), p, sc, z, g)
+    eager = sqp.w4a16_gemm(dx, dp, dsc, dz, g)
+    given = torch.empty_like(eager)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        own = sqp.w4a16_gemm(dx, dp, dsc, dz, g)
+        sqp.w4a16_gemm(dx, dp, dsc, dz, g, out=given)
+    first = None
+    for _ in range(3):
+        own.zero_(), given.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(own, eager)
+        ok, worst, nbad = gemm_tolerance_ok(orc, given[-4:].cpu().numpy(), y_ref, t_ref)
+        assert ok, (worst, nbad)
+        first = given.clone() if first is None else first
+        assert torch.equal(given, first) and torch.equal(sqp.w4a16_gemm(dx, dp, dsc, dz, g), eager)
 
 
 def test_native_marshalling_equals_general_path(orc, sqp):

@@ -221,6 +221,27 @@ def test_prefill_launches_invariants(L):
     assert L.sqp_debug_prefill_launches(3001, 44032, 8192, 128, 256, out) == 2 and tuple(out[4:8]) == (4, 2, 32, 8)
 
 
+def test_calls_that_touch_no_workspace(L):
+    """Shapes with work for the whole chip never split through the workspace, which all calls of a device
+    share: callers run them beside calls that use it.  More tiles of 128 x 512 than a quarter of the
+    compute units (256 where there is no GPU), or at most 64 rows and fewer than eight chunks of K."""
+    for (M, N, K, group) in [(2048, 10240, 8192, 128), (3001, 44032, 8192, 128), (320, 44032, 8192, 128), (2050, 8144, 2048, 128),
+                             (640, 8192, 8192, 128), (700, 8200, 1024, 64), (700, 8200, 1024, 32)]:
+        assert -(-M // 128) * -(-N // 512) > 64
+        assert L.sqp_w4a16_gemm_workspace_bytes(M, N, K, group) == L.sqp_w4a16_gemm_workspace_least_bytes(M, N, K, group) == 0
+        assert L.sqp_w4a16_gemm_scratch_bytes(M, N, K, group) <= 48 << 20
+    assert L.sqp_w4a16_gemm_scratch_bytes(2048, 10240, 8192, 128) > 0
+    for group in (64, 128, 256):
+        for M in (17, 33, 48, 49, 64):
+            for (K, N) in [(512, 8), (512, 264), (768, 10240), (768, 1024), (256, 22016)]:
+                if group >= 128:
+                    assert L.sqp_w4a16_gemm_workspace_bytes(M, N, K, group) == 0, (M, N, K, group)
+                assert L.sqp_w4a16_gemm_scratch_bytes(M, N, K, group) == 0
+    # few tiles: the workspace serves them, and they need no scratch
+    for (M, N, K, group) in [(160, 8192, 8192, 128), (256, 2056, 4096, 64), (65, 520, 2048, 128)]:
+        assert L.sqp_w4a16_gemm_workspace_bytes(M, N, K, group) > 0 and L.sqp_w4a16_gemm_scratch_bytes(M, N, K, group) == 0
+
+
 def test_quant_loss_argument_errors(L):
     P = ctypes.c_void_p
     good, odd, null = P(0x1000), P(0x1008), P(0)
