@@ -170,7 +170,8 @@ int sqp_set_workspace(void *dev_ptr, size_t bytes, void *stream);
 /* Quantisation loss of one layer, Eq. 4:  *loss = || x w - x_hat w_hat ||_F^2  with
  * w_hat the dequantised weights of (packed, scales, zeros) (Eq. 1) - the quantity the search
  * over the smoothing strength alpha minimises (Sec 2.2, Eq. 6), for one layer.  Both products
- * are accumulated together in fp32 (the difference is formed before any rounding to fp16),
+ * are accumulated together in fp32, 16 k of each in turn (the difference is formed before any
+ * rounding to fp16, and rounding is relative to it and not to x w),
  * the squares are summed in fp64 in a fixed order (run-to-run deterministic).
  *   x     [M][K] fp16  calibration activations        w [K][N] fp16  the unsmoothed weight
  *   x_hat [M][K] fp16  smoothed activations (Eq. 5)   packed/scales/zeros: quantised smoothed weight
@@ -201,8 +202,7 @@ int sqp_w4a16_gemm_static(int M, int N, int K, int group, const void *x, const u
 
 /* Search of the smoothing strength for one layer (Sec 2.2: alpha is chosen on a grid to
  * minimise the quantisation loss of Eq. 4; the paper's grid is 0, 0.05, ..., 1).  The
- * per-channel maxima of Eq. 6 and the product x_cal * w do not depend on alpha and are computed
- * once (the product where w_s has room to hold it meanwhile, in fp32); then for each
+ * per-channel maxima of Eq. 6 do not depend on alpha and are computed once; then for each
  * alphas[i], in order:  s = Eq. 6,  x_hat = x_cal / s and w_s = s * w (Eq. 5),  w_s quantised
  * (Eq. 1),  loss[i] = Eq. 4 on the calibration rows.  *best = index of the smallest loss (the
  * lowest index on ties).  loss[i] equals what the entry points above would give, bit for bit.

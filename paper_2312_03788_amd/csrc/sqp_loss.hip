@@ -3,16 +3,14 @@
 // with X_hat = X diag(s)^-1 and the quantised W_hat of diag(s) W (Eq. 5), as the search over the
 // smoothing strength alpha needs it (Sec 2.2: alpha is chosen to minimise the loss).
 //
-// The two products are never rounded to fp16: that would swamp their difference.  Two kernels:
-//
-//   loss_split_kernel (K a multiple of 128, groups of 32 or a multiple of 64: every layer of the
-//     paper's models): acc = X W over all of K, then acc -= X_hat W_hat over all of K, one fp32
-//     accumulator per output element throughout.  X W does not depend on alpha, so the search
-//     runs the first half once, keeps the accumulators (fp32) in device memory, and starts the
-//     second half of every alpha from them: half the matrix work per alpha, and the same bits as
-//     a single call, which runs both halves in one launch.
-//   quant_loss_kernel (any other K or group): both products interleaved k-step by k-step.
-//
+// The two products are never rounded to fp16: that would swamp their difference.  For the same reason
+// they are one contraction over the concatenated inner dimension [X, X_hat] * [W; -W_hat], taken 16 k
+// of the one and 16 k of the other in turn into one fp32 accumulator per output element, which
+// thus stays near the difference: summed one after the other, every rounding would be relative to
+// |X W| with its outlier channels (an order of magnitude more at K = 5120).  Two kernels do that:
+//   loss_tile_kernel   K a multiple of 64, groups of 32 or a multiple of 64: every layer of the paper's
+//                      models
+//   quant_loss_kernel  any other K or group
 // A workgroup owns a 128 x 128 tile, squares and sums its accumulators in fp64 and writes one
 // partial; a second kernel adds the partials in a fixed order, so the result does not depend on
 // scheduling.
@@ -24,36 +22,36 @@ namespace {
 
 constexpr int LBM = 128, LBN = 128, LBK = 64, LPAD = 8;  // row stride 144 bytes: 16-byte reads of 32 rows spread over the banks
 
-// ---------------------------------------------------------------- both halves, one after the other
+// ---------------------------------------------------------------- wave tiles of 64 x 64
 //
 // Eight waves: wave (kh, wm, wn) owns rows 64 wm .. +64 and columns 64 wn .. +64 of the tile (2 x 2
-// tiles of v_mfma_f32_32x32x16_f16) for the k's of half kh of every 128-k stage; the two halves'
-// sums meet in LDS.  A wave tile of 64 x 64 and not smaller, because the reads of X_hat from LDS
-// bound the kernel otherwise: 64 x 32 per wave asks for 128 bytes per clock and compute unit, all
-// that LDS gives, 64 x 64 for half of it.  The K halves give two waves per SIMD (one unpacks while
-// the other multiplies) without smaller tiles.
-//   X W: tiles through registers into LDS, W transposed on the way (8 rows x 2 columns per
-//     thread, v_perm_b32), the next stage's loads in flight while one is multiplied.
-//   X_hat W_hat: X_hat by direct global->LDS loads into a ring of three 32 KB slots (rows of
-//     256 bytes, 16-byte pieces XOR-swizzled by row so that a read of 32 rows spreads over the
-//     banks), packed words straight into registers (a word is one lane's B operand), two stages in
-//     flight, one barrier per stage; loads and waits in assembly as in the GEMM kernels.  The search
-//     stores X_hat with every 8 k in the order of the unpacked codes (MODE 2): no permute here.
+// tiles of v_mfma_f32_32x32x16_f16) for the k's of half kh of every 64-k stage; the two halves'
+// sums meet in LDS.  A wave tile of 64 x 64 and not smaller, because the reads of fragments from LDS
+// bound the kernel otherwise (six 16-byte reads per lane feed eight MFMAs; five feed four with 64 x 32).
+// The K halves give two waves per SIMD (one unpacks while the other multiplies) without smaller tiles.
+//   X, X_hat: direct global->LDS loads into a ring of three slots (rows of 128 bytes, 16-byte pieces
+//     XOR-swizzled by row so that a read of 32 rows spreads over the banks).
+//   W: through registers into one of two LDS buffers, transposed on the way (8 rows x 2 columns per
+//     lane, v_perm_b32): fetched one stage ahead of X, written while the stage in front is multiplied.
+//   W_hat: packed words straight into registers (a word is one lane's B operand).
+// Two stages in flight, one barrier per stage; loads and waits in assembly as in the GEMM kernels.
+// CODE: X_hat is stored with every 8 k in the order of the unpacked codes (the search does that): no
+// permute here.
 // Column mapping: accumulator tile t, lane l: column 64 wn + 2 (l % 32) + t (two adjacent columns
 // per lane: 8-byte loads of packed words).
-// MODE: 0 = both halves, partials[block];  1 = X W only, accumulators to yacc;  2 = X_hat W_hat
-// starting from yacc, partials[block].  yacc: [block][wm, wn][register / 4][lane][4] floats.
-// What bounds it: the memory pipeline (48 KB per stage and compute unit out of L2), the unpack and the
-// matrix cores take 0.4 to 0.5 us of a stage each and overlap in part: 1.0 us per stage (1.2 with all
-// loads of a stage issued at once).  Reads from LDS and a fourth ring slot change nothing.
-// Measured on 512 x 5120 x 5120 (160 tiles): second half 46 us, first half 75 us, both in one call
-// 114 us, where the interleaved kernel takes 147 (8192 x 8192: 188 against 230).  The loss is off its
-// 64-bit value by up to 7e-8 relative, as with the interleaved kernel.
-constexpr int SBK = 128;                      // k per stage
-constexpr int SSLOT = LBM * SBK * 2;          // bytes of X_hat per stage
-constexpr int SROW = SBK + LPAD;              // halves per LDS row of the X W tiles
+// What bounds it: the loads (52 KB per stage and compute unit out of L2) and the matrix cores, which
+// overlap in part: 1.1 us per stage, of which the MFMAs are 0.45 (timing probes on 512 x 5120 x 5120, 92
+// us complete: 74 without MFMAs, 82 without W's way, 57 without both, 90 without the unpack, 93 without
+// the reads from LDS).  Measured against quant_loss_kernel: 512 x 5120 x 5120 (160 tiles) 153 -> 88 us,
+// 512 x 8192 x 8192 292 -> 173, 64 x 4096 x 4096 in groups of 64 171 -> 68; rounding as there, 0.5 to 1.3
+// times 2^-24 sqrt(K / 16) of a sum of 16 products.
+constexpr int SBK = 64;                       // k per stage
+constexpr int SHALF = LBM * SBK * 2;          // bytes of X (and of X_hat) per stage
+constexpr int SSLOT = 2 * SHALF;
+constexpr int SROW = (SBK + LPAD) * 2;        // bytes per LDS row of W
+constexpr int SWBUF = LBN * SROW;
 
-// PREP (MODE 2; 0 or the group size): the workgroups past row loss_rows of the grid, as many as the loss
+// PREP (0 or the group size): the workgroups past row loss_rows of the grid, as many as the loss
 // leaves compute units idle, prepare the next alpha meanwhile: weight tiles smoothed and quantised in
 // turn, activations divided.
 struct NextAlpha {
@@ -65,15 +63,16 @@ struct NextAlpha {
     uint8_t *zeros;
     int loss_rows, workgroups;
 };
-template <int MODE, bool G32, int PREP>
+template <bool G32, bool CODE, int PREP>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
-loss_split_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, const h16 *__restrict__ w,
-                  const h16 *__restrict__ xh, const uint32_t *__restrict__ packed, const h16 *__restrict__ scales,
-                  const uint8_t *__restrict__ zeros, float *__restrict__ yacc, double *__restrict__ partials, NextAlpha next)
+loss_tile_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, const h16 *__restrict__ w,
+                 const h16 *__restrict__ xh, const uint32_t *__restrict__ packed, const h16 *__restrict__ scales,
+                 const uint8_t *__restrict__ zeros, double *__restrict__ partials, NextAlpha next)
 {
-    constexpr int D = 3;                      // ring slots / register stages of the second half
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[D * SSLOT];
+    constexpr int D = 3;                      // ring slots and register stages
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[D * SSLOT + 2 * SWBUF];
     __shared__ double red[8];
+    static_assert(sizeof(lds) + sizeof(red) <= 160 * 1024, "LDS of a workgroup");
     if constexpr (PREP != 0) {
         if ((int)blockIdx.y >= next.loss_rows) {
             typedef QuantizeTile<PREP, 512> Tile;
@@ -93,7 +92,6 @@ loss_split_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, con
             return;
         }
     }
-    static_assert(2 * 128 * SROW * 2 <= D * SSLOT && 4 * 64 * 64 * 4 <= D * SSLOT, "the tiles of X W and the exchange reuse the ring");
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -104,6 +102,7 @@ loss_split_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, con
     const int stages = K / SBK;
     const int ncol = n0 + wn * 64 + 2 * l32;                   // this lane's two columns (N is even: both in or out)
     const bool ncol_ok = ncol < N;
+    const UnpackConsts uc = SQP_UNPACK_CONSTS;
 
     f32x16 acc[2][2];
 #pragma unroll
@@ -113,8 +112,239 @@ loss_split_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, con
 #pragma unroll
             for (int r = 0; r < 16; r++) acc[mt][t][r] = 0.f;
 
+    struct Stage {
+        u32x2 w[2];   // per k-step of 16 of this wave's half: the packed words of the lane's two columns
+        uint32_t sc;  // two fp16 steps
+        uint32_t zr;  // two zero points, one byte each
+    };
+    // Wave-uniform byte pointers, stepped per stage; past the last stage they stop and the look-ahead
+    // re-reads it.  Lanes past the last column read column 0, rows past M read row M - 1: defined data
+    // whose results are masked at the end.
+    const int col = ncol_ok ? ncol : 0;
+    const uint32_t voff_p = (uint32_t)(kb * N + col) * 4u, voff_s = (uint32_t)col * 2u, voff_z = (uint32_t)col;
+    const uint32_t voff_w = n0 + 2 * lane < N ? (uint32_t)(n0 + 2 * lane) * 2u : 0u;  // W: this lane's column pair
+    const long nrow = (long)N * 2;            // one row of W in bytes
+    const unsigned char *pq = reinterpret_cast<const unsigned char *>(packed) + (long)kh * 8 * nrow;  // 32 k: four packed rows
+    const unsigned char *xq = reinterpret_cast<const unsigned char *>(x), *hq = reinterpret_cast<const unsigned char *>(xh);
+    const unsigned char *wq = reinterpret_cast<const unsigned char *>(w) + (long)wave * 8 * nrow;     // this wave's 8 rows of a stage
+    const int spg = G32 ? 1 : __builtin_amdgcn_readfirstlane(group / SBK);  // stages per group (G32: two groups per stage)
+    int kin = 0;                              // position of the stage being issued in its group
+    int prow = G32 ? kh : 0;                  // its parameter row
+    int ist = 0, wst = 0;                     // stage being issued: of X, X_hat and W_hat; of W
+    // X, X_hat: wave w copies blocks w and w + 8 of the stage (a block = 8 rows x 128 bytes); lane i of a
+    // block handles row i / 8 and fetches piece (i % 8) ^ ((row / 2) % 8) of it
+    uint32_t xoff[2];
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+        const int row = (wave + 8 * j) * 8 + (lane >> 3);
+        const int grow = m0 + row < M ? m0 + row : M - 1;
+        xoff[j] = (uint32_t)grow * (uint32_t)K * 2u + (uint32_t)(((lane & 7) ^ ((row >> 1) & 7)) * 16);
+    }
+    constexpr int OG = 16;                    // loads per wave and stage: X 2, X_hat 2, words 2, steps, zero points, W 8
+    // A stage's loads go out in four parts, one in front of every four MFMAs of the stage in progress (in two
+    // parts they hold the waves up in front of their arithmetic: 92 us against 84 on 512 x 5120 x 5120).
+    auto issue_x_part = [&](Stage &st, int slot, int j) {
+        unsigned char *dst = lds + slot * SSLOT + wave * 1024;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(xq + xoff[j]),
+                                         (__attribute__((address_space(3))) void *)(dst + j * 8192), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(hq + xoff[j]),
+                                         (__attribute__((address_space(3))) void *)(dst + SHALF + j * 8192), 16, 0, 0);
+        if (j == 0) {
+            const unsigned char *p1 = pq + 4 * nrow;
+            asm volatile("global_load_dwordx2 %[w0], %[vp], %[p0]\n\t"
+                         "global_load_dwordx2 %[w1], %[vp], %[p1]"
+                         : [w0] "=&v"(st.w[0]), [w1] "=&v"(st.w[1])
+                         : [vp] "v"(voff_p), [p0] "s"(pq), [p1] "s"(p1)
+                         : "memory");
+            return;
+        }
+        const long row = (long)__builtin_amdgcn_readfirstlane(prow) * N;
+        const unsigned char *sg = reinterpret_cast<const unsigned char *>(scales) + row * 2, *zg = zeros + row;
+        asm volatile("global_load_dword %[sc], %[vs], %[sg]\n\t"
+                     "global_load_ushort %[zr], %[vz], %[zg]"
+                     : [sc] "=&v"(st.sc), [zr] "=&v"(st.zr)
+                     : [vs] "v"(voff_s), [vz] "v"(voff_z), [sg] "s"(sg), [zg] "s"(zg)
+                     : "memory");
+        const bool more = ist + 1 < stages;
+        ist += more ? 1 : 0;
+        pq += more ? 16 * nrow : 0;
+        xq += more ? SBK * 2 : 0;
+        hq += more ? SBK * 2 : 0;
+        if constexpr (G32) {
+            prow += more ? 2 : 0;
+        } else {
+            kin += more ? 1 : 0;
+            const bool wrap = kin == spg;
+            kin = wrap ? 0 : kin;
+            prow += wrap ? 1 : 0;
+        }
+    };
+    auto issue_x = [&](Stage &st, int slot) {
+        issue_x_part(st, slot, 0);
+        issue_x_part(st, slot, 1);
+    };
+    auto issue_w_part = [&](uint32_t (&r)[8], int h) {
+        const unsigned char *b[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) b[i] = wq + (4 * h + i) * nrow;  // wave-uniform
+        asm volatile("global_load_dword %[r0], %[v], %[b0]\n\t"
+                     "global_load_dword %[r1], %[v], %[b1]\n\t"
+                     "global_load_dword %[r2], %[v], %[b2]\n\t"
+                     "global_load_dword %[r3], %[v], %[b3]"
+                     : [r0] "=&v"(r[4 * h]), [r1] "=&v"(r[4 * h + 1]), [r2] "=&v"(r[4 * h + 2]), [r3] "=&v"(r[4 * h + 3])
+                     : [v] "v"(voff_w), [b0] "s"(b[0]), [b1] "s"(b[1]), [b2] "s"(b[2]), [b3] "s"(b[3])
+                     : "memory");
+        if (h == 0) return;
+        const bool more = wst + 1 < stages;
+        wst += more ? 1 : 0;
+        wq += more ? (long)SBK * nrow : 0;
+    };
+    auto issue_w = [&](uint32_t (&r)[8]) {
+        issue_w_part(r, 0);
+        issue_w_part(r, 1);
+    };
+    auto tie_w = [&](uint32_t (&r)[8]) {       // no use ahead of the wait in front
+#pragma unroll
+        for (int i = 0; i < 8; i++) asm volatile("" : "+v"(r[i]));
+    };
+    // The pair of columns of W this lane holds -> two LDS rows (column 2 c of a wave's 64 in row c, column
+    // 2 c + 1 in row 32 + c), 8 k each.  Written in assembly, like every LDS access of the loop: the
+    // compiler would wait for all direct loads in flight.
+    const uint32_t wwr = (uint32_t)(size_t)lds + (uint32_t)(D * SSLOT + ((lane >> 5) * 64 + l32) * SROW + wave * 16);
+    auto store_w = [&](const uint32_t (&r)[8], int buf) {
+        u32x4 c0, c1;  // the low halves of the 8 rows; the high halves
+        c0.x = __builtin_amdgcn_perm(r[1], r[0], 0x05040100u); c1.x = __builtin_amdgcn_perm(r[1], r[0], 0x07060302u);
+        c0.y = __builtin_amdgcn_perm(r[3], r[2], 0x05040100u); c1.y = __builtin_amdgcn_perm(r[3], r[2], 0x07060302u);
+        c0.z = __builtin_amdgcn_perm(r[5], r[4], 0x05040100u); c1.z = __builtin_amdgcn_perm(r[5], r[4], 0x07060302u);
+        c0.w = __builtin_amdgcn_perm(r[7], r[6], 0x05040100u); c1.w = __builtin_amdgcn_perm(r[7], r[6], 0x07060302u);
+        const uint32_t a = wwr + (uint32_t)(buf * SWBUF);
+        asm volatile("ds_write_b128 %0, %1" ::"v"(a), "v"(c0) : "memory");
+        asm volatile("ds_write_b128 %0, %1 offset:%2" ::"v"(a), "v"(c1), "n"(32 * SROW) : "memory");
+    };
+
+    // LDS addresses of this lane's fragments: X and X_hat (row 64 wm + l32, + 32 for the second row tile),
+    // W (row 64 wn + l32, + 32 for the second column)
+    const uint32_t xrd = (uint32_t)(size_t)lds + (uint32_t)((wm * 64 + l32) * 128);
+    const int xkey = (l32 >> 1) & 7;
+    const uint32_t wrd = (uint32_t)(size_t)lds + (uint32_t)(D * SSLOT + (wn * 64 + l32) * SROW + kh * 64 + kb * 16);
+
+    Stage st[D];
+    uint32_t wr[D][8];
+    int buf = 0;                               // LDS buffer of W of the stage being consumed
+    // Stage s (slot and register stage d = s % 3): its X, X_hat and W_hat, and W of stage s + 1, have landed
+    // for this wave once all but the youngest group of loads have; after the barrier that holds for all
+    // waves, W of stage s is in its buffer, and no wave reads the slot or the buffer of stage s - 1
+    // any more, which are filled meanwhile: with W of stage s + 1 out of registers, and the loads
+    // of stage s + 2 (W: s + 3, into the registers that held W of stage s).
+    auto iteration = [&](Stage &cur, Stage &fill, uint32_t (&w_next)[8], uint32_t (&w_fill)[8], int slot, int fill_slot) {
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(OG) : "memory");
+#pragma unroll
+        for (int ks = 0; ks < 2; ks++) asm volatile("" : "+v"(cur.w[ks]));
+        asm volatile("" : "+v"(cur.sc));
+        asm volatile("" : "+v"(cur.zr));
+        tie_w(w_next);
+        asm volatile("s_barrier" ::: "memory");
+        u32x4 xa[2][2], xb[2][2], wb[2][2];    // fragments of X, X_hat and W: [k-step][row or column tile]
+        auto read = [&](int ks) {
+            const uint32_t a = xrd + (uint32_t)(slot * SSLOT) + (uint32_t)(((kh * 4 + ks * 2 + kb) ^ xkey) * 16);
+            const uint32_t b = wrd + (uint32_t)(buf * SWBUF + ks * 32);
+            asm volatile("ds_read_b128 %0, %1" : "=&v"(xa[ks][0]) : "v"(a) : "memory");
+            asm volatile("ds_read_b128 %0, %1 offset:4096" : "=&v"(xa[ks][1]) : "v"(a) : "memory");
+            asm volatile("ds_read_b128 %0, %1" : "=&v"(wb[ks][0]) : "v"(b) : "memory");
+            asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(wb[ks][1]) : "v"(b), "n"(32 * SROW) : "memory");
+            asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(xb[ks][0]) : "v"(a), "n"(SHALF) : "memory");
+            asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(xb[ks][1]) : "v"(a), "n"(SHALF + 4096) : "memory");
+        };
+        read(0);
+        h16x2 neg_hi[2], neg_lo[2], delta[2];
+#pragma unroll
+        for (int t = 0; t < 2; t++) {
+            const uint32_t z = (cur.zr >> (8 * t)) & 0xffu;
+            neg_hi[t] = neg_hi_of(z);
+            neg_lo[t] = neg_lo_of(z);
+            const uint32_t sw = cur.sc ^ 0x80008000u;  // the negated steps
+            delta[t] = __builtin_bit_cast(h16x2, __builtin_amdgcn_perm(sw, sw, t ? 0x03020302u : 0x01000100u));
+        }
+#pragma unroll
+        for (int ks = 0; ks < 2; ks++) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+            for (int i = 0; i < 2; i++) {
+                asm volatile("" : "+v"(xa[ks][i]));
+                asm volatile("" : "+v"(xb[ks][i]));
+                asm volatile("" : "+v"(wb[ks][i]));
+            }
+            if (ks == 0) {
+                read(1);
+                issue_x_part(fill, fill_slot, 0);
+            } else {
+                store_w(w_next, buf ^ 1);
+                issue_w_part(w_fill, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            // X W of 16 k, the words of X_hat W_hat unpacked between the MFMAs (the scheduler is told so), then
+            // X_hat W_hat of the same 16 k
+            h16x8 b[2], a[2];
+#pragma unroll
+            for (int t = 0; t < 2; t++) b[t] = dequant_word_scaled(cur.w[ks][t], neg_hi[t], neg_lo[t], delta[t], uc);
+#pragma unroll
+            for (int mt = 0; mt < 2; mt++) a[mt] = CODE ? __builtin_bit_cast(h16x8, xb[ks][mt]) : permute_x(xb[ks][mt]);
+#pragma unroll
+            for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+                for (int t = 0; t < 2; t++)
+                    acc[mt][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h16x8, xa[ks][mt]),
+                                                                        __builtin_bit_cast(h16x8, wb[ks][t]), acc[mt][t], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);            // 1 MFMA
+                __builtin_amdgcn_sched_group_barrier(0x002, CODE ? 7 : 9, 0);  // VALU
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (ks == 0) issue_x_part(fill, fill_slot, 1);
+            else issue_w_part(w_fill, 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+                for (int t = 0; t < 2; t++)
+                    acc[mt][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[mt], b[t], acc[mt][t], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        buf ^= 1;
+    };
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // nothing of the compiler's own is counted below
+    issue_w(wr[0]);
+    issue_x(st[0], 0);
+    issue_w(wr[1]);
+    issue_x(st[1], 1);
+    issue_w(wr[2]);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * OG) : "memory");
+    tie_w(wr[0]);
+    store_w(wr[0], 0);
+    for (int s = 0;;) {
+        iteration(st[0], st[2], wr[1], wr[0], 0, 2);
+        if (++s == stages) break;
+        iteration(st[1], st[0], wr[2], wr[1], 1, 0);
+        if (++s == stages) break;
+        iteration(st[2], st[1], wr[0], wr[2], 2, 1);
+        if (++s == stages) break;
+    }
+    // the look-ahead loads still in flight land in registers and slots that nothing else may use before
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int j = 0; j < D; j++) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ks++) asm volatile("" ::"v"(st[j].w[ks]));
+        asm volatile("" ::"v"(st[j].sc));
+        asm volatile("" ::"v"(st[j].zr));
+#pragma unroll
+        for (int i = 0; i < 8; i++) asm volatile("" ::"v"(wr[j][i]));
+    }
+
     // the second half's waves (kh == 1) hand their sums to the first's: acc(kh = 0) += acc(kh = 1)
-    auto join = [&]() {
+    {
+        static_assert(4 * 64 * 64 * 4 <= D * SSLOT, "the exchange reuses the ring");
         f32x4 *ex = reinterpret_cast<f32x4 *>(lds) + (size_t)(wave & 3) * 16 * 64 + lane;
         __syncthreads();
         if (kh == 1) {
@@ -132,307 +362,53 @@ loss_split_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, con
 #pragma unroll
                 for (int r = 0; r < 4; r++) acc[q >> 3][(q >> 2) & 1][(q & 3) * 4 + r] += v[r];
             }
-        } else {
-#pragma unroll
-            for (int mt = 0; mt < 2; mt++)
-#pragma unroll
-                for (int t = 0; t < 2; t++)
-#pragma unroll
-                    for (int r = 0; r < 16; r++) acc[mt][t][r] = 0.f;
-        }
-        __syncthreads();
-    };
-
-    if constexpr (MODE != 2) {
-        // ---- X W
-        h16 (*sx)[SROW] = reinterpret_cast<h16 (*)[SROW]>(lds);
-        h16 (*sw)[SROW] = reinterpret_cast<h16 (*)[SROW]>(lds + 128 * SROW * 2);
-        const int arow = tid >> 2, apart = tid & 3;            // X: row, 32-half part of the 128 k
-        const int agrow = m0 + arow < M ? m0 + arow : M - 1;   // rows past M: duplicates, masked at the end
-        const int wkb = tid >> 6, wcp = tid & 63;              // W: k-blocks wkb and wkb + 8 of 8 rows, column pair
-        const int wcol = n0 + 2 * wcp < N ? n0 + 2 * wcp : 0;  // columns past N likewise
-        const h16 *px = x + (size_t)agrow * K + apart * 32;
-        const h16 *pw = w + (size_t)(wkb * 8) * N + wcol;
-        const int wrow = (wcp >> 5) * 64 + (wcp & 31);         // LDS row of the pair's first column; the second's is 32 further
-        u32x4 rx[4];
-        uint32_t rw[2][8];
-        auto fetch = [&]() {
-#pragma unroll
-            for (int j = 0; j < 4; j++) rx[j] = *reinterpret_cast<const u32x4 *>(px + j * 8);
-#pragma unroll
-            for (int h = 0; h < 2; h++)
-#pragma unroll
-                for (int i = 0; i < 8; i++) rw[h][i] = *reinterpret_cast<const uint32_t *>(pw + (size_t)(h * 64 + i) * N);
-            px += SBK;
-            pw += (size_t)SBK * N;
-        };
-        fetch();
-        for (int s = 0; s < stages; s++) {
-#pragma unroll
-            for (int j = 0; j < 4; j++) *reinterpret_cast<u32x4 *>(&sx[arow][apart * 32 + j * 8]) = rx[j];
-#pragma unroll
-            for (int h = 0; h < 2; h++) {
-                uint4 c0, c1;  // the low halves of the 8 rows; the high halves
-                c0.x = __builtin_amdgcn_perm(rw[h][1], rw[h][0], 0x05040100u); c1.x = __builtin_amdgcn_perm(rw[h][1], rw[h][0], 0x07060302u);
-                c0.y = __builtin_amdgcn_perm(rw[h][3], rw[h][2], 0x05040100u); c1.y = __builtin_amdgcn_perm(rw[h][3], rw[h][2], 0x07060302u);
-                c0.z = __builtin_amdgcn_perm(rw[h][5], rw[h][4], 0x05040100u); c1.z = __builtin_amdgcn_perm(rw[h][5], rw[h][4], 0x07060302u);
-                c0.w = __builtin_amdgcn_perm(rw[h][7], rw[h][6], 0x05040100u); c1.w = __builtin_amdgcn_perm(rw[h][7], rw[h][6], 0x07060302u);
-                *reinterpret_cast<uint4 *>(&sw[wrow][h * 64 + wkb * 8]) = c0;
-                *reinterpret_cast<uint4 *>(&sw[wrow + 32][h * 64 + wkb * 8]) = c1;
-            }
-            __syncthreads();
-            if (s + 1 < stages) fetch();
-#pragma unroll
-            for (int ks = 0; ks < 4; ks++) {
-                const int kk = kh * 64 + ks * 16 + kb * 8;
-                h16x8 a[2], b[2];
-#pragma unroll
-                for (int i = 0; i < 2; i++) {
-                    a[i] = *reinterpret_cast<const h16x8 *>(&sx[wm * 64 + i * 32 + l32][kk]);
-                    b[i] = *reinterpret_cast<const h16x8 *>(&sw[wn * 64 + i * 32 + l32][kk]);
-                }
-#pragma unroll
-                for (int mt = 0; mt < 2; mt++)
-#pragma unroll
-                    for (int t = 0; t < 2; t++)
-                        acc[mt][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[mt], b[t], acc[mt][t], 0, 0, 0);
-            }
-            __syncthreads();
-        }
-        join();
-        if constexpr (MODE == 1) {
-            if (kh == 0) {
-                f32x4 *yo = reinterpret_cast<f32x4 *>(yacc) + ((size_t)block * 4 + wave) * 16 * 64 + lane;
-#pragma unroll
-                for (int q = 0; q < 16; q++) {
-                    const f32x16 &a = acc[q >> 3][(q >> 2) & 1];
-                    yo[q * 64] = f32x4{a[(q & 3) * 4], a[(q & 3) * 4 + 1], a[(q & 3) * 4 + 2], a[(q & 3) * 4 + 3]};
-                }
-            }
-            return;
-        }
-    } else {
-        if (kh == 0) {
-            const f32x4 *yi = reinterpret_cast<const f32x4 *>(yacc) + ((size_t)block * 4 + wave) * 16 * 64 + lane;
-#pragma unroll
-            for (int q = 0; q < 16; q++) {
-                const f32x4 v = yi[q * 64];
-#pragma unroll
-                for (int r = 0; r < 4; r++) acc[q >> 3][(q >> 2) & 1][(q & 3) * 4 + r] = v[r];
-            }
         }
     }
-
-    if constexpr (MODE != 1) {
-        // ---- - X_hat W_hat
-        constexpr int NQ = G32 ? 2 : 1;       // quantisation groups per half stage (64 k)
-        constexpr int OX = 4, OW = 4 + 2 * NQ;  // loads per wave and stage: X_hat, words and group parameters
-        const UnpackConsts uc = SQP_UNPACK_CONSTS;
-        struct Stage {
-            u32x2 w[4];       // per k-step of 16: the packed words of the lane's two columns
-            uint32_t sc[NQ];  // two fp16 steps
-            uint32_t zr[NQ];  // two zero points, one byte each
-        };
-        const int col = ncol_ok ? ncol : 0;
-        const uint32_t voff_w = (uint32_t)(kb * N + col) * 4u, voff_s = (uint32_t)col * 2u, voff_z = (uint32_t)col;
-        const long wrow2 = (long)N * 8;       // two packed rows (one k-step) in bytes
-        // wave-uniform byte pointers, stepped per stage; past the last stage they stop and the
-        // look-ahead re-reads it
-        const unsigned char *wq = reinterpret_cast<const unsigned char *>(packed) + (long)kh * 4 * wrow2;
-        const unsigned char *xq = reinterpret_cast<const unsigned char *>(xh);
-        const int hpg = G32 ? 1 : __builtin_amdgcn_readfirstlane(group / 64);  // half stages per group (G32: two groups per half stage)
-        int kin = hpg == 1 ? 0 : kh;           // position of this wave's half stage in its group
-        int prow = G32 ? kh * 2 : (hpg == 1 ? kh : 0);  // parameter row of the half stage being issued
-        int ist = 0;                           // stage being issued
-        // X_hat: wave w copies blocks w, w + 8, ... of the stage (a block = 4 rows x 256 bytes); lane i
-        // of a block handles row i / 16 and fetches piece (i % 16) ^ (row % 16) of it
-        uint32_t xoff[OX];
+    // ---- sum of squares of the tile.  Register r of row tile mt: row 8*(r/4) + 4*(lane/32) + r%4
+    double ss = 0.0;
+    if (kh == 0) {
 #pragma unroll
-        for (int j = 0; j < OX; j++) {
-            const int row = (wave + 8 * j) * 4 + (lane >> 4);
-            const int grow = m0 + row < M ? m0 + row : M - 1;
-            xoff[j] = (uint32_t)grow * (uint32_t)K * 2u + (uint32_t)(((lane & 15) ^ (row & 15)) * 16);
-        }
-        // One quarter of a stage's loads (spread over the k-steps of the stage in progress: all at once they
-        // fill the memory pipeline and hold the waves up in front of their arithmetic).
-        auto issue_part = [&](Stage &st, int slot, int part) {
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(xq + xoff[part]),
-                                             (__attribute__((address_space(3))) void *)(lds + slot * SSLOT + (wave + 8 * part) * 1024), 16, 0, 0);
-            const unsigned char *base = wq + part * wrow2;  // wave-uniform
-            asm volatile("global_load_dwordx2 %0, %1, %2" : "=v"(st.w[part]) : "v"(voff_w), "s"(base) : "memory");
-            if (part < NQ) {
-                const long row = (long)__builtin_amdgcn_readfirstlane(prow + part) * N;  // wave-uniform
-                const unsigned char *sg = reinterpret_cast<const unsigned char *>(scales) + row * 2, *zg = zeros + row;
-                asm volatile("global_load_dword %0, %1, %2" : "=v"(st.sc[part]) : "v"(voff_s), "s"(sg) : "memory");
-                asm volatile("global_load_ushort %0, %1, %2" : "=v"(st.zr[part]) : "v"(voff_z), "s"(zg) : "memory");
-            }
-            if (part < 3) return;
-            // step to the next stage, unless this was the last
-            const bool more = ist + 1 < stages;
-            ist += more ? 1 : 0;
-            wq += more ? 8 * wrow2 : 0;
-            xq += more ? SBK * 2 : 0;
-            if constexpr (G32) {
-                prow += more ? 4 : 0;
-            } else {                           // groups of 64: two rows per stage
-                kin += more ? 2 : 0;
-                if (kin >= hpg) { kin -= hpg; prow++; }
-                if (kin >= hpg) { kin -= hpg; prow++; }
-            }
-        };
-        auto issue = [&](Stage &st, int slot) {
+        for (int mt = 0; mt < 2; mt++)
 #pragma unroll
-            for (int i = 0; i < 4; i++) issue_part(st, slot, i);
-        };
-        auto landed = [&](Stage &st) {         // all but the youngest stage's loads have arrived
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(OX + OW) : "memory");
+            for (int t = 0; t < 2; t++)
 #pragma unroll
-            for (int ks = 0; ks < 4; ks++) asm volatile("" : "+v"(st.w[ks]));
-#pragma unroll
-            for (int g = 0; g < NQ; g++) {
-                asm volatile("" : "+v"(st.sc[g]));
-                asm volatile("" : "+v"(st.zr[g]));
-            }
-        };
-        // LDS address of this lane's A fragment (row 64 wm + l32, + 32 for the second row tile) in slot 0
-        const uint32_t xrd = (uint32_t)(size_t)lds + (uint32_t)((wm * 64 + l32) * 256);
-        const int xkey = l32 & 15;
-        // stage st in `slot`, with the loads into stage nst and slot nslot in between
-        auto compute = [&](const Stage &st, int slot, Stage &nst, int nslot) {
-            u32x4 xa[2][2];
-            auto read_a = [&](int ks) {
-                const uint32_t a = xrd + (uint32_t)(slot * SSLOT) + (uint32_t)(((kh * 8 + ks * 2 + kb) ^ xkey) * 16);
-                asm volatile("ds_read_b128 %0, %1" : "=&v"(xa[ks & 1][0]) : "v"(a) : "memory");
-                asm volatile("ds_read_b128 %0, %1 offset:8192" : "=&v"(xa[ks & 1][1]) : "v"(a) : "memory");
-            };
-            read_a(0);
-            h16x2 neg_hi[NQ][2], neg_lo[NQ][2], delta[NQ][2];
-#pragma unroll
-            for (int g = 0; g < NQ; g++)
-#pragma unroll
-                for (int t = 0; t < 2; t++) {
-                    const uint32_t z = (st.zr[g] >> (8 * t)) & 0xffu;
-                    neg_hi[g][t] = neg_hi_of(z);
-                    neg_lo[g][t] = neg_lo_of(z);
-                    const uint32_t sw = st.sc[g] ^ 0x80008000u;  // the negated steps
-                    delta[g][t] = __builtin_bit_cast(h16x2, __builtin_amdgcn_perm(sw, sw, t ? 0x03020302u : 0x01000100u));
+                for (int r = 0; r < 16; r++) {
+                    const int row = m0 + wm * 64 + mt * 32 + 8 * (r >> 2) + 4 * kb + (r & 3);
+                    if (row < M && ncol_ok) ss += (double)acc[mt][t][r] * (double)acc[mt][t][r];
                 }
-            // The fragments of the next k-step are on their way from LDS, and its words are unpacked
-            // between the MFMAs of this one (the scheduler is told so: left alone it puts the read and
-            // its wait next to each other and the unpack in front of the MFMAs).
-            h16x8 b[2][2];
-            auto unpack = [&](int ks) {
-                const int g = G32 ? ks >> 1 : 0;
-#pragma unroll
-                for (int t = 0; t < 2; t++) b[ks & 1][t] = dequant_word_scaled(st.w[ks][t], neg_hi[g][t], neg_lo[g][t], delta[g][t], uc);
-            };
-            unpack(0);
-#pragma unroll
-            for (int ks = 0; ks < 4; ks++) {
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-                for (int mt = 0; mt < 2; mt++) asm volatile("" : "+v"(xa[ks & 1][mt]));
-                if (ks < 3) read_a(ks + 1);
-                issue_part(nst, nslot, ks);
-                __builtin_amdgcn_sched_barrier(0);
-                if (ks < 3) unpack(ks + 1);
-#pragma unroll
-                for (int mt = 0; mt < 2; mt++) {
-                    // (MODE 2: the search stores X_hat in the order of the unpacked codes)
-                    const h16x8 a = MODE == 2 ? __builtin_bit_cast(h16x8, xa[ks & 1][mt]) : permute_x(xa[ks & 1][mt]);
-#pragma unroll
-                    for (int t = 0; t < 2; t++)
-                        acc[mt][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b[ks & 1][t], acc[mt][t], 0, 0, 0);
-                }
-                if constexpr (MODE != 2) __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);  // first operand: 4 VALU
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // 1 MFMA
-                __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        };
-        Stage st[D];
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // nothing of the compiler's own is counted below
-        issue(st[0], 0);
-        issue(st[1], 1);
-        const int nblk = (stages + D - 1) / D;
-        for (int b = 0; b < nblk; b++) {
-#pragma unroll
-            for (int d = 0; d < D; d++) {
-                // Stage s = b D + d has landed for this wave; after the barrier for all of them,
-                // and no wave reads the slot of stage s - 1 any more, which is filled next.
-                // Stages past the end only keep the load counts in step.
-                landed(st[d]);
-                asm volatile("s_barrier" ::: "memory");
-                if (b * D + d < stages) compute(st[d], d, st[(d + 2) % D], (d + 2) % D);
-                else issue(st[(d + 2) % D], (d + 2) % D);
-            }
-        }
-        // the look-ahead loads still in flight land in registers and slots that nothing else may use before
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-#pragma unroll
-        for (int j = 0; j < D; j++) {
-#pragma unroll
-            for (int ks = 0; ks < 4; ks++) asm volatile("" ::"v"(st[j].w[ks]));
-#pragma unroll
-            for (int g = 0; g < NQ; g++) {
-                asm volatile("" ::"v"(st[j].sc[g]));
-                asm volatile("" ::"v"(st[j].zr[g]));
-            }
-        }
-        join();
-
-        // ---- sum of squares of the tile.  Register r of row tile mt: row 8*(r/4) + 4*(lane/32) + r%4
-        double ss = 0.0;
-        if (kh == 0) {
-#pragma unroll
-            for (int mt = 0; mt < 2; mt++)
-#pragma unroll
-                for (int t = 0; t < 2; t++)
-#pragma unroll
-                    for (int r = 0; r < 16; r++) {
-                        const int row = m0 + wm * 64 + mt * 32 + 8 * (r >> 2) + 4 * kb + (r & 3);
-                        if (row < M && ncol_ok) ss += (double)acc[mt][t][r] * (double)acc[mt][t][r];
-                    }
-        }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 64);
-        if (lane == 0) red[wave] = ss;
-        __syncthreads();
-        if (tid == 0) partials[block] = (red[0] + red[1]) + (red[2] + red[3]);
     }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 64);
+    if (lane == 0) red[wave] = ss;
+    __syncthreads();
+    if (tid == 0) partials[block] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// Whether loss_split_kernel covers a shape.
-bool loss_split_covers(int K, int group) { return K % SBK == 0 && (group == 32 || group % 64 == 0); }
+// Whether loss_tile_kernel covers a shape.
+bool loss_tile_covers(int K, int group) { return K % SBK == 0 && (group == 32 || group % SBK == 0); }
 
-template <int MODE>
-void launch_loss_split(int M, int N, int K, int group, const void *x, const void *w, const void *x_hat, const uint32_t *packed,
-                       const void *scales, const uint8_t *zeros, float *yacc, double *partials, hipStream_t st)
+template <bool CODE>
+void launch_loss_tile(int M, int N, int K, int group, const void *x, const void *w, const void *x_hat, const uint32_t *packed,
+                      const void *scales, const uint8_t *zeros, double *partials, hipStream_t st)
 {
     const dim3 grid((N + LBN - 1) / LBN, (M + LBM - 1) / LBM);
     if (group == 32)
-        loss_split_kernel<MODE, true, 0><<<grid, 512, 0, st>>>(M, N, K, group, (const h16 *)x, (const h16 *)w, (const h16 *)x_hat, packed,
-                                                               (const h16 *)scales, zeros, yacc, partials, NextAlpha());
+        loss_tile_kernel<true, CODE, 0><<<grid, 512, 0, st>>>(M, N, K, group, (const h16 *)x, (const h16 *)w, (const h16 *)x_hat, packed,
+                                                              (const h16 *)scales, zeros, partials, NextAlpha());
     else
-        loss_split_kernel<MODE, false, 0><<<grid, 512, 0, st>>>(M, N, K, group, (const h16 *)x, (const h16 *)w, (const h16 *)x_hat, packed,
-                                                                (const h16 *)scales, zeros, yacc, partials, NextAlpha());
+        loss_tile_kernel<false, CODE, 0><<<grid, 512, 0, st>>>(M, N, K, group, (const h16 *)x, (const h16 *)w, (const h16 *)x_hat, packed,
+                                                               (const h16 *)scales, zeros, partials, NextAlpha());
 }
 
-// The second half of one alpha beside the preparation of the next (groups of 32, 64, 128, 256).
-void launch_loss_and_next(int M, int N, int K, int group, const void *x_hat, const uint32_t *packed, const void *scales,
-                          const uint8_t *zeros, float *yacc, double *partials, NextAlpha next, hipStream_t st)
+// The loss of one alpha beside the preparation of the next (groups of 32, 64, 128, 256).
+void launch_loss_and_next(int M, int N, int K, int group, const void *x, const void *w, const void *x_hat, const uint32_t *packed,
+                          const void *scales, const uint8_t *zeros, double *partials, NextAlpha next, hipStream_t st)
 {
     const int gx = (N + LBN - 1) / LBN, gy = (M + LBM - 1) / LBM;
     next.loss_rows = gy;
     const dim3 grid(gx, gy + (next.workgroups + gx - 1) / gx);
 #define SQP_LOSS_NEXT(G32, G) \
-    loss_split_kernel<2, G32, G><<<grid, 512, 0, st>>>(M, N, K, group, nullptr, nullptr, (const h16 *)x_hat, packed, (const h16 *)scales, zeros, yacc, partials, next)
+    loss_tile_kernel<G32, true, G><<<grid, 512, 0, st>>>(M, N, K, group, (const h16 *)x, (const h16 *)w, (const h16 *)x_hat, packed, (const h16 *)scales, zeros, partials, next)
     if (group == 32) SQP_LOSS_NEXT(true, 32);
     else if (group == 64) SQP_LOSS_NEXT(false, 64);
     else if (group == 128) SQP_LOSS_NEXT(false, 128);
@@ -440,12 +416,10 @@ void launch_loss_and_next(int M, int N, int K, int group, const void *x_hat, con
 #undef SQP_LOSS_NEXT
 }
 
-// ---------------------------------------------------------------- both products interleaved
+// ---------------------------------------------------------------- any K and group
 //
-// One contraction over the concatenated inner dimension [X, X_hat] * [W; -W_hat]: per k-step one
-// MFMA with the fp16 weights and one with the negated dequantised codes; eight waves with tiles of
-// 64 x 32, all tiles through registers into LDS, packed words unpacked in registers.  The global
-// loads of the next k-step are issued before the current one is multiplied.
+// Eight waves with tiles of 64 x 32, all tiles through registers into LDS, packed words unpacked in
+// registers.  The global loads of the next k-step are issued before the current one is multiplied.
 
 // FULL: M and N are multiples of the tile and K of the k-step, so no access needs a bounds check.
 template <bool FULL>
@@ -628,8 +602,8 @@ extern "C" int sqp_quant_loss(int M, int N, int K, int group, const void *x, con
     const int gy = (M + LBM - 1) / LBM, gx = (N + LBN - 1) / LBN;
     if (gy > 65535) return SQP_ERR_SHAPE;
     hipStream_t st = (hipStream_t)stream;
-    if (loss_split_covers(K, group))
-        launch_loss_split<0>(M, N, K, group, x, w, x_hat, packed, scales, zeros, nullptr, scratch, st);
+    if (loss_tile_covers(K, group))
+        launch_loss_tile<false>(M, N, K, group, x, w, x_hat, packed, scales, zeros, scratch, st);
     else if (M % LBM == 0 && N % LBN == 0 && K % LBK == 0)
         quant_loss_kernel<true><<<dim3(gx, gy), 512, 0, st>>>(M, N, K, group, (const h16 *)x, (const h16 *)w, (const h16 *)x_hat,
                                                              packed, (const h16 *)scales, zeros, scratch);
@@ -662,28 +636,25 @@ extern "C" int sqp_alpha_search(int T, int N, int K, int group, int n_alpha, con
     // every check any step below would make has passed: from here on only launch errors can occur
     hipStream_t st = (hipStream_t)stream;
     rc = sqp_channel_absmax(T, K, N, x_cal, w, amax, st);
-    // X W once for all alphas.  Its accumulators, the factors of all alphas and the tile sums live in
-    // w_s, which the search otherwise fills with the smoothed weight: here the quantisation
-    // smooths the weight as it reads it, and w_s gets the last alpha's smoothed weight at the end.
-    // Taken wherever they fit there, i.e. from about K = 2 T on (4 bytes per element of the padded
-    // [T][N] against 2 per element of [K][N]); shorter K runs the single calls in turn.
-    // Measured, 21 alphas on 512 x 5120 x 5120: 4.71 -> 1.26 ms.
+    // The factors of all alphas and the tile sums live in w_s, which the search otherwise fills with
+    // the smoothed weight: here the quantisation smooths the weight as it reads it, and w_s gets the
+    // last alpha's smoothed weight at the end.  Taken wherever they fit there (N from about twice the
+    // number of alphas on); narrower layers run the single calls in turn.
     const size_t blocks = (size_t)((T + LBM - 1) / LBM) * ((N + LBN - 1) / LBN);
-    const size_t ybytes = blocks * LBM * LBN * sizeof(float), fbytes = (size_t)n_alpha * K * sizeof(float);
-    if (loss_split_covers(K, group) && ybytes + fbytes + n_alpha * blocks * sizeof(double) <= (size_t)K * N * sizeof(h16)) {
-        float *yacc = (float *)w_s, *factors = (float *)((unsigned char *)w_s + ybytes);
-        double *tile_sums = (double *)((unsigned char *)w_s + ybytes + fbytes);
+    const size_t fbytes = (size_t)n_alpha * K * sizeof(float);
+    if (loss_tile_covers(K, group) && fbytes + n_alpha * blocks * sizeof(double) <= (size_t)K * N * sizeof(h16)) {
+        float *factors = (float *)w_s;
+        double *tile_sums = (double *)((unsigned char *)w_s + fbytes);
         if (rc == SQP_OK) rc = sqp_smooth_factors(K, n_alpha, alphas, amax, factors, st);
         if (rc == SQP_OK) rc = sqp_smooth_factor(K, alphas[n_alpha - 1], amax, s, st);
         if (rc != SQP_OK) return rc;
-        launch_loss_split<1>(T, N, K, group, x_cal, w, nullptr, nullptr, nullptr, nullptr, yacc, nullptr, st);
         // Where the loss tiles leave at least a quarter of the chip idle (160 of 256 on 512 x 5120), the next
         // alpha is prepared there meanwhile, into a second set of buffers behind the tile sums; the last
-        // alpha uses the caller's set.  Per alpha on 512 x 5120 x 5120: 69 us one after the other, 56 beside.
+        // alpha uses the caller's set.  Per alpha on 512 x 5120 x 5120: 108 us one after the other, 88 beside.
         const int idle = sqp_compute_units() - (int)(blocks < 65536 ? blocks : 65536);
         auto up256 = [](size_t v) { return (v + 255) & ~(size_t)255; };
         const size_t rows = (size_t)(K / group);
-        const size_t at_packed = up256(ybytes + fbytes + n_alpha * blocks * sizeof(double));
+        const size_t at_packed = up256(fbytes + n_alpha * blocks * sizeof(double));
         const size_t at_scales = up256(at_packed + (size_t)K / 8 * N * 4), at_zeros = up256(at_scales + rows * N * 2);
         const size_t at_x = up256(at_zeros + rows * N), end = at_x + (size_t)T * K * sizeof(h16);
         const bool beside = 4 * idle >= sqp_compute_units() && (group == 32 || group == 64 || group == 128 || group == 256) &&
@@ -702,9 +673,9 @@ extern "C" int sqp_alpha_search(int T, int N, int K, int group, int n_alpha, con
             if (beside && i + 1 < n_alpha) {
                 const NextAlpha next = {factors + (size_t)(i + 1) * K, (const uint4 *)x_cal, (const uint4 *)w, (uint4 *)nxt.x_hat,
                                         nxt.packed, (uint16_t *)nxt.scales, nxt.zeros, 0, idle};
-                launch_loss_and_next(T, N, K, group, cur.x_hat, cur.packed, cur.scales, cur.zeros, yacc, tile_sums + i * blocks, next, st);
+                launch_loss_and_next(T, N, K, group, x_cal, w, cur.x_hat, cur.packed, cur.scales, cur.zeros, tile_sums + i * blocks, next, st);
             } else {
-                launch_loss_split<2>(T, N, K, group, nullptr, nullptr, cur.x_hat, cur.packed, cur.scales, cur.zeros, yacc, tile_sums + i * blocks, st);
+                launch_loss_tile<true>(T, N, K, group, x_cal, w, cur.x_hat, cur.packed, cur.scales, cur.zeros, tile_sums + i * blocks, st);
             }
         }
         sum_partials_kernel<<<n_alpha, 256, 0, st>>>(tile_sums, (long)blocks, loss);

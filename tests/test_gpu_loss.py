@@ -10,10 +10,10 @@ from gpu_util import dev, host
 pytestmark = pytest.mark.gpu
 
 # Tolerance of the loss.  The kernel forms d = x w - x_hat w_hat per output element in one fp32
-# accumulator over 2K products; its error e is about sqrt(2K) 2^-24 times the size of the
-# partial sums (~4e-6 |y| at K = 8192).  E = sum d^2 changes by 2 sum d e, i.e. by about
-# 2 |e| / |d| relatively, and |d| is a few per cent of |y| for 4-bit weights: <~ 1e-3 if all
-# errors lined up, far less with random signs.
+# accumulator over 2K products, 16 of the one and 16 of the other in turn; its error e is about
+# sqrt(K / 16) 2^-24 times the size of a sum of 16 products (~1e-7 |y|).  E = sum d^2 changes by
+# 2 sum d e, i.e. by about 2 |e| / |d| relatively, and |d| is a few per cent of |y| for 4-bit
+# weights: far below this bar, which also covers codes that differ (none do).
 LOSS_RTOL = 2e-3
 
 
@@ -35,9 +35,10 @@ def _oracle_chain(orc, xcal, w, alpha, group):
 @pytest.mark.parametrize("M,K,N,group,alpha", [
     (4, 1024, 1024, 128, 0.5), (37, 264, 72, 24, 0.25), (130, 512, 136, 64, 0.85), (129, 40, 8, 8, 0.5),
     (512, 2048, 520, 128, 0.5), (300, 1024, 1000, 256, 0.0),
-    (256, 1024, 384, 128, 0.5), (128, 192, 128, 32, 0.3),  # whole tiles only (the variant without bounds checks)
-    # one product after the other: one row, one column octet, one stage; groups of 1.5 stages; two groups per half stage
-    (1, 128, 8, 64, 0.5), (257, 384, 200, 192, 0.5), (129, 256, 72, 32, 0.35)])
+    (256, 1024, 384, 128, 0.5), (128, 192, 128, 32, 0.3),  # whole tiles only
+    (128, 192, 128, 96, 0.3),                              # likewise, any group (the variant without bounds checks)
+    # one row, one column octet, one and two stages; groups of three stages; two groups per stage; rows past a tile
+    (1, 64, 8, 64, 0.5), (1, 128, 8, 64, 0.5), (257, 384, 200, 192, 0.5), (129, 256, 72, 32, 0.35), (70, 320, 136, 320, 0.5)])
 def test_quant_loss_parity(orc, sqp, M, K, N, group, alpha):
     print("case loss", M, K, N, group, alpha, flush=True)
     _, xcal, w = wl.layer_inputs(1, K, N)
@@ -47,6 +48,32 @@ def test_quant_loss_parity(orc, sqp, M, K, N, group, alpha):
     e2 = float(host(sqp.quant_loss(dev(xcal), dev(w), dev(xh), dev(p), dev(sc), dev(z), group))[0])
     assert e == e2, "not deterministic"
     assert abs(e - e_ref) <= LOSS_RTOL * e_ref, (e, e_ref)
+
+
+@pytest.mark.parametrize("M,K,N,group,big", [
+    (64, 5120, 128, 128, 0), (64, 5120, 128, 128, 2), (64, 8192, 72, 128, 2), (200, 5120, 136, 32, 2), (64, 5120, 128, 64, 0),
+    (64, 5376, 128, 256, 2), (64, 3072, 128, 96, 2)])
+def test_quant_loss_rounding_is_that_of_the_difference(sqp, M, K, N, group, big):
+    """A weight that its codes give exactly and x_hat = x: the true loss is 0 and what comes back is
+    rounding alone, with 1 % of the channels 50 times larger and `big` of them 1000 times.  The two products
+    alternate every 16 k, so a sum of 16 products p is rounded once, by at most 2^-23 |p|, and
+    then taken off again: rms 2 2^-24 a sqrt(K / 16) with a = sqrt(sum of 16 (x w)^2); the bound is
+    1.5 times that (measured 0.5 to 1.3 of 2^-24 a sqrt(K / 16)).  Summed one after the other the
+    roundings are relative to the whole of x w: 7.5 and more at K = 5120."""
+    print("case loss rounding", M, K, N, group, big, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K + group)
+    gain = torch.ones(K, device="cuda")
+    order = torch.randperm(K, generator=gen, device="cuda")
+    gain[order[:K // 100]] = 50.0
+    gain[order[:big]] = 1000.0
+    x = (torch.randn((M, K), generator=gen, device="cuda") * gain).half()
+    w = (torch.randn((K, N), generator=gen, device="cuda") * 0.02 / gain.sqrt()[:, None]).half()
+    q = sqp.quantize_pack(w, group)
+    w_hat = sqp.dequantize(*q, group)
+    loss = float(sqp.quant_loss(x, w_hat, x, *q, group))
+    a2 = float((x.double().square() @ w_hat.double().square()).sum()) / (K / 16)   # sum over the elements of a^2
+    assert loss <= (3 * 2.0 ** -24) ** 2 * a2 * (K / 16), (loss / a2 / (K / 16)) ** 0.5 * 2 ** 24
 
 
 def test_quant_loss_exact_integers(orc, sqp):
@@ -122,14 +149,16 @@ def test_alpha_search_equals_single_calls(orc, sqp):
 
 
 @pytest.mark.parametrize("T,K,N,group,n", [
-    (40, 640, 128, 128, 3),    # the product with the unsmoothed weight kept in w_s; one tile, five stages
+    (40, 640, 128, 128, 3),    # one tile, ten stages
     (129, 1408, 200, 64, 3),   # two tiles of rows, the second with one row; ragged columns
-    (64, 1024, 256, 256, 3),   # groups of two stages; the next alpha prepared beside the loss
+    (64, 1024, 256, 256, 3),   # groups of four stages; the next alpha prepared beside the loss
     (30, 2048, 200, 64, 3), (20, 1408, 264, 128, 2), (17, 2048, 136, 32, 3), (20, 1408, 264, 128, 1), (33, 2304, 520, 128, 4),  # likewise
     (1, 768, 136, 384, 3),     # a group size whose quantise kernel reads twice
-    (200, 1152, 328, 32, 3),   # two groups per half stage
-    (130, 384, 136, 32, 3),    # K too short for w_s to hold the product: single calls in turn
-    (70, 192, 72, 64, 3)])     # K not a multiple of 128: the interleaved loss kernel
+    (200, 1152, 328, 32, 3),   # two groups per stage
+    (130, 384, 136, 32, 3),
+    (130, 384, 8, 32, 4),      # N too narrow for w_s to hold the factors: single calls in turn
+    (70, 192, 72, 64, 3), (5, 64, 16, 64, 2),  # three stages, one stage
+    (70, 240, 72, 40, 3)])     # K not a multiple of 64: the loss kernel for any group
 def test_alpha_search_routes_equal_single_calls(sqp, T, K, N, group, n):
     """Every route of the search gives the losses of the single calls bit for bit, and leaves the
     last alpha's factors, activations, weight and codes in its work buffers."""
