@@ -110,6 +110,13 @@ def _native(t):
     return _fast is not None and isinstance(t, torch.Tensor) and t.is_cuda
 
 
+def _ended(y, what):
+    """The native call's result: its output, or SqpError for the code the library returned."""
+    if type(y) is int:
+        _check(y, what)
+    return y
+
+
 _workspaces = {}  # device index -> torch buffer handed to the library (kept alive here)
 _held = {}        # device index -> size of the one in use
 
@@ -211,7 +218,7 @@ def smooth_apply_x(x, s, out=None):
     if _native(x):
         o = _fast.apply_x(x, s, out, *_here())
         if o is not None:
-            return o
+            return _ended(o, "sqp_smooth_apply_x")
     M, K = x.shape
     o = out if out is not None else torch.empty_like(x)
     _check(lib().sqp_smooth_apply_x(M, K, _dev(x, torch.float16, "x"), _dev(s, torch.float32, "s"),
@@ -262,7 +269,7 @@ def w4a16_gemm(x, packed, scales, zeros, group=128, out=None):
         dev, stream = _here()
         y = _fast.gemm(0, x, packed, scales, zeros, group, out, dev, stream, _held.get(dev, 0))
         if y is not None:
-            return y
+            return _ended(y, "sqp_w4a16_gemm")
     return _gemm(0, x, packed, scales, zeros, group, out)
 
 
@@ -273,7 +280,7 @@ def w4a16_gemm_static(x, packed, scales, zeros, group=128, out=None):
     if _native(x):
         y = _fast.gemm(2, x, packed, scales, zeros, group, out, *_here(), 0)
         if y is not None:
-            return y
+            return _ended(y, "sqp_w4a16_gemm_static")
     M, K = x.shape
     N = packed.shape[1]
     if packed.shape[0] * 8 != K:
@@ -291,7 +298,7 @@ def w4a16_gemm_silu_mul(x, packed, scales, zeros, group=128, out=None):
         dev, stream = _here()
         y = _fast.gemm(1, x, packed, scales, zeros, group, out, dev, stream, _held.get(dev, 0))
         if y is not None:
-            return y
+            return _ended(y, "sqp_w4a16_gemm_silu_mul")
     return _gemm(1, x, packed, scales, zeros, group, out)
 
 
@@ -300,7 +307,7 @@ def rmsnorm(x, gamma, eps, out=None):
     if _native(x):
         y = _fast.rmsnorm(x, gamma, eps, out, *_here())
         if y is not None:
-            return y
+            return _ended(y, "sqp_rmsnorm")
     M, H = x.shape
     y = out if out is not None else torch.empty_like(x)
     _check(lib().sqp_rmsnorm(M, H, _dev(x, torch.float16, "x"), _dev(gamma, torch.float16, "gamma"), float(eps),

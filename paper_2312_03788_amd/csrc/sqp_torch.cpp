@@ -5,9 +5,12 @@
 // that the binding loaded).
 //
 // Every function returns the output tensor, or None for anything but the plain case (wrong type,
-// device, layout or shape, tensor subclasses, a workspace that has to grow, an error code): the
-// binding then takes its general path, which reports the error.  Tensor methods may throw (nested
-// tensors have no size in every dimension), so all of them are called inside a try block.  The library's
+// device, layout or shape, tensor subclasses, a workspace that has to grow): nothing has been enqueued
+// then, and the binding takes its general path, which reports the error.  Once the library has been
+// called its code is the result: an error comes back as an integer, never as None, because the call
+// may have been enqueued all the same (the status also carries errors of earlier work) and must not run
+// twice.  Tensor methods may throw (nested tensors have no size in every dimension), so all of
+// them are called inside a try block.  The library's
 // calls run without the GIL, as under ctypes: a launch may have to wait for room in the queue.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
@@ -55,8 +58,9 @@ bool output(PyObject *out, const at::Tensor &like, long rows, long cols, long de
     return true;
 }
 
-PyObject *result(PyObject *out, const at::Tensor &y)
+PyObject *result(int rc, PyObject *out, const at::Tensor &y)
 {
+    if (rc != 0) return PyLong_FromLong(rc);
     if (out == Py_None) return THPVariable_Wrap(y);
     Py_INCREF(out);
     return out;
@@ -101,8 +105,7 @@ PyObject *gemm(PyObject *, PyObject *const *a, Py_ssize_t n)
         else
             rc = g_gemm[which]((int)M, (int)N, (int)K, (int)group, xp, (const uint32_t *)pp, sp, (const uint8_t *)zp, yp, stream);
         Py_END_ALLOW_THREADS
-        if (rc != 0) Py_RETURN_NONE;
-        return result(a[6], y);
+        return result(rc, a[6], y);
     } catch (...) {  // e.g. out of memory: the general path raises it as Python does
         Py_RETURN_NONE;
     }
@@ -131,8 +134,7 @@ PyObject *rmsnorm(PyObject *, PyObject *const *a, Py_ssize_t n)
         Py_BEGIN_ALLOW_THREADS
         rc = g_rmsnorm((int)M, (int)H, xp, gp, (float)eps, yp, stream);
         Py_END_ALLOW_THREADS
-        if (rc != 0) Py_RETURN_NONE;
-        return result(a[3], y);
+        return result(rc, a[3], y);
     } catch (...) {
         Py_RETURN_NONE;
     }
@@ -160,8 +162,7 @@ PyObject *apply_x(PyObject *, PyObject *const *a, Py_ssize_t n)
         Py_BEGIN_ALLOW_THREADS
         rc = g_apply_x((int)M, (int)K, xp, (const float *)sp, yp, stream);
         Py_END_ALLOW_THREADS
-        if (rc != 0) Py_RETURN_NONE;
-        return result(a[2], y);
+        return result(rc, a[2], y);
     } catch (...) {
         Py_RETURN_NONE;
     }

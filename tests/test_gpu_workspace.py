@@ -509,6 +509,53 @@ def test_native_marshalling_equals_general_path(orc, sqp):
     torch.cuda.synchronize()
 
 
+def test_native_marshalling_reports_the_librarys_code(sqp):
+    """A code that the library returns ends in the general path's error after one call: a launch error may
+    stem from earlier work while this call's kernels were enqueued, so it neither disappears nor is
+    the call made again (in place, smooth_apply_x would divide twice).  The library's entry points are
+    replaced by counting stubs."""
+    import paper_2312_03788_amd.binding as b
+    L = sqp.lib()
+    c, vp = ctypes.c_int, ctypes.c_void_p
+    calls = []
+
+    def stub(nargs, types):
+        def run(*a):
+            calls.append(len(a))
+            return -5
+        return ctypes.CFUNCTYPE(*types)(run)
+
+    gemm = [c] + [c] * 4 + [vp] * 6
+    entries = [stub(10, gemm) for _ in range(3)] + [L.sqp_w4a16_gemm_workspace_bytes]
+    entries += [stub(7, [c, c, c, vp, vp, ctypes.c_float, vp, vp]), stub(6, [c, c, c, vp, vp, vp, vp])]
+    entries += [stub(13, [c] * 6 + [vp] * 6 + [ctypes.c_size_t, vp]), L.sqp_w4a16_gemm_scratch_bytes]
+    address = lambda f: ctypes.cast(f, vp).value
+    x, s = torch.randn((5, 512), device="cuda").half(), torch.full((512,), 2.0, device="cuda")
+    p = torch.zeros((64, 272), dtype=torch.int32, device="cuda")
+    sc = torch.zeros((4, 272), dtype=torch.float16, device="cuda")
+    z = torch.zeros((4, 272), dtype=torch.uint8, device="cuda")
+    gamma, before = torch.ones(512, dtype=torch.float16, device="cuda"), x.clone()
+    sqp.set_workspace(1 << 20)
+    real = [L.sqp_w4a16_gemm, L.sqp_w4a16_gemm_silu_mul, L.sqp_w4a16_gemm_static, L.sqp_w4a16_gemm_workspace_bytes, L.sqp_rmsnorm,
+            L.sqp_smooth_apply_x, L.sqp_w4a16_gemm_scratch, L.sqp_w4a16_gemm_scratch_bytes]
+    try:
+        b._fast.bind(*[address(f) for f in entries])
+        for name, call in (("sqp_smooth_apply_x", lambda: sqp.smooth_apply_x(x, s, out=x)),
+                           ("sqp_rmsnorm", lambda: sqp.rmsnorm(x, gamma, 1e-5, out=x)),
+                           ("sqp_w4a16_gemm", lambda: sqp.w4a16_gemm(x, p, sc, z, 128)),
+                           ("sqp_w4a16_gemm_silu_mul", lambda: sqp.w4a16_gemm_silu_mul(x, p, sc, z, 128)),
+                           ("sqp_w4a16_gemm_static", lambda: sqp.w4a16_gemm_static(x, p, sc, z, 128))):
+            calls.clear()
+            with pytest.raises(b.SqpError, match=name + r" failed: HIP launch error \(-5\)"):
+                call()
+            assert len(calls) == 1, name
+        torch.cuda.synchronize()
+        assert torch.equal(x, before)
+    finally:
+        b._fast.bind(*[address(f) for f in real])
+        sqp.set_workspace(0)
+
+
 def test_native_marshalling_declines_without_aborting(sqp):
     """Tensor methods that throw (a nested tensor has no size in its ragged dimension) end in
     the general path's exception, never in an abort."""
