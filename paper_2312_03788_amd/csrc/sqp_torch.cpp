@@ -34,10 +34,12 @@ ScratchGemmFn g_gemm_scratch;
 RmsnormFn g_rmsnorm;
 ApplyFn g_apply_x;
 
-// The tensor behind an argument if it is a dense GPU tensor of this type on device `dev`, else null.
+// The tensor behind an argument if it is a dense GPU tensor of this type on device `dev`, else null.  A
+// subclass other than torch.nn.Parameter has semantics of its own (__torch_function__, the type of
+// what torch.empty_like makes of it), with or without a dispatch key that tells.
 const at::Tensor *plain(PyObject *o, at::ScalarType type, long dev)
 {
-    if (!THPVariable_Check(o)) return nullptr;
+    if (!THPVariable_CheckExact(o)) return nullptr;
     const at::Tensor &t = THPVariable_Unpack(o);
     if (!t.defined() || t.key_set().has(c10::DispatchKey::Python) || t.layout() != at::kStrided || !t.is_cuda()) return nullptr;
     if (t.scalar_type() != type || t.get_device() != dev || !t.is_contiguous()) return nullptr;

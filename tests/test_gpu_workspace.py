@@ -496,7 +496,11 @@ def test_native_marshalling_equals_general_path(orc, sqp):
             got = fn(*args, out=out)
             assert out is None or got is out
             assert torch.equal(got.reshape(5, n), want) and got.dtype == torch.float16
-        assert torch.equal(fn(args[0].as_subclass(Tagged), *args[1:]).as_subclass(torch.Tensor), want)
+        tagged = (args[0].as_subclass(Tagged),) + args[1:]
+        got, seen = fn(*tagged), general(fn, *tagged)
+        assert type(got) is type(seen) and torch.equal(got.as_subclass(torch.Tensor), want)
+        kept = torch.nn.Parameter(args[0], requires_grad=False)
+        assert type(fn(kept, *args[1:])) is type(general(fn, kept, *args[1:])) is torch.Tensor
         bad = [(x.float(),) + args[1:], (x.cpu(),) + args[1:], (torch.cat([x, x], 1)[:, ::2],) + args[1:],
                (x.reshape(-1)[:5 * 512 - 5].reshape(5, 511),) + args[1:], args[:1] + (args[1].double(),) + args[2:]]
         for a in bad:
