@@ -233,12 +233,19 @@ static size_t plan_bytes(const Plan &p, int N, int K, int group, int kspg, int m
     return bytes;
 }
 
+// Fewer K parts where the partial tiles would not fit `room` bytes (one part needs none).
+static void fit_split(Plan &p, int N, int K, int group, int kspg, int mt, size_t room)
+{
+    while (p.split > 1 && plan_bytes(p, N, K, group, kspg, mt) > room) p.split--;
+}
+
 // The same for the plan by strips: one group per chunk, row tiles in steps of 16, 32 and 64.
 static size_t strips_bytes(int M, int N, int K, int group)
 {
-    const int kspg = group == 32 ? 1 : (group == 64 ? 2 : 4);
-    return plan_bytes(make_plan(M, N, K, kspg == 4 ? 128 : group, M <= 16 && group == 128), N, K, group, kspg,
-                      M <= 16 ? 1 : (M <= 32 ? 2 : 4));
+    const int kspg = group == 32 ? 1 : (group == 64 ? 2 : 4), mt = M <= 16 ? 1 : (M <= 32 ? 2 : 4);
+    Plan p = make_plan(M, N, K, kspg == 4 ? 128 : group, M <= 16 && group == 128);
+    fit_split(p, N, K, group, kspg, mt, SQP_STATIC_PARTIAL_BYTES);
+    return plan_bytes(p, N, K, group, kspg, mt);
 }
 
 // The plan a call runs with: the heuristic's, overridden by the test hooks, without a split
@@ -256,6 +263,9 @@ static Plan plan_for(int M, int N, int K, int group, bool have_workspace)
     } else {
         p = make_plan(M, N, K, chunk, M <= 16 && group == 128);
     }
+    // No plan of the library's own needs more than the static array holds.  (Rounding can take one past it:
+    // 623 two-strip tiles x 5 parts x 16 KB, 6976 -> 39816 in groups of 64.)
+    if (chunk) fit_split(p, N, K, group, chunk / 32, sqp_strip_row_tiles(M), SQP_STATIC_PARTIAL_BYTES);
     if (g_force_plan.nw > 0) p = g_force_plan;
     if (g_force_split > 0) p.split = g_force_split;
     if (!have_workspace) p.split = 1;
@@ -303,7 +313,7 @@ int sqp_gemm_decode(int M, int N, int K, int group, const h16 *x, const uint32_t
     }
     Plan p = plan_for(M, N, K, group, ws.partial != nullptr);
     if (ws.partial != nullptr && ws.partial_bytes >= sqp_gemm_decode_least_bytes(M, N, K, group))
-        while (p.split > 1 && plan_bytes(p, N, K, group, kspg, sqp_strip_row_tiles(M)) > ws.partial_bytes) p.split--;
+        fit_split(p, N, K, group, kspg, sqp_strip_row_tiles(M), ws.partial_bytes);
     if (kspg < 4) return sqp_strip_one_group(group, p, M, N, K, 1, x, packed, scales, zeros, y, epi, ws, stream);
     if (group == 32) return sqp_strip_g32(p, M, N, K, 1, x, packed, scales, zeros, y, epi, ws, stream);
     if (group == 64) return sqp_strip_g64(p, M, N, K, 1, x, packed, scales, zeros, y, epi, ws, stream);

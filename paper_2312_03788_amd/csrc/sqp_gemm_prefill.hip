@@ -522,6 +522,17 @@ static int decode_in_row_blocks(int M, int N, int K, int group, const h16 *x, co
     return SQP_OK;
 }
 
+// Group sizes the tiled kernel covers (others run in row blocks).
+static bool tiled_covers(int K, int group) { return group % BK == 0 || (group == 32 && K % BK == 0); }
+
+// What the row blocks of a call need: blocks of 64 rows and a last one of fewer, whose plan may split where
+// theirs does not.
+static size_t most_of_row_blocks(size_t (*bytes)(int, int, int, int), int M, int N, int K, int group)
+{
+    const size_t whole = M >= 64 ? bytes(64, N, K, group) : 0, last = M % 64 ? bytes(M % 64, N, K, group) : 0;
+    return whole > last ? whole : last;
+}
+
 // Launch plan of the tiled path: `full` full tiles (128 x 512 with wm == 1, 256 x 256 with
 // wm == 2) in a first launch, then `half` half-width tiles (starting at full tile `full`), the
 // latter times `ksplit` K parts.
@@ -717,14 +728,14 @@ static size_t plan_partial_bytes(const LaunchPlan &q)
 
 size_t sqp_gemm_prefill_partial_bytes(int M, int N, int K, int group)
 {
-    if (group % BK != 0 && !(group == 32 && K % BK == 0)) return sqp_gemm_decode_partial_bytes(M < 64 ? M : 64, N, K, group);  // row-block fallback
+    if (!tiled_covers(K, group)) return most_of_row_blocks(sqp_gemm_decode_partial_bytes, M, N, K, group);
     const LaunchPlan q = plan_launches(M, N, K, group, sqp_compute_units(), SIZE_MAX, 0);
     return plan_partial_bytes(q);
 }
 
 size_t sqp_gemm_prefill_scratch_bytes(int M, int N, int K, int group)
 {
-    if (group % BK != 0 && !(group == 32 && K % BK == 0)) return 0;
+    if (!tiled_covers(K, group)) return 0;
     const LaunchPlan q = plan_launches(M, N, K, group, sqp_compute_units(), SIZE_MAX, SIZE_MAX);
     return q.own ? plan_partial_bytes(q) : 0;
 }
@@ -733,7 +744,7 @@ size_t sqp_gemm_prefill_scratch_bytes(int M, int N, int K, int group)
 // tiles as [parts][M][N].  With less than the preferred plan's bytes, one that fits runs.
 size_t sqp_gemm_prefill_least_bytes(int M, int N, int K, int group)
 {
-    if (group % BK != 0 && !(group == 32 && K % BK == 0)) return sqp_gemm_decode_least_bytes(M < 64 ? M : 64, N, K, group);
+    if (!tiled_covers(K, group)) return most_of_row_blocks(sqp_gemm_decode_least_bytes, M, N, K, group);
     const size_t want = sqp_gemm_prefill_partial_bytes(M, N, K, group);
     if (g_force_rt > 0) return want;
     const TilePlan p = plan_tiles(M, N, K, group, sqp_compute_units(), true);
@@ -752,8 +763,7 @@ static void launch_variant(const TileLaunch &l, int M, int N, int K, int group, 
 int sqp_gemm_prefill(int M, int N, int K, int group, const h16 *x, const uint32_t *packed,
                      const h16 *scales, const uint8_t *zeros, h16 *y, int epi, const SqpWorkspace &ws, hipStream_t stream)
 {
-    // group sizes the tiled kernel does not cover (neither a multiple of 64, nor 32 with K a multiple of 64)
-    if (!(group % BK == 0 || (group == 32 && K % BK == 0)))
+    if (!tiled_covers(K, group))
         return decode_in_row_blocks(M, N, K, group, x, packed, scales, zeros, y, epi, ws, stream);
     const size_t room_ws = ws.partial ? ws.partial_bytes : 0, room_own = ws.own ? ws.own_bytes : 0;
     if (room_ws > 0 && room_ws < sqp_gemm_prefill_least_bytes(M, N, K, group)) return SQP_ERR_WORKSPACE;

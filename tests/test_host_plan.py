@@ -2,6 +2,7 @@
 decode path's strips and K split, the tiled path's tile mix and K parts) and the argument
 checks of the loss entry point."""
 import ctypes
+import random
 
 import pytest
 
@@ -219,6 +220,28 @@ def test_prefill_launches_invariants(L):
     assert one(190, 8192, 8192) == (1, (3, 2, 64, 4))        # two of 96
     assert one(512, 22016, 4096) == (1, (4, 4, 172, 1))
     assert L.sqp_debug_prefill_launches(3001, 44032, 8192, 128, 256, out) == 2 and tuple(out[4:8]) == (4, 2, 32, 8)
+
+
+def test_plans_fit_the_static_array(L):
+    """No shape's own plan needs more partial sums than the static array of sqp_w4a16_gemm_static holds, the
+    least size of a workspace is at most the preferred one, and a call in blocks of 64 rows reports what
+    its last block of fewer rows needs too.  Shapes at random, K mostly not a multiple
+    of 128, and some that rounding would take past the limit."""
+    limit = (512 << 10) + (48 << 20)
+    rng = random.Random(7)
+    shapes = [(64, 39816, 6976, 64), (64, 39816, 7008, 32), (2815, 39816, 6944, 32), (85, 71504, 6880, 32), (426, 118528, 2592, 32),
+              (95, 110360, 3360, 32), (1346, 8192, 2048, 128), (1152, 8192, 22016, 64)]
+    for _ in range(20000):
+        group = rng.choice([8, 24, 32, 32, 64, 64, 96, 128, 192, 256])
+        shapes.append((int(2 ** rng.uniform(0, 12.5)), 8 * int(2 ** rng.uniform(0, 14.5)), group * int(2 ** rng.uniform(0, 8.5)), group))
+    for (M, N, K, group) in shapes:
+        if max(M * K, K * N, M * N) >= 1 << 31:
+            continue
+        want, least = L.sqp_w4a16_gemm_workspace_bytes(M, N, K, group), L.sqp_w4a16_gemm_workspace_least_bytes(M, N, K, group)
+        assert least <= want <= limit, (M, N, K, group, want)
+        if M > 64 and M % 64 and group % 64 and (group != 32 or K % 64):
+            assert L.sqp_w4a16_gemm_workspace_least_bytes(M % 64, N, K, group) <= least, (M, N, K, group)
+            assert L.sqp_w4a16_gemm_workspace_bytes(M % 64, N, K, group) <= want, (M, N, K, group)
 
 
 def test_calls_that_touch_no_workspace(L):
