@@ -103,6 +103,34 @@ def test_quantize_dequantize_bit_exact(orc, sqp, kind, K, N, group):
     assert np.array_equal(what.view(np.uint16), orc.dequantize(p_ref, s_ref, z_ref, group).view(np.uint16))
 
 
+@pytest.mark.parametrize("K,N,group", [(96, 72, 32), (192, 264, 64), (256, 520, 128), (512, 72, 256), (48, 72, 24), (192, 72, 96)])
+def test_quantize_not_finite(sqp, K, N, group):
+    """A NaN is quantised as a weight of 0 is (code Z, no part in the range), whatever stands beside it; a
+    group with an infinity has an infinite step and code and zero point 0.  All other groups keep
+    their values."""
+    print("case quantize not finite", K, N, group, flush=True)
+    rng = np.random.Generator(np.random.PCG64(K + N))
+    w = rng.normal(0.0, 0.02, size=(K, N)).astype(np.float16)
+    holes = rng.random((K, N)) < 0.02
+    holes[:, 5] = True                       # a column of nothing else
+    holes[:group, 3] = False
+    holes[0, 3] = holes[group - 1, 3] = True
+    with_nan, with_zero = w.copy(), w.copy()
+    with_nan[holes], with_zero[holes] = np.nan, 0.0
+    got, want = sqp.quantize_pack(dev(with_nan), group), sqp.quantize_pack(dev(with_zero), group)
+    for a, b in zip(got, want):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    inf = with_zero.copy()
+    inf[group // 2, 1], inf[K - 1, 2] = np.inf, -np.inf
+    p, sc, z = (host(t) for t in sqp.quantize_pack(dev(inf), group))
+    wp, wsc, wz = (host(t) for t in want)
+    for (t, n) in ((0, 1), (K // group - 1, 2)):
+        assert np.isinf(sc[t, n]) and z[t, n] == 0 and (p[t * group // 8:(t + 1) * group // 8, n] == 0).all()
+        p[t * group // 8:(t + 1) * group // 8, n] = wp[t * group // 8:(t + 1) * group // 8, n]
+        sc[t, n], z[t, n] = wsc[t, n], wz[t, n]
+    assert np.array_equal(p, wp) and np.array_equal(sc.view(np.uint16), wsc.view(np.uint16)) and np.array_equal(z, wz)
+
+
 def test_dequantize_random_words(orc, sqp):
     """Dequantise arbitrary words / steps / zero points (not produced by the quantiser)."""
     rng = np.random.Generator(np.random.PCG64(77))
