@@ -36,15 +36,14 @@ extern "C" int sqp_debug_plain_copy(const void *src, void *dst, size_t bytes, vo
 // without the non-temporal hint: the read bandwidth the chip reaches with nothing else to do,
 // the reference the weight-streaming GEMM is measured against beside the published peak.
 // Benchmark hook, not part of the ABI.
-typedef uint32_t probe_u32x4 __attribute__((ext_vector_type(4)));
 template <bool NT>
-__global__ void __launch_bounds__(256) read_probe_kernel(const probe_u32x4 *__restrict__ src, size_t n, uint32_t *__restrict__ sink)
+__global__ void __launch_bounds__(256) read_probe_kernel(const u32x4 *__restrict__ src, size_t n, uint32_t *__restrict__ sink)
 {
     size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
     const size_t stride = (size_t)gridDim.x * 256;
     uint32_t acc = 0;
     for (; i + 7 * stride < n; i += 8 * stride) {
-        probe_u32x4 v[8];
+        u32x4 v[8];
 #pragma unroll
         for (int j = 0; j < 8; j++) v[j] = NT ? __builtin_nontemporal_load(src + i + j * stride) : src[i + j * stride];
 #pragma unroll
@@ -56,8 +55,8 @@ extern "C" int sqp_debug_read_probe(const void *src, size_t bytes, int nt, int b
 {
     if (!src || !sink || (bytes & 15) || blocks <= 0 || blocks > 65535) return SQP_ERR_SHAPE;
     const size_t n = bytes / 16;
-    if (nt) read_probe_kernel<true><<<blocks, 256, 0, (hipStream_t)stream>>>((const probe_u32x4 *)src, n, (uint32_t *)sink);
-    else read_probe_kernel<false><<<blocks, 256, 0, (hipStream_t)stream>>>((const probe_u32x4 *)src, n, (uint32_t *)sink);
+    if (nt) read_probe_kernel<true><<<blocks, 256, 0, (hipStream_t)stream>>>((const u32x4 *)src, n, (uint32_t *)sink);
+    else read_probe_kernel<false><<<blocks, 256, 0, (hipStream_t)stream>>>((const u32x4 *)src, n, (uint32_t *)sink);
     return sqp_launch_status();
 }
 

@@ -9,15 +9,6 @@
 // All three are single streaming passes (HBM-bound, 16-byte accesses).
 #include "sqp_common.h"
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-// Weights are read once per call: non-temporal, past the caches (interleaving 5120 x 13824 twice
-// 97 -> 89 us, and the maximum over its result that follows 65 -> 59).
-__device__ __forceinline__ uint4 load_stream(const uint4 *p)
-{
-    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
-
 namespace {
 
 __device__ __forceinline__ float lo_of(uint32_t v) { return (float)__builtin_bit_cast(h16x2, v).x; }

@@ -4,18 +4,6 @@
 #pragma once
 #include "sqp_common.h"
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-// Streaming reads of the weight, every byte of which is touched once per call: the non-temporal
-// hint lets them pass through the caches (a plain read probe streams 12-15 % faster with it on this
-// chip).  Stores go without it: with hinted loads, plain stores are faster (weight scaling on
-// 22016 x 8192 115 -> 105 us, transpose 147 -> 125 us), and so is the activation tensor's pass, which
-// fits the Infinity Cache.
-__device__ __forceinline__ uint4 load_stream(const uint4 *p)
-{
-    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
 namespace {
 
 __device__ __forceinline__ float h2f_lo(uint32_t v) { return (float)__builtin_bit_cast(h16x2, v).x; }

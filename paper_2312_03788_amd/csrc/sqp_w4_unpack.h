@@ -3,7 +3,6 @@
 #pragma once
 #include "sqp_common.h"
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 // Constants of the nibble unpack, held in registers: v_and_or_b32 cannot take literals.
