@@ -47,7 +47,7 @@ void sqp_debug_prefill_plan(int M, int N, int K, int cus, long *full, long *half
 
 /* What a call launches: returns the number of launches (1 or 2) and their (rt, nt, tiles, K parts) in
  * out8.  The plan above, or one round of tiles of another height where that is faster, and with K
- * parts for few left-over tiles.  Host arithmetic only. */
+ * parts for few left-over tiles; workspace and scratch as large as it likes.  Host arithmetic only. */
 int sqp_debug_prefill_launches(int M, int N, int K, int group, int cus, int *out8);
 
 /* Calibration kernels for the benchmark: a plain device copy of `bytes` (a multiple of 16)

@@ -641,9 +641,13 @@ static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, size_t 
     }
     const bool hooked = g_tile_mode != 0 || g_tile_shape != 0 || g_ksplit >= 0;
     // Everything in one round of the chip: the variant and the number of K parts with the least estimated time.
-    // Estimate (us), fitted to 400 measured launches of 51 shapes (rms 7 %): per 64-row stage of K
-    // 0.72 / 0.77 / 0.97 / 1.11 for tiles of 96 / 128 / 160 / 192 rows x 256 columns and 1.43 for
-    // 128 x 512, plus the fp32 parts' way out and back at 5.6 TB/s; more than 12 parts never won.
+    // The estimate (us) ranks plans: per 64-row stage of K 0.72 / 0.77 / 0.97 / 1.11 for tiles of 96 / 128 / 160 /
+    // 192 rows x 256 columns and 1.43 for 128 x 512, plus the fp32 parts' way out and back at 5.6 TB/s;
+    // more than 12 parts never won.  It leaves out what all plans share, so it is low throughout: 609
+    // measured launches of 51 shapes take 6.7 us more, those with K parts another 1.8 for the reduction's
+    // launch (with both, rms 6 %).  The plan it picks is 0.5 % slower than the best one measured in the
+    // mean of the shapes and 5.5 % at worst, with the reduction's cost in it 0.4 % and 5.5 %.
+    // Groups of 32 keep the plan in 128-row tiles: only its two tiles are built for two groups per stage.
     // What it buys (us, 128-row tiles only -> chosen): 8192->8192 at 72 / 150 / 190 / 320 / 640 rows
     // 33.6 -> 27.7, 47.0 -> 37.9, 47.6 -> 39.8, 71.1 -> 56.7, 116 -> 96; 4096->22016 at 80 / 160 / 320 rows
     // 43.7 -> 35.4, 65.5 -> 47.9, 99 -> 76; 8192->10240 at 160 rows 56 -> 43: a 128-row tile computes
@@ -691,7 +695,7 @@ static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, size_t 
             const double part_us = (double)p.half * 128 * 256 * 8 / 4.5e6;
             double best = stages * 0.77;
             for (int n = 2; n <= most; n++) {
-                const double t = (stages + n - 1) / n * 0.77 + n * part_us + 3;
+                const double t = (stages + n - 1) / n * 0.77 + n * part_us + 3;  // (3: the reduction's launch)
                 if (t < best && launch_partial_bytes(TileLaunch{4, 2, 0, p.half, 0, n}, 1) <= room) {
                     best = t;
                     parts = n;

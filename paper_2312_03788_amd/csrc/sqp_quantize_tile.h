@@ -95,9 +95,10 @@ constexpr float NEAR_TIE = 4.0e-6f;
 // is not clamped, see NEAR_TIE -- then round, clamp to [0, 15] as a float, and the eight codes of a
 // word are assembled by a fused multiply-add chain (sum c_i 16^i per half word is exact in fp32).
 // A word containing a value within NEAR_TIE of a rounding tie is redone with the division of the
-// definition (wave-uniform branch, about 0.4 % of the words), and so are the words of a thread that holds
-// a NaN or an infinity, which the clamp would turn into code 0: a NaN gets code Z (as a weight of 0 does),
-// whatever its neighbours hold.
+// definition (wave-uniform branch, about 0.4 % of the words), and so is one with a NaN among its t (from a
+// NaN or an infinity), which the clamp would turn into code 0: a NaN gets code Z, as a weight of 0 does,
+// whatever its neighbours hold.  The maximum over |t - rint(t)| propagates NaNs (v_maximum3_f32), which
+// costs nothing over one that does not.
 // SMOOTH: the weight is multiplied by the smoothing factor of its row as it is read (one rounding to
 // fp16, as sqp_smooth_apply_w does it), which saves the smoothed weight's way out and back.
 // (bx, by): the workgroup's tile of 256 columns and 16 PARTS rows.  All threads take part; a caller that
@@ -136,15 +137,11 @@ __device__ __forceinline__ void quantize_tile(int bx, int by, int N, int K, cons
             asm volatile("" : "+v"(v[i].x), "+v"(v[i].y), "+v"(v[i].z), "+v"(v[i].w));
         }
     }
-    h16x2 mn[4], mx[4], off[4];  // off: 0 times every weight, which stays +0 for finite ones
-    const h16x2 zero = {(h16)0.0f, (h16)0.0f};
+    h16x2 mn[4], mx[4];
     {
         const uint32_t q[4] = {v[0].x, v[0].y, v[0].z, v[0].w};
 #pragma unroll
-        for (int c = 0; c < 4; c++) {
-            mn[c] = mx[c] = __builtin_bit_cast(h16x2, q[c]);
-            off[c] = __builtin_elementwise_fma(mn[c], zero, zero);
-        }
+        for (int c = 0; c < 4; c++) mn[c] = mx[c] = __builtin_bit_cast(h16x2, q[c]);
     }
 #pragma unroll
     for (int i = 1; i < 16; i++) {
@@ -154,11 +151,8 @@ __device__ __forceinline__ void quantize_tile(int bx, int by, int N, int K, cons
             const h16x2 e = __builtin_bit_cast(h16x2, q[c]);
             mn[c] = __builtin_elementwise_min(mn[c], e);
             mx[c] = __builtin_elementwise_max(mx[c], e);
-            off[c] = __builtin_elementwise_fma(e, zero, off[c]);
         }
     }
-    const bool not_finite = ((__builtin_bit_cast(uint32_t, off[0]) | __builtin_bit_cast(uint32_t, off[1])) |
-                             (__builtin_bit_cast(uint32_t, off[2]) | __builtin_bit_cast(uint32_t, off[3]))) != 0u;
     auto as_u4 = [](const h16x2 (&a)[4]) {
         return make_uint4(__builtin_bit_cast(uint32_t, a[0]), __builtin_bit_cast(uint32_t, a[1]),
                           __builtin_bit_cast(uint32_t, a[2]), __builtin_bit_cast(uint32_t, a[3]));
@@ -210,13 +204,13 @@ __device__ __forceinline__ void quantize_tile(int bx, int by, int N, int K, cons
                 const float x = (c & 1) ? h2f_hi(dw) : h2f_lo(dw);
                 const float tq = fmaf(x, inv, zf);
                 const float r = rintf(tq);
-                worst = fmaxf(worst, fabsf(tq - r));
+                worst = __builtin_elementwise_maximum(worst, fabsf(tq - r));
                 code[i] = fminf(fmaxf(r, 0.0f), 15.0f);
             }
             const float lo4 = fmaf(fmaf(fmaf(code[3], 16.0f, code[2]), 16.0f, code[1]), 16.0f, code[0]);
             const float hi4 = fmaf(fmaf(fmaf(code[7], 16.0f, code[6]), 16.0f, code[5]), 16.0f, code[4]);
             word[c] = (uint32_t)lo4 | ((uint32_t)hi4 << 16);
-            if (__builtin_amdgcn_ballot_w64(worst >= 0.5f - NEAR_TIE || not_finite) != 0ull) {
+            if (__builtin_amdgcn_ballot_w64(!(worst < 0.5f - NEAR_TIE)) != 0ull) {
                 GroupParams gp;
                 gp.d = sh.par_d[grp][oct * 8 + c];
                 gp.z = (int)zf;
