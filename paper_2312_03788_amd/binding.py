@@ -110,11 +110,9 @@ def _native(t):
     return _fast is not None and isinstance(t, torch.Tensor) and t.is_cuda
 
 
-def _ended(y, what):
-    """The native call's result: its output, or SqpError for the code the library returned."""
-    if type(y) is int:
-        _check(y, what)
-    return y
+def _ended(rc, what):
+    """A native call that ended with a code of the library's instead of its output."""
+    _check(rc, what)
 
 
 _workspaces = {}  # device index -> torch buffer handed to the library (kept alive here)
@@ -218,7 +216,7 @@ def smooth_apply_x(x, s, out=None):
     if _native(x):
         o = _fast.apply_x(x, s, out, *_here())
         if o is not None:
-            return _ended(o, "sqp_smooth_apply_x")
+            return o if type(o) is not int else _ended(o, "sqp_smooth_apply_x")
     M, K = x.shape
     o = out if out is not None else torch.empty_like(x)
     _check(lib().sqp_smooth_apply_x(M, K, _dev(x, torch.float16, "x"), _dev(s, torch.float32, "s"),
@@ -269,7 +267,7 @@ def w4a16_gemm(x, packed, scales, zeros, group=128, out=None):
         dev, stream = _here()
         y = _fast.gemm(0, x, packed, scales, zeros, group, out, dev, stream, _held.get(dev, 0))
         if y is not None:
-            return _ended(y, "sqp_w4a16_gemm")
+            return y if type(y) is not int else _ended(y, "sqp_w4a16_gemm")
     return _gemm(0, x, packed, scales, zeros, group, out)
 
 
@@ -280,7 +278,7 @@ def w4a16_gemm_static(x, packed, scales, zeros, group=128, out=None):
     if _native(x):
         y = _fast.gemm(2, x, packed, scales, zeros, group, out, *_here(), 0)
         if y is not None:
-            return _ended(y, "sqp_w4a16_gemm_static")
+            return y if type(y) is not int else _ended(y, "sqp_w4a16_gemm_static")
     M, K = x.shape
     N = packed.shape[1]
     if packed.shape[0] * 8 != K:
@@ -298,7 +296,7 @@ def w4a16_gemm_silu_mul(x, packed, scales, zeros, group=128, out=None):
         dev, stream = _here()
         y = _fast.gemm(1, x, packed, scales, zeros, group, out, dev, stream, _held.get(dev, 0))
         if y is not None:
-            return _ended(y, "sqp_w4a16_gemm_silu_mul")
+            return y if type(y) is not int else _ended(y, "sqp_w4a16_gemm_silu_mul")
     return _gemm(1, x, packed, scales, zeros, group, out)
 
 
@@ -307,7 +305,7 @@ def rmsnorm(x, gamma, eps, out=None):
     if _native(x):
         y = _fast.rmsnorm(x, gamma, eps, out, *_here())
         if y is not None:
-            return _ended(y, "sqp_rmsnorm")
+            return y if type(y) is not int else _ended(y, "sqp_rmsnorm")
     M, H = x.shape
     y = out if out is not None else torch.empty_like(x)
     _check(lib().sqp_rmsnorm(M, H, _dev(x, torch.float16, "x"), _dev(gamma, torch.float16, "gamma"), float(eps),
