@@ -129,6 +129,8 @@ int sqp_dequantize(int N, int K, int group, const uint32_t *packed, const void *
  *   - workspace smaller than sqp_w4a16_gemm_workspace_bytes() of the shape: a plan that fits
  *     it runs, down to sqp_w4a16_gemm_workspace_least_bytes(); below that SQP_ERR_WORKSPACE,
  *     nothing enqueued.
+ * (Up to 32 rows some of these shapes run a plan that leaves the workspace untouched; sizes and
+ * refusals are the same for them.)
  * Calls that use the workspace must not overlap on the device (order them on one stream, or
  * with events): they share its tickets and partial sums.  Calls of shapes whose
  * sqp_w4a16_gemm_workspace_bytes() is 0 may overlap with anything. */

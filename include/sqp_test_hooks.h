@@ -21,11 +21,14 @@ void sqp_debug_set_decode_plan(int nw, int split); /* force strips per workgroup
 void sqp_debug_set_decode_kw(int kw);              /* waves per strip: 0 = automatic, 1 = never two, 2 = two wherever built */
 void sqp_debug_set_decode_kp(int kp);              /* two chunks per iteration (twice the waves): 0 = automatic, 1 = never,
                                                       2 = where the rules would with enough chunks, 3 = wherever built */
-void sqp_debug_set_decode_slice(int mode);         /* column-slice kernel (M <= 16, groups of 128): 0 = automatic, -1 = never,
-                                                      1 = always with 32-column slices, 2 = always with 64-column slices */
-/* Which kernel a call would take: -1 = the strip kernel below, 0 / 1 = the column-slice kernel
- * with 32- / 64-column slices.  Host arithmetic only. */
+void sqp_debug_set_decode_slice(int mode);         /* column-slice kernel (M <= 32): 0 = automatic, -1 = never, 1 = always with
+                                                      32-column slices, 2 = always with 64-column slices (eight waves) */
+void sqp_debug_set_slice_plan(int tb, int wv, int grouped); /* tb > 0: column slices of 16 tb columns, wv waves, for every call they cover */
+/* Whether a layer fills the chip with slices of 32 (0) or 64 (1) columns and takes the column-slice kernel for
+ * that alone (-1: the launch plan decides by N, K and the group).  Host arithmetic only. */
 int sqp_debug_decode_slice_choice(int M, int N, int K, int group);
+/* The slices a call takes: columns / 16 and waves per workgroup (0, 0: the strip kernel below or the generic one). */
+void sqp_debug_decode_slice_plan(int M, int N, int K, int group, int *tb, int *wv);
 /* The plan by strips for a shape: strips per workgroup, K parts, k-steps of one group up to 128 k
  * (0 = the generic one-thread-per-element kernel).  Calls with up to 16 rows and groups that are
  * multiples of 128 run it.  Host arithmetic only. */

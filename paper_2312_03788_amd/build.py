@@ -14,8 +14,9 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsqp.so")
 TORCH_LIB = os.path.join(HERE, "_sqp_torch.so")
 
-SOURCES = ["sqp_api.hip", "sqp_companion.hip", "sqp_gemm_decode.hip", "sqp_gemm_prefill.hip", "sqp_gemm_slice.hip", "sqp_loss.hip", "sqp_mlp.hip", "sqp_static.hip",
-           "sqp_strip_g128_rows32.hip", "sqp_strip_g128_rows64.hip", "sqp_strip_g64.hip", "sqp_strip_g32.hip", "sqp_strip_one_group.hip"]
+SOURCES = ["sqp_api.hip", "sqp_companion.hip", "sqp_gemm_decode.hip", "sqp_gemm_prefill.hip", "sqp_loss.hip", "sqp_mlp.hip", "sqp_static.hip",
+           "sqp_strip_g128_rows32.hip", "sqp_strip_g128_rows64.hip", "sqp_strip_g64.hip", "sqp_strip_g32.hip", "sqp_strip_one_group.hip",
+           "sqp_slice_g128.hip", "sqp_slice_g256.hip", "sqp_slice_g64.hip", "sqp_slice_g32.hip"]
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-I" + os.path.join(ROOT, "include"),
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
@@ -30,7 +31,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hi
 #                  must come after the kernel's last barrier, i.e. after the main loop and its
 #                  final wait for all outstanding loads (checked in the generated assembly).
 GUARDED_KERNELS = {**{s: ("w4a16_decode_kernel", "none") for s in SOURCES if s.startswith("sqp_strip_")},
-                   "sqp_gemm_slice.hip": ("w4a16_decode_slice_kernel", "none"),
+                   **{s: ("w4a16_decode_slice_kernel", "none") for s in SOURCES if s.startswith("sqp_slice_")},
                    "sqp_gemm_prefill.hip": ("w4a16_prefill_kernel", "after-last-barrier"),
                    "sqp_loss.hip": ("loss_tile_kernel", "none")}
 

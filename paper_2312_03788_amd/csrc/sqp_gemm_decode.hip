@@ -1,5 +1,6 @@
 // Launch plans of the weight-streaming W4A16 GEMM (up to 64 rows) and its fallback kernel.  The
-// kernels themselves: sqp_strip_kernel.h, sqp_gemm_slice.hip.
+// kernels themselves: sqp_strip_kernel.h, sqp_slice_kernel.h.
+#include "sqp_slice.h"
 #include "sqp_strip.h"
 
 namespace {
@@ -180,8 +181,8 @@ extern "C" void sqp_debug_set_decode_kp(int kp) { sqp_strip_kp_hook = kp; }
 static int g_slice_mode = 0;
 extern "C" void sqp_debug_set_decode_slice(int mode) { g_slice_mode = mode; }
 
-// Whether a call takes the column-slice kernel (-1: no), and which variant (0: 32-column
-// slices, 1: 64-column slices).  From sweeps on Code Llama shapes: the slice kernel has no
+// Layers that fill the chip with slices of 32 (0) or 64 (1) columns and take them whatever the rule of
+// slice_plan below says (-1: none; up to 16 rows, groups of 128).  The slice kernel has no
 // hand-over between workgroups, but every workgroup fetches all of x from L2, and that traffic
 // (workgroups x fetched rows x K) is what it costs.  It wins up to 8 rows (a third to a half of
 // the activation traffic of 16 rows at K = 8192) and beyond that where x is small (short K) and
@@ -191,8 +192,7 @@ extern "C" void sqp_debug_set_decode_slice(int mode) { g_slice_mode = mode; }
 // activations dominate again; 5 to 12 rows: only with K up to 8192, 13 to 16: up to 4096).
 static int slice_variant(int M, int N, int K, int group)
 {
-    if (g_slice_mode < 0 || !sqp_gemm_slice_covers(M, N, K, group)) return -1;
-    if (g_slice_mode > 0) return g_slice_mode - 1;
+    if (M > 16 || group != 128) return -1;
     const long xbytes = 4L * ((M + 3) / 4) * K * 2;  // activations a workgroup fetches
     const int slices64 = (N + 63) / 64, slices32 = (N + 31) / 32;
     if (slices64 >= 150) return (M <= 8 || xbytes <= (128L << 10) || (xbytes <= (192L << 10) && slices64 <= 400)) ? 1 : -1;
@@ -200,6 +200,62 @@ static int slice_variant(int M, int N, int K, int group)
     return -1;
 }
 extern "C" int sqp_debug_decode_slice_choice(int M, int N, int K, int group) { return slice_variant(M, N, K, group); }
+static SqpSlicePlan g_slice_plan = {0, 0, false};
+extern "C" void sqp_debug_set_slice_plan(int tb, int wv, int grouped) { g_slice_plan = SqpSlicePlan{tb, wv, grouped != 0}; }
+
+// Whether a call of up to 32 rows takes the column-slice kernel, and how wide its slices are.  From a sweep
+// over 1356 calls (N 1024 to 44032, K 1024 to 22016, groups of 32, 64, 128 and 256, weights from HBM): 1.21
+// times faster than the plans before in the geometric mean, 0.6 % behind the best variant of each call.
+//   Width: the narrowest that fits the chip in one round, i.e. 16 columns up to 4096, 32 up to 8192, 64 from
+//   there on (one workgroup too many costs a round: 4352 columns in 16s 10.5 us, in 32s 8.8 at one row and
+//   K = 8192).  Above 16384 columns 64, or 32 in groups of 32 up to 16 rows and 32768 columns (their unpack
+//   is the longer one: 22016 columns, K = 2112, 6 rows 12.3 -> 9.8 us).
+//   Waves: eight; 16 for one to four rows on narrow layers with long K (4096->1024 at one row 4.7 -> 4.4 us);
+//   four with 64 columns, up to 8 rows and two slices per compute unit (4096->22016 at one row 11.8 -> 11.0).
+//   K: the strip kernel's hand-over costs about the same whatever K, the slices' latency and activations grow
+//   with K, so longer K goes to the strips: us at 1 / 8 / 16 / 32 rows, strips against slices, N = 1024:
+//   K = 4096 7.2 / 7.3 / 7.4 / 9.3 against 4.4 / 5.1 / 6.0 / 7.3, K = 12288 9.5 / 9.6 / 9.9 / 11.9 against
+//   8.5 / 10.6 / 13.0 / 17.4.  Groups of several chunks hold out longer (the strip kernel takes one chunk per
+//   iteration there).  K not a multiple of 128: always slices (the strips take chunks of one group there).
+static SqpSlicePlan slice_plan(int M, int N, int K, int group)
+{
+    const SqpSlicePlan none = {0, 0, false};
+    if (g_slice_mode < 0 || M > 32 || (group != 32 && group != 64 && group % 128 != 0)) return none;
+    if (g_slice_plan.tb > 0) return g_slice_plan;
+    if (g_slice_mode > 0) return SqpSlicePlan{2 * g_slice_mode, 8, false};
+    const int width = N <= 4096 ? 0 : (N <= 8192 ? 1 : (N <= 16384 ? 2 : 3));
+    const int blocks = M > 16 ? 4 : (M + 3) / 4 - 1;  // blocks of four rows less one; 17 to 32 rows
+    constexpr int ANY = 1 << 30;
+    static const int longest[4][5] = {{12288, 9216, 9216, 6144, 6144}, {16384, 13312, 10240, 6144, 6144}, {ANY, ANY, 13312, 6144, 6144}, {ANY, ANY, 5120, 4096, 0}};
+    int most = longest[width][blocks];
+    if (width == 2 && M > 12 && N >= 11008) most = 9216;   // 172 and more slices
+    if (width == 3 && M > 16 && N >= 32768) most = 2048;   // the strips have more than 256 tiles
+    if (group > 128 && width > 0) most = width == 3 && M > 8 ? (M > 16 && K < 2048 ? 0 : 11264) : (most == ANY ? ANY : most + most / 2);
+    if (group == 32 && width == 2) most = ANY;
+    const bool odd = K % 128 != 0 && !(group == 32 && N > 32768 && M > 4);
+    if (K > most && !odd && slice_variant(M, N, K, group) < 0) return none;
+    SqpSlicePlan p = {width == 0 ? 1 : (width == 1 ? 2 : 4), 8, width < 2};
+    if (group == 32 && width == 3 && N <= 32768 && M <= 16) p.tb = 2, p.grouped = true;
+    if (M <= 16 && width < 2 && K > 2048 && M <= (width == 0 ? 4 : 2)) p.wv = 16;
+    if (M <= 8 && p.tb == 4 && width == 3 && N <= 32768 && group >= 64) p.wv = 4;
+    return p;
+}
+
+// Calls that take slices and report no workspace.  The others that take them, since the rule above, go on
+// reporting what the strip kernel would use, and are refused with less: sizes that callers have
+// stored, and what they were told about too small a buffer, stay true.
+static bool slices_alone(int M, int N, int K, int group)
+{
+    if (g_slice_mode < 0) return false;
+    return g_slice_plan.tb > 0 || g_slice_mode > 0 ? slice_plan(M, N, K, group).tb > 0 : slice_variant(M, N, K, group) >= 0;
+}
+
+extern "C" void sqp_debug_decode_slice_plan(int M, int N, int K, int group, int *tb, int *wv)
+{
+    const SqpSlicePlan p = slice_plan(M, N, K, group);
+    *tb = p.tb;
+    *wv = p.wv;
+}
 
 int sqp_gemm_generic(int M, int N, int K, int group, const h16 *x, const uint32_t *packed, const h16 *scales,
                      const uint8_t *zeros, h16 *y, hipStream_t stream)
@@ -286,7 +342,7 @@ size_t sqp_gemm_decode_partial_bytes(int M, int N, int K, int group)
 {
     const int kspg = chunk_ksteps(K, group);
     if (kspg == 0) return 0;  // generic kernel
-    if (slice_variant(M, N, K, group) >= 0) return 0;
+    if (slices_alone(M, N, K, group)) return 0;
     return plan_bytes(plan_for(M, N, K, group, true), N, K, group, kspg, sqp_strip_row_tiles(M));
 }
 
@@ -304,8 +360,15 @@ size_t sqp_gemm_decode_least_bytes(int M, int N, int K, int group)
 int sqp_gemm_decode(int M, int N, int K, int group, const h16 *x, const uint32_t *packed, const h16 *scales,
                     const uint8_t *zeros, h16 *y, int epi, const SqpWorkspace &ws, hipStream_t stream)
 {
-    const int sv = slice_variant(M, N, K, group);
-    if (sv >= 0) return sqp_gemm_slice(sv, M, N, K, x, packed, scales, zeros, y, epi, stream);
+    SqpSlicePlan sp = slice_plan(M, N, K, group);
+    if (sp.tb) {
+        if (ws.partial != nullptr && ws.partial_bytes < sqp_gemm_decode_least_bytes(M, N, K, group)) return SQP_ERR_WORKSPACE;
+        if (epi != 0 && sp.tb == 1) sp.tb = 2;  // a lane's columns are whole (gate, up) pairs
+        if (group == 32) return sqp_slice_g32(sp, M, N, K, 1, x, packed, scales, zeros, y, epi, stream);
+        if (group == 64) return sqp_slice_g64(sp, M, N, K, 1, x, packed, scales, zeros, y, epi, stream);
+        if (group == 128) return sqp_slice_g128(sp, M, N, K, 1, x, packed, scales, zeros, y, epi, stream);
+        return sqp_slice_g256(sp, M, N, K, group / 128, x, packed, scales, zeros, y, epi, stream);
+    }
     const int kspg = chunk_ksteps(K, group);
     if (kspg == 0) {
         if (epi != 0) return SQP_ERR_SHAPE;  // the fused activation needs a group size the matrix-core kernels cover

@@ -1,0 +1,489 @@
+// Column-slice variant of the weight-streaming W4A16 GEMM (decode, up to 32 rows): y = x * w_hat, Eq. 3 of
+// arXiv 2312.03788 with w_hat = (code - Z) * Delta of Eq. 1, group-wise along K (Sec 2.2).
+//
+// The strip kernel splits K across workgroups to fill the chip, and the hand-over of partial
+// sums between workgroups (through memory, with a ticket) costs a fixed few microseconds per
+// launch - as much as streaming the whole layer on the narrowest ones.  Here a workgroup owns a
+// slice of 16 TB output columns (16, 32 or 64) over ALL of K and K is split between its waves
+// instead: wave w takes the chunks (128 k each) w, w + WV, w + 2 WV, ...; the waves never meet
+// in the main loop (each fetches the activations of its own chunks into LDS slots of
+// its own, so there is no barrier) and add their fp32 sums through LDS at the end, in wave
+// order: no workspace, no tickets, and the result does not depend on scheduling.
+// The price: every workgroup fetches all of x (from L2), workgroups x rows x K x 2 bytes per
+// launch.  Only the blocks of four rows that hold real rows are fetched.
+//
+// Column mapping: lane (lc = lane % 16, lk = lane / 16) holds the TB adjacent columns
+// n0 + TB lc ... (one load per k-step: their packed words, k-block lk), which are
+// the B operands of TB v_mfma_f32_16x16x32_f16 (column block b = every TB-th column of the
+// slice, starting at b); their steps Delta are one load, their zero points another.  With the
+// fused SiLU(gate)*up output a lane's columns are whole (gate, up) pairs (TB >= 2).
+//
+// Unpack.  A nibble masked out of the word IS an fp16 number: the bits 3:0 of a half are the denormal
+// q * 2^-24 and the bits 7:4 are q * 2^-20, which the matrix cores multiply exactly.  So a word costs one
+// shift and four ANDs instead of nine operations (no exponent to put in, no offset to take out), the
+// two scales go to two accumulators (lo, hi: the same-scale halves of two k-steps make one operand), and
+// the zero point leaves through sum_k x (q - Z) = sum_k x q - Z sum_k x, with sum_k x from one more MFMA
+// against ones per operand of x.  All products are exact and all sums fp32, as before; what joins them
+// is three FMAs per accumulator register, column and group.  Rows are repeated in the 16-row operand
+// so that up to 4 (8) rows need only 1 (2) of the 4 registers of a lane scaled.
+// Groups of 32 have one k-step per group and keep the other unpack (dequant_word), and so do 9 and more rows
+// with four columns per lane (4096->22016, 16 rows: 14.4 against 13.7 us) and 17 and more rows, where three FMAs
+// for each of the registers cost what the unpack saves.
+//
+// What bounds it: up to 8 rows the vector instructions (one row, 64 columns: 220 -> 140 per chunk and wave with
+// the new unpack), on narrow layers the latency of a wave's chunks, with many rows the activations.
+// us per launch in a replayed graph, before -> now, 1 / 8 / 16 rows (before: the strip kernel where N < 3072
+// or K = 11008): 1024->1024 6.2 / 6.3 / 6.4 -> 2.0 / 2.1 / 2.3, 4096->1024 6.7 / 6.9 / 7.0 -> 2.8 / 3.0 / 3.5,
+// 4096->4096 4.4 / 5.2 / 5.7 -> 2.9 / 4.1 / 4.8, 4096->12288 6.7 / 7.5 / 8.4 -> 5.7 / 6.7 / 7.6,
+// 4096->22016 11.3 / 12.7 / 13.9 -> 10.0 / 11.4 / 13.5, 11008->4096 at one row 8.9 -> 8.0.
+// Three and four stages per wave are slower everywhere (again, also with loads masked instead of skipped
+// at the end).
+#pragma once
+#include <type_traits>
+
+#include "sqp_common.h"
+#include "sqp_slice.h"
+#include "sqp_w4_unpack.h"
+
+namespace {
+
+// MT: 16-row tiles.  TB: columns per lane.  WV: waves per workgroup, each with two stages (registers for
+// the weight side, LDS slots for the activations): one chunk is in flight while one is consumed.
+// XB: blocks of four activation rows that are fetched (M <= 4 XB).
+// GS: k-steps of a chunk that belong to one group: four, two (groups of 64) or one (groups of 32).
+// CPG: groups of several chunks (GS == 4).
+template <int MT, int TB, int WV, int XB, int GS, bool CPG>
+__global__ void __launch_bounds__(WV * 64) __attribute__((amdgpu_waves_per_eu(MT == 1 && TB == 4 && WV == 8 && GS == 4 ? 4 : 1)))
+w4a16_decode_slice_kernel(int M, int N, int K, int cpg, int grouped, const h16 *__restrict__ x, const uint32_t *__restrict__ packed,
+                          const h16 *__restrict__ scales, const uint8_t *__restrict__ zeros, h16 *__restrict__ y, int epi)
+{
+    constexpr int NQ = 4 / GS;            // groups per chunk
+    constexpr int XSTAGE = XB * 1024;     // one chunk of x: 4 XB rows of 256 bytes, as 1 KB blocks of four rows
+    // Row i of the matrix operand is row i / RS of x: a lane's accumulator registers 4 lk + r then repeat, and
+    // RR of the four are distinct.
+    constexpr int RR = XB == 1 ? 1 : (XB == 2 ? 2 : 4), RS = 4 / RR;
+    // Nibbles as they are (see above) wherever that is less work: groups of two and more k-steps, and not with
+    // four columns or two row tiles whose registers all have to be scaled.
+    constexpr bool NIBBLES = GS > 1 && MT == 1 && (RR < 4 || TB < 4);
+    static_assert(TB == 1 || TB == 2 || TB == 4, "columns per lane");
+    static_assert(MT == 1 ? XB <= 4 : XB > 4 && XB <= 8, "row tiles");
+    static_assert(!CPG || GS == 4, "several chunks per group");
+    constexpr int RING = WV * 2 * XSTAGE, EXCH = WV * MT * RR * TB * 256;  // the exchange of sums at the end reuses the rings
+    __shared__ __attribute__((aligned(1024))) unsigned char xring[RING > EXCH ? RING : EXCH];
+    static_assert(sizeof(xring) <= 160 * 1024, "LDS of a workgroup");
+
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lc = lane & 15, lk = lane >> 4;
+    // Workgroups go to the eight XCDs in turn.  grouped: four adjacent slices run on one XCD, so that the
+    // 128-byte lines of weights, steps and zero points they share come through one L2 once.
+    int slice = blockIdx.x;
+    if (grouped && slice < ((int)gridDim.x & ~31)) slice = (slice & ~31) + (slice & 7) * 4 + ((slice >> 3) & 3);
+    const int n0 = slice * (16 * TB);
+    const int chunks = (K + 127) / 128;
+    const int tail_ks = GS < 4 ? (K - (chunks - 1) * 128) / 32 : 4;  // k-steps of the last chunk
+    // lanes past the last column read column 0 instead; their results are never stored
+    const int nout = n0 + TB * lc;
+    const int ncol = nout < N ? nout : 0;
+    // this wave's chunks: wv, wv + WV, ...  (none when the layer has fewer chunks than waves)
+    const int nmine = wv < chunks ? (chunks - wv + WV - 1) / WV : 0;
+    const int c0 = wv < chunks ? wv : 0;
+    const bool my_tail = GS < 4 && tail_ks < 4 && c0 + (nmine - 1) * WV == chunks - 1;  // this wave's last chunk is a short one
+
+    float acc[MT][TB][RR];
+    auto clear = [&]() {
+#pragma unroll
+        for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+            for (int b = 0; b < TB; b++)
+#pragma unroll
+                for (int r = 0; r < RR; r++) acc[mt][b][r] = 0.f;
+    };
+    clear();
+
+    typedef typename std::conditional<TB == 1, uint32_t, uint32_t __attribute__((ext_vector_type(TB == 1 ? 2 : TB)))>::type wvec;  // the packed words of the lane's columns
+    typedef typename std::conditional<TB == 4, u32x2, uint32_t>::type svec;                                                       // their fp16 steps
+    struct Stage {
+        wvec w[4];       // per k-step
+        svec sc[NQ];     // per group
+        uint32_t zr[NQ];  // zero points, one byte each
+    };
+
+    // Addresses: a wave-uniform byte pointer per stream (stepped on the scalar unit) plus a
+    // per-lane 32-bit offset that never changes.
+    const uint32_t voff_w = (uint32_t)(lk * N + ncol) * 4u;
+    const uint32_t voff_s = (uint32_t)ncol * 2u, voff_z = (uint32_t)ncol;
+    const long wstep1 = (long)N * 16;  // one k-step: four packed rows, in bytes
+    const long dw = (long)WV * 4 * wstep1;
+    const int drem = CPG ? WV % cpg : 0;
+    const long drow = CPG ? WV / cpg : WV * NQ;
+    const unsigned char *wq, *sq, *zq, *xq;
+    int rem, cis;  // position of the chunk being issued in its group; that chunk
+    auto start = [&]() {
+        const long row = CPG ? c0 / cpg : (long)c0 * NQ;
+        rem = CPG ? c0 % cpg : 0;
+        cis = c0;
+        wq = reinterpret_cast<const unsigned char *>(packed) + (long)c0 * 4 * wstep1;
+        sq = reinterpret_cast<const unsigned char *>(scales) + row * N * 2;
+        zq = zeros + row * N;
+        xq = reinterpret_cast<const unsigned char *>(x) + (long)c0 * 256;
+    };
+    start();
+
+    // Activations of a chunk: XB direct global->LDS loads of 1 KB (four rows of 256 bytes
+    // each).  Lane i of a block handles row i / 16 of the block and fetches piece
+    // (i % 16) ^ (row % 16) of that row, so that a row's pieces (whole 128-byte lines) come from
+    // adjacent lanes, while in LDS (where the hardware puts lane i at byte 16 i of the block)
+    // the pieces the 16 rows need for one k-step fall into 16 different bank groups.  Rows past
+    // M re-read row M - 1.
+    unsigned char *const ring = xring + wv * (2 * XSTAGE);
+    uint32_t xoff[XB];
+#pragma unroll
+    for (int j = 0; j < XB; j++) {
+        const int row = j * 4 + (lane >> 4);
+        const int rowc = row < M ? row : M - 1;
+        xoff[j] = (uint32_t)rowc * (uint32_t)K * 2u + (uint32_t)(((lane ^ row) & 15) * 16);
+    }
+
+    // Loads of one chunk, the weight side in assembly so that this kernel decides when to wait for them (a stage
+    // must not be read before `landed`) and with the non-temporal hint (every weight byte
+    // is read once per launch).  A short last chunk (K not a multiple of 128) reads its last k-step and
+    // group again in the place of those past K, and the first piece of each row of x; compute clears
+    // those fragments of x.
+    auto issue = [&](Stage &s, int slot) {
+        const bool tail = GS < 4 && tail_ks < 4 && cis == chunks - 1;  // wave-uniform
+#pragma unroll
+        for (int j = 0; j < XB; j++) {
+            uint32_t xo = xoff[j];
+            if constexpr (GS < 4)
+                if (tail) {
+                    const int piece = (lane ^ (j * 4 + (lane >> 4))) & 15;
+                    if (piece >= tail_ks * 4) xo -= (uint32_t)(piece * 16);
+                }
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(xq + xo),
+                                             (__attribute__((address_space(3))) void *)(ring + slot * XSTAGE + j * 1024), 16, 0, 0);
+        }
+        const unsigned char *b0 = wq, *b1 = b0 + wstep1, *b2 = b1 + wstep1, *b3 = b2 + wstep1;
+        if (GS < 4 && tail) {
+            b1 = tail_ks > 1 ? b1 : b0;
+            b2 = tail_ks > 2 ? b2 : b1;
+            b3 = b2;
+        }
+#define SQP_SLICE_WORDS(OP)                                                                                                  \
+    asm volatile(OP " %0, %4, %5 nt\n\t" OP " %1, %4, %6 nt\n\t" OP " %2, %4, %7 nt\n\t" OP " %3, %4, %8 nt"                 \
+                 : "=&v"(s.w[0]), "=&v"(s.w[1]), "=&v"(s.w[2]), "=&v"(s.w[3])                                               \
+                 : "v"(voff_w), "s"(b0), "s"(b1), "s"(b2), "s"(b3)                                                          \
+                 : "memory")
+        if constexpr (TB == 1) SQP_SLICE_WORDS("global_load_dword");
+        else if constexpr (TB == 2) SQP_SLICE_WORDS("global_load_dwordx2");
+        else SQP_SLICE_WORDS("global_load_dwordx4");
+#undef SQP_SLICE_WORDS
+        const unsigned char *sb = sq, *zb = zq;
+#pragma unroll
+        for (int q = 0; q < NQ; q++) {
+#define SQP_SLICE_PARAMS(OS, OZ)                                                           \
+    asm volatile(OS " %0, %2, %4 nt\n\t" OZ " %1, %3, %5 nt"                               \
+                 : "=&v"(s.sc[q]), "=&v"(s.zr[q])                                          \
+                 : "v"(voff_s), "v"(voff_z), "s"(sb), "s"(zb)                              \
+                 : "memory")
+            if constexpr (TB == 1) SQP_SLICE_PARAMS("global_load_ushort", "global_load_ubyte");
+            else if constexpr (TB == 2) SQP_SLICE_PARAMS("global_load_dword", "global_load_ushort");
+            else SQP_SLICE_PARAMS("global_load_dwordx2", "global_load_dword");
+#undef SQP_SLICE_PARAMS
+            const bool more = !tail || (q + 1) * GS < tail_ks;
+            sb += more ? (long)N * 2 : 0;
+            zb += more ? (long)N : 0;
+        }
+        wq += dw;
+        xq += WV * 256;
+        sq += drow * N * 2;
+        zq += drow * N;
+        if constexpr (GS < 4) cis += WV;
+        if constexpr (CPG) {
+            rem += drem;
+            const bool wrap = rem >= cpg;
+            rem -= wrap ? cpg : 0;
+            sq += wrap ? (long)N * 2 : 0;
+            zq += wrap ? (long)N : 0;
+        }
+    };
+    auto landed = [&](Stage &s) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // one chunk is in flight at a time
+#pragma unroll
+        for (int ks = 0; ks < 4; ks++) asm volatile("" : "+v"(s.w[ks]));
+#pragma unroll
+        for (int q = 0; q < NQ; q++) {
+            asm volatile("" : "+v"(s.sc[q]));
+            asm volatile("" : "+v"(s.zr[q]));
+        }
+    };
+
+    // LDS byte addresses of this lane's A fragments (row lc of the operand) in slot 0, per k-step and row tile
+    // (operand rows past the fetched ones repeat fetched rows: defined data, unused results)
+    uint32_t xrd[4][MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; mt++) {
+        int row = mt * 16 + lc / RS;
+        if (row >= 4 * XB) row -= 4 * XB - 16 * mt;
+        const uint32_t at = (uint32_t)(size_t)ring + (uint32_t)((row >> 2) * 1024 + (row & 3) * 256);
+#pragma unroll
+        for (int ks = 0; ks < 4; ks++) xrd[ks][mt] = at + (uint32_t)((((ks * 4 + lk) ^ row) & 15) * 16);
+    }
+    auto word_of = [](const Stage &s, int ks, int b) -> uint32_t {
+        if constexpr (TB == 1) return s.w[ks];
+        else return s.w[ks][b];
+    };
+    auto zero_of = [](const Stage &s, int q, int b) -> uint32_t { return (s.zr[q] >> (8 * b)) & 0xffu; };
+    auto step_of = [](const Stage &s, int q, int b) -> float {
+        uint32_t pair;
+        if constexpr (TB == 4) pair = s.sc[q][b >> 1];
+        else pair = s.sc[q];
+        const h16x2 v = __builtin_bit_cast(h16x2, pair);
+        return (float)((b & 1) ? v.y : v.x);
+    };
+
+    // One chunk.  CODES: the nibbles themselves; otherwise (also in the second pass below) the exact fp16
+    // differences code - Z.
+    auto compute = [&](const Stage &s, auto SLOT, bool tail, auto CODES) {
+        constexpr int slot = decltype(SLOT)::value;
+        // The A fragments are read with instructions written in assembly: the compiler cannot
+        // tell which ring slot a direct load filled and would wait for every outstanding load.
+        u32x4 xa[4][MT];
+#pragma unroll
+        for (int ks = 0; ks < 4; ks++)
+#pragma unroll
+            for (int mt = 0; mt < MT; mt++)
+                asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(xa[ks][mt]) : "v"(xrd[ks][mt]), "n"(slot * XSTAGE) : "memory");
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int ks = 0; ks < 4; ks++)
+#pragma unroll
+            for (int mt = 0; mt < MT; mt++) asm volatile("" : "+v"(xa[ks][mt]));  // no use ahead of the wait
+        if constexpr (GS < 4)
+            if (tail) {
+#pragma unroll
+                for (int ks = 1; ks < 4; ks++)
+#pragma unroll
+                    for (int mt = 0; mt < MT; mt++)
+                        if (ks >= tail_ks) xa[ks][mt] = u32x4{0, 0, 0, 0};
+            }
+        // The accumulators are kept whole until a sum of theirs has been read (the asm statements behind the
+        // FMAs): a register that nothing reads would otherwise be free for an instruction in assembly while
+        // the MFMA still writes it, and the compiler adds no wait states for those.
+        const f32x4 none = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < NQ; q++) {
+            if constexpr (decltype(CODES)::value) {
+                const h16x8 ones = __builtin_bit_cast(h16x8, u32x4{0x3c003c00u, 0x3c003c00u, 0x3c003c00u, 0x3c003c00u});
+                f32x4 lo[MT][TB], hi[MT][TB], sx[MT];
+#pragma unroll
+                for (int mt = 0; mt < MT; mt++) {
+                    sx[mt] = none;
+#pragma unroll
+                    for (int b = 0; b < TB; b++) lo[mt][b] = hi[mt][b] = none;
+                }
+#pragma unroll
+                for (int ks = q * GS; ks < q * GS + GS; ks += 2) {
+                    h16x8 al[MT], ah[MT];  // of two k-steps: k 0, 4, 2, 6 of each word; k 1, 5, 3, 7
+#pragma unroll
+                    for (int mt = 0; mt < MT; mt++) {
+                        const h16x8 p0 = permute_x(xa[ks][mt]), p1 = permute_x(xa[ks + 1][mt]);
+                        al[mt] = h16x8{p0.s0, p0.s1, p0.s4, p0.s5, p1.s0, p1.s1, p1.s4, p1.s5};
+                        ah[mt] = h16x8{p0.s2, p0.s3, p0.s6, p0.s7, p1.s2, p1.s3, p1.s6, p1.s7};
+                        sx[mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[mt], ones, sx[mt], 0, 0, 0);
+                        sx[mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[mt], ones, sx[mt], 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int b = 0; b < TB; b++) {
+                        const uint32_t w0 = word_of(s, ks, b), w1 = word_of(s, ks + 1, b), e0 = w0 >> 8, e1 = w1 >> 8;
+                        constexpr uint32_t ML = 0x000f000fu, MH = 0x00f000f0u;
+                        const h16x8 bl = __builtin_bit_cast(h16x8, u32x4{w0 & ML, e0 & ML, w1 & ML, e1 & ML});
+                        const h16x8 bh = __builtin_bit_cast(h16x8, u32x4{w0 & MH, e0 & MH, w1 & MH, e1 & MH});
+#pragma unroll
+                        for (int mt = 0; mt < MT; mt++) {
+                            lo[mt][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[mt], bl, lo[mt][b], 0, 0, 0);
+                            hi[mt][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[mt], bh, hi[mt][b], 0, 0, 0);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int b = 0; b < TB; b++) {
+                    const float z = (float)zero_of(s, q, b), d = step_of(s, q, b);
+#pragma unroll
+                    for (int mt = 0; mt < MT; mt++) {
+#pragma unroll
+                        for (int r = 0; r < RR; r++) {
+                            const float v = fmaf(hi[mt][b][r * RS], 1.0f / 16, lo[mt][b][r * RS]);  // in units of 2^-24
+                            acc[mt][b][r] = fmaf(d, fmaf(v, 16777216.0f, -z * sx[mt][r * RS]), acc[mt][b][r]);
+                        }
+                        asm volatile("" : "+v"(acc[mt][b][0]) : "v"(lo[mt][b]), "v"(hi[mt][b]), "v"(sx[mt]));
+                    }
+                }
+            } else {
+                // (column by column: the second pass must not need more registers than the first)
+                const UnpackConsts uc = SQP_UNPACK_CONSTS;
+#pragma unroll
+                for (int b = 0; b < TB; b++) {
+                    const uint32_t z = zero_of(s, q, b);
+                    const h16x2 neg_hi = neg_hi_of(z), neg_lo = neg_lo_of(z);
+                    const float d = step_of(s, q, b);
+                    f32x4 g[MT];
+#pragma unroll
+                    for (int ks = q * GS; ks < q * GS + GS; ks++) {
+                        const h16x8 w = dequant_word(word_of(s, ks, b), neg_hi, neg_lo, uc);
+#pragma unroll
+                        for (int mt = 0; mt < MT; mt++)
+                            g[mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(permute_x(xa[ks][mt]), w, ks == q * GS ? none : g[mt], 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int mt = 0; mt < MT; mt++) {
+#pragma unroll
+                        for (int r = 0; r < RR; r++) acc[mt][b][r] = fmaf(d, g[mt][r * RS], acc[mt][b][r]);
+                        asm volatile("" : "+v"(acc[mt][b][0]) : "v"(g[mt]));
+                    }
+                }
+            }
+        }
+    };
+
+    // Software pipeline over the wave's own chunks: the next one is in flight while one is consumed.
+    // Slot and stage of chunk i + 1 were consumed in iteration i - 1 by this same wave (its LDS
+    // reads have been waited for), so no barrier is needed.  Nothing is issued past the last chunk
+    // (wave-uniform branches): look-ahead loads that fetched its activations again cost the wait for
+    // them at the end (1 to 4 % per launch).
+    constexpr std::integral_constant<int, 0> S0 = {};
+    constexpr std::integral_constant<int, 1> S1 = {};
+    Stage st[2];
+    auto walk = [&](auto CODES) {
+        if (nmine > 0) issue(st[0], 0);
+        for (int i = 0; i < nmine; i += 2) {
+            landed(st[0]);
+            if (i + 1 < nmine) issue(st[1], 1);
+            compute(st[0], S0, my_tail && i == nmine - 1, CODES);
+            if (i + 1 < nmine) {
+                landed(st[1]);
+                if (i + 2 < nmine) issue(st[0], 0);
+                compute(st[1], S1, my_tail && i + 1 == nmine - 1, CODES);
+            }
+        }
+    };
+    walk(std::integral_constant<bool, NIBBLES>());
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (nothing is in flight here: for the reader of the assembly)
+#pragma unroll
+    for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+        for (int b = 0; b < TB; b++)
+#pragma unroll
+            for (int r = 0; r < RR; r++) asm volatile("" : "+v"(acc[mt][b][r]));
+    if constexpr (NIBBLES) {
+        // An infinity or a NaN in x makes sum x q - Z sum x a NaN where sum x (q - Z) need not be one: such
+        // a wave walks its chunks again with the differences.
+        float bad = 0.f;
+#pragma unroll
+        for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+            for (int b = 0; b < TB; b++)
+#pragma unroll
+                for (int r = 0; r < RR; r++) bad = fmaf(acc[mt][b][r], 0.f, bad);  // NaN if any sum is not finite
+        if (__builtin_amdgcn_ballot_w64(bad != 0.f) != 0ull) {  // (a NaN is not equal to 0)
+            clear();
+            start();
+            for (int i = 0; i < nmine; i++) {
+                issue(st[0], 0);
+                landed(st[0]);
+                compute(st[0], S0, my_tail && i == nmine - 1, std::false_type());
+            }
+        }
+    }
+
+    // ---- the waves add their sums through LDS (the rings are idle once every wave is here), in
+    // wave order: wave v < MT RR adds and stores register v % RR of row tile v / RR, i.e. the rows
+    // 16 mt + RR lk + r.  [wave][mt][r][lane] of TB floats.
+    __syncthreads();
+    typedef float fvec __attribute__((ext_vector_type(TB == 1 ? 2 : TB)));
+    typedef typename std::conditional<TB == 1, float, fvec>::type sums;
+    sums *ex = reinterpret_cast<sums *>(xring);
+#pragma unroll
+    for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+        for (int r = 0; r < RR; r++) {
+            sums v;
+            if constexpr (TB == 1) v = acc[mt][0][r];
+            else {
+#pragma unroll
+                for (int b = 0; b < TB; b++) v[b] = acc[mt][b][r];
+            }
+            ex[((wv * MT + mt) * RR + r) * 64 + lane] = v;
+        }
+    __syncthreads();
+    if (nout >= N) return;
+    for (int part = wv; part < MT * RR; part += WV) {
+        const int m = (part / RR) * 16 + RR * lk + part % RR;
+        if (m >= M) continue;
+        sums sum = ex[part * 64 + lane];
+#pragma unroll
+        for (int w = 1; w < WV; w++) sum += ex[(w * MT * RR + part) * 64 + lane];
+        // epi == 0: the fp16 values themselves, y [M][N].  epi == 1: the lane's columns are
+        // (gate, up) pairs of a merged, interleaved gate/up projection and the output is
+        // SiLU(gate) * up, y [M][N/2] (the LlamaMLP activation of Fig. 5, from the fp32 sums).
+        if constexpr (TB == 1) {
+            y[(size_t)m * N + nout] = (h16)sum;
+        } else if (epi == 0) {
+            typedef h16 hvec __attribute__((ext_vector_type(TB)));
+            hvec o;
+#pragma unroll
+            for (int b = 0; b < TB; b++) o[b] = (h16)sum[b];
+            *reinterpret_cast<hvec *>(y + (size_t)m * N + nout) = o;
+        } else {
+            h16 *out = y + (size_t)m * (N >> 1) + (nout >> 1);
+            if constexpr (TB == 2) {
+                out[0] = (h16)(sqp_silu(sum[0]) * sum[1]);
+            } else {
+                h16x2 o;
+                o.x = (h16)(sqp_silu(sum[0]) * sum[1]);
+                o.y = (h16)(sqp_silu(sum[2]) * sum[3]);
+                *reinterpret_cast<h16x2 *>(out) = o;
+            }
+        }
+    }
+}
+
+template <int MT, int TB, int WV, int XB, int GS, bool CPG>
+int launch_slices(bool grouped, int M, int N, int K, int cpg, const h16 *x, const uint32_t *packed, const h16 *scales, const uint8_t *zeros, h16 *y,
+                  int epi, hipStream_t st)
+{
+    w4a16_decode_slice_kernel<MT, TB, WV, XB, GS, CPG>
+        <<<(N + 16 * TB - 1) / (16 * TB), WV * 64, 0, st>>>(M, N, K, cpg, grouped, x, packed, scales, zeros, y, epi);
+    return sqp_launch_status();
+}
+
+// Up to 16 rows, by the blocks of four rows that hold real rows.
+template <int TB, int WV, int GS, bool CPG>
+int slices_rows16(bool grouped, int M, int N, int K, int cpg, const h16 *x, const uint32_t *packed, const h16 *scales, const uint8_t *zeros, h16 *y,
+                  int epi, hipStream_t st)
+{
+    if (M <= 4) return launch_slices<1, TB, WV, 1, GS, CPG>(grouped, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
+    if (M <= 8) return launch_slices<1, TB, WV, 2, GS, CPG>(grouped, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
+    if (M <= 12) return launch_slices<1, TB, WV, 3, GS, CPG>(grouped, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
+    return launch_slices<1, TB, WV, 4, GS, CPG>(grouped, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
+}
+
+template <int GS, bool CPG>
+int dispatch_slices(const SqpSlicePlan &p, int M, int N, int K, int cpg, const h16 *x, const uint32_t *packed, const h16 *scales,
+                    const uint8_t *zeros, h16 *y, int epi, hipStream_t st)
+{
+    const bool g = p.grouped;
+    if (M > 16) {
+        if (p.tb == 1) return launch_slices<2, 1, 8, 8, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
+        if (p.tb == 2) return launch_slices<2, 2, 8, 8, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
+        return launch_slices<2, 4, 8, 8, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
+    }
+    if (p.tb == 1 && p.wv == 8) return slices_rows16<1, 8, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
+    if (p.tb == 1) return slices_rows16<1, 16, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
+    if (p.tb == 2 && p.wv == 8) return slices_rows16<2, 8, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
+    if (p.tb == 2) return slices_rows16<2, 16, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
+    if (p.wv == 4) return slices_rows16<4, 4, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
+    return slices_rows16<4, 8, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
+}
+
+}  // namespace

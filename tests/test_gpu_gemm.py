@@ -430,6 +430,60 @@ def test_decode_slice_integer_exact(orc, sqp, mode):
     assert np.array_equal(y, (x @ q).astype(np.float16))
 
 
+@pytest.mark.parametrize("tb,wv,grouped", [(1, 8, 0), (1, 16, 1), (2, 8, 1), (2, 16, 0), (4, 4, 0), (4, 8, 1)])
+@pytest.mark.parametrize("M,K,N,group", [
+    (1, 128, 8, 128), (4, 1152, 520, 128), (5, 128 * 17, 40, 128), (8, 2304, 1032, 768), (9, 512, 2056, 256), (16, 128 * 19, 264, 128),
+    (2, 64, 24, 64), (7, 192, 520, 64), (12, 64 * 33, 1032, 64), (3, 32, 16, 32), (6, 1120, 264, 32), (13, 1056, 72, 32), (16, 992, 2056, 32),
+    (17, 384, 136, 128), (24, 768, 520, 384), (31, 1088, 1032, 64), (32, 1248, 264, 32)])
+def test_decode_slice_variants(orc, sqp, M, K, N, group, tb, wv, grouped):
+    """Every slice width and wave count of the column-slice kernel, forced: fewer chunks than waves and chunk
+    counts that do not divide among them, a last chunk of one to three k-steps, several groups per
+    chunk and several chunks per group (also with a group boundary inside a wave's stride), ragged
+    columns, slices mapped to XCDs in fours with and without a remainder; bit-identical repeats."""
+    print("case slice variants", M, K, N, group, tb, wv, grouped, flush=True)
+    xs, p, sc, z = _layer(orc, M, K, N, group)
+    L = sqp.lib()
+    L.sqp_debug_set_slice_plan(tb, wv, grouped)
+    try:
+        y0 = _check(orc, sqp, xs, p, sc, z, group)
+        y1 = _check(orc, sqp, xs, p, sc, z, group)
+        assert np.array_equal(y0.view(np.uint16), y1.view(np.uint16))
+    finally:
+        L.sqp_debug_set_slice_plan(0, 0, 0)
+
+
+@pytest.mark.parametrize("M,group,tb,wv", [(1, 128, 1, 8), (6, 64, 2, 8), (16, 256, 2, 16), (3, 128, 4, 8), (20, 64, 2, 8)])
+def test_decode_slice_nonfinite_activations(orc, sqp, M, group, tb, wv):
+    """An infinity or a NaN among the activations gives what the strip kernel gives for it (sums over the
+    differences code - Z: an infinity times a code above, below or at the zero point), and rows without any
+    are not touched by it."""
+    K, N = 1024, 264
+    xs, p, sc, z = _layer(orc, M, K, N, group)
+    clean = xs.copy()
+    xs[0, 333] = np.inf
+    if M > 2:
+        xs[2, 100], xs[2, 900] = -np.inf, np.nan
+    L = sqp.lib()
+    run = lambda a: host(sqp.w4a16_gemm(dev(a), dev(p), dev(sc), dev(z), group))
+    try:
+        L.sqp_debug_set_decode_slice(-1)
+        want = run(xs)
+        L.sqp_debug_set_decode_slice(0)
+        L.sqp_debug_set_slice_plan(tb, wv, 0)
+        got, ref = run(xs), run(clean)
+    finally:
+        L.sqp_debug_set_decode_slice(0)
+        L.sqp_debug_set_slice_plan(0, 0, 0)
+    hit = [0] if M <= 2 else [0, 2]
+    assert np.isinf(want[0]).any()
+    assert np.array_equal(np.isnan(got[hit]), np.isnan(want[hit]))
+    inf = np.isinf(want[hit])
+    assert np.array_equal(got[hit][inf], want[hit][inf])
+    rest = [m for m in range(M) if m not in hit]
+    # their sums are those of the differences where a wave walked its chunks again: fp32 rounding, then fp16's
+    assert np.allclose(got[rest].astype(np.float64), ref[rest].astype(np.float64), rtol=2e-3, atol=1e-3 * np.abs(ref).max())
+
+
 @pytest.mark.parametrize("M,K,N,group", _random_shapes(202, 8, 65, 700))
 def test_prefill_random_shapes(orc, sqp, M, K, N, group):
     """Random shapes above 64 rows (tiled kernel: wide and narrow tiles, K parts; groups of 32

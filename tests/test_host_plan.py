@@ -102,6 +102,21 @@ def test_slice_calls_need_no_workspace(L):
         assert L.sqp_w4a16_gemm_workspace_bytes(16, N, K, 128) > 512 << 10
 
 
+def test_slice_plan_values(L):
+    """Widths and waves at the edges of the rule: one round of 16, 32 and 64 columns, the K from which the
+    strip kernel takes over, groups and K that it covers badly."""
+    def plan(M, N, K, g):
+        tb, wv = ctypes.c_int(), ctypes.c_int()
+        L.sqp_debug_decode_slice_plan(M, N, K, g, ctypes.byref(tb), ctypes.byref(wv))
+        return tb.value, wv.value
+    assert plan(1, 4096, 4096, 128) == (1, 16) and plan(1, 4104, 4096, 128)[0] == 2
+    assert plan(8, 8192, 4096, 128) == (2, 8) and plan(8, 8200, 4096, 128) == (4, 8)
+    assert plan(1, 1024, 12288, 128) == (1, 16) and plan(1, 1024, 12416, 128) == (0, 0)
+    assert plan(16, 1024, 6144, 64) == (1, 8) and plan(16, 1024, 6208, 64) == (1, 8) and plan(16, 1024, 6272, 64) == (0, 0)
+    assert plan(32, 16384, 9216, 128)[0] == 4 and plan(33, 16384, 1024, 128) == (0, 0)
+    assert plan(4, 22016, 4096, 128) == (4, 4) and plan(4, 22016, 4096, 32) == (2, 8) and plan(1, 4096, 4096, 24) == (0, 0)
+
+
 def test_decode_plan_many_rows(L):
     """More than 32 rows: two strips per workgroup, the split of the 16-row plan."""
     for (K, N) in wl.MODEL_SHAPES["34b"]:
