@@ -219,6 +219,18 @@ int sqp_alpha_search(int T, int N, int K, int group, int n_alpha, const float *a
                      const void *w, float *amax, float *s, void *x_hat, void *w_s, uint32_t *packed,
                      void *scales, uint8_t *zeros, double *scratch, double *loss, int *best, void *stream);
 
+/* The same search for callers that want the losses alone: all work buffers lie in one scratch buffer, which
+ * may be larger, so that several alphas share a launch and the next ones are prepared beside them.
+ * The losses are those of sqp_alpha_search, bit for bit.
+ *   scratch  device, 16-byte aligned, overwritten; nothing in it is needed before or after the call
+ *   scratch_bytes  sqp_alpha_search_scratch_bytes() for the preferred plan; with less a plan that fits
+ *                  runs, and where not even one alpha's operands fit the call is refused with
+ *                  SQP_ERR_WORKSPACE, nothing enqueued
+ * sqp_alpha_search_scratch_bytes: host arithmetic only, 0 for invalid arguments. */
+size_t sqp_alpha_search_scratch_bytes(int T, int N, int K, int group, int n_alpha);
+int sqp_alpha_search_scratch(int T, int N, int K, int group, int n_alpha, const float *alphas, const void *x_cal,
+                             const void *w, void *scratch, size_t scratch_bytes, double *loss, int *best, void *stream);
+
 #pragma GCC visibility pop
 #ifdef __cplusplus
 }

@@ -17,7 +17,7 @@ _LIB_PATH = os.environ.get("SQP_LIBRARY", os.path.join(_HERE, "libsqp.so"))  # o
 EXPORTS = ["sqp_status_string", "sqp_smooth_scales", "sqp_smooth_apply_x", "sqp_smooth_apply_w",
            "sqp_quantize_pack", "sqp_dequantize", "sqp_w4a16_gemm", "sqp_quant_loss", "sqp_transpose_nk",
            "sqp_w4a16_gemm_silu_mul", "sqp_rmsnorm", "sqp_scale_columns", "sqp_interleave_gate_up",
-           "sqp_set_workspace", "sqp_alpha_search", "sqp_w4a16_gemm_static", "sqp_w4a16_gemm_scratch"]
+           "sqp_set_workspace", "sqp_alpha_search", "sqp_w4a16_gemm_static", "sqp_w4a16_gemm_scratch", "sqp_alpha_search_scratch"]
 
 
 class SqpError(RuntimeError):
@@ -57,6 +57,9 @@ def lib():
         L.sqp_quant_loss_scratch_doubles.argtypes = [i, i]
         L.sqp_set_workspace.argtypes = [vp, ctypes.c_size_t, vp]
         L.sqp_alpha_search.argtypes = [i, i, i, i, i, ctypes.POINTER(ctypes.c_float)] + [vp] * 13
+        L.sqp_alpha_search_scratch.argtypes = [i, i, i, i, i, ctypes.POINTER(ctypes.c_float), vp, vp, vp, ctypes.c_size_t, vp, vp, vp]
+        L.sqp_alpha_search_scratch_bytes.argtypes = [i, i, i, i, i]
+        L.sqp_alpha_search_scratch_bytes.restype = ctypes.c_size_t
         L.sqp_w4a16_gemm_workspace_bytes.argtypes = [i, i, i, i]
         L.sqp_w4a16_gemm_workspace_bytes.restype = ctypes.c_size_t
         L.sqp_w4a16_gemm_workspace_least_bytes.argtypes = [i, i, i, i]
@@ -358,7 +361,7 @@ def quant_loss(x, w, x_hat, packed, scales, zeros, group=128, out=None):
 
 
 def alpha_search(x_cal, w, group=128, alphas=None):
-    """Single-layer search for the smoothing strength (Sec 2.2) through sqp_alpha_search: the
+    """Single-layer search for the smoothing strength (Sec 2.2) through sqp_alpha_search_scratch: the
     per-channel maxima once, then Eq. 6 -> Eq. 5 -> Eq. 1 -> Eq. 4 per alpha and the argmin, all
     in library kernels.  Returns (best alpha, list of (alpha, loss))."""
     if alphas is None:
@@ -371,22 +374,13 @@ def alpha_search(x_cal, w, group=128, alphas=None):
     dev = w.device
     n = len(alphas)
     host_alphas = (ctypes.c_float * n)(*[float(a) for a in alphas])
-    amax = torch.empty(2 * K, dtype=torch.float32, device=dev)
-    s = torch.empty(K, dtype=torch.float32, device=dev)
-    xh = torch.empty_like(x_cal)
-    ws = torch.empty_like(w)
-    packed = torch.empty((K // 8, N), dtype=torch.int32, device=dev)
-    scales = torch.empty((K // group, N), dtype=torch.float16, device=dev)
-    zeros = torch.empty((K // group, N), dtype=torch.uint8, device=dev)
-    scratch = torch.empty(int(L.sqp_quant_loss_scratch_doubles(T, N)), dtype=torch.float64, device=dev)
+    nbytes = int(L.sqp_alpha_search_scratch_bytes(T, N, K, group, n))
+    scratch = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=dev)
     loss = torch.empty(n, dtype=torch.float64, device=dev)
     best = torch.empty(1, dtype=torch.int32, device=dev)
-    _check(L.sqp_alpha_search(T, N, K, group, n, host_alphas, _dev(x_cal, torch.float16, "x_cal"), _dev(w, torch.float16, "w"),
-                              _dev(amax, torch.float32, "amax"), _dev(s, torch.float32, "s"), _dev(xh, torch.float16, "x_hat"),
-                              _dev(ws, torch.float16, "w_s"), _dev(packed, torch.int32, "packed"),
-                              _dev(scales, torch.float16, "scales"), _dev(zeros, torch.uint8, "zeros"),
-                              _dev(scratch, torch.float64, "scratch"), _dev(loss, torch.float64, "loss"),
-                              _dev(best, torch.int32, "best"), _stream()), "sqp_alpha_search")
+    _check(L.sqp_alpha_search_scratch(T, N, K, group, n, host_alphas, _dev(x_cal, torch.float16, "x_cal"), _dev(w, torch.float16, "w"),
+                                      _dev(scratch, torch.uint8, "scratch"), scratch.numel(), _dev(loss, torch.float64, "loss"),
+                                      _dev(best, torch.int32, "best"), _stream()), "sqp_alpha_search")
     vals = [float(v) for v in loss.cpu()]
     b = int(best.cpu()[0])
     return float(alphas[b]), list(zip([float(a) for a in alphas], vals))

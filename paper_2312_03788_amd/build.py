@@ -33,7 +33,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hi
 GUARDED_KERNELS = {**{s: ("w4a16_decode_kernel", "none") for s in SOURCES if s.startswith("sqp_strip_")},
                    **{s: ("w4a16_decode_slice_kernel", "none") for s in SOURCES if s.startswith("sqp_slice_")},
                    "sqp_gemm_prefill.hip": ("w4a16_prefill_kernel", "after-last-barrier"),
-                   "sqp_loss.hip": ("loss_tile_kernel", "none")}
+                   "sqp_loss.hip": ("loss_", "none")}
 
 
 def _check_no_spills(src, remarks):

@@ -9,7 +9,7 @@
 // thus stays near the difference: summed one after the other, every rounding would be relative to
 // |X W| with its outlier channels (an order of magnitude more at K = 5120).  Two kernels do that:
 //   loss_tile_kernel   K a multiple of 64, groups of 32 or a multiple of 64: every layer of the paper's
-//                      models
+//                      models (loss_pair_kernel: the same for two alphas of a search at once)
 //   quant_loss_kernel  any other K or group
 // A workgroup owns a 128 x 128 tile, squares and sums its accumulators in fp64 and writes one
 // partial; a second kernel adds the partials in a fixed order, so the result does not depend on
@@ -51,44 +51,69 @@ constexpr int SSLOT = 2 * SHALF;
 constexpr int SROW = (SBK + LPAD) * 2;        // bytes per LDS row of W
 constexpr int SWBUF = LBN * SROW;
 
-// PREP (0 or the group size): the workgroups past row loss_rows of the grid, as many as the loss
-// leaves compute units idle, prepare the next alpha meanwhile: weight tiles smoothed and quantised in
-// turn, activations divided.
-struct NextAlpha {
-    const float *s;            // [K] its smoothing factors
-    const uint4 *x, *w;        // activations, unsmoothed weight
-    uint4 *x_hat;              // what it fills
-    uint32_t *packed;
-    uint16_t *scales;
-    uint8_t *zeros;
-    int loss_rows, workgroups;
+
+// ---------------------------------------------------------------- preparation of a search's alphas
+
+struct SearchSets {                            // the prepared operands of one alpha, `stride` bytes apart
+    unsigned char *base;
+    size_t stride, at_scales, at_zeros, at_x;
+    __host__ __device__ uint32_t *packed(int i) const { return (uint32_t *)(base + i * stride); }
+    __host__ __device__ h16 *scales(int i) const { return (h16 *)(base + i * stride + at_scales); }
+    __host__ __device__ uint8_t *zeros(int i) const { return base + i * stride + at_zeros; }
+    __host__ __device__ h16 *x_hat(int i) const { return (h16 *)(base + i * stride + at_x); }
 };
+struct SearchBatch {
+    int set, n;                                // first set and number of alphas of the loss
+    int next_set, next_n;                      // of the preparation
+    const float *next_factors;                 // [next_n][K]
+};
+constexpr int SEARCH_X_OCTS = 4096;            // 8-element pieces of x per workgroup of the preparation
+
+// Piece `item` of the preparation of `n` alphas: weight tiles first, each for all alphas in turn (the tile then
+// comes out of L2), then x.
+template <int G>
+__device__ __forceinline__ void prepare_piece(int item, int T, int N, int K, const h16 *x, const h16 *w, const SearchSets &sets, int set, int n,
+                                              const float *factors, unsigned char *lds)
+{
+    typedef QuantizeTile<G, 512> Tile;
+    const int tx = (N + 255) / 256, tiles = tx * ((K + 255) / 256);
+    const int at = item / n, a = item % n;
+    const float *s = factors + (size_t)a * K;
+    if (at < tiles) {
+        quantize_tile<G, 512, true>(at % tx, at / tx, N, K, (const uint4 *)w, s, sets.packed(set + a), (uint16_t *)sets.scales(set + a),
+                                    sets.zeros(set + a), *reinterpret_cast<Tile *>(lds));
+        return;
+    }
+    const int KO = K >> 3;
+    const long first = (long)(at - tiles) * SEARCH_X_OCTS, octs = (long)T * KO;
+    const float4 *s4 = reinterpret_cast<const float4 *>(s);
+    uint4 *out = (uint4 *)sets.x_hat(set + a);
+    for (long i = first + threadIdx.x; i < octs && i < first + SEARCH_X_OCTS; i += 512) {
+        const int ko = (int)(i % KO);
+        out[i] = code_order(smooth_x8(((const uint4 *)x)[i], s4[2 * ko], s4[2 * ko + 1]));
+    }
+}
+int prepare_pieces(int T, int N, int K, int n)
+{
+    return n * (((N + 255) / 256) * ((K + 255) / 256) + (int)(((long)T * (K / 8) + SEARCH_X_OCTS - 1) / SEARCH_X_OCTS));
+}
+
+// PREP (0 or the group size): the workgroups behind the `losses` of the grid prepare the next alpha, one piece each.
 template <bool G32, bool CODE, int PREP>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
 loss_tile_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, const h16 *__restrict__ w,
                  const h16 *__restrict__ xh, const uint32_t *__restrict__ packed, const h16 *__restrict__ scales,
-                 const uint8_t *__restrict__ zeros, double *__restrict__ partials, NextAlpha next)
+                 const uint8_t *__restrict__ zeros, double *__restrict__ partials, SearchSets sets, SearchBatch batch)
 {
     constexpr int D = 3;                      // ring slots and register stages
     __shared__ __attribute__((aligned(1024))) unsigned char lds[D * SSLOT + 2 * SWBUF];
     __shared__ double red[8];
     static_assert(sizeof(lds) + sizeof(red) <= 160 * 1024, "LDS of a workgroup");
+    const int tiles_x = (N + LBN - 1) / LBN, losses = tiles_x * ((M + LBM - 1) / LBM);
     if constexpr (PREP != 0) {
-        if ((int)blockIdx.y >= next.loss_rows) {
-            typedef QuantizeTile<PREP, 512> Tile;
-            static_assert(sizeof(Tile) <= sizeof(lds), "the quantiser's LDS fits the ring");
-            const int wg = ((int)blockIdx.y - next.loss_rows) * gridDim.x + blockIdx.x;
-            if (wg >= next.workgroups) return;
-            const int tx = (N + 255) / 256, tiles = tx * ((K + 255) / 256);
-            for (int t = wg; t < tiles; t += next.workgroups)
-                quantize_tile<PREP, 512, true>(t % tx, t / tx, N, K, next.w, next.s, next.packed, next.scales, next.zeros,
-                                               *reinterpret_cast<Tile *>(lds));
-            const int KO = K >> 3;
-            const float4 *s4 = reinterpret_cast<const float4 *>(next.s);
-            for (long i = (long)wg * 512 + threadIdx.x; i < (long)M * KO; i += (long)next.workgroups * 512) {
-                const int ko = (int)(i % KO);
-                next.x_hat[i] = code_order(smooth_x8(next.x[i], s4[2 * ko], s4[2 * ko + 1]));
-            }
+        static_assert(sizeof(QuantizeTile<PREP, 512>) <= sizeof(lds), "the quantiser's LDS fits the ring");
+        if ((int)blockIdx.x >= losses) {
+            prepare_piece<PREP>(blockIdx.x - losses, M, N, K, x, w, sets, batch.next_set, batch.next_n, batch.next_factors, lds);
             return;
         }
     }
@@ -97,8 +122,7 @@ loss_tile_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, cons
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kh = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
     const int l32 = lane & 31, kb = lane >> 5;
-    const int m0 = blockIdx.y * LBM, n0 = blockIdx.x * LBN;
-    const long block = (long)blockIdx.y * gridDim.x + blockIdx.x;
+    const int m0 = (int)blockIdx.x / tiles_x * LBM, n0 = (int)blockIdx.x % tiles_x * LBN;
     const int stages = K / SBK;
     const int ncol = n0 + wn * 64 + 2 * l32;                   // this lane's two columns (N is even: both in or out)
     const bool ncol_ok = ncol < N;
@@ -381,40 +405,435 @@ loss_tile_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, cons
     for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 64);
     if (lane == 0) red[wave] = ss;
     __syncthreads();
-    if (tid == 0) partials[block] = (red[0] + red[1]) + (red[2] + red[3]);
+    if (tid == 0) partials[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 // Whether loss_tile_kernel covers a shape.
 bool loss_tile_covers(int K, int group) { return K % SBK == 0 && (group == 32 || group % SBK == 0); }
 
+int loss_tiles(int M, int N) { return ((M + LBM - 1) / LBM) * ((N + LBN - 1) / LBN); }
+
 template <bool CODE>
 void launch_loss_tile(int M, int N, int K, int group, const void *x, const void *w, const void *x_hat, const uint32_t *packed,
                       const void *scales, const uint8_t *zeros, double *partials, hipStream_t st)
 {
-    const dim3 grid((N + LBN - 1) / LBN, (M + LBM - 1) / LBM);
     if (group == 32)
-        loss_tile_kernel<true, CODE, 0><<<grid, 512, 0, st>>>(M, N, K, group, (const h16 *)x, (const h16 *)w, (const h16 *)x_hat, packed,
-                                                              (const h16 *)scales, zeros, partials, NextAlpha());
+        loss_tile_kernel<true, CODE, 0><<<loss_tiles(M, N), 512, 0, st>>>(M, N, K, group, (const h16 *)x, (const h16 *)w, (const h16 *)x_hat,
+                                                                          packed, (const h16 *)scales, zeros, partials, SearchSets(), SearchBatch());
     else
-        loss_tile_kernel<false, CODE, 0><<<grid, 512, 0, st>>>(M, N, K, group, (const h16 *)x, (const h16 *)w, (const h16 *)x_hat, packed,
-                                                               (const h16 *)scales, zeros, partials, NextAlpha());
+        loss_tile_kernel<false, CODE, 0><<<loss_tiles(M, N), 512, 0, st>>>(M, N, K, group, (const h16 *)x, (const h16 *)w, (const h16 *)x_hat,
+                                                                           packed, (const h16 *)scales, zeros, partials, SearchSets(), SearchBatch());
 }
 
-// The loss of one alpha beside the preparation of the next (groups of 32, 64, 128, 256).
-void launch_loss_and_next(int M, int N, int K, int group, const void *x, const void *w, const void *x_hat, const uint32_t *packed,
-                          const void *scales, const uint8_t *zeros, double *partials, NextAlpha next, hipStream_t st)
+// The loss of one alpha (set b.set) beside the preparation of the next.
+template <int G>
+void launch_loss_and_next(int M, int N, int K, int group, const void *x, const void *w, const SearchSets &sets, const SearchBatch &b, double *partials,
+                          hipStream_t st)
 {
-    const int gx = (N + LBN - 1) / LBN, gy = (M + LBM - 1) / LBM;
-    next.loss_rows = gy;
-    const dim3 grid(gx, gy + (next.workgroups + gx - 1) / gx);
-#define SQP_LOSS_NEXT(G32, G) \
-    loss_tile_kernel<G32, true, G><<<grid, 512, 0, st>>>(M, N, K, group, (const h16 *)x, (const h16 *)w, (const h16 *)x_hat, packed, (const h16 *)scales, zeros, partials, next)
-    if (group == 32) SQP_LOSS_NEXT(true, 32);
-    else if (group == 64) SQP_LOSS_NEXT(false, 64);
-    else if (group == 128) SQP_LOSS_NEXT(false, 128);
-    else SQP_LOSS_NEXT(false, 256);
-#undef SQP_LOSS_NEXT
+    loss_tile_kernel<G == 32, true, G><<<loss_tiles(M, N) + prepare_pieces(M, N, K, b.next_n), 512, 0, st>>>(
+        M, N, K, group, (const h16 *)x, (const h16 *)w, sets.x_hat(b.set), sets.packed(b.set), sets.scales(b.set), sets.zeros(b.set), partials, sets, b);
 }
+
+// ---------------------------------------------------------------- two alphas of a search at once
+//
+// The tile, the waves and the order of every sum are loss_tile_kernel's, so each loss has its bits; but a
+// workgroup accumulates the tile of TWO alphas: X and W, which do not depend on alpha, come from L2 and out of
+// LDS once for both (72 KB per stage instead of 104, eight 16-byte reads per lane for 16 MFMAs instead
+// of six for eight).  A stage's loads then have twice the arithmetic to hide behind, so that two
+// ring slots do where one alpha needs three.  The fragments of a k-step are read where the previous
+// ones have just been used up (X and W while X_hat W_hat is multiplied, X_hat while X W is): 128
+// accumulator registers leave no room for two sets of them.
+// What bounds it: matrix cores and loads, which overlap in part (512 x 5120 x 5120, one pair on 160 compute units:
+// 147 us, twice 88 one by one; 105 without MFMAs, 118 without the direct loads, 142 without W's way or the
+// unpack; bringing lines into L2 three stages ahead made it 160).  Searches, before -> now: 512 x 5120 x 5120, 21
+// alphas 1907 -> 1574 us; 353 x 2304 x 2792, 6 alphas 331 -> 169; 644 x 7808 x 1328, 11 alphas 1451 -> 617;
+// 64 x 4096 x 4096 in groups of 32, 21 alphas 1507 -> 480.
+// A launch holds `pairs` such pairs, as many as fill the chip, and behind them one workgroup per piece of the
+// next alphas' preparation (a tile of the weight smoothed and quantised, a piece of x divided), which takes what
+// compute units the loss leaves idle and evens out its end.
+template <int G>
+__global__ void __launch_bounds__(512)
+search_prepare_kernel(int T, int N, int K, const h16 *__restrict__ x, const h16 *__restrict__ w, SearchSets sets, SearchBatch batch)
+{
+    __shared__ __attribute__((aligned(16))) unsigned char lds[sizeof(QuantizeTile<G, 512>)];
+    prepare_piece<G>(blockIdx.x, T, N, K, x, w, sets, batch.next_set, batch.next_n, batch.next_factors, lds);
+}
+
+template <int G>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
+loss_pair_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, const h16 *__restrict__ w, SearchSets sets, SearchBatch batch,
+                 double *__restrict__ tile_sums)
+{
+    constexpr bool G32 = G == 32;
+    constexpr int SLOT = 3 * SHALF;            // X, X_hat of the one alpha and of the other
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * SLOT + 2 * SWBUF];
+    __shared__ double red[2][4];
+    static_assert(sizeof(lds) + sizeof(red) <= 160 * 1024, "LDS of a workgroup");
+    const int rows = (M + LBM - 1) / LBM, ctiles = (N + LBN - 1) / LBN, pairs = (batch.n + 1) / 2;
+    const int losses = ctiles * rows * pairs;
+    if ((int)blockIdx.x >= losses) {
+        static_assert(sizeof(QuantizeTile<G, 512>) <= sizeof(lds), "the quantiser's LDS fits the ring");
+        prepare_piece<G>(blockIdx.x - losses, M, N, K, x, w, sets, batch.next_set, batch.next_n, batch.next_factors, lds);
+        return;
+    }
+    // Workgroups go to the eight XCDs in turn: each XCD takes a run of neighbours in the order column, row, pair,
+    // so that the workgroups that read the same W (and X) share it in one L2.
+    const int xcd = (int)blockIdx.x & 7, run = losses >> 3, more = losses & 7;
+    const int at = xcd * run + (xcd < more ? xcd : more) + ((int)blockIdx.x >> 3);
+    const int pair = at % pairs, row_tile = at / pairs % rows, col_tile = at / pairs / rows;
+    const bool both = 2 * pair + 1 < batch.n;   // an odd alpha out is its own partner, and only its first sums count
+    const int sa = batch.set + 2 * pair, sb = sa + (both ? 1 : 0);
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kh = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
+    const int l32 = lane & 31, kb = lane >> 5;
+    const int m0 = row_tile * LBM, n0 = col_tile * LBN;
+    const int stages = K / SBK;
+    const int ncol = n0 + wn * 64 + 2 * l32;                   // this lane's two columns (N is even: both in or out)
+    const bool ncol_ok = ncol < N;
+    const UnpackConsts uc = SQP_UNPACK_CONSTS;
+
+    f32x16 acc[2][2][2];                       // [alpha][row tile][column]
+#pragma unroll
+    for (int i = 0; i < 8; i++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) acc[i >> 2][(i >> 1) & 1][i & 1][r] = 0.f;
+
+    struct Stage {                             // per alpha
+        u32x2 w[2];   // per k-step of 16 of this wave's half: the packed words of the lane's two columns
+        uint32_t sc;  // two fp16 steps
+        uint32_t zr;  // two zero points, one byte each
+    };
+    const int col = ncol_ok ? ncol : 0;
+    const uint32_t voff_p = (uint32_t)(kb * N + col) * 4u, voff_s = (uint32_t)col * 2u, voff_z = (uint32_t)col;
+    const uint32_t voff_w = n0 + 2 * lane < N ? (uint32_t)(n0 + 2 * lane) * 2u : 0u;  // W: this lane's column pair
+    const long nrow = (long)N * 2;            // one row of W in bytes
+    const unsigned char *pa = reinterpret_cast<const unsigned char *>(sets.packed(sa)) + (long)kh * 8 * nrow;  // 32 k: four packed rows
+    const long pdiff = (const unsigned char *)sets.packed(sb) - (const unsigned char *)sets.packed(sa);        // the partner's operands, all of them
+    const unsigned char *xq = reinterpret_cast<const unsigned char *>(x), *ha = reinterpret_cast<const unsigned char *>(sets.x_hat(sa));
+    const unsigned char *sca = reinterpret_cast<const unsigned char *>(sets.scales(sa)), *zra = sets.zeros(sa);
+    const unsigned char *wq = reinterpret_cast<const unsigned char *>(w) + (long)wave * 8 * nrow;     // this wave's 8 rows of a stage
+    const int spg = G32 ? 1 : __builtin_amdgcn_readfirstlane(group / SBK);  // stages per group (G32: two groups per stage)
+    int kin = 0, prow = G32 ? kh : 0;          // position of the stage being issued in its group, its parameter row
+    int ist = 0, wst = 0;                      // stage being issued: of X, X_hat and W_hat; of W
+    uint32_t xoff[2];                          // as in loss_tile_kernel
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+        const int row = (wave + 8 * j) * 8 + (lane >> 3);
+        const int grow = m0 + row < M ? m0 + row : M - 1;
+        xoff[j] = (uint32_t)grow * (uint32_t)K * 2u + (uint32_t)(((lane & 7) ^ ((row >> 1) & 7)) * 16);
+    }
+    constexpr int OX = 7, OW = 8;              // loads per wave and stage: two parts of OX (X, X_hat twice; words, steps, zero points), W
+    auto issue_x_part = [&](Stage (&st)[2], int slot, int j) {
+        if (j == 0) {
+            auto direct = [&](const unsigned char *src, int at) {
+#pragma unroll
+                for (int i = 0; i < 2; i++)
+                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + xoff[i]),
+                                                     (__attribute__((address_space(3))) void *)(lds + slot * SLOT + wave * 1024 + i * 8192 + at), 16, 0, 0);
+            };
+            direct(xq, 0);
+            direct(ha, SHALF);
+            direct(ha + pdiff, 2 * SHALF);
+            return;
+        }
+        {
+            const unsigned char *p1 = pa + 4 * nrow, *q0 = pa + pdiff, *q1 = p1 + pdiff;
+            asm volatile("global_load_dwordx2 %[a0], %[vp], %[p0]\n\t"
+                         "global_load_dwordx2 %[a1], %[vp], %[p1]\n\t"
+                         "global_load_dwordx2 %[b0], %[vp], %[q0]\n\t"
+                         "global_load_dwordx2 %[b1], %[vp], %[q1]"
+                         : [a0] "=&v"(st[0].w[0]), [a1] "=&v"(st[0].w[1]), [b0] "=&v"(st[1].w[0]), [b1] "=&v"(st[1].w[1])
+                         : [vp] "v"(voff_p), [p0] "s"(pa), [p1] "s"(p1), [q0] "s"(q0), [q1] "s"(q1)
+                         : "memory");
+        }
+        const long row = (long)__builtin_amdgcn_readfirstlane(prow) * N;
+        const unsigned char *s0 = sca + row * 2, *z0 = zra + row, *s1 = s0 + pdiff, *z1 = z0 + pdiff;
+        asm volatile("global_load_dword %[a], %[vs], %[s0]\n\t"
+                     "global_load_ushort %[b], %[vz], %[z0]\n\t"
+                     "global_load_dword %[c], %[vs], %[s1]\n\t"
+                     "global_load_ushort %[d], %[vz], %[z1]"
+                     : [a] "=&v"(st[0].sc), [b] "=&v"(st[0].zr), [c] "=&v"(st[1].sc), [d] "=&v"(st[1].zr)
+                     : [vs] "v"(voff_s), [vz] "v"(voff_z), [s0] "s"(s0), [z0] "s"(z0), [s1] "s"(s1), [z1] "s"(z1)
+                     : "memory");
+        const bool more = ist + 1 < stages;    // past the last stage the pointers stop and the look-ahead re-reads it
+        ist += more ? 1 : 0;
+        pa += more ? 16 * nrow : 0;
+        xq += more ? SBK * 2 : 0;
+        ha += more ? SBK * 2 : 0;
+        if constexpr (G32) {
+            prow += more ? 2 : 0;
+        } else {
+            kin += more ? 1 : 0;
+            const bool wrap = kin == spg;
+            kin = wrap ? 0 : kin;
+            prow += wrap ? 1 : 0;
+        }
+    };
+    auto issue_w_part = [&](uint32_t (&r)[8], int h) {
+        const unsigned char *b[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) b[i] = wq + (4 * h + i) * nrow;  // wave-uniform
+        asm volatile("global_load_dword %[r0], %[v], %[b0]\n\t"
+                     "global_load_dword %[r1], %[v], %[b1]\n\t"
+                     "global_load_dword %[r2], %[v], %[b2]\n\t"
+                     "global_load_dword %[r3], %[v], %[b3]"
+                     : [r0] "=&v"(r[4 * h]), [r1] "=&v"(r[4 * h + 1]), [r2] "=&v"(r[4 * h + 2]), [r3] "=&v"(r[4 * h + 3])
+                     : [v] "v"(voff_w), [b0] "s"(b[0]), [b1] "s"(b[1]), [b2] "s"(b[2]), [b3] "s"(b[3])
+                     : "memory");
+        if (h == 0) return;
+        const bool more = wst + 1 < stages;
+        wst += more ? 1 : 0;
+        wq += more ? (long)SBK * nrow : 0;
+    };
+    auto tie_w = [&](uint32_t (&r)[8]) {       // no use ahead of the wait in front
+#pragma unroll
+        for (int i = 0; i < 8; i++) asm volatile("" : "+v"(r[i]));
+    };
+    const uint32_t wwr = (uint32_t)(size_t)lds + (uint32_t)(2 * SLOT + ((lane >> 5) * 64 + l32) * SROW + wave * 16);
+    auto store_w = [&](const uint32_t (&r)[8], int buf) {
+        u32x4 c0, c1;  // the low halves of the 8 rows; the high halves
+        c0.x = __builtin_amdgcn_perm(r[1], r[0], 0x05040100u); c1.x = __builtin_amdgcn_perm(r[1], r[0], 0x07060302u);
+        c0.y = __builtin_amdgcn_perm(r[3], r[2], 0x05040100u); c1.y = __builtin_amdgcn_perm(r[3], r[2], 0x07060302u);
+        c0.z = __builtin_amdgcn_perm(r[5], r[4], 0x05040100u); c1.z = __builtin_amdgcn_perm(r[5], r[4], 0x07060302u);
+        c0.w = __builtin_amdgcn_perm(r[7], r[6], 0x05040100u); c1.w = __builtin_amdgcn_perm(r[7], r[6], 0x07060302u);
+        const uint32_t a = wwr + (uint32_t)(buf * SWBUF);
+        asm volatile("ds_write_b128 %0, %1" ::"v"(a), "v"(c0) : "memory");
+        asm volatile("ds_write_b128 %0, %1 offset:%2" ::"v"(a), "v"(c1), "n"(32 * SROW) : "memory");
+    };
+    const uint32_t xrd = (uint32_t)(size_t)lds + (uint32_t)((wm * 64 + l32) * 128);
+    const int xkey = (l32 >> 1) & 7;
+    const uint32_t wrd = (uint32_t)(size_t)lds + (uint32_t)(2 * SLOT + (wn * 64 + l32) * SROW + kh * 64 + kb * 16);
+
+    u32x4 xa[2], wb[2], xb[2][2];              // fragments of X, W and X_hat (per alpha) of one k-step: [row or column tile]
+    auto read_xw = [&](int slot, int ks) {
+        const uint32_t a = xrd + (uint32_t)(slot * SLOT) + (uint32_t)(((kh * 4 + ks * 2 + kb) ^ xkey) * 16);
+        const uint32_t b = wrd + (uint32_t)(slot * SWBUF + ks * 32);
+        asm volatile("ds_read_b128 %0, %1" : "=&v"(xa[0]) : "v"(a) : "memory");
+        asm volatile("ds_read_b128 %0, %1 offset:4096" : "=&v"(xa[1]) : "v"(a) : "memory");
+        asm volatile("ds_read_b128 %0, %1" : "=&v"(wb[0]) : "v"(b) : "memory");
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(wb[1]) : "v"(b), "n"(32 * SROW) : "memory");
+    };
+    auto read_xh = [&](int slot, int ks) {
+        const uint32_t a = xrd + (uint32_t)(slot * SLOT) + (uint32_t)(((kh * 4 + ks * 2 + kb) ^ xkey) * 16);
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(xb[0][0]) : "v"(a), "n"(SHALF) : "memory");
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(xb[0][1]) : "v"(a), "n"(SHALF + 4096) : "memory");
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(xb[1][0]) : "v"(a), "n"(2 * SHALF) : "memory");
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(xb[1][1]) : "v"(a), "n"(2 * SHALF + 4096) : "memory");
+    };
+    auto tie_xw = [&]() {                      // no use ahead of the wait in front
+#pragma unroll
+        for (int i = 0; i < 2; i++) {
+            asm volatile("" : "+v"(xa[i]));
+            asm volatile("" : "+v"(wb[i]));
+        }
+    };
+    auto tie_xh = [&]() {
+#pragma unroll
+        for (int a = 0; a < 2; a++)
+#pragma unroll
+            for (int i = 0; i < 2; i++) asm volatile("" : "+v"(xb[a][i]));
+    };
+    auto tie_stage = [&](Stage (&cur)[2]) {
+#pragma unroll
+        for (int a = 0; a < 2; a++) {
+#pragma unroll
+            for (int ks = 0; ks < 2; ks++) asm volatile("" : "+v"(cur[a].w[ks]));
+            asm volatile("" : "+v"(cur[a].sc));
+            asm volatile("" : "+v"(cur[a].zr));
+        }
+    };
+    // Stage s (slot, LDS buffer of W and registers by its parity).  On entry its X, X_hat, W and words have landed
+    // for all waves, the first fragments are on their way, and no wave reads the other slot and buffer
+    // any more, which are filled meanwhile: with the loads of stage s + 1 and, once it has landed, W of that
+    // stage; W of stage s + 2 follows into the registers that held W of stage s.  The hand-over to stage
+    // s + 1 (wait for its loads, barrier) sits between the last MFMAs of the two alphas, when all fragments
+    // have been read: the barrier's wait and the next fragments' way hide behind those MFMAs.
+    auto iteration = [&](Stage (&cur)[2], Stage (&fill)[2], uint32_t (&w_next)[8], uint32_t (&w_fill)[8], int slot) {
+        h16x2 neg_hi[2][2], neg_lo[2][2], delta[2][2];
+#pragma unroll
+        for (int a = 0; a < 2; a++)
+#pragma unroll
+            for (int t = 0; t < 2; t++) {
+                const uint32_t z = (cur[a].zr >> (8 * t)) & 0xffu;
+                neg_hi[a][t] = neg_hi_of(z);
+                neg_lo[a][t] = neg_lo_of(z);
+                const uint32_t sw = cur[a].sc ^ 0x80008000u;  // the negated steps
+                delta[a][t] = __builtin_bit_cast(h16x2, __builtin_amdgcn_perm(sw, sw, t ? 0x03020302u : 0x01000100u));
+            }
+#pragma unroll
+        for (int ks = 0; ks < 2; ks++) {
+            asm volatile("s_waitcnt lgkmcnt(4)" ::: "memory");  // X and W (the reads of X_hat are younger)
+            tie_xw();
+            if (ks == 0) {
+                issue_x_part(fill, slot ^ 1, 0);
+            } else {
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * OX) : "memory");  // W of the next stage, issued in the last iteration
+                tie_w(w_next);
+                store_w(w_next, slot ^ 1);
+                issue_w_part(w_fill, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            // X W of 16 k for both alphas, the words of the first unpacked between the MFMAs (the scheduler is told so)
+            h16x8 b[2];
+#pragma unroll
+            for (int t = 0; t < 2; t++) b[t] = dequant_word_scaled(cur[0].w[ks][t], neg_hi[0][t], neg_lo[0][t], delta[0][t], uc);
+#pragma unroll
+            for (int a = 0; a < 2; a++)
+#pragma unroll
+                for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+                    for (int t = 0; t < 2; t++)
+                        acc[a][mt][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h16x8, xa[mt]), __builtin_bit_cast(h16x8, wb[t]),
+                                                                               acc[a][mt][t], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 8; i++) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // 1 MFMA
+                __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);  // VALU
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (ks == 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            else asm volatile("s_waitcnt lgkmcnt(2)" ::: "memory");  // (the two writes of W are younger)
+            tie_xh();
+            if (ks == 0) {
+                read_xw(slot, 1);
+                issue_x_part(fill, slot ^ 1, 1);
+            } else {
+                issue_w_part(w_fill, 1);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            // X_hat W_hat of the same 16 k, the words of the second alpha unpacked between the MFMAs of the first
+            h16x8 c[2];
+#pragma unroll
+            for (int t = 0; t < 2; t++) c[t] = dequant_word_scaled(cur[1].w[ks][t], neg_hi[1][t], neg_lo[1][t], delta[1][t], uc);
+#pragma unroll
+            for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+                for (int t = 0; t < 2; t++)
+                    acc[0][mt][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h16x8, xb[0][mt]), b[t], acc[0][mt][t], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (ks == 1) {
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(OW) : "memory");  // all of stage s + 1 (W of the one behind it is younger)
+                tie_stage(fill);
+                asm volatile("s_barrier" ::: "memory");
+                read_xw(slot ^ 1, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+                for (int t = 0; t < 2; t++)
+                    acc[1][mt][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h16x8, xb[1][mt]), c[t], acc[1][mt][t], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (ks == 0) read_xh(slot, 1);
+            else read_xh(slot ^ 1, 0);
+        }
+    };
+    Stage st[2][2];                            // [parity of the stage][alpha]
+    uint32_t wr[2][8];                         // W of a stage of that parity
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // nothing of the compiler's own is counted below
+    issue_w_part(wr[0], 0);
+    issue_w_part(wr[0], 1);
+    issue_x_part(st[0], 0, 0);
+    issue_x_part(st[0], 0, 1);
+    issue_w_part(wr[1], 0);
+    issue_w_part(wr[1], 1);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * OX + OW) : "memory");
+    tie_w(wr[0]);
+    store_w(wr[0], 0);
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(OW) : "memory");
+    tie_stage(st[0]);
+    asm volatile("s_barrier" ::: "memory");
+    read_xw(0, 0);
+    read_xh(0, 0);
+    for (int s = 0;;) {
+        iteration(st[0], st[1], wr[1], wr[0], 0);
+        if (++s == stages) break;
+        iteration(st[1], st[0], wr[0], wr[1], 1);
+        if (++s == stages) break;
+    }
+    // the look-ahead loads still in flight land in registers and slots that nothing else may use before
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+#pragma unroll
+        for (int a = 0; a < 2; a++) {
+            asm volatile("" ::"v"(st[j][a].w[0]), "v"(st[j][a].w[1]));
+            asm volatile("" ::"v"(st[j][a].sc), "v"(st[j][a].zr));
+        }
+#pragma unroll
+        for (int i = 0; i < 8; i++) asm volatile("" ::"v"(wr[j][i]));
+        asm volatile("" ::"v"(xa[j]), "v"(wb[j]), "v"(xb[j][0]), "v"(xb[j][1]));
+    }
+
+    // the second half's waves (kh == 1) hand their sums to the first's, then the squares of the tile: as in loss_tile_kernel
+    static_assert(4 * 64 * 64 * 4 <= 2 * SLOT, "the exchange reuses the ring");
+#pragma unroll
+    for (int al = 0; al < 2; al++) {
+        f32x4 *ex = reinterpret_cast<f32x4 *>(lds) + (size_t)(wave & 3) * 16 * 64 + lane;
+        __syncthreads();
+        if (kh == 1) {
+#pragma unroll
+            for (int q = 0; q < 16; q++) {
+                const f32x16 &a = acc[al][q >> 3][(q >> 2) & 1];
+                ex[q * 64] = f32x4{a[(q & 3) * 4], a[(q & 3) * 4 + 1], a[(q & 3) * 4 + 2], a[(q & 3) * 4 + 3]};
+            }
+        }
+        __syncthreads();
+        if (kh == 0) {
+            double ss = 0.0;
+#pragma unroll
+            for (int q = 0; q < 16; q++) {
+                const f32x4 v = ex[q * 64];
+#pragma unroll
+                for (int r = 0; r < 4; r++) acc[al][q >> 3][(q >> 2) & 1][(q & 3) * 4 + r] += v[r];
+            }
+#pragma unroll
+            for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+                for (int t = 0; t < 2; t++)
+#pragma unroll
+                    for (int r = 0; r < 16; r++) {
+                        const int row = m0 + wm * 64 + mt * 32 + 8 * (r >> 2) + 4 * kb + (r & 3);
+                        if (row < M && ncol_ok) ss += (double)acc[al][mt][t][r] * (double)acc[al][mt][t][r];
+                    }
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 64);
+            if (lane == 0) red[al][wave] = ss;
+        }
+    }
+    __syncthreads();
+    if (tid < (both ? 2 : 1))
+        tile_sums[((size_t)2 * pair + tid) * ctiles * rows + (size_t)row_tile * ctiles + col_tile] =
+            (red[tid][0] + red[tid][1]) + (red[tid][2] + red[tid][3]);
+}
+
+// Preparation of batch.next_n alphas; the losses of batch.n alphas beside the preparation of next_n others.
+template <int G>
+void launch_prepare(int T, int N, int K, const void *x, const void *w, const SearchSets &sets, const SearchBatch &b, hipStream_t st)
+{
+    search_prepare_kernel<G><<<prepare_pieces(T, N, K, b.next_n), 512, 0, st>>>(T, N, K, (const h16 *)x, (const h16 *)w, sets, b);
+}
+template <int G>
+void launch_loss_pairs(int T, int N, int K, int group, const void *x, const void *w, const SearchSets &sets, const SearchBatch &b, double *tile_sums,
+                       hipStream_t st)
+{
+    const int grid = loss_tiles(T, N) * ((b.n + 1) / 2) + (b.next_n ? prepare_pieces(T, N, K, b.next_n) : 0);
+    loss_pair_kernel<G><<<grid, 512, 0, st>>>(T, N, K, group, (const h16 *)x, (const h16 *)w, sets, b, tile_sums);
+}
+#define SQP_BY_GROUP(CALL)               \
+    switch (group) {                     \
+        case 32: CALL(32); break;        \
+        case 64: CALL(64); break;        \
+        case 128: CALL(128); break;      \
+        default: CALL(256); break;       \
+    }
 
 // ---------------------------------------------------------------- any K and group
 //
@@ -614,6 +1033,144 @@ extern "C" int sqp_quant_loss(int M, int N, int K, int group, const void *x, con
     return sqp_launch_status();
 }
 
+// ---------------------------------------------------------------- search over alpha
+
+static size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
+
+// How a buffer holds a search: factors [n_alpha][K], tile sums [n_alpha][tiles], then `sets` sets of prepared operands.
+struct SearchRoom {
+    int sets;                                  // 0: not even one set fits
+    size_t at_sums, at_sets;
+    SearchSets layout;                         // base not set
+};
+
+static SearchRoom search_room(int T, int N, int K, int group, int n_alpha, size_t bytes)
+{
+    SearchRoom r = {};
+    if (!loss_tile_covers(K, group)) return r;
+    const size_t rows = (size_t)(K / group), blocks = (size_t)sqp_quant_loss_scratch_doubles(T, N);
+    r.at_sums = up256((size_t)n_alpha * K * sizeof(float));
+    r.at_sets = r.at_sums + up256(n_alpha * blocks * sizeof(double));
+    r.layout.at_scales = up256((size_t)K / 8 * N * 4);
+    r.layout.at_zeros = r.layout.at_scales + up256(rows * N * 2);
+    r.layout.at_x = r.layout.at_zeros + up256(rows * N);
+    r.layout.stride = r.layout.at_x + up256((size_t)T * K * sizeof(h16));
+    if (bytes >= r.at_sets + r.layout.stride) {
+        const size_t n = (bytes - r.at_sets) / r.layout.stride;
+        r.sets = n < 4096 ? (int)n : 4096;
+    }
+    return r;
+}
+
+static size_t search_bytes(int T, int N, int K, int group, int n_alpha, int sets)
+{
+    const SearchRoom r = search_room(T, N, K, group, n_alpha, 0);
+    return r.at_sets + sets * r.layout.stride;
+}
+
+// Alphas per launch: the number of pairs for which an estimate of the whole search is shortest, in units of
+// a loss workgroup's time.  A launch takes at least as many rounds of the chip (one workgroup per compute
+// unit) as its losses need, and at least its work spread evenly: losses and the next batch's preparation
+// (0.45 of the losses' work: 21 us on the whole chip against 147 us on 160 compute units per pair,
+// 512 x 5120 x 5120).  The first batch is prepared alone, a last single alpha takes 0.6.
+// Measured against the estimate, 512 x 5120 x 5120, 21 alphas, 1 to 6 pairs: 1796, 1860, 1749, 1686, 1717,
+// 1793 us (10.9, 11.2, 10.6, 10.0, 10.9, 10.7); 644 x 7808 x 1328, 11 alphas: 1234, 758, 619 (3, taken), 821.
+static int search_batch(int T, int N, int n_alpha)
+{
+    const double tiles = (double)sqp_quant_loss_scratch_doubles(T, N), cus = sqp_compute_units();
+    constexpr double PREPARE = 0.45, SINGLE = 0.6;
+    int best = 1;
+    double shortest = 0;
+    for (int p = 1; p <= (n_alpha + 1) / 2 && p <= 16; p++) {
+        double t = 0;
+        for (int i = 0; i < n_alpha; i += 2 * p) {
+            const int n = n_alpha - i < 2 * p ? n_alpha - i : 2 * p, next = n_alpha - i - n < 2 * p ? n_alpha - i - n : 2 * p;
+            if (i == 0) t += PREPARE * n / 2 * tiles / cus;
+            const double losses = n == 1 ? SINGLE * tiles : (n + 1) / 2 * tiles, even = (losses + PREPARE * next / 2 * tiles) / cus;
+            const double rounds = (n == 1 ? SINGLE : 1.0) * (double)(long)(((n + 1) / 2 * tiles + cus - 1) / cus);
+            t += rounds > even ? rounds : even;
+        }
+        if (p == 1 || t < shortest * 0.999) shortest = t, best = p;
+    }
+    return 2 * best;
+}
+
+static bool prepares_in_tiles(int group) { return group == 32 || group == 64 || group == 128 || group == 256; }
+
+// Two batches of sets, one being used and one being prepared.
+static int search_sets_wanted(int T, int N, int K, int group, int n_alpha)
+{
+    const int batch = search_batch(T, N, n_alpha);
+    const size_t most = ((size_t)1 << 30) / search_room(T, N, K, group, n_alpha, 0).layout.stride;  // 1 GB of them, or two batches of one pair
+    const int want = n_alpha <= batch ? n_alpha : 2 * batch;
+    return (size_t)want <= most ? want : (most > 4 ? (int)most : (want < 4 ? want : 4));
+}
+
+// The losses of all alphas and the argmin, everything in `region` (amax is given).
+static int search_all(int T, int N, int K, int group, int n_alpha, const float *alphas, const void *x_cal, const void *w, const float *amax,
+                      void *region, const SearchRoom &room, double *loss, int *best, hipStream_t st)
+{
+    unsigned char *const base = (unsigned char *)region;
+    const size_t blocks = (size_t)sqp_quant_loss_scratch_doubles(T, N);
+    float *factors = (float *)base;
+    double *tile_sums = (double *)(base + room.at_sums);
+    SearchSets sets = room.layout;
+    sets.base = base + room.at_sets;
+    int rc = sqp_smooth_factors(K, n_alpha, alphas, amax, factors, st);
+    if (rc != SQP_OK) return rc;
+    // Sets for two batches: the next one is prepared beside the losses.  With two or three sets, single losses beside
+    // the next alpha's preparation where the tiles leave room for that (90 us per alpha on 512 x 5120 x 5120),
+    // pairs behind the preparation of both otherwise (95 there, but 113 against 135 with 66 tiles and K = 7808).
+    // One set, or one alpha: the kernel for one.
+    int batch = search_batch(T, N, n_alpha);
+    const bool tiled = prepares_in_tiles(group);
+    bool beside = tiled && batch < n_alpha && room.sets >= 4;
+    if (beside) {
+        batch = 2 * batch <= room.sets ? batch : room.sets / 4 * 2;
+    } else {
+        batch = batch <= room.sets ? batch : room.sets;
+        const long tiles = loss_tiles(T, N), cus = sqp_compute_units();
+        if (tiled && batch < n_alpha && room.sets >= 2 && 16 * tiles > 7 * cus && 16 * tiles <= 13 * cus) batch = 1, beside = true;
+    }
+    auto prepare = [&](int first, int n, int set) {
+        if (tiled) {
+            const SearchBatch b = {0, 0, set, n, factors + (size_t)first * K};
+#define SQP_PREPARE(G) launch_prepare<G>(T, N, K, x_cal, w, sets, b, st)
+            SQP_BY_GROUP(SQP_PREPARE)
+#undef SQP_PREPARE
+            return sqp_launch_status();
+        }
+        int e = SQP_OK;
+        for (int i = 0; i < n && e == SQP_OK; i++)
+            e = sqp_smooth_quantize(T, N, K, group, x_cal, w, factors + (size_t)(first + i) * K, sets.x_hat(set + i), sets.packed(set + i),
+                                    sets.scales(set + i), sets.zeros(set + i), st);
+        return e;
+    };
+    for (int i = 0, half = 0; i < n_alpha && rc == SQP_OK; i += batch, half ^= beside ? 1 : 0) {
+        const int n = n_alpha - i < batch ? n_alpha - i : batch, after = n_alpha - i - n < batch ? n_alpha - i - n : batch;
+        const int set = half * batch;
+        if (!beside || i == 0) rc = prepare(i, n, set);
+        if (rc != SQP_OK) break;
+        if (n == 1 && beside && after > 0) {
+            const SearchBatch b = {set, 1, (half ^ 1) * batch, after, factors + (size_t)(i + n) * K};
+#define SQP_LOSS_NEXT(G) launch_loss_and_next<G>(T, N, K, group, x_cal, w, sets, b, tile_sums + i * blocks, st)
+            SQP_BY_GROUP(SQP_LOSS_NEXT)
+#undef SQP_LOSS_NEXT
+        } else if (n == 1) {
+            launch_loss_tile<true>(T, N, K, group, x_cal, w, sets.x_hat(set), sets.packed(set), sets.scales(set), sets.zeros(set), tile_sums + i * blocks, st);
+        } else {
+            const SearchBatch b = {set, n, beside ? (half ^ 1) * batch : 0, beside ? after : 0, factors + (size_t)(i + n) * K};
+#define SQP_PAIRS(G) launch_loss_pairs<G>(T, N, K, group, x_cal, w, sets, b, tile_sums + i * blocks, st)
+            SQP_BY_GROUP(SQP_PAIRS)
+#undef SQP_PAIRS
+        }
+    }
+    if (rc != SQP_OK) return rc;
+    sum_partials_kernel<<<n_alpha, 256, 0, st>>>(tile_sums, (long)blocks, loss);
+    argmin_kernel<<<1, 64, 0, st>>>(loss, n_alpha, best);
+    return sqp_launch_status();
+}
+
 extern "C" int sqp_alpha_search(int T, int N, int K, int group, int n_alpha, const float *alphas, const void *x_cal,
                                 const void *w, float *amax, float *s, void *x_hat, void *w_s, uint32_t *packed,
                                 void *scales, uint8_t *zeros, double *scratch, double *loss, int *best, void *stream)
@@ -636,54 +1193,18 @@ extern "C" int sqp_alpha_search(int T, int N, int K, int group, int n_alpha, con
     // every check any step below would make has passed: from here on only launch errors can occur
     hipStream_t st = (hipStream_t)stream;
     rc = sqp_channel_absmax(T, K, N, x_cal, w, amax, st);
-    // The factors of all alphas and the tile sums live in w_s, which the search otherwise fills with
-    // the smoothed weight: here the quantisation smooths the weight as it reads it, and w_s gets the
-    // last alpha's smoothed weight at the end.  Taken wherever they fit there (N from about twice the
-    // number of alphas on); narrower layers run the single calls in turn.
-    const size_t blocks = (size_t)((T + LBM - 1) / LBM) * ((N + LBN - 1) / LBN);
-    const size_t fbytes = (size_t)n_alpha * K * sizeof(float);
-    if (loss_tile_covers(K, group) && fbytes + n_alpha * blocks * sizeof(double) <= (size_t)K * N * sizeof(h16)) {
-        float *factors = (float *)w_s;
-        double *tile_sums = (double *)((unsigned char *)w_s + fbytes);
-        if (rc == SQP_OK) rc = sqp_smooth_factors(K, n_alpha, alphas, amax, factors, st);
+    if (rc != SQP_OK) return rc;
+    // The factors, the tile sums and the prepared operands live in w_s, which the search otherwise fills with
+    // the smoothed weight: here the quantisation smooths the weight as it reads it, and the last alpha's values
+    // are put into the caller's buffers at the end.  Shapes that do not fit there run the single calls in turn.
+    const SearchRoom room = search_room(T, N, K, group, n_alpha, (size_t)K * N * sizeof(h16));
+    if (room.sets > 0) {
+        rc = search_all(T, N, K, group, n_alpha, alphas, x_cal, w, amax, w_s, room, loss, best, st);
         if (rc == SQP_OK) rc = sqp_smooth_factor(K, alphas[n_alpha - 1], amax, s, st);
-        if (rc != SQP_OK) return rc;
-        // Where the loss tiles leave at least a quarter of the chip idle (160 of 256 on 512 x 5120), the next
-        // alpha is prepared there meanwhile, into a second set of buffers behind the tile sums; the last
-        // alpha uses the caller's set.  Per alpha on 512 x 5120 x 5120: 108 us one after the other, 88 beside.
-        const int idle = sqp_compute_units() - (int)(blocks < 65536 ? blocks : 65536);
-        auto up256 = [](size_t v) { return (v + 255) & ~(size_t)255; };
-        const size_t rows = (size_t)(K / group);
-        const size_t at_packed = up256(fbytes + n_alpha * blocks * sizeof(double));
-        const size_t at_scales = up256(at_packed + (size_t)K / 8 * N * 4), at_zeros = up256(at_scales + rows * N * 2);
-        const size_t at_x = up256(at_zeros + rows * N), end = at_x + (size_t)T * K * sizeof(h16);
-        const bool beside = 4 * idle >= sqp_compute_units() && (group == 32 || group == 64 || group == 128 || group == 256) &&
-                            end <= (size_t)K * N * sizeof(h16);
-        unsigned char *const base = (unsigned char *)w_s;
-        struct {
-            void *x_hat;
-            uint32_t *packed;
-            void *scales;
-            uint8_t *zeros;
-        } set[2] = {{x_hat, packed, scales, zeros}, {base + at_x, (uint32_t *)(base + at_packed), base + at_scales, base + at_zeros}};
-        for (int i = 0; i < n_alpha && rc == SQP_OK; i++) {
-            const auto &cur = set[beside ? (n_alpha - 1 - i) & 1 : 0], &nxt = set[beside ? (n_alpha - i) & 1 : 0];
-            if (!beside || i == 0)
-                rc = sqp_smooth_quantize(T, N, K, group, x_cal, w, factors + (size_t)i * K, cur.x_hat, cur.packed, cur.scales, cur.zeros, st);
-            if (beside && i + 1 < n_alpha) {
-                const NextAlpha next = {factors + (size_t)(i + 1) * K, (const uint4 *)x_cal, (const uint4 *)w, (uint4 *)nxt.x_hat,
-                                        nxt.packed, (uint16_t *)nxt.scales, nxt.zeros, 0, idle};
-                launch_loss_and_next(T, N, K, group, x_cal, w, cur.x_hat, cur.packed, cur.scales, cur.zeros, tile_sums + i * blocks, next, st);
-            } else {
-                launch_loss_tile<true>(T, N, K, group, x_cal, w, cur.x_hat, cur.packed, cur.scales, cur.zeros, tile_sums + i * blocks, st);
-            }
-        }
-        sum_partials_kernel<<<n_alpha, 256, 0, st>>>(tile_sums, (long)blocks, loss);
-        argmin_kernel<<<1, 64, 0, st>>>(loss, n_alpha, best);
-        // x_hat and w_s as the single calls leave them
-        if (rc == SQP_OK) rc = sqp_smooth_apply_x(T, K, x_cal, s, x_hat, stream);
+        if (rc == SQP_OK) rc = sqp_smooth_quantize(T, N, K, group, x_cal, w, s, x_hat, packed, scales, zeros, st);
+        if (rc == SQP_OK) rc = sqp_smooth_apply_x(T, K, x_cal, s, x_hat, stream);  // (not in code order)
         if (rc == SQP_OK) rc = sqp_smooth_apply_w(K, N, w, s, w_s, stream);
-        return rc != SQP_OK ? rc : sqp_launch_status();
+        return rc;
     }
     for (int i = 0; i < n_alpha && rc == SQP_OK; i++) {
         rc = sqp_smooth_factor(K, alphas[i], amax, s, st);
@@ -695,4 +1216,62 @@ extern "C" int sqp_alpha_search(int T, int N, int K, int group, int n_alpha, con
     if (rc != SQP_OK) return rc;
     argmin_kernel<<<1, 64, 0, st>>>(loss, n_alpha, best);
     return sqp_launch_status();
+}
+
+// The buffers of a search in one scratch buffer: what the single calls need, or what the fused search wants.
+static size_t single_calls_bytes(int T, int N, int K, int group)
+{
+    return up256((size_t)2 * K * 4) + up256((size_t)K * 4) + up256((size_t)T * K * 2) + up256((size_t)K * N * 2) + up256((size_t)K / 8 * N * 4) +
+           up256((size_t)(K / group) * N * 2) + up256((size_t)(K / group) * N) + up256((size_t)sqp_quant_loss_scratch_doubles(T, N) * 8);
+}
+
+static int check_search(int T, int N, int K, int group, int n_alpha)
+{
+    if (T <= 0 || n_alpha <= 0 || n_alpha > 4096) return SQP_ERR_SHAPE;
+    const int rc = sqp_check_quant_shape(N, K, group);
+    if (rc) return rc;
+    if (sqp_too_big(T, K) || sqp_too_big(T, N)) return SQP_ERR_SHAPE;
+    if ((T + LBM - 1) / LBM > 65535 || K / group > 65535) return SQP_ERR_SHAPE;
+    return SQP_OK;
+}
+
+extern "C" size_t sqp_alpha_search_scratch_bytes(int T, int N, int K, int group, int n_alpha)
+{
+    if (check_search(T, N, K, group, n_alpha) != SQP_OK) return 0;
+    if (!loss_tile_covers(K, group)) return single_calls_bytes(T, N, K, group);
+    const size_t head = up256((size_t)2 * K * sizeof(float));
+    return head + search_bytes(T, N, K, group, n_alpha, search_sets_wanted(T, N, K, group, n_alpha));
+}
+
+extern "C" int sqp_alpha_search_scratch(int T, int N, int K, int group, int n_alpha, const float *alphas, const void *x_cal, const void *w,
+                                        void *scratch, size_t scratch_bytes, double *loss, int *best, void *stream)
+{
+    if (!alphas || !x_cal || !w || !scratch || !loss || !best) return SQP_ERR_NULL;
+    const int rc = check_search(T, N, K, group, n_alpha);
+    if (rc) return rc;
+    for (int i = 0; i < n_alpha; i++)
+        if (!(alphas[i] >= 0.0f && alphas[i] <= 1.0f)) return SQP_ERR_ARG;
+    if (sqp_misaligned(x_cal) || sqp_misaligned(w) || sqp_misaligned(scratch)) return SQP_ERR_ALIGN;
+    if ((reinterpret_cast<uintptr_t>(loss) & 7u) || (reinterpret_cast<uintptr_t>(best) & 3u)) return SQP_ERR_ALIGN;
+    unsigned char *const base = (unsigned char *)scratch;
+    const size_t head = up256((size_t)2 * K * sizeof(float));
+    if (loss_tile_covers(K, group)) {
+        const SearchRoom room = search_room(T, N, K, group, n_alpha, scratch_bytes < head ? 0 : scratch_bytes - head);
+        if (room.sets == 0) return SQP_ERR_WORKSPACE;
+        const int e = sqp_channel_absmax(T, K, N, x_cal, w, (float *)base, (hipStream_t)stream);
+        return e != SQP_OK ? e : search_all(T, N, K, group, n_alpha, alphas, x_cal, w, (float *)base, base + head, room, loss, best, (hipStream_t)stream);
+    }
+    if (scratch_bytes < single_calls_bytes(T, N, K, group)) return SQP_ERR_WORKSPACE;
+    size_t at = 0;
+    auto take = [&](size_t bytes) {
+        void *p = base + at;
+        at += up256(bytes);
+        return p;
+    };
+    float *amax = (float *)take((size_t)2 * K * 4), *s = (float *)take((size_t)K * 4);
+    void *x_hat = take((size_t)T * K * 2), *w_s = take((size_t)K * N * 2), *packed = take((size_t)K / 8 * N * 4);
+    void *scales = take((size_t)(K / group) * N * 2), *zeros = take((size_t)(K / group) * N);
+    void *sums = take((size_t)sqp_quant_loss_scratch_doubles(T, N) * 8);
+    return sqp_alpha_search(T, N, K, group, n_alpha, alphas, x_cal, w, amax, s, x_hat, w_s, (uint32_t *)packed, scales, (uint8_t *)zeros,
+                            (double *)sums, loss, best, stream);
 }

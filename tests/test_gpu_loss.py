@@ -185,3 +185,45 @@ def test_alpha_search_routes_equal_single_calls(sqp, T, K, N, group, n):
     assert list(host(loss)) == singles and int(host(best)[0]) == int(np.argmin(singles))
     for got, want in ((s, s1), (xh, xh1), (ws, ws1), (p, q1[0]), (sc, q1[1]), (z, q1[2])):
         assert torch.equal(got.view(torch.uint8), want.view(torch.uint8))
+
+
+@pytest.mark.parametrize("T,K,N,group,n,sets", [
+    (512, 640, 2056, 128, 5, 0), (130, 384, 136, 32, 7, 0), (129, 1408, 200, 64, 4, 0), (64, 1024, 256, 256, 1, 0),  # the preferred size
+    (1, 768, 136, 384, 5, 0), (70, 240, 72, 40, 3, 0),  # a group that no tile quantiser covers; K not a multiple of 64
+    (129, 1408, 200, 64, 5, 1), (129, 1408, 200, 64, 5, 2), (40, 640, 2056, 128, 5, 3),  # one set; two and three: pairs in turn
+    (513, 128, 4000, 64, 4, 2), (513, 128, 4000, 32, 3, 3),  # 160 tiles: one alpha at a time beside the next one's preparation
+    (129, 1408, 200, 64, 9, 5), (33, 2304, 520, 128, 6, 4)])  # two batches of pairs, room for more than one batch
+def test_alpha_search_scratch_routes(sqp, T, K, N, group, n, sets):
+    """The search in one scratch buffer: every route (by how many alphas' operands the buffer holds; 0: the
+    preferred size) gives the losses of the single calls bit for bit and stays inside the buffer; a buffer
+    for less than one alpha is refused with nothing written."""
+    import ctypes
+    print("case search scratch", T, K, N, group, n, sets, flush=True)
+    _, _, w = wl.layer_inputs(1, K, N)
+    dx, dw = dev(wl.activation(T, K, seed=3000)), dev(w)
+    alphas = [0.5, 0.0, 0.35, 0.9, 0.35, 1.0, 0.2, 0.6, 0.75][:n]
+    L = sqp.lib()
+    up = lambda v: (v + 255) // 256 * 256
+    tiles = L.sqp_quant_loss_scratch_doubles(T, N)
+    head = up(8 * K) + up(4 * n * K) + up(8 * n * tiles)
+    one = up(K // 8 * N * 4) + up(K // group * N * 2) + up(K // group * N) + up(2 * T * K)
+    want = int(L.sqp_alpha_search_scratch_bytes(T, N, K, group, n))
+    nbytes = head + sets * one if sets else want
+    assert nbytes <= want or sets
+    buf = torch.full((nbytes + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    loss, best = torch.full((n,), -1.0, dtype=torch.float64, device="cuda"), torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    ptr = lambda t: ctypes.c_void_p(t.data_ptr())
+    run = lambda size: L.sqp_alpha_search_scratch(T, N, K, group, n, (ctypes.c_float * n)(*alphas), ptr(dx), ptr(dw), ptr(buf), size, ptr(loss), ptr(best),
+                                                  ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    if group % 32 == 0:
+        assert run(head + one - 1) == -6
+    torch.cuda.synchronize()
+    assert (loss == -1).all() and (buf == 0xA5).all()
+    assert run(nbytes) == 0
+    singles = []
+    for a in alphas:
+        s1 = sqp.smooth_scales(dx, dw, a)
+        q1 = sqp.quantize_pack(sqp.smooth_apply_w(dw, s1), group)
+        singles.append(float(host(sqp.quant_loss(dx, dw, sqp.smooth_apply_x(dx, s1), *q1, group))[0]))
+    assert list(host(loss)) == singles and int(host(best)[0]) == int(np.argmin(singles))
+    assert (buf[nbytes:] == 0xA5).all()
