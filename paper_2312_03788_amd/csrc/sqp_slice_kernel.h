@@ -308,14 +308,12 @@ w4a16_decode_slice_kernel(int M, int N, int K, int cpg, int grouped, const h16 *
                 }
 #pragma unroll
                 for (int b = 0; b < TB; b++) {
-                    const float z = (float)zero_of(s, q, b), d = step_of(s, q, b);
+                    const float d = step_of(s, q, b), dl = d * 16777216.0f, dh = d * 1048576.0f, dz = -d * (float)zero_of(s, q, b);  // 2^24, 2^20
 #pragma unroll
                     for (int mt = 0; mt < MT; mt++) {
 #pragma unroll
-                        for (int r = 0; r < RR; r++) {
-                            const float v = fmaf(hi[mt][b][r * RS], 1.0f / 16, lo[mt][b][r * RS]);  // in units of 2^-24
-                            acc[mt][b][r] = fmaf(d, fmaf(v, 16777216.0f, -z * sx[mt][r * RS]), acc[mt][b][r]);
-                        }
+                        for (int r = 0; r < RR; r++)
+                            acc[mt][b][r] = fmaf(dz, sx[mt][r * RS], fmaf(dh, hi[mt][b][r * RS], fmaf(dl, lo[mt][b][r * RS], acc[mt][b][r])));
                         asm volatile("" : "+v"(acc[mt][b][0]) : "v"(lo[mt][b]), "v"(hi[mt][b]), "v"(sx[mt]));
                     }
                 }
