@@ -48,6 +48,12 @@ void sqp_debug_set_prefill_variant(int rt, int nt, int parts);  /* one launch of
  * launch, half-width tiles of the second, K parts.  Host arithmetic only. */
 void sqp_debug_prefill_plan(int M, int N, int K, int cus, long *full, long *half, int *ksplit);
 
+void sqp_debug_set_row_blocks(int mt, int split, int kp);  /* more than 64 rows (K % 128 == 0): the strip kernel in row blocks of
+                                                      16 mt rows (3, 4), K parts, chunks per iteration; 0 = automatic, -1 = never */
+/* What a call takes of these: rows / 16 (0: the tiled kernel), K parts, chunks per iteration; with a workspace of
+ * the reported size or without.  Host arithmetic only. */
+void sqp_debug_row_blocks(int M, int N, int K, int group, int cus, int workspace, int *out3);
+
 /* What a call launches: returns the number of launches (1 or 2) and their (rt, nt, tiles, K parts) in
  * out8.  The plan above, or one round of tiles of another height where that is faster, and with K
  * parts for few left-over tiles; workspace and scratch as large as it likes.  Host arithmetic only. */

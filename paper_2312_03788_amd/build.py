@@ -15,7 +15,7 @@ LIB = os.path.join(HERE, "libsqp.so")
 TORCH_LIB = os.path.join(HERE, "_sqp_torch.so")
 
 SOURCES = ["sqp_api.hip", "sqp_companion.hip", "sqp_gemm_decode.hip", "sqp_gemm_prefill.hip", "sqp_loss.hip", "sqp_mlp.hip", "sqp_static.hip",
-           "sqp_strip_g128_rows32.hip", "sqp_strip_g128_rows64.hip", "sqp_strip_g64.hip", "sqp_strip_g32.hip", "sqp_strip_one_group.hip",
+           "sqp_strip_g128_rows32.hip", "sqp_strip_g128_rows64.hip", "sqp_strip_g64.hip", "sqp_strip_g32.hip", "sqp_strip_one_group.hip", "sqp_strip_row_blocks.hip",
            "sqp_slice_g128.hip", "sqp_slice_g256.hip", "sqp_slice_g64.hip", "sqp_slice_g32.hip"]
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-I" + os.path.join(ROOT, "include"),

@@ -56,10 +56,10 @@ bool sqp_strip_two_chunks(int chunks, int split)
 
 // The split a launch really runs with (at most one part per chunk; none when the layer has
 // more tiles than the workspace has tickets: such a layer fills the chip anyway) and the
-// bytes of fp32 partial tiles it then leaves in the workspace.
-int sqp_strip_split(int mt, int nw, int kspg, int N, int K, int split, size_t *partial_bytes)
+// bytes of fp32 partial tiles it then leaves in the workspace.  blocks: row blocks of 16 mt rows.
+int sqp_strip_split(int mt, int nw, int kspg, int blocks, int N, int K, int split, size_t *partial_bytes)
 {
-    const int tiles = (N + 64 * nw - 1) / (64 * nw);
+    const int tiles = (N + 64 * nw - 1) / (64 * nw) * blocks;
     const int chunks = K / (32 * kspg);
     if (split > chunks) split = chunks;
     if (split < 1) split = 1;
@@ -285,7 +285,7 @@ static size_t plan_bytes(const Plan &p, int N, int K, int group, int kspg, int m
     int nw = p.nw;
     if (nw != 2 && !(nw == 1 && one_group) && !(nw == 8 && one_group && mt < 3)) nw = 4;
     size_t bytes = 0;
-    sqp_strip_split(mt, nw, kspg, N, K, p.split, &bytes);
+    sqp_strip_split(mt, nw, kspg, 1, N, K, p.split, &bytes);
     return bytes;
 }
 

@@ -28,6 +28,7 @@
 #include <type_traits>
 
 #include "sqp_common.h"
+#include "sqp_strip.h"
 #include "sqp_w4_unpack.h"
 
 namespace {
@@ -588,6 +589,9 @@ extern "C" void sqp_debug_prefill_plan(int M, int N, int K, int cus, long *full,
     *ksplit = p.ksplit;
 }
 
+// Estimated time of a 64-row stage of K for tiles of 32 rt rows x 256 columns.
+static const double stage_us[7] = {0, 0, 0, 0.72, 0.77, 0.97, 1.11};
+
 // What a call launches: up to two launches of tiles of 32 rt rows x 32 nt columns per wave, each over
 // `tiles` tiles from tile0 of a grid with tn tiles per row, in `parts` K parts (1: straight to y).
 struct TileLaunch {
@@ -662,7 +666,6 @@ static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, size_t 
             q.count = 1;
             q.l[0] = TileLaunch{4, 4, 0, tiles44, (N + 511) / 512, 1};
         }
-        const double stage_us[7] = {0, 0, 0, 0.72, 0.77, 0.97, 1.11};
         const int tn = (N + 255) / 256;
         for (int rt = 3; rt <= 6; rt++) {
             const long tiles = (long)tn * ((M + 32 * rt - 1) / (32 * rt));
@@ -730,11 +733,117 @@ static size_t plan_partial_bytes(const LaunchPlan &q)
     return need;
 }
 
+// Estimated time (us) of the launches of a plan, without what all launches share: see plan_launches.
+static double launches_us(const LaunchPlan &q, int K, int group, int cus)
+{
+    double t = 0;
+    for (int i = 0; i < q.count; i++) {
+        const TileLaunch &l = q.l[i];
+        const long rounds = (l.tiles * l.parts + cus - 1) / cus;
+        t += rounds * ((K / BK + l.parts - 1) / l.parts) * (l.nt == 4 ? 1.43 : stage_us[l.rt]);
+        if (l.parts > 1) t += 2.0 * launch_partial_bytes(l, q.wm) / 5.6e6 + 1.8;
+    }
+    return t + (group == 32 ? 2.0 : 0.0);
+}
+
+// Test hook: row blocks of 16 mt rows with this K split and kp chunks per iteration (0: automatic, -1: never).
+static SqpStripPlan g_row_blocks = {0, 0, 0, 0, 0};
+extern "C" void sqp_debug_set_row_blocks(int mt, int split, int kp) { g_row_blocks = SqpStripPlan{2, split, 2, kp, mt}; }
+
+// Calls of more than 64 rows on layers too small for the tiled kernel: the strip kernel in row blocks of 48 or
+// 64 rows, all in one launch (mt 0: none).  A tile of the tiled kernel takes 9 us at K = 1024 and 50 at K = 8192
+// with a compute unit to itself, however few tiles there are, and splitting its K costs a second launch
+// and the fp32 parts through memory; the strip kernel's workgroups are small, walk K with two waves per SIMD
+// and hand partial tiles over in the same launch.  It reads the weights once per row block (the second and
+// later ones from L2 or the last-level cache) and unpacks them again, so it loses once the chip is full:
+// taken where its estimated time is 8 % below that of the tiles (plan_launches' estimate and the 6.7 us that
+// it leaves out).
+// The estimate: A + iterations * (B + L * workgroups / compute units) + (H + S * parts), the last two terms with
+// more than one K part; at most one eight-wave workgroup (kp = 2) or two four-wave ones per compute unit.
+// Fitted to 13700 launches of 1547 shapes (65 to 1024 rows, N 768 to 24576, K 512 to 8192, groups of 32, 64, 128
+// and 256, weights from HBM): rms 3 to 6 %, the choice 1 % behind the best variant in the mean, 2 % slower than the
+// tiles at worst and 1.41 times faster in the geometric mean.  us, tiles -> row blocks, groups of 128:
+// 1024->1024 at 65 rows 12.1 -> 8.2, 1024->4096 at 160 rows 15.4 -> 9.2, 4096->4096 at 128 rows 21.7 -> 13.8, 2048->8192 at
+// 256 rows 26.0 -> 15.3, 8192->8192 at 65 / 128 rows 26.6 -> 25.0 / 32.8 -> 28.8 (at 160 rows 38.4 against 39.6).
+// limit: bytes of partial tiles the call may leave in its workspace.
+static SqpStripPlan row_blocks_plan(int M, int N, int K, int group, int cus, double tiles_us, size_t limit)
+{
+    struct Cost { double a, b, l, h, s; };
+    static const Cost cost[2][3] = {  // 48 and 64 rows; kp = 1 with up to one and two workgroups per unit, kp = 2
+        {{3.92, 0.651, 0.062, 2.14, 0.28}, {5.25, 0.755, 0.152, 1.77, 0.40}, {4.83, 1.025, 0.096, 1.60, 0.22}},
+        {{4.19, 0.736, 0.079, 2.03, 0.31}, {5.75, 0.820, 0.211, 1.68, 0.47}, {5.11, 1.154, 0.150, 1.58, 0.29}},
+    };
+    SqpStripPlan best = {2, 1, 2, 1, 0};
+    if (M <= 64 || K % 128 != 0) return best;
+    const int chunks = K / 128;
+    double least = (tiles_us + 6.7) / 1.08;
+    for (int mt = 3; mt <= 4; mt++) {
+        const long blocks = (M + 16 * mt - 1) / (16 * mt), tiles = (N + 127) / 128 * blocks;
+        for (int kp = 1; kp <= (group > 128 ? 1 : 2); kp++) {
+            for (int split = 1; split == 1 || 2 * split <= chunks; split++) {  // at least two chunks per part
+                const long groups = tiles * split;
+                if (groups > (kp == 2 ? cus : 2 * cus)) break;
+                size_t bytes = 0;
+                if (sqp_strip_split(mt, 2, 4, (int)blocks, N, K, split, &bytes) != split || bytes > limit) break;
+                const Cost &c = cost[mt - 3][kp == 2 ? 2 : (groups > cus ? 1 : 0)];
+                const int iterations = ((chunks + split - 1) / split + kp - 1) / kp;
+                double t = c.a + iterations * (c.b + c.l * groups / cus) + (split > 1 ? c.h + c.s * split : 0.0);
+                if (group < 128) t *= 1.05;  // steps and zero points of more groups
+                if (t < least) {
+                    least = t;
+                    best = SqpStripPlan{2, split, 2, kp, mt};
+                }
+            }
+        }
+    }
+    return best;
+}
+
+// What a call takes beside the tiled launches q: none where those are forced by a test hook.
+static SqpStripPlan row_blocks_for(const LaunchPlan &q, int M, int N, int K, int group, int cus, size_t limit)
+{
+    const bool hooked = g_tile_mode != 0 || g_tile_shape != 0 || g_ksplit >= 0 || g_force_rt > 0;
+    if (g_row_blocks.mt > 0 && K % 128 == 0) return g_row_blocks;
+    if (hooked || g_row_blocks.mt < 0) return SqpStripPlan{2, 1, 2, 1, 0};
+    return row_blocks_plan(M, N, K, group, cus, launches_us(q, K, group, cus), limit);
+}
+
+static size_t row_blocks_bytes(const SqpStripPlan &p, int M, int N, int K)
+{
+    size_t bytes = 0;
+    if (p.mt) sqp_strip_split(p.mt, p.nw, 4, (M + 16 * p.mt - 1) / (16 * p.mt), N, K, p.split, &bytes);
+    return bytes;
+}
+
+// Test hook: the row blocks of a call (rows / 16, K parts, chunks per iteration; rows 0: none), with a workspace of
+// the reported size or without.  Host arithmetic only.
+extern "C" void sqp_debug_row_blocks(int M, int N, int K, int group, int cus, int workspace, int *out3)
+{
+    const bool covered = tiled_covers(K, group);
+    SqpStripPlan p = {2, 0, 2, 0, 0};
+    if (covered) {
+        const LaunchPlan q = plan_launches(M, N, K, group, cus, workspace ? SIZE_MAX : 0, 0);
+        p = row_blocks_for(q, M, N, K, group, cus, workspace && plan_partial_bytes(q) > 0 ? SIZE_MAX : 0);
+    }
+    out3[0] = p.mt;
+    out3[1] = p.split;
+    out3[2] = p.kp;
+}
+
+// Bytes the tiled launches of a call leave in its workspace (0: it reports none and never touches it).
+static size_t tiles_bytes(int M, int N, int K, int group)
+{
+    return plan_partial_bytes(plan_launches(M, N, K, group, sqp_compute_units(), SIZE_MAX, 0));
+}
+
 size_t sqp_gemm_prefill_partial_bytes(int M, int N, int K, int group)
 {
     if (!tiled_covers(K, group)) return most_of_row_blocks(sqp_gemm_decode_partial_bytes, M, N, K, group);
     const LaunchPlan q = plan_launches(M, N, K, group, sqp_compute_units(), SIZE_MAX, 0);
-    return plan_partial_bytes(q);
+    const size_t tiles = plan_partial_bytes(q);
+    if (tiles == 0 && g_row_blocks.mt <= 0) return 0;  // (a forced plan says what it needs)
+    const size_t rows = row_blocks_bytes(row_blocks_for(q, M, N, K, group, sqp_compute_units(), SIZE_MAX), M, N, K);
+    return rows > tiles ? rows : tiles;
 }
 
 size_t sqp_gemm_prefill_scratch_bytes(int M, int N, int K, int group)
@@ -745,11 +854,11 @@ size_t sqp_gemm_prefill_scratch_bytes(int M, int N, int K, int group)
 }
 
 // What a workspace has to hold at least for a call not to be refused: the K parts of the plan in 128-row
-// tiles as [parts][M][N].  With less than the preferred plan's bytes, one that fits runs.
+// tiles as [parts][M][N].  With less than the preferred plan's bytes, one that fits runs, of row blocks too.
 size_t sqp_gemm_prefill_least_bytes(int M, int N, int K, int group)
 {
     if (!tiled_covers(K, group)) return most_of_row_blocks(sqp_gemm_decode_least_bytes, M, N, K, group);
-    const size_t want = sqp_gemm_prefill_partial_bytes(M, N, K, group);
+    const size_t want = tiles_bytes(M, N, K, group);
     if (g_force_rt > 0) return want;
     const TilePlan p = plan_tiles(M, N, K, group, sqp_compute_units(), true);
     const size_t base = p.ksplit >= 2 ? (size_t)p.ksplit * M * N * sizeof(float) : 0;
@@ -774,6 +883,11 @@ int sqp_gemm_prefill(int M, int N, int K, int group, const h16 *x, const uint32_
     const LaunchPlan q = plan_launches(M, N, K, group, sqp_compute_units(), room_ws, room_own);
     float *const part = q.own ? ws.own : ws.partial;
     if (plan_partial_bytes(q) > (q.own ? room_own : room_ws)) return SQP_ERR_WORKSPACE;
+    // Parts of row blocks go to the workspace where the shape reports one: the others may run beside calls that
+    // use it.
+    const size_t limit = room_ws > 0 && ws.tickets && tiles_bytes(M, N, K, group) > 0 ? room_ws : 0;
+    const SqpStripPlan rows = row_blocks_for(q, M, N, K, group, sqp_compute_units(), limit);
+    if (rows.mt) return sqp_strip_row_blocks(group, rows, M, N, K, group <= 128 ? 1 : group / 128, x, packed, scales, zeros, y, epi, ws, stream);
     for (int i = 0; i < q.count; i++) {
         const TileLaunch &l = q.l[i];
 #define SQP_TILES(RT, NT, WM, G32) launch_variant<RT, NT, WM, G32>(l, M, N, K, group, x, packed, scales, zeros, y, epi, part, stream)

@@ -69,6 +69,13 @@ __device__ __forceinline__ void store_row4(h16 *y, int m, int N, int n, int epi,
     }
 }
 
+// a / b of wave-uniform values, a < 2^20: the error of the reciprocal and the product is far below the distance
+// of (a + 1/2) / b from a whole number.
+__device__ __forceinline__ unsigned small_divide(unsigned a, unsigned b)
+{
+    return __builtin_amdgcn_readfirstlane((unsigned)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b)));
+}
+
 // Split-K tickets: one per 128-byte line (atomics on one line are served one after the other).
 constexpr int TICKET_STRIDE = 32;
 
@@ -84,7 +91,13 @@ constexpr int TICKET_STRIDE = 32;
 // making a wave's share of a chunk smaller); the halves add up through LDS like KW's.
 // GS: k-steps of a chunk that belong to one quantisation group: KSPG, or two and one where a chunk of
 // four k-steps holds two groups of 64 or four of 32 (cpg is 1 then).
-template <int MT, int NW, int KSPG, int KW, int KP, int GS>
+// RB: a grid of row blocks (z) of 16 MT rows, as many calls next to each other (calls of more than 64 rows).
+// SAME: workgroups are renumbered such that the K parts of a tile run on the same XCD (except at the ends of an
+// XCD's run), as they do by themselves where the tiles are a multiple of 8.  The hand-over is faster there: 4096->6912
+// at 64 rows (54 tiles, 4 parts) 17.9 -> 14.4 us, 4096->1792 at 24 rows 10.4 -> 9.2; 4, 6 and 9 % in the mean of odd tile
+// counts at 17 to 32, 33 to 48 and 49 to 64 rows, nothing up to 16.  A variant, not a branch: the
+// arithmetic before the first load costs 0.1 us.
+template <int MT, int NW, int KSPG, int KW, int KP, int GS, bool RB = false, bool SAME = false>
 __global__ void __launch_bounds__(NW * KW * KP * 64) __attribute__((amdgpu_waves_per_eu(KW * KP >= 2 ? 2 : (MT == 1 && NW >= 4 && KSPG < 4 * GS ? 3 : 1))))
 w4a16_decode_kernel(int M, int N, int K, int cpg, const h16 *__restrict__ x, const uint32_t *__restrict__ packed,
                     const h16 *__restrict__ scales, const uint8_t *__restrict__ zeros, h16 *__restrict__ y,
@@ -129,9 +142,25 @@ w4a16_decode_kernel(int M, int N, int K, int cpg, const h16 *__restrict__ x, con
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);    // wave-uniform, kept scalar
     const int wave = wv % NW, kh = (wv / NW) % KW, ph = wv / (NW * KW);   // strip, which k-steps of a chunk, which chunk of an iteration
     const int lc = lane & 15, lk = lane >> 4;
-    const int tile = blockIdx.x;
-    const int n0 = tile * BN + wave * 64;
-    const int split = gridDim.y, sidx = blockIdx.y;
+    const int split = gridDim.y;
+    int col = blockIdx.x, sidx = blockIdx.y, block = RB ? blockIdx.z : 0;
+    if constexpr (SAME) {
+        // Workgroups are dealt to the 8 XCDs in turn: each takes one run of (column tile, row block, part).
+        const unsigned blocks = RB ? gridDim.z : 1u, all = gridDim.x * split * blocks;
+        const unsigned id = blockIdx.x + gridDim.x * (blockIdx.y + split * (RB ? blockIdx.z : 0u)), xcd = id & 7u, more = all & 7u;
+        const unsigned p = xcd * (all >> 3) + (xcd < more ? xcd : more) + (id >> 3), u = small_divide(p, split);
+        sidx = p - u * split;
+        col = RB ? small_divide(u, blocks) : u;
+        block = u - col * blocks;
+    }
+    const int n0 = col * BN + wave * 64;
+    const int tile = block * gridDim.x + col;  // of the partial tiles and tickets
+    if constexpr (RB) {
+        x += (size_t)block * (16 * MT) * K;
+        y += (size_t)block * (16 * MT) * (epi == 0 ? N : N >> 1);
+        M -= block * (16 * MT);
+        M = M < 16 * MT ? M : 16 * MT;
+    }
     const int chunks = K / (32 * KSPG);
     // this workgroup's chunk range (all waves walk it together)
     const int g0 = (int)((long)chunks * sidx / split), g1 = (int)((long)chunks * (sidx + 1) / split);
@@ -158,7 +187,8 @@ w4a16_decode_kernel(int M, int N, int K, int cpg, const h16 *__restrict__ x, con
     // written in assembly so that this kernel, not the compiler, decides when to wait for
     // them: a stage must not be read before `landed` below.  They carry the non-temporal hint:
     // every weight byte is read once per launch, and a plain streaming probe reads 12-15 % faster
-    // with it on this chip (the kernel gains about 2 %).
+    // with it on this chip (the kernel gains about 2 %).  Row blocks read it once each and go without
+    // (5 % in the mean of 45 shapes, up to 15).
     const uint32_t voff_w = (uint32_t)(lk * N + ncol) * 4u;
     const int wrow_stride = N;
     const uint32_t voff_s = (uint32_t)ncol * 2u, voff_z = (uint32_t)ncol;
@@ -256,36 +286,44 @@ w4a16_decode_kernel(int M, int N, int K, int cpg, const h16 *__restrict__ x, con
                          : "memory", "scc");  // s_and_b32 writes SCC
         } else if constexpr (KS == 2 && NQ == 1) {
             const unsigned char *b1 = b0 + wstep1;
-            asm volatile("s_mov_b64 %[sv], exec\n\t"
-                         "s_and_b32 exec_lo, exec_lo, %[m]\n\t"
-                         "s_and_b32 exec_hi, exec_hi, %[m]\n\t"
-                         "global_load_dwordx4 %[w0], %[vw], %[b0] nt\n\t"
-                         "global_load_dwordx4 %[w1], %[vw], %[b1] nt\n\t"
-                         "global_load_dwordx2 %[sc0], %[vs], %[s0] nt\n\t"
-                         "global_load_dword %[zr0], %[vz], %[z0] nt\n\t"
-                         "s_mov_b64 exec, %[sv]"
-                         : [w0] "=&v"(s.w[0]), [w1] "=&v"(s.w[1]), [sc0] "=&v"(s.sc[0]), [zr0] "=&v"(s.zr[0]), [sv]
-                           "=&s"(saved)
-                         : [m] "s"(m), [vw] "v"(voff_w), [vs] "v"(voff_s), [vz] "v"(voff_z), [b0] "s"(b0), [b1] "s"(b1), [s0]
-                           "s"(sq), [z0] "s"(zq)
-                         : "memory", "scc");  // s_and_b32 writes SCC
+#define SQP_ISSUE(HINT) \
+    asm volatile("s_mov_b64 %[sv], exec\n\t" \
+                 "s_and_b32 exec_lo, exec_lo, %[m]\n\t" \
+                 "s_and_b32 exec_hi, exec_hi, %[m]\n\t" \
+                 "global_load_dwordx4 %[w0], %[vw], %[b0]" HINT "\n\t" \
+                 "global_load_dwordx4 %[w1], %[vw], %[b1]" HINT "\n\t" \
+                 "global_load_dwordx2 %[sc0], %[vs], %[s0]" HINT "\n\t" \
+                 "global_load_dword %[zr0], %[vz], %[z0]" HINT "\n\t" \
+                 "s_mov_b64 exec, %[sv]" \
+                 : [w0] "=&v"(s.w[0]), [w1] "=&v"(s.w[1]), [sc0] "=&v"(s.sc[0]), [zr0] "=&v"(s.zr[0]), [sv] \
+                   "=&s"(saved) \
+                 : [m] "s"(m), [vw] "v"(voff_w), [vs] "v"(voff_s), [vz] "v"(voff_z), [b0] "s"(b0), [b1] "s"(b1), [s0] \
+                   "s"(sq), [z0] "s"(zq) \
+                 : "memory", "scc")  /* s_and_b32 writes SCC */
+            if constexpr (RB) SQP_ISSUE("");
+            else SQP_ISSUE(" nt");
+#undef SQP_ISSUE
         } else if constexpr (KS == 2 && NQ == 2) {
             const unsigned char *b1 = b0 + wstep1, *s1 = sq + (long)N * 2, *z1 = zq + N;
-            asm volatile("s_mov_b64 %[sv], exec\n\t"
-                         "s_and_b32 exec_lo, exec_lo, %[m]\n\t"
-                         "s_and_b32 exec_hi, exec_hi, %[m]\n\t"
-                         "global_load_dwordx4 %[w0], %[vw], %[b0] nt\n\t"
-                         "global_load_dwordx4 %[w1], %[vw], %[b1] nt\n\t"
-                         "global_load_dwordx2 %[sc0], %[vs], %[s0] nt\n\t"
-                         "global_load_dword %[zr0], %[vz], %[z0] nt\n\t"
-                         "global_load_dwordx2 %[sc1], %[vs], %[s1] nt\n\t"
-                         "global_load_dword %[zr1], %[vz], %[z1] nt\n\t"
-                         "s_mov_b64 exec, %[sv]"
-                         : [w0] "=&v"(s.w[0]), [w1] "=&v"(s.w[1]), [sc0] "=&v"(s.sc[0]), [zr0] "=&v"(s.zr[0]), [sc1]
-                           "=&v"(s.sc[1]), [zr1] "=&v"(s.zr[1]), [sv] "=&s"(saved)
-                         : [m] "s"(m), [vw] "v"(voff_w), [vs] "v"(voff_s), [vz] "v"(voff_z), [b0] "s"(b0), [b1] "s"(b1), [s0]
-                           "s"(sq), [z0] "s"(zq), [s1] "s"(s1), [z1] "s"(z1)
-                         : "memory", "scc");  // s_and_b32 writes SCC
+#define SQP_ISSUE(HINT) \
+    asm volatile("s_mov_b64 %[sv], exec\n\t" \
+                 "s_and_b32 exec_lo, exec_lo, %[m]\n\t" \
+                 "s_and_b32 exec_hi, exec_hi, %[m]\n\t" \
+                 "global_load_dwordx4 %[w0], %[vw], %[b0]" HINT "\n\t" \
+                 "global_load_dwordx4 %[w1], %[vw], %[b1]" HINT "\n\t" \
+                 "global_load_dwordx2 %[sc0], %[vs], %[s0]" HINT "\n\t" \
+                 "global_load_dword %[zr0], %[vz], %[z0]" HINT "\n\t" \
+                 "global_load_dwordx2 %[sc1], %[vs], %[s1]" HINT "\n\t" \
+                 "global_load_dword %[zr1], %[vz], %[z1]" HINT "\n\t" \
+                 "s_mov_b64 exec, %[sv]" \
+                 : [w0] "=&v"(s.w[0]), [w1] "=&v"(s.w[1]), [sc0] "=&v"(s.sc[0]), [zr0] "=&v"(s.zr[0]), [sc1] \
+                   "=&v"(s.sc[1]), [zr1] "=&v"(s.zr[1]), [sv] "=&s"(saved) \
+                 : [m] "s"(m), [vw] "v"(voff_w), [vs] "v"(voff_s), [vz] "v"(voff_z), [b0] "s"(b0), [b1] "s"(b1), [s0] \
+                   "s"(sq), [z0] "s"(zq), [s1] "s"(s1), [z1] "s"(z1) \
+                 : "memory", "scc")  /* s_and_b32 writes SCC */
+            if constexpr (RB) SQP_ISSUE("");
+            else SQP_ISSUE(" nt");
+#undef SQP_ISSUE
         } else if constexpr (KS == 1 && NQ == 1) {
             asm volatile("s_mov_b64 %[sv], exec\n\t"
                          "s_and_b32 exec_lo, exec_lo, %[m]\n\t"
@@ -681,10 +719,19 @@ w4a16_decode_kernel(int M, int N, int K, int cpg, const h16 *__restrict__ x, con
 
 // ---------------------------------------------------------------- launch
 
+// Whether a launch takes the SAME variant (see the kernel; its division holds below 2^20 workgroups).
+inline bool parts_together(int tiles, int split, int blocks) { return split > 1 && tiles % 8 != 0 && (long)tiles * split * blocks < (1 << 20); }
+
 template <int MT, int NW, int KSPG, int KW, int KP, int GS>
 int launch_variant(int M, int N, int K, int cpg, int tiles, int split, const h16 *x, const uint32_t *packed, const h16 *scales,
                    const uint8_t *zeros, h16 *y, int epi, const Workspace &ws, hipStream_t st)
 {
+    if constexpr (MT >= 2 && NW == 2 && KW == 2)
+        if (parts_together(tiles, split, 1)) {
+            w4a16_decode_kernel<MT, NW, KSPG, KW, KP, GS, false, true><<<dim3(tiles, split), NW * KW * KP * 64, 0, st>>>(
+                M, N, K, cpg, x, packed, scales, zeros, y, ws, epi);
+            return sqp_launch_status();
+        }
     w4a16_decode_kernel<MT, NW, KSPG, KW, KP, GS><<<dim3(tiles, split), NW * KW * KP * 64, 0, st>>>(
         M, N, K, cpg, x, packed, scales, zeros, y, ws, epi);
     return sqp_launch_status();
@@ -698,7 +745,7 @@ int launch(int M, int N, int K, int cpg, const SqpStripPlan &plan, const h16 *x,
     constexpr int BN = 64 * NW;
     const int tiles = (N + BN - 1) / BN;
     size_t need = 0;
-    const int split = sqp_strip_split(MT, NW, KSPG, N, K, plan.split, &need);
+    const int split = sqp_strip_split(MT, NW, KSPG, 1, N, K, plan.split, &need);
     Workspace ws = {nullptr, nullptr};
     if (split > 1) {
         if (!cws.partial || !cws.tickets || need > cws.partial_bytes) return SQP_ERR_WORKSPACE;

@@ -452,6 +452,63 @@ def test_decode_slice_variants(orc, sqp, M, K, N, group, tb, wv, grouped):
         L.sqp_debug_set_slice_plan(0, 0, 0)
 
 
+@pytest.mark.parametrize("mt,split,kp", [(3, 1, 1), (3, 3, 2), (4, 1, 2), (4, 2, 1)])
+@pytest.mark.parametrize("M,K,N,group", [(65, 768, 8, 128), (96, 1024, 144, 64), (97, 896, 520, 32), (128, 2304, 272, 768), (145, 1280, 392, 128), (193, 768, 1040, 256)])
+def test_row_blocks(orc, sqp, M, K, N, group, mt, split, kp):
+    """More than 64 rows by the strip kernel in row blocks of 48 and 64, forced: whole last blocks and last
+    blocks of 1 to 33 rows, ragged columns, parts of unequal length, several groups per chunk and
+    several chunks per group; the fused activation; bit-identical repeats; nothing written past y."""
+    print("case row blocks", M, K, N, group, mt, split, kp, flush=True)
+    xs, p, sc, z = _layer(orc, M, K, N, group)
+    L = sqp.lib()
+    L.sqp_debug_set_row_blocks(mt, split, kp)
+    try:
+        y0 = _check(orc, sqp, xs, p, sc, z, group)
+        buf = torch.full((M * N + 4096,), -7.0, dtype=torch.half, device="cuda")
+        sqp.w4a16_gemm(dev(xs), dev(p), dev(sc), dev(z), group, out=buf[:M * N].view(M, N))
+        assert np.array_equal(host(buf[:M * N]).view(np.uint16), y0.reshape(-1).view(np.uint16))
+        assert bool((buf[M * N:] == -7.0).all())
+        if N % 16:
+            return
+        act = host(sqp.w4a16_gemm_silu_mul(dev(xs), dev(p), dev(sc), dev(z), group)).astype(np.float64)
+    finally:
+        L.sqp_debug_set_row_blocks(0, 0, 0)
+    y = orc.w4a16_gemm_ref(xs, p, sc, z, group)
+    gate, up, tg, tu = y[0][:, 0::2], y[0][:, 1::2], y[1][:, 0::2], y[1][:, 1::2]
+    sig = 1 / (1 + np.exp(-gate))
+    # the tolerances of the two sums (1e-3 of their terms) through silu (|silu'| < 1.1) and the product, half an ulp
+    # of fp16 at the result (2^-11 of it, or of its smallest normal) and of silu itself
+    tol = 1e-3 * (1.1 * tg * (np.abs(up) + 1e-3 * tu) + np.abs(gate * sig) * tu) + 2.0 ** -10 * np.abs(gate * sig * up) + 2.0 ** -24
+    assert (np.abs(act - gate * sig * up) <= tol).all()
+
+
+@pytest.mark.parametrize("M,K,N,group,blocks", [(65, 1024, 1024, 128, True), (160, 4096, 1024, 64, True), (160, 8192, 8192, 128, False), (700, 512, 2056, 32, True)])
+def test_row_blocks_workspace(sqp, M, K, N, group, blocks):
+    """Row blocks by the rule and the tiles agree to the roundings of their sums; a shape that reports no
+    workspace takes no K parts, and one that does takes them within what it reports."""
+    print("case row blocks rule", M, K, N, group, flush=True)
+    L = sqp.lib()
+    out = (ctypes.c_int * 3)()
+    reported = sqp.workspace_bytes(M, N, K, group)
+    L.sqp_debug_row_blocks(M, N, K, group, 256, int(reported > 0), out)
+    assert (out[0] > 0) == blocks
+    if blocks:
+        assert out[1] == 1 or (512 << 10) + out[1] * -(-M // (16 * out[0])) * 16 * out[0] * -(-N // 128) * 128 * 4 <= reported
+    gen = torch.Generator(device="cuda").manual_seed(M + N)
+    w = torch.randn(K, N, generator=gen, device="cuda").half() * 0.02
+    p, sc, z = sqp.quantize_pack(w, group)
+    x = torch.randn(M, K, generator=gen, device="cuda").half()
+    y = sqp.w4a16_gemm(x, p, sc, z, group)
+    L.sqp_debug_set_row_blocks(-1, 0, 0)
+    try:
+        t = sqp.w4a16_gemm(x, p, sc, z, group)
+    finally:
+        L.sqp_debug_set_row_blocks(0, 0, 0)
+    # both multiply the same rounded weights: K fp32 additions of terms with absolute sum A (error K 2^-24 A), one fp16 ulp
+    a = x.abs().float() @ sqp.dequantize(p, sc, z, group).abs().float()
+    assert bool(((y - t).abs().float() <= K * 2.0 ** -23 * a + 2.0 ** -10 * t.abs().float() + 2.0 ** -24).all())
+
+
 @pytest.mark.parametrize("M,group,tb,wv", [(1, 128, 1, 8), (6, 64, 2, 8), (16, 256, 2, 16), (3, 128, 4, 8), (20, 64, 2, 8)])
 def test_decode_slice_nonfinite_activations(orc, sqp, M, group, tb, wv):
     """An infinity or a NaN among the activations gives what the strip kernel gives for it (sums over the
