@@ -73,6 +73,9 @@ def lib():
         fast.bind(*[ctypes.cast(f, ctypes.c_void_p).value for f in (
             L.sqp_w4a16_gemm, L.sqp_w4a16_gemm_silu_mul, L.sqp_w4a16_gemm_static, L.sqp_w4a16_gemm_workspace_bytes,
             L.sqp_rmsnorm, L.sqp_smooth_apply_x, L.sqp_w4a16_gemm_scratch, L.sqp_w4a16_gemm_scratch_bytes)])
+        fast.bind_preparation(*[ctypes.cast(f, ctypes.c_void_p).value for f in (
+            L.sqp_smooth_apply_w, L.sqp_scale_columns, L.sqp_smooth_scales, L.sqp_quantize_pack, L.sqp_dequantize,
+            L.sqp_transpose_nk, L.sqp_interleave_gate_up)])
         _fast = fast
         _lib = L
     return _lib
@@ -203,6 +206,10 @@ def _gemm(fused, x, packed, scales, zeros, group, out):
 
 def smooth_scales(x_cal, w, alpha, out=None):
     """Eq. 6: s [K] fp32 from calibration activations x_cal [T,K] and weight w [K,N]."""
+    if _native(w):
+        o = _fast.smooth_scales(x_cal, w, alpha, out, *_here())
+        if o is not None:
+            return o if type(o) is not int else _ended(o, "sqp_smooth_scales")
     T, K = x_cal.shape
     K2, N = w.shape
     if K != K2:
@@ -217,7 +224,7 @@ def smooth_scales(x_cal, w, alpha, out=None):
 def smooth_apply_x(x, s, out=None):
     """Eq. 5, activation side: x / s per input channel."""
     if _native(x):
-        o = _fast.apply_x(x, s, out, *_here())
+        o = _fast.apply(0, x, s, out, *_here())
         if o is not None:
             return o if type(o) is not int else _ended(o, "sqp_smooth_apply_x")
     M, K = x.shape
@@ -229,6 +236,10 @@ def smooth_apply_x(x, s, out=None):
 
 def smooth_apply_w(w, s, out=None):
     """Eq. 5, weight side: s * w per input channel."""
+    if _native(w):
+        o = _fast.apply(1, w, s, out, *_here())
+        if o is not None:
+            return o if type(o) is not int else _ended(o, "sqp_smooth_apply_w")
     K, N = w.shape
     o = out if out is not None else torch.empty_like(w)
     _check(lib().sqp_smooth_apply_w(K, N, _dev(w, torch.float16, "w"), _dev(s, torch.float32, "s"),
@@ -239,6 +250,10 @@ def smooth_apply_w(w, s, out=None):
 def quantize_pack(w, group=128, out=None):
     """Eq. 1 group-wise along K: returns (packed int32 [K/8,N] holding the uint32 words,
     scales fp16 [K/group,N], zeros uint8 [K/group,N])."""
+    if out is None and _native(w):
+        o = _fast.quantize_pack(w, group, *_here())
+        if o is not None:
+            return o if type(o) is not int else _ended(o, "sqp_quantize_pack")
     K, N = w.shape
     if out is not None:
         packed, scales, zeros = out
@@ -256,6 +271,10 @@ def quantize_pack(w, group=128, out=None):
 
 def dequantize(packed, scales, zeros, group=128, out=None):
     """Second line of Eq. 1: w_hat fp16 [K,N]."""
+    if _native(packed):
+        o = _fast.dequantize(packed, scales, zeros, group, out, *_here())
+        if o is not None:
+            return o if type(o) is not int else _ended(o, "sqp_dequantize")
     K, N = packed.shape[0] * 8, packed.shape[1]
     o = out if out is not None else torch.empty((K, N), dtype=torch.float16, device=packed.device)
     _check(lib().sqp_dequantize(N, K, group, _dev(packed, torch.int32, "packed"), _dev(scales, torch.float16, "scales"),
@@ -318,6 +337,10 @@ def rmsnorm(x, gamma, eps, out=None):
 
 def scale_columns(w, s, out=None):
     """w[k][n] / s[n] in fp16: a smoothing factor folded into the producing layer's columns."""
+    if _native(w):
+        o = _fast.apply(2, w, s, out, *_here())
+        if o is not None:
+            return o if type(o) is not int else _ended(o, "sqp_scale_columns")
     K, N = w.shape
     o = out if out is not None else torch.empty_like(w)
     _check(lib().sqp_scale_columns(K, N, _dev(w, torch.float16, "w"), _dev(s, torch.float32, "s"),
@@ -327,6 +350,10 @@ def scale_columns(w, s, out=None):
 
 def interleave_gate_up(w_gate, w_up, out=None):
     """[K,I] x 2 -> [K,2I], column 2j = gate j, column 2j+1 = up j."""
+    if _native(w_gate):
+        o = _fast.interleave_gate_up(w_gate, w_up, out, *_here())
+        if o is not None:
+            return o if type(o) is not int else _ended(o, "sqp_interleave_gate_up")
     K, I = w_gate.shape
     o = out if out is not None else torch.empty((K, 2 * I), dtype=torch.float16, device=w_gate.device)
     _check(lib().sqp_interleave_gate_up(K, I, _dev(w_gate, torch.float16, "w_gate"), _dev(w_up, torch.float16, "w_up"),
@@ -336,6 +363,10 @@ def interleave_gate_up(w_gate, w_up, out=None):
 
 def transpose_nk(w_nk, out=None):
     """[N,K] fp16 (checkpoint orientation) -> [K,N] fp16 (the orientation of Eq. 2)."""
+    if _native(w_nk):
+        o = _fast.transpose_nk(w_nk, out, *_here())
+        if o is not None:
+            return o if type(o) is not int else _ended(o, "sqp_transpose_nk")
     N, K = w_nk.shape
     o = out if out is not None else torch.empty((K, N), dtype=torch.float16, device=w_nk.device)
     _check(lib().sqp_transpose_nk(N, K, _dev(w_nk, torch.float16, "w_nk"), _dev(o, torch.float16, "w_kn"), _stream()),

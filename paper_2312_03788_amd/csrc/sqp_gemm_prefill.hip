@@ -779,12 +779,13 @@ static SqpStripPlan row_blocks_plan(int M, int N, int K, int group, int cus, dou
     double least = (tiles_us + 6.7) / 1.08;
     for (int mt = 3; mt <= 4; mt++) {
         const long blocks = (M + 16 * mt - 1) / (16 * mt), tiles = (N + 127) / 128 * blocks;
+        size_t part = 0;  // bytes of one K part's tiles (two for all: none where the tickets do not reach)
+        if (2 <= chunks && sqp_strip_split(mt, 2, 4, (int)blocks, N, K, 2, &part) == 2) part /= 2;
         for (int kp = 1; kp <= (group > 128 ? 1 : 2); kp++) {
             for (int split = 1; split == 1 || 2 * split <= chunks; split++) {  // at least two chunks per part
                 const long groups = tiles * split;
                 if (groups > (kp == 2 ? cus : 2 * cus)) break;
-                size_t bytes = 0;
-                if (sqp_strip_split(mt, 2, 4, (int)blocks, N, K, split, &bytes) != split || bytes > limit) break;
+                if (split > 1 && (part == 0 || part * split > limit)) break;
                 const Cost &c = cost[mt - 3][kp == 2 ? 2 : (groups > cus ? 1 : 0)];
                 const int iterations = ((chunks + split - 1) / split + kp - 1) / kp;
                 double t = c.a + iterations * (c.b + c.l * groups / cus) + (split > 1 ? c.h + c.s * split : 0.0);

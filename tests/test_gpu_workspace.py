@@ -513,6 +513,58 @@ def test_native_marshalling_equals_general_path(orc, sqp):
     torch.cuda.synchronize()
 
 
+def test_native_marshalling_of_preparation_equals_the_general_path(orc, sqp):
+    """The calls that prepare a weight: the general path's bits with and without outputs (also a flat one and,
+    where that path takes one, a larger one), its types for subclasses and parameters, its errors."""
+    import paper_2312_03788_amd.binding as b
+    _, xcal, wn = wl.layer_inputs(1, 512, 272)
+    x, w = dev(np.ascontiguousarray(xcal[:7])), dev(wn)
+    s, cols = dev(orc.smooth_scales(xcal, wn, 0.5)), torch.rand(272, device="cuda") + 0.5
+    pk = sqp.quantize_pack(w, 64)
+
+    class Tagged(torch.Tensor):
+        pass
+
+    def general(fn, *args, **kw):
+        held, b._fast = b._fast, None
+        try:
+            return fn(*args, **kw)
+        finally:
+            b._fast = held
+
+    tup = lambda o: o if isinstance(o, tuple) else (o,)
+    calls = [(sqp.smooth_scales, (x, w, 0.5), 1), (sqp.smooth_apply_w, (w, s), 0), (sqp.scale_columns, (w, cols), 0), (sqp.transpose_nk, (w,), 0),
+             (sqp.interleave_gate_up, (w, w * 2), 0), (sqp.quantize_pack, (w, 64), 0), (sqp.dequantize, (*pk, 64), 0)]
+    for fn, args, where in calls:
+        want = tup(general(fn, *args))
+        outs = [None, tuple(torch.empty_like(o) for o in want)]
+        if len(want) == 1:
+            outs += [(torch.empty(want[0].numel(), dtype=want[0].dtype, device="cuda"),), (torch.zeros(want[0].numel() + 8, dtype=want[0].dtype, device="cuda"),)]
+        for out in outs:
+            got = tup(fn(*args) if out is None else fn(*args, out=out if len(out) > 1 else out[0]))
+            assert out is None or all(g is o for g, o in zip(got, out))
+            for g, o in zip(got, want):
+                assert g.dtype == o.dtype and torch.equal(g.reshape(-1)[:o.numel()], o.reshape(-1)), fn.__name__
+                assert out is not None or g.shape == o.shape
+        for cast in (lambda t: t.as_subclass(Tagged), lambda t: torch.nn.Parameter(t, requires_grad=False)):
+            odd = args[:where] + (cast(args[where]),) + args[where + 1:]
+            for g, o, v in zip(tup(fn(*odd)), tup(general(fn, *odd)), want):
+                assert type(g) is type(o) and torch.equal(g.as_subclass(torch.Tensor), v)
+        first = args[where]
+        for v in (first.double(), first.cpu(), torch.cat([first, first], 1)[:, ::2], first[:0]):
+            a = args[:where] + (v,) + args[where + 1:]
+            messages = []
+            for run in (fn, lambda *q: general(fn, *q)):
+                with pytest.raises((b.SqpError, RuntimeError)) as e:
+                    run(*a)
+                messages.append(str(e.value))
+            assert messages[0] == messages[1], (fn.__name__, messages)
+    for bad in (lambda: sqp.quantize_pack(w, 0), lambda: sqp.quantize_pack(w, 100), lambda: sqp.smooth_scales(x[:, :508].contiguous(), w, 0.5)):
+        with pytest.raises(b.SqpError):
+            bad()
+    torch.cuda.synchronize()
+
+
 def test_native_marshalling_reports_the_librarys_code(sqp):
     """A code that the library returns ends in the general path's error after one call: a launch error may
     stem from earlier work while this call's kernels were enqueued, so it neither disappears nor is
