@@ -102,6 +102,7 @@ def _stream():
 
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # absent in builds without a GPU runtime
 _current_device = getattr(torch._C, "_cuda_getDevice", None)
+_Tensor = torch.Tensor
 
 
 def _here():
@@ -285,9 +286,9 @@ def dequantize(packed, scales, zeros, group=128, out=None):
 
 def w4a16_gemm(x, packed, scales, zeros, group=128, out=None):
     """Eq. 3: y [M,N] fp16 = x [M,K] fp16 times the group-wise 4-bit weight."""
-    if _native(x):
-        dev, stream = _here()
-        y = _fast.gemm(0, x, packed, scales, zeros, group, out, dev, stream, _held.get(dev, 0))
+    if _fast is not None and isinstance(x, _Tensor) and x.is_cuda:  # (written out: calls cost 0.1 us each)
+        dev = _current_device()
+        y = _fast.gemm(0, x, packed, scales, zeros, group, out, dev, _raw_stream(dev), _held.get(dev, 0))
         if y is not None:
             return y if type(y) is not int else _ended(y, "sqp_w4a16_gemm")
     return _gemm(0, x, packed, scales, zeros, group, out)
@@ -297,8 +298,9 @@ def w4a16_gemm_static(x, packed, scales, zeros, group=128, out=None):
     """Eq. 3 through the entry point that allocates nothing and needs no workspace (partial
     sums in the library's static device array); `out` should be passed by callers that must
     not allocate."""
-    if _native(x):
-        y = _fast.gemm(2, x, packed, scales, zeros, group, out, *_here(), 0)
+    if _fast is not None and isinstance(x, _Tensor) and x.is_cuda:
+        dev = _current_device()
+        y = _fast.gemm(2, x, packed, scales, zeros, group, out, dev, _raw_stream(dev), 0)
         if y is not None:
             return y if type(y) is not int else _ended(y, "sqp_w4a16_gemm_static")
     M, K = x.shape
@@ -314,9 +316,9 @@ def w4a16_gemm_static(x, packed, scales, zeros, group=128, out=None):
 
 def w4a16_gemm_silu_mul(x, packed, scales, zeros, group=128, out=None):
     """Merged, interleaved gate/up projection with SiLU(gate) * up fused: y [M, N/2] fp16."""
-    if _native(x):
-        dev, stream = _here()
-        y = _fast.gemm(1, x, packed, scales, zeros, group, out, dev, stream, _held.get(dev, 0))
+    if _fast is not None and isinstance(x, _Tensor) and x.is_cuda:  # (written out: calls cost 0.1 us each)
+        dev = _current_device()
+        y = _fast.gemm(1, x, packed, scales, zeros, group, out, dev, _raw_stream(dev), _held.get(dev, 0))
         if y is not None:
             return y if type(y) is not int else _ended(y, "sqp_w4a16_gemm_silu_mul")
     return _gemm(1, x, packed, scales, zeros, group, out)
