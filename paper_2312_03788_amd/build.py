@@ -110,7 +110,7 @@ def _build_torch_part():
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-w",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I" + sysconfig.get_paths()["include"]]
     cmd += ["-I" + p for p in cpp_extension.include_paths()]
-    cmd += [os.path.join(CSRC, "sqp_torch.cpp"), "-o", TORCH_LIB, "-L" + libdir, "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath," + libdir]
+    cmd += [os.path.join(CSRC, "sqp_torch.cpp"), "-o", TORCH_LIB, "-L" + libdir, "-ltorch_python", "-ltorch_hip", "-ltorch_cpu", "-lc10", "-Wl,-rpath," + libdir]
     subprocess.run(cmd, check=True)
 
 

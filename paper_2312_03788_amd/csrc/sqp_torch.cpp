@@ -16,6 +16,8 @@
 #include <Python.h>
 
 #include <ATen/ops/empty.h>
+#include <ATen/ops/empty_cuda_dispatch.h>
+#include <c10/core/impl/LocalDispatchKeySet.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <climits>
@@ -57,12 +59,23 @@ const at::Tensor *plain(PyObject *o, at::ScalarType type, long dev)
     return &t;
 }
 
+// A new tensor on the device of `like`.  Without dispatch modes, transforms, inference or grad modes that change the
+// thread's dispatch keys the dispatcher ends at the GPU's own `empty`: that is called straight away then
+// (0.7 us of a call of 4 to 5 instead of 0.8).
+at::Tensor fresh(at::IntArrayRef size, at::ScalarType type, const at::Tensor &like)
+{
+    const c10::impl::LocalDispatchKeySet tls = c10::impl::tls_local_dispatch_key_set();
+    if (tls.included_ == c10::default_included_set && tls.excluded_ == c10::default_excluded_set)
+        return at::cuda::empty(size, type, at::kStrided, like.device(), false, c10::nullopt);
+    return at::empty(size, like.options().dtype(type));
+}
+
 // `out` as given, or a new tensor like `like` with rows x cols elements (a given one is only taken
 // if it has exactly that many).
 bool output(PyObject *out, const at::Tensor &like, long rows, long cols, long dev, at::Tensor &y, at::ScalarType type = at::kHalf)
 {
     if (out == Py_None) {
-        y = at::empty({rows, cols}, like.options().dtype(type));
+        y = fresh({rows, cols}, type, like);
         return true;
     }
     const at::Tensor *t = plain(out, type, dev);
@@ -109,7 +122,7 @@ PyObject *gemm(PyObject *, PyObject *const *a, Py_ssize_t n)
         if (!output(a[6], *x, M, which == 1 ? N / 2 : N, dev, y)) Py_RETURN_NONE;
         const void *xp = x->data_ptr(), *pp = packed->data_ptr(), *sp = scales->data_ptr(), *zp = zeros->data_ptr();
         void *yp = y.data_ptr();
-        if (own > 0) scratch = at::empty({(long)own}, x->options().dtype(at::kByte));
+        if (own > 0) scratch = fresh({(long)own}, at::kByte, *x);
         void *op = own > 0 ? scratch.data_ptr() : nullptr;
         int rc;
         Py_BEGIN_ALLOW_THREADS
@@ -209,7 +222,7 @@ PyObject *smooth_scales(PyObject *, PyObject *const *a, Py_ssize_t n)
         const long T = x->size(0), K = x->size(1), N = w->size(1);
         if (!fits(T) || !fits(K) || !fits(N)) Py_RETURN_NONE;
         at::Tensor s;
-        if (a[3] == Py_None) s = at::empty({K}, w->options().dtype(at::kFloat));
+        if (a[3] == Py_None) s = fresh({K}, at::kFloat, *w);
         else if (!output(a[3], *w, K, 1, dev, s, at::kFloat)) Py_RETURN_NONE;
         const void *xp = x->data_ptr(), *wp = w->data_ptr();
         void *sp = s.data_ptr();
@@ -239,8 +252,8 @@ PyObject *quantize_pack(PyObject *, PyObject *const *a, Py_ssize_t n)
         if (!w || w->dim() != 2 || !fits(group)) Py_RETURN_NONE;
         const long K = w->size(0), N = w->size(1);
         if (!fits(K) || !fits(N) || K % group || K % 8) Py_RETURN_NONE;
-        const at::Tensor packed = at::empty({K / 8, N}, w->options().dtype(at::kInt)), scales = at::empty({K / group, N}, w->options()),
-                         zeros = at::empty({K / group, N}, w->options().dtype(at::kByte));
+        const at::Tensor packed = fresh({K / 8, N}, at::kInt, *w), scales = fresh({K / group, N}, at::kHalf, *w),
+                         zeros = fresh({K / group, N}, at::kByte, *w);
         const void *wp = w->data_ptr();
         void *pp = packed.data_ptr(), *sp = scales.data_ptr(), *zp = zeros.data_ptr();
         int rc;

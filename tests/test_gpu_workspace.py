@@ -565,6 +565,31 @@ def test_native_marshalling_of_preparation_equals_the_general_path(orc, sqp):
     torch.cuda.synchronize()
 
 
+def test_native_outputs_under_dispatch_modes(orc, sqp):
+    """Outputs are allocated through the dispatcher wherever a mode or the inference mode wants to know of them."""
+    from torch.utils._python_dispatch import TorchDispatchMode
+    seen = []
+
+    class Watch(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            seen.append(str(func))
+            return func(*args, **(kwargs or {}))
+
+    w = torch.randn((512, 272), device="cuda").half()
+    x = torch.randn((3, 512), device="cuda").half()
+    p = sqp.quantize_pack(w, 128)
+    want = sqp.w4a16_gemm(x, *p, 128)
+    with Watch():
+        got = sqp.w4a16_gemm(x, *p, 128)
+    assert any("empty" in f for f in seen) and torch.equal(got, want)
+    with torch.inference_mode():
+        got = sqp.w4a16_gemm(x, *p, 128)
+        assert got.is_inference() and torch.equal(got, want)
+    with torch.no_grad():
+        got = sqp.w4a16_gemm(x, *p, 128)
+    assert not got.is_inference() and not got.requires_grad and torch.equal(got, want)
+
+
 def test_native_marshalling_reports_the_librarys_code(sqp):
     """A code that the library returns ends in the general path's error after one call: a launch error may
     stem from earlier work while this call's kernels were enqueued, so it neither disappears nor is
