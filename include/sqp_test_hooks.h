@@ -48,7 +48,8 @@ void sqp_debug_set_prefill_variant(int rt, int nt, int parts);  /* one launch of
  * launch, half-width tiles of the second, K parts.  Host arithmetic only. */
 void sqp_debug_prefill_plan(int M, int N, int K, int cus, long *full, long *half, int *ksplit);
 
-void sqp_debug_set_row_blocks(int mt, int split, int kp);  /* more than 64 rows (K % 128 == 0): the strip kernel in row blocks of
+void sqp_debug_set_row_blocks(int mt, int split, int kp);  /* more than 64 rows (K % 128 == 0, groups of 32, 64
+                                                      and multiples of 128): the strip kernel in row blocks of
                                                       16 mt rows (3, 4), K parts, chunks per iteration; 0 = automatic, -1 = never */
 /* What a call takes of these: rows / 16 (0: the tiled kernel), K parts, chunks per iteration; with a workspace of
  * the reported size or without.  Host arithmetic only. */

@@ -750,6 +750,10 @@ static double launches_us(const LaunchPlan &q, int K, int group, int cus)
 static SqpStripPlan g_row_blocks = {0, 0, 0, 0, 0};
 extern "C" void sqp_debug_set_row_blocks(int mt, int split, int kp) { g_row_blocks = SqpStripPlan{2, split, 2, kp, mt}; }
 
+// Groups the row blocks cover: their chunks of 128 k hold whole groups or are parts of one (the tiled kernel also takes
+// 192, 320 and other odd multiples of 64, whose ends lie inside a chunk).
+static bool row_blocks_cover(int K, int group) { return K % 128 == 0 && (group == 32 || group == 64 || group % 128 == 0); }
+
 // Calls of more than 64 rows on layers too small for the tiled kernel: the strip kernel in row blocks of 48 or
 // 64 rows, all in one launch (mt 0: none).  A tile of the tiled kernel takes 9 us at K = 1024 and 50 at K = 8192
 // with a compute unit to itself, however few tiles there are, and splitting its K costs a second launch
@@ -774,7 +778,7 @@ static SqpStripPlan row_blocks_plan(int M, int N, int K, int group, int cus, dou
         {{4.19, 0.736, 0.079, 2.03, 0.31}, {5.75, 0.820, 0.211, 1.68, 0.47}, {5.11, 1.154, 0.150, 1.58, 0.29}},
     };
     SqpStripPlan best = {2, 1, 2, 1, 0};
-    if (M <= 64 || K % 128 != 0) return best;
+    if (M <= 64 || !row_blocks_cover(K, group)) return best;
     const int chunks = K / 128;
     double least = (tiles_us + 6.7) / 1.08;
     for (int mt = 3; mt <= 4; mt++) {
@@ -804,7 +808,7 @@ static SqpStripPlan row_blocks_plan(int M, int N, int K, int group, int cus, dou
 static SqpStripPlan row_blocks_for(const LaunchPlan &q, int M, int N, int K, int group, int cus, size_t limit)
 {
     const bool hooked = g_tile_mode != 0 || g_tile_shape != 0 || g_ksplit >= 0 || g_force_rt > 0;
-    if (g_row_blocks.mt > 0 && K % 128 == 0) return g_row_blocks;
+    if (g_row_blocks.mt > 0 && row_blocks_cover(K, group)) return g_row_blocks;
     if (hooked || g_row_blocks.mt < 0) return SqpStripPlan{2, 1, 2, 1, 0};
     return row_blocks_plan(M, N, K, group, cus, launches_us(q, K, group, cus), limit);
 }

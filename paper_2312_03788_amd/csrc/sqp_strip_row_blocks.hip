@@ -46,6 +46,7 @@ int by_rows(const SqpStripPlan &p, int M, int N, int K, int cpg, const h16 *x, c
 
 int sqp_strip_row_blocks(int group, SQP_STRIP_ARGS)
 {
+    if (K % 128 != 0 || (group != 32 && group != 64 && group % 128 != 0)) return SQP_ERR_SHAPE;  // (a plan's mistake)
     if (group == 32) return by_rows<1>(p, M, N, K, cpg, x, packed, scales, zeros, y, epi, ws, st);
     if (group == 64) return by_rows<2>(p, M, N, K, cpg, x, packed, scales, zeros, y, epi, ws, st);
     return by_rows<4>(p, M, N, K, cpg, x, packed, scales, zeros, y, epi, ws, st);

@@ -482,6 +482,15 @@ def test_row_blocks(orc, sqp, M, K, N, group, mt, split, kp):
     assert (np.abs(act - gate * sig * up) <= tol).all()
 
 
+@pytest.mark.parametrize("M,K,N,group", [(161, 384, 776, 192), (65, 768, 1024, 192), (100, 1920, 520, 320), (70, 128, 264, 128)])
+def test_more_than_64_rows_by_the_rule(orc, sqp, M, K, N, group):
+    """Small layers above 64 rows with groups whose ends lie inside a chunk of 128 k (and one that is a chunk),
+    nothing forced."""
+    print("case rows by rule", M, K, N, group, flush=True)
+    xs, p, sc, z = _layer(orc, M, K, N, group)
+    _check(orc, sqp, xs, p, sc, z, group)
+
+
 @pytest.mark.parametrize("M,K,N,group,blocks", [(65, 1024, 1024, 128, True), (160, 4096, 1024, 64, True), (160, 8192, 8192, 128, False), (700, 512, 2056, 32, True)])
 def test_row_blocks_workspace(sqp, M, K, N, group, blocks):
     """Row blocks by the rule and the tiles agree to the roundings of their sums; a shape that reports no

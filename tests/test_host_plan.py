@@ -313,3 +313,29 @@ def test_mlp_entry_argument_errors(L):
     assert g(4, 1024, 1024, 128, good, good, null, good, good, null) == -1
     assert L.sqp_transpose_nk(1024, 1020, good, good, null) == -2
     assert L.sqp_transpose_nk(1024, 1024, good, odd, null) == -3
+
+
+def test_row_blocks_take_whole_groups_only(L):
+    """The strip kernel's chunks of 128 k hold whole groups or are parts of one: calls of more than 64 rows with other
+    multiples of 64 (192, 320, ...) keep the tiled kernel, by the rule and with forced row blocks; the
+    same shapes with a group that divides into chunks do take row blocks."""
+    out = (ctypes.c_int * 3)()
+
+    def rows(M, K, N, group, ws):
+        L.sqp_debug_row_blocks(M, N, K, group, 256, ws, out)
+        return out[0]
+    rng = random.Random(17)
+    shapes = [(161, 384, 776, 192), (65, 768, 1024, 192), (128, 1920, 1024, 320), (100, 4992, 4096, 192), (128, 3840, 2048, 192)]
+    shapes += [(rng.randint(65, 1024), 128 * g // 64 * rng.randint(1, 8), 8 * rng.randint(96, 1024), g) for g in (192, 320, 448, 576) for _ in range(100)]
+    taken = 0
+    for force in (0, 3):
+        L.sqp_debug_set_row_blocks(force, 1, 1)
+        try:
+            for M, K, N, g in shapes:
+                assert K % g == 0 and K % 128 == 0
+                for ws in (0, 1):
+                    assert rows(M, K, N, g, ws) == 0, (M, K, N, g, ws, force)
+                    taken += rows(M, K, N, 128, ws) > 0
+        finally:
+            L.sqp_debug_set_row_blocks(0, 0, 0)
+    assert taken > len(shapes)
