@@ -18,24 +18,20 @@
 // slice, starting at b); their steps Delta are one load, their zero points another.  With the
 // fused SiLU(gate)*up output a lane's columns are whole (gate, up) pairs (TB >= 2).
 //
-// Unpack.  A nibble masked out of the word IS an fp16 number: the bits 3:0 of a half are the denormal
-// q * 2^-24 and the bits 7:4 are q * 2^-20, which the matrix cores multiply exactly.  So a word costs one
-// shift and four ANDs instead of nine operations (no exponent to put in, no offset to take out), the
-// two scales go to two accumulators (lo, hi: the same-scale halves of two k-steps make one operand), and
-// the zero point leaves through sum_k x (q - Z) = sum_k x q - Z sum_k x, with sum_k x from one more MFMA
-// against ones per operand of x.  All products are exact and all sums fp32, as before; what joins them
-// is three FMAs per accumulator register, column and group.  Rows are repeated in the 16-row operand
-// so that up to 4 (8) rows need only 1 (2) of the 4 registers of a lane scaled.
-// Groups of 32 have one k-step per group and keep the other unpack (dequant_word), and so do 9 and more rows
-// with four columns per lane (4096->22016, 16 rows: 14.4 against 13.7 us) and 17 and more rows, where three FMAs
-// for each of the registers cost what the unpack saves.
+// Unpack: the exact fp16 differences code - Z (dequant_word) are multiplied, a group is summed in fp32, and its
+// sum is added with one FMA by its step.  Rows are repeated in the 16-row operand so that up to 4 (8) rows need
+// only 1 (2) of the 4 registers of a lane scaled.  (The nibbles masked out of a word are fp16 denormals that the
+// matrix cores take as they are: four operations of nine less per word, with Z sum x taken off a group's sum
+// afterwards.  That subtracts two sums of the size Z sum |x| - a column whose codes are all Z did not give
+// 0, errors grew by up to 3 % behind the fp16 rounding - and it was no faster: 0.5 % slower in the mean of
+// 6814 calls, 1 % faster at one to four rows.)
 //
-// What bounds it: up to 8 rows the vector instructions (one row, 64 columns: 220 -> 140 per chunk and wave with
-// the new unpack), on narrow layers the latency of a wave's chunks, with many rows the activations.
-// us per launch in a replayed graph, before -> now, 1 / 8 / 16 rows (before: the strip kernel where N < 3072
-// or K = 11008): 1024->1024 6.2 / 6.3 / 6.4 -> 2.0 / 2.1 / 2.3, 4096->1024 6.7 / 6.9 / 7.0 -> 2.8 / 3.0 / 3.5,
-// 4096->4096 4.4 / 5.2 / 5.7 -> 2.9 / 4.1 / 4.8, 4096->12288 6.7 / 7.5 / 8.4 -> 5.7 / 6.7 / 7.6,
-// 4096->22016 11.3 / 12.7 / 13.9 -> 10.0 / 11.4 / 13.5, 11008->4096 at one row 8.9 -> 8.0.
+// What bounds it: up to 8 rows on wide layers the vector instructions beside the loads, on narrow layers the
+// latency of a wave's chunks, with many rows the activations.
+// us per launch, weights from HBM, strip kernel or 32- and 64-column slices of eight waves alone -> now, 1 / 8 / 16
+// rows: 1024->1024 6.3 / 6.5 / 6.6 -> 2.4 / 2.5 / 2.7, 4096->1024 7.2 / 7.3 / 7.4 -> 4.4 / 5.0 / 5.9,
+// 4096->4096 5.7 / 6.2 / 7.1 -> 4.8 / 5.3 / 6.1, 4096->12288 8.2 / 8.8 / 9.7 -> 7.5 / 8.1 / 9.1,
+// 4096->22016 13.4 / 14.1 / 15.8 -> 11.6 / 13.0 / 15.0, 12288->4096 at one row 10.6 -> 9.7.
 // Three and four stages per wave are slower everywhere (again, also with loads masked instead of skipped
 // at the end).
 #pragma once
@@ -62,9 +58,6 @@ w4a16_decode_slice_kernel(int M, int N, int K, int cpg, int grouped, const h16 *
     // Row i of the matrix operand is row i / RS of x: a lane's accumulator registers 4 lk + r then repeat, and
     // RR of the four are distinct.
     constexpr int RR = XB == 1 ? 1 : (XB == 2 ? 2 : 4), RS = 4 / RR;
-    // Nibbles as they are (see above) wherever that is less work: groups of two and more k-steps, and not with
-    // four columns or two row tiles whose registers all have to be scaled.
-    constexpr bool NIBBLES = GS > 1 && MT == 1 && (RR < 4 || TB < 4);
     static_assert(TB == 1 || TB == 2 || TB == 4, "columns per lane");
     static_assert(MT == 1 ? XB <= 4 : XB > 4 && XB <= 8, "row tiles");
     static_assert(!CPG || GS == 4, "several chunks per group");
@@ -91,15 +84,12 @@ w4a16_decode_slice_kernel(int M, int N, int K, int cpg, int grouped, const h16 *
     const bool my_tail = GS < 4 && tail_ks < 4 && c0 + (nmine - 1) * WV == chunks - 1;  // this wave's last chunk is a short one
 
     float acc[MT][TB][RR];
-    auto clear = [&]() {
 #pragma unroll
-        for (int mt = 0; mt < MT; mt++)
+    for (int mt = 0; mt < MT; mt++)
 #pragma unroll
-            for (int b = 0; b < TB; b++)
+        for (int b = 0; b < TB; b++)
 #pragma unroll
-                for (int r = 0; r < RR; r++) acc[mt][b][r] = 0.f;
-    };
-    clear();
+            for (int r = 0; r < RR; r++) acc[mt][b][r] = 0.f;
 
     typedef typename std::conditional<TB == 1, uint32_t, uint32_t __attribute__((ext_vector_type(TB == 1 ? 2 : TB)))>::type wvec;  // the packed words of the lane's columns
     typedef typename std::conditional<TB == 4, u32x2, uint32_t>::type svec;                                                       // their fp16 steps
@@ -117,18 +107,11 @@ w4a16_decode_slice_kernel(int M, int N, int K, int cpg, int grouped, const h16 *
     const long dw = (long)WV * 4 * wstep1;
     const int drem = CPG ? WV % cpg : 0;
     const long drow = CPG ? WV / cpg : WV * NQ;
-    const unsigned char *wq, *sq, *zq, *xq;
-    int rem, cis;  // position of the chunk being issued in its group; that chunk
-    auto start = [&]() {
-        const long row = CPG ? c0 / cpg : (long)c0 * NQ;
-        rem = CPG ? c0 % cpg : 0;
-        cis = c0;
-        wq = reinterpret_cast<const unsigned char *>(packed) + (long)c0 * 4 * wstep1;
-        sq = reinterpret_cast<const unsigned char *>(scales) + row * N * 2;
-        zq = zeros + row * N;
-        xq = reinterpret_cast<const unsigned char *>(x) + (long)c0 * 256;
-    };
-    start();
+    const long row0 = CPG ? c0 / cpg : (long)c0 * NQ;
+    int rem = CPG ? c0 % cpg : 0, cis = c0;  // position of the chunk being issued in its group; that chunk
+    const unsigned char *wq = reinterpret_cast<const unsigned char *>(packed) + (long)c0 * 4 * wstep1;
+    const unsigned char *sq = reinterpret_cast<const unsigned char *>(scales) + row0 * N * 2, *zq = zeros + row0 * N;
+    const unsigned char *xq = reinterpret_cast<const unsigned char *>(x) + (long)c0 * 256;
 
     // Activations of a chunk: XB direct global->LDS loads of 1 KB (four rows of 256 bytes
     // each).  Lane i of a block handles row i / 16 of the block and fetches piece
@@ -242,9 +225,7 @@ w4a16_decode_slice_kernel(int M, int N, int K, int cpg, int grouped, const h16 *
         return (float)((b & 1) ? v.y : v.x);
     };
 
-    // One chunk.  CODES: the nibbles themselves; otherwise (also in the second pass below) the exact fp16
-    // differences code - Z.
-    auto compute = [&](const Stage &s, auto SLOT, bool tail, auto CODES) {
+    auto compute = [&](const Stage &s, auto SLOT, bool tail) {
         constexpr int slot = decltype(SLOT)::value;
         // The A fragments are read with instructions written in assembly: the compiler cannot
         // tell which ring slot a direct load filled and would wait for every outstanding load.
@@ -271,74 +252,31 @@ w4a16_decode_slice_kernel(int M, int N, int K, int cpg, int grouped, const h16 *
         // FMAs): a register that nothing reads would otherwise be free for an instruction in assembly while
         // the MFMA still writes it, and the compiler adds no wait states for those.
         const f32x4 none = {0.f, 0.f, 0.f, 0.f};
+        const UnpackConsts uc = SQP_UNPACK_CONSTS;
 #pragma unroll
         for (int q = 0; q < NQ; q++) {
-            if constexpr (decltype(CODES)::value) {
-                const h16x8 ones = __builtin_bit_cast(h16x8, u32x4{0x3c003c00u, 0x3c003c00u, 0x3c003c00u, 0x3c003c00u});
-                f32x4 lo[MT][TB], hi[MT][TB], sx[MT];
+            f32x4 g[MT][TB];
 #pragma unroll
-                for (int mt = 0; mt < MT; mt++) {
-                    sx[mt] = none;
+            for (int ks = q * GS; ks < q * GS + GS; ks++) {
+                h16x8 a[MT];
 #pragma unroll
-                    for (int b = 0; b < TB; b++) lo[mt][b] = hi[mt][b] = none;
-                }
-#pragma unroll
-                for (int ks = q * GS; ks < q * GS + GS; ks += 2) {
-                    h16x8 al[MT], ah[MT];  // of two k-steps: k 0, 4, 2, 6 of each word; k 1, 5, 3, 7
-#pragma unroll
-                    for (int mt = 0; mt < MT; mt++) {
-                        const h16x8 p0 = permute_x(xa[ks][mt]), p1 = permute_x(xa[ks + 1][mt]);
-                        al[mt] = h16x8{p0.s0, p0.s1, p0.s4, p0.s5, p1.s0, p1.s1, p1.s4, p1.s5};
-                        ah[mt] = h16x8{p0.s2, p0.s3, p0.s6, p0.s7, p1.s2, p1.s3, p1.s6, p1.s7};
-                        sx[mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[mt], ones, sx[mt], 0, 0, 0);
-                        sx[mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[mt], ones, sx[mt], 0, 0, 0);
-                    }
-#pragma unroll
-                    for (int b = 0; b < TB; b++) {
-                        const uint32_t w0 = word_of(s, ks, b), w1 = word_of(s, ks + 1, b), e0 = w0 >> 8, e1 = w1 >> 8;
-                        constexpr uint32_t ML = 0x000f000fu, MH = 0x00f000f0u;
-                        const h16x8 bl = __builtin_bit_cast(h16x8, u32x4{w0 & ML, e0 & ML, w1 & ML, e1 & ML});
-                        const h16x8 bh = __builtin_bit_cast(h16x8, u32x4{w0 & MH, e0 & MH, w1 & MH, e1 & MH});
-#pragma unroll
-                        for (int mt = 0; mt < MT; mt++) {
-                            lo[mt][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[mt], bl, lo[mt][b], 0, 0, 0);
-                            hi[mt][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[mt], bh, hi[mt][b], 0, 0, 0);
-                        }
-                    }
-                }
-#pragma unroll
-                for (int b = 0; b < TB; b++) {
-                    const float d = step_of(s, q, b), dl = d * 16777216.0f, dh = d * 1048576.0f, dz = -d * (float)zero_of(s, q, b);  // 2^24, 2^20
-#pragma unroll
-                    for (int mt = 0; mt < MT; mt++) {
-#pragma unroll
-                        for (int r = 0; r < RR; r++)
-                            acc[mt][b][r] = fmaf(dz, sx[mt][r * RS], fmaf(dh, hi[mt][b][r * RS], fmaf(dl, lo[mt][b][r * RS], acc[mt][b][r])));
-                        asm volatile("" : "+v"(acc[mt][b][0]) : "v"(lo[mt][b]), "v"(hi[mt][b]), "v"(sx[mt]));
-                    }
-                }
-            } else {
-                // (column by column: the second pass must not need more registers than the first)
-                const UnpackConsts uc = SQP_UNPACK_CONSTS;
+                for (int mt = 0; mt < MT; mt++) a[mt] = permute_x(xa[ks][mt]);
 #pragma unroll
                 for (int b = 0; b < TB; b++) {
                     const uint32_t z = zero_of(s, q, b);
-                    const h16x2 neg_hi = neg_hi_of(z), neg_lo = neg_lo_of(z);
-                    const float d = step_of(s, q, b);
-                    f32x4 g[MT];
+                    const h16x8 w = dequant_word(word_of(s, ks, b), neg_hi_of(z), neg_lo_of(z), uc);
 #pragma unroll
-                    for (int ks = q * GS; ks < q * GS + GS; ks++) {
-                        const h16x8 w = dequant_word(word_of(s, ks, b), neg_hi, neg_lo, uc);
+                    for (int mt = 0; mt < MT; mt++) g[mt][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[mt], w, ks == q * GS ? none : g[mt][b], 0, 0, 0);
+                }
+            }
 #pragma unroll
-                        for (int mt = 0; mt < MT; mt++)
-                            g[mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(permute_x(xa[ks][mt]), w, ks == q * GS ? none : g[mt], 0, 0, 0);
-                    }
+            for (int b = 0; b < TB; b++) {
+                const float d = step_of(s, q, b);
 #pragma unroll
-                    for (int mt = 0; mt < MT; mt++) {
+                for (int mt = 0; mt < MT; mt++) {
 #pragma unroll
-                        for (int r = 0; r < RR; r++) acc[mt][b][r] = fmaf(d, g[mt][r * RS], acc[mt][b][r]);
-                        asm volatile("" : "+v"(acc[mt][b][0]) : "v"(g[mt]));
-                    }
+                    for (int r = 0; r < RR; r++) acc[mt][b][r] = fmaf(d, g[mt][b][r * RS], acc[mt][b][r]);
+                    asm volatile("" : "+v"(acc[mt][b][0]) : "v"(g[mt][b]));
                 }
             }
         }
@@ -352,47 +290,18 @@ w4a16_decode_slice_kernel(int M, int N, int K, int cpg, int grouped, const h16 *
     constexpr std::integral_constant<int, 0> S0 = {};
     constexpr std::integral_constant<int, 1> S1 = {};
     Stage st[2];
-    auto walk = [&](auto CODES) {
-        if (nmine > 0) issue(st[0], 0);
-        for (int i = 0; i < nmine; i += 2) {
-            landed(st[0]);
-            if (i + 1 < nmine) issue(st[1], 1);
-            compute(st[0], S0, my_tail && i == nmine - 1, CODES);
-            if (i + 1 < nmine) {
-                landed(st[1]);
-                if (i + 2 < nmine) issue(st[0], 0);
-                compute(st[1], S1, my_tail && i + 1 == nmine - 1, CODES);
-            }
-        }
-    };
-    walk(std::integral_constant<bool, NIBBLES>());
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (nothing is in flight here: for the reader of the assembly)
-#pragma unroll
-    for (int mt = 0; mt < MT; mt++)
-#pragma unroll
-        for (int b = 0; b < TB; b++)
-#pragma unroll
-            for (int r = 0; r < RR; r++) asm volatile("" : "+v"(acc[mt][b][r]));
-    if constexpr (NIBBLES) {
-        // An infinity or a NaN in x makes sum x q - Z sum x a NaN where sum x (q - Z) need not be one: such
-        // a wave walks its chunks again with the differences.
-        float bad = 0.f;
-#pragma unroll
-        for (int mt = 0; mt < MT; mt++)
-#pragma unroll
-            for (int b = 0; b < TB; b++)
-#pragma unroll
-                for (int r = 0; r < RR; r++) bad = fmaf(acc[mt][b][r], 0.f, bad);  // NaN if any sum is not finite
-        if (__builtin_amdgcn_ballot_w64(bad != 0.f) != 0ull) {  // (a NaN is not equal to 0)
-            clear();
-            start();
-            for (int i = 0; i < nmine; i++) {
-                issue(st[0], 0);
-                landed(st[0]);
-                compute(st[0], S0, my_tail && i == nmine - 1, std::false_type());
-            }
+    if (nmine > 0) issue(st[0], 0);
+    for (int i = 0; i < nmine; i += 2) {
+        landed(st[0]);
+        if (i + 1 < nmine) issue(st[1], 1);
+        compute(st[0], S0, my_tail && i == nmine - 1);
+        if (i + 1 < nmine) {
+            landed(st[1]);
+            if (i + 2 < nmine) issue(st[0], 0);
+            compute(st[1], S1, my_tail && i + 1 == nmine - 1);
         }
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (nothing is in flight here: for the reader of the assembly)
 
     // ---- the waves add their sums through LDS (the rings are idle once every wave is here), in
     // wave order: wave v < MT RR adds and stores register v % RR of row tile v / RR, i.e. the rows

@@ -521,8 +521,8 @@ def test_row_blocks_workspace(sqp, M, K, N, group, blocks):
 @pytest.mark.parametrize("M,group,tb,wv", [(1, 128, 1, 8), (6, 64, 2, 8), (16, 256, 2, 16), (3, 128, 4, 8), (20, 64, 2, 8)])
 def test_decode_slice_nonfinite_activations(orc, sqp, M, group, tb, wv):
     """An infinity or a NaN among the activations gives what the strip kernel gives for it (sums over the
-    differences code - Z: an infinity times a code above, below or at the zero point), and rows without any
-    are not touched by it."""
+    differences code - Z: an infinity times a code above, below or at the zero point), and the other rows
+    keep every bit."""
     K, N = 1024, 264
     xs, p, sc, z = _layer(orc, M, K, N, group)
     clean = xs.copy()
@@ -546,8 +546,38 @@ def test_decode_slice_nonfinite_activations(orc, sqp, M, group, tb, wv):
     inf = np.isinf(want[hit])
     assert np.array_equal(got[hit][inf], want[hit][inf])
     rest = [m for m in range(M) if m not in hit]
-    # their sums are those of the differences where a wave walked its chunks again: fp32 rounding, then fp16's
-    assert np.allclose(got[rest].astype(np.float64), ref[rest].astype(np.float64), rtol=2e-3, atol=1e-3 * np.abs(ref).max())
+    assert np.array_equal(got[rest].view(np.uint16), ref[rest].view(np.uint16))
+
+
+@pytest.mark.parametrize("M,K,N,group", [(1, 4096, 1024, 128), (3, 1024, 264, 64), (8, 1024, 520, 128), (13, 1152, 136, 32), (16, 1024, 264, 256), (20, 1024, 264, 64), (40, 1024, 264, 128), (70, 1024, 264, 128)])
+@pytest.mark.parametrize("tb,wv", [(0, 0), (1, 8), (1, 16), (2, 8), (4, 4), (4, 8)])
+def test_codes_at_the_zero_point_count_nothing(orc, sqp, M, K, N, group, tb, wv):
+    """A weight whose code is the zero point is exactly 0: whatever finite activations meet such weights only, also next
+    to the largest fp16 value, their sum is exactly 0, by the rule and in every slice variant; one other code in
+    the column then gives its own product alone, rounded as the plain product is."""
+    if M > 32 and tb:
+        pytest.skip("the column-slice kernel takes up to 32 rows")
+    print("case zero codes", M, K, N, group, tb, wv, flush=True)
+    rng = np.random.Generator(np.random.PCG64(M + K))
+    z = rng.integers(0, 16, size=(K // group, N)).astype(np.uint8)
+    q = np.repeat(z, group, 0).astype(np.uint32)
+    single = rng.integers(0, K, size=N // 2)   # the even columns get one other code, a step of 1 / 64
+    q[single, np.arange(0, N, 2)] ^= 1
+    p = np.zeros((K // 8, N), np.uint32)
+    for i in range(8):
+        p |= q[i::8] << np.uint32(4 * i)
+    sc = np.full((K // group, N), 1 / 64, np.float16)
+    x = (rng.standard_normal((M, K)) * np.where(rng.random(K) < 0.05, 20000, 1)).clip(-60000, 60000).astype(np.float16)
+    want = np.zeros((M, N), np.float16)
+    sign = (q[single, np.arange(0, N, 2)].astype(np.int64) - z[single // group, np.arange(0, N, 2)])
+    want[:, 0::2] = (x[:, single].astype(np.float64) * sign / 64).astype(np.float16)
+    L = sqp.lib()
+    L.sqp_debug_set_slice_plan(tb, wv, 0)
+    try:
+        y = host(sqp.w4a16_gemm(dev(x), dev(p), dev(sc), dev(z), group))
+    finally:
+        L.sqp_debug_set_slice_plan(0, 0, 0)
+    assert np.array_equal(y, want)  # (0 == -0)
 
 
 @pytest.mark.parametrize("M,K,N,group", _random_shapes(202, 8, 65, 700))
