@@ -1,5 +1,7 @@
 // Launch plans of the weight-streaming W4A16 GEMM (up to 64 rows) and its fallback kernel.  The
 // kernels themselves: sqp_strip_kernel.h, sqp_slice_kernel.h.
+#include <limits.h>
+
 #include "sqp_slice.h"
 #include "sqp_strip.h"
 
@@ -203,37 +205,53 @@ extern "C" int sqp_debug_decode_slice_choice(int M, int N, int K, int group) { r
 static SqpSlicePlan g_slice_plan = {0, 0, false};
 extern "C" void sqp_debug_set_slice_plan(int tb, int wv, int grouped) { g_slice_plan = SqpSlicePlan{tb, wv, grouped != 0}; }
 
-// Whether a call of up to 32 rows takes the column-slice kernel, and how wide its slices are.  From a sweep
-// over 1356 calls (N 1024 to 44032, K 1024 to 22016, groups of 32, 64, 128 and 256, weights from HBM): 1.21
-// times faster than the plans before in the geometric mean, 0.6 % behind the best variant of each call.
+// Whether a call of up to 32 rows takes the column-slice kernel, and how wide its slices are.
 //   Width: the narrowest that fits the chip in one round, i.e. 16 columns up to 4096, 32 up to 8192, 64 from
-//   there on (one workgroup too many costs a round: 4352 columns in 16s 10.5 us, in 32s 8.8 at one row and
+//   there on (one workgroup too many costs a round: 4352 columns in 16s 10.8 us, in 32s 8.7 at one row and
 //   K = 8192).  Above 16384 columns 64, or 32 in groups of 32 up to 16 rows and 32768 columns (their unpack
 //   is the longer one: 22016 columns, K = 2112, 6 rows 12.3 -> 9.8 us).
 //   Waves: eight; 16 for one to four rows on narrow layers with long K (4096->1024 at one row 4.7 -> 4.4 us);
-//   four with 64 columns, up to 8 rows and two slices per compute unit (4096->22016 at one row 11.8 -> 11.0).
+//   four with 64 columns, up to 8 rows and two slices per compute unit (4096->22016 at one row 12.8 -> 11.6).
 //   K: the strip kernel's hand-over costs about the same whatever K, the slices' latency and activations grow
-//   with K, so longer K goes to the strips: us at 1 / 8 / 16 / 32 rows, strips against slices, N = 1024:
-//   K = 4096 7.2 / 7.3 / 7.4 / 9.3 against 4.4 / 5.1 / 6.0 / 7.3, K = 12288 9.5 / 9.6 / 9.9 / 11.9 against
-//   8.5 / 10.6 / 13.0 / 17.4.  Groups of several chunks hold out longer (the strip kernel takes one chunk per
-//   iteration there).  K not a multiple of 128: always slices (the strips take chunks of one group there).
+//   with K, so K above `longest` goes to the strips: us at 1 / 8 / 16 / 32 rows, strips against slices, N = 1024:
+//   K = 4096 7.1 / 7.2 / 7.3 / 9.2 against 4.4 / 5.0 / 5.9 / 7.3, K = 12288 9.4 / 9.5 / 9.9 / 11.9 against
+//   8.5 / 10.5 / 13.0 / 17.4.  From 257 to 320 slices of 64 columns the chip is a round and a little full, and
+//   short K only is worth it (17904 columns, K = 9984, 5 rows: 30.3 against 24.2).  K not a multiple of 128:
+//   the strips take chunks of one group there, so slices pay up to 1.6 times that K, from 8192 columns on
+//   with any.  Above 8192 columns groups of several chunks hold out longer (the strip kernel takes one chunk
+//   per iteration there).
+//   The lengths are those with the least time over 6814 calls (1 to 32 rows, N 512 to 44032, K 512 to 22016, groups
+//   of 32 to 384, three in four drawn over these ranges, weights from HBM): 1.27 times faster than without slices
+//   in the geometric mean, 0.4 % behind the better of the two kernels; 1.5 % of the calls are more than 3 % slower
+//   than without slices, at worst 19 % (decode_routes_sweep.md among the profiles).
 static SqpSlicePlan slice_plan(int M, int N, int K, int group)
 {
     const SqpSlicePlan none = {0, 0, false};
     if (g_slice_mode < 0 || M > 32 || (group != 32 && group != 64 && group % 128 != 0)) return none;
     if (g_slice_plan.tb > 0) return g_slice_plan;
     if (g_slice_mode > 0) return SqpSlicePlan{2 * g_slice_mode, 8, false};
-    const int width = N <= 4096 ? 0 : (N <= 8192 ? 1 : (N <= 16384 ? 2 : 3));
     const int blocks = M > 16 ? 4 : (M + 3) / 4 - 1;  // blocks of four rows less one; 17 to 32 rows
-    constexpr int ANY = 1 << 30;
-    static const int longest[4][5] = {{12288, 9216, 9216, 6144, 6144}, {16384, 13312, 10240, 6144, 6144}, {ANY, ANY, 13312, 6144, 6144}, {ANY, ANY, 5120, 4096, 0}};
-    int most = longest[width][blocks];
-    if (width == 2 && M > 12 && N >= 11008) most = 9216;   // 172 and more slices
-    if (width == 3 && M > 16 && N >= 32768) most = 2048;   // the strips have more than 256 tiles
-    if (group > 128 && width > 0) most = width == 3 && M > 8 ? (M > 16 && K < 2048 ? 0 : 11264) : (most == ANY ? ANY : most + most / 2);
-    if (group == 32 && width == 2) most = ANY;
-    const bool odd = K % 128 != 0 && !(group == 32 && N > 32768 && M > 4);
-    if (K > most && !odd && slice_variant(M, N, K, group) < 0) return none;
+    constexpr int ANY = 1 << 28;
+    static const struct { int columns, longest[5]; } lengths[8] = {
+        {2048, {12288, 8192, 7168, 6144, 6144}},
+        {4096, {13312, 9728, 8704, 6144, 5632}},
+        {8192, {13312, 12288, 9728, 6656, 6144}},
+        {12288, {16384, 13312, 12288, 8704, 8704}},
+        {16384, {ANY, ANY, 20480, 11264, 13312}},
+        {20480, {4096, 2560, 2560, 2048, 0}},
+        {32768, {16384, 8192, 7680, 4096, 0}},
+        {INT_MAX, {9728, 9216, 4096, 2560, 2048}},
+    };
+    int row = 0;
+    while (N > lengths[row].columns) row++;
+    double most = lengths[row].longest[blocks];
+    if (N > 16384) most *= group == 32 ? 0.85 : (group > 128 ? 2.0 : 1.0);
+    else if (N > 8192 && group == 32) most = 11264;
+    else if (N > 8192 && group > 128) most *= 1.3;
+    if (N > 32768 && M > 16 && K < 1024) most = 0;
+    if (K % 128 != 0) most = N <= 8192 ? 1.6 * most : (N <= 32768 || M > 16 ? ANY : 0.75 * most);
+    if (K > most && slice_variant(M, N, K, group) < 0) return none;
+    const int width = N <= 4096 ? 0 : (N <= 8192 ? 1 : (N <= 16384 ? 2 : 3));
     SqpSlicePlan p = {width == 0 ? 1 : (width == 1 ? 2 : 4), 8, width < 2};
     if (group == 32 && width == 3 && N <= 32768 && M <= 16) p.tb = 2, p.grouped = true;
     if (M <= 16 && width < 2 && K > 2048 && M <= (width == 0 ? 4 : 2)) p.wv = 16;

@@ -117,6 +117,21 @@ def test_slice_plan_values(L):
     assert plan(4, 22016, 4096, 128) == (4, 4) and plan(4, 22016, 4096, 32) == (2, 8) and plan(1, 4096, 4096, 24) == (0, 0)
 
 
+def test_slice_plan_between_model_shapes(L):
+    """Layers between the models' shapes that run up to 1.4 times slower in slices than in strips take strips (a little
+    more than 256 slices and long K; K not a multiple of 128, narrow and long; short K and many columns at 17
+    and more rows), and their neighbours that run faster in slices keep them."""
+    def sliced(M, N, K, g):
+        tb, wv = ctypes.c_int(), ctypes.c_int()
+        L.sqp_debug_decode_slice_plan(M, N, K, g, ctypes.byref(tb), ctypes.byref(wv))
+        return tb.value > 0
+    for call in [(7, 17816, 6784, 64), (5, 17904, 9984, 64), (22, 21128, 5888, 256), (19, 20808, 2816, 256), (11, 888, 19648, 64), (31, 888, 19648, 64),
+                 (12, 9848, 17024, 32), (22, 33104, 512, 64), (30, 39936, 512, 128), (15, 35624, 2848, 32), (32, 4016, 6144, 32), (29, 952, 13600, 32)]:
+        assert not sliced(*call), call
+    for call in [(5, 17904, 1024, 64), (17, 23296, 6336, 32), (32, 22016, 2112, 32), (11, 888, 8640, 64), (12, 9848, 8192, 32), (32, 39936, 1024, 128), (6, 22016, 2112, 32)]:
+        assert sliced(*call), call
+
+
 def test_decode_plan_many_rows(L):
     """More than 32 rows: two strips per workgroup, the split of the 16-row plan."""
     for (K, N) in wl.MODEL_SHAPES["34b"]:
