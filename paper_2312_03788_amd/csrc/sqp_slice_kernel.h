@@ -271,7 +271,8 @@ w4a16_decode_slice_kernel(int M, int N, int K, int cpg, int grouped, const h16 *
             }
 #pragma unroll
             for (int b = 0; b < TB; b++) {
-                const float d = step_of(s, q, b);
+                float d = step_of(s, q, b);
+                if (GS < 4 && tail && q * GS >= tail_ks) d = 0.f;  // no such group: an infinite step read again times 0 would be NaN
 #pragma unroll
                 for (int mt = 0; mt < MT; mt++) {
 #pragma unroll

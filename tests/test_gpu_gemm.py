@@ -549,6 +549,28 @@ def test_decode_slice_nonfinite_activations(orc, sqp, M, group, tb, wv):
     assert np.array_equal(got[rest].view(np.uint16), ref[rest].view(np.uint16))
 
 
+@pytest.mark.parametrize("M,K,N,group,tb,wv", [(1, 1056, 264, 32, 1, 8), (7, 1088, 136, 32, 2, 8), (20, 1120, 136, 32, 4, 8), (3, 1088, 264, 64, 1, 16), (16, 192, 72, 64, 4, 8)])
+def test_decode_slice_infinite_step_of_the_last_group(orc, sqp, M, K, N, group, tb, wv):
+    """A last chunk of one to three k-steps: its last group has a step of infinity in every second column, and the
+    results are the strip kernel's infinities (an infinite step counts once, with its own group's sum)."""
+    print("case infinite step", M, K, N, group, tb, wv, flush=True)
+    xs, p, sc, z = _layer(orc, M, K, N, group)
+    sc[-1, 0::2] = np.inf
+    L = sqp.lib()
+    run = lambda: host(sqp.w4a16_gemm(dev(xs), dev(p), dev(sc), dev(z), group))
+    try:
+        L.sqp_debug_set_decode_slice(-1)
+        want = run()
+        L.sqp_debug_set_decode_slice(0)
+        L.sqp_debug_set_slice_plan(tb, wv, 0)
+        got = run()
+    finally:
+        L.sqp_debug_set_decode_slice(0)
+        L.sqp_debug_set_slice_plan(0, 0, 0)
+    assert np.isinf(want[:, 0::2]).all()
+    assert np.array_equal(got[:, 0::2], want[:, 0::2]) and np.isfinite(got[:, 1::2]).all()
+
+
 @pytest.mark.parametrize("M,K,N,group", [(1, 4096, 1024, 128), (3, 1024, 264, 64), (8, 1024, 520, 128), (13, 1152, 136, 32), (16, 1024, 264, 256), (20, 1024, 264, 64), (40, 1024, 264, 128), (70, 1024, 264, 128)])
 @pytest.mark.parametrize("tb,wv", [(0, 0), (1, 8), (1, 16), (2, 8), (4, 4), (4, 8)])
 def test_codes_at_the_zero_point_count_nothing(orc, sqp, M, K, N, group, tb, wv):
