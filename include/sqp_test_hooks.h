@@ -55,6 +55,11 @@ void sqp_debug_set_row_blocks(int mt, int split, int kp);  /* more than 64 rows 
  * the reported size or without.  Host arithmetic only. */
 void sqp_debug_row_blocks(int M, int N, int K, int group, int cus, int workspace, int *out3);
 
+/* How an alpha search runs: sets of prepared operands that fit a region of `bytes` (-1: not even its factors and sums
+ * fit: single calls in turn), alphas per launch, whether the next ones are prepared beside them; bytes 0: the
+ * buffers of sqp_alpha_search.  Host arithmetic only. */
+void sqp_debug_search_plan(int T, int N, int K, int group, int n_alpha, size_t bytes, int *out3);
+
 /* What a call launches: returns the number of launches (1 or 2) and their (rt, nt, tiles, K parts) in
  * out8.  The plan above, or one round of tiles of another height where that is faster, and with K
  * parts for few left-over tiles; workspace and scratch as large as it likes.  Host arithmetic only. */

@@ -54,18 +54,26 @@ constexpr int SWBUF = LBN * SROW;
 
 // ---------------------------------------------------------------- preparation of a search's alphas
 
+constexpr int OWN_SET = 1 << 20;               // the caller's own buffers as a set (for single losses)
 struct SearchSets {                            // the prepared operands of one alpha, `stride` bytes apart
     unsigned char *base;
     size_t stride, at_scales, at_zeros, at_x;
-    __host__ __device__ uint32_t *packed(int i) const { return (uint32_t *)(base + i * stride); }
-    __host__ __device__ h16 *scales(int i) const { return (h16 *)(base + i * stride + at_scales); }
-    __host__ __device__ uint8_t *zeros(int i) const { return base + i * stride + at_zeros; }
-    __host__ __device__ h16 *x_hat(int i) const { return (h16 *)(base + i * stride + at_x); }
+    struct {
+        uint32_t *packed;
+        h16 *scales;
+        uint8_t *zeros;
+        h16 *x_hat;
+    } own;
+    __host__ __device__ uint32_t *packed(int i) const { return i == OWN_SET ? own.packed : (uint32_t *)(base + i * stride); }
+    __host__ __device__ h16 *scales(int i) const { return i == OWN_SET ? own.scales : (h16 *)(base + i * stride + at_scales); }
+    __host__ __device__ uint8_t *zeros(int i) const { return i == OWN_SET ? own.zeros : base + i * stride + at_zeros; }
+    __host__ __device__ h16 *x_hat(int i) const { return i == OWN_SET ? own.x_hat : (h16 *)(base + i * stride + at_x); }
 };
 struct SearchBatch {
     int set, n;                                // first set and number of alphas of the loss
     int next_set, next_n;                      // of the preparation
     const float *next_factors;                 // [next_n][K]
+    int next_pieces;                           // beside single losses: of that preparation
 };
 constexpr int SEARCH_X_OCTS = 4096;            // 8-element pieces of x per workgroup of the preparation
 
@@ -98,7 +106,7 @@ int prepare_pieces(int T, int N, int K, int n)
     return n * (((N + 255) / 256) * ((K + 255) / 256) + (int)(((long)T * (K / 8) + SEARCH_X_OCTS - 1) / SEARCH_X_OCTS));
 }
 
-// PREP (0 or the group size): the workgroups behind the `losses` of the grid prepare the next alpha, one piece each.
+// PREP (0 or the group size): the workgroups behind the `losses` of the grid prepare the next alpha.
 template <bool G32, bool CODE, int PREP>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
 loss_tile_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, const h16 *__restrict__ w,
@@ -113,7 +121,8 @@ loss_tile_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, cons
     if constexpr (PREP != 0) {
         static_assert(sizeof(QuantizeTile<PREP, 512>) <= sizeof(lds), "the quantiser's LDS fits the ring");
         if ((int)blockIdx.x >= losses) {
-            prepare_piece<PREP>(blockIdx.x - losses, M, N, K, x, w, sets, batch.next_set, batch.next_n, batch.next_factors, lds);
+            for (int i = (int)blockIdx.x - losses; i < batch.next_pieces; i += (int)gridDim.x - losses)
+                prepare_piece<PREP>(i, M, N, K, x, w, sets, batch.next_set, batch.next_n, batch.next_factors, lds);
             return;
         }
     }
@@ -425,12 +434,16 @@ void launch_loss_tile(int M, int N, int K, int group, const void *x, const void 
                                                                            packed, (const h16 *)scales, zeros, partials, SearchSets(), SearchBatch());
 }
 
-// The loss of one alpha (set b.set) beside the preparation of the next.
+// The loss of one alpha (set b.set) beside the preparation of the next, whose workgroups are as many as the loss leaves
+// compute units idle and take its pieces in turn (one workgroup per piece: 3 % more per alpha on
+// 512 x 4096 x 4096 in groups of 64).
 template <int G>
-void launch_loss_and_next(int M, int N, int K, int group, const void *x, const void *w, const SearchSets &sets, const SearchBatch &b, double *partials,
+void launch_loss_and_next(int M, int N, int K, int group, const void *x, const void *w, const SearchSets &sets, SearchBatch b, double *partials,
                           hipStream_t st)
 {
-    loss_tile_kernel<G == 32, true, G><<<loss_tiles(M, N) + prepare_pieces(M, N, K, b.next_n), 512, 0, st>>>(
+    const int losses = loss_tiles(M, N), idle = sqp_compute_units() - losses % sqp_compute_units();
+    b.next_pieces = prepare_pieces(M, N, K, b.next_n);
+    loss_tile_kernel<G == 32, true, G><<<losses + (b.next_pieces < idle ? b.next_pieces : idle), 512, 0, st>>>(
         M, N, K, group, (const h16 *)x, (const h16 *)w, sets.x_hat(b.set), sets.packed(b.set), sets.scales(b.set), sets.zeros(b.set), partials, sets, b);
 }
 
@@ -814,6 +827,15 @@ loss_pair_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, cons
             (red[tid][0] + red[tid][1]) + (red[tid][2] + red[tid][3]);
 }
 
+// The weight of set `i` in the caller's own buffers.
+__global__ void __launch_bounds__(256) copy_to_own_kernel(SearchSets sets, int i, long packed16, long scales16, long zeros8)
+{
+    const long at = (long)blockIdx.x * 256 + threadIdx.x;
+    if (at < packed16) reinterpret_cast<uint4 *>(sets.own.packed)[at] = reinterpret_cast<const uint4 *>(sets.packed(i))[at];
+    if (at < scales16) reinterpret_cast<uint4 *>(sets.own.scales)[at] = reinterpret_cast<const uint4 *>(sets.scales(i))[at];
+    if (at < zeros8) reinterpret_cast<uint2 *>(sets.own.zeros)[at] = reinterpret_cast<const uint2 *>(sets.zeros(i))[at];
+}
+
 // Preparation of batch.next_n alphas; the losses of batch.n alphas beside the preparation of next_n others.
 template <int G>
 void launch_prepare(int T, int N, int K, const void *x, const void *w, const SearchSets &sets, const SearchBatch &b, hipStream_t st)
@@ -1106,35 +1128,84 @@ static int search_sets_wanted(int T, int N, int K, int group, int n_alpha)
     return (size_t)want <= most ? want : (most > 4 ? (int)most : (want < 4 ? want : 4));
 }
 
-// The losses of all alphas and the argmin, everything in `region` (amax is given).
-static int search_all(int T, int N, int K, int group, int n_alpha, const float *alphas, const void *x_cal, const void *w, const float *amax,
-                      void *region, const SearchRoom &room, double *loss, int *best, hipStream_t st)
+// Alphas per launch, and whether the next ones are prepared beside their losses; own: the caller's buffers serve as a
+// set beside the `sets` of the region.
+struct SearchPlan {
+    int batch;
+    bool beside;
+};
+static SearchPlan search_plan(int T, int N, int K, int group, int n_alpha, int sets, bool own)
 {
-    unsigned char *const base = (unsigned char *)region;
-    const size_t blocks = (size_t)sqp_quant_loss_scratch_doubles(T, N);
-    float *factors = (float *)base;
-    double *tile_sums = (double *)(base + room.at_sums);
-    SearchSets sets = room.layout;
-    sets.base = base + room.at_sets;
-    int rc = sqp_smooth_factors(K, n_alpha, alphas, amax, factors, st);
-    if (rc != SQP_OK) return rc;
     // Sets for two batches: the next one is prepared beside the losses.  With two or three sets, single losses beside
     // the next alpha's preparation where the tiles leave room for that (90 us per alpha on 512 x 5120 x 5120),
     // pairs behind the preparation of both otherwise (95 there, but 113 against 135 with 66 tiles and K = 7808).
-    // One set, or one alpha: the kernel for one.
-    int batch = search_batch(T, N, n_alpha);
+    // One set, or one alpha: the kernel for one.  One set and the caller's own: single losses beside the next
+    // alpha's preparation where the loss leaves at least a quarter of the chip idle (88 us per alpha on 512 x 5120 x
+    // 5120 against 108 one after the other); no set: the caller's own, one alpha after the other.
+    SearchPlan p = {search_batch(T, N, n_alpha), false};
     const bool tiled = prepares_in_tiles(group);
-    bool beside = tiled && batch < n_alpha && room.sets >= 4;
-    if (beside) {
-        batch = 2 * batch <= room.sets ? batch : room.sets / 4 * 2;
+    const long tiles = loss_tiles(T, N), cus = sqp_compute_units();
+    p.beside = tiled && p.batch < n_alpha && sets >= 4;
+    if (p.beside) {
+        p.batch = 2 * p.batch <= sets ? p.batch : sets / 4 * 2;
     } else {
-        batch = batch <= room.sets ? batch : room.sets;
-        const long tiles = loss_tiles(T, N), cus = sqp_compute_units();
-        if (tiled && batch < n_alpha && room.sets >= 2 && 16 * tiles > 7 * cus && 16 * tiles <= 13 * cus) batch = 1, beside = true;
+        p.batch = p.batch <= sets ? p.batch : sets;
+        if (tiled && p.batch < n_alpha && sets >= 2 && 16 * tiles > 7 * cus && 16 * tiles <= 13 * cus) p.batch = 1, p.beside = true;
     }
+    // (Two sets: pairs in turn lose with short K, 1.06 times on 128 x 1024 x 1024.)
+    const bool idle = 4 * (cus - tiles) >= cus;
+    if (own && (p.batch <= 1 || n_alpha == 1 || (tiled && idle && sets == 2 && K <= 2048))) {
+        p.beside = tiled && n_alpha > 1 && (p.beside || (sets >= 1 && idle));
+        p.batch = 1;
+    }
+    return p;
+}
+
+// Whether the region holds the factors and the tile sums.
+static bool search_fits(int T, int N, int n_alpha, const SearchRoom &room, size_t bytes)
+{
+    return room.at_sets > 0 && room.at_sums + (size_t)n_alpha * sqp_quant_loss_scratch_doubles(T, N) * sizeof(double) <= bytes;
+}
+
+// Test hook: sets that fit a region of this size (-1: not even the factors and sums), alphas per launch (0: none) and
+// whether the next ones are prepared beside them; bytes 0: sqp_alpha_search's own region.  Host arithmetic only.
+extern "C" void sqp_debug_search_plan(int T, int N, int K, int group, int n_alpha, size_t bytes, int *out3)
+{
+    const bool own = bytes == 0;
+    if (own) bytes = (size_t)K * N * sizeof(h16);
+    const SearchRoom room = search_room(T, N, K, group, n_alpha, bytes);
+    const bool fits = search_fits(T, N, n_alpha, room, bytes);
+    const SearchPlan p = fits && (own || room.sets) ? search_plan(T, N, K, group, n_alpha, room.sets, own) : SearchPlan{0, false};
+    out3[0] = fits ? room.sets : -1;
+    out3[1] = p.batch;
+    out3[2] = p.beside;
+}
+
+// The losses of all alphas and the argmin, everything in `region` (amax is given).  With sets.own (sqp_alpha_search) its
+// weight is the last alpha's at the end, and it serves as a set where the losses are computed one by one.
+static int search_all(int T, int N, int K, int group, int n_alpha, const float *alphas, const void *x_cal, const void *w, const float *amax,
+                      void *region, const SearchRoom &room, SearchSets sets, double *loss, int *best, hipStream_t st)
+{
+    unsigned char *const base = (unsigned char *)region;
+    const size_t blocks = (size_t)sqp_quant_loss_scratch_doubles(T, N);
+    const bool own = sets.own.packed != nullptr;
+    float *factors = (float *)base;
+    double *tile_sums = (double *)(base + room.at_sums);
+    sets.base = base + room.at_sets;
+    int rc = sqp_smooth_factors(K, n_alpha, alphas, amax, factors, st);
+    if (rc != SQP_OK) return rc;
+    const SearchPlan plan = search_plan(T, N, K, group, n_alpha, room.sets, own);
+    const int batch = plan.batch;
+    const bool beside = plan.beside;
+    const bool tiled = prepares_in_tiles(group);
+    // the first set of the batch that starts with alpha i (single losses: the last alpha gets the caller's set)
+    auto set_of = [&](int i) {
+        if (own && batch == 1) return beside && (n_alpha - 1 - i) % 2 ? 0 : OWN_SET;
+        return beside && i / batch % 2 ? batch : 0;
+    };
     auto prepare = [&](int first, int n, int set) {
-        if (tiled) {
-            const SearchBatch b = {0, 0, set, n, factors + (size_t)first * K};
+        if (tiled && n > 1) {
+            const SearchBatch b = {0, 0, set, n, factors + (size_t)first * K, 0};
 #define SQP_PREPARE(G) launch_prepare<G>(T, N, K, x_cal, w, sets, b, st)
             SQP_BY_GROUP(SQP_PREPARE)
 #undef SQP_PREPARE
@@ -1146,20 +1217,20 @@ static int search_all(int T, int N, int K, int group, int n_alpha, const float *
                                     sets.scales(set + i), sets.zeros(set + i), st);
         return e;
     };
-    for (int i = 0, half = 0; i < n_alpha && rc == SQP_OK; i += batch, half ^= beside ? 1 : 0) {
+    for (int i = 0; i < n_alpha && rc == SQP_OK; i += batch) {
         const int n = n_alpha - i < batch ? n_alpha - i : batch, after = n_alpha - i - n < batch ? n_alpha - i - n : batch;
-        const int set = half * batch;
+        const int set = set_of(i), next = set_of(i + n);
         if (!beside || i == 0) rc = prepare(i, n, set);
         if (rc != SQP_OK) break;
         if (n == 1 && beside && after > 0) {
-            const SearchBatch b = {set, 1, (half ^ 1) * batch, after, factors + (size_t)(i + n) * K};
+            const SearchBatch b = {set, 1, next, after, factors + (size_t)(i + n) * K, 0};
 #define SQP_LOSS_NEXT(G) launch_loss_and_next<G>(T, N, K, group, x_cal, w, sets, b, tile_sums + i * blocks, st)
             SQP_BY_GROUP(SQP_LOSS_NEXT)
 #undef SQP_LOSS_NEXT
         } else if (n == 1) {
             launch_loss_tile<true>(T, N, K, group, x_cal, w, sets.x_hat(set), sets.packed(set), sets.scales(set), sets.zeros(set), tile_sums + i * blocks, st);
         } else {
-            const SearchBatch b = {set, n, beside ? (half ^ 1) * batch : 0, beside ? after : 0, factors + (size_t)(i + n) * K};
+            const SearchBatch b = {set, n, beside ? next : 0, beside ? after : 0, factors + (size_t)(i + n) * K, 0};
 #define SQP_PAIRS(G) launch_loss_pairs<G>(T, N, K, group, x_cal, w, sets, b, tile_sums + i * blocks, st)
             SQP_BY_GROUP(SQP_PAIRS)
 #undef SQP_PAIRS
@@ -1168,6 +1239,11 @@ static int search_all(int T, int N, int K, int group, int n_alpha, const float *
     if (rc != SQP_OK) return rc;
     sum_partials_kernel<<<n_alpha, 256, 0, st>>>(tile_sums, (long)blocks, loss);
     argmin_kernel<<<1, 64, 0, st>>>(loss, n_alpha, best);
+    if (own && batch > 1) {  // (a copy: 6 us on 5120 x 5120, where preparing the weight takes 21)
+        const long packed16 = (long)K / 32 * N, scales16 = (long)(K / group) * (N / 8);  // (N % 8 == 0, K % 64 == 0)
+        copy_to_own_kernel<<<(unsigned)((packed16 + 255) / 256), 256, 0, st>>>(sets, set_of((n_alpha - 1) / batch * batch) + (n_alpha - 1) % batch,
+                                                                                packed16, scales16, scales16);
+    }
     return sqp_launch_status();
 }
 
@@ -1194,14 +1270,17 @@ extern "C" int sqp_alpha_search(int T, int N, int K, int group, int n_alpha, con
     hipStream_t st = (hipStream_t)stream;
     rc = sqp_channel_absmax(T, K, N, x_cal, w, amax, st);
     if (rc != SQP_OK) return rc;
-    // The factors, the tile sums and the prepared operands live in w_s, which the search otherwise fills with
-    // the smoothed weight: here the quantisation smooths the weight as it reads it, and the last alpha's values
-    // are put into the caller's buffers at the end.  Shapes that do not fit there run the single calls in turn.
-    const SearchRoom room = search_room(T, N, K, group, n_alpha, (size_t)K * N * sizeof(h16));
-    if (room.sets > 0) {
-        rc = search_all(T, N, K, group, n_alpha, alphas, x_cal, w, amax, w_s, room, loss, best, st);
+    // The factors, the tile sums and as many sets of prepared operands as fit beside them live in w_s, which the search
+    // otherwise fills with the smoothed weight: here the quantisation smooths the weight as it reads it, and x_hat
+    // and w_s get the last alpha's values at the end.  Layers too narrow for the factors and sums run the
+    // single calls in turn.
+    const size_t bytes = (size_t)K * N * sizeof(h16);
+    const SearchRoom room = search_room(T, N, K, group, n_alpha, bytes);
+    if (search_fits(T, N, n_alpha, room, bytes)) {
+        SearchSets sets = room.layout;
+        sets.own = {packed, (h16 *)scales, zeros, (h16 *)x_hat};
+        rc = search_all(T, N, K, group, n_alpha, alphas, x_cal, w, amax, w_s, room, sets, loss, best, st);
         if (rc == SQP_OK) rc = sqp_smooth_factor(K, alphas[n_alpha - 1], amax, s, st);
-        if (rc == SQP_OK) rc = sqp_smooth_quantize(T, N, K, group, x_cal, w, s, x_hat, packed, scales, zeros, st);
         if (rc == SQP_OK) rc = sqp_smooth_apply_x(T, K, x_cal, s, x_hat, stream);  // (not in code order)
         if (rc == SQP_OK) rc = sqp_smooth_apply_w(K, N, w, s, w_s, stream);
         return rc;
@@ -1259,7 +1338,7 @@ extern "C" int sqp_alpha_search_scratch(int T, int N, int K, int group, int n_al
         const SearchRoom room = search_room(T, N, K, group, n_alpha, scratch_bytes < head ? 0 : scratch_bytes - head);
         if (room.sets == 0) return SQP_ERR_WORKSPACE;
         const int e = sqp_channel_absmax(T, K, N, x_cal, w, (float *)base, (hipStream_t)stream);
-        return e != SQP_OK ? e : search_all(T, N, K, group, n_alpha, alphas, x_cal, w, (float *)base, base + head, room, loss, best, (hipStream_t)stream);
+        return e != SQP_OK ? e : search_all(T, N, K, group, n_alpha, alphas, x_cal, w, (float *)base, base + head, room, room.layout, loss, best, (hipStream_t)stream);
     }
     if (scratch_bytes < single_calls_bytes(T, N, K, group)) return SQP_ERR_WORKSPACE;
     size_t at = 0;

@@ -156,6 +156,11 @@ def test_alpha_search_equals_single_calls(orc, sqp):
     (1, 768, 136, 384, 3),     # a group size whose quantise kernel reads twice
     (200, 1152, 328, 32, 3),   # two groups per stage
     (130, 384, 136, 32, 3),
+    (512, 512, 640, 128, 3), (512, 512, 640, 128, 1), (400, 768, 264, 384, 2),  # no set beside the caller's own buffers
+    (512, 512, 2048, 128, 4), (512, 512, 2048, 64, 3), (512, 512, 2048, 32, 1),  # one: alternating with the caller's own
+    (1024, 128, 4096, 128, 3), (256, 768, 1032, 384, 3),  # one, nothing beside
+    (513, 128, 4000, 64, 4),   # 160 tiles
+    (512, 2048, 4096, 64, 3),  # more pieces of preparation than idle compute units
     (130, 384, 8, 32, 4),      # N too narrow for w_s to hold the factors: single calls in turn
     (70, 192, 72, 64, 3), (5, 64, 16, 64, 2),  # three stages, one stage
     (70, 240, 72, 40, 3)])     # K not a multiple of 64: the loss kernel for any group

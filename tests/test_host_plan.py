@@ -354,3 +354,19 @@ def test_row_blocks_take_whole_groups_only(L):
         finally:
             L.sqp_debug_set_row_blocks(0, 0, 0)
     assert taken > len(shapes)
+
+
+@pytest.mark.parametrize("T,K,N,group,n,plan", [
+    (512, 4096, 2048, 128, 21, (1, 1, 1)),   # one set beside the caller's own: the next alpha prepared beside the loss
+    (512, 4096, 640, 128, 21, (0, 1, 0)),    # none: the fused search one alpha after the other in the caller's own buffers
+    (1024, 128, 4096, 128, 3, (1, 1, 0)),    # 256 tiles leave no room beside them
+    (512, 5120, 5120, 128, 1, (2, 1, 0)),    # one alpha
+    (512, 5120, 5120, 128, 21, (2, 1, 1)),   # two sets, 160 tiles: singles beside
+    (64, 4096, 4096, 32, 21, (3, 3, 0)), (33, 2304, 520, 128, 4, (3, 3, 0)), (33, 2304, 2304, 64, 4, (3, 3, 0)),  # pairs in turn
+    (128, 1024, 1024, 128, 21, (2, 1, 1)), (512, 2048, 4096, 64, 3, (2, 1, 1)),  # short K: singles
+    (130, 384, 8, 32, 4, (-1, 0, 0)), (70, 240, 72, 40, 3, (-1, 0, 0))])  # single calls in turn
+def test_alpha_search_plan_in_its_own_buffers(L, T, K, N, group, n, plan):
+    """What sqp_alpha_search makes of the buffers that its callers have handed over since before it kept several sets."""
+    out = (ctypes.c_int * 3)()
+    L.sqp_debug_search_plan(T, N, K, group, n, ctypes.c_size_t(0), out)
+    assert tuple(out) == plan
