@@ -779,6 +779,7 @@ static SqpStripPlan row_blocks_plan(int M, int N, int K, int group, int cus, dou
     };
     SqpStripPlan best = {2, 1, 2, 1, 0};
     if (M <= 64 || !row_blocks_cover(K, group)) return best;
+    if ((long)((N + 127) / 128) * ((M + 63) / 64) > 2 * cus) return best;  // (no launch below fits: long prompts end here)
     const int chunks = K / 128;
     double least = (tiles_us + 6.7) / 1.08;
     for (int mt = 3; mt <= 4; mt++) {
@@ -835,16 +836,17 @@ extern "C" void sqp_debug_row_blocks(int M, int N, int K, int group, int cus, in
     out3[2] = p.kp;
 }
 
-// Bytes the tiled launches of a call leave in its workspace (0: it reports none and never touches it).
-static size_t tiles_bytes(int M, int N, int K, int group)
+// The launches with as large a workspace as they like.  The bytes they leave there are 0 for shapes that report
+// none and never touch it.
+static LaunchPlan preferred_launches(int M, int N, int K, int group)
 {
-    return plan_partial_bytes(plan_launches(M, N, K, group, sqp_compute_units(), SIZE_MAX, 0));
+    return plan_launches(M, N, K, group, sqp_compute_units(), SIZE_MAX, 0);
 }
 
 size_t sqp_gemm_prefill_partial_bytes(int M, int N, int K, int group)
 {
     if (!tiled_covers(K, group)) return most_of_row_blocks(sqp_gemm_decode_partial_bytes, M, N, K, group);
-    const LaunchPlan q = plan_launches(M, N, K, group, sqp_compute_units(), SIZE_MAX, 0);
+    const LaunchPlan q = preferred_launches(M, N, K, group);
     const size_t tiles = plan_partial_bytes(q);
     if (tiles == 0 && g_row_blocks.mt <= 0) return 0;  // (a forced plan says what it needs)
     const size_t rows = row_blocks_bytes(row_blocks_for(q, M, N, K, group, sqp_compute_units(), SIZE_MAX), M, N, K);
@@ -855,19 +857,24 @@ size_t sqp_gemm_prefill_scratch_bytes(int M, int N, int K, int group)
 {
     if (!tiled_covers(K, group)) return 0;
     const LaunchPlan q = plan_launches(M, N, K, group, sqp_compute_units(), SIZE_MAX, SIZE_MAX);
-    return q.own ? plan_partial_bytes(q) : 0;
+    return q.own ? plan_partial_bytes(q) : 0;  // (also where row blocks run and leave it untouched: 1 shape in 200)
 }
 
 // What a workspace has to hold at least for a call not to be refused: the K parts of the plan in 128-row
 // tiles as [parts][M][N].  With less than the preferred plan's bytes, one that fits runs, of row blocks too.
+// tiles: bytes of the preferred launches.
+static size_t least_bytes(size_t tiles, int M, int N, int K, int group)
+{
+    if (g_force_rt > 0 || tiles == 0) return tiles;
+    const TilePlan p = plan_tiles(M, N, K, group, sqp_compute_units(), true);
+    const size_t base = p.ksplit >= 2 ? (size_t)p.ksplit * M * N * sizeof(float) : 0;
+    return base < tiles ? base : tiles;
+}
+
 size_t sqp_gemm_prefill_least_bytes(int M, int N, int K, int group)
 {
     if (!tiled_covers(K, group)) return most_of_row_blocks(sqp_gemm_decode_least_bytes, M, N, K, group);
-    const size_t want = tiles_bytes(M, N, K, group);
-    if (g_force_rt > 0) return want;
-    const TilePlan p = plan_tiles(M, N, K, group, sqp_compute_units(), true);
-    const size_t base = p.ksplit >= 2 ? (size_t)p.ksplit * M * N * sizeof(float) : 0;
-    return base < want ? base : want;
+    return least_bytes(plan_partial_bytes(preferred_launches(M, N, K, group)), M, N, K, group);
 }
 
 template <int RT, int NT, int WM, bool G32>
@@ -884,13 +891,17 @@ int sqp_gemm_prefill(int M, int N, int K, int group, const h16 *x, const uint32_
     if (!tiled_covers(K, group))
         return decode_in_row_blocks(M, N, K, group, x, packed, scales, zeros, y, epi, ws, stream);
     const size_t room_ws = ws.partial ? ws.partial_bytes : 0, room_own = ws.own ? ws.own_bytes : 0;
-    if (room_ws > 0 && room_ws < sqp_gemm_prefill_least_bytes(M, N, K, group)) return SQP_ERR_WORKSPACE;
-    const LaunchPlan q = plan_launches(M, N, K, group, sqp_compute_units(), room_ws, room_own);
+    // The preferred launches are looked for once: they are what runs wherever their parts fit the workspace, unless
+    // the call brings scratch for a shape that has no parts there.
+    LaunchPlan q = preferred_launches(M, N, K, group);
+    const size_t reported = plan_partial_bytes(q);
+    if (room_ws > 0 && room_ws < least_bytes(reported, M, N, K, group)) return SQP_ERR_WORKSPACE;
+    if (q.own ? room_own > 0 : room_ws < reported) q = plan_launches(M, N, K, group, sqp_compute_units(), room_ws, room_own);
     float *const part = q.own ? ws.own : ws.partial;
     if (plan_partial_bytes(q) > (q.own ? room_own : room_ws)) return SQP_ERR_WORKSPACE;
     // Parts of row blocks go to the workspace where the shape reports one: the others may run beside calls that
     // use it.
-    const size_t limit = room_ws > 0 && ws.tickets && tiles_bytes(M, N, K, group) > 0 ? room_ws : 0;
+    const size_t limit = room_ws > 0 && ws.tickets && reported > 0 ? room_ws : 0;
     const SqpStripPlan rows = row_blocks_for(q, M, N, K, group, sqp_compute_units(), limit);
     if (rows.mt) return sqp_strip_row_blocks(group, rows, M, N, K, group <= 128 ? 1 : group / 128, x, packed, scales, zeros, y, epi, ws, stream);
     for (int i = 0; i < q.count; i++) {
