@@ -361,7 +361,8 @@ def test_workspace_between_least_and_preferred(orc, sqp, M, K, N, group):
 @pytest.mark.parametrize("M,K,N,group,fused", [(2050, 2048, 8144, 128, 0), (660, 2048, 5184, 64, 1)])
 def test_scratch_of_one_call(orc, sqp, M, K, N, group, fused):
     """Grids that fill the chip: no workspace asked for and none touched; with a scratch buffer of the
-    call's own the K parts stay inside it, whatever its size; a misaligned one is refused."""
+    call's own the K parts stay inside it, whatever its size; a misaligned one is refused.  (Without row
+    blocks, which one of the shapes takes and which leave the scratch untouched.)"""
     print("case scratch", M, K, N, group, fused, flush=True)
     L = sqp.lib()
     want = int(L.sqp_w4a16_gemm_scratch_bytes(M, N, K, group))
@@ -376,6 +377,7 @@ def test_scratch_of_one_call(orc, sqp, M, K, N, group, fused):
     call = lambda own, size: L.sqp_w4a16_gemm_scratch(M, N, K, group, fused, _ptr(dx), _ptr(dp), _ptr(dsc), _ptr(dz), y.ptr, own,
                                                       ctypes.c_size_t(size), st)
     outs = []
+    L.sqp_debug_set_row_blocks(-1, 0, 0)
     try:
         _set_ws(L, ws.ptr, 1 << 20)
         torch.cuda.synchronize()
@@ -405,6 +407,7 @@ def test_scratch_of_one_call(orc, sqp, M, K, N, group, fused):
                 assert bool((d <= 4 * 2.0 ** -11 * h.abs() + 2.0 ** -10 * gu[:, 1::2].abs() * gu[:, 0::2].abs() + 1e-3).all())
         assert call(ctypes.c_void_p(own.raw.data_ptr() + GUARD + 8), want) == -3
     finally:
+        L.sqp_debug_set_row_blocks(0, 0, 0)
         torch.cuda.synchronize()
         sqp.set_workspace(0)
 
