@@ -174,6 +174,9 @@ int chunk_ksteps(int K, int group)
     return group == 32 ? 1 : (group == 64 ? 2 : 0);
 }
 
+// A test hook that forces a plan by strips keeps a call from the column slices.
+bool strips_forced() { return g_force_plan.nw > 0 || g_force_split > 0; }
+
 }  // namespace
 
 extern "C" void sqp_debug_set_decode_split(int split) { g_force_split = split; }
@@ -230,6 +233,7 @@ static SqpSlicePlan slice_plan(int M, int N, int K, int group)
     if (g_slice_mode < 0 || M > 32 || (group != 32 && group != 64 && group % 128 != 0)) return none;
     if (g_slice_plan.tb > 0) return g_slice_plan;
     if (g_slice_mode > 0) return SqpSlicePlan{2 * g_slice_mode, 8, false};
+    if (strips_forced()) return none;
     const int blocks = M > 16 ? 4 : (M + 3) / 4 - 1;  // blocks of four rows less one; 17 to 32 rows
     constexpr int ANY = 1 << 28;
     static const struct { int columns, longest[5]; } lengths[8] = {
@@ -265,7 +269,7 @@ static SqpSlicePlan slice_plan(int M, int N, int K, int group)
 static bool slices_alone(int M, int N, int K, int group)
 {
     if (g_slice_mode < 0) return false;
-    return g_slice_plan.tb > 0 || g_slice_mode > 0 ? slice_plan(M, N, K, group).tb > 0 : slice_variant(M, N, K, group) >= 0;
+    return g_slice_plan.tb > 0 || g_slice_mode > 0 || strips_forced() ? slice_plan(M, N, K, group).tb > 0 : slice_variant(M, N, K, group) >= 0;
 }
 
 extern "C" void sqp_debug_decode_slice_plan(int M, int N, int K, int group, int *tb, int *wv)

@@ -220,6 +220,17 @@ def test_gemm_outputs_between_guards(orc, sqp, M, K, N, group, with_ws):
         sqp.set_workspace(0)   # through the binding, so that it knows no workspace is set any more
 
 
+@pytest.mark.parametrize("M,K,N,group", [(65, 256, 264, 128), (130, 384, 72, 64), (300, 1024, 520, 128), (100, 128, 64, 32)])
+@pytest.mark.parametrize("with_ws", [True, False])
+def test_tiled_gemm_outputs_between_guards(orc, sqp, M, K, N, group, with_ws):
+    """The same in the tiled kernel, on shapes that the rule gives to the strip kernel's row blocks."""
+    sqp.lib().sqp_debug_set_row_blocks(-1, 0, 0)
+    try:
+        test_gemm_outputs_between_guards(orc, sqp, M, K, N, group, with_ws)
+    finally:
+        sqp.lib().sqp_debug_set_row_blocks(0, 0, 0)
+
+
 @pytest.mark.parametrize("mode", [1, 2])
 @pytest.mark.parametrize("M,K,N", [(1, 256, 8), (5, 512, 72), (9, 1152, 200), (16, 2048, 328), (13, 128, 1032), (4, 128 * 9, 48)])
 def test_slice_kernel_outputs_between_guards(orc, sqp, M, K, N, mode):
@@ -356,6 +367,16 @@ def test_workspace_between_least_and_preferred(orc, sqp, M, K, N, group):
     finally:
         torch.cuda.synchronize()
         sqp.set_workspace(0)
+
+
+@pytest.mark.parametrize("M,K,N,group", [(65, 2048, 520, 128), (130, 1024, 264, 32), (150, 1536, 1032, 256)])
+def test_workspace_between_least_and_preferred_in_tiles(orc, sqp, M, K, N, group):
+    """The same for the tiled kernel's parts, on shapes that the rule gives to the strip kernel's row blocks."""
+    sqp.lib().sqp_debug_set_row_blocks(-1, 0, 0)
+    try:
+        test_workspace_between_least_and_preferred(orc, sqp, M, K, N, group)
+    finally:
+        sqp.lib().sqp_debug_set_row_blocks(0, 0, 0)
 
 
 @pytest.mark.parametrize("M,K,N,group,fused", [(2050, 2048, 8144, 128, 0), (660, 2048, 5184, 64, 1)])

@@ -370,3 +370,20 @@ def test_alpha_search_plan_in_its_own_buffers(L, T, K, N, group, n, plan):
     out = (ctypes.c_int * 3)()
     L.sqp_debug_search_plan(T, N, K, group, n, ctypes.c_size_t(0), out)
     assert tuple(out) == plan
+
+
+def test_forced_strips_are_strips(L):
+    """A forced plan by strips, or a forced split, is what a call launches and reports, also where the rule takes column
+    slices: tests that force one mean the strip kernel."""
+    tb, wv = ctypes.c_int(), ctypes.c_int()
+    for M, N, K, g in [(16, 328, 2048, 128), (7, 1032, 1024, 128), (20, 264, 512, 64), (1, 12288, 4096, 128)]:
+        L.sqp_debug_decode_slice_plan(M, N, K, g, ctypes.byref(tb), ctypes.byref(wv))
+        assert tb.value > 0
+        for force, reset in ((lambda: L.sqp_debug_set_decode_plan(2, 2), lambda: L.sqp_debug_set_decode_plan(0, 0)),
+                             (lambda: L.sqp_debug_set_decode_split(2), lambda: L.sqp_debug_set_decode_split(0))):
+            force()
+            try:
+                L.sqp_debug_decode_slice_plan(M, N, K, g, ctypes.byref(tb), ctypes.byref(wv))
+                assert tb.value == 0 and L.sqp_w4a16_gemm_workspace_bytes(M, N, K, g) > 512 << 10
+            finally:
+                reset()
