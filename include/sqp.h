@@ -224,10 +224,11 @@ int sqp_alpha_search(int T, int N, int K, int group, int n_alpha, const float *a
  * The losses are those of sqp_alpha_search, bit for bit.
  *   scratch  device, 16-byte aligned, overwritten; nothing in it is needed before or after the call
  *   scratch_bytes  sqp_alpha_search_scratch_bytes() for the preferred plan; with less a plan that fits
- *                  runs, and where not even one alpha's operands fit the call is refused with
- *                  SQP_ERR_WORKSPACE, nothing enqueued
- * sqp_alpha_search_scratch_bytes: host arithmetic only, 0 for invalid arguments. */
+ *                  runs, and below sqp_alpha_search_scratch_least_bytes(), where not even one alpha's
+ *                  operands fit, the call is refused with SQP_ERR_WORKSPACE, nothing enqueued
+ * The two sizes: host arithmetic only, 0 for invalid arguments. */
 size_t sqp_alpha_search_scratch_bytes(int T, int N, int K, int group, int n_alpha);
+size_t sqp_alpha_search_scratch_least_bytes(int T, int N, int K, int group, int n_alpha);
 int sqp_alpha_search_scratch(int T, int N, int K, int group, int n_alpha, const float *alphas, const void *x_cal,
                              const void *w, void *scratch, size_t scratch_bytes, double *loss, int *best, void *stream);
 

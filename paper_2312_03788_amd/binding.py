@@ -60,6 +60,8 @@ def lib():
         L.sqp_alpha_search_scratch.argtypes = [i, i, i, i, i, ctypes.POINTER(ctypes.c_float), vp, vp, vp, ctypes.c_size_t, vp, vp, vp]
         L.sqp_alpha_search_scratch_bytes.argtypes = [i, i, i, i, i]
         L.sqp_alpha_search_scratch_bytes.restype = ctypes.c_size_t
+        L.sqp_alpha_search_scratch_least_bytes.argtypes = [i, i, i, i, i]
+        L.sqp_alpha_search_scratch_least_bytes.restype = ctypes.c_size_t
         L.sqp_w4a16_gemm_workspace_bytes.argtypes = [i, i, i, i]
         L.sqp_w4a16_gemm_workspace_bytes.restype = ctypes.c_size_t
         L.sqp_w4a16_gemm_workspace_least_bytes.argtypes = [i, i, i, i]
@@ -393,6 +395,20 @@ def quant_loss(x, w, x_hat, packed, scales, zeros, group=128, out=None):
     return o
 
 
+def _search_scratch(T, N, K, group, n, device):
+    """Scratch of a search: the preferred size (up to 1 GB, or four alphas' operands), or half of it as often as that
+    does not fit the device's memory, down to one alpha's operands."""
+    nbytes = max(int(lib().sqp_alpha_search_scratch_bytes(T, N, K, group, n)), 16)
+    while True:
+        try:
+            return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        except torch.cuda.OutOfMemoryError:
+            least = int(lib().sqp_alpha_search_scratch_least_bytes(T, N, K, group, n))
+            if nbytes <= least:
+                raise
+            nbytes = max(least, nbytes // 2)
+
+
 def alpha_search(x_cal, w, group=128, alphas=None):
     """Single-layer search for the smoothing strength (Sec 2.2) through sqp_alpha_search_scratch: the
     per-channel maxima once, then Eq. 6 -> Eq. 5 -> Eq. 1 -> Eq. 4 per alpha and the argmin, all
@@ -407,8 +423,7 @@ def alpha_search(x_cal, w, group=128, alphas=None):
     dev = w.device
     n = len(alphas)
     host_alphas = (ctypes.c_float * n)(*[float(a) for a in alphas])
-    nbytes = int(L.sqp_alpha_search_scratch_bytes(T, N, K, group, n))
-    scratch = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=dev)
+    scratch = _search_scratch(T, N, K, group, n, dev)
     loss = torch.empty(n, dtype=torch.float64, device=dev)
     best = torch.empty(1, dtype=torch.int32, device=dev)
     _check(L.sqp_alpha_search_scratch(T, N, K, group, n, host_alphas, _dev(x_cal, torch.float16, "x_cal"), _dev(w, torch.float16, "w"),

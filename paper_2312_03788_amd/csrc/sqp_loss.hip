@@ -1322,6 +1322,13 @@ extern "C" size_t sqp_alpha_search_scratch_bytes(int T, int N, int K, int group,
     return head + search_bytes(T, N, K, group, n_alpha, search_sets_wanted(T, N, K, group, n_alpha));
 }
 
+extern "C" size_t sqp_alpha_search_scratch_least_bytes(int T, int N, int K, int group, int n_alpha)
+{
+    if (check_search(T, N, K, group, n_alpha) != SQP_OK) return 0;
+    if (!loss_tile_covers(K, group)) return single_calls_bytes(T, N, K, group);
+    return up256((size_t)2 * K * sizeof(float)) + search_bytes(T, N, K, group, n_alpha, 1);
+}
+
 extern "C" int sqp_alpha_search_scratch(int T, int N, int K, int group, int n_alpha, const float *alphas, const void *x_cal, const void *w,
                                         void *scratch, size_t scratch_bytes, double *loss, int *best, void *stream)
 {

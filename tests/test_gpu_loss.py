@@ -214,14 +214,17 @@ def test_alpha_search_scratch_routes(sqp, T, K, N, group, n, sets):
     one = up(K // 8 * N * 4) + up(K // group * N * 2) + up(K // group * N) + up(2 * T * K)
     want = int(L.sqp_alpha_search_scratch_bytes(T, N, K, group, n))
     nbytes = head + sets * one if sets else want
-    assert nbytes <= want or sets
+    least = int(L.sqp_alpha_search_scratch_least_bytes(T, N, K, group, n))
+    if K % 64 == 0:  # whole sets behind the head
+        assert want >= head + one and (want - head) % one == 0 and least == head + one
+    else:
+        assert want == least
     buf = torch.full((nbytes + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
     loss, best = torch.full((n,), -1.0, dtype=torch.float64, device="cuda"), torch.full((1,), -1, dtype=torch.int32, device="cuda")
     ptr = lambda t: ctypes.c_void_p(t.data_ptr())
     run = lambda size: L.sqp_alpha_search_scratch(T, N, K, group, n, (ctypes.c_float * n)(*alphas), ptr(dx), ptr(dw), ptr(buf), size, ptr(loss), ptr(best),
                                                   ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
-    if group % 32 == 0:
-        assert run(head + one - 1) == -6
+    assert run(least - 1) == -6
     torch.cuda.synchronize()
     assert (loss == -1).all() and (buf == 0xA5).all()
     assert run(nbytes) == 0
@@ -232,3 +235,34 @@ def test_alpha_search_scratch_routes(sqp, T, K, N, group, n, sets):
         singles.append(float(host(sqp.quant_loss(dx, dw, sqp.smooth_apply_x(dx, s1), *q1, group))[0]))
     assert list(host(loss)) == singles and int(host(best)[0]) == int(np.argmin(singles))
     assert (buf[nbytes:] == 0xA5).all()
+
+
+@pytest.mark.parametrize("room", [0, 1, 3])
+def test_alpha_search_with_less_memory(sqp, monkeypatch, room):
+    """Where the preferred scratch does not fit the device's memory the search runs in less, down to one alpha's operands:
+    the same losses; where those do not fit it raises."""
+    T, K, N, group = 64, 512, 520, 64
+    _, _, w = wl.layer_inputs(1, K, N)
+    dx, dw = dev(wl.activation(T, K, seed=3000)), dev(w)
+    alphas = [0.0, 0.25, 0.5, 0.75, 1.0]
+    want = sqp.alpha_search(dx, dw, group, alphas)
+    L = sqp.lib()
+    preferred, least = (int(f(T, N, K, group, len(alphas))) for f in (L.sqp_alpha_search_scratch_bytes, L.sqp_alpha_search_scratch_least_bytes))
+    assert preferred > 2 * least
+    limit = least - 1 if room == 0 else room * least
+    empty, refused = torch.empty, []
+
+    def tight(*shape, **kw):
+        if kw.get("dtype") == torch.uint8 and shape[0] > limit:
+            refused.append(shape[0])
+            raise torch.cuda.OutOfMemoryError("out of memory")
+        return empty(*shape, **kw)
+
+    monkeypatch.setattr(torch, "empty", tight)
+    if room == 0:
+        with pytest.raises(torch.cuda.OutOfMemoryError):
+            sqp.alpha_search(dx, dw, group, alphas)
+        assert refused[-1] == least
+    else:
+        assert sqp.alpha_search(dx, dw, group, alphas) == want
+    assert refused[0] == preferred

@@ -387,3 +387,30 @@ def test_forced_strips_are_strips(L):
                 assert tb.value == 0 and L.sqp_w4a16_gemm_workspace_bytes(M, N, K, g) > 512 << 10
             finally:
                 reset()
+
+
+def test_alpha_search_scratch_sizes(L):
+    """The preferred scratch holds two batches of alphas, all of them where one batch does, within 1 GB (or four alphas'
+    operands, where those are more); the least holds one alpha's; both 0 for invalid arguments."""
+    sizes = []
+    for f in (L.sqp_alpha_search_scratch_bytes, L.sqp_alpha_search_scratch_least_bytes):
+        f.restype = ctypes.c_size_t
+        sizes.append(f)
+    up = lambda v: (v + 255) // 256 * 256
+
+    def sets(T, N, K, group, n):
+        head = up(8 * K) + up(4 * n * K) + up(8 * n * (-(-T // 128) * -(-N // 128)))
+        one = up(K // 2 * N) + up(K // group * N * 2) + up(K // group * N) + up(2 * T * K)
+        most, least = (f(T, N, K, group, n) for f in sizes)
+        assert least == head + one and (most - head) % one == 0
+        assert most - head <= max(1 << 30, 4 * one)
+        return (most - head) // one
+    assert sets(512, 5120, 5120, 128, 1) == 1         # one alpha
+    assert sets(512, 5120, 5120, 128, 21) == 16       # two batches of four pairs
+    assert sets(64, 1024, 1024, 128, 4) == 4          # all alphas in one batch
+    big = sets(512, 44032, 8192, 128, 21)             # 198 MB each: the cap
+    assert big in (4, 5)
+    assert sets(4096, 65536, 16384, 128, 21) == 4     # 705 MB each: four all the same
+    for bad in [(0, 8, 8, 8, 1), (8, 8, 64, 64, 0), (8, 12, 64, 64, 1), (8, 8, 64, 48, 1)]:
+        assert [f(*bad) for f in sizes] == [0, 0]
+    assert sizes[0](70, 72, 240, 40, 3) == sizes[1](70, 72, 240, 40, 3) > 0   # single calls
