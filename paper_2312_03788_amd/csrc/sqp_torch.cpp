@@ -17,6 +17,7 @@
 
 #include <ATen/ops/empty.h>
 #include <ATen/ops/empty_cuda_dispatch.h>
+#include <ATen/record_function.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -61,11 +62,11 @@ const at::Tensor *plain(PyObject *o, at::ScalarType type, long dev)
 
 // A new tensor on the device of `like`.  Without dispatch modes, transforms, inference or grad modes that change the
 // thread's dispatch keys the dispatcher ends at the GPU's own `empty`: that is called straight away then
-// (0.7 us of a call of 4 to 5 instead of 0.8).
+// (0.7 us of a call of 4 to 5 instead of 0.8), unless a profiler or another observer records the operators.
 at::Tensor fresh(at::IntArrayRef size, at::ScalarType type, const at::Tensor &like)
 {
     const c10::impl::LocalDispatchKeySet tls = c10::impl::tls_local_dispatch_key_set();
-    if (tls.included_ == c10::default_included_set && tls.excluded_ == c10::default_excluded_set)
+    if (tls.included_ == c10::default_included_set && tls.excluded_ == c10::default_excluded_set && !at::hasCallbacks())
         return at::cuda::empty(size, type, at::kStrided, like.device(), false, c10::nullopt);
     return at::empty(size, like.options().dtype(type));
 }

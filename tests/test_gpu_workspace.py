@@ -614,6 +614,19 @@ def test_native_outputs_under_dispatch_modes(orc, sqp):
     assert not got.is_inference() and not got.requires_grad and torch.equal(got, want)
 
 
+def test_native_outputs_under_a_profiler(sqp):
+    """A profiler's operator records show the allocation of a native call's output, as they show any other operator's."""
+    w = torch.randn((512, 272), device="cuda").half()
+    x = torch.randn((3, 512), device="cuda").half()
+    p, ones = sqp.quantize_pack(w, 128), torch.ones(512, device="cuda")
+    sqp.w4a16_gemm(x, *p, 128)
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU]) as prof:
+        sqp.w4a16_gemm(x, *p, 128)
+        sqp.smooth_apply_w(w, ones)
+    seen = {e.key: e.count for e in prof.key_averages()}
+    assert seen.get("aten::empty", 0) >= 2, seen
+
+
 def test_native_marshalling_reports_the_librarys_code(sqp):
     """A code that the library returns ends in the general path's error after one call: a launch error may
     stem from earlier work while this call's kernels were enqueued, so it neither disappears nor is
