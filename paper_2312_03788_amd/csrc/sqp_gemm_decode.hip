@@ -221,8 +221,8 @@ extern "C" void sqp_debug_set_slice_plan(int tb, int wv, int grouped) { g_slice_
 //   8.5 / 10.5 / 13.0 / 17.4.  From 257 to 320 slices of 64 columns the chip is a round and a little full, and
 //   short K only is worth it (17904 columns, K = 9984, 5 rows: 30.3 against 24.2).  K not a multiple of 128:
 //   the strips take chunks of one group there, so slices pay up to 1.6 times that K, from 8192 columns on
-//   with any.  Above 8192 columns groups of several chunks hold out longer (the strip kernel takes one chunk
-//   per iteration there).
+//   with any.  Above 8192 columns other groups than those of 128 hold out longer (the strip kernel takes one chunk
+//   per iteration with several chunks per group).
 //   The lengths are those with the least time over 6814 calls (1 to 32 rows, N 512 to 44032, K 512 to 22016, groups
 //   of 32 to 384, three in four drawn over these ranges, weights from HBM): 1.27 times faster than without slices
 //   in the geometric mean, 0.4 % behind the better of the two kernels; 1.5 % of the calls are more than 3 % slower
@@ -240,7 +240,7 @@ static SqpSlicePlan slice_plan(int M, int N, int K, int group)
         {2048, {12288, 8192, 7168, 6144, 6144}},
         {4096, {13312, 9728, 8704, 6144, 5632}},
         {8192, {13312, 12288, 9728, 6656, 6144}},
-        {12288, {16384, 13312, 12288, 8704, 8704}},
+        {12288, {16384, 13312, 12288, 7168, 7168}},
         {16384, {ANY, ANY, 20480, 11264, 13312}},
         {20480, {4096, 2560, 2560, 2048, 0}},
         {32768, {16384, 8192, 7680, 4096, 0}},
@@ -251,7 +251,7 @@ static SqpSlicePlan slice_plan(int M, int N, int K, int group)
     double most = lengths[row].longest[blocks];
     if (N > 16384) most *= group == 32 ? 0.85 : (group > 128 ? 2.0 : 1.0);
     else if (N > 8192 && group == 32) most = 11264;
-    else if (N > 8192 && group > 128) most *= 1.3;
+    else if (N > 8192 && M > 12) most *= group == 64 ? 1.3 : (group > 128 ? 1.6 : 1.0);
     if (N > 32768 && M > 16 && K < 1024) most = 0;
     if (K % 128 != 0) most = N <= 8192 ? 1.6 * most : (N <= 32768 || M > 16 ? ANY : 0.75 * most);
     if (K > most && slice_variant(M, N, K, group) < 0) return none;
