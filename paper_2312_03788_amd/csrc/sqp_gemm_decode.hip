@@ -226,7 +226,7 @@ extern "C" void sqp_debug_set_slice_plan(int tb, int wv, int grouped) { g_slice_
 //   The lengths are those with the least time over 6814 calls (1 to 32 rows, N 512 to 44032, K 512 to 22016, groups
 //   of 32 to 384, three in four drawn over these ranges, weights from HBM): 1.27 times faster than without slices
 //   in the geometric mean, 0.4 % behind the better of the two kernels; 1.5 % of the calls are more than 3 % slower
-//   than without slices, at worst 19 % (decode_routes_sweep.md among the profiles).
+//   than without slices, at worst 19 % (the sweep is among the profiles).
 static SqpSlicePlan slice_plan(int M, int N, int K, int group)
 {
     const SqpSlicePlan none = {0, 0, false};
