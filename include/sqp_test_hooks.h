@@ -23,7 +23,8 @@ void sqp_debug_set_decode_kp(int kp);              /* two chunks per iteration (
                                                       2 = where the rules would with enough chunks, 3 = wherever built */
 void sqp_debug_set_decode_slice(int mode);         /* column-slice kernel (M <= 32): 0 = automatic, -1 = never, 1 = always with
                                                       32-column slices, 2 = always with 64-column slices (eight waves) */
-void sqp_debug_set_slice_plan(int tb, int wv, int grouped); /* tb > 0: column slices of 16 tb columns, wv waves, for every call they cover */
+void sqp_debug_set_slice_plan(int tb, int wv, int grouped); /* tb > 0: column slices of 16 tb columns, wv waves (eight where that many are
+                                                      not built for the rows), for every call they cover */
 /* Whether a layer fills the chip with slices of 32 (0) or 64 (1) columns and takes the column-slice kernel for
  * that alone (-1: the launch plan decides by N, K and the group).  Host arithmetic only. */
 int sqp_debug_decode_slice_choice(int M, int N, int K, int group);

@@ -386,11 +386,16 @@ int dispatch_slices(const SqpSlicePlan &p, int M, int N, int K, int cpg, const h
         if (p.tb == 2) return launch_slices<2, 2, 8, 8, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
         return launch_slices<2, 4, 8, 8, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
     }
-    if (p.tb == 1 && p.wv == 8) return slices_rows16<1, 8, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
-    if (p.tb == 1) return slices_rows16<1, 16, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
-    if (p.tb == 2 && p.wv == 8) return slices_rows16<2, 8, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
-    if (p.tb == 2) return slices_rows16<2, 16, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
-    if (p.wv == 4) return slices_rows16<4, 4, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
+    // 16 waves exist for up to four rows, four for up to eight in groups of 64 and more: eight otherwise
+    if constexpr (GS > 1)
+        if (p.tb == 4 && p.wv == 4 && M <= 8) {
+            if (M <= 4) return launch_slices<1, 4, 4, 1, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
+            return launch_slices<1, 4, 4, 2, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
+        }
+    if (p.wv == 16 && M <= 4 && p.tb == 1) return launch_slices<1, 1, 16, 1, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
+    if (p.wv == 16 && M <= 4 && p.tb == 2) return launch_slices<1, 2, 16, 1, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
+    if (p.tb == 1) return slices_rows16<1, 8, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
+    if (p.tb == 2) return slices_rows16<2, 8, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
     return slices_rows16<4, 8, GS, CPG>(g, M, N, K, cpg, x, packed, scales, zeros, y, epi, st);
 }
 

@@ -414,3 +414,18 @@ def test_alpha_search_scratch_sizes(L):
     for bad in [(0, 8, 8, 8, 1), (8, 8, 64, 64, 0), (8, 12, 64, 64, 1), (8, 8, 64, 48, 1)]:
         assert [f(*bad) for f in sizes] == [0, 0]
     assert sizes[0](70, 72, 240, 40, 3) == sizes[1](70, 72, 240, 40, 3) > 0   # single calls
+
+
+def test_slice_plans_are_built(L):
+    """The rule asks for 16 waves up to four rows and for four up to eight in groups of 64 and more: the only rows that those
+    variants exist for (the dispatch takes eight waves otherwise, which the rule did not mean)."""
+    rng, seen, tb, wv = random.Random(23), set(), ctypes.c_int(), ctypes.c_int()
+    for _ in range(30000):
+        g = rng.choice([32, 64, 128, 256, 384])
+        M, N, K = rng.randint(1, 32), 8 * int(2 ** rng.uniform(4, 12.5)), g * rng.randint(1, 22016 // g)
+        L.sqp_debug_decode_slice_plan(M, N, K, g, ctypes.byref(tb), ctypes.byref(wv))
+        seen.add((tb.value, wv.value))
+        assert (tb.value, wv.value) in ((0, 0), (1, 8), (2, 8), (4, 8), (1, 16), (2, 16), (4, 4))
+        assert wv.value != 16 or M <= 4
+        assert wv.value != 4 or (M <= 8 and g >= 64)
+    assert len(seen) == 7
