@@ -221,12 +221,13 @@ extern "C" void sqp_debug_set_slice_plan(int tb, int wv, int grouped) { g_slice_
 //   8.5 / 10.5 / 13.0 / 17.4.  From 257 to 320 slices of 64 columns the chip is a round and a little full, and
 //   short K only is worth it (17904 columns, K = 9984, 5 rows: 30.3 against 24.2).  K not a multiple of 128:
 //   the strips take chunks of one group there, so slices pay up to 1.6 times that K, from 8192 columns on
-//   with any.  Above 8192 columns other groups than those of 128 hold out longer (the strip kernel takes one chunk
-//   per iteration with several chunks per group).
-//   The lengths are those with the least time over 6814 calls (1 to 32 rows, N 512 to 44032, K 512 to 22016, groups
-//   of 32 to 384, three in four drawn over these ranges, weights from HBM): 1.27 times faster than without slices
-//   in the geometric mean, 0.4 % behind the better of the two kernels; 1.5 % of the calls are more than 3 % slower
-//   than without slices, at worst 19 % (the sweep is among the profiles).
+//   with any.  Above 8192 columns groups of several chunks hold out longer (the strip kernel takes one chunk
+//   per iteration there).
+//   The lengths have the least time over 6814 calls (1 to 32 rows, N 512 to 44032, K 512 to 22016, groups of 32 to
+//   384, three in four drawn over these ranges, weights from HBM), what is slower than before slices took these
+//   calls counted several times.  On 3616 other calls drawn likewise: 1.30 times faster than before in the
+//   geometric mean, 1.3 % behind the best variant of each; 1.9 % of them more than 3 % slower than before, at
+//   worst 21 % (the sweep is among the profiles).
 static SqpSlicePlan slice_plan(int M, int N, int K, int group)
 {
     const SqpSlicePlan none = {0, 0, false};
@@ -251,7 +252,7 @@ static SqpSlicePlan slice_plan(int M, int N, int K, int group)
     double most = lengths[row].longest[blocks];
     if (N > 16384) most *= group == 32 ? 0.85 : (group > 128 ? 2.0 : 1.0);
     else if (N > 8192 && group == 32) most = 11264;
-    else if (N > 8192 && M > 12) most *= group == 64 ? 1.3 : (group > 128 ? 1.6 : 1.0);
+    else if (N > 8192 && M > 12 && group > 128) most *= 1.6;
     if (N > 32768 && M > 16 && K < 1024) most = 0;
     if (K % 128 != 0) most = N <= 8192 ? 1.6 * most : (N <= 32768 || M > 16 ? ANY : 0.75 * most);
     if (K > most && slice_variant(M, N, K, group) < 0) return none;

@@ -765,8 +765,9 @@ static bool row_blocks_cover(int K, int group) { return K % 128 == 0 && (group =
 // The estimate: A + iterations * (B + L * workgroups / compute units) + (H + S * parts), the last two terms with
 // more than one K part; at most one eight-wave workgroup (kp = 2) or two four-wave ones per compute unit.
 // Fitted to 13700 launches of 1547 shapes (65 to 1024 rows, N 768 to 24576, K 512 to 8192, groups of 32, 64, 128
-// and 256, weights from HBM): rms 3 to 6 %, the choice 1 % behind the best variant in the mean, 2 % slower than the
-// tiles at worst and 1.41 times faster in the geometric mean.  us, tiles -> row blocks, groups of 128:
+// and 256, weights from HBM): rms 3 to 6 %, the choice 1 % behind the best variant in the mean.  On 945 other calls
+// that take row blocks, drawn over these ranges: 1.46 times faster than the tiles in the geometric mean, 1.5 % of
+// them more than 3 % slower, at worst 12 % (the sweep is among the profiles).  us, tiles -> row blocks, groups of 128:
 // 1024->1024 at 65 rows 12.1 -> 8.2, 1024->4096 at 160 rows 15.4 -> 9.2, 4096->4096 at 128 rows 21.7 -> 13.8, 2048->8192 at
 // 256 rows 26.0 -> 15.3, 8192->8192 at 65 / 128 rows 26.6 -> 25.0 / 32.8 -> 28.8 (at 160 rows 38.4 against 39.6).
 // limit: bytes of partial tiles the call may leave in its workspace.
