@@ -64,10 +64,11 @@ struct SearchSets {                            // the prepared operands of one a
         uint8_t *zeros;
         h16 *x_hat;
     } own;
-    __host__ __device__ uint32_t *packed(int i) const { return i == OWN_SET ? own.packed : (uint32_t *)(base + i * stride); }
-    __host__ __device__ h16 *scales(int i) const { return i == OWN_SET ? own.scales : (h16 *)(base + i * stride + at_scales); }
-    __host__ __device__ uint8_t *zeros(int i) const { return i == OWN_SET ? own.zeros : base + i * stride + at_zeros; }
-    __host__ __device__ h16 *x_hat(int i) const { return i == OWN_SET ? own.x_hat : (h16 *)(base + i * stride + at_x); }
+    // OWN: the set may be the caller's (pairs never take that one, and their kernel is spared the question)
+    template <bool OWN = true> __host__ __device__ uint32_t *packed(int i) const { return OWN && i == OWN_SET ? own.packed : (uint32_t *)(base + i * stride); }
+    template <bool OWN = true> __host__ __device__ h16 *scales(int i) const { return OWN && i == OWN_SET ? own.scales : (h16 *)(base + i * stride + at_scales); }
+    template <bool OWN = true> __host__ __device__ uint8_t *zeros(int i) const { return OWN && i == OWN_SET ? own.zeros : base + i * stride + at_zeros; }
+    template <bool OWN = true> __host__ __device__ h16 *x_hat(int i) const { return OWN && i == OWN_SET ? own.x_hat : (h16 *)(base + i * stride + at_x); }
 };
 struct SearchBatch {
     int set, n;                                // first set and number of alphas of the loss
@@ -79,7 +80,7 @@ constexpr int SEARCH_X_OCTS = 4096;            // 8-element pieces of x per work
 
 // Piece `item` of the preparation of `n` alphas: weight tiles first, each for all alphas in turn (the tile then
 // comes out of L2), then x.
-template <int G>
+template <int G, bool OWN>
 __device__ __forceinline__ void prepare_piece(int item, int T, int N, int K, const h16 *x, const h16 *w, const SearchSets &sets, int set, int n,
                                               const float *factors, unsigned char *lds)
 {
@@ -88,14 +89,14 @@ __device__ __forceinline__ void prepare_piece(int item, int T, int N, int K, con
     const int at = item / n, a = item % n;
     const float *s = factors + (size_t)a * K;
     if (at < tiles) {
-        quantize_tile<G, 512, true>(at % tx, at / tx, N, K, (const uint4 *)w, s, sets.packed(set + a), (uint16_t *)sets.scales(set + a),
-                                    sets.zeros(set + a), *reinterpret_cast<Tile *>(lds));
+        quantize_tile<G, 512, true>(at % tx, at / tx, N, K, (const uint4 *)w, s, sets.packed<OWN>(set + a), (uint16_t *)sets.scales<OWN>(set + a),
+                                    sets.zeros<OWN>(set + a), *reinterpret_cast<Tile *>(lds));
         return;
     }
     const int KO = K >> 3;
     const long first = (long)(at - tiles) * SEARCH_X_OCTS, octs = (long)T * KO;
     const float4 *s4 = reinterpret_cast<const float4 *>(s);
-    uint4 *out = (uint4 *)sets.x_hat(set + a);
+    uint4 *out = (uint4 *)sets.x_hat<OWN>(set + a);
     for (long i = first + threadIdx.x; i < octs && i < first + SEARCH_X_OCTS; i += 512) {
         const int ko = (int)(i % KO);
         out[i] = code_order(smooth_x8(((const uint4 *)x)[i], s4[2 * ko], s4[2 * ko + 1]));
@@ -122,7 +123,7 @@ loss_tile_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, cons
         static_assert(sizeof(QuantizeTile<PREP, 512>) <= sizeof(lds), "the quantiser's LDS fits the ring");
         if ((int)blockIdx.x >= losses) {
             for (int i = (int)blockIdx.x - losses; i < batch.next_pieces; i += (int)gridDim.x - losses)
-                prepare_piece<PREP>(i, M, N, K, x, w, sets, batch.next_set, batch.next_n, batch.next_factors, lds);
+                prepare_piece<PREP, true>(i, M, N, K, x, w, sets, batch.next_set, batch.next_n, batch.next_factors, lds);
             return;
         }
     }
@@ -469,7 +470,7 @@ __global__ void __launch_bounds__(512)
 search_prepare_kernel(int T, int N, int K, const h16 *__restrict__ x, const h16 *__restrict__ w, SearchSets sets, SearchBatch batch)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds[sizeof(QuantizeTile<G, 512>)];
-    prepare_piece<G>(blockIdx.x, T, N, K, x, w, sets, batch.next_set, batch.next_n, batch.next_factors, lds);
+    prepare_piece<G, false>(blockIdx.x, T, N, K, x, w, sets, batch.next_set, batch.next_n, batch.next_factors, lds);
 }
 
 template <int G>
@@ -486,7 +487,7 @@ loss_pair_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, cons
     const int losses = ctiles * rows * pairs;
     if ((int)blockIdx.x >= losses) {
         static_assert(sizeof(QuantizeTile<G, 512>) <= sizeof(lds), "the quantiser's LDS fits the ring");
-        prepare_piece<G>(blockIdx.x - losses, M, N, K, x, w, sets, batch.next_set, batch.next_n, batch.next_factors, lds);
+        prepare_piece<G, false>(blockIdx.x - losses, M, N, K, x, w, sets, batch.next_set, batch.next_n, batch.next_factors, lds);
         return;
     }
     // Workgroups go to the eight XCDs in turn: each XCD takes a run of neighbours in the order column, row, pair,
@@ -522,10 +523,10 @@ loss_pair_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, cons
     const uint32_t voff_p = (uint32_t)(kb * N + col) * 4u, voff_s = (uint32_t)col * 2u, voff_z = (uint32_t)col;
     const uint32_t voff_w = n0 + 2 * lane < N ? (uint32_t)(n0 + 2 * lane) * 2u : 0u;  // W: this lane's column pair
     const long nrow = (long)N * 2;            // one row of W in bytes
-    const unsigned char *pa = reinterpret_cast<const unsigned char *>(sets.packed(sa)) + (long)kh * 8 * nrow;  // 32 k: four packed rows
-    const long pdiff = (const unsigned char *)sets.packed(sb) - (const unsigned char *)sets.packed(sa);        // the partner's operands, all of them
-    const unsigned char *xq = reinterpret_cast<const unsigned char *>(x), *ha = reinterpret_cast<const unsigned char *>(sets.x_hat(sa));
-    const unsigned char *sca = reinterpret_cast<const unsigned char *>(sets.scales(sa)), *zra = sets.zeros(sa);
+    const unsigned char *pa = reinterpret_cast<const unsigned char *>(sets.packed<false>(sa)) + (long)kh * 8 * nrow;  // 32 k: four packed rows
+    const long pdiff = (const unsigned char *)sets.packed<false>(sb) - (const unsigned char *)sets.packed<false>(sa);        // the partner's operands, all of them
+    const unsigned char *xq = reinterpret_cast<const unsigned char *>(x), *ha = reinterpret_cast<const unsigned char *>(sets.x_hat<false>(sa));
+    const unsigned char *sca = reinterpret_cast<const unsigned char *>(sets.scales<false>(sa)), *zra = sets.zeros<false>(sa);
     const unsigned char *wq = reinterpret_cast<const unsigned char *>(w) + (long)wave * 8 * nrow;     // this wave's 8 rows of a stage
     const int spg = G32 ? 1 : __builtin_amdgcn_readfirstlane(group / SBK);  // stages per group (G32: two groups per stage)
     int kin = 0, prow = G32 ? kh : 0;          // position of the stage being issued in its group, its parameter row

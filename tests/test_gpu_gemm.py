@@ -571,14 +571,15 @@ def test_decode_slice_infinite_step_of_the_last_group(orc, sqp, M, K, N, group, 
     assert np.array_equal(got[:, 0::2], want[:, 0::2]) and np.isfinite(got[:, 1::2]).all()
 
 
-@pytest.mark.parametrize("M,K,N,group", [(1, 4096, 1024, 128), (3, 1024, 264, 64), (8, 1024, 520, 128), (13, 1152, 136, 32), (16, 1024, 264, 256), (20, 1024, 264, 64), (40, 1024, 264, 128), (70, 1024, 264, 128)])
-@pytest.mark.parametrize("tb,wv", [(0, 0), (1, 8), (1, 16), (2, 8), (4, 4), (4, 8)])
+_ZERO_CODE_SHAPES = [(1, 4096, 1024, 128), (3, 1024, 264, 64), (8, 1024, 520, 128), (13, 1152, 136, 32), (16, 1024, 264, 256), (20, 1024, 264, 64)]
+
+
+@pytest.mark.parametrize("M,K,N,group,tb,wv", [(*s, *v) for s in _ZERO_CODE_SHAPES for v in [(0, 0), (1, 8), (1, 16), (2, 8), (4, 4), (4, 8)]] +
+                         [(40, 1024, 264, 128, 0, 0), (70, 1024, 264, 128, 0, 0)])
 def test_codes_at_the_zero_point_count_nothing(orc, sqp, M, K, N, group, tb, wv):
     """A weight whose code is the zero point is exactly 0: whatever finite activations meet such weights only, also next
     to the largest fp16 value, their sum is exactly 0, by the rule and in every slice variant; one other code in
     the column then gives its own product alone, rounded as the plain product is."""
-    if M > 32 and tb:
-        pytest.skip("the column-slice kernel takes up to 32 rows")
     print("case zero codes", M, K, N, group, tb, wv, flush=True)
     rng = np.random.Generator(np.random.PCG64(M + K))
     z = rng.integers(0, 16, size=(K // group, N)).astype(np.uint8)
