@@ -218,16 +218,18 @@ extern "C" void sqp_debug_set_slice_plan(int tb, int wv, int grouped) { g_slice_
 //   K: the strip kernel's hand-over costs about the same whatever K, the slices' latency and activations grow
 //   with K, so K above `longest` goes to the strips: us at 1 / 8 / 16 / 32 rows, strips against slices, N = 1024:
 //   K = 4096 7.1 / 7.2 / 7.3 / 9.2 against 4.4 / 5.0 / 5.9 / 7.3, K = 12288 9.4 / 9.5 / 9.9 / 11.9 against
-//   8.5 / 10.5 / 13.0 / 17.4.  From 257 to 320 slices of 64 columns the chip is a round and a little full, and
-//   short K only is worth it (17904 columns, K = 9984, 5 rows: 30.3 against 24.2).  K not a multiple of 128:
-//   the strips take chunks of one group there, so slices pay up to 1.6 times that K, from 8192 columns on
-//   with any.  Above 8192 columns groups of several chunks hold out longer (the strip kernel takes one chunk
-//   per iteration there).
-//   The lengths have the least time over 6814 calls (1 to 32 rows, N 512 to 44032, K 512 to 22016, groups of 32 to
-//   384, three in four drawn over these ranges, weights from HBM), what is slower than before slices took these
-//   calls counted several times.  On 3616 other calls drawn likewise: 1.30 times faster than before in the
-//   geometric mean, 1.3 % behind the best variant of each; 1.9 % of them more than 3 % slower than before, at
-//   worst 21 % (the sweep is among the profiles).
+//   8.5 / 10.5 / 13.0 / 17.4.  From 257 to 320 and from 513 to 576 slices of 64 columns the chip is a round or two
+//   and a little full, and short K only is worth it (17904 columns, K = 9984, 5 rows: 30.3 against 24.2).  K not
+//   a multiple of 128: the strips take chunks of one group there, so slices pay up to 1.6 times that K, from
+//   8192 columns on with any.  Above 8192 columns groups of several chunks hold out longer (the strip kernel
+//   takes one chunk per iteration there).  Rows of packed words that are not whole 128-byte lines (N % 32) cost
+//   slices more lines than strips: 20840 columns, K = 13952, one row 41.5 against 32.6, 21920 columns, K = 12032
+//   30.9 against 35.5.
+//   The lengths have the least time over 10430 calls (1 to 32 rows, N 512 to 44032, K 512 to 22016, groups of 32 to
+//   384, most of them drawn over these ranges, weights from HBM), what is slower than before slices took these
+//   calls counted several times.  On 3223 other calls drawn likewise: 1.28 times faster than before in the
+//   geometric mean, 1.3 % behind the best variant of each; 1.5 % of them more than 3 % slower than before, at
+//   worst 15 % (the sweep is among the profiles).
 static SqpSlicePlan slice_plan(int M, int N, int K, int group)
 {
     const SqpSlicePlan none = {0, 0, false};
@@ -237,7 +239,7 @@ static SqpSlicePlan slice_plan(int M, int N, int K, int group)
     if (strips_forced()) return none;
     const int blocks = M > 16 ? 4 : (M + 3) / 4 - 1;  // blocks of four rows less one; 17 to 32 rows
     constexpr int ANY = 1 << 28;
-    static const struct { int columns, longest[5]; } lengths[8] = {
+    static const struct { int columns, longest[5]; } lengths[9] = {
         {2048, {12288, 8192, 7168, 6144, 6144}},
         {4096, {13312, 9728, 8704, 6144, 5632}},
         {8192, {13312, 12288, 9728, 6656, 6144}},
@@ -245,7 +247,8 @@ static SqpSlicePlan slice_plan(int M, int N, int K, int group)
         {16384, {ANY, ANY, 20480, 11264, 13312}},
         {20480, {4096, 2560, 2560, 2048, 0}},
         {32768, {16384, 8192, 7680, 4096, 0}},
-        {INT_MAX, {9728, 9216, 4096, 2560, 2048}},
+        {36864, {3072, 2816, 2048, 1536, 0}},
+        {INT_MAX, {9728, 9216, 8192, 4096, 2048}},
     };
     int row = 0;
     while (N > lengths[row].columns) row++;
@@ -254,7 +257,13 @@ static SqpSlicePlan slice_plan(int M, int N, int K, int group)
     else if (N > 8192 && group == 32) most = 11264;
     else if (N > 8192 && M > 12 && group > 128) most *= 1.6;
     if (N > 32768 && M > 16 && K < 1024) most = 0;
-    if (K % 128 != 0) most = N <= 8192 ? 1.6 * most : (N <= 32768 || M > 16 ? ANY : 0.75 * most);
+    if (N % 32 != 0) most *= group <= 64 ? 0.8 : (N > 8192 ? 0.9 : 1.0);
+    if (K % 128 != 0) {
+        if (N <= 8192) most *= 1.6;
+        else if (N > 16384 && N <= 20480 && group == 64 && M > 8) most = 2048;
+        else if (N <= 32768 || M > 16) most = ANY;
+        else most *= group == 32 && M > 8 ? 0.0 : 0.75;
+    }
     if (K > most && slice_variant(M, N, K, group) < 0) return none;
     const int width = N <= 4096 ? 0 : (N <= 8192 ? 1 : (N <= 16384 ? 2 : 3));
     SqpSlicePlan p = {width == 0 ? 1 : (width == 1 ? 2 : 4), 8, width < 2};
