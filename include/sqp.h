@@ -124,8 +124,8 @@ int sqp_dequantize(int N, int K, int group, const uint32_t *packed, const void *
  * inside each workgroup); M <= 64 with a K of fewer than eight chunks of 128 (or of one group of 32 or
  * 64); larger M with more tiles of 128 x 512 than a quarter of the chip's compute units (those can
  * split too, but only in a scratch buffer of their own: sqp_w4a16_gemm_scratch).  For the others:
- *   - no workspace set: the plan without a split runs (same result within the tolerance of
- *     Eq. 3's fp32 accumulation, slower on narrow layers);
+ *   - no workspace set: a plan without a split across workgroups runs (same result within the
+ *     tolerance of Eq. 3's fp32 accumulation, slower on narrow layers with long K);
  *   - workspace smaller than sqp_w4a16_gemm_workspace_bytes() of the shape: a plan that fits
  *     it runs, down to sqp_w4a16_gemm_workspace_least_bytes(); below that SQP_ERR_WORKSPACE,
  *     nothing enqueued.

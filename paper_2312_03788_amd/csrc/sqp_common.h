@@ -58,7 +58,7 @@ int sqp_zero_tickets(unsigned *tickets, hipStream_t stream);
 // Decode (weight-streaming) and prefill (tiled matrix-core) back ends of sqp_w4a16_gemm.
 // Arguments are already validated.
 // epi: 0 = y [M][N] fp16; 1 = SiLU(gate) * up of interleaved (gate, up) column pairs, y [M][N/2].
-// A plan that splits K needs ws; without one (partial == nullptr) the non-split plan runs; with one below
+// A plan that splits K needs ws; without one (partial == nullptr) a plan that does not split runs; with one below
 // the least size (see below) the call fails with SQP_ERR_WORKSPACE and enqueues nothing.
 int sqp_gemm_decode(int M, int N, int K, int group, const h16 *x, const uint32_t *packed,
                     const h16 *scales, const uint8_t *zeros, h16 *y, int epi, const SqpWorkspace &ws, hipStream_t stream);

@@ -230,7 +230,11 @@ extern "C" void sqp_debug_set_slice_plan(int tb, int wv, int grouped) { g_slice_
 //   calls counted several times.  On 3223 other calls drawn likewise: 1.28 times faster than before in the
 //   geometric mean, 1.3 % behind the best variant of each; 1.5 % of them more than 3 % slower than before, at
 //   worst 15 % (the sweep is among the profiles).
-static SqpSlicePlan slice_plan(int M, int N, int K, int group)
+//   Without a workspace the strips cannot split K: slices are taken wherever they would, but for 17 and more rows
+//   and K below 3072 above 16384 columns (0.86 to 1.1 there).  1 to 32 rows without one, strips against slices: 3.9 times their time in the mean of 263 such
+//   calls up to 4096 columns, 3.6 (54) up to 8192, 2.5 (18) up to 16384, 1.6 (60) from there on.
+static Plan plan_for(int M, int N, int K, int group, bool have_workspace);
+static SqpSlicePlan slice_plan(int M, int N, int K, int group, bool have_workspace)
 {
     const SqpSlicePlan none = {0, 0, false};
     if (g_slice_mode < 0 || M > 32 || (group != 32 && group != 64 && group % 128 != 0)) return none;
@@ -264,7 +268,7 @@ static SqpSlicePlan slice_plan(int M, int N, int K, int group)
         else if (N <= 32768 || M > 16) most = ANY;
         else most *= group == 32 && M > 8 ? 0.0 : 0.75;
     }
-    if (K > most && slice_variant(M, N, K, group) < 0) return none;
+    if (K > most && slice_variant(M, N, K, group) < 0 && (have_workspace || (N > 16384 && M > 16 && K < 3072) || plan_for(M, N, K, group, true).split < 2)) return none;
     const int width = N <= 4096 ? 0 : (N <= 8192 ? 1 : (N <= 16384 ? 2 : 3));
     SqpSlicePlan p = {width == 0 ? 1 : (width == 1 ? 2 : 4), 8, width < 2};
     if (group == 32 && width == 3 && N <= 32768 && M <= 16) p.tb = 2, p.grouped = true;
@@ -279,12 +283,12 @@ static SqpSlicePlan slice_plan(int M, int N, int K, int group)
 static bool slices_alone(int M, int N, int K, int group)
 {
     if (g_slice_mode < 0) return false;
-    return g_slice_plan.tb > 0 || g_slice_mode > 0 || strips_forced() ? slice_plan(M, N, K, group).tb > 0 : slice_variant(M, N, K, group) >= 0;
+    return g_slice_plan.tb > 0 || g_slice_mode > 0 || strips_forced() ? slice_plan(M, N, K, group, true).tb > 0 : slice_variant(M, N, K, group) >= 0;
 }
 
 extern "C" void sqp_debug_decode_slice_plan(int M, int N, int K, int group, int *tb, int *wv)
 {
-    const SqpSlicePlan p = slice_plan(M, N, K, group);
+    const SqpSlicePlan p = slice_plan(M, N, K, group, true);
     *tb = p.tb;
     *wv = p.wv;
 }
@@ -392,7 +396,7 @@ size_t sqp_gemm_decode_least_bytes(int M, int N, int K, int group)
 int sqp_gemm_decode(int M, int N, int K, int group, const h16 *x, const uint32_t *packed, const h16 *scales,
                     const uint8_t *zeros, h16 *y, int epi, const SqpWorkspace &ws, hipStream_t stream)
 {
-    SqpSlicePlan sp = slice_plan(M, N, K, group);
+    SqpSlicePlan sp = slice_plan(M, N, K, group, ws.partial != nullptr);
     if (sp.tb) {
         if (ws.partial != nullptr && ws.partial_bytes < sqp_gemm_decode_least_bytes(M, N, K, group)) return SQP_ERR_WORKSPACE;
         if (epi != 0 && sp.tb == 1) sp.tb = 2;  // a lane's columns are whole (gate, up) pairs

@@ -379,6 +379,33 @@ def test_workspace_between_least_and_preferred_in_tiles(orc, sqp, M, K, N, group
         sqp.lib().sqp_debug_set_row_blocks(0, 0, 0)
 
 
+@pytest.mark.parametrize("M,K,N,group", [(11, 16448, 136, 64), (2, 14080, 264, 128), (20, 7168, 520, 256), (32, 9216, 72, 32)])
+def test_without_a_workspace_long_k_takes_slices(orc, sqp, M, K, N, group):
+    """K so long that the strip kernel is faster where it can split: without a workspace it cannot, and the column slices
+    run (the bits of the forced ones); with one the strips do."""
+    print("case no workspace", M, K, N, group, flush=True)
+    L = sqp.lib()
+    tb, wv = ctypes.c_int(), ctypes.c_int()
+    L.sqp_debug_decode_slice_plan(M, N, K, group, ctypes.byref(tb), ctypes.byref(wv))
+    assert tb.value == 0
+    xs, p, sc, z = _layer(orc, M, K, N, group)
+    dx, dp, dsc, dz = _dev(xs), _dev(p), _dev(sc), _dev(z)
+    y, forced = Guarded(2 * M * N, torch.float16, (M, N)), Guarded(2 * M * N, torch.float16, (M, N))
+    assert L.sqp_set_workspace(None, ctypes.c_size_t(0), None) == 0
+    try:
+        assert _gemm(L, M, N, K, group, dx, dp, dsc, dz, y.ptr) == 0
+        L.sqp_debug_set_slice_plan(1, 16 if M <= 4 else 8, 1)
+        assert _gemm(L, M, N, K, group, dx, dp, dsc, dz, forced.ptr) == 0
+    finally:
+        L.sqp_debug_set_slice_plan(0, 0, 0)
+        torch.cuda.synchronize()
+        sqp.set_workspace(0)
+    y.check("y")
+    ok, worst, nbad = gemm_tolerance_ok(orc, y.numpy(), *orc.w4a16_gemm_ref(xs, p, sc, z, group))
+    assert ok, (worst, nbad)
+    assert np.array_equal(y.numpy().view(np.uint16), forced.numpy().view(np.uint16))
+
+
 @pytest.mark.parametrize("M,K,N,group,fused", [(2050, 2048, 8144, 128, 0), (660, 2048, 5184, 64, 1)])
 def test_scratch_of_one_call(orc, sqp, M, K, N, group, fused):
     """Grids that fill the chip: no workspace asked for and none touched; with a scratch buffer of the
