@@ -225,7 +225,7 @@ w4a16_decode_slice_kernel(int M, int N, int K, int cpg, int grouped, const h16 *
         return (float)((b & 1) ? v.y : v.x);
     };
 
-    auto compute = [&](const Stage &s, auto SLOT, bool tail) {
+    auto compute = [&](Stage &s, auto SLOT, bool tail) {
         constexpr int slot = decltype(SLOT)::value;
         // The A fragments are read with instructions written in assembly: the compiler cannot
         // tell which ring slot a direct load filled and would wait for every outstanding load.
@@ -240,13 +240,24 @@ w4a16_decode_slice_kernel(int M, int N, int K, int cpg, int grouped, const h16 *
         for (int ks = 0; ks < 4; ks++)
 #pragma unroll
             for (int mt = 0; mt < MT; mt++) asm volatile("" : "+v"(xa[ks][mt]));  // no use ahead of the wait
+        // A short last chunk: no activations past K, and no step of a group past it (the last group's, read again, may be
+        // infinite, and infinity times a sum of 0 is NaN).  Branches: the asm statements keep the compiler
+        // from selects, which every chunk would pay for (32 of 220 vector instructions in groups of 64).
         if constexpr (GS < 4)
             if (tail) {
 #pragma unroll
                 for (int ks = 1; ks < 4; ks++)
+                    if (ks >= tail_ks) {
 #pragma unroll
-                    for (int mt = 0; mt < MT; mt++)
-                        if (ks >= tail_ks) xa[ks][mt] = u32x4{0, 0, 0, 0};
+                        for (int mt = 0; mt < MT; mt++) {
+                            xa[ks][mt] = u32x4{0, 0, 0, 0};
+                            asm volatile("" : "+v"(xa[ks][mt]));
+                        }
+                        if (ks % GS == 0) {
+                            s.sc[ks / GS] = svec{};
+                            asm volatile("" : "+v"(s.sc[ks / GS]));
+                        }
+                    }
             }
         // The accumulators are kept whole until a sum of theirs has been read (the asm statements behind the
         // FMAs): a register that nothing reads would otherwise be free for an instruction in assembly while
@@ -271,8 +282,7 @@ w4a16_decode_slice_kernel(int M, int N, int K, int cpg, int grouped, const h16 *
             }
 #pragma unroll
             for (int b = 0; b < TB; b++) {
-                float d = step_of(s, q, b);
-                if (GS < 4 && tail && q * GS >= tail_ks) d = 0.f;  // no such group: an infinite step read again times 0 would be NaN
+                const float d = step_of(s, q, b);
 #pragma unroll
                 for (int mt = 0; mt < MT; mt++) {
 #pragma unroll
