@@ -28,7 +28,8 @@ void sqp_debug_set_slice_plan(int tb, int wv, int grouped); /* tb > 0: column sl
 /* Whether a layer fills the chip with slices of 32 (0) or 64 (1) columns and takes the column-slice kernel for
  * that alone (-1: the launch plan decides by N, K and the group).  Host arithmetic only. */
 int sqp_debug_decode_slice_choice(int M, int N, int K, int group);
-/* The slices a call takes: columns / 16 and waves per workgroup (0, 0: the strip kernel below or the generic one). */
+/* The slices a call takes with a workspace set: columns / 16 and waves per workgroup (0, 0: the strip kernel below or the
+ * generic one). */
 void sqp_debug_decode_slice_plan(int M, int N, int K, int group, int *tb, int *wv);
 /* The plan by strips for a shape: strips per workgroup, K parts, k-steps of one group up to 128 k
  * (0 = the generic one-thread-per-element kernel).  Calls with up to 16 rows and groups that are
