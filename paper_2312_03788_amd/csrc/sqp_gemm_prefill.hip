@@ -58,6 +58,36 @@ struct Order {
     }
 };
 
+// Which tile a workgroup takes.  The tiles are numbered in groups of up to gm rows of tiles, row index fastest
+// within a column, so that consecutive numbers are compact blocks; workgroups are dealt to the eight XCDs in turn, so
+// each XCD gets one run of consecutive numbers (of all K parts: tiles of one part first).  The workgroups that an
+// XCD has resident then share its L2: of a stage's 16 KB of activations and 16 KB of weights per 128 x 512 tile
+// it fetches 12 blocks for 32 tiles (8 rows x 4 columns) instead of about 35 with column-major numbers over all XCDs.
+struct TileMap {
+    int tile0;   // number of the launch's first tile
+    int tn, tm;  // columns and rows of tiles
+    int gm;      // rows per group
+    int halves;  // 1: the launch's tiles are the left and right halves of the numbered ones (tile0 counts halves)
+};
+constexpr int XCDS = 8;
+
+// Workgroup w of `total` (a launch's linear index): its place when every XCD has one run.
+__device__ __forceinline__ uint32_t xcd_run(uint32_t w, uint32_t total)
+{
+    const uint32_t xcd = w % XCDS, len = total / XCDS, more = total % XCDS;
+    return xcd * len + (xcd < more ? xcd : more) + w / XCDS;
+}
+
+__device__ __forceinline__ void tile_at(const TileMap &m, uint32_t i, int &row, int &col)
+{
+    const uint32_t n = (m.tile0 + i) >> m.halves;
+    const uint32_t g = n / (uint32_t)(m.gm * m.tn), in = n - g * (uint32_t)(m.gm * m.tn);
+    const uint32_t left = m.tm - g * m.gm, rows = left < (uint32_t)m.gm ? left : m.gm;
+    const uint32_t c = in / rows;
+    row = (int)(g * m.gm + in - c * rows);
+    col = (int)(m.halves ? 2 * c + ((m.tile0 + i) & 1) : c);
+}
+
 // RT, NT: 32-row and 32-column MFMA tiles per wave; WM: waves along the rows, the other 4 / WM along
 // the columns.  A workgroup owns 32 RT WM rows x 32 NT (4 / WM) columns:
 //   <4, 4, 1>: 128 x 512, the four waves side by side on the same 128 rows.  Every packed word
@@ -69,14 +99,12 @@ struct Order {
 //           the K-split launches.
 //   <3, 2, 1>, <5, 2, 1>, <6, 2, 1>: 96, 160 or 192 rows x 256 columns, K-split launches of row
 //           counts that would leave much of a 128-row tile empty.
-// Workgroup b of the launch handles tile tile0 + b of the grid of such tiles (column index fastest,
-// tn tiles per row).
 // G32: quantisation groups of 32 rows, i.e. two groups per 64-row stage (the steps and zero
 // points of both are loaded per stage and the unpack switches sets after the second k-step);
 // otherwise the group is a multiple of 64 rows.
 template <int RT, int NT, int WM, bool G32>
 __global__ void __launch_bounds__(256)
-w4a16_prefill_kernel(int M, int N, int K, int group, int tile0, int tn, const h16 *__restrict__ x,
+w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__restrict__ x,
                      const uint32_t *__restrict__ packed, const h16 *__restrict__ scales,
                      const uint8_t *__restrict__ zeros, h16 *__restrict__ y, float *__restrict__ part, int epi)
 {
@@ -101,15 +129,18 @@ w4a16_prefill_kernel(int M, int N, int K, int group, int tile0, int tn, const h1
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / WNW, wn = wave % WNW;
     const int l32 = lane & 31, kb = lane >> 5;
-    const int tile = tile0 + (int)blockIdx.x;
-    const int nbase = (tile % tn) * WGN;
-    const int m0 = (tile / tn) * BM;
-    const int n0 = nbase + wn * WN;
     // K split across gridDim.y workgroups (part != nullptr): this one takes stages
-    // [stage0, stage0 + stages) and leaves its fp32 sums in part[blockIdx.y][blockIdx.x][BM][WGN].
+    // [stage0, stage0 + stages) and leaves its fp32 sums in part[kpart][launch's tile][BM][WGN].
+    const uint32_t place = xcd_run(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
+    const uint32_t kpart = gridDim.y == 1 ? 0 : place / gridDim.x;
+    int trow, tcol;
+    tile_at(map, place - kpart * gridDim.x, trow, tcol);
+    const int nbase = tcol * WGN;
+    const int m0 = trow * BM;
+    const int n0 = nbase + wn * WN;
     const int stages_all = K / BK;
-    const int stage0 = (int)((long)stages_all * blockIdx.y / gridDim.y);
-    const int stages = (int)((long)stages_all * (blockIdx.y + 1) / gridDim.y) - stage0;
+    const int stage0 = (int)((uint32_t)stages_all * kpart / gridDim.y);
+    const int stages = (int)((uint32_t)stages_all * (kpart + 1) / gridDim.y) - stage0;
     const int spg = G32 ? 1 : group / BK;  // stages per quantisation group (G32: two groups per stage)
 
     int ncol = n0 + NT * l32;
@@ -406,7 +437,7 @@ w4a16_prefill_kernel(int M, int N, int K, int group, int tile0, int tn, const h1
     const int nout = nbase + nloc;
     const int mloc0 = (e_wave / WNW) * 32 * RT + 4 * e_kb, mrow0 = m0 + mloc0;
     if (part != nullptr) {
-        float *ptile = part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * (BM * WGN) + nloc;
+        float *ptile = part + (size_t)place * (BM * WGN) + nloc;
 #pragma unroll
         for (int mt = 0; mt < RT; mt++)
 #pragma unroll
@@ -457,15 +488,15 @@ w4a16_prefill_kernel(int M, int N, int K, int group, int tile0, int tn, const h1
 }
 
 // y = fp16(sum over the K parts, in part order) of the fp32 partial tiles part[parts][tiles][bm][wgn]
-// that the launch of tiles tile0 .. left: 8 adjacent columns per thread.  grid: (bm wgn / 2048, tiles);
-// wgn 128 or 256.
-__global__ void __launch_bounds__(256) splitk_reduce_kernel(const float *__restrict__ part, int M, int N, int bm, int wgn, int tile0, int tn,
+// that a launch left: 8 adjacent columns per thread.  grid: (bm wgn / 2048, tiles); wgn 128 or 256.
+__global__ void __launch_bounds__(256) splitk_reduce_kernel(const float *__restrict__ part, int M, int N, int bm, int wgn, TileMap map,
                                                             int parts, h16 *__restrict__ y, int epi)
 {
     const int e = (blockIdx.x * 256 + threadIdx.x) * 8;      // element of the tile
     const int row = wgn == 256 ? e >> 8 : e >> 7, col = e & (wgn - 1);
-    const int tile = tile0 + blockIdx.y;
-    const int m = (tile / tn) * bm + row, n = (tile % tn) * wgn + col;
+    int trow, tcol;
+    tile_at(map, blockIdx.y, trow, tcol);
+    const int m = trow * bm + row, n = tcol * wgn + col;
     if (m >= M || n >= N) return;
     const f32x4 *p = reinterpret_cast<const f32x4 *>(part + (size_t)blockIdx.y * bm * wgn + e);
     const size_t stride = (size_t)gridDim.y * bm * wgn / 4;  // one part, in 16-byte pieces
@@ -593,11 +624,13 @@ extern "C" void sqp_debug_prefill_plan(int M, int N, int K, int cus, long *full,
 static const double stage_us[7] = {0, 0, 0, 0.72, 0.77, 0.97, 1.11};
 
 // What a call launches: up to two launches of tiles of 32 rt rows x 32 nt columns per wave, each over
-// `tiles` tiles from tile0 of a grid with tn tiles per row, in `parts` K parts (1: straight to y).
+// `tiles` tiles from tile0 of a grid with tn columns of tiles, in `parts` K parts (1: straight to y).  With nt == 2
+// behind a launch of full tiles, tile0 counts half tiles and tn full ones (halves).
 struct TileLaunch {
     int rt, nt;
     long tile0, tiles;
     int tn, parts;
+    bool halves;
 };
 struct LaunchPlan {
     int wm, count;
@@ -640,7 +673,7 @@ static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, size_t 
         q.count = 1;
         int parts = g_force_nt == 2 && have_workspace ? g_force_parts : 1;
         if (parts > stages) parts = stages;
-        q.l[0] = TileLaunch{g_force_rt, g_force_nt, 0, (long)tn * tm, tn, parts < 1 ? 1 : parts};
+        q.l[0] = TileLaunch{g_force_rt, g_force_nt, 0, (long)tn * tm, tn, parts < 1 ? 1 : parts, false};
         return q;
     }
     const bool hooked = g_tile_mode != 0 || g_tile_shape != 0 || g_ksplit >= 0;
@@ -664,7 +697,7 @@ static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, size_t 
             best = stages * 1.43;
             q.wm = 1;
             q.count = 1;
-            q.l[0] = TileLaunch{4, 4, 0, tiles44, (N + 511) / 512, 1};
+            q.l[0] = TileLaunch{4, 4, 0, tiles44, (N + 511) / 512, 1, false};
         }
         const int tn = (N + 255) / 256;
         for (int rt = 3; rt <= 6; rt++) {
@@ -675,7 +708,7 @@ static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, size_t 
             if (tiles > cus) continue;
             for (int parts = 1; parts <= (most > 1 ? most : 1); parts++) {
                 const double t = (stages + parts - 1) / parts * stage_us[rt] + (parts > 1 ? parts * part_us : 0.0);
-                const TileLaunch l = {rt, 2, 0, tiles, tn, parts};
+                const TileLaunch l = {rt, 2, 0, tiles, tn, parts, false};
                 if (launch_partial_bytes(l, 1) <= room && (q.count == 0 || t < best)) {
                     best = t;
                     q.count = 1;
@@ -685,10 +718,10 @@ static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, size_t 
         }
         if (q.count) return q;
     }
-    if (p.full > 0) q.l[q.count++] = TileLaunch{4, 4, 0, p.full, tnf, 1};
+    if (p.full > 0) q.l[q.count++] = TileLaunch{4, 4, 0, p.full, tnf, 1, false};
     if (p.half > 0) {
         int parts = p.ksplit;
-        while (!hooked && parts > 1 && launch_partial_bytes(TileLaunch{4, 2, 0, p.half, 0, parts}, p.wm) > room) parts--;
+        while (!hooked && parts > 1 && launch_partial_bytes(TileLaunch{4, 2, 0, p.half, 0, parts, true}, p.wm) > room) parts--;
         // Few tiles left over after the whole rounds: split in K as well, as far as they then fill the
         // chip once.
         if (!hooked && p.full > 0 && have_workspace) {
@@ -699,13 +732,13 @@ static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, size_t 
             double best = stages * 0.77;
             for (int n = 2; n <= most; n++) {
                 const double t = (stages + n - 1) / n * 0.77 + n * part_us + 3;  // (3: the reduction's launch)
-                if (t < best && launch_partial_bytes(TileLaunch{4, 2, 0, p.half, 0, n}, 1) <= room) {
+                if (t < best && launch_partial_bytes(TileLaunch{4, 2, 0, p.half, 0, n, true}, 1) <= room) {
                     best = t;
                     parts = n;
                 }
             }
         }
-        q.l[q.count++] = TileLaunch{4, 2, 2 * p.full, p.half, 2 * tnf, parts};
+        q.l[q.count++] = TileLaunch{4, 2, 2 * p.full, p.half, tnf, parts, true};
     }
     return q;
 }
@@ -878,12 +911,22 @@ size_t sqp_gemm_prefill_least_bytes(int M, int N, int K, int group)
     return least_bytes(plan_partial_bytes(preferred_launches(M, N, K, group)), M, N, K, group);
 }
 
+// Rows per group of the numbering: 8 for full tiles, whose stage takes as many bytes of x per row of tiles as of
+// weights per column (8 x 4 of the 32 that an XCD holds: 12 blocks of 16 KB, 5.7 x 5.7 would be the least), 4 for tiles
+// of half the columns; groups of equal size where the rows do not divide.
+static TileMap tile_map(const TileLaunch &l, int wm, int M)
+{
+    const int bm = 32 * l.rt * wm, most = l.nt == 4 || l.halves ? 8 / wm : 4;
+    const int tm = (M + bm - 1) / bm, groups = (tm + most - 1) / most;
+    return TileMap{(int)l.tile0, l.tn, tm, (tm + groups - 1) / groups, l.halves};
+}
+
 template <int RT, int NT, int WM, bool G32>
 static void launch_variant(const TileLaunch &l, int M, int N, int K, int group, const h16 *x, const uint32_t *packed, const h16 *scales,
                            const uint8_t *zeros, h16 *y, int epi, float *part, hipStream_t stream)
 {
     w4a16_prefill_kernel<RT, NT, WM, G32><<<dim3((unsigned)l.tiles, l.parts), 256, 0, stream>>>(
-        M, N, K, group, (int)l.tile0, l.tn, x, packed, scales, zeros, y, l.parts >= 2 ? part : nullptr, epi);
+        M, N, K, group, tile_map(l, WM, M), x, packed, scales, zeros, y, l.parts >= 2 ? part : nullptr, epi);
 }
 
 int sqp_gemm_prefill(int M, int N, int K, int group, const h16 *x, const uint32_t *packed,
@@ -927,7 +970,7 @@ int sqp_gemm_prefill(int M, int N, int K, int group, const h16 *x, const uint32_
 #undef SQP_TILES
         if (l.parts >= 2) {
             const int bm = 32 * l.rt * q.wm, wgn = l.nt * 128 / q.wm;
-            splitk_reduce_kernel<<<dim3(bm * wgn / 2048, (unsigned)l.tiles), 256, 0, stream>>>(part, M, N, bm, wgn, (int)l.tile0, l.tn, l.parts, y, epi);
+            splitk_reduce_kernel<<<dim3(bm * wgn / 2048, (unsigned)l.tiles), 256, 0, stream>>>(part, M, N, bm, wgn, tile_map(l, q.wm, M), l.parts, y, epi);
         }
     }
     return sqp_launch_status();
