@@ -73,6 +73,25 @@ def _check_scratch_after_last_barrier(src, asm_path, kernels):
                                "assume spills only in the epilogue" % (src, k))
 
 
+# The tiled kernel's MFMAs are asm statements too, so the compiler puts no wait states between one and a read of its
+# result; the kernel spends them (s_nop 15) wherever a run of stages ends.  No accumulator may be copied or stored
+# between an MFMA and the next such wait (the order of the lines is that of the control flow there: loop body, wait).
+def _check_results_behind_wait(src, asm_path, want):
+    kernel, waiting = None, False
+    for l in open(asm_path):
+        m = re.match(r"(_Z\S+):", l)
+        if m:
+            kernel, waiting = (m.group(1) if want in m.group(1) else None), False
+        elif kernel is None:
+            continue
+        elif "v_mfma" in l:
+            waiting = True
+        elif re.match(r"\s*s_nop 15\b", l):
+            waiting = False
+        elif waiting and re.match(r"\s*(v_accvgpr|(global|scratch)_store.*\ba)", l):
+            raise RuntimeError("%s: kernel %s uses a matrix result too early: %s" % (src, kernel, l.strip()))
+
+
 def _compile(src):
     obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
     guard = ["-Rpass-analysis=kernel-resource-usage", "-save-temps=obj"] if src in GUARDED_KERNELS else []
@@ -86,6 +105,8 @@ def _compile(src):
         if spilling:
             stem = os.path.splitext(src)[0]
             _check_scratch_after_last_barrier(src, os.path.join(OBJ, stem + "-hip-amdgcn-amd-amdhsa-gfx950.s"), spilling)
+        if src == "sqp_gemm_prefill.hip":
+            _check_results_behind_wait(src, os.path.join(OBJ, os.path.splitext(src)[0] + "-hip-amdgcn-amd-amdhsa-gfx950.s"), "w4a16_prefill_kernel")
         keep, skip = [], 0
         for l in lines:  # drop the remarks (and the source excerpt lines that follow the first of each kernel)
             if "[-Rpass-analysis=kernel-resource-usage]" in l:

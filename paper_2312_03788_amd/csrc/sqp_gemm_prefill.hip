@@ -8,9 +8,9 @@
 //   - Weights never pass through LDS: one dwordx4 load per lane fetches, for k-block
 //     (lane / 32), the packed words of 4 adjacent columns; a word is 8 consecutive k of one
 //     column, i.e. one lane's B operand of the 32x32x16 MFMA (column = lane % 32).  The word
-//     is unpacked in registers to the fp16 dequantised weights (13 VALU ops) and each B
-//     operand feeds 4 MFMAs (the 4 row tiles); each activation fragment feeds 4 as well
-//     (4.25 VALU ops per MFMA).
+//     is unpacked in registers to the fp16 dequantised weights (16 VALU ops, in the order of k) and each B
+//     operand feeds 4 MFMAs (the 4 row tiles); each activation fragment feeds 4 as well, as it comes from
+//     LDS (4 VALU ops per MFMA).
 //   - Activations are the shared operand: a 128 x 64 (256 x 64) slice of x per stage is copied
 //     once per workgroup straight into a four-slot LDS ring (direct global->LDS loads of whole
 //     128-byte lines, pieces XOR-swizzled so that the 16-byte reads of one k-step spread over
@@ -22,6 +22,12 @@
 //     its loads, barrier) sits inside the last k-step, so the pipeline never drains.
 //   - Loads, waits and the per-stage barrier are explicit (assembly), as in the decode
 //     kernel: two stages stay in flight while one is consumed.
+// What bounds it: below a full chip the issue of instructions, on a full one the power limit.  us per call (M x K x N),
+// with column-major tile numbers -> with one compact run of tiles per XCD -> with the unpack in the order of k, no
+// padded stages (the loop of three used to round a K part of 16 up to 18) and an epilogue that reads one row tile at a
+// time (it used to spill, and every reload waited for the stores under way): 512 x 4096 x 22016 113 -> 111 -> 98,
+// 160 x 8192 x 8192 40.3 -> 40.0 -> 35.3, 1000 x 4096 x 12288 110 -> 109 -> 98, 4096 x 4096 x 4096 131 -> 129 -> 118,
+// 2048 x 8192 x 44032 1375 -> 1346 -> 1255 (1.18 PFLOP/s).
 // Eight waves of 128 x 64 (two per SIMD) needed fewer cycles per MFMA, but the chip then
 // clocked lower under its power limit and the result was a little slower, so one wave per SIMD
 // it is.
@@ -35,26 +41,17 @@ namespace {
 
 constexpr int BK = 64;
 
-// Issue order of the vector instructions of one k-step, in groups of four, for a wave tile of RT x NT
-// MFMA tiles (see the kernel): P<m> and P0' the A operands, S the shifts, AO / ADD / MUL<t> the B
-// operands.  P<m> starts when row tile m - 1's MFMAs do; P0' and the last MUL close the list.
-enum { G_P = 0, G_P0N = 8, G_S = 9, G_AO = 10, G_ADD = G_AO + 4, G_MUL = G_ADD + 4 };
-template <int RT, int NT>
+// The vector instructions of one k-step in issue order, in groups of four: the four steps of the unpack of each of
+// the NT words of the next k-step.
+enum { G_PERM = 0, G_AND = 4, G_ADD = 8, G_MUL = 12 };
+template <int NT>
 struct Order {
-    static constexpr int NG = RT + 1 + 3 * NT;
+    static constexpr int NG = 4 * NT;
     int g[NG];
     constexpr Order() : g()
     {
-        for (int i = 0; i < NG; i++) g[i] = -1;
-        for (int m = 1; m < RT; m++) g[NG * (m - 1) / RT] = G_P + m;
-        g[NG - 2] = G_P0N;
-        g[NG - 1] = G_MUL + NT - 1;
-        int at = 0;
-        auto put = [&](int v) { while (g[at] >= 0) at++; g[at] = v; };
-        put(G_S);
-        for (int t = 0; t < NT; t++) put(G_AO + t);
-        for (int t = 0; t < NT; t++) put(G_ADD + t);
-        for (int t = 0; t + 1 < NT; t++) put(G_MUL + t);
+        for (int i = 0; i < 4; i++)
+            for (int t = 0; t < NT; t++) g[i * NT + t] = 4 * i + t;
     }
 };
 
@@ -153,7 +150,6 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
         for (int t = 0; t < NT; t++)
 #pragma unroll
             for (int r = 0; r < 16; r++) acc[mt][t][r] = 0.f;
-    const UnpackConsts uc = SQP_UNPACK_CONSTS;
 
     struct Stage {
         wvec w[4];    // per k-step: packed words of the lane's NT columns
@@ -162,8 +158,8 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
     };
 
     // The loading side walks the stages with wave-uniform byte pointers that are advanced by
-    // constant strides (scalar adds only); past the last stage they stop, so that the padded
-    // stages of the branch-free loop re-read the last one (cache hits).
+    // constant strides (scalar adds only); past the last stage they stop, so that the look-ahead
+    // of the branch-free stages re-reads the last one (cache hits).
     const long wrow2 = (long)N * 8;        // two packed rows (one k-step) in bytes
     const unsigned char *wq = reinterpret_cast<const unsigned char *>(packed) + (long)stage0 * 4 * wrow2;
     const long prow = G32 ? (long)stage0 * 2 : (long)(stage0 / spg);  // first parameter row of this workgroup
@@ -251,10 +247,10 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
         for (int mt = 0; mt < RT; mt++) asm volatile("" : "+v"(xa[mt]));
     };
 
-    // per-stage constants of the unpack: -(1024 + Z), -(64 + Z) and the step, each in both
-    // halves of a register; a stage past the end gets a step of 0 and adds nothing
-    // (one set per quantisation group of the stage)
-    h16x2 neg_hi[NQ][NT], neg_lo[NQ][NT], delta[NQ][NT];
+    // Per-stage constants of the unpack: (-(1024 + Z), -(64 + Z)) and the step in both halves of a register
+    // (one set per quantisation group of the stage).  A stage past the end (calls of fewer stages than the loop's three)
+    // gets a step of 0 and adds nothing.
+    h16x2 neg[NQ][NT], delta[NQ][NT];
     auto stage_consts = [&](const Stage &s, bool live) {
         const uint32_t sel_even = live ? 0x01000100u : 0x0c0c0c0cu;  // byte selectors of v_perm_b32
         const uint32_t sel_odd = live ? 0x03020302u : 0x0c0c0c0cu;   // (0x0c selects a zero byte)
@@ -263,8 +259,7 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
 #pragma unroll
             for (int t = 0; t < NT; t++) {
                 const uint32_t z = (s.zr[g] >> (8 * t)) & 0xffu;
-                neg_hi[g][t] = neg_hi_of(z);
-                neg_lo[g][t] = neg_lo_of(z);
+                neg[g][t] = neg_pair_of(z);
                 uint32_t sw;
                 if constexpr (NT == 4) sw = s.sc[g][t >> 1]; else sw = s.sc[g];
                 delta[g][t] = __builtin_bit_cast(h16x2, __builtin_amdgcn_perm(sw, sw, (t & 1) ? sel_odd : sel_even));
@@ -280,14 +275,8 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
     // (four slots) and weight registers (three stages) are refilled during stage s with the
     // loads of stage s+2.
     Stage stg[D];
-    u32x4 xa[2][RT];         // raw A fragments from LDS: [k-step parity][row tile]
-    // permuted A operand of row tile m in aq[m % AQ]: never the one that the row tile in front is using,
-    // for row tile 0 of the next k-step behind the last either
-    constexpr int AQ = RT % 2 == 0 ? 2 : 3;
-    uint32_t aq[AQ][4];
+    u32x4 xa[2][RT];         // A operands as they lie in memory: [k-step parity][row tile]
     uint32_t bq[2][NT][4];   // B operands (dequantised weights): [k-step parity][column tile]
-    uint32_t w8[NT];
-    const uint32_t sel_a = 0x05040100u, sel_b = 0x07060302u;  // v_perm_b32 selectors of permute_x
 
     // ---- The instruction stream of one k-step, in issue order, written out by hand.
     // With one wave per SIMD the order of issue is the schedule: measured on this chip, an
@@ -295,52 +284,36 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
     // 32x32x16 MFMA, but one that depends on the instruction just before it costs about 8, and
     // the compiler's own order left many such pairs.  So every MFMA and every vector
     // instruction of the k-step is a volatile asm statement (these keep their order), grouped
-    // so that a result is used no sooner than 4 instructions later:
-    //   MFMA i (row tile i / NT, column tile i % NT), then the next 4-5 entries of the list, e.g. for 4 x 4
-    //     P1, S, AO.., P2, AO.., ADD.., P3, ADD.., MUL.., P0', MUL
-    //   P<m>: 4 perms giving row tile m's A operand (P0': row tile 0 of the NEXT k-step, after
-    //   the wait for its LDS reads); S: word >> 8; AO/ADD/MUL<t>: the and-or, add and multiply
-    //   of the 4 registers of the next k-step's B operand t.
+    // so that a result is used no sooner than 4 instructions later: MFMA i (row tile i / NT, column tile
+    // i % NT), then its share of the unpack of the next k-step's B operands.
+    // The unpack takes each byte of a word to both halves of a register, under the high bytes of 1024.0 and 64.0, and
+    // masks the other nibble of each half out: pairs in the order of k, as the activations have theirs, so that
+    // those go to the matrix core as they come from LDS.  (One shift, four and-ors per word give pairs four apart: 3
+    // instructions less per word, but 4 more per 32 x 16 activations in every wave, 17 to 19 per word and column tile
+    // instead of 16 with 4 x 4 tiles and up to 25 with 6 x 2.)
     // The compiler does not look inside asm statements, so the wait states it would insert
     // are guaranteed by the order itself: vector write -> MFMA read needs 2 (every operand is
     // written >= 4 instructions ahead), vector write -> packed-math read needs 1.
-    auto mfma = [&](f32x16 &c, const uint32_t (&av)[4], const uint32_t (&bv)[4]) {
-        const u32x4 a4 = {av[0], av[1], av[2], av[3]};
+    auto mfma = [&](f32x16 &c, const u32x4 &a4, const uint32_t (&bv)[4]) {
         const u32x4 b4 = {bv[0], bv[1], bv[2], bv[3]};
         asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+a"(c) : "v"(a4), "v"(b4));
     };
-    auto perm4 = [&](uint32_t (&dst)[4], const u32x4 &v, int j) {
-        if (j == 0) asm volatile("v_perm_b32 %0, %1, %2, %3" : "=v"(dst[0]) : "v"(v.z), "v"(v.x), "s"(sel_a));
-        if (j == 1) asm volatile("v_perm_b32 %0, %1, %2, %3" : "=v"(dst[1]) : "v"(v.z), "v"(v.x), "s"(sel_b));
-        if (j == 2) asm volatile("v_perm_b32 %0, %1, %2, %3" : "=v"(dst[2]) : "v"(v.w), "v"(v.y), "s"(sel_a));
-        if (j == 3) asm volatile("v_perm_b32 %0, %1, %2, %3" : "=v"(dst[3]) : "v"(v.w), "v"(v.y), "s"(sel_b));
-    };
-    constexpr Order<RT, NT> order{};
-    constexpr int NG = Order<RT, NT>::NG;
+    constexpr Order<NT> order{};
+    constexpr int NG = Order<NT>::NG;
     constexpr int NMF = RT * NT;                        // MFMAs per k-step
-    constexpr int WAIT_AT = NMF * (NG - 2) / NG - 1;    // the LDS wait goes in front of this MFMA (P0' follows the next)
+    uint32_t high_bytes = PAIR_HIGH_BYTES;
+    asm volatile("" : "+v"(high_bytes));
 
     // one entry j of group g; wn = the packed words of the next k-step, kn = that k-step's
     // position in its stage (it selects the quantisation group's constants)
     auto valu = [&](int g, int j, int cur, const wvec &wn, int kn) {
-        const int nxt = cur ^ 1;
+        const int t = g & 3;
+        uint32_t &b = bq[cur ^ 1][t][j];
         const int qs = G32 ? (kn >> 1) : 0;
-        if (g > G_P && g < G_P0N) perm4(aq[(g - G_P) % AQ], xa[cur][g - G_P], j);
-        else if (g == G_P0N) perm4(aq[0], xa[nxt][0], j);
-        else if (g == G_S) {
-            if (j < NT) asm volatile("v_lshrrev_b32 %0, 8, %1" : "=v"(w8[j]) : "v"(wn[j]));
-        } else if (g < G_ADD) {
-            const int t = g - G_AO;
-            if (j & 1) asm volatile("v_and_or_b32 %0, %1, %2, %3" : "=v"(bq[nxt][t][j]) : "v"(j < 2 ? wn[t] : w8[t]), "v"(uc.mask_hi), "v"(uc.magic_hi));
-            else       asm volatile("v_and_or_b32 %0, %1, %2, %3" : "=v"(bq[nxt][t][j]) : "v"(j < 2 ? wn[t] : w8[t]), "v"(uc.mask_lo), "v"(uc.magic_lo));
-        } else if (g < G_MUL) {
-            const int t = g - G_ADD;
-            if (j & 1) asm volatile("v_pk_add_f16 %0, %0, %1" : "+v"(bq[nxt][t][j]) : "v"(neg_lo[qs][t]));
-            else       asm volatile("v_pk_add_f16 %0, %0, %1" : "+v"(bq[nxt][t][j]) : "v"(neg_hi[qs][t]));
-        } else {
-            const int t = g - G_MUL;
-            asm volatile("v_pk_mul_f16 %0, %0, %1" : "+v"(bq[nxt][t][j]) : "v"(delta[qs][t]));
-        }
+        if (g < G_AND) asm volatile("v_perm_b32 %0, %1, %2, %3" : "=v"(b) : "v"(high_bytes), "v"(wn[t]), "s"(PAIR_SELECT + 0x00010001u * j));
+        else if (g < G_ADD) asm volatile("v_and_b32 %0, %1, %0" : "+v"(b) : "s"(PAIR_MASK));
+        else if (g < G_MUL) asm volatile("v_pk_add_f16 %0, %0, %1" : "+v"(b) : "v"(neg[qs][t]));
+        else asm volatile("v_pk_mul_f16 %0, %0, %1" : "+v"(b) : "v"(delta[qs][t]));
     };
 
     issue_w(stg[0]);
@@ -355,108 +328,128 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
     asm volatile("s_barrier" ::: "memory");
     stage_consts(stg[0], true);
     read_a(xa[0], 0, 0);
-    // first operands of the pipeline, by the ordinary helpers
+    // first operands of the pipeline, by the ordinary helper
 #pragma unroll
     for (int t = 0; t < NT; t++) {
-        const u32x4 bw = __builtin_bit_cast(u32x4, dequant_word_scaled(stg[0].w[0][t], neg_hi[0][t], neg_lo[0][t], delta[0][t], uc));
+        const u32x4 bw = __builtin_bit_cast(u32x4, dequant_word_pairs(stg[0].w[0][t], neg[0][t], delta[0][t]));
         bq[0][t][0] = bw.x; bq[0][t][1] = bw.y; bq[0][t][2] = bw.z; bq[0][t][3] = bw.w;
     }
     wait_a(xa[0]);
-    {
-        const u32x4 a0 = __builtin_bit_cast(u32x4, permute_x(xa[0][0]));
-        aq[0][0] = a0.x; aq[0][1] = a0.y; aq[0][2] = a0.z; aq[0][3] = a0.w;
-    }
     asm volatile("s_nop 3" ::: "memory");  // compiler-issued vector writes above -> asm MFMA reads below
 
     int slot = 0;  // ring slot of the stage being consumed
-    const int nblk = (stages + D - 1) / D;
-    for (int blk = 0; blk < nblk; blk++) {
+    // One stage, with the registers of its place in the ring of D.
+    auto stage = [&](auto place) {
+        constexpr int d = decltype(place)::value;
+        Stage &cur_s = stg[d];
+        Stage &next_s = stg[(d + 1) % D];
+        Stage &fill_s = stg[(d + 2) % D];
+        const int slot_next = (slot + 1) & (XD - 1), slot_fill = (slot + 2) & (XD - 1);
+        issue_w(fill_s);
 #pragma unroll
-        for (int d = 0; d < D; d++) {
-            const int st = blk * D + d;
-            Stage &cur_s = stg[d];
-            Stage &next_s = stg[(d + 1) % D];
-            Stage &fill_s = stg[(d + 2) % D];
-            const int slot_next = (slot + 1) & (XD - 1), slot_fill = (slot + 2) & (XD - 1);
-            issue_w(fill_s);
+        for (int ks = 0; ks < 4; ks++) {
+            const int cur = ks & 1, nxt = cur ^ 1;
 #pragma unroll
-            for (int ks = 0; ks < 4; ks++) {
-                const int cur = ks & 1, nxt = cur ^ 1;
-#pragma unroll
-                for (int j = OX * ks / 4; j < OX * (ks + 1) / 4; j++) issue_x(slot_fill, j);
-                if (ks < 3) {
-                    read_a(xa[nxt], slot, ks + 1);
-                } else {
-                    advance();
-                    landed(next_s, std::integral_constant<int, OX + OW>());
-                    asm volatile("s_barrier" ::: "memory");
-                    stage_consts(next_s, st + 1 < stages);
-                    read_a(xa[nxt], slot_next, 0);
-                }
-                const wvec wn = ks < 3 ? cur_s.w[ks + 1] : next_s.w[0];
-#pragma unroll
-                for (int i = 0; i < NMF; i++) {
-                    if (i == WAIT_AT) wait_a(xa[nxt]);
-                    mfma(acc[i / NT][i % NT], aq[(i / NT) % AQ], bq[cur][i % NT]);
-#pragma unroll
-                    for (int e = i * (4 * NG) / NMF; e < (i + 1) * (4 * NG) / NMF; e++)
-                        valu(order.g[e / 4], e % 4, cur, wn, (ks + 1) & 3);
-                }
+            for (int j = OX * ks / 4; j < OX * (ks + 1) / 4; j++) issue_x(slot_fill, j);
+            if (ks < 3) {
+                read_a(xa[nxt], slot, ks + 1);
+            } else {
+                advance();
+                landed(next_s, std::integral_constant<int, OX + OW>());
+                asm volatile("s_barrier" ::: "memory");
+                stage_consts(next_s, d == D - 1 || stages > d + 1);
+                read_a(xa[nxt], slot_next, 0);
             }
-            // End of the last iteration.  (1) Drain the clamped look-ahead loads: their
-            // destination registers are dead as far as the compiler can tell, but the hardware
-            // still writes them when the data arrives, so the empty uses keep every stage
-            // allocated until the wait has completed.  (2) The compiler does not know that the
-            // asm statements above wrote the accumulators with MFMAs, so it will not insert the
-            // wait states a matrix result needs before another instruction may read it (up to
-            // 18); the epilogue's reads follow the loop directly, so they are spent here.
-            if (d == D - 1 && blk == nblk - 1) {
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            const wvec wn = ks < 3 ? cur_s.w[ks + 1] : next_s.w[0];
 #pragma unroll
-                for (int j = 0; j < D; j++) {
+            for (int i = 0; i < NMF; i++) {
+                mfma(acc[i / NT][i % NT], xa[cur][i / NT], bq[cur][i % NT]);
 #pragma unroll
-                    for (int ks = 0; ks < 4; ks++) asm volatile("" ::"v"(stg[j].w[ks]));
-#pragma unroll
-                    for (int g = 0; g < NQ; g++) {
-                        asm volatile("" ::"v"(stg[j].sc[g]));
-                        asm volatile("" ::"v"(stg[j].zr[g]));
-                    }
-                }
-                asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+                for (int e = i * (4 * NG) / NMF; e < (i + 1) * (4 * NG) / NMF; e++)
+                    valu(order.g[e / 4], e % 4, cur, wn, (ks + 1) & 3);
             }
-            slot = slot_next;
+            wait_a(xa[nxt]);
+        }
+        slot = slot_next;
+    };
+    // The compiler does not know that the asm statements above wrote the accumulators with MFMAs, so it will not insert the
+    // wait states a matrix result needs before another instruction may read it (up to 18): they are spent wherever
+    // control flow ends a run of stages (there the compiler may copy accumulators; the build checks that it does not do
+    // so earlier).
+    auto settle = [&]() {
+        asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[0][0]), "+a"(acc[0][1]), "+a"(acc[1][0]), "+a"(acc[1][1]), "+a"(acc[2][0]), "+a"(acc[2][1]));
+#pragma unroll
+        for (int i = 0; i < NMF; i++)
+            if (i / NT > 2 || i % NT > 1) asm volatile("" : "+a"(acc[i / NT][i % NT]));
+    };
+    typedef std::integral_constant<int, 0> First;
+    typedef std::integral_constant<int, 1> Second;
+    typedef std::integral_constant<int, 2> Third;
+    int blocks = stages < D ? 1 : stages / D;
+    do {
+        stage(First());
+        stage(Second());
+        stage(Third());
+    } while (--blocks > 0);
+    settle();
+    if (stages > D && stages % D > 0) {
+        stage(First());
+        settle();
+        if (stages % D > 1) {
+            stage(Second());
+            settle();
+        }
+    }
+    // Drain the clamped look-ahead loads: their destination registers are dead as far as the compiler can
+    // tell, but the hardware still writes them when the data arrives, so the empty uses keep every stage
+    // allocated until the wait has completed.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int j = 0; j < D; j++) {
+#pragma unroll
+        for (int ks = 0; ks < 4; ks++) asm volatile("" ::"v"(stg[j].w[ks]));
+#pragma unroll
+        for (int g = 0; g < NQ; g++) {
+            asm volatile("" ::"v"(stg[j].sc[g]));
+            asm volatile("" ::"v"(stg[j].zr[g]));
         }
     }
 
     // epilogue: accumulator register r of tile (mt, t): row 8*(r/4) + 4*(lane/32) + r%4 of the
     // 32-row tile, column NT*(lane%32) + t of the wave's 32*NT
+    // (`ready` in front of each row tile's stores: the compiler would otherwise read all accumulators first, spill, and
+    // wait for the stores under way wherever it reloads: 7 us of a 130 us launch.)
+    auto ready = [&](int mt) {
+#pragma unroll
+        for (int t = 0; t < NT; t++) asm volatile("" : "+v"(acc[mt][t])::"memory");
+    };
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int e_l32 = tid & 31, e_kb = (tid >> 5) & 1, e_wave = tid >> 6;
     const int nloc = (e_wave % WNW) * WN + NT * e_l32;   // first column within the tile
     const int nout = nbase + nloc;
     const int mloc0 = (e_wave / WNW) * 32 * RT + 4 * e_kb, mrow0 = m0 + mloc0;
-    if (part != nullptr) {
+    if (NT == 2 && part != nullptr) {  // (launches in K parts are of half-width tiles)
         float *ptile = part + (size_t)place * (BM * WGN) + nloc;
 #pragma unroll
-        for (int mt = 0; mt < RT; mt++)
+        for (int mt = 0; mt < RT; mt++) {
+            ready(mt);
 #pragma unroll
             for (int r = 0; r < 16; r++) {
                 const int mo = mt * 32 + 8 * (r >> 2) + (r & 3);
                 if (mrow0 + mo < M && nout < N) {
                     float *p = ptile + (size_t)(mloc0 + mo) * WGN;
-                    if constexpr (NT == 4)
-                        *reinterpret_cast<f32x4 *>(p) = f32x4{acc[mt][0][r], acc[mt][1][r], acc[mt][2][r], acc[mt][3][r]};
-                    else
-                        *reinterpret_cast<float2 *>(p) = make_float2(acc[mt][0][r], acc[mt][1][r]);
+                    *reinterpret_cast<float2 *>(p) = make_float2(acc[mt][0][r], acc[mt][1][r]);
                 }
             }
+        }
         return;
     }
     if (nout < N) {
         h16 *ycol = y + nout;
 #pragma unroll
-        for (int mt = 0; mt < RT; mt++)
+        for (int mt = 0; mt < RT; mt++) {
+            ready(mt);
 #pragma unroll
             for (int r = 0; r < 16; r++) {
                 const int m = mrow0 + mt * 32 + 8 * (r >> 2) + (r & 3);
@@ -484,6 +477,7 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
                     }
                 }
             }
+        }
     }
 }
 

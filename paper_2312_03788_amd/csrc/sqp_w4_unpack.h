@@ -68,3 +68,23 @@ __device__ __forceinline__ h16x8 permute_x(const u32x4 &v)
     p.w = __builtin_amdgcn_perm(v.w, v.y, 0x07060302u);  // (x3, x7)
     return __builtin_bit_cast(h16x8, p);
 }
+
+// The unpack in the order of k, for kernels in which many waves read the same activations (those then need no
+// permutation): byte i of a word holds the codes of k = 2 i and 2 i + 1.  v_perm_b32 puts it under the high bytes of
+// 1024.0 and 64.0, one AND clears the other nibble of each half, and the offsets 1024 + Z and 64 + Z go with one exact
+// packed add.
+constexpr uint32_t PAIR_HIGH_BYTES = 0x54006400u, PAIR_MASK = 0xfff0ff0fu;
+constexpr uint32_t PAIR_SELECT = 0x07000500u;  // + 0x00010001 i: (byte i of the word, its high byte), twice
+__device__ __forceinline__ h16x2 neg_pair_of(uint32_t z) { return __builtin_bit_cast(h16x2, z * 0x00100001u + 0xd400e400u); }
+
+// packed word -> the fp16 dequantised weights fp16((code - Z) * Delta) of k = 0 .. 7, neg = neg_pair_of(Z).
+__device__ __forceinline__ h16x8 dequant_word_pairs(uint32_t w, h16x2 neg, h16x2 delta)
+{
+    u32x4 r;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const uint32_t t = __builtin_amdgcn_perm(PAIR_HIGH_BYTES, w, PAIR_SELECT + 0x00010001u * i) & PAIR_MASK;
+        r[i] = __builtin_bit_cast(uint32_t, (__builtin_bit_cast(h16x2, t) + neg) * delta);
+    }
+    return __builtin_bit_cast(h16x8, r);
+}

@@ -231,6 +231,22 @@ def test_prefill_tile_heights(orc, sqp, M, K, N, group, rt, nt, parts):
     assert np.array_equal(y0.view(np.uint16), y1.view(np.uint16))
 
 
+@pytest.mark.parametrize("rt,nt", [(3, 2), (4, 2), (4, 4), (5, 2), (6, 2)])
+@pytest.mark.parametrize("stages", [1, 2, 3, 4, 5, 7])
+def test_prefill_few_stages(orc, sqp, rt, nt, stages):
+    """Every remainder of the loop over three stages of 64 k, and calls of fewer, at each tile size, on grids of tiles
+    that do not divide among the eight XCDs nor into equal groups of tile rows (9 or more rows of tiles)."""
+    M, K, N = 9 * 32 * rt - 5, 64 * stages, 392
+    print("case few stages", M, K, N, rt, nt, flush=True)
+    xs, p, sc, z = _layer(orc, M, K, N, 64)
+    L = sqp.lib()
+    L.sqp_debug_set_prefill_variant(rt, nt, 1)
+    try:
+        _check(orc, sqp, xs, p, sc, z, 64)
+    finally:
+        L.sqp_debug_set_prefill_variant(0, 0, 0)
+
+
 def test_prefill_left_over_k_parts(orc, sqp):
     """A grid of one full round and a few tiles, K long enough that the left-over half-width tiles are
     split in K too (M = 2050, N = 8144: 17 x 16 = 272 tiles).  Sampled rows against the oracle, from
