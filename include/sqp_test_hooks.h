@@ -45,7 +45,8 @@ void sqp_debug_set_prefill_tiles(int mode);        /* 0 = automatic, 1 = full ti
 void sqp_debug_set_prefill_shape(int shape);       /* 0 = automatic, 1 = 128 x 512 full tiles, 2 = 256 x 256 */
 void sqp_debug_set_prefill_ksplit(int k);          /* -1 = automatic, 0 or 1 = never, k >= 2 = k parts */
 void sqp_debug_set_prefill_variant(int rt, int nt, int parts);  /* one launch of tiles of 32 rt rows x 128 nt columns, K parts
-                                                      (rt 3 to 6 with nt 2, or 4 with nt 4; parts > 1 with nt 2); 0 = automatic */
+                                                      (rt 3 to 6 with nt 2, or 4 with nt 4; parts > 1 with nt 2; nt 2 + 16:
+                                                      half the columns, the waves halve K, K % 128 == 0); 0 = automatic */
 /* The plan in 128-row tiles for a shape on a chip of `cus` compute units: full tiles of the first
  * launch, half-width tiles of the second, K parts.  Host arithmetic only. */
 void sqp_debug_prefill_plan(int M, int N, int K, int cus, long *full, long *half, int *ksplit);
@@ -62,10 +63,14 @@ void sqp_debug_row_blocks(int M, int N, int K, int group, int cus, int workspace
  * buffers of sqp_alpha_search.  Host arithmetic only. */
 void sqp_debug_search_plan(int T, int N, int K, int group, int n_alpha, size_t bytes, int *out3);
 
-/* What a call launches: returns the number of launches (1 or 2) and their (rt, nt, tiles, K parts) in
- * out8.  The plan above, or one round of tiles of another height where that is faster, and with K
+/* The launches that a call's workspace and scratch sizes are reported for: returns their number (1 or 2) and their
+ * (rt, nt, tiles, K parts) in out8.  The plan above, or one round of tiles of another height where that is faster, and with K
  * parts for few left-over tiles; workspace and scratch as large as it likes.  Host arithmetic only. */
 int sqp_debug_prefill_launches(int M, int N, int K, int group, int cus, int *out8);
+
+/* What a call launches in their place with `room` bytes for its K parts (workspace or its own scratch, whichever the
+ * shape uses): as above, with (rt, nt, tiles, K parts, 2 where the waves halve K) in out10. */
+int sqp_debug_prefill_choice(int M, int N, int K, int group, int cus, size_t room, int *out10);
 
 /* Calibration kernels for the benchmark: a plain device copy of `bytes` (a multiple of 16)
  * whose traffic is known, and a loop of nothing but independent 32x32x16 fp16 matrix

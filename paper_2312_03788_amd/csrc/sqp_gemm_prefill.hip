@@ -57,9 +57,11 @@ struct Order {
 
 // Which tile a workgroup takes.  The tiles are numbered in groups of up to gm rows of tiles, row index fastest
 // within a column, so that consecutive numbers are compact blocks; workgroups are dealt to the eight XCDs in turn, so
-// each XCD gets one run of consecutive numbers (of all K parts: tiles of one part first).  The workgroups that an
-// XCD has resident then share its L2: of a stage's 16 KB of activations and 16 KB of weights per 128 x 512 tile
+// each XCD gets one run of consecutive numbers.  The workgroups that an XCD has resident then share its L2: of a stage's 16 KB of activations and 16 KB of weights per 128 x 512 tile
 // it fetches 12 blocks for 32 tiles (8 rows x 4 columns) instead of about 35 with column-major numbers over all XCDs.
+// Launches in K parts keep the tiles dealt over all XCDs, a part behind the other: with runs they are up to 3 us slower
+// (328x6208x1168 19.2 -> 21.9 with the tiles of a part together, 18.4 with the parts of a tile; 196x3136x3320 21.3 ->
+// 22.7, 22.4) and nothing faster (160x8192x8192 33.0 -> 32.9, 33.1).
 struct TileMap {
     int tile0;   // number of the launch's first tile
     int tn, tm;  // columns and rows of tiles
@@ -68,7 +70,7 @@ struct TileMap {
 };
 constexpr int XCDS = 8;
 
-// Workgroup w of `total` (a launch's linear index): its place when every XCD has one run.
+// Workgroup w of `total`: its place when every XCD has one run.
 __device__ __forceinline__ uint32_t xcd_run(uint32_t w, uint32_t total)
 {
     const uint32_t xcd = w % XCDS, len = total / XCDS, more = total % XCDS;
@@ -96,48 +98,51 @@ __device__ __forceinline__ void tile_at(const TileMap &m, uint32_t i, int &row, 
 //           the K-split launches.
 //   <3, 2, 1>, <5, 2, 1>, <6, 2, 1>: 96, 160 or 192 rows x 256 columns, K-split launches of row
 //           counts that would leave much of a 128-row tile empty.
+// KH = 2: the waves of a column pair halve K between them, stage by stage (a stage is 128 k then), and add their sums
+// through LDS at the end: tiles of half the columns in half as many K parts (see plan_launches).
 // G32: quantisation groups of 32 rows, i.e. two groups per 64-row stage (the steps and zero
 // points of both are loaded per stage and the unpack switches sets after the second k-step);
 // otherwise the group is a multiple of 64 rows.
-template <int RT, int NT, int WM, bool G32>
-__global__ void __launch_bounds__(256)
+template <int RT, int NT, int WM, int KH, bool G32>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KH == 1 && NT == 2 && RT <= 4 && WM == 1 ? 2 : 1)))
 w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__restrict__ x,
                      const uint32_t *__restrict__ packed, const h16 *__restrict__ scales,
                      const uint8_t *__restrict__ zeros, h16 *__restrict__ y, float *__restrict__ part, int epi)
 {
     constexpr int W = 4;                   // waves: one per SIMD
-    constexpr int WNW = W / WM;            // waves along the columns
+    constexpr int WNW = W / WM / KH;       // waves along the columns
     constexpr int BM = 32 * RT * WM;       // rows per workgroup
     constexpr int WN = 32 * NT;            // columns per wave
     static_assert(NT == 2 || NT == 4, "a lane's columns are one load");
+    static_assert(KH == 1 || (WM == 1 && !G32), "waves that halve K");
     typedef uint32_t wvec __attribute__((ext_vector_type(NT)));
     typedef std::conditional_t<NT == 4, u32x2, uint32_t> scvec;
     constexpr int D = 3;                   // register stages of packed weights (two in flight)
-    constexpr int XD = 4;                  // LDS slots of activations
-    constexpr int XSTAGE = BM * BK * 2;    // blocks of 8 rows x 128 bytes
-    constexpr int OX = (BM / 8) / W;       // direct loads per wave per stage (one per 1 KB block), spread over its four k-steps
+    constexpr int XD = KH == 1 ? 4 : 3;    // LDS slots of activations
+    constexpr int XHALF = BM * BK * 2;     // 64 k of activations: blocks of 8 rows x 128 bytes
+    constexpr int XSTAGE = KH * XHALF;
+    constexpr int OX = KH * (BM / 8) / W;  // direct loads per wave per stage (one per 1 KB block), spread over its four k-steps
     constexpr int WGN = WNW * WN;          // columns per workgroup
     constexpr int NQ = G32 ? 2 : 1;        // quantisation groups per stage
     constexpr int OW = 4 + 2 * NQ;
     static_assert(2 * (OX + OW) < 64, "vmcnt field");
     __shared__ __attribute__((aligned(1024))) unsigned char xring[XD * XSTAGE];
+    static_assert(sizeof(xring) <= 160 * 1024, "LDS of a workgroup");
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wm = wave / WNW, wn = wave % WNW;
+    const int wm = KH == 1 ? wave / WNW : 0, wn = wave % WNW, kh = KH == 1 ? 0 : wave / WNW;
     const int l32 = lane & 31, kb = lane >> 5;
     // K split across gridDim.y workgroups (part != nullptr): this one takes stages
-    // [stage0, stage0 + stages) and leaves its fp32 sums in part[kpart][launch's tile][BM][WGN].
-    const uint32_t place = xcd_run(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
-    const uint32_t kpart = gridDim.y == 1 ? 0 : place / gridDim.x;
+    // [stage0, stage0 + stages) and leaves its fp32 sums in part[blockIdx.y][blockIdx.x][BM][WGN].
     int trow, tcol;
-    tile_at(map, place - kpart * gridDim.x, trow, tcol);
+    tile_at(map, gridDim.y == 1 ? xcd_run(blockIdx.x, gridDim.x) : blockIdx.x, trow, tcol);
     const int nbase = tcol * WGN;
     const int m0 = trow * BM;
     const int n0 = nbase + wn * WN;
-    const int stages_all = K / BK;
-    const int stage0 = (int)((uint32_t)stages_all * kpart / gridDim.y);
-    const int stages = (int)((uint32_t)stages_all * (kpart + 1) / gridDim.y) - stage0;
+    const int stages_all = K / (BK * KH);
+    const int stage0 = (int)((uint32_t)stages_all * blockIdx.y / gridDim.y);
+    const int stages = (int)((uint32_t)stages_all * (blockIdx.y + 1) / gridDim.y) - stage0;
     const int spg = G32 ? 1 : group / BK;  // stages per quantisation group (G32: two groups per stage)
 
     int ncol = n0 + NT * l32;
@@ -161,12 +166,13 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
     // constant strides (scalar adds only); past the last stage they stop, so that the look-ahead
     // of the branch-free stages re-reads the last one (cache hits).
     const long wrow2 = (long)N * 8;        // two packed rows (one k-step) in bytes
-    const unsigned char *wq = reinterpret_cast<const unsigned char *>(packed) + (long)stage0 * 4 * wrow2;
-    const long prow = G32 ? (long)stage0 * 2 : (long)(stage0 / spg);  // first parameter row of this workgroup
+    const unsigned char *wq = reinterpret_cast<const unsigned char *>(packed) + (long)(stage0 * KH + kh) * 4 * wrow2;
+    const long prow = G32 ? (long)stage0 * 2 : (long)((stage0 * KH + kh) / spg);  // first parameter row of this wave
+    const int prow_step = KH / spg, kin_step = KH % spg;  // groups and part of one that a stage advances by
     const unsigned char *sq = reinterpret_cast<const unsigned char *>(scales) + prow * N * 2;
     const unsigned char *zq = zeros + prow * N;
-    const unsigned char *xq = reinterpret_cast<const unsigned char *>(x) + (long)stage0 * (BK * 2);
-    int ist = 0, kin = stage0 % spg;        // stage being issued (relative), its position inside its group
+    const unsigned char *xq = reinterpret_cast<const unsigned char *>(x) + (long)stage0 * (KH * BK * 2);
+    int ist = 0, kin = (stage0 * KH + kh) % spg;        // stage being issued (relative), its position inside its group
     const uint32_t voff_w = (uint32_t)(kb * N + ncol) * 4u;
     const uint32_t voff_s = (uint32_t)ncol * 2u, voff_z = (uint32_t)ncol;
     auto issue_w = [&](Stage &s) {
@@ -207,12 +213,12 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
     uint32_t xoff[OX];
 #pragma unroll
     for (int j = 0; j < OX; j++) {
-        const int b = wave + W * j;
+        const int b = (wave + W * j) % (BM / 8);  // (KH == 2: the blocks of the second 64 k follow those of the first)
         const int row = b * 8 + (lane >> 3);
         int grow = m0 + row;
         if (grow >= M) grow = M - 1;
         const int piece = (lane & 7) ^ ((row >> 1) & 7);
-        xoff[j] = (uint32_t)grow * (uint32_t)K * 2u + (uint32_t)(piece * 16);
+        xoff[j] = (uint32_t)grow * (uint32_t)K * 2u + (uint32_t)((wave + W * j) / (BM / 8) * (BK * 2) + piece * 16);
     }
     auto issue_x = [&](int slot, int j) {
         unsigned char *dst = xring + slot * XSTAGE + (wave + W * j) * 1024;
@@ -223,16 +229,25 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
     auto advance = [&]() {
         const bool more = ist + 1 < stages;
         ist += more ? 1 : 0;
-        wq += more ? 4 * wrow2 : 0;
-        xq += more ? BK * 2 : 0;
-        kin += more ? 1 : 0;
-        const bool wrap = kin == spg;
-        kin = wrap ? 0 : kin;
-        sq += wrap ? (long)N * 2 * NQ : 0;
-        zq += wrap ? (long)N * NQ : 0;
+        wq += more ? KH * 4 * wrow2 : 0;
+        xq += more ? KH * BK * 2 : 0;
+        if constexpr (KH == 1) {
+            kin += more ? 1 : 0;
+            const bool wrap = kin == spg;
+            kin = wrap ? 0 : kin;
+            sq += wrap ? (long)N * 2 * NQ : 0;
+            zq += wrap ? (long)N * NQ : 0;
+        } else if (more) {
+            kin += kin_step;
+            const bool wrap = kin >= spg;
+            kin -= wrap ? spg : 0;
+            const int rows = prow_step + (wrap ? 1 : 0);
+            sq += (long)rows * N * 2;
+            zq += (long)rows * N;
+        }
     };
     const uint32_t xrd0 = (uint32_t)(size_t)xring +
-                          (uint32_t)(((wm * 32 * RT + l32) >> 3) * 1024 + ((wm * 32 * RT + l32) & 7) * 128);
+                          (uint32_t)(kh * XHALF + ((wm * 32 * RT + l32) >> 3) * 1024 + ((wm * 32 * RT + l32) & 7) * 128);
     const int xkey = (l32 >> 1) & 7;
 
     auto read_a = [&](u32x4 (&xa)[RT], int slot, int ks) {
@@ -270,10 +285,10 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
     // issue, the A fragments of the next k-step come from LDS and the next weight word is
     // unpacked.  The hand-over to the next stage happens inside the last k-step of a stage
     // (wait for the next stage's loads, barrier, new constants), so the first LDS reads and
-    // the first unpack of a stage are hidden like any other.  Ring discipline: the barrier in
-    // the last k-step of stage s-1 proves every wave has finished stage s-2, whose LDS slot
-    // (four slots) and weight registers (three stages) are refilled during stage s with the
-    // loads of stage s+2.
+    // the first unpack of a stage are hidden like any other.  Ring discipline: at the barrier in
+    // the last k-step of stage s-1 every wave has that stage's last fragments in registers, so its LDS
+    // slot (three are enough; four where they fit anyway) and weight registers (three stages) may be refilled during
+    // stage s with the loads of stage s+2.
     Stage stg[D];
     u32x4 xa[2][RT];         // A operands as they lie in memory: [k-step parity][row tile]
     uint32_t bq[2][NT][4];   // B operands (dequantised weights): [k-step parity][column tile]
@@ -344,7 +359,7 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
         Stage &cur_s = stg[d];
         Stage &next_s = stg[(d + 1) % D];
         Stage &fill_s = stg[(d + 2) % D];
-        const int slot_next = (slot + 1) & (XD - 1), slot_fill = (slot + 2) & (XD - 1);
+        const int slot_next = slot + 1 < XD ? slot + 1 : 0, slot_fill = slot + 2 < XD ? slot + 2 : slot + 2 - XD;
         issue_w(fill_s);
 #pragma unroll
         for (int ks = 0; ks < 4; ks++) {
@@ -423,16 +438,48 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
 #pragma unroll
         for (int t = 0; t < NT; t++) asm volatile("" : "+v"(acc[mt][t])::"memory");
     };
+    if constexpr (KH == 2) {
+        // The two waves of a column pair finish every other row tile each: sums of the first half + of the second.
+        f32x4 *ex = reinterpret_cast<f32x4 *>(xring) + (size_t)wn * (RT * NT * 4 * 64) + lane;
+        static_assert(WNW * RT * NT * 4096 <= sizeof(xring), "the exchange reuses the ring");
+        asm volatile("s_barrier" ::: "memory");  // (all loads into LDS have landed, all reads of it too)
+#pragma unroll
+        for (int mt = 0; mt < RT; mt++) {
+            ready(mt);
+            if ((mt & 1) != kh) {
+#pragma unroll
+                for (int t = 0; t < NT; t++)
+#pragma unroll
+                    for (int q = 0; q < 4; q++)
+                        ex[((mt * NT + t) * 4 + q) * 64] = f32x4{acc[mt][t][4 * q], acc[mt][t][4 * q + 1], acc[mt][t][4 * q + 2], acc[mt][t][4 * q + 3]};
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int mt = 0; mt < RT; mt++)
+            if ((mt & 1) == kh) {
+#pragma unroll
+                for (int t = 0; t < NT; t++)
+#pragma unroll
+                    for (int q = 0; q < 4; q++) {
+                        const f32x4 v = ex[((mt * NT + t) * 4 + q) * 64];
+#pragma unroll
+                        for (int r = 0; r < 4; r++) acc[mt][t][4 * q + r] += v[r];
+                    }
+            }
+    }
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int e_l32 = tid & 31, e_kb = (tid >> 5) & 1, e_wave = tid >> 6;
+    auto mine = [&](int mt) { return KH == 1 || (mt & 1) == kh; };  // wave-uniform
     const int nloc = (e_wave % WNW) * WN + NT * e_l32;   // first column within the tile
     const int nout = nbase + nloc;
-    const int mloc0 = (e_wave / WNW) * 32 * RT + 4 * e_kb, mrow0 = m0 + mloc0;
+    const int mloc0 = (KH == 1 ? e_wave / WNW : 0) * 32 * RT + 4 * e_kb, mrow0 = m0 + mloc0;
     if (NT == 2 && part != nullptr) {  // (launches in K parts are of half-width tiles)
-        float *ptile = part + (size_t)place * (BM * WGN) + nloc;
+        float *ptile = part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * (BM * WGN) + nloc;
 #pragma unroll
         for (int mt = 0; mt < RT; mt++) {
+            if (!mine(mt)) continue;
             ready(mt);
 #pragma unroll
             for (int r = 0; r < 16; r++) {
@@ -449,6 +496,7 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
         h16 *ycol = y + nout;
 #pragma unroll
         for (int mt = 0; mt < RT; mt++) {
+            if (!mine(mt)) continue;
             ready(mt);
 #pragma unroll
             for (int r = 0; r < 16; r++) {
@@ -625,7 +673,9 @@ struct TileLaunch {
     long tile0, tiles;
     int tn, parts;
     bool halves;
+    int kh;  // 2: waves that halve K, tiles of half the columns
 };
+static int tile_columns(const TileLaunch &l, int wm) { return l.nt * 128 / wm / l.kh; }
 struct LaunchPlan {
     int wm, count;
     bool own;  // K parts go to the call's own scratch, not to the workspace
@@ -633,17 +683,18 @@ struct LaunchPlan {
 };
 
 // Test hook: one launch of this variant over the whole output (0: automatic).
-static int g_force_rt = 0, g_force_nt = 0, g_force_parts = 0;
+static int g_force_rt = 0, g_force_nt = 0, g_force_parts = 0, g_force_kh = 1;
 extern "C" void sqp_debug_set_prefill_variant(int rt, int nt, int parts)
 {
     g_force_rt = rt;
-    g_force_nt = nt;
+    g_force_nt = nt & 15;
+    g_force_kh = nt >= 16 ? 2 : 1;
     g_force_parts = parts;
 }
 
 static size_t launch_partial_bytes(const TileLaunch &l, int wm)
 {
-    return l.parts >= 2 ? (size_t)l.parts * l.tiles * (32 * l.rt * wm) * (l.nt * 128 / wm) * sizeof(float) : 0;
+    return l.parts >= 2 ? (size_t)l.parts * l.tiles * (32 * l.rt * wm) * tile_columns(l, wm) * sizeof(float) : 0;
 }
 
 // room_ws, room_own: bytes there are for partial sums in the workspace and in the call's own scratch (0:
@@ -661,13 +712,14 @@ static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, size_t 
     LaunchPlan q = {p.wm, 0, own, {}};
     const int stages = K / BK, tnf = (N + (4 / p.wm) * 128 - 1) / ((4 / p.wm) * 128);
     if (g_force_rt > 0 && group != 32) {
-        const int wg = 128 * g_force_nt;
+        const int kh = g_force_kh == 2 && g_force_nt == 2 && K % (2 * BK) == 0 ? 2 : 1;
+        const int wg = 128 * g_force_nt / kh;
         const int tn = (N + wg - 1) / wg, tm = (M + 32 * g_force_rt - 1) / (32 * g_force_rt);
         q.wm = 1;
         q.count = 1;
         int parts = g_force_nt == 2 && have_workspace ? g_force_parts : 1;
-        if (parts > stages) parts = stages;
-        q.l[0] = TileLaunch{g_force_rt, g_force_nt, 0, (long)tn * tm, tn, parts < 1 ? 1 : parts, false};
+        if (parts > stages / kh) parts = stages / kh;
+        q.l[0] = TileLaunch{g_force_rt, g_force_nt, 0, (long)tn * tm, tn, parts < 1 ? 1 : parts, false, kh};
         return q;
     }
     const bool hooked = g_tile_mode != 0 || g_tile_shape != 0 || g_ksplit >= 0;
@@ -691,7 +743,7 @@ static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, size_t 
             best = stages * 1.43;
             q.wm = 1;
             q.count = 1;
-            q.l[0] = TileLaunch{4, 4, 0, tiles44, (N + 511) / 512, 1, false};
+            q.l[0] = TileLaunch{4, 4, 0, tiles44, (N + 511) / 512, 1, false, 1};
         }
         const int tn = (N + 255) / 256;
         for (int rt = 3; rt <= 6; rt++) {
@@ -702,7 +754,7 @@ static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, size_t 
             if (tiles > cus) continue;
             for (int parts = 1; parts <= (most > 1 ? most : 1); parts++) {
                 const double t = (stages + parts - 1) / parts * stage_us[rt] + (parts > 1 ? parts * part_us : 0.0);
-                const TileLaunch l = {rt, 2, 0, tiles, tn, parts, false};
+                const TileLaunch l = {rt, 2, 0, tiles, tn, parts, false, 1};
                 if (launch_partial_bytes(l, 1) <= room && (q.count == 0 || t < best)) {
                     best = t;
                     q.count = 1;
@@ -712,10 +764,10 @@ static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, size_t 
         }
         if (q.count) return q;
     }
-    if (p.full > 0) q.l[q.count++] = TileLaunch{4, 4, 0, p.full, tnf, 1, false};
+    if (p.full > 0) q.l[q.count++] = TileLaunch{4, 4, 0, p.full, tnf, 1, false, 1};
     if (p.half > 0) {
         int parts = p.ksplit;
-        while (!hooked && parts > 1 && launch_partial_bytes(TileLaunch{4, 2, 0, p.half, 0, parts, true}, p.wm) > room) parts--;
+        while (!hooked && parts > 1 && launch_partial_bytes(TileLaunch{4, 2, 0, p.half, 0, parts, true, 1}, p.wm) > room) parts--;
         // Few tiles left over after the whole rounds: split in K as well, as far as they then fill the
         // chip once.
         if (!hooked && p.full > 0 && have_workspace) {
@@ -726,18 +778,18 @@ static LaunchPlan plan_launches(int M, int N, int K, int group, int cus, size_t 
             double best = stages * 0.77;
             for (int n = 2; n <= most; n++) {
                 const double t = (stages + n - 1) / n * 0.77 + n * part_us + 3;  // (3: the reduction's launch)
-                if (t < best && launch_partial_bytes(TileLaunch{4, 2, 0, p.half, 0, n, true}, 1) <= room) {
+                if (t < best && launch_partial_bytes(TileLaunch{4, 2, 0, p.half, 0, n, true, 1}, 1) <= room) {
                     best = t;
                     parts = n;
                 }
             }
         }
-        q.l[q.count++] = TileLaunch{4, 2, 2 * p.full, p.half, tnf, parts, true};
+        q.l[q.count++] = TileLaunch{4, 2, 2 * p.full, p.half, tnf, parts, true, 1};
     }
     return q;
 }
 
-// Test hook: the launches of a call (no GPU needed): up to two of (rt, nt, tiles, parts).
+// Test hook: the launches that a call's sizes are reported for (no GPU needed): up to two of (rt, nt, tiles, parts).
 extern "C" int sqp_debug_prefill_launches(int M, int N, int K, int group, int cus, int *out8)
 {
     const LaunchPlan q = plan_launches(M, N, K, group, cus, SIZE_MAX, SIZE_MAX);
@@ -758,6 +810,56 @@ static size_t plan_partial_bytes(const LaunchPlan &q)
         need = b > need ? b : need;
     }
     return need;
+}
+
+// Estimated time (us) of one launch of tiles with all that belongs to it, on a chip that it fills once:
+// a + stages * (b + l * workgroups / compute units) + (h + p * MB), the last two with K parts (MB: their fp32 sums
+// written and read); a stage is 64 k, 128 with waves that halve K.  Up to one workgroup per compute unit, or two of the
+// variants that leave half the registers.  Fitted to 9200 launches of 289 shapes (65 to 1536 rows, N 1024 to 24576,
+// K 1024 to 16384, groups of 128): rms 2.6 to 4.5 % by variant.  0: not covered.
+static double launch_us(const TileLaunch &l, int M, int N, int K, int cus)
+{
+    struct Cost { double a, b, l, h, p; };
+    static const Cost one[4] = {{7.40, 0.543, 0.093, 1.65, 0.167}, {8.53, 0.662, 0.109, 1.14, 0.154}, {9.49, 0.763, 0.173, 1.54, 0.129}, {10.26, 0.873, 0.224, 1.46, 0.117}};
+    static const Cost halves[4] = {{6.76, 0.578, 0.121, 1.53, 0.238}, {7.38, 0.688, 0.141, 1.92, 0.216}, {8.73, 0.783, 0.222, 1.54, 0.198}, {9.04, 0.932, 0.257, 1.79, 0.180}};
+    static const Cost two[2] = {{9.82, 0.615, 0.365, 2.72, 0.077}, {10.44, 0.821, 0.455, 2.04, 0.082}}, wide = {8.25, 1.123, 0.360, 0, 0};
+    const long groups = l.tiles * l.parts;
+    if (groups > 2L * cus || (groups > cus && (l.nt == 4 || l.kh == 2 || l.rt > 4))) return 0;
+    const Cost &c = l.nt == 4 ? wide : l.kh == 2 ? halves[l.rt - 3] : groups > cus ? two[l.rt - 3] : one[l.rt - 3];
+    const int stages = (K / (BK * l.kh) + l.parts - 1) / l.parts;
+    return c.a + stages * (c.b + c.l * (double)groups / cus) + (l.parts > 1 ? c.h + c.p * l.parts * ((double)M * N * 8e-6) : 0.0);
+}
+
+// Of a plan that is one launch of at most one workgroup per compute unit: a quicker one, if there is one by 3 % by the
+// estimate, whose parts fit the room that the plan's have.  Tiles of half the columns whose waves halve K need half
+// the K parts (or none) for as many workgroups, at the price of twice the activations per compute unit; tiles of 96 and
+// 128 rows x 256 columns leave half of the registers, so that two workgroups per compute unit hide each other's
+// waits.  The sizes reported to callers are those of the plan itself: what they have stored goes on to hold.
+// us, plan -> quicker one: 160x8192x8192 36.3 -> 34.4, 160x4096x22016 44.5 -> 39.8, 300x5120x15360 59.6 -> 55.5, 490x2816x5840
+// 32.5 -> 25.9, 999x2176x3832 32.8 -> 24.3, 403x3072x22792 72.2 -> 68.7; over the fitted shapes the pick is 0.4 %
+// behind the best in the mean.
+static double quicker_launch(LaunchPlan &q, int M, int N, int K, int group, int cus, size_t room)
+{
+    const bool hooked = g_tile_mode != 0 || g_tile_shape != 0 || g_ksplit >= 0 || g_force_rt > 0;
+    if (hooked || group == 32 || q.count != 1 || q.wm != 1) return 0;
+    double best = launch_us(q.l[0], M, N, K, cus), least = best * 0.97;
+    if (best == 0) return 0;
+    const int stages = K / BK;
+    for (int rt = 3; rt <= 6; rt++)
+        for (int kh = 1; kh <= (K % (2 * BK) == 0 ? 2 : 1); kh++) {
+            const int wg = 256 / kh, tn = (N + wg - 1) / wg;
+            const long tiles = (long)tn * ((M + 32 * rt - 1) / (32 * rt)), slots = rt <= 4 && kh == 1 ? 2 * cus : cus;
+            for (int parts = 1; parts <= 12 && tiles * parts <= slots; parts++) {
+                const TileLaunch l = {rt, 2, 0, tiles, tn, parts, false, kh};
+                if (parts > 1 && (stages < 8 * parts || launch_partial_bytes(l, 1) > room)) break;
+                const double t = launch_us(l, M, N, K, cus);
+                if (t < least) {
+                    least = best = t;
+                    q.l[0] = l;
+                }
+            }
+        }
+    return best;
 }
 
 // Estimated time (us) of the launches of a plan, without what all launches share: see plan_launches.
@@ -787,8 +889,8 @@ static bool row_blocks_cover(int K, int group) { return K % 128 == 0 && (group =
 // and the fp32 parts through memory; the strip kernel's workgroups are small, walk K with two waves per SIMD
 // and hand partial tiles over in the same launch.  It reads the weights once per row block (the second and
 // later ones from L2 or the last-level cache) and unpacks them again, so it loses once the chip is full:
-// taken where its estimated time is 8 % below that of the tiles (plan_launches' estimate and the 6.7 us that
-// it leaves out).
+// taken where its estimated time is 3 % below that of the tiles (launch_us; 8 % below plan_launches' coarser estimate and
+// the 6.7 us that it leaves out).
 // The estimate: A + iterations * (B + L * workgroups / compute units) + (H + S * parts), the last two terms with
 // more than one K part; at most one eight-wave workgroup (kp = 2) or two four-wave ones per compute unit.
 // Fitted to 13700 launches of 1547 shapes (65 to 1024 rows, N 768 to 24576, K 512 to 8192, groups of 32, 64, 128
@@ -809,7 +911,7 @@ static SqpStripPlan row_blocks_plan(int M, int N, int K, int group, int cus, dou
     if (M <= 64 || !row_blocks_cover(K, group)) return best;
     if ((long)((N + 127) / 128) * ((M + 63) / 64) > 2 * cus) return best;  // (no launch below fits: long prompts end here)
     const int chunks = K / 128;
-    double least = (tiles_us + 6.7) / 1.08;
+    double least = tiles_us;
     for (int mt = 3; mt <= 4; mt++) {
         const long blocks = (M + 16 * mt - 1) / (16 * mt), tiles = (N + 127) / 128 * blocks;
         size_t part = 0;  // bytes of one K part's tiles (two for all: none where the tickets do not reach)
@@ -833,13 +935,26 @@ static SqpStripPlan row_blocks_plan(int M, int N, int K, int group, int cus, dou
     return best;
 }
 
-// What a call takes beside the tiled launches q: none where those are forced by a test hook.
-static SqpStripPlan row_blocks_for(const LaunchPlan &q, int M, int N, int K, int group, int cus, size_t limit)
+// Test hook: the launches of a call with `room` bytes for K parts (no GPU needed): up to two of (rt, nt, tiles, parts, kh).
+extern "C" int sqp_debug_prefill_choice(int M, int N, int K, int group, int cus, size_t room, int *out10)
+{
+    LaunchPlan q = plan_launches(M, N, K, group, cus, room, room);
+    quicker_launch(q, M, N, K, group, cus, room);
+    for (int i = 0; i < q.count; i++) {
+        const int v[5] = {q.l[i].rt, q.l[i].nt, (int)q.l[i].tiles, q.l[i].parts, q.l[i].kh};
+        for (int j = 0; j < 5; j++) out10[5 * i + j] = v[j];
+    }
+    return q.count;
+}
+
+// What a call takes beside the tiled launches q: none where those are forced by a test hook.  us: their estimated
+// time, 0 where launch_us has none.
+static SqpStripPlan row_blocks_for(const LaunchPlan &q, int M, int N, int K, int group, int cus, size_t limit, double us)
 {
     const bool hooked = g_tile_mode != 0 || g_tile_shape != 0 || g_ksplit >= 0 || g_force_rt > 0;
     if (g_row_blocks.mt > 0 && row_blocks_cover(K, group)) return g_row_blocks;
     if (hooked || g_row_blocks.mt < 0) return SqpStripPlan{2, 1, 2, 1, 0};
-    return row_blocks_plan(M, N, K, group, cus, launches_us(q, K, group, cus), limit);
+    return row_blocks_plan(M, N, K, group, cus, us > 0 ? us / 1.03 : (launches_us(q, K, group, cus) + 6.7) / 1.08, limit);
 }
 
 static size_t row_blocks_bytes(const SqpStripPlan &p, int M, int N, int K)
@@ -856,8 +971,10 @@ extern "C" void sqp_debug_row_blocks(int M, int N, int K, int group, int cus, in
     const bool covered = tiled_covers(K, group);
     SqpStripPlan p = {2, 0, 2, 0, 0};
     if (covered) {
-        const LaunchPlan q = plan_launches(M, N, K, group, cus, workspace ? SIZE_MAX : 0, 0);
-        p = row_blocks_for(q, M, N, K, group, cus, workspace && plan_partial_bytes(q) > 0 ? SIZE_MAX : 0);
+        LaunchPlan q = plan_launches(M, N, K, group, cus, workspace ? SIZE_MAX : 0, 0);
+        const size_t limit = workspace && plan_partial_bytes(q) > 0 ? SIZE_MAX : 0;
+        const double us = quicker_launch(q, M, N, K, group, cus, workspace && !q.own ? SIZE_MAX : 0);
+        p = row_blocks_for(q, M, N, K, group, cus, limit, us);
     }
     out3[0] = p.mt;
     out3[1] = p.split;
@@ -877,15 +994,21 @@ size_t sqp_gemm_prefill_partial_bytes(int M, int N, int K, int group)
     const LaunchPlan q = preferred_launches(M, N, K, group);
     const size_t tiles = plan_partial_bytes(q);
     if (tiles == 0 && g_row_blocks.mt <= 0) return 0;  // (a forced plan says what it needs)
-    const size_t rows = row_blocks_bytes(row_blocks_for(q, M, N, K, group, sqp_compute_units(), SIZE_MAX), M, N, K);
+    // (row blocks as the launches above would leave them: what a quicker launch leaves is less)
+    const size_t rows = row_blocks_bytes(row_blocks_for(q, M, N, K, group, sqp_compute_units(), SIZE_MAX, 0), M, N, K);
     return rows > tiles ? rows : tiles;
 }
+
+// Scratch that a call may ask for its own K parts (the static array's size).
+static constexpr size_t OWN_MOST = 48u << 20;
 
 size_t sqp_gemm_prefill_scratch_bytes(int M, int N, int K, int group)
 {
     if (!tiled_covers(K, group)) return 0;
-    const LaunchPlan q = plan_launches(M, N, K, group, sqp_compute_units(), SIZE_MAX, SIZE_MAX);
-    return q.own ? plan_partial_bytes(q) : 0;  // (also where row blocks run and leave it untouched: 1 shape in 200)
+    LaunchPlan q = plan_launches(M, N, K, group, sqp_compute_units(), SIZE_MAX, SIZE_MAX);
+    const size_t bytes = plan_partial_bytes(q);
+    if (q.own) quicker_launch(q, M, N, K, group, sqp_compute_units(), OWN_MOST);
+    return q.own ? (plan_partial_bytes(q) > bytes ? plan_partial_bytes(q) : bytes) : 0;  // (also where row blocks run and leave it untouched: 1 shape in 200)
 }
 
 // What a workspace has to hold at least for a call not to be refused: the K parts of the plan in 128-row
@@ -907,19 +1030,20 @@ size_t sqp_gemm_prefill_least_bytes(int M, int N, int K, int group)
 
 // Rows per group of the numbering: 8 for full tiles, whose stage takes as many bytes of x per row of tiles as of
 // weights per column (8 x 4 of the 32 that an XCD holds: 12 blocks of 16 KB, 5.7 x 5.7 would be the least), 4 for tiles
-// of half the columns; groups of equal size where the rows do not divide.
+// of half the columns; groups of equal size where the rows do not divide.  One row per group in launches of K parts alone
+// (291x5952x1072 18.9 us, 20.4 with groups of four).
 static TileMap tile_map(const TileLaunch &l, int wm, int M)
 {
-    const int bm = 32 * l.rt * wm, most = l.nt == 4 || l.halves ? 8 / wm : 4;
+    const int bm = 32 * l.rt * wm, most = l.halves || l.nt == 4 ? 8 / wm : l.parts > 1 ? 1 : 4;
     const int tm = (M + bm - 1) / bm, groups = (tm + most - 1) / most;
     return TileMap{(int)l.tile0, l.tn, tm, (tm + groups - 1) / groups, l.halves};
 }
 
-template <int RT, int NT, int WM, bool G32>
+template <int RT, int NT, int WM, bool G32, int KH = 1>
 static void launch_variant(const TileLaunch &l, int M, int N, int K, int group, const h16 *x, const uint32_t *packed, const h16 *scales,
                            const uint8_t *zeros, h16 *y, int epi, float *part, hipStream_t stream)
 {
-    w4a16_prefill_kernel<RT, NT, WM, G32><<<dim3((unsigned)l.tiles, l.parts), 256, 0, stream>>>(
+    w4a16_prefill_kernel<RT, NT, WM, KH, G32><<<dim3((unsigned)l.tiles, l.parts), 256, 0, stream>>>(
         M, N, K, group, tile_map(l, WM, M), x, packed, scales, zeros, y, l.parts >= 2 ? part : nullptr, epi);
 }
 
@@ -940,11 +1064,13 @@ int sqp_gemm_prefill(int M, int N, int K, int group, const h16 *x, const uint32_
     // Parts of row blocks go to the workspace where the shape reports one: the others may run beside calls that
     // use it.
     const size_t limit = room_ws > 0 && ws.tickets && reported > 0 ? room_ws : 0;
-    const SqpStripPlan rows = row_blocks_for(q, M, N, K, group, sqp_compute_units(), limit);
+    const double us = quicker_launch(q, M, N, K, group, sqp_compute_units(), q.own ? room_own : room_ws);
+    const SqpStripPlan rows = row_blocks_for(q, M, N, K, group, sqp_compute_units(), limit, us);
     if (rows.mt) return sqp_strip_row_blocks(group, rows, M, N, K, group <= 128 ? 1 : group / 128, x, packed, scales, zeros, y, epi, ws, stream);
     for (int i = 0; i < q.count; i++) {
         const TileLaunch &l = q.l[i];
 #define SQP_TILES(RT, NT, WM, G32) launch_variant<RT, NT, WM, G32>(l, M, N, K, group, x, packed, scales, zeros, y, epi, part, stream)
+#define SQP_TILES_KH(RT) launch_variant<RT, 2, 1, false, 2>(l, M, N, K, group, x, packed, scales, zeros, y, epi, part, stream)
         if (group == 32) {
             if (l.nt == 4) SQP_TILES(4, 4, 1, true);
             else SQP_TILES(4, 2, 1, true);
@@ -953,6 +1079,13 @@ int sqp_gemm_prefill(int M, int N, int K, int group, const h16 *x, const uint32_
             else SQP_TILES(4, 2, 2, false);
         } else if (l.nt == 4) {
             SQP_TILES(4, 4, 1, false);
+        } else if (l.kh == 2) {
+            switch (l.rt) {
+                case 3: SQP_TILES_KH(3); break;
+                case 5: SQP_TILES_KH(5); break;
+                case 6: SQP_TILES_KH(6); break;
+                default: SQP_TILES_KH(4); break;
+            }
         } else {
             switch (l.rt) {
                 case 3: SQP_TILES(3, 2, 1, false); break;
@@ -962,8 +1095,9 @@ int sqp_gemm_prefill(int M, int N, int K, int group, const h16 *x, const uint32_
             }
         }
 #undef SQP_TILES
+#undef SQP_TILES_KH
         if (l.parts >= 2) {
-            const int bm = 32 * l.rt * q.wm, wgn = l.nt * 128 / q.wm;
+            const int bm = 32 * l.rt * q.wm, wgn = tile_columns(l, q.wm);
             splitk_reduce_kernel<<<dim3(bm * wgn / 2048, (unsigned)l.tiles), 256, 0, stream>>>(part, M, N, bm, wgn, tile_map(l, q.wm, M), l.parts, y, epi);
         }
     }

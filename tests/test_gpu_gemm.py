@@ -247,6 +247,28 @@ def test_prefill_few_stages(orc, sqp, rt, nt, stages):
         L.sqp_debug_set_prefill_variant(0, 0, 0)
 
 
+@pytest.mark.parametrize("rt", [3, 4, 5, 6])
+@pytest.mark.parametrize("M_off,K,N,group,parts", [
+    (0, 128, 8, 64, 1), (-1, 256, 136, 128, 1), (1, 384, 120, 192, 1), (33, 640, 264, 64, 1), (-17, 1024, 392, 512, 4), (5, 1920, 248, 320, 3),
+    (64, 1792, 128, 256, 2)])
+def test_prefill_waves_halve_k(orc, sqp, M_off, K, N, group, parts, rt):
+    """Tiles of 128 columns whose waves halve every stage of 128 k between them: one row or column past a tile and
+    short of it, one to fifteen stages, groups that end in the middle of a stage or span several, with and without K
+    parts; plain and with the fused activation; repeated runs are bit-identical, and equal to whole-K tiles within
+    the fp32 accumulation."""
+    M = max(1, 64 * rt + M_off)
+    print("case halved k", M, K, N, group, rt, parts, flush=True)
+    xs, p, sc, z = _layer(orc, M, K, N, group)
+    L = sqp.lib()
+    L.sqp_debug_set_prefill_variant(rt, 2 + 16, parts)
+    try:
+        y0 = _check(orc, sqp, xs, p, sc, z, group)
+        y1 = _check(orc, sqp, xs, p, sc, z, group)
+    finally:
+        L.sqp_debug_set_prefill_variant(0, 0, 0)
+    assert np.array_equal(y0.view(np.uint16), y1.view(np.uint16))
+
+
 def test_prefill_left_over_k_parts(orc, sqp):
     """A grid of one full round and a few tiles, K long enough that the left-over half-width tiles are
     split in K too (M = 2050, N = 8144: 17 x 16 = 272 tiles).  Sampled rows against the oracle, from

@@ -252,6 +252,32 @@ def test_prefill_launches_invariants(L):
     assert L.sqp_debug_prefill_launches(3001, 44032, 8192, 128, 256, out) == 2 and tuple(out[4:8]) == (4, 2, 32, 8)
 
 
+def test_prefill_choice_stays_in_its_room(L):
+    """What a call launches in the place of the reported plan: every tile once, at most one workgroup per compute unit
+    (two of the variants with half the registers), at least eight stages of 64 k per part, parts within the
+    room given, waves that halve K only where K is whole stages of 128 and groups are not of 32."""
+    out, seen = (ctypes.c_int * 10)(), set()
+    L.sqp_debug_prefill_choice.argtypes = [ctypes.c_int] * 5 + [ctypes.c_size_t, ctypes.POINTER(ctypes.c_int)]
+    rng = random.Random(19)
+    for _ in range(4000):
+        group = rng.choice([128, 128, 64, 32, 192, 256])
+        M, N, K = int(2 ** rng.uniform(6.1, 11.5)), 8 * int(2 ** rng.uniform(5, 12.4)), group * int(2 ** rng.uniform(0, 7))
+        if K % 64:
+            continue
+        room = rng.choice([0, 1 << 20, 8 << 20, 48 << 20])
+        n = L.sqp_debug_prefill_choice(M, N, K, group, 256, room, out)
+        for i in range(n):
+            rt, nt, tiles, parts, kh = out[5 * i:5 * i + 5]
+            seen.add((rt, nt, kh, tiles * parts > 256))
+            assert kh == 1 or (kh == 2 and nt == 2 and K % 128 == 0 and group % 64 == 0)
+            assert parts == 1 or (nt == 2 and K // 64 >= 8 * parts and parts * tiles * 32 * rt * (256 // kh) * 4 <= room)
+            if n == 1:
+                assert tiles >= -(-N // (128 * nt // kh)) * -(-M // (32 * rt))
+            if parts > 1 or kh == 2:
+                assert tiles * parts <= (512 if nt == 2 and kh == 1 and rt <= 4 else 256)
+    assert {(rt, 2, kh, False) for rt in (3, 4, 5, 6) for kh in (1, 2)} <= seen and (3, 2, 1, True) in seen
+
+
 def test_plans_fit_the_static_array(L):
     """No shape's own plan needs more partial sums than the static array of sqp_w4a16_gemm_static holds, the
     least size of a workspace is at most the preferred one, and a call in blocks of 64 rows reports what
