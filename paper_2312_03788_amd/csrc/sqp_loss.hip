@@ -136,7 +136,7 @@ loss_tile_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, cons
     const int stages = K / SBK;
     const int ncol = n0 + wn * 64 + 2 * l32;                   // this lane's two columns (N is even: both in or out)
     const bool ncol_ok = ncol < N;
-    const UnpackConsts uc = SQP_UNPACK_CONSTS;
+    const UnpackConsts uc = unpack_consts();
 
     f32x16 acc[2][2];
 #pragma unroll
@@ -506,7 +506,7 @@ loss_pair_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, cons
     const int stages = K / SBK;
     const int ncol = n0 + wn * 64 + 2 * l32;                   // this lane's two columns (N is even: both in or out)
     const bool ncol_ok = ncol < N;
-    const UnpackConsts uc = SQP_UNPACK_CONSTS;
+    const UnpackConsts uc = unpack_consts();
 
     f32x16 acc[2][2][2];                       // [alpha][row tile][column]
 #pragma unroll
@@ -879,7 +879,7 @@ quant_loss_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, con
     const int wm = wave >> 2, wn = wave & 3;                   // wave tile: rows wm*64 .. +64, columns wn*32 .. +32
     const int l32 = lane & 31, kb = lane >> 5;
     const int m0 = blockIdx.y * LBM, n0 = blockIdx.x * LBN;
-    const UnpackConsts uc = SQP_UNPACK_CONSTS;
+    const UnpackConsts uc = unpack_consts();
 
     f32x16 acc[2];
 #pragma unroll

@@ -263,7 +263,7 @@ w4a16_decode_slice_kernel(int M, int N, int K, int cpg, int grouped, const h16 *
         // FMAs): a register that nothing reads would otherwise be free for an instruction in assembly while
         // the MFMA still writes it, and the compiler adds no wait states for those.
         const f32x4 none = {0.f, 0.f, 0.f, 0.f};
-        const UnpackConsts uc = SQP_UNPACK_CONSTS;
+        const UnpackConsts uc = unpack_consts();
 #pragma unroll
         for (int q = 0; q < NQ; q++) {
             f32x4 g[MT][TB];

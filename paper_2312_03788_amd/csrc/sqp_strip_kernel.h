@@ -23,6 +23,12 @@
 //   - Weight loads and all waits are written in assembly: D - 1 chunks of weights stay in
 //     flight per wave while one is consumed, and the compiler's conservative waits (it cannot
 //     tell ring slots apart) would serialise that.
+// What bounds it beside the stream: the instructions a wave issues, one every four to five cycles (a wave alone and two of
+// a SIMD alike).  us per launch, weights from HBM, before -> with the scalar work of an iteration cut from 70
+// instructions to 25 -> with the words unpacked between the matrix instructions of the one before (and no wait
+// states behind the unpack): 16 rows 8192->10240 13.9 -> 13.2 -> 12.8, 22016->8192 22.8 -> 22.2 -> 21.5, 8192->44032 39.3 ->
+// 38.9 -> 38.7; 48 rows 5120->27648 27.7 -> 26.5 -> 25.8, 5120->15360 20.0 -> 19.1 -> 18.5; 20 rows in groups of 64
+// 4096->22016 19.5 -> 17.9 -> 17.5; 28 rows in groups of 32 23.3 -> 20.7 -> 20.1.
 // With SPLIT > 1 workgroups along K, fp32 partial tiles go to a workspace and the workgroup
 // that arrives last (atomic ticket) adds them in split order, so the result does not depend
 // on scheduling.
@@ -74,6 +80,14 @@ __device__ __forceinline__ void store_row4(h16 *y, int m, int N, int n, int epi,
 __device__ __forceinline__ unsigned small_divide(unsigned a, unsigned b)
 {
     return __builtin_amdgcn_readfirstlane((unsigned)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b)));
+}
+
+// Direct global -> LDS load of 16 bytes per lane: lane i's from base + lane_offset + offset to dst + 16 i (dst and offset
+// wave-uniform).  A buffer load: neither a 64-bit address per lane nor one per call; bytes: size of the buffer.
+__device__ __forceinline__ void copy16_to_lds(const void *base, uint32_t bytes, uint32_t lane_offset, uint32_t offset, void *dst)
+{
+    const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void *)dst, 16, lane_offset, offset, 0, 0);
 }
 
 // Split-K tickets: one per 128-byte line (atomics on one line are served one after the other).
@@ -174,7 +188,7 @@ w4a16_decode_kernel(int M, int N, int K, int cpg, const h16 *__restrict__ x, con
     for (int mt = 0; mt < MT; mt++)
 #pragma unroll
         for (int t = 0; t < 4; t++) acc[mt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const UnpackConsts uc = SQP_UNPACK_CONSTS;
+    const UnpackConsts uc = unpack_consts();
 
     struct Stage {
         u32x4 w[KS];
@@ -189,156 +203,99 @@ w4a16_decode_kernel(int M, int N, int K, int cpg, const h16 *__restrict__ x, con
     // every weight byte is read once per launch, and a plain streaming probe reads 12-15 % faster
     // with it on this chip (the kernel gains about 2 %).  Row blocks read it once each and go without
     // (5 % in the mean of 45 shapes, up to 15).
-    const uint32_t voff_w = (uint32_t)(lk * N + ncol) * 4u;
-    const int wrow_stride = N;
-    const uint32_t voff_s = (uint32_t)ncol * 2u, voff_z = (uint32_t)ncol;
-    // The loading side walks the chunks with wave-uniform byte pointers stepped by constant
-    // strides (scalar adds, no multiplies or divisions in the loop).
-    const long wstep1 = (long)wrow_stride * 16;                 // one k-step: 4 packed rows, in bytes
+    // A wave issues one instruction every four to five cycles at best, scalar ones among them, so the loop keeps its
+    // scalar work short (25 instructions per iteration where pointers clamped at the end of the range, 64-bit adds
+    // per row and a mask formed in a vector register took 70): one base per stream, stepped by a constant, with the rows of
+    // an iteration in the lanes' offsets; past the range the bases run on and only the execution mask tells.
+    const long wstep1 = (long)N * 16;                            // one k-step: 4 packed rows, in bytes
     // An iteration covers KP consecutive chunks; this wave's are g0 + ph, g0 + ph + KP, ...  (with
     // KP = 2 and an odd range the second half of the waves has one chunk fewer; a wave without
     // any chunk points at g0 and never computes).  The activations are fetched per iteration
     // for all KP chunks by all waves together.
     const int nsup = (g1 - g0 + KP - 1) / KP;                    // iterations of this workgroup
-    const bool own_any = g0 + ph < g1;
-    const int cs = own_any ? g0 + ph : g0;                       // this wave's first chunk
-    const int wlast = own_any ? cs + ((g1 - 1 - cs) / KP) * KP : cs;  // and its last
-    const unsigned char *wq = reinterpret_cast<const unsigned char *>(packed) + (long)cs * KSPG * wstep1;
+    const int nown = g0 + ph < g1 ? (g1 - g0 - ph + KP - 1) / KP : 0;  // and of this wave
+    const int cs = nown > 0 ? g0 + ph : g0;                      // this wave's first chunk
+    const unsigned char *wq = reinterpret_cast<const unsigned char *>(packed) + ((long)cs * KSPG + kh * KS) * wstep1;
     // first parameter row of this wave: chunk / cpg, or (chunks of several groups) chunk * gpc + its share
     const long prow = GPC > 1 ? (long)cs * GPC + kh * KS / GS : (long)(cs / cpg);
     const unsigned char *sq = reinterpret_cast<const unsigned char *>(scales) + prow * N * 2;
     const unsigned char *zq = zeros + prow * N;
-    const unsigned char *xq = reinterpret_cast<const unsigned char *>(x) + (long)g0 * (64 * KSPG);
-    int gi = cs, kin = cs % cpg;                                 // own chunk being issued, its position in its group
-    int xg = g0;                                                 // first chunk of the iteration whose activations are being issued
-    // `live` (wave-uniform) is false for the look-ahead loads past the end of the workgroup's range:
-    // those are issued with an empty execution mask, so they fetch nothing (with the streaming
+    int kin = cs % cpg;                                          // position of the chunk being issued in its group
+    uint32_t voff_w[KS], voff_s[NQ], voff_z[NQ];                 // rows of a wave's share of a chunk
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) voff_w[ks] = (uint32_t)((lk + 4 * ks) * N + ncol) * 4u;
+#pragma unroll
+    for (int q = 0; q < NQ; q++) {
+        voff_s[q] = (uint32_t)(q * N + ncol) * 2u;
+        voff_z[q] = (uint32_t)(q * N + ncol);
+    }
+    // `i` (wave-uniform) is the wave's iteration that the loads are for; look-ahead loads past its last one
+    // are issued with an empty execution mask, so they fetch nothing (with the streaming
     // hint their lines would not be cache hits) and write no register, but still take their
     // place in the in-order load queue, which keeps the wait counts below the same for every
     // iteration.  Mask change, loads and mask restore are one asm statement, so the compiler can
     // place nothing of its own under the changed mask.
-    auto issue_w = [&](Stage &s, bool live) {
-        const unsigned char *b0 = wq + (kh * KS) * wstep1;  // wave-uniform
-        const uint32_t m = __builtin_amdgcn_readfirstlane(live ? 0xffffffffu : 0u);  // both halves of the mask
+    auto issue_w = [&](Stage &s, int i) {
         uint64_t saved;
+#define SQP_MASKED(LOADS) "s_mov_b64 %[sv], exec\n\ts_cmp_lt_i32 %[i], %[n]\n\ts_cselect_b64 exec, exec, 0\n\t" LOADS "s_mov_b64 exec, %[sv]"
+#define SQP_W(I, HINT) "global_load_dwordx4 %[w" #I "], %[vw" #I "], %[b]" HINT "\n\t"
+#define SQP_Q(I, HINT) "global_load_dwordx2 %[sc" #I "], %[vs" #I "], %[sb]" HINT "\n\tglobal_load_dword %[zr" #I "], %[vz" #I "], %[zb]" HINT "\n\t"
+#define SQP_OUT_W(I) [w##I] "=&v"(s.w[I])
+#define SQP_OUT_Q(I) [sc##I] "=&v"(s.sc[I]), [zr##I] "=&v"(s.zr[I])
+#define SQP_IN_W(I) [vw##I] "v"(voff_w[I])
+#define SQP_IN_Q(I) [vs##I] "v"(voff_s[I]), [vz##I] "v"(voff_z[I])
+#define SQP_BASES [i] "s"(i), [n] "s"(nown), [b] "s"(wq), [sb] "s"(sq), [zb] "s"(zq)
         if constexpr (KS == 4 && NQ == 1) {
-            const unsigned char *b1 = b0 + wstep1, *b2 = b0 + 2 * wstep1, *b3 = b0 + 3 * wstep1;
-            asm volatile("s_mov_b64 %[sv], exec\n\t"
-                         "s_and_b32 exec_lo, exec_lo, %[m]\n\t"
-                         "s_and_b32 exec_hi, exec_hi, %[m]\n\t"
-                         "global_load_dwordx4 %[w0], %[vw], %[b0] nt\n\t"
-                         "global_load_dwordx4 %[w1], %[vw], %[b1] nt\n\t"
-                         "global_load_dwordx4 %[w2], %[vw], %[b2] nt\n\t"
-                         "global_load_dwordx4 %[w3], %[vw], %[b3] nt\n\t"
-                         "global_load_dwordx2 %[sc0], %[vs], %[s0] nt\n\t"
-                         "global_load_dword %[zr0], %[vz], %[z0] nt\n\t"
-                         "s_mov_b64 exec, %[sv]"
-                         : [w0] "=&v"(s.w[0]), [w1] "=&v"(s.w[1]), [w2] "=&v"(s.w[2]), [w3] "=&v"(s.w[3]), [sc0]
-                           "=&v"(s.sc[0]), [zr0] "=&v"(s.zr[0]), [sv] "=&s"(saved)
-                         : [m] "s"(m), [vw] "v"(voff_w), [vs] "v"(voff_s), [vz] "v"(voff_z), [b0] "s"(b0), [b1] "s"(b1), [b2]
-                           "s"(b2), [b3] "s"(b3), [s0] "s"(sq), [z0] "s"(zq)
-                         : "memory", "scc");  // s_and_b32 writes SCC
+            asm volatile(SQP_MASKED(SQP_W(0, " nt") SQP_W(1, " nt") SQP_W(2, " nt") SQP_W(3, " nt") SQP_Q(0, " nt"))
+                         : SQP_OUT_W(0), SQP_OUT_W(1), SQP_OUT_W(2), SQP_OUT_W(3), SQP_OUT_Q(0), [sv] "=&s"(saved)
+                         : SQP_IN_W(0), SQP_IN_W(1), SQP_IN_W(2), SQP_IN_W(3), SQP_IN_Q(0), SQP_BASES
+                         : "memory", "scc");
         } else if constexpr (KS == 4 && NQ == 2) {
-            const unsigned char *b1 = b0 + wstep1, *b2 = b0 + 2 * wstep1, *b3 = b0 + 3 * wstep1, *s1 = sq + (long)N * 2, *z1 = zq + N;
-            asm volatile("s_mov_b64 %[sv], exec\n\t"
-                         "s_and_b32 exec_lo, exec_lo, %[m]\n\t"
-                         "s_and_b32 exec_hi, exec_hi, %[m]\n\t"
-                         "global_load_dwordx4 %[w0], %[vw], %[b0] nt\n\t"
-                         "global_load_dwordx4 %[w1], %[vw], %[b1] nt\n\t"
-                         "global_load_dwordx4 %[w2], %[vw], %[b2] nt\n\t"
-                         "global_load_dwordx4 %[w3], %[vw], %[b3] nt\n\t"
-                         "global_load_dwordx2 %[sc0], %[vs], %[s0] nt\n\t"
-                         "global_load_dword %[zr0], %[vz], %[z0] nt\n\t"
-                         "global_load_dwordx2 %[sc1], %[vs], %[s1] nt\n\t"
-                         "global_load_dword %[zr1], %[vz], %[z1] nt\n\t"
-                         "s_mov_b64 exec, %[sv]"
-                         : [w0] "=&v"(s.w[0]), [w1] "=&v"(s.w[1]), [w2] "=&v"(s.w[2]), [w3] "=&v"(s.w[3]), [sc0]
-                           "=&v"(s.sc[0]), [zr0] "=&v"(s.zr[0]), [sc1] "=&v"(s.sc[1]), [zr1] "=&v"(s.zr[1]), [sv]
-                           "=&s"(saved)
-                         : [m] "s"(m), [vw] "v"(voff_w), [vs] "v"(voff_s), [vz] "v"(voff_z), [b0] "s"(b0), [b1] "s"(b1), [b2]
-                           "s"(b2), [b3] "s"(b3), [s0] "s"(sq), [z0] "s"(zq), [s1] "s"(s1), [z1] "s"(z1)
-                         : "memory", "scc");  // s_and_b32 writes SCC
+            asm volatile(SQP_MASKED(SQP_W(0, " nt") SQP_W(1, " nt") SQP_W(2, " nt") SQP_W(3, " nt") SQP_Q(0, " nt") SQP_Q(1, " nt"))
+                         : SQP_OUT_W(0), SQP_OUT_W(1), SQP_OUT_W(2), SQP_OUT_W(3), SQP_OUT_Q(0), SQP_OUT_Q(1), [sv] "=&s"(saved)
+                         : SQP_IN_W(0), SQP_IN_W(1), SQP_IN_W(2), SQP_IN_W(3), SQP_IN_Q(0), SQP_IN_Q(1), SQP_BASES
+                         : "memory", "scc");
         } else if constexpr (KS == 4 && NQ == 4) {
-            const unsigned char *b1 = b0 + wstep1, *b2 = b0 + 2 * wstep1, *b3 = b0 + 3 * wstep1, *s1 = sq + (long)N * 2, *z1 = zq + N, *s2 = sq + (long)N * 4, *z2 = zq + (long)N * 2, *s3 = sq + (long)N * 6, *z3 = zq + (long)N * 3;
-            asm volatile("s_mov_b64 %[sv], exec\n\t"
-                         "s_and_b32 exec_lo, exec_lo, %[m]\n\t"
-                         "s_and_b32 exec_hi, exec_hi, %[m]\n\t"
-                         "global_load_dwordx4 %[w0], %[vw], %[b0] nt\n\t"
-                         "global_load_dwordx4 %[w1], %[vw], %[b1] nt\n\t"
-                         "global_load_dwordx4 %[w2], %[vw], %[b2] nt\n\t"
-                         "global_load_dwordx4 %[w3], %[vw], %[b3] nt\n\t"
-                         "global_load_dwordx2 %[sc0], %[vs], %[s0] nt\n\t"
-                         "global_load_dword %[zr0], %[vz], %[z0] nt\n\t"
-                         "global_load_dwordx2 %[sc1], %[vs], %[s1] nt\n\t"
-                         "global_load_dword %[zr1], %[vz], %[z1] nt\n\t"
-                         "global_load_dwordx2 %[sc2], %[vs], %[s2] nt\n\t"
-                         "global_load_dword %[zr2], %[vz], %[z2] nt\n\t"
-                         "global_load_dwordx2 %[sc3], %[vs], %[s3] nt\n\t"
-                         "global_load_dword %[zr3], %[vz], %[z3] nt\n\t"
-                         "s_mov_b64 exec, %[sv]"
-                         : [w0] "=&v"(s.w[0]), [w1] "=&v"(s.w[1]), [w2] "=&v"(s.w[2]), [w3] "=&v"(s.w[3]), [sc0]
-                           "=&v"(s.sc[0]), [zr0] "=&v"(s.zr[0]), [sc1] "=&v"(s.sc[1]), [zr1] "=&v"(s.zr[1]), [sc2]
-                           "=&v"(s.sc[2]), [zr2] "=&v"(s.zr[2]), [sc3] "=&v"(s.sc[3]), [zr3] "=&v"(s.zr[3]), [sv]
-                           "=&s"(saved)
-                         : [m] "s"(m), [vw] "v"(voff_w), [vs] "v"(voff_s), [vz] "v"(voff_z), [b0] "s"(b0), [b1] "s"(b1), [b2]
-                           "s"(b2), [b3] "s"(b3), [s0] "s"(sq), [z0] "s"(zq), [s1] "s"(s1), [z1] "s"(z1), [s2] "s"(s2), [z2]
-                           "s"(z2), [s3] "s"(s3), [z3] "s"(z3)
-                         : "memory", "scc");  // s_and_b32 writes SCC
+            asm volatile(SQP_MASKED(SQP_W(0, " nt") SQP_W(1, " nt") SQP_W(2, " nt") SQP_W(3, " nt") SQP_Q(0, " nt") SQP_Q(1, " nt") SQP_Q(2, " nt")
+                                        SQP_Q(3, " nt"))
+                         : SQP_OUT_W(0), SQP_OUT_W(1), SQP_OUT_W(2), SQP_OUT_W(3), SQP_OUT_Q(0), SQP_OUT_Q(1), SQP_OUT_Q(2), SQP_OUT_Q(3),
+                           [sv] "=&s"(saved)
+                         : SQP_IN_W(0), SQP_IN_W(1), SQP_IN_W(2), SQP_IN_W(3), SQP_IN_Q(0), SQP_IN_Q(1), SQP_IN_Q(2), SQP_IN_Q(3), SQP_BASES
+                         : "memory", "scc");
         } else if constexpr (KS == 2 && NQ == 1) {
-            const unsigned char *b1 = b0 + wstep1;
-#define SQP_ISSUE(HINT) \
-    asm volatile("s_mov_b64 %[sv], exec\n\t" \
-                 "s_and_b32 exec_lo, exec_lo, %[m]\n\t" \
-                 "s_and_b32 exec_hi, exec_hi, %[m]\n\t" \
-                 "global_load_dwordx4 %[w0], %[vw], %[b0]" HINT "\n\t" \
-                 "global_load_dwordx4 %[w1], %[vw], %[b1]" HINT "\n\t" \
-                 "global_load_dwordx2 %[sc0], %[vs], %[s0]" HINT "\n\t" \
-                 "global_load_dword %[zr0], %[vz], %[z0]" HINT "\n\t" \
-                 "s_mov_b64 exec, %[sv]" \
-                 : [w0] "=&v"(s.w[0]), [w1] "=&v"(s.w[1]), [sc0] "=&v"(s.sc[0]), [zr0] "=&v"(s.zr[0]), [sv] \
-                   "=&s"(saved) \
-                 : [m] "s"(m), [vw] "v"(voff_w), [vs] "v"(voff_s), [vz] "v"(voff_z), [b0] "s"(b0), [b1] "s"(b1), [s0] \
-                   "s"(sq), [z0] "s"(zq) \
-                 : "memory", "scc")  /* s_and_b32 writes SCC */
+#define SQP_ISSUE(HINT)                                                                                                    \
+    asm volatile(SQP_MASKED(SQP_W(0, HINT) SQP_W(1, HINT) SQP_Q(0, HINT))                                                  \
+                 : SQP_OUT_W(0), SQP_OUT_W(1), SQP_OUT_Q(0), [sv] "=&s"(saved)                                             \
+                 : SQP_IN_W(0), SQP_IN_W(1), SQP_IN_Q(0), SQP_BASES                                                        \
+                 : "memory", "scc")
             if constexpr (RB) SQP_ISSUE("");
             else SQP_ISSUE(" nt");
 #undef SQP_ISSUE
         } else if constexpr (KS == 2 && NQ == 2) {
-            const unsigned char *b1 = b0 + wstep1, *s1 = sq + (long)N * 2, *z1 = zq + N;
-#define SQP_ISSUE(HINT) \
-    asm volatile("s_mov_b64 %[sv], exec\n\t" \
-                 "s_and_b32 exec_lo, exec_lo, %[m]\n\t" \
-                 "s_and_b32 exec_hi, exec_hi, %[m]\n\t" \
-                 "global_load_dwordx4 %[w0], %[vw], %[b0]" HINT "\n\t" \
-                 "global_load_dwordx4 %[w1], %[vw], %[b1]" HINT "\n\t" \
-                 "global_load_dwordx2 %[sc0], %[vs], %[s0]" HINT "\n\t" \
-                 "global_load_dword %[zr0], %[vz], %[z0]" HINT "\n\t" \
-                 "global_load_dwordx2 %[sc1], %[vs], %[s1]" HINT "\n\t" \
-                 "global_load_dword %[zr1], %[vz], %[z1]" HINT "\n\t" \
-                 "s_mov_b64 exec, %[sv]" \
-                 : [w0] "=&v"(s.w[0]), [w1] "=&v"(s.w[1]), [sc0] "=&v"(s.sc[0]), [zr0] "=&v"(s.zr[0]), [sc1] \
-                   "=&v"(s.sc[1]), [zr1] "=&v"(s.zr[1]), [sv] "=&s"(saved) \
-                 : [m] "s"(m), [vw] "v"(voff_w), [vs] "v"(voff_s), [vz] "v"(voff_z), [b0] "s"(b0), [b1] "s"(b1), [s0] \
-                   "s"(sq), [z0] "s"(zq), [s1] "s"(s1), [z1] "s"(z1) \
-                 : "memory", "scc")  /* s_and_b32 writes SCC */
+#define SQP_ISSUE(HINT)                                                                                                    \
+    asm volatile(SQP_MASKED(SQP_W(0, HINT) SQP_W(1, HINT) SQP_Q(0, HINT) SQP_Q(1, HINT))                                   \
+                 : SQP_OUT_W(0), SQP_OUT_W(1), SQP_OUT_Q(0), SQP_OUT_Q(1), [sv] "=&s"(saved)                               \
+                 : SQP_IN_W(0), SQP_IN_W(1), SQP_IN_Q(0), SQP_IN_Q(1), SQP_BASES                                           \
+                 : "memory", "scc")
             if constexpr (RB) SQP_ISSUE("");
             else SQP_ISSUE(" nt");
 #undef SQP_ISSUE
         } else if constexpr (KS == 1 && NQ == 1) {
-            asm volatile("s_mov_b64 %[sv], exec\n\t"
-                         "s_and_b32 exec_lo, exec_lo, %[m]\n\t"
-                         "s_and_b32 exec_hi, exec_hi, %[m]\n\t"
-                         "global_load_dwordx4 %[w0], %[vw], %[b0] nt\n\t"
-                         "global_load_dwordx2 %[sc0], %[vs], %[s0] nt\n\t"
-                         "global_load_dword %[zr0], %[vz], %[z0] nt\n\t"
-                         "s_mov_b64 exec, %[sv]"
-                         : [w0] "=&v"(s.w[0]), [sc0] "=&v"(s.sc[0]), [zr0] "=&v"(s.zr[0]), [sv] "=&s"(saved)
-                         : [m] "s"(m), [vw] "v"(voff_w), [vs] "v"(voff_s), [vz] "v"(voff_z), [b0] "s"(b0), [s0] "s"(sq), [z0]
-                           "s"(zq)
-                         : "memory", "scc");  // s_and_b32 writes SCC
+            asm volatile(SQP_MASKED(SQP_W(0, " nt") SQP_Q(0, " nt"))
+                         : SQP_OUT_W(0), SQP_OUT_Q(0), [sv] "=&s"(saved)
+                         : SQP_IN_W(0), SQP_IN_Q(0), SQP_BASES
+                         : "memory", "scc");
         } else {
             static_assert(KS == 0, "k-steps and groups per wave and chunk");
         }
+#undef SQP_MASKED
+#undef SQP_W
+#undef SQP_Q
+#undef SQP_OUT_W
+#undef SQP_OUT_Q
+#undef SQP_IN_W
+#undef SQP_IN_Q
+#undef SQP_BASES
     };
     // wait until at most `after` loads are outstanding, then tie the stage's registers to the
     // wait so that no use of them is scheduled ahead of it
@@ -369,18 +326,18 @@ w4a16_decode_kernel(int M, int N, int K, int cpg, const h16 *__restrict__ x, con
         const int rowc = row < M ? row : M - 1;
         xoff[i] = (uint32_t)rowc * (uint32_t)K * 2u + (uint32_t)((xpp ^ (row % PP)) * 16);
     }
+    // Past the workgroup's range (look-ahead, the second chunk of an odd range's last iteration) its last chunk is fetched
+    // again: cache hits, from which nothing is computed.
+    const uint32_t xmost = (uint32_t)(g1 - 1) * (64 * KSPG);
+    uint32_t xat = (uint32_t)g0 * (64 * KSPG);                   // byte offset in a row of the iteration whose activations are being issued
     auto issue_x = [&](int slot) {
 #pragma unroll
         for (int i = 0; i < OX; i++) {
             if (i + 1 == OX && !x_full) break;
             const int b = (wv + i * WAVES) % XBLOCKS;
-            // block b belongs to chunk xg + b / CBLOCKS of the iteration; past the range (the
-            // second chunk of an odd range's last iteration) the first chunk is fetched again
-            const int sub = b / CBLOCKS;
-            const unsigned char *src = xq + (KP > 1 && xg + sub < g1 ? sub * (64 * KSPG) : 0) + xoff[i];
-            unsigned char *dst = xring + slot * XSTAGE + b * 1024;
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
-                                             (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
+            // block b belongs to chunk b / CBLOCKS of the iteration
+            const uint32_t at = KP > 1 ? xat + (uint32_t)(b / CBLOCKS) * (64 * KSPG) : xat;
+            copy16_to_lds(x, (uint32_t)M * (uint32_t)K * 2u, xoff[i], at < xmost ? at : xmost, xring + slot * XSTAGE + b * 1024);
         }
     };
     // LDS byte address of this lane's A fragment (row lc of m-tile mt) in slot 0, piece 0
@@ -407,9 +364,8 @@ w4a16_decode_kernel(int M, int N, int K, int cpg, const h16 *__restrict__ x, con
         for (int q = 0; q < NQ; q++)
 #pragma unroll
             for (int c = 0; c < 4; c++) {
-                const uint32_t z = (s.zr[q] >> (8 * c)) & 0xffu;
-                neg_hi[q][c] = neg_hi_of(z);
-                neg_lo[q][c] = neg_lo_of(z);
+                neg_hi[q][c] = neg_hi_at(s.zr[q], c);
+                neg_lo[q][c] = neg_lo_at(s.zr[q] << 4, c);
                 const h16x2 sv = __builtin_bit_cast(h16x2, (uint32_t)s.sc[q][c >> 1]);
                 const h16 d16 = (c & 1) ? sv.y : sv.x;
                 delta[q][c] = (float)d16;
@@ -439,69 +395,60 @@ w4a16_decode_kernel(int M, int N, int K, int cpg, const h16 *__restrict__ x, con
 #pragma unroll
             for (int i = 0; i < n; i++) asm volatile("" : "+v"(dst[i]));  // no use ahead of the wait
         };
-        if constexpr (MT == 1) {
-            // one row tile: all of the wave's fragments of the chunk in one batch (other waves of
-            // the SIMD, where there are any, cover the wait)
-            u32x4 xa[KS];
+        // One word (8 k of a column per lane) after the other: a word is unpacked between the matrix instructions of the word
+        // before it, and so is what is left of a k-step's activations to be permuted (the scheduler is
+        // kept to that).  The first word needs no activations and is unpacked while they come from LDS; with one row tile
+        // all of the wave's fragments are read in one batch, with more those of the next k-step while this one's are used.
+        auto unpacked = [&](int i) {
+            const int ks = i >> 2, c = i & 3, q = ks / SQ;
+            if constexpr (SCALED_B) return dequant_word_scaled(s.w[ks][c], neg_hi[q][c], neg_lo[q][c], delta2[q][c], uc);
+            else return dequant_word(s.w[ks][c], neg_hi[q][c], neg_lo[q][c], uc);
+        };
+        constexpr int XA = MT == 1 ? KS : 2;   // fragment sets
+        constexpr int UNPACK = SCALED_B ? 13 : 9;
+        u32x4 xa[XA][MT];
 #pragma unroll
-            for (int ks = 0; ks < KS; ks++) read_x(&xa[ks], ks);
-            wait_x(xa, KS);
+        for (int ks = 0; ks < (MT == 1 ? KS : 1); ks++) read_x(xa[ks], ks);
+        h16x8 w = unpacked(0), a[MT];
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int ks = 0; ks < KS; ks++) {
-                const h16x8 a = permute_x(xa[ks]);
+        for (int ks = 0; ks < (MT == 1 ? KS : 1); ks++) wait_x(xa[ks], MT);
 #pragma unroll
-                for (int c = 0; c < 4; c++) {
-                    const h16x8 b = dequant_word(s.w[ks][c], neg_hi[ks / SQ][c], neg_lo[ks / SQ][c], uc);
-                    accg[0][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, accg[0][c], 0, 0, 0);
-                }
-                if (ks % SQ == SQ - 1) {
+        for (int mt = 0; mt < MT; mt++) a[mt] = permute_x(xa[0][mt]);
+#pragma unroll
+        for (int i = 0; i < 4 * KS; i++) {
+            const int ks = i >> 2, c = i & 3;
+            if (MT > 1 && c == 0 && ks + 1 < KS) read_x(xa[(ks + 1) % XA], ks + 1);
+            if (MT > 1 && c == 3 && ks + 1 < KS) wait_x(xa[(ks + 1) % XA], MT);
+            const h16x8 cur = w;
+            h16x8 an[MT];
+            const bool turn = c == 3 && ks + 1 < KS;   // the next k-step's activations go with this word
+            if (i + 1 < 4 * KS) w = unpacked(i + 1);
+            if (turn) {
+#pragma unroll
+                for (int mt = 0; mt < MT; mt++) an[mt] = permute_x(xa[(ks + 1) % XA][mt]);
+            }
+#pragma unroll
+            for (int mt = 0; mt < MT; mt++) {
+                if constexpr (SCALED_B) acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[mt], cur, acc[mt][c], 0, 0, 0);
+                else accg[mt][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[mt], cur, accg[mt][c], 0, 0, 0);
+            }
+#pragma unroll
+            for (int mt = 0; mt < MT; mt++) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                 // 1 MFMA
+                if (turn) __builtin_amdgcn_sched_group_barrier(0x002, (UNPACK + 5 * MT - 1) / MT, 0);  // VALU
+                else __builtin_amdgcn_sched_group_barrier(0x002, (UNPACK + MT - 1) / MT, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (turn) {
+#pragma unroll
+                for (int mt = 0; mt < MT; mt++) a[mt] = an[mt];
+            }
+            if constexpr (!SCALED_B)
+                if (c == 3 && ks % SQ == SQ - 1) {
                     scale_g(ks / SQ);
                     if (ks + 1 < KS) clear_g();
                 }
-            }
-        } else {
-            // several row tiles, one or two waves per SIMD: the fragments of the next k-step are
-            // on their way from LDS while this one's MFMAs issue, and the scheduler is told to
-            // put the unpack and permute instructions between the MFMAs (they hide behind them)
-            // instead of in front of them.
-            u32x4 xa[2][MT];
-            read_x(xa[0], 0);
-            wait_x(xa[0], MT);
-#pragma unroll
-            for (int ks = 0; ks < KS; ks++) {
-                const int cur = ks & 1, nxt = cur ^ 1;
-                if (ks + 1 < KS) read_x(xa[nxt], ks + 1);
-                __builtin_amdgcn_sched_barrier(0);
-                h16x8 a[MT];
-#pragma unroll
-                for (int mt = 0; mt < MT; mt++) a[mt] = permute_x(xa[cur][mt]);
-#pragma unroll
-                for (int c = 0; c < 4; c++) {
-                    if constexpr (SCALED_B) {
-                        const h16x8 b = dequant_word_scaled(s.w[ks][c], neg_hi[ks / SQ][c], neg_lo[ks / SQ][c], delta2[ks / SQ][c], uc);
-#pragma unroll
-                        for (int mt = 0; mt < MT; mt++)
-                            acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[mt], b, acc[mt][c], 0, 0, 0);
-                    } else {
-                        const h16x8 b = dequant_word(s.w[ks][c], neg_hi[ks / SQ][c], neg_lo[ks / SQ][c], uc);
-#pragma unroll
-                        for (int mt = 0; mt < MT; mt++)
-                            accg[mt][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[mt], b, accg[mt][c], 0, 0, 0);
-                    }
-                }
-#pragma unroll
-                for (int i = 0; i < 4 * MT; i++) {
-                    __builtin_amdgcn_sched_group_barrier(0x002, MT == 2 ? 6 : 4, 0);  // VALU
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                // 1 MFMA
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                if (ks + 1 < KS) wait_x(xa[nxt], MT);
-                if constexpr (!SCALED_B)
-                    if (ks % SQ == SQ - 1) {
-                        scale_g(ks / SQ);
-                        if (ks + 1 < KS) clear_g();
-                    }
-            }
         }
     };
 
@@ -517,50 +464,41 @@ w4a16_decode_kernel(int M, int N, int K, int cpg, const h16 *__restrict__ x, con
     // padded iterations is skipped.  Every iteration of a wave thus issues the same number of
     // loads (OX + OW, or one fewer on the waves that copy one block less), and since loads
     // complete in issue order "at most P-1 iterations' worth of loads outstanding" means all but
-    // the last P-1 iterations' have landed.  Past the range the pointers stop.
-    const int xlast = g0 + (nsup > 0 ? nsup - 1 : 0) * KP;  // first chunk of the last iteration
+    // the last P-1 iterations' have landed.
     auto advance = [&]() {
-        const bool more = gi < wlast;
-        gi += more ? KP : 0;
-        wq += more ? KP * KSPG * wstep1 : 0;
+        wq += KP * KSPG * wstep1;
         if constexpr (GPC > 1) {  // several groups per chunk
-            sq += more ? (long)KP * GPC * N * 2 : 0;
-            zq += more ? (long)KP * GPC * N : 0;
+            sq += (long)KP * GPC * N * 2;
+            zq += (long)KP * GPC * N;
         } else if constexpr (KP == 1) {
-            kin += more ? 1 : 0;
-            const bool wrap = kin == cpg;
+            const bool wrap = ++kin == cpg;
             kin = wrap ? 0 : kin;
             sq += wrap ? (long)N * 2 : 0;
             zq += wrap ? (long)N : 0;
         } else {  // launched only with one chunk per group (cpg == 1)
-            sq += more ? (long)KP * N * 2 : 0;
-            zq += more ? (long)KP * N : 0;
+            sq += (long)KP * N * 2;
+            zq += (long)KP * N;
         }
-        const bool xmore = xg < xlast;
-        xg += xmore ? KP : 0;
-        xq += xmore ? KP * 64 * KSPG : 0;
+        xat += KP * 64 * KSPG;
     };
     Stage st[D];
 #pragma unroll
     for (int j = 0; j < P; j++) {
         issue_x(j);
-        issue_w(st[j], cs + j * KP < g1 && own_any);
+        issue_w(st[j], j);
         advance();
     }
-    int slot = 0;  // ring slot of iteration it
     const int nblk = (nsup + D - 1) / D;
     for (int b = 0; b < nblk; b++) {
 #pragma unroll
         for (int d = 0; d < D; d++) {
-            const int it = b * D + d;             // iteration; this wave's chunk in it: cs + it * KP
+            const int it = b * D + d;             // iteration (ring slot d); this wave's chunk in it: cs + it * KP
             landed(st[d]);
             asm volatile("s_barrier" ::: "memory");
-            const int fill = slot >= 1 ? slot - 1 : XD - 1;  // (slot + P) % XD
-            issue_x(fill);
-            issue_w(st[(d + P) % D], own_any && cs + (it + P) * KP < g1);
+            issue_x((d + P) % XD);
+            issue_w(st[(d + P) % D], it + P);
             advance();
-            if (own_any && cs + it * KP < g1) compute(st[d], slot);  // padded iterations only keep the load counts in step
-            slot = slot + 1 == XD ? 0 : slot + 1;
+            if (it < nown) compute(st[d], d);     // padded iterations only keep the load counts in step
         }
     }
     // Look-ahead loads may still be in flight here (a range shorter than the pipeline issues

@@ -5,16 +5,35 @@
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-// Constants of the nibble unpack, held in registers: v_and_or_b32 cannot take literals.
+// Constants of the nibble unpack, held in registers (v_and_or_b32 takes no literals, and one scalar).  (The empty asm hides their
+// values, so the compiler keeps them there and makes one instruction of each and-or below.  Those were asm statements
+// themselves; behind one of them it puts a wait state wherever the next instruction reads the result, 10 % of
+// the instructions of the column slices' loop.)
 struct UnpackConsts {
     uint32_t mask_lo, mask_hi, magic_lo, magic_hi;
 };
-#define SQP_UNPACK_CONSTS {0x000f000fu, 0x00f000f0u, 0x64006400u, 0x54005400u}
+__device__ __forceinline__ UnpackConsts unpack_consts()
+{
+    UnpackConsts uc = {0x000f000fu, 0x00f000f0u, 0x64006400u, 0x54005400u};
+    asm("" : "+s"(uc.mask_lo), "+s"(uc.mask_hi), "+v"(uc.magic_lo), "+v"(uc.magic_hi));
+    return uc;
+}
 
 // fp16 bit patterns of -(1024 + Z) and -(64 + Z), replicated into both halves:
 // 1024 + Z is 0x6400 + Z and 64 + Z is 0x5400 + 16 Z for Z <= 15.
 __device__ __forceinline__ h16x2 neg_hi_of(uint32_t z) { return __builtin_bit_cast(h16x2, z * 0x00010001u + 0xe400e400u); }
 __device__ __forceinline__ h16x2 neg_lo_of(uint32_t z) { return __builtin_bit_cast(h16x2, z * 0x00100010u + 0xd400d400u); }
+
+// The same from byte c of four zero points, one v_perm_b32 each: the byte (for the second one z16 = the four zero points
+// << 4, which stay within their bytes) under the high bytes.
+__device__ __forceinline__ h16x2 neg_hi_at(uint32_t z, int c)
+{
+    return __builtin_bit_cast(h16x2, __builtin_amdgcn_perm(0xe400e400u, z, 0x07000500u + 0x00010001u * c));
+}
+__device__ __forceinline__ h16x2 neg_lo_at(uint32_t z16, int c)
+{
+    return __builtin_bit_cast(h16x2, __builtin_amdgcn_perm(0xd400d400u, z16, 0x07000500u + 0x00010001u * c));
+}
 
 // packed word (8 codes of one column) -> 8 exact fp16 values (code - Z), in the order
 // (k0,k4),(k1,k5),(k2,k6),(k3,k7): the nibbles are OR-ed into the mantissa of 1024.0
@@ -23,11 +42,8 @@ __device__ __forceinline__ h16x2 neg_lo_of(uint32_t z) { return __builtin_bit_ca
 __device__ __forceinline__ h16x8 dequant_word(uint32_t w, h16x2 neg_hi, h16x2 neg_lo, const UnpackConsts &uc)
 {
     const uint32_t w8 = w >> 8;
-    uint32_t t0, t1, t2, t3;
-    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(t0) : "v"(w), "v"(uc.mask_lo), "v"(uc.magic_lo));
-    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(t1) : "v"(w), "v"(uc.mask_hi), "v"(uc.magic_hi));
-    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(t2) : "v"(w8), "v"(uc.mask_lo), "v"(uc.magic_lo));
-    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(t3) : "v"(w8), "v"(uc.mask_hi), "v"(uc.magic_hi));
+    const uint32_t t0 = (w & uc.mask_lo) | uc.magic_lo, t1 = (w & uc.mask_hi) | uc.magic_hi;
+    const uint32_t t2 = (w8 & uc.mask_lo) | uc.magic_lo, t3 = (w8 & uc.mask_hi) | uc.magic_hi;
     h16x2 b0 = __builtin_bit_cast(h16x2, t0) + neg_hi;
     h16x2 b1 = __builtin_bit_cast(h16x2, t1) + neg_lo;
     h16x2 b2 = __builtin_bit_cast(h16x2, t2) + neg_hi;
@@ -43,11 +59,8 @@ __device__ __forceinline__ h16x8 dequant_word(uint32_t w, h16x2 neg_hi, h16x2 ne
 __device__ __forceinline__ h16x8 dequant_word_scaled(uint32_t w, h16x2 neg_hi, h16x2 neg_lo, h16x2 delta, const UnpackConsts &uc)
 {
     const uint32_t w8 = w >> 8;
-    uint32_t t0, t1, t2, t3;
-    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(t0) : "v"(w), "v"(uc.mask_lo), "v"(uc.magic_lo));
-    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(t1) : "v"(w), "v"(uc.mask_hi), "v"(uc.magic_hi));
-    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(t2) : "v"(w8), "v"(uc.mask_lo), "v"(uc.magic_lo));
-    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(t3) : "v"(w8), "v"(uc.mask_hi), "v"(uc.magic_hi));
+    const uint32_t t0 = (w & uc.mask_lo) | uc.magic_lo, t1 = (w & uc.mask_hi) | uc.magic_hi;
+    const uint32_t t2 = (w8 & uc.mask_lo) | uc.magic_lo, t3 = (w8 & uc.mask_hi) | uc.magic_hi;
     h16x2 b0 = (__builtin_bit_cast(h16x2, t0) + neg_hi) * delta;
     h16x2 b1 = (__builtin_bit_cast(h16x2, t1) + neg_lo) * delta;
     h16x2 b2 = (__builtin_bit_cast(h16x2, t2) + neg_hi) * delta;
