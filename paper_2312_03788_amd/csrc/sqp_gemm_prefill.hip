@@ -21,13 +21,15 @@
 //     LDS and the next weight words are unpacked; the hand-over to the next stage (wait for
 //     its loads, barrier) sits inside the last k-step, so the pipeline never drains.
 //   - Loads, waits and the per-stage barrier are explicit (assembly), as in the decode
-//     kernel: two stages stay in flight while one is consumed.
-// What bounds it: below a full chip the issue of instructions, on a full one the power limit.  us per call (M x K x N),
-// with column-major tile numbers -> with one compact run of tiles per XCD -> with the unpack in the order of k, no
+//     kernel: two stages stay in flight while one is consumed, issued between its MFMAs.
+// What bounds it: the matrix cores, at their own rate below a full chip (31 of 32 cycles per MFMA on 1024x8192x8192, 128
+// tiles; without the unpack 13 % less time), under the power limit on a full one.  us per call (M x K x N): tiles numbered
+// along a row of the output over all XCDs -> one compact run of tiles per XCD -> with the unpack in the order of k, no
 // padded stages (the loop of three used to round a K part of 16 up to 18) and an epilogue that reads one row tile at a
-// time (it used to spill, and every reload waited for the stores under way): 512 x 4096 x 22016 113 -> 111 -> 98,
-// 160 x 8192 x 8192 40.3 -> 40.0 -> 35.3, 1000 x 4096 x 12288 110 -> 109 -> 98, 4096 x 4096 x 4096 131 -> 129 -> 118,
-// 2048 x 8192 x 44032 1375 -> 1346 -> 1255 (1.18 PFLOP/s).
+// time (it used to spill, and every reload waited for the stores under way) -> with half the scalar instructions
+// per stage and every LDS read and load between two MFMAs instead of in clusters in front of a k-step:
+// 512 x 4096 x 22016 111 -> 109 -> 95 -> 88, 1000 x 4096 x 12288 108 -> 107 -> 95 -> 91, 4096 x 4096 x 4096 128 -> 126 ->
+// 113 -> 109, 2048 x 8192 x 10240 318 -> 318 -> 296 -> 279, 2048 x 8192 x 44032 1330 -> 1300 -> 1210 -> 1145 (1.29 PFLOP/s).
 // Eight waves of 128 x 64 (two per SIMD) needed fewer cycles per MFMA, but the chip then
 // clocked lower under its power limit and the result was a little slower, so one wave per SIMD
 // it is.
@@ -162,38 +164,55 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
         uint32_t zr[NQ];  // NT zero points, one byte each
     };
 
-    // The loading side walks the stages with wave-uniform byte pointers that are advanced by
-    // constant strides (scalar adds only); past the last stage they stop, so that the look-ahead
-    // of the branch-free stages re-reads the last one (cache hits).
-    const long wrow2 = (long)N * 8;        // two packed rows (one k-step) in bytes
-    const unsigned char *wq = reinterpret_cast<const unsigned char *>(packed) + (long)(stage0 * KH + kh) * 4 * wrow2;
-    const long prow = G32 ? (long)stage0 * 2 : (long)((stage0 * KH + kh) / spg);  // first parameter row of this wave
+    // The loading side walks the stages with one 32-bit scalar offset per stream (buffer loads; a row's place is in the
+    // lanes' offsets); past the last stage the offsets stop, so that the look-ahead of the branch-free stages re-reads
+    // the last one (cache hits).  Every scalar instruction costs the wave as much as a vector one: 30 per stage, where
+    // 64-bit pointers with a clamp each took 56.
+    typedef int rsrc_t __attribute__((ext_vector_type(4)));
+    auto buffer_of = [&](const void *p, uint32_t bytes) {
+        const uint64_t at = reinterpret_cast<uint64_t>(p);
+        return rsrc_t{(int)(uint32_t)at, (int)(uint32_t)(at >> 32), (int)bytes, 0x00020000};
+    };
+    const rsrc_t w_buf = buffer_of(packed, (uint32_t)(K / 8) * (uint32_t)N * 4u);
+    const rsrc_t s_buf = buffer_of(scales, (uint32_t)(K / group) * (uint32_t)N * 2u), z_buf = buffer_of(zeros, (uint32_t)(K / group) * (uint32_t)N);
+    const uint32_t wstage = (uint32_t)N * 32u;    // eight packed rows (64 k) in bytes
+    const int first = stage0 * KH + kh;           // this wave's first 64 k
+    uint32_t w_at = (uint32_t)first * wstage;
+    const uint32_t w_most = w_at + (uint32_t)(stages - 1) * (KH * wstage);
     const int prow_step = KH / spg, kin_step = KH % spg;  // groups and part of one that a stage advances by
-    const unsigned char *sq = reinterpret_cast<const unsigned char *>(scales) + prow * N * 2;
-    const unsigned char *zq = zeros + prow * N;
-    const unsigned char *xq = reinterpret_cast<const unsigned char *>(x) + (long)stage0 * (KH * BK * 2);
-    int ist = 0, kin = (stage0 * KH + kh) % spg;        // stage being issued (relative), its position inside its group
-    const uint32_t voff_w = (uint32_t)(kb * N + ncol) * 4u;
-    const uint32_t voff_s = (uint32_t)ncol * 2u, voff_z = (uint32_t)ncol;
-    auto issue_w = [&](Stage &s) {
+    int kin = first % spg;                        // position of the stage being issued inside its group
+    uint32_t z_at = (uint32_t)(first / spg) * (uint32_t)(N * NQ);  // zero points of its group; the steps are at twice that
+    const uint32_t z_most = (uint32_t)((first + (stages - 1) * KH) / spg) * (uint32_t)(N * NQ);
+    const uint32_t z_inc = (uint32_t)prow_step * (uint32_t)(N * NQ), z_wrap = z_inc + (uint32_t)(N * NQ);
+    uint32_t x_at = (uint32_t)stage0 * (KH * BK * 2);
+    const uint32_t x_most = x_at + (uint32_t)(stages - 1) * (KH * BK * 2), x_bytes = (uint32_t)M * (uint32_t)K * 2u;
+    uint32_t voff_w[4], voff_s[NQ], voff_z[NQ];
 #pragma unroll
-        for (int ks = 0; ks < 4; ks++) {
-            const unsigned char *base = wq + ks * wrow2;  // wave-uniform
+    for (int ks = 0; ks < 4; ks++) voff_w[ks] = (uint32_t)((kb + 2 * ks) * N + ncol) * 4u;
+#pragma unroll
+    for (int g = 0; g < NQ; g++) {
+        voff_z[g] = (uint32_t)(g * N + ncol);
+        voff_s[g] = voff_z[g] * 2u;
+    }
+    // load j of the OW on the weight side of a stage
+    auto issue_w = [&](Stage &s, int j) {
+        if (j < 4) {
             if constexpr (NT == 4)
-                asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(s.w[ks]) : "v"(voff_w), "s"(base) : "memory");
+                asm volatile("buffer_load_dwordx4 %0, %1, %2, %3 offen" : "=v"(s.w[j]) : "v"(voff_w[j]), "s"(w_buf), "s"(w_at) : "memory");
             else
-                asm volatile("global_load_dwordx2 %0, %1, %2" : "=v"(s.w[ks]) : "v"(voff_w), "s"(base) : "memory");
-        }
-#pragma unroll
-        for (int g = 0; g < NQ; g++) {
-            const unsigned char *sg = sq + (long)g * N * 2, *zg = zq + (long)g * N;  // wave-uniform
-            if constexpr (NT == 4) {
-                asm volatile("global_load_dwordx2 %0, %1, %2" : "=v"(s.sc[g]) : "v"(voff_s), "s"(sg) : "memory");
-                asm volatile("global_load_dword %0, %1, %2" : "=v"(s.zr[g]) : "v"(voff_z), "s"(zg) : "memory");
-            } else {
-                asm volatile("global_load_dword %0, %1, %2" : "=v"(s.sc[g]) : "v"(voff_s), "s"(sg) : "memory");
-                asm volatile("global_load_ushort %0, %1, %2" : "=v"(s.zr[g]) : "v"(voff_z), "s"(zg) : "memory");
-            }
+                asm volatile("buffer_load_dwordx2 %0, %1, %2, %3 offen" : "=v"(s.w[j]) : "v"(voff_w[j]), "s"(w_buf), "s"(w_at) : "memory");
+        } else if ((j & 1) == 0) {
+            const int g = (j - 4) >> 1;
+            if constexpr (NT == 4)
+                asm volatile("buffer_load_dwordx2 %0, %1, %2, %3 offen" : "=v"(s.sc[g]) : "v"(voff_s[g]), "s"(s_buf), "s"(z_at * 2u) : "memory");
+            else
+                asm volatile("buffer_load_dword %0, %1, %2, %3 offen" : "=v"(s.sc[g]) : "v"(voff_s[g]), "s"(s_buf), "s"(z_at * 2u) : "memory");
+        } else {
+            const int g = (j - 4) >> 1;
+            if constexpr (NT == 4)
+                asm volatile("buffer_load_dword %0, %1, %2, %3 offen" : "=v"(s.zr[g]) : "v"(voff_z[g]), "s"(z_buf), "s"(z_at) : "memory");
+            else
+                asm volatile("buffer_load_ushort %0, %1, %2, %3 offen" : "=v"(s.zr[g]) : "v"(voff_z[g]), "s"(z_buf), "s"(z_at) : "memory");
         }
     };
     auto landed = [&](Stage &s, auto after) {
@@ -221,40 +240,25 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
         xoff[j] = (uint32_t)grow * (uint32_t)K * 2u + (uint32_t)((wave + W * j) / (BM / 8) * (BK * 2) + piece * 16);
     }
     auto issue_x = [&](int slot, int j) {
-        unsigned char *dst = xring + slot * XSTAGE + (wave + W * j) * 1024;
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(xq + xoff[j]),
-                                         (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
+        copy16_to_lds(x, x_bytes, xoff[j], x_at, xring + slot * XSTAGE + (wave + W * j) * 1024);
     };
-    // all loads of the stage have been issued: step the pointers unless it was the last stage
+    // all loads of the stage have been issued: step the offsets up to the last stage's
     auto advance = [&]() {
-        const bool more = ist + 1 < stages;
-        ist += more ? 1 : 0;
-        wq += more ? KH * 4 * wrow2 : 0;
-        xq += more ? KH * BK * 2 : 0;
-        if constexpr (KH == 1) {
-            kin += more ? 1 : 0;
-            const bool wrap = kin == spg;
-            kin = wrap ? 0 : kin;
-            sq += wrap ? (long)N * 2 * NQ : 0;
-            zq += wrap ? (long)N * NQ : 0;
-        } else if (more) {
-            kin += kin_step;
-            const bool wrap = kin >= spg;
-            kin -= wrap ? spg : 0;
-            const int rows = prow_step + (wrap ? 1 : 0);
-            sq += (long)rows * N * 2;
-            zq += (long)rows * N;
-        }
+        w_at = min(w_at + KH * wstage, w_most);
+        x_at = min(x_at + KH * BK * 2, x_most);
+        kin += kin_step;
+        const bool wrap = kin >= spg;
+        kin -= wrap ? spg : 0;
+        z_at = min(z_at + (wrap ? z_wrap : z_inc), z_most);
     };
     const uint32_t xrd0 = (uint32_t)(size_t)xring +
                           (uint32_t)(kh * XHALF + ((wm * 32 * RT + l32) >> 3) * 1024 + ((wm * 32 * RT + l32) & 7) * 128);
     const int xkey = (l32 >> 1) & 7;
 
-    auto read_a = [&](u32x4 (&xa)[RT], int slot, int ks) {
+    // fragment of row tile mt of a k-step
+    auto read_a = [&](u32x4 (&xa)[RT], int slot, int ks, int mt) {
         const uint32_t poff = xrd0 + (uint32_t)(slot * XSTAGE) + (uint32_t)((((ks * 2 + kb) ^ xkey)) * 16);
-#pragma unroll
-        for (int mt = 0; mt < RT; mt++)
-            asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(xa[mt]) : "v"(poff), "n"(mt * 4096) : "memory");
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(xa[mt]) : "v"(poff), "n"(mt * 4096) : "memory");
     };
     auto wait_a = [&](u32x4 (&xa)[RT]) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -331,18 +335,19 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
         else asm volatile("v_pk_mul_f16 %0, %0, %1" : "+v"(b) : "v"(delta[qs][t]));
     };
 
-    issue_w(stg[0]);
 #pragma unroll
-    for (int j = 0; j < OX; j++) issue_x(0, j);
-    advance();
-    issue_w(stg[1]);
+    for (int p = 0; p < 2; p++) {
 #pragma unroll
-    for (int j = 0; j < OX; j++) issue_x(1, j);
-    advance();
+        for (int j = 0; j < OX; j++) issue_x(p, j);
+#pragma unroll
+        for (int j = 0; j < OW; j++) issue_w(stg[p], j);
+        advance();
+    }
     landed(stg[0], std::integral_constant<int, OX + OW>());
     asm volatile("s_barrier" ::: "memory");
     stage_consts(stg[0], true);
-    read_a(xa[0], 0, 0);
+#pragma unroll
+    for (int mt = 0; mt < RT; mt++) read_a(xa[0], 0, 0, mt);
     // first operands of the pipeline, by the ordinary helper
 #pragma unroll
     for (int t = 0; t < NT; t++) {
@@ -360,29 +365,37 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
         Stage &next_s = stg[(d + 1) % D];
         Stage &fill_s = stg[(d + 2) % D];
         const int slot_next = slot + 1 < XD ? slot + 1 : 0, slot_fill = slot + 2 < XD ? slot + 2 : slot + 2 - XD;
-        issue_w(fill_s);
 #pragma unroll
         for (int ks = 0; ks < 4; ks++) {
             const int cur = ks & 1, nxt = cur ^ 1;
-#pragma unroll
-            for (int j = OX * ks / 4; j < OX * (ks + 1) / 4; j++) issue_x(slot_fill, j);
-            if (ks < 3) {
-                read_a(xa[nxt], slot, ks + 1);
-            } else {
-                advance();
+            if (ks == 3) {
                 landed(next_s, std::integral_constant<int, OX + OW>());
                 asm volatile("s_barrier" ::: "memory");
                 stage_consts(next_s, d == D - 1 || stages > d + 1);
-                read_a(xa[nxt], slot_next, 0);
             }
             const wvec wn = ks < 3 ? cur_s.w[ks + 1] : next_s.w[0];
+            // Behind the MFMAs, one each: the fragments of the next k-step, then this one's share of the loads of stage
+            // s + 2 (all of them are issued by the end of k-step 2).
+            const int x0 = OX * ks / 3, x1 = ks < 3 ? OX * (ks + 1) / 3 : x0, w0 = OW * ks / 3, w1 = ks < 3 ? OW * (ks + 1) / 3 : w0;
 #pragma unroll
             for (int i = 0; i < NMF; i++) {
                 mfma(acc[i / NT][i % NT], xa[cur][i / NT], bq[cur][i % NT]);
+                if (i < RT) {
+                    if (ks < 3) read_a(xa[nxt], slot, ks + 1, i);
+                    else read_a(xa[nxt], slot_next, 0, i);
+                }
 #pragma unroll
                 for (int e = i * (4 * NG) / NMF; e < (i + 1) * (4 * NG) / NMF; e++)
                     valu(order.g[e / 4], e % 4, cur, wn, (ks + 1) & 3);
+                if (i >= RT) {
+#pragma unroll
+                    for (int l = (i - RT) * (x1 - x0 + w1 - w0) / (NMF - RT); l < (i - RT + 1) * (x1 - x0 + w1 - w0) / (NMF - RT); l++) {
+                        if (l < x1 - x0) issue_x(slot_fill, x0 + l);
+                        else issue_w(fill_s, w0 + l - (x1 - x0));
+                    }
+                }
             }
+            if (ks == 2) advance();
             wait_a(xa[nxt]);
         }
         slot = slot_next;
@@ -815,14 +828,14 @@ static size_t plan_partial_bytes(const LaunchPlan &q)
 // Estimated time (us) of one launch of tiles with all that belongs to it, on a chip that it fills once:
 // a + stages * (b + l * workgroups / compute units) + (h + p * MB), the last two with K parts (MB: their fp32 sums
 // written and read); a stage is 64 k, 128 with waves that halve K.  Up to one workgroup per compute unit, or two of the
-// variants that leave half the registers.  Fitted to 9200 launches of 289 shapes (65 to 1536 rows, N 1024 to 24576,
-// K 1024 to 16384, groups of 128): rms 2.6 to 4.5 % by variant.  0: not covered.
+// variants that leave half the registers.  Fitted to 9085 launches of 294 shapes (65 to 1536 rows, N 1024 to 24576,
+// K 1024 to 16384, groups of 128): rms 2.7 to 5.0 % by variant.  0: not covered.
 static double launch_us(const TileLaunch &l, int M, int N, int K, int cus)
 {
     struct Cost { double a, b, l, h, p; };
-    static const Cost one[4] = {{7.40, 0.543, 0.093, 1.65, 0.167}, {8.53, 0.662, 0.109, 1.14, 0.154}, {9.49, 0.763, 0.173, 1.54, 0.129}, {10.26, 0.873, 0.224, 1.46, 0.117}};
-    static const Cost halves[4] = {{6.76, 0.578, 0.121, 1.53, 0.238}, {7.38, 0.688, 0.141, 1.92, 0.216}, {8.73, 0.783, 0.222, 1.54, 0.198}, {9.04, 0.932, 0.257, 1.79, 0.180}};
-    static const Cost two[2] = {{9.82, 0.615, 0.365, 2.72, 0.077}, {10.44, 0.821, 0.455, 2.04, 0.082}}, wide = {8.25, 1.123, 0.360, 0, 0};
+    static const Cost one[4] = {{7.36, 0.465, 0.112, 1.75, 0.164}, {8.72, 0.479, 0.206, 1.35, 0.140}, {9.94, 0.558, 0.278, 1.39, 0.119}, {10.87, 0.648, 0.318, 1.23, 0.113}};
+    static const Cost halves[4] = {{6.76, 0.460, 0.174, 1.81, 0.214}, {7.20, 0.494, 0.266, 2.28, 0.188}, {8.69, 0.576, 0.346, 1.58, 0.187}, {9.20, 0.660, 0.387, 1.53, 0.185}};
+    static const Cost two[2] = {{8.92, 0.545, 0.350, 3.09, 0.080}, {10.60, 0.734, 0.409, 1.19, 0.094}}, wide = {8.65, 0.951, 0.372, 0, 0};
     const long groups = l.tiles * l.parts;
     if (groups > 2L * cus || (groups > cus && (l.nt == 4 || l.kh == 2 || l.rt > 4))) return 0;
     const Cost &c = l.nt == 4 ? wide : l.kh == 2 ? halves[l.rt - 3] : groups > cus ? two[l.rt - 3] : one[l.rt - 3];
@@ -835,8 +848,8 @@ static double launch_us(const TileLaunch &l, int M, int N, int K, int cus)
 // the K parts (or none) for as many workgroups, at the price of twice the activations per compute unit; tiles of 96 and
 // 128 rows x 256 columns leave half of the registers, so that two workgroups per compute unit hide each other's
 // waits.  The sizes reported to callers are those of the plan itself: what they have stored goes on to hold.
-// us, plan -> quicker one: 160x8192x8192 36.3 -> 34.4, 160x4096x22016 44.5 -> 39.8, 300x5120x15360 59.6 -> 55.5, 490x2816x5840
-// 32.5 -> 25.9, 999x2176x3832 32.8 -> 24.3, 403x3072x22792 72.2 -> 68.7; over the fitted shapes the pick is 0.4 %
+// us, plan -> quicker one when it was built: 160x8192x8192 36.3 -> 34.4, 160x4096x22016 44.5 -> 39.8, 300x5120x15360 59.6 ->
+// 55.5, 490x2816x5840 32.5 -> 25.9, 999x2176x3832 32.8 -> 24.3, 403x3072x22792 72.2 -> 68.7; over the fitted shapes the pick is 0.5 %
 // behind the best in the mean.
 static double quicker_launch(LaunchPlan &q, int M, int N, int K, int group, int cus, size_t room)
 {
@@ -892,7 +905,8 @@ static bool row_blocks_cover(int K, int group) { return K % 128 == 0 && (group =
 // taken where its estimated time is 3 % below that of the tiles (launch_us; 8 % below plan_launches' coarser estimate and
 // the 6.7 us that it leaves out).
 // The estimate: A + iterations * (B + L * workgroups / compute units) + (H + S * parts), the last two terms with
-// more than one K part; at most one eight-wave workgroup (kp = 2) or two four-wave ones per compute unit.
+// more than one K part (B and L 6 % below the fit since the kernel's iterations are that much shorter: 91 other calls); at
+// most one eight-wave workgroup (kp = 2) or two four-wave ones per compute unit.
 // Fitted to 13700 launches of 1547 shapes (65 to 1024 rows, N 768 to 24576, K 512 to 8192, groups of 32, 64, 128
 // and 256, weights from HBM): rms 3 to 6 %, the choice 1 % behind the best variant in the mean.  On 945 other calls
 // that take row blocks, drawn over these ranges: 1.46 times faster than the tiles in the geometric mean, 1.5 % of
@@ -904,8 +918,8 @@ static SqpStripPlan row_blocks_plan(int M, int N, int K, int group, int cus, dou
 {
     struct Cost { double a, b, l, h, s; };
     static const Cost cost[2][3] = {  // 48 and 64 rows; kp = 1 with up to one and two workgroups per unit, kp = 2
-        {{3.92, 0.651, 0.062, 2.14, 0.28}, {5.25, 0.755, 0.152, 1.77, 0.40}, {4.83, 1.025, 0.096, 1.60, 0.22}},
-        {{4.19, 0.736, 0.079, 2.03, 0.31}, {5.75, 0.820, 0.211, 1.68, 0.47}, {5.11, 1.154, 0.150, 1.58, 0.29}},
+        {{3.92, 0.612, 0.058, 2.14, 0.28}, {5.25, 0.710, 0.143, 1.77, 0.40}, {4.83, 0.964, 0.090, 1.60, 0.22}},
+        {{4.19, 0.692, 0.074, 2.03, 0.31}, {5.75, 0.771, 0.198, 1.68, 0.47}, {5.11, 1.085, 0.141, 1.58, 0.29}},
     };
     SqpStripPlan best = {2, 1, 2, 1, 0};
     if (M <= 64 || !row_blocks_cover(K, group)) return best;

@@ -82,14 +82,6 @@ __device__ __forceinline__ unsigned small_divide(unsigned a, unsigned b)
     return __builtin_amdgcn_readfirstlane((unsigned)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b)));
 }
 
-// Direct global -> LDS load of 16 bytes per lane: lane i's from base + lane_offset + offset to dst + 16 i (dst and offset
-// wave-uniform).  A buffer load: neither a 64-bit address per lane nor one per call; bytes: size of the buffer.
-__device__ __forceinline__ void copy16_to_lds(const void *base, uint32_t bytes, uint32_t lane_offset, uint32_t offset, void *dst)
-{
-    const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void *)dst, 16, lane_offset, offset, 0, 0);
-}
-
 // Split-K tickets: one per 128-byte line (atomics on one line are served one after the other).
 constexpr int TICKET_STRIDE = 32;
 

@@ -1,9 +1,17 @@
-// Device helpers shared by the W4A16 GEMM kernels: 4-bit code unpack and the matching
+// Device helpers shared by the W4A16 GEMM kernels: loads with a scalar offset, 4-bit code unpack and the matching
 // permutation of activations (Eq. 1 of arXiv 2312.03788, second line: (code - Z) * Delta).
 #pragma once
 #include "sqp_common.h"
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+// Direct global -> LDS load of 16 bytes per lane: lane i's from base + lane_offset + offset to dst + 16 i (dst and offset
+// wave-uniform).  A buffer load: neither a 64-bit address per lane nor one per call; bytes: size of the buffer.
+__device__ __forceinline__ void copy16_to_lds(const void *base, uint32_t bytes, uint32_t lane_offset, uint32_t offset, void *dst)
+{
+    const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void *)dst, 16, lane_offset, offset, 0, 0);
+}
 
 // Constants of the nibble unpack, held in registers (v_and_or_b32 takes no literals, and one scalar).  (The empty asm hides their
 // values, so the compiler keeps them there and makes one instruction of each and-or below.  Those were asm statements
