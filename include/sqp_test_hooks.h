@@ -45,7 +45,7 @@ void sqp_debug_set_prefill_tiles(int mode);        /* 0 = automatic, 1 = full ti
 void sqp_debug_set_prefill_shape(int shape);       /* 0 = automatic, 1 = 128 x 512 full tiles, 2 = 256 x 256 */
 void sqp_debug_set_prefill_ksplit(int k);          /* -1 = automatic, 0 or 1 = never, k >= 2 = k parts */
 void sqp_debug_set_prefill_variant(int rt, int nt, int parts);  /* one launch of tiles of 32 rt rows x 128 nt columns, K parts
-                                                      (rt 3 to 6 with nt 2, or 4 with nt 4; parts > 1 with nt 2; nt 2 + 16:
+                                                      (rt 3 to 6 with nt 2, 4 or 5 with nt 3, or 4 with nt 4; parts > 1 with nt 2; nt 2 + 16:
                                                       half the columns, the waves halve K, K % 128 == 0); 0 = automatic */
 /* The plan in 128-row tiles for a shape on a chip of `cus` compute units: full tiles of the first
  * launch, half-width tiles of the second, K parts.  Host arithmetic only. */

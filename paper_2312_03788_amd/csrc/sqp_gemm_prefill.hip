@@ -89,6 +89,23 @@ __device__ __forceinline__ void tile_at(const TileMap &m, uint32_t i, int &row, 
     col = (int)(m.halves ? 2 * c + ((m.tile0 + i) & 1) : c);
 }
 
+// Final store of 8 adjacent columns of row m: the fp16 values themselves, y [M][N], or with epi the (gate, up) pairs'
+// SiLU(gate) * up, y [M][N/2].
+__device__ __forceinline__ void store_octet(h16 *y, int m, int N, int n, int epi, const f32x4 &a, const f32x4 &b)
+{
+    if (epi != 0) {
+        h16x4 o;
+        o.x = (h16)(sqp_silu(a.x) * a.y); o.y = (h16)(sqp_silu(a.z) * a.w);
+        o.z = (h16)(sqp_silu(b.x) * b.y); o.w = (h16)(sqp_silu(b.z) * b.w);
+        *reinterpret_cast<h16x4 *>(y + (size_t)m * (N >> 1) + (n >> 1)) = o;
+        return;
+    }
+    h16x8 o;
+    o.s0 = (h16)a.x; o.s1 = (h16)a.y; o.s2 = (h16)a.z; o.s3 = (h16)a.w;
+    o.s4 = (h16)b.x; o.s5 = (h16)b.y; o.s6 = (h16)b.z; o.s7 = (h16)b.w;
+    *reinterpret_cast<h16x8 *>(y + (size_t)m * N + n) = o;
+}
+
 // RT, NT: 32-row and 32-column MFMA tiles per wave; WM: waves along the rows, the other 4 / WM along
 // the columns.  A workgroup owns 32 RT WM rows x 32 NT (4 / WM) columns:
 //   <4, 4, 1>: 128 x 512, the four waves side by side on the same 128 rows.  Every packed word
@@ -98,6 +115,7 @@ __device__ __forceinline__ void tile_at(const TileMap &m, uint32_t i, int &row, 
 //   <4, 2, *>: the same with half the columns (128 x 256 / 256 x 128), used for the tiles left over
 //           after the last full round so that the tail of a launch costs half a round, and for
 //           the K-split launches.
+//   <4, 3, 1>, <5, 3, 1>: 128 or 160 x 384 (quicker_launch).
 //   <3, 2, 1>, <5, 2, 1>, <6, 2, 1>: 96, 160 or 192 rows x 256 columns, K-split launches of row
 //           counts that would leave much of a 128-row tile empty.
 // KH = 2: the waves of a column pair halve K between them, stage by stage (a stage is 128 k then), and add their sums
@@ -115,10 +133,12 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
     constexpr int WNW = W / WM / KH;       // waves along the columns
     constexpr int BM = 32 * RT * WM;       // rows per workgroup
     constexpr int WN = 32 * NT;            // columns per wave
-    static_assert(NT == 2 || NT == 4, "a lane's columns are one load");
+    static_assert(NT >= 2 && NT <= 4, "a lane's columns are one load");
+    static_assert(NT != 3 || (WM == 1 && KH == 1 && !G32), "three columns per lane");
     static_assert(KH == 1 || (WM == 1 && !G32), "waves that halve K");
     typedef uint32_t wvec __attribute__((ext_vector_type(NT)));
     typedef std::conditional_t<NT == 4, u32x2, uint32_t> scvec;
+    constexpr int PL = NT == 3 ? 3 : 1;    // loads that a lane's steps take, and its zero points
     constexpr int D = 3;                   // register stages of packed weights (two in flight)
     constexpr int XD = KH == 1 ? 4 : 3;    // LDS slots of activations
     constexpr int XHALF = BM * BK * 2;     // 64 k of activations: blocks of 8 rows x 128 bytes
@@ -126,7 +146,7 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
     constexpr int OX = KH * (BM / 8) / W;  // direct loads per wave per stage (one per 1 KB block), spread over its four k-steps
     constexpr int WGN = WNW * WN;          // columns per workgroup
     constexpr int NQ = G32 ? 2 : 1;        // quantisation groups per stage
-    constexpr int OW = 4 + 2 * NQ;
+    constexpr int OW = 4 + 2 * NQ * PL;
     static_assert(2 * (OX + OW) < 64, "vmcnt field");
     __shared__ __attribute__((aligned(1024))) unsigned char xring[XD * XSTAGE];
     static_assert(sizeof(xring) <= 160 * 1024, "LDS of a workgroup");
@@ -148,6 +168,7 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
     const int spg = G32 ? 1 : group / BK;  // stages per quantisation group (G32: two groups per stage)
 
     int ncol = n0 + NT * l32;
+    if (NT == 3 && ncol + 2 >= N && ncol < N) ncol = N - 3;  // (the columns of the lane before again: none past the row is read)
     if (ncol >= N) ncol = 0;
 
     f32x16 acc[RT][NT];
@@ -160,8 +181,8 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
 
     struct Stage {
         wvec w[4];    // per k-step: packed words of the lane's NT columns
-        scvec sc[NQ];     // NT fp16 steps (per group of the stage)
-        uint32_t zr[NQ];  // NT zero points, one byte each
+        scvec sc[NQ * PL];     // NT fp16 steps (per group of the stage; three columns: one each, no load is aligned to them)
+        uint32_t zr[NQ * PL];  // NT zero points, one byte each
     };
 
     // The loading side walks the stages with one 32-bit scalar offset per stream (buffer loads; a row's place is in the
@@ -186,12 +207,12 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
     const uint32_t z_inc = (uint32_t)prow_step * (uint32_t)(N * NQ), z_wrap = z_inc + (uint32_t)(N * NQ);
     uint32_t x_at = (uint32_t)stage0 * (KH * BK * 2);
     const uint32_t x_most = x_at + (uint32_t)(stages - 1) * (KH * BK * 2), x_bytes = (uint32_t)M * (uint32_t)K * 2u;
-    uint32_t voff_w[4], voff_s[NQ], voff_z[NQ];
+    uint32_t voff_w[4], voff_s[NQ * PL], voff_z[NQ * PL];
 #pragma unroll
     for (int ks = 0; ks < 4; ks++) voff_w[ks] = (uint32_t)((kb + 2 * ks) * N + ncol) * 4u;
 #pragma unroll
-    for (int g = 0; g < NQ; g++) {
-        voff_z[g] = (uint32_t)(g * N + ncol);
+    for (int g = 0; g < NQ * PL; g++) {
+        voff_z[g] = NT == 3 ? (uint32_t)(ncol + g) : (uint32_t)(g * N + ncol);
         voff_s[g] = voff_z[g] * 2u;
     }
     // load j of the OW on the weight side of a stage
@@ -199,17 +220,23 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
         if (j < 4) {
             if constexpr (NT == 4)
                 asm volatile("buffer_load_dwordx4 %0, %1, %2, %3 offen" : "=v"(s.w[j]) : "v"(voff_w[j]), "s"(w_buf), "s"(w_at) : "memory");
+            else if constexpr (NT == 3)
+                asm volatile("buffer_load_dwordx3 %0, %1, %2, %3 offen" : "=v"(s.w[j]) : "v"(voff_w[j]), "s"(w_buf), "s"(w_at) : "memory");
             else
                 asm volatile("buffer_load_dwordx2 %0, %1, %2, %3 offen" : "=v"(s.w[j]) : "v"(voff_w[j]), "s"(w_buf), "s"(w_at) : "memory");
         } else if ((j & 1) == 0) {
             const int g = (j - 4) >> 1;
-            if constexpr (NT == 4)
+            if constexpr (NT == 3)
+                asm volatile("buffer_load_ushort %0, %1, %2, %3 offen" : "=v"(s.sc[g]) : "v"(voff_s[g]), "s"(s_buf), "s"(z_at * 2u) : "memory");
+            else if constexpr (NT == 4)
                 asm volatile("buffer_load_dwordx2 %0, %1, %2, %3 offen" : "=v"(s.sc[g]) : "v"(voff_s[g]), "s"(s_buf), "s"(z_at * 2u) : "memory");
             else
                 asm volatile("buffer_load_dword %0, %1, %2, %3 offen" : "=v"(s.sc[g]) : "v"(voff_s[g]), "s"(s_buf), "s"(z_at * 2u) : "memory");
         } else {
             const int g = (j - 4) >> 1;
-            if constexpr (NT == 4)
+            if constexpr (NT == 3)
+                asm volatile("buffer_load_ubyte %0, %1, %2, %3 offen" : "=v"(s.zr[g]) : "v"(voff_z[g]), "s"(z_buf), "s"(z_at) : "memory");
+            else if constexpr (NT == 4)
                 asm volatile("buffer_load_dword %0, %1, %2, %3 offen" : "=v"(s.zr[g]) : "v"(voff_z[g]), "s"(z_buf), "s"(z_at) : "memory");
             else
                 asm volatile("buffer_load_ushort %0, %1, %2, %3 offen" : "=v"(s.zr[g]) : "v"(voff_z[g]), "s"(z_buf), "s"(z_at) : "memory");
@@ -220,7 +247,7 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
 #pragma unroll
         for (int ks = 0; ks < 4; ks++) asm volatile("" : "+v"(s.w[ks]));
 #pragma unroll
-        for (int g = 0; g < NQ; g++) {
+        for (int g = 0; g < NQ * PL; g++) {
             asm volatile("" : "+v"(s.sc[g]));
             asm volatile("" : "+v"(s.zr[g]));
         }
@@ -277,11 +304,13 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
         for (int g = 0; g < NQ; g++)
 #pragma unroll
             for (int t = 0; t < NT; t++) {
-                const uint32_t z = (s.zr[g] >> (8 * t)) & 0xffu;
+                const uint32_t z = NT == 3 ? s.zr[t] : (s.zr[g] >> (8 * t)) & 0xffu;
                 neg[g][t] = neg_pair_of(z);
                 uint32_t sw;
-                if constexpr (NT == 4) sw = s.sc[g][t >> 1]; else sw = s.sc[g];
-                delta[g][t] = __builtin_bit_cast(h16x2, __builtin_amdgcn_perm(sw, sw, (t & 1) ? sel_odd : sel_even));
+                if constexpr (NT == 4) sw = s.sc[g][t >> 1];
+                else if constexpr (NT == 3) sw = s.sc[t];
+                else sw = s.sc[g];
+                delta[g][t] = __builtin_bit_cast(h16x2, __builtin_amdgcn_perm(sw, sw, NT != 3 && (t & 1) ? sel_odd : sel_even));
             }
     };
 
@@ -437,7 +466,7 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
 #pragma unroll
         for (int ks = 0; ks < 4; ks++) asm volatile("" ::"v"(stg[j].w[ks]));
 #pragma unroll
-        for (int g = 0; g < NQ; g++) {
+        for (int g = 0; g < NQ * PL; g++) {
             asm volatile("" ::"v"(stg[j].sc[g]));
             asm volatile("" ::"v"(stg[j].zr[g]));
         }
@@ -505,6 +534,33 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
         }
         return;
     }
+    if constexpr (NT == 3) {
+        // Three columns per lane are no aligned store, nor whole (gate, up) pairs: a row tile at a time goes through this
+        // wave's part of the ring and out in octets of a row.
+        constexpr int STRIDE = WN + 4;  // floats per row of the exchange
+        static_assert(W * 32 * STRIDE * 4 <= sizeof(xring) || RT < 4, "the exchange reuses the ring");
+        if constexpr (W * 32 * STRIDE * 4 <= sizeof(xring)) {
+            float *ex = reinterpret_cast<float *>(xring) + e_wave * (32 * STRIDE);
+            const int n0 = nbase + e_wave * WN, own = NT * e_l32, ecol = own + 2 >= N - n0 && own < N - n0 ? N - 3 - n0 : own;
+            asm volatile("s_barrier" ::: "memory");  // (all loads into LDS have landed, all reads of it too)
+#pragma unroll
+            for (int mt = 0; mt < RT; mt++) {
+                ready(mt);
+#pragma unroll
+                for (int r = 0; r < 16; r++)
+#pragma unroll
+                    for (int t = 0; t < NT; t++) ex[(8 * (r >> 2) + 4 * e_kb + (r & 3)) * STRIDE + ecol + t] = acc[mt][t][r];
+#pragma unroll
+                for (int i = 0; i < 32 * WN / 8 / 64; i++) {
+                    const int o = i * 64 + (tid & 63), row = o / (WN / 8), col = o % (WN / 8) * 8;
+                    const f32x4 a = *reinterpret_cast<const f32x4 *>(ex + row * STRIDE + col), b = *reinterpret_cast<const f32x4 *>(ex + row * STRIDE + col + 4);
+                    const int m = m0 + mt * 32 + row, n = n0 + col;
+                    if (m < M && n < N) store_octet(y, m, N, n, epi, a, b);
+                }
+            }
+        }
+        return;
+    }
     if (nout < N) {
         h16 *ycol = y + nout;
 #pragma unroll
@@ -561,17 +617,7 @@ __global__ void __launch_bounds__(256) splitk_reduce_kernel(const float *__restr
         a += q[0];
         b += q[1];
     }
-    if (epi != 0) {  // (gate, up) pairs -> SiLU(gate) * up; 8 adjacent columns of [M][N] are 4 of [M][N/2]
-        h16x4 o;
-        o.x = (h16)(sqp_silu(a.x) * a.y); o.y = (h16)(sqp_silu(a.z) * a.w);
-        o.z = (h16)(sqp_silu(b.x) * b.y); o.w = (h16)(sqp_silu(b.z) * b.w);
-        *reinterpret_cast<h16x4 *>(y + (size_t)m * (N >> 1) + (n >> 1)) = o;
-        return;
-    }
-    h16x8 o;
-    o.s0 = (h16)a.x; o.s1 = (h16)a.y; o.s2 = (h16)a.z; o.s3 = (h16)a.w;
-    o.s4 = (h16)b.x; o.s5 = (h16)b.y; o.s6 = (h16)b.z; o.s7 = (h16)b.w;
-    *reinterpret_cast<h16x8 *>(y + (size_t)m * N + n) = o;
+    store_octet(y, m, N, n, epi, a, b);
 }
 
 }  // namespace
@@ -836,27 +882,38 @@ static double launch_us(const TileLaunch &l, int M, int N, int K, int cus)
     static const Cost one[4] = {{7.36, 0.465, 0.112, 1.75, 0.164}, {8.72, 0.479, 0.206, 1.35, 0.140}, {9.94, 0.558, 0.278, 1.39, 0.119}, {10.87, 0.648, 0.318, 1.23, 0.113}};
     static const Cost halves[4] = {{6.76, 0.460, 0.174, 1.81, 0.214}, {7.20, 0.494, 0.266, 2.28, 0.188}, {8.69, 0.576, 0.346, 1.58, 0.187}, {9.20, 0.660, 0.387, 1.53, 0.185}};
     static const Cost two[2] = {{8.92, 0.545, 0.350, 3.09, 0.080}, {10.60, 0.734, 0.409, 1.19, 0.094}}, wide = {8.65, 0.951, 0.372, 0, 0};
+    static const Cost three[2] = {{7.72, 0.729, 0.411, 0, 0}, {8.51, 0.876, 0.453, 0, 0}};
     const long groups = l.tiles * l.parts;
-    if (groups > 2L * cus || (groups > cus && (l.nt == 4 || l.kh == 2 || l.rt > 4))) return 0;
-    const Cost &c = l.nt == 4 ? wide : l.kh == 2 ? halves[l.rt - 3] : groups > cus ? two[l.rt - 3] : one[l.rt - 3];
+    if (groups > 2L * cus || (groups > cus && (l.nt != 2 || l.kh == 2 || l.rt > 4))) return 0;
+    const Cost &c = l.nt == 4 ? wide : l.nt == 3 ? three[l.rt - 4] : l.kh == 2 ? halves[l.rt - 3] : groups > cus ? two[l.rt - 3] : one[l.rt - 3];
     const int stages = (K / (BK * l.kh) + l.parts - 1) / l.parts;
-    return c.a + stages * (c.b + c.l * (double)groups / cus) + (l.parts > 1 ? c.h + c.p * l.parts * ((double)M * N * 8e-6) : 0.0);
+    const double t = c.a + stages * (c.b + c.l * (double)groups / cus) + (l.parts > 1 ? c.h + c.p * l.parts * ((double)M * N * 8e-6) : 0.0);
+    // (activations that two L2s would not hold, read by twice as many columns of tiles: measured 10 to 18 % longer, 5 % with
+    // whole-K waves)
+    return l.kh == 2 && l.parts > 1 && 2.0 * M * K > 8e6 ? 1.12 * t : t;
 }
 
-// Of a plan that is one launch of at most one workgroup per compute unit: a quicker one, if there is one by 3 % by the
+// Of a plan that is one launch of at most one workgroup per compute unit, or one full round of the chip and few tiles left
+// over: a quicker one, if there is one by 3 % by the
 // estimate, whose parts fit the room that the plan's have.  Tiles of half the columns whose waves halve K need half
 // the K parts (or none) for as many workgroups, at the price of twice the activations per compute unit; tiles of 96 and
 // 128 rows x 256 columns leave half of the registers, so that two workgroups per compute unit hide each other's
-// waits.  The sizes reported to callers are those of the plan itself: what they have stored goes on to hold.
+// waits; 128 or 160 rows x 384 columns fill one round where 128 x 512 leave a third of the chip idle or spill over.  The sizes reported to callers are those of the plan itself: what they have stored goes on to hold.
 // us, plan -> quicker one when it was built: 160x8192x8192 36.3 -> 34.4, 160x4096x22016 44.5 -> 39.8, 300x5120x15360 59.6 ->
-// 55.5, 490x2816x5840 32.5 -> 25.9, 999x2176x3832 32.8 -> 24.3, 403x3072x22792 72.2 -> 68.7; over the fitted shapes the pick is 0.5 %
+// 55.5, 490x2816x5840 32.5 -> 25.9, 999x2176x3832 32.8 -> 24.3, 403x3072x22792 72.2 -> 68.7, 512x4096x22016 88.0 -> 82.5, 772x3456x18968 111 -> 93; over the fitted shapes the pick is 0.5 %
 // behind the best in the mean.
 static double quicker_launch(LaunchPlan &q, int M, int N, int K, int group, int cus, size_t room)
 {
     const bool hooked = g_tile_mode != 0 || g_tile_shape != 0 || g_ksplit >= 0 || g_force_rt > 0;
-    if (hooked || group == 32 || q.count != 1 || q.wm != 1) return 0;
-    double best = launch_us(q.l[0], M, N, K, cus), least = best * 0.97;
+    if (hooked || group == 32 || q.wm != 1) return 0;
+    double best = launch_us(q.l[0], M, N, K, cus);
     if (best == 0) return 0;
+    if (q.count == 2) {
+        TileLaunch rest = q.l[1];
+        rest.halves = false;
+        best += launch_us(rest, 128, (int)(rest.tiles * 256), K, cus);
+    }
+    double least = best * 0.97;
     const int stages = K / BK;
     for (int rt = 3; rt <= 6; rt++)
         for (int kh = 1; kh <= (K % (2 * BK) == 0 ? 2 : 1); kh++) {
@@ -868,10 +925,21 @@ static double quicker_launch(LaunchPlan &q, int M, int N, int K, int group, int 
                 const double t = launch_us(l, M, N, K, cus);
                 if (t < least) {
                     least = best = t;
+                    q.count = 1;
                     q.l[0] = l;
                 }
             }
         }
+    const int tn = (N + 383) / 384;
+    for (int rt = 4; rt <= 5; rt++) {
+        const TileLaunch l = {rt, 3, 0, (long)tn * ((M + 32 * rt - 1) / (32 * rt)), tn, 1, false, 1};
+        const double t = l.tiles <= cus ? launch_us(l, M, N, K, cus) : 0;
+        if (t > 0 && t < least) {
+            least = best = t;
+            q.count = 1;
+            q.l[0] = l;
+        }
+    }
     return best;
 }
 
@@ -902,7 +970,7 @@ static bool row_blocks_cover(int K, int group) { return K % 128 == 0 && (group =
 // and the fp32 parts through memory; the strip kernel's workgroups are small, walk K with two waves per SIMD
 // and hand partial tiles over in the same launch.  It reads the weights once per row block (the second and
 // later ones from L2 or the last-level cache) and unpacks them again, so it loses once the chip is full:
-// taken where its estimated time is 3 % below that of the tiles (launch_us; 8 % below plan_launches' coarser estimate and
+// taken where its estimated time is below that of the tiles (launch_us; 8 % below plan_launches' coarser estimate and
 // the 6.7 us that it leaves out).
 // The estimate: A + iterations * (B + L * workgroups / compute units) + (H + S * parts), the last two terms with
 // more than one K part (B and L 6 % below the fit since the kernel's iterations are that much shorter: 91 other calls); at
@@ -968,7 +1036,7 @@ static SqpStripPlan row_blocks_for(const LaunchPlan &q, int M, int N, int K, int
     const bool hooked = g_tile_mode != 0 || g_tile_shape != 0 || g_ksplit >= 0 || g_force_rt > 0;
     if (g_row_blocks.mt > 0 && row_blocks_cover(K, group)) return g_row_blocks;
     if (hooked || g_row_blocks.mt < 0) return SqpStripPlan{2, 1, 2, 1, 0};
-    return row_blocks_plan(M, N, K, group, cus, us > 0 ? us / 1.03 : (launches_us(q, K, group, cus) + 6.7) / 1.08, limit);
+    return row_blocks_plan(M, N, K, group, cus, us > 0 ? us : (launches_us(q, K, group, cus) + 6.7) / 1.08, limit);
 }
 
 static size_t row_blocks_bytes(const SqpStripPlan &p, int M, int N, int K)
@@ -1048,7 +1116,7 @@ size_t sqp_gemm_prefill_least_bytes(int M, int N, int K, int group)
 // (291x5952x1072 18.9 us, 20.4 with groups of four).
 static TileMap tile_map(const TileLaunch &l, int wm, int M)
 {
-    const int bm = 32 * l.rt * wm, most = l.halves || l.nt == 4 ? 8 / wm : l.parts > 1 ? 1 : 4;
+    const int bm = 32 * l.rt * wm, most = l.halves || l.nt >= 3 ? 8 / wm : l.parts > 1 ? 1 : 4;
     const int tm = (M + bm - 1) / bm, groups = (tm + most - 1) / most;
     return TileMap{(int)l.tile0, l.tn, tm, (tm + groups - 1) / groups, l.halves};
 }
@@ -1093,6 +1161,9 @@ int sqp_gemm_prefill(int M, int N, int K, int group, const h16 *x, const uint32_
             else SQP_TILES(4, 2, 2, false);
         } else if (l.nt == 4) {
             SQP_TILES(4, 4, 1, false);
+        } else if (l.nt == 3) {
+            if (l.rt == 5) SQP_TILES(5, 3, 1, false);
+            else SQP_TILES(4, 3, 1, false);
         } else if (l.kh == 2) {
             switch (l.rt) {
                 case 3: SQP_TILES_KH(3); break;

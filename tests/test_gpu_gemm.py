@@ -247,6 +247,32 @@ def test_prefill_few_stages(orc, sqp, rt, nt, stages):
         L.sqp_debug_set_prefill_variant(0, 0, 0)
 
 
+@pytest.mark.parametrize("rt", [4, 5])
+@pytest.mark.parametrize("M_off,K,N,group", [(0, 64, 8, 64), (-1, 448, 384, 64), (1, 320, 392, 320), (70, 1024, 760, 256), (-40, 640, 96, 128)])
+def test_prefill_three_columns_per_lane(orc, sqp, M_off, K, N, group, rt):
+    """Tiles of 384 columns: rows and columns at the edges of a tile, of a wave's 96 columns and of a lane's three (the
+    last columns of a row end in the middle of a lane's), plain and with the fused activation."""
+    M = 32 * rt + M_off
+    print("case three columns", M, K, N, group, rt, flush=True)
+    xs, p, sc, z = _layer(orc, M, K, N, group)
+    L = sqp.lib()
+    L.sqp_debug_set_prefill_variant(rt, 3, 1)
+    try:
+        y0 = _check(orc, sqp, xs, p, sc, z, group)
+        h = host(sqp.w4a16_gemm_silu_mul(dev(xs), dev(p), dev(sc), dev(z), group)) if N % 16 == 0 else None
+    finally:
+        L.sqp_debug_set_prefill_variant(0, 0, 0)
+    L.sqp_debug_set_prefill_variant(4, 4, 1)
+    try:  # the same products in the same order
+        y1 = host(sqp.w4a16_gemm(dev(xs), dev(p), dev(sc), dev(z), group))
+        h1 = host(sqp.w4a16_gemm_silu_mul(dev(xs), dev(p), dev(sc), dev(z), group)) if N % 16 == 0 else None
+    finally:
+        L.sqp_debug_set_prefill_variant(0, 0, 0)
+    assert np.array_equal(y0.view(np.uint16), y1.view(np.uint16))
+    if h is not None:
+        assert np.array_equal(h.view(np.uint16), h1.view(np.uint16))
+
+
 @pytest.mark.parametrize("rt", [3, 4, 5, 6])
 @pytest.mark.parametrize("M_off,K,N,group,parts", [
     (0, 128, 8, 64, 1), (-1, 256, 136, 128, 1), (1, 384, 120, 192, 1), (33, 640, 264, 64, 1), (-17, 1024, 392, 512, 4), (5, 1920, 248, 320, 3),

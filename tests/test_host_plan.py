@@ -270,12 +270,14 @@ def test_prefill_choice_stays_in_its_room(L):
             rt, nt, tiles, parts, kh = out[5 * i:5 * i + 5]
             seen.add((rt, nt, kh, tiles * parts > 256))
             assert kh == 1 or (kh == 2 and nt == 2 and K % 128 == 0 and group % 64 == 0)
+            assert nt != 3 or (rt in (4, 5) and n == 1 and tiles <= 256 and group != 32)
             assert parts == 1 or (nt == 2 and K // 64 >= 8 * parts and parts * tiles * 32 * rt * (256 // kh) * 4 <= room)
             if n == 1:
                 assert tiles >= -(-N // (128 * nt // kh)) * -(-M // (32 * rt))
             if parts > 1 or kh == 2:
                 assert tiles * parts <= (512 if nt == 2 and kh == 1 and rt <= 4 else 256)
-    assert {(rt, 2, kh, False) for rt in (3, 4, 5, 6) for kh in (1, 2)} <= seen and (3, 2, 1, True) in seen
+    assert {(rt, 2, kh, False) for rt in (3, 4, 5, 6) for kh in (1, 2)} <= seen
+    assert {(3, 2, 1, True), (4, 3, 1, False), (5, 3, 1, False)} <= seen
 
 
 def test_plans_fit_the_static_array(L):
