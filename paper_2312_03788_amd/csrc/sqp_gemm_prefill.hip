@@ -189,11 +189,6 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
     // lanes' offsets); past the last stage the offsets stop, so that the look-ahead of the branch-free stages re-reads
     // the last one (cache hits).  Every scalar instruction costs the wave as much as a vector one: 30 per stage, where
     // 64-bit pointers with a clamp each took 56.
-    typedef int rsrc_t __attribute__((ext_vector_type(4)));
-    auto buffer_of = [&](const void *p, uint32_t bytes) {
-        const uint64_t at = reinterpret_cast<uint64_t>(p);
-        return rsrc_t{(int)(uint32_t)at, (int)(uint32_t)(at >> 32), (int)bytes, 0x00020000};
-    };
     const rsrc_t w_buf = buffer_of(packed, (uint32_t)(K / 8) * (uint32_t)N * 4u);
     const rsrc_t s_buf = buffer_of(scales, (uint32_t)(K / group) * (uint32_t)N * 2u), z_buf = buffer_of(zeros, (uint32_t)(K / group) * (uint32_t)N);
     const uint32_t wstage = (uint32_t)N * 32u;    // eight packed rows (64 k) in bytes

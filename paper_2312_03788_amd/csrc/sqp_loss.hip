@@ -45,12 +45,35 @@ constexpr int LBM = 128, LBN = 128, LBK = 64, LPAD = 8;  // row stride 144 bytes
 // the reads from LDS).  Measured against quant_loss_kernel: 512 x 5120 x 5120 (160 tiles) 153 -> 88 us,
 // 512 x 8192 x 8192 292 -> 173, 64 x 4096 x 4096 in groups of 64 171 -> 68; rounding as there, 0.5 to 1.3
 // times 2^-24 sqrt(K / 16) of a sum of 16 products.
+
+// dequant_word_scaled with the and-ors as assembly, which the scheduler does not count among the vector instructions it
+// deals out between the MFMAs but puts in front of them.  Here that is the faster place: quant_loss of 512 x 5120 x 5120
+// takes 88 us with it and 94 with plain and-ors (128 x 4096 x 4096: 68 and 72), though those have 5 % fewer instructions
+// (no wait states behind assembly); the strips and column slices, whose words wait for memory, are faster the other way.
+struct LossConsts {
+    uint32_t mask_lo = 0x000f000fu, mask_hi = 0x00f000f0u, magic_lo = 0x64006400u, magic_hi = 0x54005400u;
+};
+__device__ __forceinline__ h16x8 dequant_word_ahead(uint32_t w, h16x2 neg_hi, h16x2 neg_lo, h16x2 delta, const LossConsts &uc)
+{
+    const uint32_t w8 = w >> 8;
+    uint32_t t0, t1, t2, t3;
+    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(t0) : "v"(w), "v"(uc.mask_lo), "v"(uc.magic_lo));
+    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(t1) : "v"(w), "v"(uc.mask_hi), "v"(uc.magic_hi));
+    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(t2) : "v"(w8), "v"(uc.mask_lo), "v"(uc.magic_lo));
+    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(t3) : "v"(w8), "v"(uc.mask_hi), "v"(uc.magic_hi));
+    u32x4 r;
+    r[0] = __builtin_bit_cast(uint32_t, (__builtin_bit_cast(h16x2, t0) + neg_hi) * delta);
+    r[1] = __builtin_bit_cast(uint32_t, (__builtin_bit_cast(h16x2, t1) + neg_lo) * delta);
+    r[2] = __builtin_bit_cast(uint32_t, (__builtin_bit_cast(h16x2, t2) + neg_hi) * delta);
+    r[3] = __builtin_bit_cast(uint32_t, (__builtin_bit_cast(h16x2, t3) + neg_lo) * delta);
+    return __builtin_bit_cast(h16x8, r);
+}
+
 constexpr int SBK = 64;                       // k per stage
 constexpr int SHALF = LBM * SBK * 2;          // bytes of X (and of X_hat) per stage
 constexpr int SSLOT = 2 * SHALF;
 constexpr int SROW = (SBK + LPAD) * 2;        // bytes per LDS row of W
 constexpr int SWBUF = LBN * SROW;
-
 
 // ---------------------------------------------------------------- preparation of a search's alphas
 
@@ -136,7 +159,7 @@ loss_tile_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, cons
     const int stages = K / SBK;
     const int ncol = n0 + wn * 64 + 2 * l32;                   // this lane's two columns (N is even: both in or out)
     const bool ncol_ok = ncol < N;
-    const UnpackConsts uc = unpack_consts();
+    const LossConsts uc;
 
     f32x16 acc[2][2];
 #pragma unroll
@@ -320,7 +343,7 @@ loss_tile_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, cons
             // X_hat W_hat of the same 16 k
             h16x8 b[2], a[2];
 #pragma unroll
-            for (int t = 0; t < 2; t++) b[t] = dequant_word_scaled(cur.w[ks][t], neg_hi[t], neg_lo[t], delta[t], uc);
+            for (int t = 0; t < 2; t++) b[t] = dequant_word_ahead(cur.w[ks][t], neg_hi[t], neg_lo[t], delta[t], uc);
 #pragma unroll
             for (int mt = 0; mt < 2; mt++) a[mt] = CODE ? __builtin_bit_cast(h16x8, xb[ks][mt]) : permute_x(xb[ks][mt]);
 #pragma unroll
@@ -506,7 +529,7 @@ loss_pair_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, cons
     const int stages = K / SBK;
     const int ncol = n0 + wn * 64 + 2 * l32;                   // this lane's two columns (N is even: both in or out)
     const bool ncol_ok = ncol < N;
-    const UnpackConsts uc = unpack_consts();
+    const LossConsts uc;
 
     f32x16 acc[2][2][2];                       // [alpha][row tile][column]
 #pragma unroll
@@ -523,14 +546,23 @@ loss_pair_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, cons
     const uint32_t voff_p = (uint32_t)(kb * N + col) * 4u, voff_s = (uint32_t)col * 2u, voff_z = (uint32_t)col;
     const uint32_t voff_w = n0 + 2 * lane < N ? (uint32_t)(n0 + 2 * lane) * 2u : 0u;  // W: this lane's column pair
     const long nrow = (long)N * 2;            // one row of W in bytes
-    const unsigned char *pa = reinterpret_cast<const unsigned char *>(sets.packed<false>(sa)) + (long)kh * 8 * nrow;  // 32 k: four packed rows
-    const long pdiff = (const unsigned char *)sets.packed<false>(sb) - (const unsigned char *)sets.packed<false>(sa);        // the partner's operands, all of them
-    const unsigned char *xq = reinterpret_cast<const unsigned char *>(x), *ha = reinterpret_cast<const unsigned char *>(sets.x_hat<false>(sa));
-    const unsigned char *sca = reinterpret_cast<const unsigned char *>(sets.scales<false>(sa)), *zra = sets.zeros<false>(sa);
-    const unsigned char *wq = reinterpret_cast<const unsigned char *>(w) + (long)wave * 8 * nrow;     // this wave's 8 rows of a stage
+    // Streams are buffer loads with a 32-bit scalar offset each: scalar instructions cost a wave as much as vector ones, and
+    // 64-bit pointers made 171 per two stages, these 107 (search of 64 x 4096 x 4096 in groups of 32, 21 alphas: 424 -> 409 us;
+    // 512 x 5120 x 5120: 1529 -> 1522).  Past the last stage the offsets stop and the look-ahead re-reads it.
+    // (W straight to registers, each row fetched by twice the waves, and a third slot in its room: 1578 -> 1631 us.)
+    const uint32_t bytes_x = (uint32_t)M * (uint32_t)K * 2u, bytes_p = (uint32_t)(K / 8) * (uint32_t)N * 4u, rows_q = (uint32_t)(K / group) * (uint32_t)N;
+    const rsrc_t buf_w = buffer_of(w, (uint32_t)K * (uint32_t)N * 2u), buf_p[2] = {buffer_of(sets.packed<false>(sa), bytes_p), buffer_of(sets.packed<false>(sb), bytes_p)};
+    const rsrc_t buf_s[2] = {buffer_of(sets.scales<false>(sa), rows_q * 2u), buffer_of(sets.scales<false>(sb), rows_q * 2u)};
+    const rsrc_t buf_z[2] = {buffer_of(sets.zeros<false>(sa), rows_q), buffer_of(sets.zeros<false>(sb), rows_q)};
+    const h16 *const hat[2] = {sets.x_hat<false>(sa), sets.x_hat<false>(sb)};
+    uint32_t p_at = (uint32_t)kh * 8u * (uint32_t)nrow, x_at = 0;  // 32 k: four packed rows
+    const uint32_t p_most = p_at + (uint32_t)(stages - 1) * 16u * (uint32_t)nrow, x_most = (uint32_t)(stages - 1) * (SBK * 2);
+    uint32_t w_at = (uint32_t)wave * 8u * (uint32_t)nrow;             // this wave's 8 rows of a stage
+    const uint32_t w_most = w_at + (uint32_t)(stages - 1) * (uint32_t)SBK * (uint32_t)nrow;
     const int spg = G32 ? 1 : __builtin_amdgcn_readfirstlane(group / SBK);  // stages per group (G32: two groups per stage)
-    int kin = 0, prow = G32 ? kh : 0;          // position of the stage being issued in its group, its parameter row
-    int ist = 0, wst = 0;                      // stage being issued: of X, X_hat and W_hat; of W
+    int kin = 0;                               // position of the stage being issued in its group
+    uint32_t z_at = G32 ? (uint32_t)(kh * N) : 0u;  // zero points of its group; the steps are at twice that
+    const uint32_t z_most = (uint32_t)(__builtin_amdgcn_readfirstlane(G32 ? 2 * (stages - 1) + kh : (stages - 1) / spg) * N);
     uint32_t xoff[2];                          // as in loss_tile_kernel
 #pragma unroll
     for (int j = 0; j < 2; j++) {
@@ -541,65 +573,41 @@ loss_pair_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, cons
     constexpr int OX = 7, OW = 8;              // loads per wave and stage: two parts of OX (X, X_hat twice; words, steps, zero points), W
     auto issue_x_part = [&](Stage (&st)[2], int slot, int j) {
         if (j == 0) {
-            auto direct = [&](const unsigned char *src, int at) {
+            auto direct = [&](const h16 *src, int at) {
 #pragma unroll
-                for (int i = 0; i < 2; i++)
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + xoff[i]),
-                                                     (__attribute__((address_space(3))) void *)(lds + slot * SLOT + wave * 1024 + i * 8192 + at), 16, 0, 0);
+                for (int i = 0; i < 2; i++) copy16_to_lds(src, bytes_x, xoff[i], x_at, lds + slot * SLOT + wave * 1024 + i * 8192 + at);
             };
-            direct(xq, 0);
-            direct(ha, SHALF);
-            direct(ha + pdiff, 2 * SHALF);
+            direct(x, 0);
+            direct(hat[0], SHALF);
+            direct(hat[1], 2 * SHALF);
             return;
         }
-        {
-            const unsigned char *p1 = pa + 4 * nrow, *q0 = pa + pdiff, *q1 = p1 + pdiff;
-            asm volatile("global_load_dwordx2 %[a0], %[vp], %[p0]\n\t"
-                         "global_load_dwordx2 %[a1], %[vp], %[p1]\n\t"
-                         "global_load_dwordx2 %[b0], %[vp], %[q0]\n\t"
-                         "global_load_dwordx2 %[b1], %[vp], %[q1]"
-                         : [a0] "=&v"(st[0].w[0]), [a1] "=&v"(st[0].w[1]), [b0] "=&v"(st[1].w[0]), [b1] "=&v"(st[1].w[1])
-                         : [vp] "v"(voff_p), [p0] "s"(pa), [p1] "s"(p1), [q0] "s"(q0), [q1] "s"(q1)
-                         : "memory");
+        const uint32_t p1 = p_at + 4u * (uint32_t)nrow, s_at = z_at * 2u;
+#pragma unroll
+        for (int a = 0; a < 2; a++) {
+            asm volatile("buffer_load_dwordx2 %0, %1, %2, %3 offen" : "=v"(st[a].w[0]) : "v"(voff_p), "s"(buf_p[a]), "s"(p_at) : "memory");
+            asm volatile("buffer_load_dwordx2 %0, %1, %2, %3 offen" : "=v"(st[a].w[1]) : "v"(voff_p), "s"(buf_p[a]), "s"(p1) : "memory");
         }
-        const long row = (long)__builtin_amdgcn_readfirstlane(prow) * N;
-        const unsigned char *s0 = sca + row * 2, *z0 = zra + row, *s1 = s0 + pdiff, *z1 = z0 + pdiff;
-        asm volatile("global_load_dword %[a], %[vs], %[s0]\n\t"
-                     "global_load_ushort %[b], %[vz], %[z0]\n\t"
-                     "global_load_dword %[c], %[vs], %[s1]\n\t"
-                     "global_load_ushort %[d], %[vz], %[z1]"
-                     : [a] "=&v"(st[0].sc), [b] "=&v"(st[0].zr), [c] "=&v"(st[1].sc), [d] "=&v"(st[1].zr)
-                     : [vs] "v"(voff_s), [vz] "v"(voff_z), [s0] "s"(s0), [z0] "s"(z0), [s1] "s"(s1), [z1] "s"(z1)
-                     : "memory");
-        const bool more = ist + 1 < stages;    // past the last stage the pointers stop and the look-ahead re-reads it
-        ist += more ? 1 : 0;
-        pa += more ? 16 * nrow : 0;
-        xq += more ? SBK * 2 : 0;
-        ha += more ? SBK * 2 : 0;
+#pragma unroll
+        for (int a = 0; a < 2; a++) {
+            asm volatile("buffer_load_dword %0, %1, %2, %3 offen" : "=v"(st[a].sc) : "v"(voff_s), "s"(buf_s[a]), "s"(s_at) : "memory");
+            asm volatile("buffer_load_ushort %0, %1, %2, %3 offen" : "=v"(st[a].zr) : "v"(voff_z), "s"(buf_z[a]), "s"(z_at) : "memory");
+        }
+        p_at = min(p_at + 16u * (uint32_t)nrow, p_most);
+        x_at = min(x_at + SBK * 2, x_most);
         if constexpr (G32) {
-            prow += more ? 2 : 0;
+            z_at = min(z_at + 2u * (uint32_t)N, z_most);
         } else {
-            kin += more ? 1 : 0;
-            const bool wrap = kin == spg;
+            const bool wrap = ++kin == spg;
             kin = wrap ? 0 : kin;
-            prow += wrap ? 1 : 0;
+            z_at = min(z_at + (wrap ? (uint32_t)N : 0u), z_most);
         }
     };
     auto issue_w_part = [&](uint32_t (&r)[8], int h) {
-        const unsigned char *b[4];
 #pragma unroll
-        for (int i = 0; i < 4; i++) b[i] = wq + (4 * h + i) * nrow;  // wave-uniform
-        asm volatile("global_load_dword %[r0], %[v], %[b0]\n\t"
-                     "global_load_dword %[r1], %[v], %[b1]\n\t"
-                     "global_load_dword %[r2], %[v], %[b2]\n\t"
-                     "global_load_dword %[r3], %[v], %[b3]"
-                     : [r0] "=&v"(r[4 * h]), [r1] "=&v"(r[4 * h + 1]), [r2] "=&v"(r[4 * h + 2]), [r3] "=&v"(r[4 * h + 3])
-                     : [v] "v"(voff_w), [b0] "s"(b[0]), [b1] "s"(b[1]), [b2] "s"(b[2]), [b3] "s"(b[3])
-                     : "memory");
-        if (h == 0) return;
-        const bool more = wst + 1 < stages;
-        wst += more ? 1 : 0;
-        wq += more ? (long)SBK * nrow : 0;
+        for (int i = 4 * h; i < 4 * h + 4; i++)
+            asm volatile("buffer_load_dword %0, %1, %2, %3 offen" : "=v"(r[i]) : "v"(voff_w), "s"(buf_w), "s"(w_at + i * (uint32_t)nrow) : "memory");
+        if (h == 1) w_at = min(w_at + (uint32_t)SBK * (uint32_t)nrow, w_most);
     };
     auto tie_w = [&](uint32_t (&r)[8]) {       // no use ahead of the wait in front
 #pragma unroll
@@ -692,7 +700,7 @@ loss_pair_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, cons
             // X W of 16 k for both alphas, the words of the first unpacked between the MFMAs (the scheduler is told so)
             h16x8 b[2];
 #pragma unroll
-            for (int t = 0; t < 2; t++) b[t] = dequant_word_scaled(cur[0].w[ks][t], neg_hi[0][t], neg_lo[0][t], delta[0][t], uc);
+            for (int t = 0; t < 2; t++) b[t] = dequant_word_ahead(cur[0].w[ks][t], neg_hi[0][t], neg_lo[0][t], delta[0][t], uc);
 #pragma unroll
             for (int a = 0; a < 2; a++)
 #pragma unroll
@@ -720,7 +728,7 @@ loss_pair_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, cons
             // X_hat W_hat of the same 16 k, the words of the second alpha unpacked between the MFMAs of the first
             h16x8 c[2];
 #pragma unroll
-            for (int t = 0; t < 2; t++) c[t] = dequant_word_scaled(cur[1].w[ks][t], neg_hi[1][t], neg_lo[1][t], delta[1][t], uc);
+            for (int t = 0; t < 2; t++) c[t] = dequant_word_ahead(cur[1].w[ks][t], neg_hi[1][t], neg_lo[1][t], delta[1][t], uc);
 #pragma unroll
             for (int mt = 0; mt < 2; mt++)
 #pragma unroll
@@ -879,7 +887,7 @@ quant_loss_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, con
     const int wm = wave >> 2, wn = wave & 3;                   // wave tile: rows wm*64 .. +64, columns wn*32 .. +32
     const int l32 = lane & 31, kb = lane >> 5;
     const int m0 = blockIdx.y * LBM, n0 = blockIdx.x * LBN;
-    const UnpackConsts uc = unpack_consts();
+    const LossConsts uc;
 
     f32x16 acc[2];
 #pragma unroll
@@ -952,7 +960,7 @@ quant_loss_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, con
         h16x8 bq[4];
 #pragma unroll
         for (int ks = 0; ks < 4; ks++)
-            bq[ks] = dequant_word_scaled(rword[ks], neg_hi_of(rz[ks]), neg_lo_of(rz[ks]),
+            bq[ks] = dequant_word_ahead(rword[ks], neg_hi_of(rz[ks]), neg_lo_of(rz[ks]),
                                          __builtin_bit_cast(h16x2, rd[ks] * 0x00010001u), uc);
         __syncthreads();
         if (k0 + LBK < K) fetch(k0 + LBK);

@@ -5,6 +5,14 @@
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
+// A buffer's descriptor for loads written in assembly.
+typedef int rsrc_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ rsrc_t buffer_of(const void *p, uint32_t bytes)
+{
+    const uint64_t at = reinterpret_cast<uint64_t>(p);
+    return rsrc_t{(int)(uint32_t)at, (int)(uint32_t)(at >> 32), (int)bytes, 0x00020000};
+}
+
 // Direct global -> LDS load of 16 bytes per lane: lane i's from base + lane_offset + offset to dst + 16 i (dst and offset
 // wave-uniform).  A buffer load: neither a 64-bit address per lane nor one per call; bytes: size of the buffer.
 __device__ __forceinline__ void copy16_to_lds(const void *base, uint32_t bytes, uint32_t lane_offset, uint32_t offset, void *dst)
