@@ -22,8 +22,8 @@
 //     its loads, barrier) sits inside the last k-step, so the pipeline never drains.
 //   - Loads, waits and the per-stage barrier are explicit (assembly), as in the decode
 //     kernel: two stages stay in flight while one is consumed, issued between its MFMAs.
-// What bounds it: the matrix cores, at their own rate below a full chip (31 of 32 cycles per MFMA on 1024x8192x8192, 128
-// tiles; without the unpack 13 % less time), under the power limit on a full one.  us per call (M x K x N): tiles numbered
+// What bounds it: the matrix cores; below a full chip with the unpack's issue slots on top (1024 x 8192 x 8192, 128 tiles: 115
+// us, 100 without the unpack, which is about what the MFMAs alone take), on a full one under the power limit.  us per call (M x K x N): tiles numbered
 // along a row of the output over all XCDs -> one compact run of tiles per XCD -> with the unpack in the order of k, no
 // padded stages (the loop of three used to round a K part of 16 up to 18) and an epilogue that reads one row tile at a
 // time (it used to spill, and every reload waited for the stores under way) -> with half the scalar instructions
