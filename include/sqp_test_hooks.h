@@ -54,8 +54,8 @@ void sqp_debug_prefill_plan(int M, int N, int K, int cus, long *full, long *half
 void sqp_debug_set_row_blocks(int mt, int split, int kp);  /* more than 64 rows (K % 128 == 0, groups of 32, 64
                                                       and multiples of 128): the strip kernel in row blocks of
                                                       16 mt rows (3, 4), K parts, chunks per iteration; 0 = automatic, -1 = never */
-/* What a call takes of these: rows / 16 (0: the tiled kernel), K parts, chunks per iteration; with a workspace of
- * the reported size or without.  Host arithmetic only. */
+/* What a call takes of these: rows / 16 (0: the tiled kernel), K parts, chunks per iteration; without a
+ * workspace (0), with one of the reported size (1) or as large as it likes (2).  Host arithmetic only. */
 void sqp_debug_row_blocks(int M, int N, int K, int group, int cus, int workspace, int *out3);
 
 /* How an alpha search runs: sets of prepared operands that fit a region of `bytes` (-1: not even its factors and sums
@@ -69,7 +69,7 @@ void sqp_debug_search_plan(int T, int N, int K, int group, int n_alpha, size_t b
 int sqp_debug_prefill_launches(int M, int N, int K, int group, int cus, int *out8);
 
 /* What a call launches in their place with `room` bytes for its K parts (workspace or its own scratch, whichever the
- * shape uses): as above, with (rt, nt, tiles, K parts, 2 where the waves halve K) in out10. */
+ * shape uses): as above, with (rt, nt, tiles, K parts, 2 where the waves halve K) in out10; 0: refused. */
 int sqp_debug_prefill_choice(int M, int N, int K, int group, int cus, size_t room, int *out10);
 
 /* Calibration kernels for the benchmark: a plain device copy of `bytes` (a multiple of 16)

@@ -1012,18 +1012,6 @@ static SqpStripPlan row_blocks_plan(int M, int N, int K, int group, int cus, dou
     return best;
 }
 
-// Test hook: the launches of a call with `room` bytes for K parts (no GPU needed): up to two of (rt, nt, tiles, parts, kh).
-extern "C" int sqp_debug_prefill_choice(int M, int N, int K, int group, int cus, size_t room, int *out10)
-{
-    LaunchPlan q = plan_launches(M, N, K, group, cus, room, room);
-    quicker_launch(q, M, N, K, group, cus, room);
-    for (int i = 0; i < q.count; i++) {
-        const int v[5] = {q.l[i].rt, q.l[i].nt, (int)q.l[i].tiles, q.l[i].parts, q.l[i].kh};
-        for (int j = 0; j < 5; j++) out10[5 * i + j] = v[j];
-    }
-    return q.count;
-}
-
 // What a call takes beside the tiled launches q: none where those are forced by a test hook.  us: their estimated
 // time, 0 where launch_us has none.
 static SqpStripPlan row_blocks_for(const LaunchPlan &q, int M, int N, int K, int group, int cus, size_t limit, double us)
@@ -1041,39 +1029,27 @@ static size_t row_blocks_bytes(const SqpStripPlan &p, int M, int N, int K)
     return bytes;
 }
 
-// Test hook: the row blocks of a call (rows / 16, K parts, chunks per iteration; rows 0: none), with a workspace of
-// the reported size or without.  Host arithmetic only.
-extern "C" void sqp_debug_row_blocks(int M, int N, int K, int group, int cus, int workspace, int *out3)
-{
-    const bool covered = tiled_covers(K, group);
-    SqpStripPlan p = {2, 0, 2, 0, 0};
-    if (covered) {
-        LaunchPlan q = plan_launches(M, N, K, group, cus, workspace ? SIZE_MAX : 0, 0);
-        const size_t limit = workspace && plan_partial_bytes(q) > 0 ? SIZE_MAX : 0;
-        const double us = quicker_launch(q, M, N, K, group, cus, workspace && !q.own ? SIZE_MAX : 0);
-        p = row_blocks_for(q, M, N, K, group, cus, limit, us);
-    }
-    out3[0] = p.mt;
-    out3[1] = p.split;
-    out3[2] = p.kp;
-}
-
 // The launches with as large a workspace as they like.  The bytes they leave there are 0 for shapes that report
 // none and never touch it.
-static LaunchPlan preferred_launches(int M, int N, int K, int group)
+static LaunchPlan preferred_launches(int M, int N, int K, int group, int cus)
 {
-    return plan_launches(M, N, K, group, sqp_compute_units(), SIZE_MAX, 0);
+    return plan_launches(M, N, K, group, cus, SIZE_MAX, 0);
+}
+
+static size_t partial_bytes(int M, int N, int K, int group, int cus)
+{
+    const LaunchPlan q = preferred_launches(M, N, K, group, cus);
+    const size_t tiles = plan_partial_bytes(q);
+    if (tiles == 0 && g_row_blocks.mt <= 0) return 0;  // (a forced plan says what it needs)
+    // (row blocks as the launches above would leave them, not as a quicker launch would)
+    const size_t rows = row_blocks_bytes(row_blocks_for(q, M, N, K, group, cus, SIZE_MAX, 0), M, N, K);
+    return rows > tiles ? rows : tiles;
 }
 
 size_t sqp_gemm_prefill_partial_bytes(int M, int N, int K, int group)
 {
     if (!tiled_covers(K, group)) return most_of_row_blocks(sqp_gemm_decode_partial_bytes, M, N, K, group);
-    const LaunchPlan q = preferred_launches(M, N, K, group);
-    const size_t tiles = plan_partial_bytes(q);
-    if (tiles == 0 && g_row_blocks.mt <= 0) return 0;  // (a forced plan says what it needs)
-    // (row blocks as the launches above would leave them: what a quicker launch leaves is less)
-    const size_t rows = row_blocks_bytes(row_blocks_for(q, M, N, K, group, sqp_compute_units(), SIZE_MAX, 0), M, N, K);
-    return rows > tiles ? rows : tiles;
+    return partial_bytes(M, N, K, group, sqp_compute_units());
 }
 
 // Scratch that a call may ask for its own K parts (the static array's size).
@@ -1091,10 +1067,10 @@ size_t sqp_gemm_prefill_scratch_bytes(int M, int N, int K, int group)
 // What a workspace has to hold at least for a call not to be refused: the K parts of the plan in 128-row
 // tiles as [parts][M][N].  With less than the preferred plan's bytes, one that fits runs, of row blocks too.
 // tiles: bytes of the preferred launches.
-static size_t least_bytes(size_t tiles, int M, int N, int K, int group)
+static size_t least_bytes(size_t tiles, int M, int N, int K, int group, int cus)
 {
     if (g_force_rt > 0 || tiles == 0) return tiles;
-    const TilePlan p = plan_tiles(M, N, K, group, sqp_compute_units(), true);
+    const TilePlan p = plan_tiles(M, N, K, group, cus, true);
     const size_t base = p.ksplit >= 2 ? (size_t)p.ksplit * M * N * sizeof(float) : 0;
     return base < tiles ? base : tiles;
 }
@@ -1102,7 +1078,69 @@ static size_t least_bytes(size_t tiles, int M, int N, int K, int group)
 size_t sqp_gemm_prefill_least_bytes(int M, int N, int K, int group)
 {
     if (!tiled_covers(K, group)) return most_of_row_blocks(sqp_gemm_decode_least_bytes, M, N, K, group);
-    return least_bytes(plan_partial_bytes(preferred_launches(M, N, K, group)), M, N, K, group);
+    const int cus = sqp_compute_units();
+    return least_bytes(plan_partial_bytes(preferred_launches(M, N, K, group, cus)), M, N, K, group, cus);
+}
+
+// What a call runs with these bytes for K parts in its workspace and in its own scratch: row blocks (rows.mt > 0) or
+// tiled launches.
+struct CallPlan {
+    LaunchPlan q;
+    SqpStripPlan rows;
+    bool refused;  // a workspace below the least size
+};
+
+static CallPlan plan_call(int M, int N, int K, int group, int cus, size_t room_ws, size_t room_own)
+{
+    // The preferred launches are looked for once: they are what runs wherever their parts fit the workspace, unless
+    // the call brings scratch for a shape that has no parts there.
+    CallPlan c = {preferred_launches(M, N, K, group, cus), {2, 1, 2, 1, 0}, true};
+    const size_t tiles = plan_partial_bytes(c.q);
+    if (room_ws > 0 && room_ws < least_bytes(tiles, M, N, K, group, cus)) return c;
+    if (c.q.own ? room_own > 0 : room_ws < tiles) c.q = plan_launches(M, N, K, group, cus, room_ws, room_own);
+    if (plan_partial_bytes(c.q) > (c.q.own ? room_own : room_ws)) return c;
+    c.refused = false;
+    // What is chosen in their place has the room that the shape reports and no more, however large the buffer is: every
+    // sufficient one gives the same launches and so the same bits (a caller's exact one, the static array, one
+    // that has grown for other shapes), and a shape that reports no workspace leaves nothing there, beside whichever
+    // call is using it.
+    const size_t room = c.q.own ? OWN_MOST : tiles, here = c.q.own ? room_own : room_ws;
+    const double us = quicker_launch(c.q, M, N, K, group, cus, here < room ? here : room);
+    // Parts of row blocks go to the workspace where the shape reports one: the others may run beside calls that
+    // use it.  (They may be larger than the tiles': the size reported is looked for only then.)
+    const size_t limit = tiles > 0 ? room_ws : 0;
+    c.rows = row_blocks_for(c.q, M, N, K, group, cus, limit, us);
+    if (row_blocks_bytes(c.rows, M, N, K) > tiles) {
+        const size_t most = partial_bytes(M, N, K, group, cus);
+        if (limit > most) c.rows = row_blocks_for(c.q, M, N, K, group, cus, most, us);
+    }
+    return c;
+}
+
+// Test hook: the tiled launches of a call with `room` bytes for K parts (no GPU needed): up to two of (rt, nt, tiles, parts,
+// kh); 0: refused.
+extern "C" int sqp_debug_prefill_choice(int M, int N, int K, int group, int cus, size_t room, int *out10)
+{
+    const CallPlan c = plan_call(M, N, K, group, cus, room, room);
+    if (c.refused) return 0;
+    for (int i = 0; i < c.q.count; i++) {
+        const TileLaunch &l = c.q.l[i];
+        const int v[5] = {l.rt, l.nt, (int)l.tiles, l.parts, l.kh};
+        for (int j = 0; j < 5; j++) out10[5 * i + j] = v[j];
+    }
+    return c.q.count;
+}
+
+// Test hook: the row blocks of a call (rows / 16, K parts, chunks per iteration; rows 0: none), without a workspace (0),
+// with one of the reported size (1) or as large as it likes (2).  Host arithmetic only.
+extern "C" void sqp_debug_row_blocks(int M, int N, int K, int group, int cus, int workspace, int *out3)
+{
+    SqpStripPlan p = {2, 0, 2, 0, 0};
+    if (tiled_covers(K, group))
+        p = plan_call(M, N, K, group, cus, workspace == 0 ? 0 : workspace == 1 ? partial_bytes(M, N, K, group, cus) : SIZE_MAX, 0).rows;
+    out3[0] = p.mt;
+    out3[1] = p.split;
+    out3[2] = p.kp;
 }
 
 // Rows per group of the numbering: 8 for full tiles, whose stage takes as many bytes of x per row of tiles as of
@@ -1129,20 +1167,11 @@ int sqp_gemm_prefill(int M, int N, int K, int group, const h16 *x, const uint32_
 {
     if (!tiled_covers(K, group))
         return decode_in_row_blocks(M, N, K, group, x, packed, scales, zeros, y, epi, ws, stream);
-    const size_t room_ws = ws.partial ? ws.partial_bytes : 0, room_own = ws.own ? ws.own_bytes : 0;
-    // The preferred launches are looked for once: they are what runs wherever their parts fit the workspace, unless
-    // the call brings scratch for a shape that has no parts there.
-    LaunchPlan q = preferred_launches(M, N, K, group);
-    const size_t reported = plan_partial_bytes(q);
-    if (room_ws > 0 && room_ws < least_bytes(reported, M, N, K, group)) return SQP_ERR_WORKSPACE;
-    if (q.own ? room_own > 0 : room_ws < reported) q = plan_launches(M, N, K, group, sqp_compute_units(), room_ws, room_own);
+    const CallPlan c = plan_call(M, N, K, group, sqp_compute_units(), ws.partial ? ws.partial_bytes : 0, ws.own ? ws.own_bytes : 0);
+    if (c.refused) return SQP_ERR_WORKSPACE;
+    const SqpStripPlan &rows = c.rows;
+    const LaunchPlan &q = c.q;
     float *const part = q.own ? ws.own : ws.partial;
-    if (plan_partial_bytes(q) > (q.own ? room_own : room_ws)) return SQP_ERR_WORKSPACE;
-    // Parts of row blocks go to the workspace where the shape reports one: the others may run beside calls that
-    // use it.
-    const size_t limit = room_ws > 0 && ws.tickets && reported > 0 ? room_ws : 0;
-    const double us = quicker_launch(q, M, N, K, group, sqp_compute_units(), q.own ? room_own : room_ws);
-    const SqpStripPlan rows = row_blocks_for(q, M, N, K, group, sqp_compute_units(), limit, us);
     if (rows.mt) return sqp_strip_row_blocks(group, rows, M, N, K, group <= 128 ? 1 : group / 128, x, packed, scales, zeros, y, epi, ws, stream);
     for (int i = 0; i < q.count; i++) {
         const TileLaunch &l = q.l[i];

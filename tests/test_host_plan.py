@@ -280,6 +280,41 @@ def test_prefill_choice_stays_in_its_room(L):
     assert {(3, 2, 1, True), (4, 3, 1, False), (5, 3, 1, False)} <= seen
 
 
+def test_every_sufficient_buffer_gives_the_same_launches(L):
+    """A buffer larger than the size reported for a shape (the static array, a workspace that has grown for other shapes)
+    changes nothing: neither the tiled launches nor the row blocks.  Drawn shapes, and some on which an estimate with more
+    room would choose differently."""
+    out, rows = (ctypes.c_int * 10)(), (ctypes.c_int * 3)()
+    L.sqp_debug_prefill_choice.argtypes = [ctypes.c_int] * 5 + [ctypes.c_size_t, ctypes.POINTER(ctypes.c_int)]
+    L.sqp_w4a16_gemm_scratch_bytes.restype = ctypes.c_size_t
+    shapes = [(314, 2456, 16128, 128), (75, 25128, 14848, 128), (569, 6128, 15104, 128), (319, 6992, 10240, 128),
+              (89, 16584, 28928, 256), (71, 25416, 21888, 128), (1434, 1632, 17280, 128), (77, 21872, 9664, 64)]
+    rng = random.Random(23)
+    for _ in range(20000):
+        group = rng.choice([128, 128, 64, 192, 256])
+        shapes.append((int(2 ** rng.uniform(6.05, 11.5)), 8 * int(2 ** rng.uniform(5, 12.5)), group * int(2 ** rng.uniform(0, 7.5)), group))
+    used = 0
+    for (M, N, K, group) in shapes:
+        if max(M * K, K * N, M * N) >= 1 << 31:
+            continue
+        want = L.sqp_w4a16_gemm_workspace_bytes(M, N, K, group)
+        got, blocks = set(), set()
+        # (no scratch is ever reported beside a workspace: the one room is that of whichever the shape uses)
+        need = want - (512 << 10) if want else L.sqp_w4a16_gemm_scratch_bytes(M, N, K, group)
+        for room in (need, max(need, 48 << 20), max(need, 64 << 20), 1 << 40):
+            n = L.sqp_debug_prefill_choice(M, N, K, group, 256, room, out)
+            got.add(tuple(out[:5 * n]))
+        for ws in (1, 2):
+            L.sqp_debug_row_blocks(M, N, K, group, 256, ws, rows)
+            blocks.add(tuple(rows))
+        assert len(got) == 1 and len(blocks) == 1, (M, N, K, group, got, blocks)
+        launches = got.pop()
+        used += want > 0 and any(launches[3::5][i] > 1 for i in range(len(launches) // 5))
+        if need == 0:  # neither buffer: nothing may be left in a shared one
+            assert all(parts == 1 for parts in launches[3::5]), (M, N, K, group, launches)
+    assert used > 4000
+
+
 def test_plans_fit_the_static_array(L):
     """No shape's own plan needs more partial sums than the static array of sqp_w4a16_gemm_static holds, the
     least size of a workspace is at most the preferred one, and a call in blocks of 64 rows reports what

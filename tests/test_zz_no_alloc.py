@@ -110,3 +110,37 @@ def test_static_entry_refuses_oversized_plan(sqp):
     assert L.sqp_w4a16_gemm_static(M, N, K, g, _ptr(dx), _ptr(dp), _ptr(dsc), _ptr(dz), _ptr(y), st) == 0
     torch.cuda.synchronize()
     assert torch.isfinite(y.float()).all() and y.any()
+
+
+@pytest.mark.parametrize("M,K,N,g", [(314, 16128, 2456, 128), (77, 9664, 21872, 64), (319, 10240, 6992, 128)])
+def test_bits_do_not_depend_on_the_size_of_a_sufficient_workspace(sqp, M, K, N, g):
+    """Shapes whose launches an estimate with more room than they report would change: the reported size, one that
+    has grown for other shapes and the static array give the same bits.  Values on sampled rows against 64 bits: fp16
+    weights, fp32 sums and one rounding to fp16 (the parity tests' bound)."""
+    print("case sizes of workspace", M, K, N, g, flush=True)
+    L = sqp.lib()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(11)
+    dp = torch.randint(-2**31, 2**31 - 1, (K // 8, N), dtype=torch.int32, device="cuda", generator=gen)
+    dsc = (torch.rand((K // g, N), device="cuda", generator=gen) * 0.05 + 0.005).half()
+    dz = torch.randint(0, 16, (K // g, N), dtype=torch.uint8, device="cuda", generator=gen)
+    dx = torch.randn((M, K), device="cuda", generator=gen).half()
+    need = sqp.workspace_bytes(M, N, K, g)
+    assert need > 0, "the case is meant to have K parts"
+    y_s, y_w = _both(L, sqp, M, K, N, g, dx, dp, dsc, dz)
+    assert np.array_equal(y_s.view(np.uint16), y_w.view(np.uint16)), "the static array gives other bits than the reported size"
+    st = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    ws = torch.empty(max(2 * need, (512 << 10) + (64 << 20)), dtype=torch.uint8, device="cuda")
+    y = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
+    assert L.sqp_set_workspace(_ptr(ws), ctypes.c_size_t(ws.numel()), st) == 0
+    try:
+        assert L.sqp_w4a16_gemm(M, N, K, g, _ptr(dx), _ptr(dp), _ptr(dsc), _ptr(dz), _ptr(y), st) == 0
+        torch.cuda.synchronize()
+    finally:
+        sqp.set_workspace(0)
+    assert np.array_equal(y.cpu().numpy().view(np.uint16), y_w.view(np.uint16)), "a larger workspace gives other bits"
+    w = sqp.dequantize(dp, dsc, dz, g).double()
+    xr = dx[:: max(1, M // 16)].double()
+    ref, size = xr @ w, xr.abs() @ w.abs()
+    err = (y[:: max(1, M // 16)].double() - ref).abs()
+    assert bool((err <= 1e-3 * size + 2.0 ** -10 * ref.abs() + 2.0 ** -24).all())
