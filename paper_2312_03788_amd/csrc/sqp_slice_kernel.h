@@ -32,8 +32,9 @@
 // rows: 1024->1024 6.3 / 6.5 / 6.6 -> 2.4 / 2.5 / 2.7, 4096->1024 7.2 / 7.3 / 7.4 -> 4.4 / 5.0 / 5.9,
 // 4096->4096 5.7 / 6.2 / 7.1 -> 4.8 / 5.3 / 6.1, 4096->12288 8.2 / 8.8 / 9.7 -> 7.5 / 8.1 / 9.1,
 // 4096->22016 13.4 / 14.1 / 15.8 -> 11.6 / 13.0 / 15.0, 12288->4096 at one row 10.6 -> 9.7; with each word unpacked in
-// front of the MFMAs of the one before 4096->12288 at one row 7.39 -> 7.23, 4096->22016 11.58 -> 11.37, 8192->44032 at four
-// 35.1 -> 34.3, 4096->4096 4.73 -> 4.71.
+// front of the MFMAs of the one before (up to 16 rows, groups of 64 and more) 4096->12288 at one row 7.31 -> 7.17 (weights
+// in the last-level cache: 6.28 -> 6.02), 4096->22016 10.63 -> 10.44 there, 8192->44032 at four rows 34.6 -> 33.8, 4096->4096
+// as before.
 // Three and four stages per wave are slower everywhere (again, also with loads masked instead of skipped
 // at the end).
 #pragma once
@@ -203,7 +204,6 @@ w4a16_decode_slice_kernel(int M, int N, int K, int cpg, int grouped, const h16 *
         }
     };
 
-    const UnpackConsts uc = unpack_consts();
     // LDS byte addresses of this lane's A fragments (row lc of the operand) in slot 0, per k-step and row tile
     // (operand rows past the fetched ones repeat fetched rows: defined data, unused results)
     uint32_t xrd[4][MT];
@@ -265,40 +265,52 @@ w4a16_decode_slice_kernel(int M, int N, int K, int cpg, int grouped, const h16 *
         // The accumulators are kept whole until a sum of theirs has been read (the asm statements behind the
         // FMAs): a register that nothing reads would otherwise be free for an instruction in assembly while
         // the MFMA still writes it, and the compiler adds no wait states for those.
-        // A word is unpacked in front of the matrix instructions of the word before it (the scheduler is kept to
+        // AHEAD: a word is unpacked in front of the matrix instructions of the word before it (the scheduler is kept to
         // that): right behind its own unpack, an MFMA waits, and where a sum moved to other registers
         // with each MFMA, what followed waited for the old ones (5 wait states per word, a third of the loop's time).
+        // Not in groups of 32, whose sums are scaled after every k-step, nor with two row tiles, where every word feeds two
+        // MFMAs anyway.  us, compiler's order / ahead: groups of 32 at one to four rows on 16385 to 32768 columns, where
+        // some compute units hold two workgroups, 1216->24576 6.1 / 7.5, 3008->17464 12.2 / 12.5; 17 to 32 rows 4096->8192 in
+        // groups of 64 7.51 / 7.67, 1536->38152 in groups of 256 18.5 / 19.1, 700 calls 0.6 % in the mean.
+        constexpr bool AHEAD = MT == 1 && GS > 1;
+        const UnpackConsts uc = unpack_consts();  // (here: held across the loop they cost the last of these shapes 3 %)
         const f32x4 none = {0.f, 0.f, 0.f, 0.f};
         auto unpacked = [&](int i) {
             const int ks = i / TB, b = i % TB;
             const uint32_t z = zero_of(s, ks / GS, b);
             return dequant_word(word_of(s, ks, b), neg_hi_of(z), neg_lo_of(z), uc);
         };
-        f32x4 g[MT][TB];
-        h16x8 a[MT], w = unpacked(0);
+        h16x8 next;
+        if constexpr (AHEAD) next = unpacked(0);
 #pragma unroll
-        for (int i = 0; i < 4 * TB; i++) {
-            const int ks = i / TB, b = i % TB;
-            if (b == 0) {
+        for (int q = 0; q < NQ; q++) {
+            f32x4 g[MT][TB];
+#pragma unroll
+            for (int ks = q * GS; ks < q * GS + GS; ks++) {
+                h16x8 a[MT];
 #pragma unroll
                 for (int mt = 0; mt < MT; mt++) a[mt] = permute_x(xa[ks][mt]);
-            }
-            const h16x8 cur = w;
-            if (i + 1 < 4 * TB) w = unpacked(i + 1);
-            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int mt = 0; mt < MT; mt++) g[mt][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[mt], cur, ks % GS == 0 ? none : g[mt][b], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            if (ks % GS == GS - 1 && b == TB - 1) {
-#pragma unroll
-                for (int c = 0; c < TB; c++) {
-                    const float d = step_of(s, ks / GS, c);
-#pragma unroll
-                    for (int mt = 0; mt < MT; mt++) {
-#pragma unroll
-                        for (int r = 0; r < RR; r++) acc[mt][c][r] = fmaf(d, g[mt][c][r * RS], acc[mt][c][r]);
-                        asm volatile("" : "+v"(acc[mt][c][0]) : "v"(g[mt][c]));
+                for (int b = 0; b < TB; b++) {
+                    const int i = ks * TB + b;
+                    const h16x8 w = AHEAD ? next : unpacked(i);
+                    if constexpr (AHEAD) {
+                        if (i + 1 < 4 * TB) next = unpacked(i + 1);
+                        __builtin_amdgcn_sched_barrier(0);
                     }
+#pragma unroll
+                    for (int mt = 0; mt < MT; mt++) g[mt][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[mt], w, ks == q * GS ? none : g[mt][b], 0, 0, 0);
+                    if constexpr (AHEAD) __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+#pragma unroll
+            for (int b = 0; b < TB; b++) {
+                const float d = step_of(s, q, b);
+#pragma unroll
+                for (int mt = 0; mt < MT; mt++) {
+#pragma unroll
+                    for (int r = 0; r < RR; r++) acc[mt][b][r] = fmaf(d, g[mt][b][r * RS], acc[mt][b][r]);
+                    asm volatile("" : "+v"(acc[mt][b][0]) : "v"(g[mt][b]));
                 }
             }
         }
