@@ -537,14 +537,23 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
         if constexpr (W * 32 * STRIDE * 4 <= sizeof(xring)) {
             float *ex = reinterpret_cast<float *>(xring) + e_wave * (32 * STRIDE);
             const int n0 = nbase + e_wave * WN, own = NT * e_l32, ecol = own + 2 >= N - n0 && own < N - n0 ? N - 3 - n0 : own;
+            // What a lane reads other lanes of its wave have written: the hardware keeps a wave's LDS accesses in order, and the
+            // fences tell the compiler to (they cost no instruction).
+            auto across_lanes = [&]() {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            };
             asm volatile("s_barrier" ::: "memory");  // (all loads into LDS have landed, all reads of it too)
 #pragma unroll
             for (int mt = 0; mt < RT; mt++) {
+                if (mt > 0) across_lanes();
                 ready(mt);
 #pragma unroll
                 for (int r = 0; r < 16; r++)
 #pragma unroll
                     for (int t = 0; t < NT; t++) ex[(8 * (r >> 2) + 4 * e_kb + (r & 3)) * STRIDE + ecol + t] = acc[mt][t][r];
+                across_lanes();
 #pragma unroll
                 for (int i = 0; i < 32 * WN / 8 / 64; i++) {
                     const int o = i * 64 + (tid & 63), row = o / (WN / 8), col = o % (WN / 8) * 8;
