@@ -74,21 +74,26 @@ def _check_scratch_after_last_barrier(src, asm_path, kernels):
 
 
 # The tiled kernel's MFMAs are asm statements too, so the compiler puts no wait states between one and a read of its
-# result; the kernel spends them (s_nop 15) wherever a run of stages ends.  No accumulator may be copied or stored
-# between an MFMA and the next such wait (the order of the lines is that of the control flow there: loop body, wait).
+# result; the kernel spends them (two s_nop 15: a result is there after up to 18) wherever a run of stages ends.  Between
+# an MFMA and the next such pair no other instruction may touch an accumulator register, to copy it or to store it to LDS or
+# memory (the order of the lines is that of the control flow there: loop body, wait).
 def _check_results_behind_wait(src, asm_path, want):
-    kernel, waiting = None, False
+    kernel, waiting, waits = None, False, 0
     for l in open(asm_path):
         m = re.match(r"(_Z\S+):", l)
         if m:
-            kernel, waiting = (m.group(1) if want in m.group(1) else None), False
-        elif kernel is None:
+            kernel, waiting, waits = (m.group(1) if want in m.group(1) else None), False, 0
             continue
-        elif "v_mfma" in l:
+        m = re.match(r"\s+([a-z]\w*)(.*)", l)
+        if kernel is None or not m:  # (labels, directives, comments)
+            continue
+        op, operands = m.group(1), m.group(2).split(";")[0]
+        waits = waits + 1 if op == "s_nop" and operands.strip() == "15" else 0
+        if op.startswith("v_mfma"):
             waiting = True
-        elif re.match(r"\s*s_nop 15\b", l):
+        elif waits == 2:
             waiting = False
-        elif waiting and re.match(r"\s*(v_accvgpr|(global|scratch)_store.*\ba)", l):
+        elif waiting and re.search(r"(?<![\w.])a(\d+\b|\[)", operands):
             raise RuntimeError("%s: kernel %s uses a matrix result too early: %s" % (src, kernel, l.strip()))
 
 
