@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import workloads as wl
-from gpu_util import dev, gemm_tolerance_ok, host
+from gpu_util import dev, gemm_tolerance_ok, host, silu_tolerance
 
 pytestmark = pytest.mark.gpu
 
@@ -247,6 +247,23 @@ def test_prefill_few_stages(orc, sqp, rt, nt, stages):
         L.sqp_debug_set_prefill_variant(0, 0, 0)
 
 
+@pytest.mark.parametrize("tiles", [1, 2])
+@pytest.mark.parametrize("stages", [1, 2, 3, 4, 5, 7])
+def test_prefill_few_stages_groups_of_32(orc, sqp, tiles, stages):
+    """The same in groups of 32, whose full and half-width tiles have two groups per stage."""
+    M, K, N = 2 * 128 - 5, 64 * stages, 520
+    print("case few stages, groups of 32", M, K, N, tiles, flush=True)
+    xs, p, sc, z = _layer(orc, M, K, N, 32)
+    L = sqp.lib()
+    L.sqp_debug_set_prefill_tiles(tiles)
+    L.sqp_debug_set_prefill_ksplit(0)
+    try:
+        _check(orc, sqp, xs, p, sc, z, 32)
+    finally:
+        L.sqp_debug_set_prefill_tiles(0)
+        L.sqp_debug_set_prefill_ksplit(-1)
+
+
 @pytest.mark.parametrize("rt", [4, 5])
 @pytest.mark.parametrize("M_off,K,N,group", [(0, 64, 8, 64), (-1, 448, 384, 64), (1, 320, 392, 320), (70, 1024, 760, 256), (-40, 640, 96, 128)])
 def test_prefill_three_columns_per_lane(orc, sqp, M_off, K, N, group, rt):
@@ -276,23 +293,40 @@ def test_prefill_three_columns_per_lane(orc, sqp, M_off, K, N, group, rt):
 @pytest.mark.parametrize("rt", [3, 4, 5, 6])
 @pytest.mark.parametrize("M_off,K,N,group,parts", [
     (0, 128, 8, 64, 1), (-1, 256, 136, 128, 1), (1, 384, 120, 192, 1), (33, 640, 264, 64, 1), (-17, 1024, 392, 512, 4), (5, 1920, 248, 320, 3),
-    (64, 1792, 128, 256, 2)])
+    (64, 1792, 128, 256, 2), (-1, 256, 144, 128, 1), (5, 1920, 240, 640, 3)])
 def test_prefill_waves_halve_k(orc, sqp, M_off, K, N, group, parts, rt):
     """Tiles of 128 columns whose waves halve every stage of 128 k between them: one row or column past a tile and
     short of it, one to fifteen stages, groups that end in the middle of a stage or span several, with and without K
-    parts; plain and with the fused activation; repeated runs are bit-identical, and equal to whole-K tiles within
-    the fp32 accumulation."""
+    parts; plain and with the fused activation (N a multiple of 16); repeated runs are bit-identical, and equal to whole-K
+    tiles within the fp32 accumulation."""
     M = max(1, 64 * rt + M_off)
     print("case halved k", M, K, N, group, rt, parts, flush=True)
     xs, p, sc, z = _layer(orc, M, K, N, group)
+    xs = xs * np.float16(0.25)                             # (the fused products stay below fp16's largest value)
+    d = (dev(xs), dev(p), dev(sc), dev(z), group)
+    fused = N % 16 == 0
     L = sqp.lib()
     L.sqp_debug_set_prefill_variant(rt, 2 + 16, parts)
     try:
         y0 = _check(orc, sqp, xs, p, sc, z, group)
         y1 = _check(orc, sqp, xs, p, sc, z, group)
+        h = host(sqp.w4a16_gemm_silu_mul(*d)).astype(np.float64) if fused else None
     finally:
         L.sqp_debug_set_prefill_variant(0, 0, 0)
     assert np.array_equal(y0.view(np.uint16), y1.view(np.uint16))
+    L.sqp_debug_set_prefill_variant(rt, 2, parts)
+    try:
+        whole = host(sqp.w4a16_gemm(*d)).astype(np.float64)
+    finally:
+        L.sqp_debug_set_prefill_variant(0, 0, 0)
+    y_ref, t_ref = orc.w4a16_gemm_ref(xs, p, sc, z, group)
+    # The same products in two orders: each sum is within K roundings of 2^-23 (cut off, not rounded) of its terms' sizes,
+    # and rounded once to fp16.
+    assert np.all(np.abs(y0.astype(np.float64) - whole) <= 2 * K * 2.0 ** -23 * t_ref + orc.ulp16(y_ref))
+    if fused:
+        h_ref, tol = silu_tolerance(orc, y_ref, t_ref)
+        assert h.shape == (M, N // 2) and np.abs(h_ref).max() < 60000
+        assert np.all(np.abs(h - h_ref) <= tol), "worst err/tol %.3f" % float((np.abs(h - h_ref) / tol).max())
 
 
 def test_prefill_left_over_k_parts(orc, sqp):

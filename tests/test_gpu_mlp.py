@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import workloads as wl
-from gpu_util import dev, host
+from gpu_util import dev, host, silu_tolerance
 
 pytestmark = pytest.mark.gpu
 
@@ -57,16 +57,6 @@ def test_fold_helpers_bit_exact(orc, sqp):
     assert np.array_equal(g2.view(np.uint16), orc.smooth_apply_x(gamma.reshape(1, K), s1).view(np.uint16))
 
 
-def _silu_tolerance(orc, y_ref, t_ref):
-    """Bound on |h_gpu - h_ref| for h = SiLU(g) u from the GEMM bound |dg| <= 1e-3 t_g,
-    |du| <= 1e-3 t_u on the fp32 sums: |dh| <= |SiLU'(g)| |u| |dg| + |SiLU(g)| |du| + |dg||du|,
-    |SiLU'| <= 1.1; plus the hardware exponential (1e-6 relative) and the final fp16 rounding."""
-    g, u = y_ref[:, 0::2], y_ref[:, 1::2]
-    dg, du = 1e-3 * t_ref[:, 0::2], 1e-3 * t_ref[:, 1::2]
-    h = orc.silu_mul_ref(g, u)
-    return h, 1.1 * np.abs(u) * dg + np.abs(orc.silu_ref(g)) * du + 1.1 * dg * du + 1e-6 * np.abs(h) + orc.ulp16(h)
-
-
 @pytest.mark.parametrize("M,K,N,group,ksplit", [
     (4, 1024, 1024, 128, -1), (16, 512, 272, 64, -1), (40, 384, 528, 128, -1), (7, 256, 64, 32, -1),
     (130, 1024, 528, 128, -1), (300, 512, 1008, 64, 0), (300, 1024, 528, 128, 3), (100, 128, 64, 32, -1),
@@ -82,7 +72,7 @@ def test_gemm_silu_mul(orc, sqp, M, K, N, group, ksplit):
     xs = orc.smooth_apply_x(x * np.float16(0.25), s)       # keep SiLU's argument in its curved range
     p, sc, z = orc.quantize_pack(orc.smooth_apply_w((w.astype(np.float32) * 8).astype(np.float16), s), group)
     y_ref, t_ref = orc.w4a16_gemm_ref(xs, p, sc, z, group)
-    h_ref, tol = _silu_tolerance(orc, y_ref, t_ref)
+    h_ref, tol = silu_tolerance(orc, y_ref, t_ref)
     L = sqp.lib()
     L.sqp_debug_set_prefill_ksplit(ksplit)
     try:
@@ -109,7 +99,7 @@ def test_gemm_silu_mul_slice_kernel(orc, sqp, M, K, N, mode):
     xs = orc.smooth_apply_x(x * np.float16(0.25), s)
     p, sc, z = orc.quantize_pack(orc.smooth_apply_w((w.astype(np.float32) * 8).astype(np.float16), s), group)
     y_ref, t_ref = orc.w4a16_gemm_ref(xs, p, sc, z, group)
-    h_ref, tol = _silu_tolerance(orc, y_ref, t_ref)
+    h_ref, tol = silu_tolerance(orc, y_ref, t_ref)
     L = sqp.lib()
     L.sqp_debug_set_decode_slice(mode)
     try:
@@ -161,7 +151,7 @@ def test_mlp_block_end_to_end(orc, sqp):
     n_d = host(sqp.rmsnorm(d(x), gamma_d, eps)).astype(np.float64)
     n_ref = orc.rmsnorm_ref(x, gamma_f, eps)
     assert np.all(np.abs(n_d - n_ref) <= orc.ulp16(n_ref))
-    h_ref, tol_h = _silu_tolerance(orc, y1, orc.w4a16_gemm_ref(n_o, *q1, g)[1])
+    h_ref, tol_h = silu_tolerance(orc, y1, orc.w4a16_gemm_ref(n_o, *q1, g)[1])
     h_on_oracle_n = host(sqp.w4a16_gemm_silu_mul(d(n_o), *q1d, g)).astype(np.float64)
     assert np.all(np.abs(h_on_oracle_n - h_ref) <= tol_h)
     y_on_oracle_h = host(sqp.w4a16_gemm(d(h_o), *q2d, g)).astype(np.float64)
