@@ -253,10 +253,11 @@ def test_prefill_launches_invariants(L):
 
 
 def test_prefill_choice_stays_in_its_room(L):
-    """What a call launches in the place of the reported plan: every tile once, at most one workgroup per compute unit
-    (two of the variants with half the registers), at least eight stages of 64 k per part, parts within the
-    room given, waves that halve K only where K is whole stages of 128 and groups are not of 32."""
-    out, seen = (ctypes.c_int * 10)(), set()
+    """What a call launches with some room for its K parts: every tile once, one launch of 256 or 384 columns at most one
+    workgroup per compute unit (two of the variants with half the registers), left-over tiles in K parts at most one, at
+    least eight stages of 64 k per part, parts within the room given, waves that halve K only where K is whole
+    stages of 128 and groups are not of 32."""
+    out, seen, drawn = (ctypes.c_int * 10)(), set(), [0, 0, 0]
     L.sqp_debug_prefill_choice.argtypes = [ctypes.c_int] * 5 + [ctypes.c_size_t, ctypes.POINTER(ctypes.c_int)]
     rng = random.Random(19)
     for _ in range(4000):
@@ -272,12 +273,19 @@ def test_prefill_choice_stays_in_its_room(L):
             assert kh == 1 or (kh == 2 and nt == 2 and K % 128 == 0 and group % 64 == 0)
             assert nt != 3 or (rt in (4, 5) and n == 1 and tiles <= 256 and group != 32)
             assert parts == 1 or (nt == 2 and K // 64 >= 8 * parts and parts * tiles * 32 * rt * (256 // kh) * 4 <= room)
-            if n == 1:
-                assert tiles >= -(-N // (128 * nt // kh)) * -(-M // (32 * rt))
-            if parts > 1 or kh == 2:
-                assert tiles * parts <= (512 if nt == 2 and kh == 1 and rt <= 4 else 256)
+            if nt < 4 and (n == 1 or parts > 1):
+                assert tiles * parts <= (512 if n == 1 and group != 32 and nt == 2 and kh == 1 and rt <= 4 else 256)
+        whole = -(-N // 512) * -(-M // 128)   # tiles of 128 x 512: left and right half of each where they are halved
+        if n == 1:
+            rt, nt, tiles, parts, kh = out[:5]
+            assert tiles == -(-N // (128 * nt // kh)) * -(-M // (32 * rt)) or ((rt, nt, kh) == (4, 2, 1) and tiles == 2 * whole)
+        elif n == 2:
+            assert tuple(out[:2]) == (4, 4) and tuple(out[3:5]) == (1, 1) and tuple(out[5:7]) == (4, 2) and out[9] == 1
+            assert out[2] % 256 == 0 and 2 * out[2] + out[7] == 2 * whole
+        drawn[n] += 1
     assert {(rt, 2, kh, False) for rt in (3, 4, 5, 6) for kh in (1, 2)} <= seen
     assert {(3, 2, 1, True), (4, 3, 1, False), (5, 3, 1, False)} <= seen
+    assert drawn[1] > 1000 and drawn[2] > 50, drawn
 
 
 def test_every_sufficient_buffer_gives_the_same_launches(L):
