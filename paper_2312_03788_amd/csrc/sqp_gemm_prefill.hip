@@ -43,20 +43,6 @@ namespace {
 
 constexpr int BK = 64;
 
-// The vector instructions of one k-step in issue order, in groups of four: the four steps of the unpack of each of
-// the NT words of the next k-step.
-enum { G_PERM = 0, G_AND = 4, G_ADD = 8, G_MUL = 12 };
-template <int NT>
-struct Order {
-    static constexpr int NG = 4 * NT;
-    int g[NG];
-    constexpr Order() : g()
-    {
-        for (int i = 0; i < 4; i++)
-            for (int t = 0; t < NT; t++) g[i * NT + t] = 4 * i + t;
-    }
-};
-
 // Which tile a workgroup takes.  The tiles are numbered in groups of up to gm rows of tiles, row index fastest
 // within a column, so that consecutive numbers are compact blocks; workgroups are dealt to the eight XCDs in turn, so
 // each XCD gets one run of consecutive numbers.  The workgroups that an XCD has resident then share its L2: of a stage's 16 KB of activations and 16 KB of weights per 128 x 512 tile
@@ -341,21 +327,21 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
         const u32x4 b4 = {bv[0], bv[1], bv[2], bv[3]};
         asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+a"(c) : "v"(a4), "v"(b4));
     };
-    constexpr Order<NT> order{};
-    constexpr int NG = Order<NT>::NG;
     constexpr int NMF = RT * NT;                        // MFMAs per k-step
+    constexpr int NV = 16 * NT;                         // vector instructions per k-step
     uint32_t high_bytes = PAIR_HIGH_BYTES;
     asm volatile("" : "+v"(high_bytes));
 
-    // one entry j of group g; wn = the packed words of the next k-step, kn = that k-step's
-    // position in its stage (it selects the quantisation group's constants)
-    auto valu = [&](int g, int j, int cur, const wvec &wn, int kn) {
-        const int t = g & 3;
+    // Vector instruction e of a k-step in issue order: the four steps of the unpack one after the other, each over the NT words of
+    // the next k-step, four instructions a word; wn = those words, kn = that k-step's position in its stage (it
+    // selects the quantisation group's constants)
+    auto valu = [&](int e, int cur, const wvec &wn, int kn) {
+        const int step = e / (4 * NT), t = e / 4 % NT, j = e % 4;
         uint32_t &b = bq[cur ^ 1][t][j];
         const int qs = G32 ? (kn >> 1) : 0;
-        if (g < G_AND) asm volatile("v_perm_b32 %0, %1, %2, %3" : "=v"(b) : "v"(high_bytes), "v"(wn[t]), "s"(PAIR_SELECT + 0x00010001u * j));
-        else if (g < G_ADD) asm volatile("v_and_b32 %0, %1, %0" : "+v"(b) : "s"(PAIR_MASK));
-        else if (g < G_MUL) asm volatile("v_pk_add_f16 %0, %0, %1" : "+v"(b) : "v"(neg[qs][t]));
+        if (step == 0) asm volatile("v_perm_b32 %0, %1, %2, %3" : "=v"(b) : "v"(high_bytes), "v"(wn[t]), "s"(PAIR_SELECT + 0x00010001u * j));
+        else if (step == 1) asm volatile("v_and_b32 %0, %1, %0" : "+v"(b) : "s"(PAIR_MASK));
+        else if (step == 2) asm volatile("v_pk_add_f16 %0, %0, %1" : "+v"(b) : "v"(neg[qs][t]));
         else asm volatile("v_pk_mul_f16 %0, %0, %1" : "+v"(b) : "v"(delta[qs][t]));
     };
 
@@ -409,8 +395,7 @@ w4a16_prefill_kernel(int M, int N, int K, int group, TileMap map, const h16 *__r
                     else read_a(xa[nxt], slot_next, 0, i);
                 }
 #pragma unroll
-                for (int e = i * (4 * NG) / NMF; e < (i + 1) * (4 * NG) / NMF; e++)
-                    valu(order.g[e / 4], e % 4, cur, wn, (ks + 1) & 3);
+                for (int e = i * NV / NMF; e < (i + 1) * NV / NMF; e++) valu(e, cur, wn, (ks + 1) & 3);
                 if (i >= RT) {
 #pragma unroll
                     for (int l = (i - RT) * (x1 - x0 + w1 - w0) / (NMF - RT); l < (i - RT + 1) * (x1 - x0 + w1 - w0) / (NMF - RT); l++) {
@@ -903,9 +888,10 @@ static double launch_us(const TileLaunch &l, int M, int N, int K, int cus)
 // the K parts (or none) for as many workgroups, at the price of twice the activations per compute unit; tiles of 96 and
 // 128 rows x 256 columns leave half of the registers, so that two workgroups per compute unit hide each other's
 // waits; 128 or 160 rows x 384 columns fill one round where 128 x 512 leave a third of the chip idle or spill over.  The sizes reported to callers are those of the plan itself: what they have stored goes on to hold.
-// us, plan -> quicker one when it was built: 160x8192x8192 36.3 -> 34.4, 160x4096x22016 44.5 -> 39.8, 300x5120x15360 59.6 ->
-// 55.5, 490x2816x5840 32.5 -> 25.9, 999x2176x3832 32.8 -> 24.3, 403x3072x22792 72.2 -> 68.7, 512x4096x22016 88.0 -> 82.5, 772x3456x18968 111 -> 93; over the fitted shapes the pick is 0.5 %
-// behind the best in the mean.
+// us per call, weights from HBM, the same kernels with the plan -> with the quicker one: 160x8192x8192 36.9 -> 34.4,
+// 160x4096x22016 42.6 -> 39.1, 300x5120x15360 57.9 -> 52.2, 490x2816x5840 29.2 -> 23.2, 999x2176x3832 26.6 -> 22.2,
+// 403x3072x22792 73.7 -> 65.7, 512x4096x22016 91.0 -> 83.3, 772x3456x18968 113.0 -> 90.5; over the fitted shapes the pick is
+// 0.5 % behind the best in the mean.
 static double quicker_launch(LaunchPlan &q, int M, int N, int K, int group, int cus, size_t room)
 {
     const bool hooked = g_tile_mode != 0 || g_tile_shape != 0 || g_ksplit >= 0 || g_force_rt > 0;
