@@ -548,7 +548,7 @@ loss_pair_kernel(int M, int N, int K, int group, const h16 *__restrict__ x, cons
     const long nrow = (long)N * 2;            // one row of W in bytes
     // Streams are buffer loads with a 32-bit scalar offset each: scalar instructions cost a wave as much as vector ones, and
     // 64-bit pointers made 171 per two stages, these 107 (search of 64 x 4096 x 4096 in groups of 32, 21 alphas: 424 -> 409 us;
-    // 512 x 5120 x 5120: 1529 -> 1522).  Past the last stage the offsets stop and the look-ahead re-reads it.
+    // 512 x 5120 x 5120: no more than its runs differ).  Past the last stage the offsets stop and the look-ahead re-reads it.
     // (W straight to registers, each row fetched by twice the waves, and a third slot in its room: 1578 -> 1631 us.)
     const uint32_t bytes_x = (uint32_t)M * (uint32_t)K * 2u, bytes_p = (uint32_t)(K / 8) * (uint32_t)N * 4u, rows_q = (uint32_t)(K / group) * (uint32_t)N;
     const rsrc_t buf_w = buffer_of(w, (uint32_t)K * (uint32_t)N * 2u), buf_p[2] = {buffer_of(sets.packed<false>(sa), bytes_p), buffer_of(sets.packed<false>(sb), bytes_p)};
