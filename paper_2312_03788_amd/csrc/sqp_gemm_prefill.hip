@@ -864,7 +864,11 @@ static size_t plan_partial_bytes(const LaunchPlan &q)
 // a + stages * (b + l * workgroups / compute units) + (h + p * MB), the last two with K parts (MB: their fp32 sums
 // written and read); a stage is 64 k, 128 with waves that halve K.  Up to one workgroup per compute unit, or two of the
 // variants that leave half the registers.  Fitted to 9085 launches of 294 shapes (65 to 1536 rows, N 1024 to 24576,
-// K 1024 to 16384, groups of 128): rms 2.7 to 5.0 % by variant.  0: not covered.
+// K 1024 to 16384, groups of 128): rms 2.7 to 5.0 % by variant.  Beyond four parts each costs 0.2 us at least, however few
+// its bytes: the reduction waits for one after the other (5004 launches of 527 other shapes, most of them of few tiles:
+// without it 4.7 to 8.7 %, waves that halve K and 9 to 12 parts of less than 0.2 MB 13 % too low).  It keeps calls of few columns
+// and a long K with the row blocks: 308x9088x136 in groups of 64 12.5 us, 14.8 in tiles of 12 parts; 219 of 6771 drawn calls,
+// 1.10 times faster in the mean.  0: not covered.
 static double launch_us(const TileLaunch &l, int M, int N, int K, int cus)
 {
     struct Cost { double a, b, l, h, p; };
@@ -876,7 +880,9 @@ static double launch_us(const TileLaunch &l, int M, int N, int K, int cus)
     if (groups > 2L * cus || (groups > cus && (l.nt != 2 || l.kh == 2 || l.rt > 4))) return 0;
     const Cost &c = l.nt == 4 ? wide : l.nt == 3 ? three[l.rt - 4] : l.kh == 2 ? halves[l.rt - 3] : groups > cus ? two[l.rt - 3] : one[l.rt - 3];
     const int stages = (K / (BK * l.kh) + l.parts - 1) / l.parts;
-    const double t = c.a + stages * (c.b + c.l * (double)groups / cus) + (l.parts > 1 ? c.h + c.p * l.parts * ((double)M * N * 8e-6) : 0.0);
+    const double part_us = c.p * ((double)M * N * 8e-6), more_us = part_us < 0.2 ? 0.2 : part_us;
+    const double parts_us = l.parts > 4 ? 4 * part_us + (l.parts - 4) * more_us : l.parts * part_us;
+    const double t = c.a + stages * (c.b + c.l * (double)groups / cus) + (l.parts > 1 ? c.h + parts_us : 0.0);
     // (activations that two L2s would not hold, read by twice as many columns of tiles: measured 10 to 18 % longer, 5 % with
     // whole-K waves)
     return l.kh == 2 && l.parts > 1 && 2.0 * M * K > 8e6 ? 1.12 * t : t;

@@ -288,6 +288,16 @@ def test_prefill_choice_stays_in_its_room(L):
     assert drawn[1] > 1000 and drawn[2] > 50, drawn
 
 
+@pytest.mark.parametrize("M,K,N,group", [(308, 9088, 136, 64), (95, 11520, 152, 64), (113, 6784, 376, 64), (79, 10496, 584, 64),
+                                         (188, 6144, 104, 128), (82, 10496, 96, 128), (200, 8320, 224, 64)])
+def test_few_columns_and_long_k_stay_with_the_row_blocks(L, M, K, N, group):
+    """Tiles in 9 to 12 K parts of a few hundred KB, whose reduction waits for one part after the other, took 13 to 18 %
+    longer than the strip kernel's row blocks on these."""
+    rows = (ctypes.c_int * 3)()
+    L.sqp_debug_row_blocks(M, N, K, group, 256, 1, rows)
+    assert rows[0] in (3, 4) and rows[1] > 4
+
+
 def test_every_sufficient_buffer_gives_the_same_launches(L):
     """A buffer larger than the size reported for a shape (the static array, a workspace that has grown for other shapes)
     changes nothing: neither the tiled launches nor the row blocks.  Drawn shapes, and some on which an estimate with more
